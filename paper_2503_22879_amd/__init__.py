@@ -1,6 +1,6 @@
 """MI355X-native 8-bit Mamba2 selective scan (the SSD hot path of Quamba2, arXiv 2503.22879).
 
-A thin ctypes binding over libquamba_ssd.so (C ABI in include/quamba_ssd.h).  Every step of the path runs in the
+A thin binding over libquamba_ssd.so (C ABI in include/quamba_ssd.h).  Every step of the path runs in the
 library's HIP kernels; this package only marshals arguments.  There is no CPU fallback: calls raise if the
 library has not been built.
 """

@@ -1,4 +1,7 @@
-"""ctypes binding of include/quamba_ssd.h: same names, argument marshalling only."""
+"""Binding of include/quamba_ssd.h: same names, argument marshalling only.
+
+The host functions go through ctypes.  The device entry points, which a program calls for every layer and token, are
+marshalled by the native extension module _bind (csrc/bind.cpp), which calls the library that ctypes has loaded."""
 from __future__ import annotations
 
 import ctypes as C
@@ -9,7 +12,9 @@ import numpy as np
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.environ.get("QUAMBA_SSD_LIBRARY", os.path.join(_PKG, "libquamba_ssd.so"))
+_BIND_PATH = os.path.join(_PKG, "_bind.so")
 _lib = None
+_bind = None  # the extension module, once loaded
 
 FLAG_GENERIC_KERNEL = 0x1
 FLAG_PRECISE_STATE = 0x2
@@ -63,12 +68,6 @@ class Gate:
     dt_q: object = None
     dt_scale: float = 0.0
     dt_bias: object = None
-
-    def struct(self, z_shape, dt_shape, nheads) -> _GateStruct:
-        import torch
-        return _GateStruct(_dp(self.z, torch.int8, z_shape, "gate.z"), float(self.z_scale),
-                           _dp(self.dt_q, torch.int8, dt_shape, "gate.dt_q"), float(self.dt_scale),
-                           _dp(self.dt_bias, torch.float32, (nheads,), "gate.dt_bias"))
 
 
 def library_path() -> str:
@@ -145,6 +144,24 @@ def load_library():
     return _lib
 
 
+def _load_bind():
+    """Load the extension module that marshals the device entry points, bound to the loaded library; raises if it has
+    not been built."""
+    global _bind
+    lib = load_library()
+    if not os.path.exists(_BIND_PATH):
+        raise FileNotFoundError(f"{_BIND_PATH} is missing: build it with `python -m paper_2503_22879_amd.build` "
+                                "(or __graft_entry__.build())")
+    from . import _bind as mod
+    # the order of Entry in csrc/bind.cpp
+    mod.bind(*(C.cast(f, C.c_void_p).value for f in (
+        lib.quamba_ssd_prefill_gated, lib.quamba_ssd_prefill_noalloc, lib.quamba_ssd_decode_step_gated,
+        lib.quamba_ssd_decode_step_q8_gated, lib.quamba_ssd_quantize_state, lib.quamba_hadamard_quantize,
+        lib.quamba_mamba1_scan_gated, lib.quamba_mamba1_decode_step_gated, lib.quamba_conv1d_q8)))
+    _bind = mod
+    return mod
+
+
 def quamba_strerror(status: int) -> str:
     return load_library().quamba_strerror(int(status)).decode()
 
@@ -205,151 +222,40 @@ def quamba_ssd_prefill(shape: Shape, scales, x, B, Cm, dt, A, D, init_state, y, 
                        workspace=None, stream=None, gate: Gate | None = None) -> None:
     """Enqueue the chunked prefill on `stream` (default: torch's current stream).  Tensors are torch device tensors.
     With `gate`, quamba_ssd_prefill_gated is called (dt may then be None if the gate carries the step-size codes)."""
-    import torch
-    s = shape
-    sc = scales.struct()
-    if gate is not None:
-        return _prefill_gated(s, sc, gate, x, B, Cm, dt, A, D, init_state, y, final_state, workspace, stream)
-    ws_ptr = _dp(workspace, name="workspace")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st_shape = (s.batch, s.nheads, s.headdim, s.d_state)
-    rc = load_library().quamba_ssd_prefill(
-        C.byref(s), C.byref(sc),
-        _dp(x, torch.int8, (s.batch, s.seqlen, s.nheads, s.headdim), "x"),
-        _dp(B, torch.int8, (s.batch, s.seqlen, s.ngroups, s.d_state), "B"),
-        _dp(Cm, torch.int8, (s.batch, s.seqlen, s.ngroups, s.d_state), "C"),
-        _dp(dt, torch.float32, (s.batch, s.seqlen, s.nheads), "dt"),
-        _dp(A, torch.float32, (s.nheads,), "A"), _dp(D, torch.float32, (s.nheads,), "D"),
-        _dp(init_state, torch.float32, st_shape, "init_state"),
-        _dp(y, torch.float16, (s.batch, s.seqlen, s.nheads, s.headdim), "y"),
-        _dp(final_state, torch.float32, st_shape, "final_state"),
-        ws_ptr, ws_bytes, _stream_ptr(stream))
+    rc = (_bind or _load_bind()).prefill(shape, scales, x, B, Cm, dt, A, D, init_state, y, final_state, workspace, stream,
+                                         gate)
     if rc != 0:
-        raise QuambaError(rc, "quamba_ssd_prefill")
+        raise QuambaError(rc, "quamba_ssd_prefill" if gate is None else "quamba_ssd_prefill_gated")
 
 
 def quamba_ssd_prefill_noalloc(shape: Shape, scales, x, B, Cm, dt, A, D, init_state, y, final_state=None,
                                stream=None) -> None:
     """Enqueue the chunked prefill with the library's own fixed scratch area instead of a caller's workspace."""
-    import torch
-    s = shape
-    sc = scales.struct()
-    st_shape = (s.batch, s.nheads, s.headdim, s.d_state)
-    rc = load_library().quamba_ssd_prefill_noalloc(
-        C.byref(s), C.byref(sc),
-        _dp(x, torch.int8, (s.batch, s.seqlen, s.nheads, s.headdim), "x"),
-        _dp(B, torch.int8, (s.batch, s.seqlen, s.ngroups, s.d_state), "B"),
-        _dp(Cm, torch.int8, (s.batch, s.seqlen, s.ngroups, s.d_state), "C"),
-        _dp(dt, torch.float32, (s.batch, s.seqlen, s.nheads), "dt"),
-        _dp(A, torch.float32, (s.nheads,), "A"), _dp(D, torch.float32, (s.nheads,), "D"),
-        _dp(init_state, torch.float32, st_shape, "init_state"),
-        _dp(y, torch.float16, (s.batch, s.seqlen, s.nheads, s.headdim), "y"),
-        _dp(final_state, torch.float32, st_shape, "final_state"), _stream_ptr(stream))
+    rc = (_bind or _load_bind()).prefill_noalloc(shape, scales, x, B, Cm, dt, A, D, init_state, y, final_state, stream)
     if rc != 0:
         raise QuambaError(rc, "quamba_ssd_prefill_noalloc")
-
-
-def _prefill_gated(s, sc, gate, x, B, Cm, dt, A, D, init_state, y, final_state, workspace, stream) -> None:
-    import torch
-    ws_ptr = _dp(workspace, name="workspace")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st_shape = (s.batch, s.nheads, s.headdim, s.d_state)
-    g = gate.struct((s.batch, s.seqlen, s.nheads, s.headdim), (s.batch, s.seqlen, s.nheads), s.nheads)
-    rc = load_library().quamba_ssd_prefill_gated(
-        C.byref(s), C.byref(sc), C.byref(g),
-        _dp(x, torch.int8, (s.batch, s.seqlen, s.nheads, s.headdim), "x"),
-        _dp(B, torch.int8, (s.batch, s.seqlen, s.ngroups, s.d_state), "B"),
-        _dp(Cm, torch.int8, (s.batch, s.seqlen, s.ngroups, s.d_state), "C"),
-        _dp(dt, torch.float32, (s.batch, s.seqlen, s.nheads), "dt"),
-        _dp(A, torch.float32, (s.nheads,), "A"), _dp(D, torch.float32, (s.nheads,), "D"),
-        _dp(init_state, torch.float32, st_shape, "init_state"),
-        _dp(y, torch.float16, (s.batch, s.seqlen, s.nheads, s.headdim), "y"),
-        _dp(final_state, torch.float32, st_shape, "final_state"),
-        ws_ptr, ws_bytes, _stream_ptr(stream))
-    if rc != 0:
-        raise QuambaError(rc, "quamba_ssd_prefill_gated")
 
 
 def quamba_ssd_decode_step(shape: Shape, scales, x, B, Cm, dt, A, D, state, y, stream=None,
                            gate: Gate | None = None) -> None:
     """Enqueue one decode step; `state` is updated in place.  With `gate`, quamba_ssd_decode_step_gated is called."""
-    import torch
-    s = shape
-    sc = scales.struct()
-    if gate is not None:
-        g = gate.struct((s.batch, s.nheads, s.headdim), (s.batch, s.nheads), s.nheads)
-        rc = load_library().quamba_ssd_decode_step_gated(
-            C.byref(s), C.byref(sc), C.byref(g),
-            _dp(x, torch.int8, (s.batch, s.nheads, s.headdim), "x"),
-            _dp(B, torch.int8, (s.batch, s.ngroups, s.d_state), "B"),
-            _dp(Cm, torch.int8, (s.batch, s.ngroups, s.d_state), "C"),
-            _dp(dt, torch.float32, (s.batch, s.nheads), "dt"),
-            _dp(A, torch.float32, (s.nheads,), "A"), _dp(D, torch.float32, (s.nheads,), "D"),
-            _dp(state, torch.float32, (s.batch, s.nheads, s.headdim, s.d_state), "state"),
-            _dp(y, torch.float16, (s.batch, s.nheads, s.headdim), "y"), _stream_ptr(stream))
-        if rc != 0:
-            raise QuambaError(rc, "quamba_ssd_decode_step_gated")
-        return
-    rc = load_library().quamba_ssd_decode_step(
-        C.byref(s), C.byref(sc),
-        _dp(x, torch.int8, (s.batch, s.nheads, s.headdim), "x"),
-        _dp(B, torch.int8, (s.batch, s.ngroups, s.d_state), "B"),
-        _dp(Cm, torch.int8, (s.batch, s.ngroups, s.d_state), "C"),
-        _dp(dt, torch.float32, (s.batch, s.nheads), "dt"),
-        _dp(A, torch.float32, (s.nheads,), "A"), _dp(D, torch.float32, (s.nheads,), "D"),
-        _dp(state, torch.float32, (s.batch, s.nheads, s.headdim, s.d_state), "state"),
-        _dp(y, torch.float16, (s.batch, s.nheads, s.headdim), "y"), _stream_ptr(stream))
+    rc = (_bind or _load_bind()).decode(shape, scales, x, B, Cm, dt, A, D, state, y, stream, gate)
     if rc != 0:
-        raise QuambaError(rc, "quamba_ssd_decode_step")
+        raise QuambaError(rc, "quamba_ssd_decode_step" if gate is None else "quamba_ssd_decode_step_gated")
 
 
 def quamba_ssd_decode_step_q8(shape: Shape, scales, state_scales, x, B, Cm, dt, A, D, state_q, y, stream=None,
                               gate: Gate | None = None) -> None:
     """Enqueue one decode step on the 8-bit cached state; `state_q` (int8) is updated in place.  With `gate` (z only),
     quamba_ssd_decode_step_q8_gated is called."""
-    import torch
-    s = shape
-    sc = scales.struct()
-    ncell = s.ngroups * s.n_head_clusters * s.n_chan_clusters
-    if gate is not None:
-        g = gate.struct((s.batch, s.nheads, s.headdim), (s.batch, s.nheads), s.nheads)
-        rc = load_library().quamba_ssd_decode_step_q8_gated(
-            C.byref(s), C.byref(sc), C.byref(g),
-            _dp(state_scales, torch.float32, (ncell, s.d_state), "state_scales"),
-            _dp(x, torch.int8, (s.batch, s.nheads, s.headdim), "x"),
-            _dp(B, torch.int8, (s.batch, s.ngroups, s.d_state), "B"),
-            _dp(Cm, torch.int8, (s.batch, s.ngroups, s.d_state), "C"),
-            _dp(dt, torch.float32, (s.batch, s.nheads), "dt"),
-            _dp(A, torch.float32, (s.nheads,), "A"), _dp(D, torch.float32, (s.nheads,), "D"),
-            _dp(state_q, torch.int8, (s.batch, s.nheads, s.headdim, s.d_state), "state_q"),
-            _dp(y, torch.float16, (s.batch, s.nheads, s.headdim), "y"), _stream_ptr(stream))
-        if rc != 0:
-            raise QuambaError(rc, "quamba_ssd_decode_step_q8_gated")
-        return
-    rc = load_library().quamba_ssd_decode_step_q8(
-        C.byref(s), C.byref(sc), _dp(state_scales, torch.float32, (ncell, s.d_state), "state_scales"),
-        _dp(x, torch.int8, (s.batch, s.nheads, s.headdim), "x"),
-        _dp(B, torch.int8, (s.batch, s.ngroups, s.d_state), "B"),
-        _dp(Cm, torch.int8, (s.batch, s.ngroups, s.d_state), "C"),
-        _dp(dt, torch.float32, (s.batch, s.nheads), "dt"),
-        _dp(A, torch.float32, (s.nheads,), "A"), _dp(D, torch.float32, (s.nheads,), "D"),
-        _dp(state_q, torch.int8, (s.batch, s.nheads, s.headdim, s.d_state), "state_q"),
-        _dp(y, torch.float16, (s.batch, s.nheads, s.headdim), "y"), _stream_ptr(stream))
+    rc = (_bind or _load_bind()).decode_q8(shape, scales, state_scales, x, B, Cm, dt, A, D, state_q, y, stream, gate)
     if rc != 0:
-        raise QuambaError(rc, "quamba_ssd_decode_step_q8")
+        raise QuambaError(rc, "quamba_ssd_decode_step_q8" if gate is None else "quamba_ssd_decode_step_q8_gated")
 
 
 def quamba_ssd_quantize_state(shape: Shape, scales, state_scales, state, state_q, stream=None) -> None:
     """Enqueue Eq. 1 on an fp32 device state with the scales of the 8-bit cache."""
-    import torch
-    s = shape
-    sc = scales.struct()
-    ncell = s.ngroups * s.n_head_clusters * s.n_chan_clusters
-    st_shape = (s.batch, s.nheads, s.headdim, s.d_state)
-    rc = load_library().quamba_ssd_quantize_state(
-        C.byref(s), C.byref(sc), _dp(state_scales, torch.float32, (ncell, s.d_state), "state_scales"),
-        _dp(state, torch.float32, st_shape, "state"), _dp(state_q, torch.int8, st_shape, "state_q"),
-        _stream_ptr(stream))
+    rc = (_bind or _load_bind()).quantize_state(shape, scales, state_scales, state, state_q, stream)
     if rc != 0:
         raise QuambaError(rc, "quamba_ssd_quantize_state")
 
@@ -374,71 +280,32 @@ def quamba_mamba1_scan(shape: Shape, scales: DeviceScales, x, B, Cm, dt, A, D, y
                        stream=None, gate: Gate | None = None) -> None:
     """Enqueue the 8-bit Mamba1 selective scan (channel-major device tensors, time last).  With `gate`,
     quamba_mamba1_scan_gated is called (dt may then be None if the gate carries the step-size codes)."""
-    import torch
-    b, L, Dn, N = shape.batch, shape.seqlen, shape.headdim, shape.d_state
-    sc = scales.struct()
-    args = (_dp(x, torch.int8, (b, Dn, L), "x"), _dp(B, torch.int8, (b, N, L), "B"),
-            _dp(Cm, torch.int8, (b, N, L), "C"), _dp(dt, torch.float32, (b, Dn, L), "dt"),
-            _dp(A, torch.float32, (Dn, N), "A"), _dp(D, torch.float32, (Dn,), "D"),
-            _dp(init_state, torch.float32, (b, Dn, N), "init_state"), _dp(y, torch.float16, (b, Dn, L), "y"),
-            _dp(final_state, torch.float32, (b, Dn, N), "final_state"), _stream_ptr(stream))
-    if gate is None:
-        rc, name = load_library().quamba_mamba1_scan(C.byref(shape), C.byref(sc), *args), "quamba_mamba1_scan"
-    else:
-        g = gate.struct((b, Dn, L), (b, Dn, L), Dn)
-        rc = load_library().quamba_mamba1_scan_gated(C.byref(shape), C.byref(sc), C.byref(g), *args)
-        name = "quamba_mamba1_scan_gated"
+    rc = (_bind or _load_bind()).mamba1_scan(shape, scales, x, B, Cm, dt, A, D, y, init_state, final_state, stream, gate)
     if rc != 0:
-        raise QuambaError(rc, name)
+        raise QuambaError(rc, "quamba_mamba1_scan" if gate is None else "quamba_mamba1_scan_gated")
 
 
 def quamba_mamba1_decode_step(shape: Shape, scales: DeviceScales, x, B, Cm, dt, A, D, state, y, stream=None,
                               gate: Gate | None = None) -> None:
     """Enqueue one generation step of the Mamba1 recurrence on the fp32 state [b, D, N], in place.  With `gate`,
     quamba_mamba1_decode_step_gated is called."""
-    import torch
-    b, Dn, N = shape.batch, shape.headdim, shape.d_state
-    sc = scales.struct()
-    args = (_dp(x, torch.int8, (b, Dn), "x"), _dp(B, torch.int8, (b, N), "B"),
-            _dp(Cm, torch.int8, (b, N), "C"), _dp(dt, torch.float32, (b, Dn), "dt"),
-            _dp(A, torch.float32, (Dn, N), "A"), _dp(D, torch.float32, (Dn,), "D"),
-            _dp(state, torch.float32, (b, Dn, N), "state"), _dp(y, torch.float16, (b, Dn), "y"), _stream_ptr(stream))
-    if gate is None:
-        rc, name = load_library().quamba_mamba1_decode_step(C.byref(shape), C.byref(sc), *args), "quamba_mamba1_decode_step"
-    else:
-        g = gate.struct((b, Dn), (b, Dn), Dn)
-        rc = load_library().quamba_mamba1_decode_step_gated(C.byref(shape), C.byref(sc), C.byref(g), *args)
-        name = "quamba_mamba1_decode_step_gated"
+    rc = (_bind or _load_bind()).mamba1_decode(shape, scales, x, B, Cm, dt, A, D, state, y, stream, gate)
     if rc != 0:
-        raise QuambaError(rc, name)
+        raise QuambaError(rc, "quamba_mamba1_decode_step" if gate is None else "quamba_mamba1_decode_step_gated")
 
 
 def quamba_conv1d_q8(shape: Shape, scales: DeviceScales, xBC, weight, bias, in_w_scale: float, x_out, B_out, C_out,
                      conv_state_in=None, conv_state_out=None, stream=None) -> None:
     """Enqueue the W8A8 causal convolution + SiLU + Eq. 1 that produces the scan's int8 x, B and C (device tensors)."""
-    import torch
-    b, L, H, P, G, N = shape.batch, shape.seqlen, shape.nheads, shape.headdim, shape.ngroups, shape.d_state
-    Ct = H * P + 2 * G * N
-    sc = scales.struct()
-    rc = load_library().quamba_conv1d_q8(
-        C.byref(shape), C.byref(sc), _dp(xBC, torch.int8, (b, L, Ct), "xBC"), _dp(weight, torch.int8, (Ct, 4), "weight"),
-        _dp(bias, torch.float32, (Ct,), "bias"), float(in_w_scale),
-        _dp(conv_state_in, torch.int8, (b, 3, Ct), "conv_state_in"), _dp(x_out, torch.int8, (b, L, H, P), "x_out"),
-        _dp(B_out, torch.int8, (b, L, G, N), "B_out"), _dp(C_out, torch.int8, (b, L, G, N), "C_out"),
-        _dp(conv_state_out, torch.int8, (b, 3, Ct), "conv_state_out"), _stream_ptr(stream))
+    rc = (_bind or _load_bind()).conv1d(shape, scales, xBC, weight, bias, in_w_scale, x_out, B_out, C_out, conv_state_in,
+                                        conv_state_out, stream)
     if rc != 0:
         raise QuambaError(rc, "quamba_conv1d_q8")
 
 
 def quamba_hadamard_quantize(y, s_y: float, out, stream=None) -> None:
     """Enqueue out = Eq.1((1/s_y) H_n y) over the last axis of the fp16 device tensor y (n = 2^k, 12 * 2^k or 20 * 2^k)."""
-    import torch
-    n = y.shape[-1]
-    rows = y.numel() // max(1, n)
-    if rows == 0 and n > 0:
-        return                      # an empty tensor has no device pointer to pass
-    rc = load_library().quamba_hadamard_quantize(_dp(y, torch.float16, name="y"), rows, n, float(s_y),
-                                                 _dp(out, torch.int8, tuple(y.shape), "out"), _stream_ptr(stream))
+    rc = (_bind or _load_bind()).hadamard(y, s_y, out, stream)
     if rc != 0:
         raise QuambaError(rc, "quamba_hadamard_quantize")
 

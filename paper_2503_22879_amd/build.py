@@ -1,8 +1,10 @@
-"""Build the HIP library for gfx950 with hipcc (cross-compiles without a GPU)."""
+"""Build the HIP library for gfx950 with hipcc (cross-compiles without a GPU), and the native argument marshalling of the
+Python binding."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -10,6 +12,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libquamba_ssd.so")
+BIND = os.path.join(PKG, "_bind.so")
 SOURCES = ["api.hip", "probe.hip", "conv1d.hip", "decode.hip", "decode_q8.hip", "hadamard.hip", "mamba1.hip", "prefill_generic.hip", "prefill_mfma.hip", "offline.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # -packed-fp32-ops is switched off: some packed fp32 forms have given wrong results on the test machines.
@@ -29,10 +32,30 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def _build_bind(force: bool) -> str:
+    """The extension module that binding.py calls (host code against torch's headers; torch's libraries are already
+    loaded when it is imported)."""
+    import torch
+    src, header = os.path.join(CSRC, "bind.cpp"), os.path.join(ROOT, "include", "quamba_ssd.h")
+    if force or not os.path.exists(BIND) or any(os.path.getmtime(d) > os.path.getmtime(BIND) for d in (src, header)):
+        base = os.path.dirname(torch.__file__)
+        cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(ROOT, "include"),
+               "-isystem", sysconfig.get_paths()["include"]]
+        for d in (os.path.join(base, "include"), os.path.join(base, "include", "torch", "csrc", "api", "include"),
+                  os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include")):
+            cmd += ["-isystem", d]
+        cmd += [src, "-o", BIND, "-L" + os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+        subprocess.check_call(cmd)
+    return BIND
+
+
 def build_library(force: bool = True, jobs: int = 8) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        bind = ex.submit(_build_bind, force)
         objs = list(ex.map(lambda s: _compile(s, force), SOURCES))
+        bind.result()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
     return LIB
 

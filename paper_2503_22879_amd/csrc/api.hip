@@ -6,8 +6,6 @@
 
 namespace {
 
-constexpr size_t kMaxLdsBytes = 160 * 1024;  // LDS of one gfx950 compute unit
-
 int check_shape(const quamba_ssd_shape_t *s, bool prefill)
 {
     if (s->batch <= 0 || s->nheads <= 0 || s->headdim <= 0 || s->d_state <= 0 || s->ngroups <= 0 ||
@@ -116,7 +114,7 @@ extern "C" int quamba_ssd_prefill_gated(const quamba_ssd_shape_t *shape, const q
     const size_t need = quamba_ssd_prefill_workspace_size(shape);
     if (!workspace || workspace_bytes < need) workspace = nullptr;
     const bool mfma = use_mfma(shape, x, B, C, y, init_state, final_state) && (!gate || aligned16(gate->z));
-    if (!mfma && quamba::prefill_generic_lds_bytes(*shape) > kMaxLdsBytes) return QUAMBA_ESHAPE;
+    if (!mfma && quamba::prefill_generic_lds_bytes(*shape) > quamba::kLdsPerCu) return QUAMBA_ESHAPE;
 
     quamba::SsdArgs a = pack(shape, scales, x, B, C, dt, A, D, init_state, final_state, y);
     rc = apply_gate(gate, dt, &a);
@@ -224,7 +222,7 @@ extern "C" int quamba_ssd_decode_step_q8_gated(const quamba_ssd_shape_t *shape, 
     if (!state_scales || !x || !B || !C || !dt || !A || !state_q || !y) return QUAMBA_ENULL;
     rc = check_shape(shape, false);
     if (rc != QUAMBA_OK) return rc;
-    if (quamba::decode_q8_lds_bytes(*shape) > kMaxLdsBytes) return QUAMBA_ESHAPE;
+    if (quamba::decode_q8_lds_bytes(*shape) > quamba::kLdsPerCu) return QUAMBA_ESHAPE;
     quamba::SsdArgs a = pack(shape, scales, x, B, C, dt, A, D, nullptr, nullptr, y);
     rc = apply_gate(gate, dt, &a);
     if (rc != QUAMBA_OK) return rc;
@@ -242,7 +240,7 @@ extern "C" int quamba_ssd_quantize_state(const quamba_ssd_shape_t *shape, const 
     if (!state_scales || !state || !state_q) return QUAMBA_ENULL;
     rc = check_shape(shape, false);
     if (rc != QUAMBA_OK) return rc;
-    if (quamba::decode_q8_lds_bytes(*shape) > kMaxLdsBytes) return QUAMBA_ESHAPE;
+    if (quamba::decode_q8_lds_bytes(*shape) > quamba::kLdsPerCu) return QUAMBA_ESHAPE;
     const quamba::SsdArgs a = pack(shape, scales, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                                    const_cast<float *>(state), nullptr);
     const hipError_t e = quamba::launch_quantize_state(a, state_scales, state_q, static_cast<hipStream_t>(hip_stream));

@@ -12,7 +12,6 @@
 // a fixed order (the header states it); the compiler must not contract multiplies and adds, and the exponential of
 // the decay is a fixed sequence of such operations instead of a library call.
 #include <algorithm>
-#include <atomic>
 
 #include "quamba_internal.h"
 
@@ -25,7 +24,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxSeqs = 16;  // sequences of one head a workgroup of the vector kernel may own
-constexpr size_t kLdsLimit = 160 * 1024;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -417,31 +415,15 @@ __global__ __launch_bounds__(kThreads) void quantize_state_kernel(SsdArgs a, con
     }
 }
 
-template <typename K, typename... Extra>
-hipError_t launch(K kernel, dim3 grid, const SsdArgs &a, const float *ss, int8_t *q, size_t lds, hipStream_t stream,
-                  Extra... extra)
+template <auto Kernel, typename... Extra>
+hipError_t launch(dim3 grid, const SsdArgs &a, const float *ss, int8_t *q, size_t lds, hipStream_t stream, Extra... extra)
 {
     if (lds > 48 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const hipError_t e = allow_full_lds<Kernel>();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds, stream, a, ss, q, extra...);
+    hipLaunchKernelGGL(Kernel, grid, dim3(kThreads), lds, stream, a, ss, q, extra...);
     return hipGetLastError();
-}
-
-// Compute units of the current device (cached per device id).
-int compute_units()
-{
-    static std::atomic<int> cached[64];  // zero-initialised; concurrent first calls store the same value
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    int n = cached[dev].load(std::memory_order_relaxed);
-    if (n == 0) {
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-        cached[dev].store(n, std::memory_order_relaxed);
-    }
-    return n;
 }
 
 // Sequences per workgroup of the vector kernel: enough workgroups to fill the chip several times over (>= 4096 when
@@ -454,7 +436,7 @@ int seqs_per_block(const quamba_ssd_shape_t &s)
     int n = (int)std::min<int64_t>(kMaxSeqs, std::max<int64_t>(1, pairs / 4096));
     if (s.d_state >= 4) n = std::min(n, std::max(1, kThreads / (s.d_state / 4)));  // one round of threads covers the slice's B rows
     while (n > 1 && vec_lds_bytes(s, n) > 64 * 1024) --n;
-    if (vec_lds_bytes(s, n) > kLdsLimit || (s.batch + n - 1) / n > 65535) return 0;
+    if (vec_lds_bytes(s, n) > kLdsPerCu || (s.batch + n - 1) / n > 65535) return 0;
     return n;
 }
 
@@ -467,12 +449,12 @@ hipError_t launch_vec(const SsdArgs &a, const float *ss, int8_t *q, int spb, hip
     // all workgroups resident at once: 4 waves of up to 128 registers each allow 4 workgroups per compute unit
     // (one wave of each per SIMD), the LDS footprint may allow fewer
     const int nslices = (a.s.batch + spb - 1) / spb;
-    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(4, kLdsLimit / lds));
+    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(4, kLdsPerCu / lds));
     const int want_y = (compute_units() * per_cu + a.s.nheads - 1) / a.s.nheads;
     const dim3 grid((unsigned)a.s.nheads, (unsigned)std::max(1, std::min(nslices, want_y)));
-    if (P % (kWaves * RPI * 2) == 0) return launch(decode_q8_vec_kernel<N, 2, true>, grid, a, ss, q, lds, stream, spb);
-    if (P % (kWaves * RPI) == 0) return launch(decode_q8_vec_kernel<N, 1, true>, grid, a, ss, q, lds, stream, spb);
-    return launch(decode_q8_vec_kernel<N, 1, false>, grid, a, ss, q, lds, stream, spb);
+    if (P % (kWaves * RPI * 2) == 0) return launch<decode_q8_vec_kernel<N, 2, true>>(grid, a, ss, q, lds, stream, spb);
+    if (P % (kWaves * RPI) == 0) return launch<decode_q8_vec_kernel<N, 1, true>>(grid, a, ss, q, lds, stream, spb);
+    return launch<decode_q8_vec_kernel<N, 1, false>>(grid, a, ss, q, lds, stream, spb);
 }
 
 }  // namespace
@@ -511,7 +493,7 @@ hipError_t launch_decode_q8(const SsdArgs &a, const float *state_scales, int8_t 
             default: break;
         }
     }
-    return launch(decode_q8_any_kernel, dim3((unsigned)(a.s.batch * a.s.nheads)), a, state_scales, state_q,
+    return launch<decode_q8_any_kernel>(dim3((unsigned)(a.s.batch * a.s.nheads)), a, state_scales, state_q,
                   decode_q8_lds_bytes(a.s), stream);
 }
 
@@ -521,8 +503,8 @@ hipError_t launch_quantize_state(const SsdArgs &a, const float *state_scales, in
     const bool vec = a.s.d_state % 4 == 0 && reinterpret_cast<uintptr_t>(a.state) % 16 == 0 &&
                      reinterpret_cast<uintptr_t>(state_q) % 4 == 0;
     const dim3 grid((unsigned)(a.s.batch * a.s.nheads));
-    return vec ? launch(quantize_state_kernel<true>, grid, a, state_scales, state_q, lds, stream)
-               : launch(quantize_state_kernel<false>, grid, a, state_scales, state_q, lds, stream);
+    return vec ? launch<quantize_state_kernel<true>>(grid, a, state_scales, state_q, lds, stream)
+               : launch<quantize_state_kernel<false>>(grid, a, state_scales, state_q, lds, stream);
 }
 
 }  // namespace quamba

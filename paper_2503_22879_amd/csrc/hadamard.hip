@@ -359,17 +359,9 @@ hipError_t launch_mixed_fast(const uint16_t *y, int64_t rows, float inv_s, int8_
     constexpr int threads = ((need > P / 2 ? need : P / 2) + 63) / 64 * 64;
     constexpr int lds = NSB * 1152 * (int)sizeof(float);
     static_assert(threads <= 1024 && lds <= 160 * 1024, "launch shape");
-    if (lds > 48 * 1024) {  // raise the kernel's LDS limit once per device
-        static std::atomic<uint32_t> done{0};
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
+    if (lds > 48 * 1024) {
+        const hipError_t e = allow_full_lds<hadamard_quantize_mixed_fast_kernel<M, LOGP>>();
         if (e != hipSuccess) return e;
-        if (dev < 0 || dev >= 32 || !(done.load() >> dev & 1u)) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(hadamard_quantize_mixed_fast_kernel<M, LOGP>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-            if (e != hipSuccess) return e;
-            if (dev >= 0 && dev < 32) done.fetch_or(1u << dev);
-        }
     }
     hipLaunchKernelGGL((hadamard_quantize_mixed_fast_kernel<M, LOGP>), dim3((unsigned)rows), dim3(threads), lds, stream, y,
                        out, inv_s);
@@ -390,15 +382,13 @@ hipError_t launch_fast(const uint16_t *y, int64_t rows, float inv_s, int8_t *out
     if (dev < 0 || dev >= 16) return hipErrorInvalidDevice;
     if (!resident[dev].load()) {
         if (lds > 48 * 1024) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(hadamard_quantize_kernel<LOGN>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            e = allow_full_lds<hadamard_quantize_kernel<LOGN>>();
             if (e != hipSuccess) return e;
         }
         int per_cu = 0, cus = 0;
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, hadamard_quantize_kernel<LOGN>, RPW * N / 32, lds);
         if (e != hipSuccess) return e;
-        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess) return e;
+        cus = compute_units();
         resident[dev].store(per_cu > 0 && cus > 0 ? 2 * per_cu * cus : 2048);
     }
     const int res = resident[dev].load();
@@ -442,16 +432,14 @@ hipError_t launch_hadamard_quantize(const uint16_t *y, int64_t rows, int n, floa
         const int aligned = reinterpret_cast<uintptr_t>(out) % 4 == 0;
         if (m == 12) {
             if (lds > 48 * 1024) {
-                const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(hadamard_quantize_mixed_kernel<12>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                const hipError_t e = allow_full_lds<hadamard_quantize_mixed_kernel<12>>();
                 if (e != hipSuccess) return e;
             }
             hipLaunchKernelGGL(hadamard_quantize_mixed_kernel<12>, dim3((unsigned)rows), dim3(256), lds, stream, y, out,
                                n / 12, inv_s, aligned);
         } else {
             if (lds > 48 * 1024) {
-                const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(hadamard_quantize_mixed_kernel<20>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+                const hipError_t e = allow_full_lds<hadamard_quantize_mixed_kernel<20>>();
                 if (e != hipSuccess) return e;
             }
             hipLaunchKernelGGL(hadamard_quantize_mixed_kernel<20>, dim3((unsigned)rows), dim3(256), lds, stream, y, out,
@@ -472,8 +460,7 @@ hipError_t launch_hadamard_quantize(const uint16_t *y, int64_t rows, int n, floa
     }
     const int lds = n * (int)sizeof(float);
     if (lds > 48 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(hadamard_quantize_small_kernel),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        const hipError_t e = allow_full_lds<hadamard_quantize_small_kernel>();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(hadamard_quantize_small_kernel, dim3((unsigned)rows), dim3(256), lds, stream, y, out, n, inv_s);

@@ -99,8 +99,7 @@ size_t prefill_generic_lds_bytes(const quamba_ssd_shape_t &s)
 hipError_t launch_prefill_generic(const SsdArgs &a, hipStream_t stream)
 {
     const size_t lds = prefill_generic_lds_bytes(a.s);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(prefill_generic_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = allow_full_lds<prefill_generic_kernel>();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(prefill_generic_kernel, dim3((unsigned)(a.s.batch * a.s.nheads)), dim3(kThreads), lds, stream,
                        a);

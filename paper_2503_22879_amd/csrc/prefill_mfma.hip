@@ -48,7 +48,6 @@
 // of the token index swapped so that the 8 tokens of one k group are 8 consecutive rows.
 #include <algorithm>
 #include <climits>
-#include <atomic>
 
 #include "quamba_internal.h"
 
@@ -1288,8 +1287,7 @@ hipError_t launch_scan_seg(const SsdArgs &a, hipStream_t stream)
     constexpr int lds = GATED ? Lds<PT>::kBytesGated : Lds<PT>::kBytes;
     const int segs = a.nseg > 1 ? a.nseg : 1;  // one set of workgroups per segment
     const dim3 grid((unsigned)(a.s.batch * a.s.nheads * (2 / PT) * segs));
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(prefill_mfma_kernel<PRECISE, PT, GATED, SEG>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const hipError_t e = allow_full_lds<prefill_mfma_kernel<PRECISE, PT, GATED, SEG>>();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((prefill_mfma_kernel<PRECISE, PT, GATED, SEG>), grid, dim3(kThreads), lds, stream, a);
     return hipGetLastError();
@@ -1316,20 +1314,6 @@ hipError_t launch_segment_state(const SsdArgs &a, hipStream_t stream)
     const dim3 grid((unsigned)(a.s.batch * a.s.nheads * (2 / PT) * (a.nseg - 1)));
     hipLaunchKernelGGL((segment_state_kernel<PRECISE, PT>), grid, dim3(kStateThreads), lds, stream, a);
     return hipGetLastError();
-}
-
-// Compute units of the current device (cached per device id).
-int compute_units()
-{
-    static std::atomic<int> cached[64];  // zero-initialised; concurrent first calls store the same value
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    int n = cached[dev].load(std::memory_order_relaxed);
-    if (n == 0) {
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-        cached[dev].store(n, std::memory_order_relaxed);
-    }
-    return n;
 }
 
 }  // namespace

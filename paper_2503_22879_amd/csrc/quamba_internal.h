@@ -2,9 +2,44 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+
 #include "quamba_ssd.h"
 
 namespace quamba {
+
+// ---- host helpers of the launchers ----
+constexpr size_t kLdsPerCu = 160 * 1024;  // LDS of one gfx950 compute unit
+
+// Compute units of the current device (asked of the runtime once per device; 256 without one).
+inline int compute_units()
+{
+    static std::atomic<int> cached[64];  // zero-initialised; concurrent first calls store the same value
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    int n = cached[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+        cached[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
+// Lets a kernel that takes dynamic LDS only use all of it.  The attribute belongs to the (kernel, device) pair and does
+// not change, so the runtime is asked once for each and not on every launch.
+template <auto Kernel>
+hipError_t allow_full_lds()
+{
+    static std::atomic<uint64_t> done{0};  // one bit per device
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev >= 0 && dev < 64 && (done.load(std::memory_order_relaxed) >> dev & 1u)) return hipSuccess;
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)kLdsPerCu);
+    if (e == hipSuccess && dev >= 0 && dev < 64) done.fetch_or((uint64_t)1 << dev, std::memory_order_relaxed);
+    return e;
+}
 
 // Device pointers of one call, shared by all kernels.
 struct SsdArgs {
