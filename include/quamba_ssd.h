@@ -281,8 +281,8 @@ int quamba_hadamard_quantize(const uint16_t *y, int64_t rows, int32_t n, float s
  *   A  device fp32 [D, N] (<= 0)             D     device fp32 [D] or NULL
  *   init_state  device fp32 [batch, D, N] or NULL (zero)      final_state  device fp32 [batch, D, N] or NULL
  *   y  device fp16 [batch, D, seqlen]
- * d_state = 16, seqlen a multiple of 16 and 16-byte aligned tensors take the wave-scan kernel; other shapes (d_state
- * <= 64) or QUAMBA_FLAG_GENERIC_KERNEL a one-thread-per-channel kernel.  fp32 throughout; y rounded to fp16.
+ * d_state = 16 and seqlen >= 16 take the wave-scan kernel; other shapes (d_state <= 64) or
+ * QUAMBA_FLAG_GENERIC_KERNEL a one-thread-per-channel kernel.  fp32 throughout; y rounded to fp16.
  * Errors: ENULL, ESHAPE, EINVAL, EHIP.
  */
 int quamba_mamba1_scan(const quamba_ssd_shape_t *shape, const quamba_ssd_scales_t *scales, const int8_t *x,
@@ -305,7 +305,7 @@ int quamba_mamba1_decode_step(const quamba_ssd_shape_t *shape, const quamba_ssd_
  *   gate->dt_q     int8, laid out like dt: the step size becomes softplus(dt_scale * dt_q + dt_bias[d]); `dt` is then
  *                  ignored and may be NULL
  *   gate->dt_bias  fp32 [D] (one per channel) or NULL
- * The wave-scan kernel additionally needs z and dt_q 16-byte aligned.  Errors as the plain entry points, plus EINVAL for
+ * Errors as the plain entry points, plus EINVAL for
  * non-finite or non-positive scales.
  */
 int quamba_mamba1_scan_gated(const quamba_ssd_shape_t *shape, const quamba_ssd_scales_t *scales,

@@ -5,13 +5,12 @@
 // x, Delta, y [b, D, L]; B, C [b, N, L]; A [D, N]; states [b, D, N].
 //
 // There is no contraction to put on the matrix cores: every (token, channel, state) element needs its own
-// exponential, so the kernel is bound by the vector ALU (about 14 instruction slots per element, 4 of them the
-// quarter-rate exponential) and is organised to keep that unit busy.  A wave owns one channel at a time and a tile of
-// 1024 tokens, 16 consecutive tokens per lane: per state it forms the 16 decay factors and inputs of its tokens,
-// reduces them to one (product, state) pair, scans the pairs over the 64 lanes with data-parallel-primitive row shifts
-// and broadcasts (the operator of a first-order linear recurrence), and replays its 16 tokens from the scanned-in state
-// while accumulating y.  The tile's B and C codes sit in LDS, shared by the workgroup's eight channels; the state at the
-// end of a tile is carried to the next tile through LDS.
+// exponential, so the kernel is bound by the vector ALU and is organised to keep that unit busy.  A group of LPC lanes owns
+// one channel at a time and a tile of 16 LPC tokens, 16 consecutive tokens per lane: per state it forms the 16 decay
+// factors and inputs of its tokens, reduces them to one (product, state) pair, scans the pairs over the group's lanes with
+// data-parallel-primitive row shifts and broadcasts (the operator of a first-order linear recurrence), and replays its 16
+// tokens from the scanned-in state while accumulating y.  The tile's B and C sit in LDS, shared by the channels of the
+// workgroup; the state at the end of a tile is carried to the next tile through LDS.
 #include <algorithm>
 
 #include "quamba_internal.h"
@@ -19,10 +18,8 @@
 namespace quamba {
 namespace {
 
-constexpr int kThreads = 512;
-constexpr int kWaves = kThreads / 64;
+constexpr int kThreads = 512;        // of the scan's workgroups
 constexpr int kE = 16;              // tokens per lane
-constexpr int kTile = 64 * kE;      // tokens per tile
 constexpr float kLog2e = 1.44269504088896340736f;
 constexpr int kDecodeSeqs = 4;      // sequences per thread and trip of the decode step
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -35,7 +32,7 @@ __device__ __forceinline__ float dpp_fetch(float old, float v)
                                                                  CTRL, ROW_MASK, 0xf, false));
 }
 
-// Inclusive scan of (P, h) pairs over the 64 lanes.  One step applies the pair fetched from an earlier lane first and
+// Inclusive scan of (P, h) pairs over groups of LPC lanes (16, 32 or 64).  One step applies the pair fetched from an earlier lane first and
 // the lane's own after it: (Ps, hs) then (P, h) -> (Ps P, P hs + h), as two instructions whose first source is the
 // shifted lane: h += hs * P, then P *= Ps.  Lanes without a source lane (and rows the mask leaves out) are not
 // written, which is the identity.  Shifts by 1, 2, 4, 8 inside rows of 16 lanes, then lane 15 of rows 0 and 2 into
@@ -45,14 +42,23 @@ __device__ __forceinline__ float dpp_fetch(float old, float v)
     "s_nop 1\n\t"                                                                    \
     "v_fmac_f32_dpp %0, %0, %1 " ctrl " bank_mask:0xf\n\t"                           \
     "v_mul_f32_dpp %1, %1, %1 " ctrl " bank_mask:0xf\n\t"
+#define QUAMBA_SCAN_ROW                                                                            \
+    "s_setprio 2\n\t" QUAMBA_SCAN_STEP("row_shr:1 row_mask:0xf") QUAMBA_SCAN_STEP("row_shr:2 row_mask:0xf") \
+    QUAMBA_SCAN_STEP("row_shr:4 row_mask:0xf") QUAMBA_SCAN_STEP("row_shr:8 row_mask:0xf")
+template <int LPC>
 __device__ __forceinline__ void wave_scan(float &P, float &h)
 {
-    asm volatile(QUAMBA_SCAN_STEP("row_shr:1 row_mask:0xf") QUAMBA_SCAN_STEP("row_shr:2 row_mask:0xf")
-                 QUAMBA_SCAN_STEP("row_shr:4 row_mask:0xf") QUAMBA_SCAN_STEP("row_shr:8 row_mask:0xf")
-                 QUAMBA_SCAN_STEP("row_bcast:15 row_mask:0xa") QUAMBA_SCAN_STEP("row_bcast:31 row_mask:0xc")
-                 "s_nop 1"
-                 : "+v"(h), "+v"(P));
+    if (LPC == 16)
+        asm volatile(QUAMBA_SCAN_ROW "s_nop 1\n\ts_setprio 0" : "+v"(h), "+v"(P));
+    else if (LPC == 32)
+        asm volatile(QUAMBA_SCAN_ROW QUAMBA_SCAN_STEP("row_bcast:15 row_mask:0xa") "s_nop 1\n\ts_setprio 0"
+                     : "+v"(h), "+v"(P));
+    else
+        asm volatile(QUAMBA_SCAN_ROW QUAMBA_SCAN_STEP("row_bcast:15 row_mask:0xa")
+                     QUAMBA_SCAN_STEP("row_bcast:31 row_mask:0xc") "s_nop 1\n\ts_setprio 0"
+                     : "+v"(h), "+v"(P));
 }
+#undef QUAMBA_SCAN_ROW
 #undef QUAMBA_SCAN_STEP
 
 // log(1 + exp(v)) = max(v, 0) + log(1 + e), e = 2^(-|v| log2 e), on the hardware's base-2 exponential and logarithm.
@@ -67,151 +73,210 @@ __device__ __forceinline__ float softplus_fast(float v)
 
 __device__ __forceinline__ float byte_to_float(uint32_t w, int k) { return (float)(int)(int8_t)(w >> (8 * k)); }
 
-// u * (fp16 half HI of w) and (fp16 half HI of w) * g + acc as one mixed-precision multiply-add each: the fp16 operand
-// is widened inside the instruction.
-__device__ __forceinline__ float mix_mul(int hi, float u, uint32_t w)  // hi is a constant after unrolling
+// 2^x of 17 values at raised wave priority.  A SIMD issues plain fp32 instructions of two waves at once, but an exponential
+// blocks it for 8 cycles.  With the exponentials of its waves scattered between the others' plain instructions the pairing
+// hardly ever happens; as uninterrupted bursts they leave stretches in which it does (a loop of 16 exponentials and 80
+// multiply-adds, 4 waves per SIMD: 192 ns per turn and SIMD, with the bursts prioritised 143).
+__device__ __forceinline__ void exp2_burst(float (&v)[kE], float &p)
 {
-    float d;
-    if (hi) asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[0,1,0] op_sel_hi:[0,1,0]" : "=v"(d) : "v"(u), "v"(w));
-    else asm("v_fma_mix_f32 %0, %1, %2, 0 op_sel:[0,0,0] op_sel_hi:[0,1,0]" : "=v"(d) : "v"(u), "v"(w));
-    return d;
-}
-__device__ __forceinline__ float mix_fma(int hi, uint32_t w, float g, float acc)
-{
-    float d;
-    if (hi) asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(w), "v"(g), "v"(acc));
-    else asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(w), "v"(g), "v"(acc));
-    return d;
+#define QUAMBA_E(i) "v_exp_f32 %" #i ", %" #i "\n\t"
+    asm volatile("s_setprio 2\n\t"
+                 QUAMBA_E(0) QUAMBA_E(1) QUAMBA_E(2) QUAMBA_E(3) QUAMBA_E(4) QUAMBA_E(5) QUAMBA_E(6) QUAMBA_E(7) QUAMBA_E(8)
+                 QUAMBA_E(9) QUAMBA_E(10) QUAMBA_E(11) QUAMBA_E(12) QUAMBA_E(13) QUAMBA_E(14) QUAMBA_E(15) QUAMBA_E(16)
+                 "s_setprio 0\n\ts_nop 0"  // also the wait a use of an exponential's result needs
+                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7]),
+                   "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15]),
+                   "+v"(p));
+#undef QUAMBA_E
 }
 
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+// 16 bytes / 4 floats / 8 halves at any byte resp. element address: the hardware takes unaligned vector accesses, so a
+// row may start anywhere (a sequence length that is no multiple of 16 shifts every row).
+typedef u32x4 u32x4_u __attribute__((aligned(1)));
+typedef u32x4 u32x4_f __attribute__((aligned(4)));
+typedef u32x4 u32x4_h __attribute__((aligned(2)));
 
-// N = 16 states, seqlen a multiple of 16, 16-byte aligned tensors.  grid = (D / kWaves, batch); wave w of a workgroup
-// owns channel blockIdx.x * kWaves + w.  The loop over states stays rolled: the 16 tokens of a lane already give every
-// instruction 16 independent copies, and unrolling further only costs registers.  The tile's B and C codes are
-// converted to fp16 once, when they are staged (exact: 8-bit integers), so that the products that consume them take
-// them as fp16 operands of a mixed-precision multiply-add instead of converting them again for every channel.
-__global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, const float *A, const float *init,
-                                                                  float *fin)
+// The 16 codes of tokens t .. t + 15 of a row of L >= 16; those past the end are zero and are not read: a lane that would
+// cross the end reads the row's last 16 codes and shifts.
+__device__ __forceinline__ u32x4 load_codes(const int8_t *row, int t, int L)
 {
-    constexpr int N = 16;
-    __shared__ u32x4 s_B[N][64][2];  // [state][lane]: the lane's 16 token codes of the tile as fp16 pairs
-    __shared__ u32x4 s_C[N][64][2];
-    __shared__ float s_carry[kWaves][N];  // per wave: the state in front of the current tile
-    __shared__ float s_silu[256];         // SiLU(z_scale * code), indexed by the gate code's byte
+    const int t1 = min(t, L - kE), k = t - t1;
+    u32x4 v = *reinterpret_cast<const u32x4_u *>(row + t1);
+    if (k > 0) {
+        if (k & 8) v = (u32x4){v[2], v[3], 0, 0};
+        if (k & 4) v = (u32x4){v[1], v[2], v[3], 0};
+        v = (u32x4){__builtin_amdgcn_alignbyte(v[1], v[0], k), __builtin_amdgcn_alignbyte(v[2], v[1], k),
+                    __builtin_amdgcn_alignbyte(v[3], v[2], k), __builtin_amdgcn_alignbyte(0, v[3], k)};
+        if (k >= kE) v = (u32x4){0, 0, 0, 0};
+    }
+    return v;
+}
+
+// N = 16 states, seqlen >= 16.  grid = (channels / (8 64 / LPC), batch); LPC lanes share a channel (64, 32 or 16), so a wave
+// holds 64 / LPC channels.  The loop over states stays rolled: the 16 tokens of a lane already give every instruction 16
+// independent copies, and unrolling further only costs registers.  B and C are staged as fp32 (converted once per workgroup
+// instead of once per channel): plain fp32 multiplies and multiply-adds of two waves can issue together, the
+// mixed-precision ones that take fp16 operands cannot.  LDS rows are [state][quarter of a lane's tokens][lane], so that a lane's
+// four 16-byte reads are consecutive across the lanes.
+// C is staged times its scale and the skip term starts the output's sum, so that the sum is y.
+// Measured at 4 x 4096 tokens, 5120 channels: 312 us (393 with fp16 operands, tiles of 1024
+// tokens and the exponentials between the other instructions); 1003 tokens of one sequence: 37 us (3010 us with one thread
+// per channel, which is what a length that is no multiple of 16 took before).
+template <int LPC>
+__global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, const float *A, const float *init, float *fin)
+{
+    constexpr int N = 16, kTile = LPC * kE, kCh = kThreads / LPC;  // channels of the workgroup
+    // separate arrays, so that the compiler sees that the state's write does not touch the C read behind it
+    __shared__ f32x4 s_B[N * 4 * LPC], s_C[N * 4 * LPC];  // [state][quarter][lane]
+    __shared__ float2 s_AH[kCh * N];                      // [channel][state]: A log2(e), the state before the tile
+    __shared__ float s_silu[256];                         // SiLU(z_scale * code), by the gate code's byte
     const int D = a.s.headdim, L = a.s.seqlen;
     const int b = blockIdx.y;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int d = blockIdx.x * kWaves + wave;
-    const bool own = d < D;  // wave-uniform; waves without a channel only help staging
+    const int sub = threadIdx.x & (LPC - 1);  // the lane inside its channel's group
+    const int ch = threadIdx.x / LPC;         // the channel inside the workgroup
+    const int d = blockIdx.x * kCh + ch;
+    const bool own = d < D;                   // lanes without a channel redo the last one and store nothing
     const int dd = own ? d : D - 1;
-    const float sB = a.B_scales[0], sC = a.C_scales[0];
+    const float sC = a.C_scales[0];
     const float sx = x_scale_lookup(a, 0, dd);
-    const float sxB = sx * sB;
-    const float *Ad = A + (size_t)dd * N;
+    const float sxB = sx * a.B_scales[0], Dx = (a.D ? a.D[dd] : 0.0f) * sx;
 
-    if (lane < N) s_carry[wave][lane] = (init && own) ? init[((size_t)b * D + d) * N + lane] : 0.0f;
-    if (a.z && threadIdx.x < 256) s_silu[threadIdx.x] = silu_of_code(a.z_scale, (int8_t)threadIdx.x);
+    for (int i = threadIdx.x; i < kCh * N; i += kThreads) {
+        const int c = min((int)blockIdx.x * kCh + i / N, D - 1), n = i % N;
+        s_AH[i] = make_float2(A[(size_t)c * N + n] * kLog2e, init ? init[((size_t)b * D + c) * N + n] : 0.0f);
+    }
+    if (a.z)
+        for (int i = threadIdx.x; i < 256; i += kThreads) s_silu[i] = silu_of_code(a.z_scale, (int8_t)i);
 
+    // Row addresses and token indices are derived anew, from a channel and lane index the compiler must take for new ones,
+    // where a tile begins and where it ends: kept across the loop over states they would take the registers that
+    // let its LDS reads be requested ahead.
+    auto anew = [&](int t0, size_t &row, int &t) {
+        int c = dd, l = sub;
+        asm volatile("" : "+v"(c), "+v"(l));
+        row = ((size_t)b * D + c) * L;
+        t = t0 + kE * l;
+    };
     for (int t0 = 0; t0 < L; t0 += kTile) {
-        // the tile's B and C codes: 2 * 16 rows of 1024 codes, 16 codes per thread and trip
-        __syncthreads();
-        for (int i = threadIdx.x; i < 2 * N * 64; i += kThreads) {
-            const int which = i / (N * 64), n = (i / 64) % N, l = i % 64;
-            const int t = t0 + kE * l;
-            u32x4 v = {0, 0, 0, 0};
-            if (t < L) v = *reinterpret_cast<const u32x4 *>((which ? a.C : a.B) + ((size_t)b * N + n) * L + t);
-            f16x8 lo, hi;
+        size_t row;
+        int t;
+        anew(t0, row, t);
+        const u32x4 xq = load_codes(a.x + row, t, L);
+        u32x4 raw[4];  // 16 fp32 step sizes, or their 16 codes in the first piece
+        if (a.dt_q) {
+            raw[0] = load_codes(a.dt_q + row, t, L);
+        } else if (t + kE <= L) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                lo[k] = (_Float16)byte_to_float(v[k >> 2], k & 3);
-                hi[k] = (_Float16)byte_to_float(v[2 + (k >> 2)], k & 3);
-            }
-            u32x4 *dst = which ? s_C[n][l] : s_B[n][l];
-            dst[0] = __builtin_bit_cast(u32x4, lo);
-            dst[1] = __builtin_bit_cast(u32x4, hi);
-        }
-        __syncthreads();
-        if (!own) continue;
-
-        const int t = t0 + kE * lane;
-        const bool live = t < L;  // whole groups of 16 tokens: seqlen is a multiple of 16
-        const size_t row = ((size_t)b * D + d) * L + t;
-        u32x4 xq = {0, 0, 0, 0}, zq = {0, 0, 0, 0};
-        float dt[kE];
-        if (live) {
-            xq = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.x + row));
-            if (a.z) zq = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.z + row));  // used after the scan
-            if (a.dt_q) {  // step size = softplus(s_dt code + bias[d]) (Section 3.2), 16 codes in one load
-                const u32x4 dq = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.dt_q + row));
-                const float bias = a.dt_bias ? a.dt_bias[d] : 0.0f;
-#pragma unroll
-                for (int i = 0; i < kE; ++i) dt[i] = softplus_fast(fmaf(a.dt_scale, byte_to_float(dq[i >> 2], i & 3), bias));
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 v = reinterpret_cast<const f32x4 *>(a.dt + row)[q];  // plain: four loads share a sector
-                    dt[4 * q] = v[0]; dt[4 * q + 1] = v[1]; dt[4 * q + 2] = v[2]; dt[4 * q + 3] = v[3];
-                }
-            }
+            for (int q = 0; q < 4; ++q)  // plain, not non-temporal: four loads share a sector
+                raw[q] = reinterpret_cast<const u32x4_f *>(a.dt + row + t)[q];
         } else {
 #pragma unroll
-            for (int i = 0; i < kE; ++i) dt[i] = 0.0f;  // identity steps: decay 1, input 0
+            for (int i = 0; i < kE; ++i)
+                raw[i >> 2][i & 3] = __builtin_bit_cast(uint32_t, a.dt[row + min(t + i, L - 1)]);
+        }
+        float dt[kE];
+        if (a.dt_q) {  // step size = softplus(s_dt code + bias[d]) (Section 3.2)
+            const float bias = a.dt_bias ? a.dt_bias[dd] : 0.0f;
+#pragma unroll
+            for (int i = 0; i < kE; ++i)
+                dt[i] = softplus_fast(fmaf(a.dt_scale, byte_to_float(raw[0][i >> 2], i & 3), bias));
+        } else {
+#pragma unroll
+            for (int i = 0; i < kE; ++i) dt[i] = from_bits(raw[i >> 2][i & 3]);
+        }
+        if (t + kE > L) {  // tokens past the end are identity steps: decay 1, input 0
+#pragma unroll
+            for (int i = 0; i < kE; ++i) dt[i] = t + i < L ? dt[i] : 0.0f;
         }
         float u[kE], y[kE];
         float dtsum = 0.0f;
 #pragma unroll
         for (int i = 0; i < kE; ++i) {
-            u[i] = dt[i] * (sxB * byte_to_float(xq[i >> 2], i & 3));  // Delta_t x_t with B's scale folded in
-            y[i] = 0.0f;
+            const float xf = byte_to_float(xq[i >> 2], i & 3);
+            u[i] = dt[i] * (sxB * xf);  // Delta_t x_t with B's scale folded in
+            y[i] = Dx * xf;
             dtsum += dt[i];
         }
+        __syncthreads();  // the workgroup is done with the tile before
+        // the tile's 32 rows of B and C codes, 16 codes per thread and trip
+#pragma unroll 1
+        for (int r = ch; r < 2 * N; r += kCh) {
+            const u32x4 v = load_codes((r < N ? a.B : a.C) + ((size_t)b * N + (r & (N - 1))) * L, t0 + kE * sub, L);
+            f32x4 *dst = (r < N ? s_B : s_C) + (r & (N - 1)) * 4 * LPC + sub;
+            const float f = r < N ? 1.0f : sC;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                dst[q * LPC] = (f32x4){byte_to_float(v[q], 0) * f, byte_to_float(v[q], 1) * f, byte_to_float(v[q], 2) * f,
+                                       byte_to_float(v[q], 3) * f};
+        }
+        __syncthreads();
 #pragma unroll 1
         for (int n = 0; n < N; ++n) {
-            const float A2 = Ad[n] * kLog2e;
-            const u32x4 b0 = s_B[n][lane][0], b1 = s_B[n][lane][1];
-            const float Hc = s_carry[wave][n];
+            const float2 ah = s_AH[ch * N + n];
             float dec[kE], in[kE];
-            float h = 0.0f;
+            float h = 0.0f, P = dtsum * ah.x;
 #pragma unroll
-            for (int i = 0; i < kE; ++i) {
-                dec[i] = __builtin_amdgcn_exp2f(dt[i] * A2);
-                in[i] = mix_mul(i & 1, u[i], i < 8 ? b0[(i & 7) >> 1] : b1[(i & 7) >> 1]);
-                h = fmaf(dec[i], h, in[i]);
+            for (int i = 0; i < kE; ++i) dec[i] = dt[i] * ah.x;
+            exp2_burst(dec, P);  // P becomes the product of the lane's 16 decay factors
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 Bv = s_B[(n * 4 + q) * LPC + sub];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int i = 4 * q + k;
+                    in[i] = u[i] * Bv[k];
+                    h = fmaf(dec[i], h, in[i]);
+                }
             }
-            float P = __builtin_amdgcn_exp2f(dtsum * A2);  // the product of the lane's 16 decay factors
-            wave_scan(P, h);
+            wave_scan<LPC>(P, h);
             // the state in front of this lane's tokens: the pairs of all earlier lanes applied to the carried state
-            const float Pex = dpp_fetch<0x138, 0xf>(1.0f, P);  // wave_shr:1
-            const float hex = dpp_fetch<0x138, 0xf>(0.0f, h);
-            float hh = fmaf(Pex, Hc, hex);
-            if (lane == 63) s_carry[wave][n] = fmaf(P, Hc, h);  // the state after the tile
-            const u32x4 c0 = s_C[n][lane][0], c1 = s_C[n][lane][1];
+            float Pex = dpp_fetch<0x138, 0xf>(1.0f, P), hex = dpp_fetch<0x138, 0xf>(0.0f, h);  // wave_shr:1
+            if (LPC < 64 && sub == 0) {
+                Pex = 1.0f;
+                hex = 0.0f;
+            }
+            float hh = fmaf(Pex, ah.y, hex);
+            if (sub == LPC - 1) s_AH[ch * N + n].y = fmaf(P, ah.y, h);  // the state after the tile
 #pragma unroll
-            for (int i = 0; i < kE; ++i) {
-                hh = fmaf(dec[i], hh, in[i]);
-                y[i] = mix_fma(i & 1, i < 8 ? c0[(i & 7) >> 1] : c1[(i & 7) >> 1], hh, y[i]);
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 Cv = s_C[(n * 4 + q) * LPC + sub];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int i = 4 * q + k;
+                    hh = fmaf(dec[i], hh, in[i]);
+                    y[i] = fmaf(Cv[k], hh, y[i]);
+                }
             }
         }
-        if (live) {
-            const float Dx = (a.D ? a.D[d] : 0.0f) * sx;
-#pragma unroll
-            for (int i = 0; i < kE; ++i) y[i] = fmaf(Dx, byte_to_float(xq[i >> 2], i & 3), sC * y[i]);
+        anew(t0, row, t);
+        if (own && t < L) {
             if (a.z) {  // y * SiLU(z) on the gate codes of the lane's 16 tokens (Section 3.2), from the table
+                const u32x4 zq = load_codes(a.z + row, t, L);
 #pragma unroll
                 for (int i = 0; i < kE; ++i) y[i] *= s_silu[(zq[i >> 2] >> (8 * (i & 3))) & 255u];
             }
-            u32x4 o[2];
+            uint16_t *yp = a.y + row + t;
+            if (t + kE <= L) {
+                u32x4 o[2];
 #pragma unroll
-            for (int i = 0; i < kE; i += 2)
-                o[i >> 3][(i >> 1) & 3] = (uint32_t)f32_to_f16_bits(y[i]) | ((uint32_t)f32_to_f16_bits(y[i + 1]) << 16);
-            u32x4 *yp = reinterpret_cast<u32x4 *>(a.y + row);
-            __builtin_nontemporal_store(o[0], yp);
-            __builtin_nontemporal_store(o[1], yp + 1);
+                for (int i = 0; i < kE; i += 2)
+                    o[i >> 3][(i >> 1) & 3] = (uint32_t)f32_to_f16_bits(y[i]) | ((uint32_t)f32_to_f16_bits(y[i + 1]) << 16);
+                __builtin_nontemporal_store(o[0], reinterpret_cast<u32x4_h *>(yp));
+                __builtin_nontemporal_store(o[1], reinterpret_cast<u32x4_h *>(yp) + 1);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kE; ++i)
+                    if (t + i < L) yp[i] = f32_to_f16_bits(y[i]);
+            }
         }
     }
-    if (fin && own && lane < N) fin[((size_t)b * D + d) * N + lane] = s_carry[wave][lane];
+    if (fin) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < kCh * N; i += kThreads) {
+            const int c = blockIdx.x * kCh + i / N;
+            if (c < D) fin[((size_t)b * D + c) * N + i % N] = s_AH[i].y;
+        }
+    }
 }
 
 // Any d_state <= 64 and any seqlen: one thread per (sequence, channel), token by token.
@@ -320,6 +385,15 @@ __global__ __launch_bounds__(256) void mamba1_decode_any_kernel(SsdArgs a, const
 
 bool aligned16(const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
+template <int LPC>
+hipError_t launch_scan(const SsdArgs &a, const float *A, const float *init, float *fin, hipStream_t stream)
+{
+    constexpr int channels = kThreads / LPC;  // of a workgroup
+    const dim3 grid((unsigned)((a.s.headdim + channels - 1) / channels), (unsigned)a.s.batch);
+    hipLaunchKernelGGL(mamba1_scan_kernel<LPC>, grid, dim3(kThreads), 0, stream, a, A, init, fin);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 bool mamba1_scan_supports_any(const quamba_ssd_shape_t &s) { return s.d_state <= kMaxStates; }
@@ -327,16 +401,17 @@ bool mamba1_scan_supports_any(const quamba_ssd_shape_t &s) { return s.d_state <=
 hipError_t launch_mamba1_scan(const SsdArgs &a, const float *A, const float *init, float *fin, hipStream_t stream)
 {
     const int D = a.s.headdim;
-    const bool fast = !(a.s.flags & QUAMBA_FLAG_GENERIC_KERNEL) && a.s.d_state == 16 && a.s.seqlen % 16 == 0 &&
-                      aligned16(a.x) && aligned16(a.B) && aligned16(a.C) && aligned16(a.dt) && aligned16(a.y) &&
-                      aligned16(a.z) && aligned16(a.dt_q);
-    if (fast) {
-        const dim3 grid((unsigned)((D + kWaves - 1) / kWaves), (unsigned)a.s.batch);
-        hipLaunchKernelGGL(mamba1_scan_kernel, grid, dim3(kThreads), 0, stream, a, A, init, fin);
-    } else {
-        const dim3 grid((unsigned)((D + 63) / 64), (unsigned)a.s.batch);
-        hipLaunchKernelGGL(mamba1_scan_any_kernel, grid, dim3(64), 0, stream, a, A, init, fin);
+    if (!(a.s.flags & QUAMBA_FLAG_GENERIC_KERNEL) && a.s.d_state == 16 && a.s.seqlen >= kE) {
+        // Lanes per channel: 16 for sequences one such tile (256 tokens) holds, where more lanes would idle; else 32,
+        // whose tiles (64 KB of LDS) let two workgroups share a compute unit; 64 when there are so few channels that a
+        // workgroup per compute unit is all there is, which halves the tiles each walks.
+        if (a.s.seqlen <= 16 * kE) return launch_scan<16>(a, A, init, fin, stream);
+        if (a.s.seqlen > 32 * kE && (int64_t)a.s.batch * ((D + 7) / 8) <= compute_units())
+            return launch_scan<64>(a, A, init, fin, stream);
+        return launch_scan<32>(a, A, init, fin, stream);
     }
+    const dim3 grid((unsigned)((D + 63) / 64), (unsigned)a.s.batch);
+    hipLaunchKernelGGL(mamba1_scan_any_kernel, grid, dim3(64), 0, stream, a, A, init, fin);
     return hipGetLastError();
 }
 

@@ -58,6 +58,14 @@ def test_wave_scan_kernel_small_shapes(gpu_lib):
     _check(gpu_lib, b=3, D=64, N=16, L=16, seed=3, with_init=True, with_D=False)       # one lane of tokens
 
 
+@pytest.mark.parametrize("D,L", [(40, 15), (33, 16), (37, 17), (70, 255), (40, 256), (33, 257), (40, 511), (16, 512),
+                                 (20, 513), (9, 1023), (9, 1025), (2060, 1037)])
+def test_sequence_lengths_around_lanes_and_tiles(gpu_lib, D, L):
+    """Rows that start at any byte and end inside a lane's 16 tokens, on every tile width: one token less and more than a
+    lane (16), and than a tile of 16, 32 and 64 lanes; 2060 channels give the 32-lane kernel several tiles."""
+    _check(gpu_lib, b=2, D=D, N=16, L=L, seed=L, with_init=L % 2 == 1, with_D=L % 3 != 0)
+
+
 def test_any_shape_kernel_and_cross_check(gpu_lib):
     _check(gpu_lib, b=2, D=70, N=16, L=45, seed=4, with_init=True)                      # seqlen no multiple of 16
     _check(gpu_lib, b=1, D=33, N=24, L=64, seed=5, nranges=3)                           # other d_state
