@@ -114,7 +114,7 @@ extern "C" int quamba_ssd_prefill_gated(const quamba_ssd_shape_t *shape, const q
     const size_t need = quamba_ssd_prefill_workspace_size(shape);
     if (!workspace || workspace_bytes < need) workspace = nullptr;
     const bool mfma = use_mfma(shape, x, B, C, y, init_state, final_state) && (!gate || aligned16(gate->z));
-    if (!mfma && quamba::prefill_generic_lds_bytes(*shape) > quamba::kLdsPerCu) return QUAMBA_ESHAPE;
+    if (!mfma && !quamba::prefill_generic_supports(*shape)) return QUAMBA_ESHAPE;
 
     quamba::SsdArgs a = pack(shape, scales, x, B, C, dt, A, D, init_state, final_state, y);
     rc = apply_gate(gate, dt, &a);

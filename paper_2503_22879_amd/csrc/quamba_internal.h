@@ -214,6 +214,6 @@ bool mamba1_scan_supports_any(const quamba_ssd_shape_t &s);
 hipError_t launch_prefill_generic(const SsdArgs &a, hipStream_t stream);
 bool prefill_mfma_supports(const quamba_ssd_shape_t &s);
 hipError_t launch_prefill_mfma(const SsdArgs &a, void *workspace, hipStream_t stream);
-size_t prefill_generic_lds_bytes(const quamba_ssd_shape_t &s);
+bool prefill_generic_supports(const quamba_ssd_shape_t &s);
 
 }  // namespace quamba

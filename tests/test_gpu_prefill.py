@@ -304,6 +304,20 @@ def test_exact_integer_case(gpu_lib):
         assert np.array_equal(yg, yref) and np.array_equal(hg, href), f"flags={flags}"
 
 
+@pytest.mark.parametrize("b,L,H,P,N,G", [(1, 256, 8, 64, 16, 1), (2, 15, 6, 20, 24, 2), (1, 257, 4, 17, 128, 2),
+                                         (2, 300, 2, 7, 3, 1), (1, 1, 2, 5, 1, 1), (1, 700, 4, 33, 17, 2),
+                                         (3, 255, 3, 16, 4, 3), (1, 40, 2, 5, 1100, 1), (20, 33, 4, 70, 20, 2)])
+def test_generic_kernel_around_lanes_tiles_and_row_blocks(gpu_lib, b, L, H, P, N, G):
+    """Lengths around a lane's 16 tokens and a tile's 256, channels around a block of 16 rows, states around a staged
+    group of 16 and in fours or not, few row blocks (four lane groups per row) and many (one): 20 x 4 heads x 5 blocks."""
+    s = W.LayerShape("g", b, L, H, P, N, G, 64, min(2, H // G), min(2, P))
+    sc, prob, _ = make_problem(s, seed=L, calib_tokens=128)
+    init = np.random.default_rng(L).normal(0, 0.1, size=(b, H, P, N)).astype(np.float32)
+    yg, hg = run_prefill(gpu_lib, s, sc, prob, init_state=init)
+    yref, href, _ = oracle.ref_prefill(sc, prob["x"], prob["B"], prob["C"], prob["dt"], prob["A"], prob["D"], init)
+    check(yg, hg, yref, href, "generic")
+
+
 def test_dt_zero_and_permutation_invariance(gpu_lib):
     s = W.CONFIGS["m2_130m"].with_(seqlen=512)
     sc, prob, _ = make_problem(s, 5, calib_tokens=256)
