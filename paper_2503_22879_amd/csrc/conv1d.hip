@@ -9,6 +9,8 @@
 // code in, one 4-way int8 dot product with the channel's packed taps gives the exact integer sum.  The code is an
 // integer decided by fp32 arithmetic; the decision sequence (stated in the header) is evaluated with every operation
 // rounded on its own.
+#include <algorithm>
+
 #include "quamba_internal.h"
 
 #pragma clang fp contract(off)
@@ -19,6 +21,7 @@ namespace {
 constexpr int kSegLong = 32;   // tokens per workgroup of the vector kernel when that still gives the device enough waves,
 constexpr int kSegShort = 16;  // else this many
 constexpr int kWaveSlots = 4096;  // resident waves at this kernel's register budget (1024 SIMDs x 4)
+constexpr int kStepSeqs = 8;   // most sequences per thread of the one-token kernel
 constexpr int kAhead = 4;      // tokens whose loads are in flight
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -249,6 +252,93 @@ __global__ __launch_bounds__(64) void conv1d_q8_vec_kernel(ConvArgs a)
     }
 }
 
+// One token per sequence (generation): a thread owns 4 consecutive channels and walks kStepSeqs sequences at most, the next
+// one's four rows (three of the carried state, the token) in flight while one is computed.  A step is bound by the chain from
+// launch to store, not by a unit: four channels per thread instead of 16 shorten the serial part (set-up and arithmetic)
+// and the scales come from two memory round trips (1792 channels at batch 1: 5.6 -> 3.2 us; 10240 channels at batch 100 and 256:
+// 7.9 -> 5.1 us and 12.0 -> 8.3 us).  Same conditions as the vector kernel, 4-byte aligned tensors.
+__global__ __launch_bounds__(64) void conv1d_q8_step_kernel(ConvArgs a, int seqs)
+{
+    const int HP = a.s.nheads * a.s.headdim, GN = a.s.ngroups * a.s.d_state, Ct = HP + 2 * GN;
+    const int c0 = 4 * (blockIdx.x * 64 + threadIdx.x);
+    if (c0 >= Ct) return;
+    const int b0 = blockIdx.y * seqs, b1 = min(b0 + seqs, a.s.batch);
+    struct Rows { uint32_t r0, r1, r2, x; };  // the codes of the 4 channels, oldest token first
+    auto request = [&](int b) {
+        Rows v = {0, 0, 0, 0};
+        if (a.state_in) {
+            const int8_t *sp = a.state_in + (size_t)b * 3 * Ct + c0;
+            v.r0 = *reinterpret_cast<const uint32_t *>(sp);
+            v.r1 = *reinterpret_cast<const uint32_t *>(sp + Ct);
+            v.r2 = *reinterpret_cast<const uint32_t *>(sp + 2 * (size_t)Ct);
+        }
+        v.x = *reinterpret_cast<const uint32_t *>(a.in + (size_t)b * Ct + c0);
+        return v;
+    };
+    Rows v = request(b0);
+    const u32x4 w = *reinterpret_cast<const u32x4 *>(a.weight + (size_t)c0 * 4);
+    f32x4 bias = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (a.bias) bias = *reinterpret_cast<const f32x4 *>(a.bias + c0);
+    // 4 divides headdim and d_state: the channels share an output tensor and a head or state group
+    float inv[4];
+    int8_t *dst; int row, col;
+    if (c0 < HP) {
+        SsdArgs t;
+        t.s = a.s; t.x_scales = a.x_scales; t.head_cluster_end = a.head_cluster_end;
+        t.chan_cluster_end = a.chan_cluster_end;
+        const int h = c0 / a.s.headdim, p0 = c0 - h * a.s.headdim;
+        if (a.s.n_chan_clusters <= 4) {
+            const Ranges4 r(t, head_cell_lookup(t, h));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) inv[j] = __fdiv_rn(1.0f, r.pick(p0 + j));
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) inv[j] = __fdiv_rn(1.0f, x_scale_lookup(t, h, p0 + j));
+        }
+        dst = a.x_out; row = HP; col = c0;
+    } else {
+        const bool isB = c0 < HP + GN;
+        const int cg = c0 - HP - (isB ? 0 : GN);
+        inv[0] = inv[1] = inv[2] = inv[3] = __fdiv_rn(1.0f, (isB ? a.B_scales : a.C_scales)[cg / a.s.d_state]);
+        dst = isB ? a.B_out : a.C_out; row = GN; col = cg;
+    }
+    for (int b = b0; b < b1; ++b) {
+        const Rows c = v;
+        if (b + 1 < b1) v = request(b + 1);
+        // byte transpose: win[j] = channel j's codes, oldest in byte 0
+        const uint32_t p01 = __builtin_amdgcn_perm(c.r1, c.r0, 0x05010400u), q01 = __builtin_amdgcn_perm(c.r1, c.r0, 0x07030602u);
+        const uint32_t p23 = __builtin_amdgcn_perm(c.x, c.r2, 0x05010400u), q23 = __builtin_amdgcn_perm(c.x, c.r2, 0x07030602u);
+        const uint32_t win[4] = {__builtin_amdgcn_perm(p23, p01, 0x05040100u), __builtin_amdgcn_perm(p23, p01, 0x07060302u),
+                                 __builtin_amdgcn_perm(q23, q01, 0x05040100u), __builtin_amdgcn_perm(q23, q01, 0x07060302u)};
+        float r[4];
+        int acc[4];
+        uint32_t redo = 0;  // wave-uniform: bit j = channel j needs the exact sequence
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            acc[j] = __builtin_amdgcn_sdot4((int)win[j], (int)w[j], 0, false);
+            r[j] = __builtin_amdgcn_fmed3f(activation_over_scale_fast(acc[j], a.in_w_scale, bias[j], inv[j]), -128.0f, 127.0f);
+            redo |= (__builtin_amdgcn_ballot_w64(near_rounding_boundary(r[j])) != 0 ? 1u : 0u) << j;
+        }
+        uint32_t o = codes4(r[0], r[1], r[2], r[3]);
+        if (redo) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (redo & (1u << j)) {
+                    const uint32_t code = code1(activation_over_scale(acc[j], a.in_w_scale, bias[j], inv[j]));
+                    o = (o & ~(0xffu << (8 * j))) | (code << (8 * j));
+                }
+        }
+        // non-temporal like the vector kernel's: with plain stores the decode step behind ran 4 % slower at batch 256
+        __builtin_nontemporal_store(o, reinterpret_cast<uint32_t *>(dst + (size_t)b * row + col));
+        if (a.state_out) {
+            int8_t *sp = a.state_out + (size_t)b * 3 * Ct + c0;
+            *reinterpret_cast<uint32_t *>(sp) = c.r1;
+            *reinterpret_cast<uint32_t *>(sp + Ct) = c.r2;
+            *reinterpret_cast<uint32_t *>(sp + 2 * (size_t)Ct) = c.x;
+        }
+    }
+}
+
 // Any shape: one thread per channel, the whole sequence.
 __global__ __launch_bounds__(256) void conv1d_q8_any_kernel(ConvArgs a)
 {
@@ -307,7 +397,13 @@ int conv1d_segments(const quamba_ssd_shape_t &s)
 hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream)
 {
     const int Ct = a.s.nheads * a.s.headdim + 2 * a.s.ngroups * a.s.d_state;
-    if (vec_ok(a)) {
+    if (vec_ok(a) && a.s.seqlen == 1) {
+        // enough waves to fill the chip, then as many sequences per thread as keep it full (the set-up is shared by them)
+        const int64_t blocks = (Ct / 4 + 63) / 64;
+        const int seqs = (int)std::min<int64_t>(kStepSeqs, std::max<int64_t>(1, blocks * a.s.batch / kWaveSlots));
+        const dim3 grid((unsigned)blocks, (unsigned)((a.s.batch + seqs - 1) / seqs));
+        hipLaunchKernelGGL(conv1d_q8_step_kernel, grid, dim3(64), 0, stream, a, seqs);
+    } else if (vec_ok(a)) {
         ConvArgs v = a;
         v.seg = conv1d_segment_tokens(a.s);
         const dim3 grid((unsigned)((Ct / 16 + 63) / 64), (unsigned)conv1d_segments(a.s), (unsigned)a.s.batch);

@@ -322,7 +322,8 @@ __global__ __launch_bounds__(256) void mamba1_decode16_kernel(SsdArgs a, const f
     const bool live = (q >> 2) < D;
     const int d = live ? q >> 2 : D - 1;  // lanes past the end redo the last channel and store nothing
     // per channel, once for all sequences of the thread: scale, skip coefficient, the quarter's row of A
-    const float sx = x_scale_lookup(a, 0, d);
+    // the cell first: the batch hides the round trip, and the loads of every range's scale cost 1 % of the stream
+    const float sx = a.x_scales[cell_lookup(a, 0, d)];
     const float sxB = sx * a.B_scales[0], sC = a.C_scales[0];
     const float Dx = (a.D ? a.D[d] : 0.0f) * sx;
     const f32x4 A2 = *(reinterpret_cast<const f32x4 *>(A + (size_t)d * 16) + j) * kLog2e;

@@ -122,10 +122,76 @@ __device__ __forceinline__ int cell_lookup(const SsdArgs &a, int h, int p, int *
     return base + j;
 }
 
-// Scale of channel position p of head h (Section 4.1: one scale per cell).
+// First cell of head h's head cluster: the number of cluster ends at or below the head.  Up to 4 clusters are loaded at once
+// (the last end is the group's head count, so reading it in place of the missing ones counts nothing).
+__device__ __forceinline__ int head_cell_lookup(const SsdArgs &a, int h)
+{
+    const int hpg = a.s.nheads / a.s.ngroups;
+    const int g = h / hpg, hl = h - g * hpg;
+    const int m = a.s.n_head_clusters, n = a.s.n_chan_clusters;
+    const int32_t *end = a.head_cluster_end + g * m;
+    int i = 0;
+    if (m <= 4) {
+        const int e0 = end[0], e1 = end[min(1, m - 1)], e2 = end[min(2, m - 1)];
+        i = (hl >= e0 ? 1 : 0) + (hl >= e1 ? 1 : 0) + (hl >= e2 ? 1 : 0);
+        i = min(i, m - 1);
+    } else {
+        for (int k = 0; k < m - 1; ++k) i += hl >= end[k] ? 1 : 0;
+    }
+    return (g * m + i) * n;
+}
+
+// The channel ranges of a head cluster with up to 4 of them, in registers: ends of the first three and the four scales,
+// loaded together (a missing range repeats the last one, whose end no position reaches).
+struct Ranges4 {
+    int e0, e1, e2;
+    float s0, s1, s2, s3;
+    __device__ __forceinline__ Ranges4(const SsdArgs &a, int base)
+    {
+        const int n = a.s.n_chan_clusters;
+        const int k1 = base + min(1, n - 1), k2 = base + min(2, n - 1), k3 = base + min(3, n - 1);
+        e0 = a.chan_cluster_end[base];
+        e1 = a.chan_cluster_end[k1];
+        e2 = a.chan_cluster_end[k2];
+        s0 = a.x_scales[base];
+        s1 = a.x_scales[k1];
+        s2 = a.x_scales[k2];
+        s3 = a.x_scales[k3];
+    }
+    // (conversions to values: a choice between members would be a choice between addresses, in memory)
+    __device__ __forceinline__ float pick(int p) const
+    {
+        const float lo = p >= e0 ? float(s1) : float(s0), hi = p >= e2 ? float(s3) : float(s2);
+        return p >= e1 ? float(hi) : float(lo);
+    }
+};
+
+// Scale of channel position p of head h (Section 4.1: one scale per cell): the scale behind the last boundary at or below
+// p.  The boundaries and the scales of the head cluster are loaded together, so two memory round trips stand in front
+// of the result (the cell's index first would be a third).
 __device__ __forceinline__ float x_scale_lookup(const SsdArgs &a, int h, int p)
 {
-    return a.x_scales[cell_lookup(a, h, p)];
+    const int hpg = a.s.nheads / a.s.ngroups;
+    const int g = h / hpg, hl = h - g * hpg;
+    const int m = a.s.n_head_clusters, n = a.s.n_chan_clusters;
+    int i = 0;
+    for (int k = 0; k < m - 1; ++k) i += hl >= a.head_cluster_end[g * m + k] ? 1 : 0;
+    const int base = (g * m + i) * n;
+    float scale = a.x_scales[base];
+    for (int k = 0; k < n - 1; ++k) {
+        const int end = a.chan_cluster_end[base + k];
+        const float next = a.x_scales[base + k + 1];
+        scale = p >= end ? next : scale;
+    }
+    return scale;
+}
+
+// The same with the loads of the two steps unrolled, for calls that wait for the result: loops of unknown length are not
+// unrolled into loads that fly together.
+__device__ __forceinline__ float x_scale_lookup_wide(const SsdArgs &a, int h, int p)
+{
+    if (a.s.n_chan_clusters > 4) return x_scale_lookup(a, h, p);
+    return Ranges4(a, head_cell_lookup(a, h)).pick(p);
 }
 
 // fp32 -> fp16 bits, round to nearest even.

@@ -100,6 +100,18 @@ def test_decode_step_updates_state_in_place(gpu_lib):
         _, state = _check(gpu_lib, s, sc, inp, state, alias=True)
 
 
+@pytest.mark.parametrize("batch,H,P,N,m,n,state", [(1, 24, 64, 128, 4, 4, True), (3, 6, 16, 16, 3, 6, True),
+                                                   (5, 5, 48, 32, 1, 1, False), (1030, 8, 64, 128, 2, 3, True)])
+def test_one_token_kernel(gpu_lib, batch, H, P, N, m, n, state):
+    """One token per sequence: channel counts that fill no whole wave, cluster counts on both sides of the four that are
+    looked up at once, no carried state, several sequences per thread (1030 x 768 channels) with a ragged last group."""
+    s = W.LayerShape("step", batch, 1, H, P, N, 1, 16, m, n)
+    sc, _, _ = make_problem(s.with_(batch=1, seqlen=8), seed=13, calib_tokens=128)
+    Ct = H * P + 2 * N
+    st = np.random.default_rng(13).integers(-128, 128, size=(batch, 3, Ct), dtype=np.int8) if state else None
+    _check(gpu_lib, s, sc, make_conv_inputs(s, seed=13), st, alias=state)
+
+
 def test_no_bias_no_state_output(gpu_lib):
     s = W.CONFIGS["m2_130m"].with_(batch=1, seqlen=40)
     sc, _, _ = make_problem(s.with_(seqlen=8), seed=4, calib_tokens=256)

@@ -61,6 +61,14 @@ def test_decode_other_shapes(gpu_lib, P, N, H, G):
     _run_steps(gpu_lib, s, steps=3, seed=6, batch=2)
 
 
+@pytest.mark.parametrize("batch,P,N,m,n", [(6600, 40, 16, 1, 1), (3, 64, 128, 5, 6), (2, 40, 128, 1, 1), (1, 16, 64, 4, 4)])
+def test_decode_passes_and_cluster_counts(gpu_lib, batch, P, N, m, n):
+    """So many workgroups of a ragged head that each takes the whole head (33000 pairs), one pass per workgroup with a
+    ragged last one, and cluster counts on both sides of the four that are looked up at once."""
+    s = W.LayerShape("t", batch, 1, 5, P, N, 1, 64, m, n)
+    _run_steps(gpu_lib, s, steps=2, seed=8, batch=batch)
+
+
 def test_decode_full_batch(gpu_lib):
     """configs[4] at full size (batch 256, 1 GiB state), 32 steps: y of every sequence against the fp64 oracle at every
     step, the whole state at the end (the oracle's fp64 state is 2 GiB of host memory)."""
