@@ -117,15 +117,20 @@ __device__ __forceinline__ Tables stage_tables(const SsdArgs &a, const float *st
 // covers 64/(N/16) rows per load instruction and keeps ROWS such loads in flight.  FULL: headdim is a multiple of the
 // rows one trip of the workgroup covers (no clamping or masking of rows).
 //
-// A workgroup owns one head and every gridDim.y-th slice of the batch; the grid is sized so that all workgroups are
-// resident at once (no tail of partly filled rounds).  Everything but the codes goes through LDS: once per workgroup
-// the head's scale rows, their reciprocals and the cell of every row; once per slice dt, the decay, the decayed scale
-// rows, x as fp32 codes, s_B B and C as fp32 codes.  The loop over the sequences of a slice then issues nothing but
-// the 16-byte code loads (one sequence ahead) and stores, so that the dependent look-ups, divisions and conversions
-// are paid once per workgroup or slice instead of once per 8 KB of state.  Four workgroups of four waves share a
-// compute unit (one wave of each per SIMD), which needs at most 128 vector registers per lane: hence the second
-// launch bound.
-template <int N, int ROWS, bool FULL>
+// A workgroup owns one head and every gridDim.y-th sequence of the batch, which it takes in slices of seqs_per_block
+// sequences; the grid is sized so that all workgroups are resident at once (no tail of partly filled rounds).  The
+// sequences are dealt singly: shares then differ by one sequence at most, and the workgroups of a head still move through
+// the batch side by side (a contiguous share each: 2 % slower at 100 sequences of 128 heads, without a gate).
+// Everything but the codes goes through LDS: once per workgroup the head's scale rows, their reciprocals and the cell of
+// every row; once per slice dt, the decay, the decayed scale rows, x as fp32 codes, s_B B and C as fp32 codes and, of a
+// gated call, SiLU(z).  The loop over the sequences of a slice then issues nothing but the 16-byte code loads (one
+// sequence ahead) and stores, so that the dependent look-ups, divisions and conversions are paid once per workgroup or
+// slice instead of once per 8 KB of state.  Four workgroups of four waves share a compute unit (one wave of each per
+// SIMD), which needs at most 128 vector registers per lane: hence the second launch bound.
+// The step (with the convolution in front), before (slices of a fixed size dealt in turn, z read behind the loop) and now:
+// 100 gated sequences of 128 heads 56.8 -> 51.3 us, 256 gated 121.9 -> 114.2, 30 gated 27.7 -> 24.0, 150 ungated of 80
+// heads 61.8 -> 59.6, 200 ungated of 24 heads 38.1 -> 30.1 (the codes alone, in and out of memory: 34, 87, 10, 32, 13).
+template <int N, int ROWS, bool FULL, bool GATED>
 __global__ __launch_bounds__(kThreads, 4) void decode_q8_vec_kernel(SsdArgs a, const float *state_scales,
                                                                     int8_t *state_q, int seqs_per_block)
 {
@@ -147,6 +152,7 @@ __global__ __launch_bounds__(kThreads, 4) void decode_q8_vec_kernel(SsdArgs a, c
     float *s_sd = s_Cf + (size_t)seqs_per_block * NP;  // [nb][n cells][NP]  decay * scale: the decayed scale rows
     const int nc = a.s.n_chan_clusters;
     float *s_inv = s_sd + (size_t)seqs_per_block * nc * NP;  // [n cells][NP]  reciprocal scale rows
+    float *s_gate = s_inv + nc * NP;                         // [nb][P]  SiLU(z) of every output (gated calls only)
     const float sB = a.B_scales[g], sC = a.C_scales[g];
     const float Dh = a.D ? a.D[h] : 0.0f;
     // The side inputs of a slice (step sizes, x, B and C codes) are requested one slice ahead and wait in registers
@@ -158,33 +164,33 @@ __global__ __launch_bounds__(kThreads, 4) void decode_q8_vec_kernel(SsdArgs a, c
     static_assert(kThreads % kQuads == 0, "whole rows of B per round of threads");
     struct Side {
         float dt;
-        uint32_t bw, cw, xw[1];
+        uint32_t bw, cw, xz;
     };
     const bool x_quads = (P & 3) == 0;
-    auto request_side = [&](int slice, Side &sd) {
+    const bool z_quads = GATED && x_quads && reinterpret_cast<uintptr_t>(a.z) % 4 == 0;
+    // the workgroup's sequences are blockIdx.y + i * gridDim.y; slice s covers i in [s seqs_per_block, (s + 1) seqs_per_block)
+    const int Y = (int)gridDim.y;
+    const int share = (a.s.batch - (int)blockIdx.y + Y - 1) / Y;  // at least 1: the grid has at most one row per sequence
+    // dword e of a slice's x codes, followed (z_quads) by its z codes: nq dwords each
+    auto quad = [&](int bb0, int nq, int e) {
+        const int xq = P >> 2, i = e < nq ? e : e - nq;
+        const int bb = i / xq, pq = i - bb * xq;
+        return *reinterpret_cast<const uint32_t *>((e < nq ? a.x : a.z) + ((size_t)(bb0 + bb * Y) * H + h) * P + 4 * pq);
+    };
+    auto request_side = [&](int i0, Side &sd) {
+        const int bb0 = (int)blockIdx.y + i0 * Y, nbs = min(seqs_per_block, share - i0);
         // a thread index the compiler cannot carry across slices: what is derived from it is recomputed here instead
         // of occupying registers throughout the main loop
         int tix = (int)threadIdx.x;
         asm volatile("" : "+v"(tix));
         const int side_bb = tix / kQuads, side_q = tix % kQuads;
-        const int bb0 = slice * seqs_per_block, nbs = min(seqs_per_block, a.s.batch - bb0);
-        if (tix < nbs) sd.dt = a.dt[(size_t)(bb0 + tix) * H + h];
+        if (tix < nbs) sd.dt = a.dt[(size_t)(bb0 + tix * Y) * H + h];
         if (side_bb < nbs) {
-            const size_t bg = (size_t)(bb0 + side_bb) * G + g;
+            const size_t bg = (size_t)(bb0 + side_bb * Y) * G + g;
             sd.bw = *reinterpret_cast<const uint32_t *>(a.B + bg * N + 4 * side_q);
             sd.cw = *reinterpret_cast<const uint32_t *>(a.C + bg * N + 4 * side_q);
         }
-        if (x_quads) {
-            const int xq = P >> 2;
-#pragma unroll
-            for (int k = 0; k < 1; ++k) {
-                const int e = tix + k * kThreads;
-                if (e < nbs * xq) {
-                    const int bb = e / xq, pq = e - bb * xq;
-                    sd.xw[k] = *reinterpret_cast<const uint32_t *>(a.x + ((size_t)(bb0 + bb) * H + h) * P + 4 * pq);
-                }
-            }
-        }
+        if (x_quads && tix < nbs * (P >> 2) * (z_quads ? 2 : 1)) sd.xz = quad(bb0, nbs * (P >> 2), tix);
     };
     auto stage_side = [&](int b_begin, int nb, const Side &sd) {
         // a thread index the compiler cannot carry across slices: what is derived from it is recomputed here instead
@@ -206,34 +212,35 @@ __global__ __launch_bounds__(kThreads, 4) void decode_q8_vec_kernel(SsdArgs a, c
             *reinterpret_cast<f32x4 *>(s_Bv + side_bb * NP + padded_pos(4 * side_q)) = bv;
             *reinterpret_cast<f32x4 *>(s_Cf + side_bb * NP + padded_pos(4 * side_q)) = cv;
         }
+        // x codes as fp32 and, of a gated call, SiLU(z) of every output, from the dwords requested ahead; what one dword
+        // per thread does not cover, or cannot (odd headdim, unaligned z), is read here
+        const int nq = nb * (P >> 2);
         if (x_quads) {
-            const int xq = P >> 2;
+            for (int e = tix; e < (z_quads ? 2 * nq : nq); e += kThreads) {
+                const uint32_t w = e == tix ? sd.xz : quad(b_begin, nq, e);
+                f32x4 v;
+                if (GATED && e >= nq) {
 #pragma unroll
-            for (int k = 0; k < 1; ++k) {
-                const int e = tix + k * kThreads;
-                if (e < nb * xq) {
-                    f32x4 xv4;
+                    for (int i = 0; i < 4; ++i) v[i] = silu_of_code(a.z_scale, (int)(int8_t)(w >> (8 * i)));
+                    *reinterpret_cast<f32x4 *>(s_gate + 4 * (e - nq)) = v;
+                } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) xv4[i] = code_to_float(sd.xw[k], i);
-                    *reinterpret_cast<f32x4 *>(s_xf + 4 * e) = xv4;
+                    for (int i = 0; i < 4; ++i) v[i] = code_to_float(w, i);
+                    *reinterpret_cast<f32x4 *>(s_xf + 4 * e) = v;
                 }
             }
-            // what one dword per thread does not cover (headdim * sequences above 4 * kThreads) is read here
-            for (int e = tix + kThreads; e < nb * xq; e += kThreads) {
-                const int bb = e / xq, pq = e - bb * xq;
-                const uint32_t w = *reinterpret_cast<const uint32_t *>(a.x + ((size_t)(b_begin + bb) * H + h) * P + 4 * pq);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) s_xf[4 * e + i] = code_to_float(w, i);
-            }
-        } else {
-            for (int e = tix; e < nb * P; e += kThreads) {
-                const int bb = e / P, p = e - bb * P;
-                s_xf[e] = (float)a.x[((size_t)(b_begin + bb) * H + h) * P + p];
-            }
         }
+        auto at = [&](int e) {
+            const int bb = e / P;
+            return ((size_t)(b_begin + bb * Y) * H + h) * P + e - bb * P;
+        };
+        if (!x_quads)
+            for (int e = tix; e < nb * P; e += kThreads) s_xf[e] = (float)a.x[at(e)];
+        if (GATED && !z_quads)
+            for (int e = tix; e < nb * P; e += kThreads) s_gate[e] = silu_of_code(a.z_scale, a.z[at(e)]);
     };
     Side side = {};
-    request_side((int)blockIdx.y, side);  // the grid has at most one row of workgroups per slice
+    request_side(0, side);
 
     const Tables t = stage_tables(a, state_scales, 0, h, lds, false);  // xv holds s_x of every row; ends in a barrier
     for (int i = threadIdx.x; i < nc * N; i += kThreads) {
@@ -241,11 +248,8 @@ __global__ __launch_bounds__(kThreads, 4) void decode_q8_vec_kernel(SsdArgs a, c
         s_inv[c * NP + padded_pos(n)] = t.inv_tab[i];
     }
 
-    // the workgroup's slices of the batch: slice s covers sequences [s seqs_per_block, (s + 1) seqs_per_block)
-    const int nslices = (a.s.batch + seqs_per_block - 1) / seqs_per_block;
-    for (int slice = blockIdx.y; slice < nslices; slice += gridDim.y) {
-    const int b_begin = slice * seqs_per_block, b_end = min(b_begin + seqs_per_block, a.s.batch);
-    const int nb = b_end - b_begin;
+    for (int i0 = 0; i0 < share; i0 += seqs_per_block) {
+    const int b_begin = (int)blockIdx.y + i0 * Y, nb = min(seqs_per_block, share - i0);
     stage_side(b_begin, nb, side);
     __syncthreads();
     for (int bb = 0; bb < nb; ++bb) {
@@ -256,7 +260,7 @@ __global__ __launch_bounds__(kThreads, 4) void decode_q8_vec_kernel(SsdArgs a, c
         }
     }
     __syncthreads();
-    if (slice + (int)gridDim.y < nslices) request_side(slice + (int)gridDim.y, side);
+    if (i0 + seqs_per_block < share) request_side(i0 + seqs_per_block, side);
 
     for (int p0 = wave * RPI * ROWS; p0 < P; p0 += kWaves * RPI * ROWS) {
         // per row of this trip: its scale rows and its x scale (the same for every sequence)
@@ -284,7 +288,7 @@ __global__ __launch_bounds__(kThreads, 4) void decode_q8_vec_kernel(SsdArgs a, c
         u32x4 nxt[ROWS], out[ROWS];
         uint16_t yout[ROWS];
         auto store_results = [&](int bb) {
-            const size_t bh = (size_t)(b_begin + bb) * H + h;
+            const size_t bh = (size_t)(b_begin + bb * Y) * H + h;
 #pragma unroll
             for (int i = 0; i < ROWS; ++i)
                 if (FULL || p0 + i * RPI + sub < P)
@@ -298,14 +302,13 @@ __global__ __launch_bounds__(kThreads, 4) void decode_q8_vec_kernel(SsdArgs a, c
         };
         load(b_begin, nxt);
         for (int bb = 0; bb < nb; ++bb) {
-            const int b = b_begin + bb;
+            const int b = b_begin + bb * Y;
             u32x4 cur[ROWS];
 #pragma unroll
             for (int i = 0; i < ROWS; ++i) cur[i] = nxt[i];
-            if (bb + 1 < nb) load(b + 1, nxt);
+            if (bb + 1 < nb) load(b + Y, nxt);
             if (bb > 0) store_results(bb - 1);
             const float dt = s_dt[bb];
-            const size_t bh = (size_t)b * H + h;
             float acc[ROWS], xv[ROWS], dtx[ROWS];
 #pragma unroll
             for (int i = 0; i < ROWS; ++i) {
@@ -340,7 +343,9 @@ __global__ __launch_bounds__(kThreads, 4) void decode_q8_vec_kernel(SsdArgs a, c
                 const int p = p0 + i * RPI + sub;
                 if (j == 0 && (FULL || p < P))
                 {
-                    const float gate = a.z ? silu_of_code(a.z_scale, a.z[bh * P + p]) : 1.0f;  // y * SiLU(z)
+                    int row = prow[i];
+                    if (GATED) asm volatile("" : "+v"(row));  // not an address carried through the loop: registers are short
+                    const float gate = GATED ? s_gate[bb * P + row] : 1.0f;  // y * SiLU(z)
                     yout[i] = f32_to_f16_bits(__builtin_fmaf(Dh, xv[i], sC * acc[i]) * gate);
                 }
             }
@@ -426,35 +431,43 @@ hipError_t launch(dim3 grid, const SsdArgs &a, const float *ss, int8_t *q, size_
     return hipGetLastError();
 }
 
-// Sequences per workgroup of the vector kernel: enough workgroups to fill the chip several times over (>= 4096 when
-// the batch allows), at most kMaxSeqs, the per-sequence arrays within 64 KB of LDS, a grid y dimension <= 65535.
-// Returns 0 when no choice fits (the caller then takes the any-shape kernel).
-size_t vec_lds_bytes(const quamba_ssd_shape_t &s, int seqs);
-int seqs_per_block(const quamba_ssd_shape_t &s)
+// Launch shape of the vector kernel: shares of the batch (the grid's y dimension) and sequences per slice of a share.
+// 4 waves of up to 128 registers each allow 4 workgroups per compute unit (one wave of each per SIMD); a slice takes as
+// many sequences as leave LDS for them (staging is paid per slice), and a share's slices are of even size.
+struct VecPlan {
+    int shares, seqs;  // seqs == 0: the shape does not fit, the caller takes the any-shape kernel
+};
+size_t vec_lds_bytes(const quamba_ssd_shape_t &s, int seqs, bool gated);
+VecPlan vec_plan(const quamba_ssd_shape_t &s, bool gated)
 {
-    const int64_t pairs = (int64_t)s.batch * s.nheads;
-    int n = (int)std::min<int64_t>(kMaxSeqs, std::max<int64_t>(1, pairs / 4096));
-    if (s.d_state >= 4) n = std::min(n, std::max(1, kThreads / (s.d_state / 4)));  // one round of threads covers the slice's B rows
-    while (n > 1 && vec_lds_bytes(s, n) > 64 * 1024) --n;
-    if (vec_lds_bytes(s, n) > kLdsPerCu || (s.batch + n - 1) / n > 65535) return 0;
-    return n;
+    int cap = kMaxSeqs;
+    if (s.d_state >= 4) cap = std::min(cap, std::max(1, kThreads / (s.d_state / 4)));  // one round of threads covers the slice's B rows
+    while (cap > 1 && vec_lds_bytes(s, cap, gated) > kLdsPerCu / 4) --cap;
+    const size_t lds = vec_lds_bytes(s, cap, gated);
+    if (lds > kLdsPerCu) return {0, 0};
+    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(4, kLdsPerCu / lds));
+    const int want = (compute_units() * per_cu + s.nheads - 1) / s.nheads;
+    VecPlan plan;
+    plan.shares = std::max(1, std::min({(int)s.batch, want, 65535}));
+    const int share = (s.batch + plan.shares - 1) / plan.shares;
+    plan.seqs = (share + (share + cap - 1) / cap - 1) / ((share + cap - 1) / cap);
+    return plan;
 }
 
 template <int N>
-hipError_t launch_vec(const SsdArgs &a, const float *ss, int8_t *q, int spb, hipStream_t stream)
+hipError_t launch_vec(const SsdArgs &a, const float *ss, int8_t *q, VecPlan plan, hipStream_t stream)
 {
     constexpr int RPI = 64 / (N / 16);
-    const int P = a.s.headdim;
-    const size_t lds = vec_lds_bytes(a.s, spb);
-    // all workgroups resident at once: 4 waves of up to 128 registers each allow 4 workgroups per compute unit
-    // (one wave of each per SIMD), the LDS footprint may allow fewer
-    const int nslices = (a.s.batch + spb - 1) / spb;
-    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(4, kLdsPerCu / lds));
-    const int want_y = (compute_units() * per_cu + a.s.nheads - 1) / a.s.nheads;
-    const dim3 grid((unsigned)a.s.nheads, (unsigned)std::max(1, std::min(nslices, want_y)));
-    if (P % (kWaves * RPI * 2) == 0) return launch<decode_q8_vec_kernel<N, 2, true>>(grid, a, ss, q, lds, stream, spb);
-    if (P % (kWaves * RPI) == 0) return launch<decode_q8_vec_kernel<N, 1, true>>(grid, a, ss, q, lds, stream, spb);
-    return launch<decode_q8_vec_kernel<N, 1, false>>(grid, a, ss, q, lds, stream, spb);
+    const int P = a.s.headdim, spb = plan.seqs;
+    const size_t lds = vec_lds_bytes(a.s, spb, a.z != nullptr);
+    const dim3 grid((unsigned)a.s.nheads, (unsigned)plan.shares);
+    auto pick = [&](auto gated) {
+        constexpr bool GATED = decltype(gated)::value;
+        if (P % (kWaves * RPI * 2) == 0) return launch<decode_q8_vec_kernel<N, 2, true, GATED>>(grid, a, ss, q, lds, stream, spb);
+        if (P % (kWaves * RPI) == 0) return launch<decode_q8_vec_kernel<N, 1, true, GATED>>(grid, a, ss, q, lds, stream, spb);
+        return launch<decode_q8_vec_kernel<N, 1, false, GATED>>(grid, a, ss, q, lds, stream, spb);
+    };
+    return a.z ? pick(std::true_type{}) : pick(std::false_type{});
 }
 
 }  // namespace
@@ -467,12 +480,12 @@ size_t decode_q8_lds_bytes(const quamba_ssd_shape_t &s)
 namespace {
 
 // LDS of the vector kernel with `seqs` sequences per workgroup: the head's tables plus the per-sequence arrays.
-size_t vec_lds_bytes(const quamba_ssd_shape_t &s, int seqs)
+size_t vec_lds_bytes(const quamba_ssd_shape_t &s, int seqs, bool gated)
 {
     const size_t xf = ((size_t)seqs * s.headdim + 3) & ~(size_t)3;
     const size_t np = (size_t)padded_row(s.d_state);
     return decode_q8_lds_bytes(s) +
-           sizeof(float) * (2 * kMaxSeqs + xf + (2 + (size_t)s.n_chan_clusters) * seqs * np + s.n_chan_clusters * np);
+           sizeof(float) * (2 * kMaxSeqs + (gated ? 2 : 1) * xf + (2 + (size_t)s.n_chan_clusters) * seqs * np + s.n_chan_clusters * np);
 }
 
 }  // namespace
@@ -482,14 +495,14 @@ hipError_t launch_decode_q8(const SsdArgs &a, const float *state_scales, int8_t 
     // the vector kernel reads the codes 16 bytes at a time and x, B and C 4 bytes at a time
     const bool al = reinterpret_cast<uintptr_t>(state_q) % 16 == 0 && reinterpret_cast<uintptr_t>(a.x) % 4 == 0 &&
                     reinterpret_cast<uintptr_t>(a.B) % 4 == 0 && reinterpret_cast<uintptr_t>(a.C) % 4 == 0;
-    const int spb = seqs_per_block(a.s);
-    if (al && spb > 0) {
+    const VecPlan plan = vec_plan(a.s, a.z != nullptr);
+    if (al && plan.seqs > 0) {
         switch (a.s.d_state) {
-            case 16: return launch_vec<16>(a, state_scales, state_q, spb, stream);
-            case 32: return launch_vec<32>(a, state_scales, state_q, spb, stream);
-            case 64: return launch_vec<64>(a, state_scales, state_q, spb, stream);
-            case 128: return launch_vec<128>(a, state_scales, state_q, spb, stream);
-            case 256: return launch_vec<256>(a, state_scales, state_q, spb, stream);
+            case 16: return launch_vec<16>(a, state_scales, state_q, plan, stream);
+            case 32: return launch_vec<32>(a, state_scales, state_q, plan, stream);
+            case 64: return launch_vec<64>(a, state_scales, state_q, plan, stream);
+            case 128: return launch_vec<128>(a, state_scales, state_q, plan, stream);
+            case 256: return launch_vec<256>(a, state_scales, state_q, plan, stream);
             default: break;
         }
     }

@@ -163,3 +163,36 @@ def test_decode_q8_gated(gpu_lib, P, N, H, G):
     with pytest.raises(q.QuambaError):
         q.quamba_ssd_decode_step_q8(to_shape(q, s), dsc, ssd, d["x"], d["B"], d["C"], d["dt"], A, D, qs, y,
                                     gate=_gate(q, g, True, True))
+
+
+@pytest.mark.parametrize("batch,H,P,N,G,off", [
+    (1, 128, 64, 128, 8, 0),      # a single sequence
+    (37, 128, 64, 128, 8, 0),     # shares of 5 and 4 sequences, x and z codes of a slice within one dword per thread
+    (37, 128, 64, 64, 8, 1),      # z off the 4-byte grid: read where it is staged
+    (70, 128, 128, 16, 8, 0),     # more x and z dwords in a slice than threads
+    (41, 128, 6, 16, 1, 0),       # headdim not a multiple of 4: x and z byte by byte
+    (27, 256, 40, 32, 8, 0),      # rows past headdim in a trip
+])
+def test_decode_q8_gated_slices(gpu_lib, batch, H, P, N, G, off):
+    """Workgroups with several sequences, uneven shares of the batch and every way the gate's codes are staged: codes
+    bit for bit, y within the fp16 tolerance (the gate is one more fp32 factor on it)."""
+    import torch
+    q = gpu_lib
+    s = W.LayerShape("t", batch, 1, H, P, N, G, 64, 2, 3)
+    sc, prob, r = make_problem(s.with_(batch=1, seqlen=4), 26, calib_tokens=256)
+    ss, codes, _ = make_state_cache(s, sc, r, 26, batch=batch)
+    dsc = q.DeviceScales(host_scales(q, sc))
+    qs = torch.from_numpy(codes.copy()).cuda()
+    y = torch.full((batch, H, P), float("nan"), dtype=torch.float16, device="cuda")
+    inp = make_decode_inputs(s, sc, r, 26, 0)
+    g = make_gate_inputs(s, r, 26, decode=True, step=0)
+    d = {n: torch.from_numpy(v).cuda() for n, v in inp.items()}
+    z = torch.zeros(batch * H * P + 4, dtype=torch.int8, device="cuda")[off:off + batch * H * P].view(batch, H, P)
+    z.copy_(torch.from_numpy(g["z"]))
+    q.quamba_ssd_decode_step_q8(to_shape(q, s), dsc, torch.from_numpy(ss).cuda(), d["x"], d["B"], d["C"], d["dt"],
+                                torch.from_numpy(prob["A"]).cuda(), torch.from_numpy(prob["D"]).cuda(), qs, y,
+                                gate=q.Gate(z=z, z_scale=g["z_scale"]))
+    yref = oracle.ref_decode_step_q8(sc, ss, inp["x"], inp["B"], inp["C"], inp["dt"], prob["A"], prob["D"], codes)
+    yref = oracle.silu_gate(yref, g["z"], g["z_scale"])
+    assert np.array_equal(qs.cpu().numpy(), codes)
+    assert np.abs(y.cpu().numpy().astype(np.float64) - yref).max() <= Y_TOL * np.abs(yref).max()
