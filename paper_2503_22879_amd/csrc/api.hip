@@ -323,7 +323,7 @@ extern "C" int quamba_conv1d_q8(const quamba_ssd_shape_t *shape, const quamba_ss
     rc = check_shape(shape, true);
     if (rc != QUAMBA_OK) return rc;
     const int64_t Ct = (int64_t)shape->nheads * shape->headdim + 2LL * shape->ngroups * shape->d_state;
-    if (Ct > 0x7fffffffLL / 4 || shape->batch > 65535 || quamba::conv1d_segments(*shape) > 65535) return QUAMBA_ESHAPE;
+    if (Ct > 0x7fffffffLL / 4 || shape->batch > 65535 || shape->seqlen > quamba::kConvMaxTokens) return QUAMBA_ESHAPE;
     if (!(in_w_scale > 0.0f) || !std::isfinite(in_w_scale)) return QUAMBA_EINVAL;
     if (conv_state_in && conv_state_in == conv_state_out && shape->seqlen > 16) return QUAMBA_EINVAL;
     quamba::ConvArgs a;

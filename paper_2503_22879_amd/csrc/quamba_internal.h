@@ -272,7 +272,8 @@ struct ConvArgs {
     int seg;                  // tokens per workgroup (set by the launcher)
 };
 hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream);
-int conv1d_segments(const quamba_ssd_shape_t &s);  // workgroups along one sequence (1: state_in may equal state_out)
+constexpr int kMaxGridY = 65535;                    // of a launch
+constexpr int kConvMaxTokens = 32 * kMaxGridY;  // longest sequence of the convolution
 // Mamba1 selective scan: shape has nheads = ngroups = 1, headdim = channels; A is [channels, d_state]
 hipError_t launch_mamba1_scan(const SsdArgs &a, const float *A, const float *init, float *fin, hipStream_t stream);
 hipError_t launch_mamba1_decode(const SsdArgs &a, const float *A, hipStream_t stream);

@@ -112,6 +112,28 @@ def test_one_token_kernel(gpu_lib, batch, H, P, N, m, n, state):
     _check(gpu_lib, s, sc, make_conv_inputs(s, seed=13), st, alias=state)
 
 
+@pytest.mark.parametrize("batch,L,H,P,N,m,n", [(2, 2, 24, 64, 128, 4, 4),      # shorter than the halo
+                                               (1, 45, 6, 16, 16, 3, 6),       # six ranges; segments of 4, a last one of 1
+                                               (9, 291, 6, 64, 128, 2, 3),     # ... a last one of 3
+                                               (15, 900, 6, 64, 16, 2, 3),     # segments of 8, the last of 4
+                                               (64, 3085, 4, 16, 16, 2, 2)])   # segments of 16, the last of 13
+def test_segments_and_carried_state(gpu_lib, batch, L, H, P, N, m, n):
+    """Every segment length of the vector kernel with ragged last segments, from a carried state."""
+    s = W.LayerShape("seg", batch, L, H, P, N, 1, 16, m, n)
+    sc, _, _ = make_problem(s.with_(batch=1, seqlen=8), seed=14, calib_tokens=128)
+    st = np.random.default_rng(14).integers(-128, 128, size=(batch, 3, H * P + 2 * N), dtype=np.int8)
+    _check(gpu_lib, s, sc, make_conv_inputs(s, seed=14), st)
+
+
+@pytest.mark.parametrize("L", [2, 7, 16])
+def test_short_sequence_with_one_buffer_as_both_states(gpu_lib, L):
+    s = W.CONFIGS["m2_130m"].with_(batch=3, seqlen=L)
+    sc, _, _ = make_problem(s.with_(batch=1, seqlen=8), seed=15, calib_tokens=128)
+    Ct = s.nheads * s.headdim + 2 * s.ngroups * s.d_state
+    st = np.random.default_rng(15).integers(-128, 128, size=(3, 3, Ct), dtype=np.int8)
+    _check(gpu_lib, s, sc, make_conv_inputs(s, seed=15), st, alias=True)
+
+
 def test_no_bias_no_state_output(gpu_lib):
     s = W.CONFIGS["m2_130m"].with_(batch=1, seqlen=40)
     sc, _, _ = make_problem(s.with_(seqlen=8), seed=4, calib_tokens=256)
