@@ -18,7 +18,6 @@
 namespace quamba {
 namespace {
 
-constexpr int kThreads = 512;        // of the scan's workgroups
 constexpr int kE = 16;              // tokens per lane
 constexpr float kLog2e = 1.44269504088896340736f;
 constexpr int kDecodeSeqs = 4;      // sequences per thread and trip of the decode step
@@ -112,22 +111,23 @@ __device__ __forceinline__ u32x4 load_codes(const int8_t *row, int t, int L)
     return v;
 }
 
-// N = 16 states, seqlen >= 16.  grid = (channels / (8 64 / LPC), batch); LPC lanes share a channel (64, 32 or 16), so a wave
-// holds 64 / LPC channels.  The loop over states stays rolled: the 16 tokens of a lane already give every instruction 16
-// independent copies, and unrolling further only costs registers.  B and C are staged as fp32 (converted once per workgroup
+// N = 16 states, seqlen >= 16.  grid = (channels / (kThreads / LPC), batch); LPC lanes share a channel (64, 32 or 16), so a
+// wave holds 64 / LPC channels.  B and C of NS states are staged at a time: 8 with workgroups of 256 threads, whose 34 KB of
+// LDS let four of them share a compute unit, all 16 with 512.  The loop over states stays rolled: the 16 tokens of a lane
+// already give every instruction 16 independent copies, and unrolling further only costs registers.  B and C are staged as fp32 (converted once per workgroup
 // instead of once per channel): plain fp32 multiplies and multiply-adds of two waves can issue together, the
 // mixed-precision ones that take fp16 operands cannot.  LDS rows are [state][quarter of a lane's tokens][lane], so that a lane's
 // four 16-byte reads are consecutive across the lanes.
 // C is staged times its scale and the skip term starts the output's sum, so that the sum is y.
 // Measured at 4 x 4096 tokens, 5120 channels: 312 us (393 with fp16 operands, tiles of 1024
-// tokens and the exponentials between the other instructions); 1003 tokens of one sequence: 37 us (3010 us with one thread
-// per channel, which is what a length that is no multiple of 16 took before).
-template <int LPC>
+// tokens and the exponentials between the other instructions); 1003 tokens of one sequence: 32 us (36.5 with workgroups of
+// 512 threads, 3010 with one thread per channel, which is what a length that is no multiple of 16 took before).
+template <int LPC, int kThreads, int NS>
 __global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, const float *A, const float *init, float *fin)
 {
     constexpr int N = 16, kTile = LPC * kE, kCh = kThreads / LPC;  // channels of the workgroup
     // separate arrays, so that the compiler sees that the state's write does not touch the C read behind it
-    __shared__ f32x4 s_B[N * 4 * LPC], s_C[N * 4 * LPC];  // [state][quarter][lane]
+    __shared__ f32x4 s_B[NS * 4 * LPC], s_C[NS * 4 * LPC];  // [state][quarter][lane]
     __shared__ float2 s_AH[kCh * N];                      // [channel][state]: A log2(e), the state before the tile
     __shared__ float s_silu[256];                         // SiLU(z_scale * code), by the gate code's byte
     const int D = a.s.headdim, L = a.s.seqlen;
@@ -197,54 +197,57 @@ __global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, con
             y[i] = Dx * xf;
             dtsum += dt[i];
         }
-        __syncthreads();  // the workgroup is done with the tile before
-        // the tile's 32 rows of B and C codes, 16 codes per thread and trip
 #pragma unroll 1
-        for (int r = ch; r < 2 * N; r += kCh) {
-            const u32x4 v = load_codes((r < N ? a.B : a.C) + ((size_t)b * N + (r & (N - 1))) * L, t0 + kE * sub, L);
-            f32x4 *dst = (r < N ? s_B : s_C) + (r & (N - 1)) * 4 * LPC + sub;
-            const float f = r < N ? 1.0f : sC;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                dst[q * LPC] = (f32x4){byte_to_float(v[q], 0) * f, byte_to_float(v[q], 1) * f, byte_to_float(v[q], 2) * f,
-                                       byte_to_float(v[q], 3) * f};
-        }
-        __syncthreads();
+        for (int n0 = 0; n0 < N; n0 += NS) {
+            __syncthreads();  // the workgroup is done with the states before
+            // the tile's NS rows each of B and C codes, 16 codes per thread and trip
 #pragma unroll 1
-        for (int n = 0; n < N; ++n) {
-            const float2 ah = s_AH[ch * N + n];
-            float dec[kE], in[kE];
-            float h = 0.0f, P = dtsum * ah.x;
+            for (int r = ch; r < 2 * NS; r += kCh) {
+                const u32x4 v = load_codes((r < NS ? a.B : a.C) + ((size_t)b * N + n0 + (r & (NS - 1))) * L, t0 + kE * sub, L);
+                f32x4 *dst = (r < NS ? s_B : s_C) + (r & (NS - 1)) * 4 * LPC + sub;
+                const float f = r < NS ? 1.0f : sC;
 #pragma unroll
-            for (int i = 0; i < kE; ++i) dec[i] = dt[i] * ah.x;
-            exp2_burst(dec, P);  // P becomes the product of the lane's 16 decay factors
+                for (int q = 0; q < 4; ++q)
+                    dst[q * LPC] = (f32x4){byte_to_float(v[q], 0) * f, byte_to_float(v[q], 1) * f, byte_to_float(v[q], 2) * f,
+                                           byte_to_float(v[q], 3) * f};
+            }
+            __syncthreads();
+#pragma unroll 1
+            for (int n = 0; n < NS; ++n) {
+                const float2 ah = s_AH[ch * N + n0 + n];
+                float dec[kE], in[kE];
+                float h = 0.0f, P = dtsum * ah.x;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 Bv = s_B[(n * 4 + q) * LPC + sub];
+                for (int i = 0; i < kE; ++i) dec[i] = dt[i] * ah.x;
+                exp2_burst(dec, P);  // P becomes the product of the lane's 16 decay factors
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int i = 4 * q + k;
-                    in[i] = u[i] * Bv[k];
-                    h = fmaf(dec[i], h, in[i]);
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 Bv = s_B[(n * 4 + q) * LPC + sub];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const int i = 4 * q + k;
+                        in[i] = u[i] * Bv[k];
+                        h = fmaf(dec[i], h, in[i]);
+                    }
                 }
-            }
-            wave_scan<LPC>(P, h);
-            // the state in front of this lane's tokens: the pairs of all earlier lanes applied to the carried state
-            float Pex = dpp_fetch<0x138, 0xf>(1.0f, P), hex = dpp_fetch<0x138, 0xf>(0.0f, h);  // wave_shr:1
-            if (LPC < 64 && sub == 0) {
-                Pex = 1.0f;
-                hex = 0.0f;
-            }
-            float hh = fmaf(Pex, ah.y, hex);
-            if (sub == LPC - 1) s_AH[ch * N + n].y = fmaf(P, ah.y, h);  // the state after the tile
+                wave_scan<LPC>(P, h);
+                // the state in front of this lane's tokens: the pairs of all earlier lanes applied to the carried state
+                float Pex = dpp_fetch<0x138, 0xf>(1.0f, P), hex = dpp_fetch<0x138, 0xf>(0.0f, h);  // wave_shr:1
+                if (LPC < 64 && sub == 0) {
+                    Pex = 1.0f;
+                    hex = 0.0f;
+                }
+                float hh = fmaf(Pex, ah.y, hex);
+                if (sub == LPC - 1) s_AH[ch * N + n0 + n].y = fmaf(P, ah.y, h);  // the state after the tile
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 Cv = s_C[(n * 4 + q) * LPC + sub];
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 Cv = s_C[(n * 4 + q) * LPC + sub];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int i = 4 * q + k;
-                    hh = fmaf(dec[i], hh, in[i]);
-                    y[i] = fmaf(Cv[k], hh, y[i]);
+                    for (int k = 0; k < 4; ++k) {
+                        const int i = 4 * q + k;
+                        hh = fmaf(dec[i], hh, in[i]);
+                        y[i] = fmaf(Cv[k], hh, y[i]);
+                    }
                 }
             }
         }
@@ -386,12 +389,12 @@ __global__ __launch_bounds__(256) void mamba1_decode_any_kernel(SsdArgs a, const
 
 bool aligned16(const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 
-template <int LPC>
+template <int LPC, int kThreads, int NS>
 hipError_t launch_scan(const SsdArgs &a, const float *A, const float *init, float *fin, hipStream_t stream)
 {
     constexpr int channels = kThreads / LPC;  // of a workgroup
     const dim3 grid((unsigned)((a.s.headdim + channels - 1) / channels), (unsigned)a.s.batch);
-    hipLaunchKernelGGL(mamba1_scan_kernel<LPC>, grid, dim3(kThreads), 0, stream, a, A, init, fin);
+    hipLaunchKernelGGL((mamba1_scan_kernel<LPC, kThreads, NS>), grid, dim3(kThreads), 0, stream, a, A, init, fin);
     return hipGetLastError();
 }
 
@@ -403,13 +406,25 @@ hipError_t launch_mamba1_scan(const SsdArgs &a, const float *A, const float *ini
 {
     const int D = a.s.headdim;
     if (!(a.s.flags & QUAMBA_FLAG_GENERIC_KERNEL) && a.s.d_state == 16 && a.s.seqlen >= kE) {
-        // Lanes per channel: 16 for sequences one such tile (256 tokens) holds, where more lanes would idle; else 32,
-        // whose tiles (64 KB of LDS) let two workgroups share a compute unit; 64 when there are so few channels that a
-        // workgroup per compute unit is all there is, which halves the tiles each walks.
-        if (a.s.seqlen <= 16 * kE) return launch_scan<16>(a, A, init, fin, stream);
-        if (a.s.seqlen > 32 * kE && (int64_t)a.s.batch * ((D + 7) / 8) <= compute_units())
-            return launch_scan<64>(a, A, init, fin, stream);
-        return launch_scan<32>(a, A, init, fin, stream);
+        // Lanes per channel: 16 for sequences one such tile (256 tokens) holds, where more lanes would idle; 64 when there
+        // are so few channels that a workgroup per compute unit is all there is, which halves the tiles each walks.
+        if (a.s.seqlen <= 16 * kE) return launch_scan<16, 512, 16>(a, A, init, fin, stream);
+        const int cus = compute_units();
+        auto per_cu = [&](int ch) { return ((int64_t)a.s.batch * ((D + ch - 1) / ch) + cus - 1) / cus * ch; };
+        if (a.s.seqlen > 32 * kE && per_cu(8) <= 8) return launch_scan<64, 512, 16>(a, A, init, fin, stream);
+        // Else the time follows the channels of the fullest compute unit times the tokens of their tiles (about 1 us per
+        // 1000, from 1003 tokens up).  16 channels of 32 lanes in a workgroup; 8 where that spreads the channels more evenly
+        // (5120 channels, one sequence: 24 instead of 32 on a unit; 1003 tokens 36.5 -> 32.2 us, 4096 117 -> 105 us; where it
+        // does not, its staging costs up to 5 %: 4 x 1003 tokens 82 against 84 us); 32 of 16 lanes where their
+        // tiles of 256 tokens leave less over (3 x 700 tokens of 5120 channels 63.5 -> 47.7 us).  A difference below an
+        // eighth does not pay.
+        auto cost = [&](int ch, int tile) { return per_cu(ch) * ((a.s.seqlen + (int64_t)tile - 1) / tile * tile); };
+        const int64_t c16 = cost(16, 32 * kE), c8 = cost(8, 32 * kE), c32 = cost(32, 16 * kE);
+        if (9 * std::min(c8, c32) <= 8 * c16) {
+            if (c8 <= c32) return launch_scan<32, 256, 8>(a, A, init, fin, stream);
+            return launch_scan<16, 512, 16>(a, A, init, fin, stream);
+        }
+        return launch_scan<32, 512, 16>(a, A, init, fin, stream);
     }
     const dim3 grid((unsigned)((D + 63) / 64), (unsigned)a.s.batch);
     hipLaunchKernelGGL(mamba1_scan_any_kernel, grid, dim3(64), 0, stream, a, A, init, fin);

@@ -59,10 +59,11 @@ def test_wave_scan_kernel_small_shapes(gpu_lib):
 
 
 @pytest.mark.parametrize("D,L", [(40, 15), (33, 16), (37, 17), (70, 255), (40, 256), (33, 257), (40, 511), (16, 512),
-                                 (20, 513), (9, 1023), (9, 1025), (2060, 1037)])
+                                 (20, 513), (9, 1023), (9, 1025), (2060, 1037), (8177, 700)])
 def test_sequence_lengths_around_lanes_and_tiles(gpu_lib, D, L):
     """Rows that start at any byte and end inside a lane's 16 tokens, on every tile width: one token less and more than a
-    lane (16), and than a tile of 16, 32 and 64 lanes; 2060 channels give the 32-lane kernel several tiles."""
+    lane (16), and than a tile of 16, 32 and 64 lanes; 2060 channels give the 32-lane kernel with the smaller
+    workgroups several tiles, 8177 of 700 tokens the 16-lane kernel."""
     _check(gpu_lib, b=2, D=D, N=16, L=L, seed=L, with_init=L % 2 == 1, with_D=L % 3 != 0)
 
 
