@@ -19,6 +19,7 @@ namespace quamba {
 namespace {
 
 constexpr int kWaveSlots = 4096;  // waves that keep the device full (1024 SIMDs x 4)
+constexpr int kSegWide = 32;     // tokens per workgroup of the 16-channel kernel
 constexpr int kStepSeqs = 8;   // most sequences per thread of the one-token kernel
 constexpr int kAhead = 4;      // tokens whose loads are in flight
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -172,7 +173,7 @@ __device__ __forceinline__ uint32_t codes_of_windows(const uint32_t (&win)[4], c
 // a segment of a.seg tokens, the loads of the next 4 in flight; grid = (channel blocks of 64 x 4, segments, batch); one
 // wave per workgroup, no LDS, no barrier.  Bound by the vector ALU where there are enough waves, by the chain from launch to
 // store where there are few.  4 channels keep the kernel at 41 registers, so that 8 waves share a SIMD, and the chain
-// short; 16 channels (116 registers, 4 waves, a quarter of the waves) and 8 were slower at every size: 16 tokens of
+// short; 16 channels (116 registers, 4 waves, a quarter of the waves) and 8 were slower below 4 of the former's waves per SIMD: 16 tokens of
 // 1792 channels 16.8 (16 channels) / 5.6 (8) / 3.6 us (4), 1531 tokens of 10240 channels 22.0 / 17.5 / 14.6 us, 8 x 2048
 // tokens of 5376 channels 67.9 / 59.5 / 55.6 us.
 __global__ __launch_bounds__(64) void conv1d_q8_vec_kernel(ConvArgs a)
@@ -229,6 +230,149 @@ __global__ __launch_bounds__(64) void conv1d_q8_vec_kernel(ConvArgs a)
             const uint32_t lo = __builtin_amdgcn_perm(win[1], win[0], 0x0c0c0400u + 0x00000101u * (k + 1));
             const uint32_t hi = __builtin_amdgcn_perm(win[3], win[2], 0x04000c0cu + 0x01010000u * (k + 1));
             *reinterpret_cast<uint32_t *>(a.state_out + ((size_t)b * 3 + k) * Ct + c0) = lo | hi;
+        }
+    }
+}
+
+// The vector kernel with 16 consecutive channels per thread, for launches that give it 4 waves per SIMD even so: the loads,
+// addresses and stores of a token are shared by four times the channels.  Same conditions; grid = (channel blocks of 64 x 16,
+// segments, batch); one wave per workgroup, no LDS, no barrier.
+__global__ __launch_bounds__(64) void conv1d_q8_wide_kernel(ConvArgs a)
+{
+    const int HP = a.s.nheads * a.s.headdim, GN = a.s.ngroups * a.s.d_state, Ct = HP + 2 * GN;
+    const int c0 = 16 * (blockIdx.x * 64 + threadIdx.x);
+    if (c0 >= Ct) return;
+    const int b = blockIdx.z, L = a.s.seqlen;
+    const int t0 = blockIdx.y * a.seg, t1 = min(t0 + a.seg, L);
+
+    // per-channel constants: packed taps, bias, reciprocal output scale (one correctly rounded division each)
+    uint32_t w[16];
+    float bias[16], inv[16];
+    int8_t *dst; int row, col;
+    {
+        const u32x4 *wp = reinterpret_cast<const u32x4 *>(a.weight + (size_t)c0 * 4);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const u32x4 v = wp[q];
+            w[4 * q] = v[0]; w[4 * q + 1] = v[1]; w[4 * q + 2] = v[2]; w[4 * q + 3] = v[3];
+        }
+        if (a.bias) {
+            const f32x4 *bp = reinterpret_cast<const f32x4 *>(a.bias + c0);  // c0 is a multiple of 16: 64-byte aligned
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 v = bp[q];
+                bias[4 * q] = v[0]; bias[4 * q + 1] = v[1]; bias[4 * q + 2] = v[2]; bias[4 * q + 3] = v[3];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) bias[j] = 0.0f;
+        }
+        // The 16 channels share one output tensor and one head or state group (16 divides headdim and d_state), so
+        // one lookup finds the first channel's cell; the channel ranges of a head are ascending, so the following
+        // channels only step to the next range when they pass its end.
+        if (c0 < HP) {
+            SsdArgs t;
+            t.s = a.s; t.x_scales = a.x_scales; t.head_cluster_end = a.head_cluster_end;
+            t.chan_cluster_end = a.chan_cluster_end;
+            const int h = c0 / a.s.headdim, p0 = c0 - h * a.s.headdim;
+            int base;
+            int cell = cell_lookup(t, h, p0, &base);
+            const int last = base + a.s.n_chan_clusters - 1;
+            int end = cell < last ? a.chan_cluster_end[cell] : a.s.headdim;
+            float iv = __fdiv_rn(1.0f, a.x_scales[cell]);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                while (p0 + j >= end) {  // at most n - 1 steps over the 16 channels together
+                    ++cell;
+                    end = cell < last ? a.chan_cluster_end[cell] : a.s.headdim;
+                    iv = __fdiv_rn(1.0f, a.x_scales[cell]);
+                }
+                inv[j] = iv;
+            }
+            dst = a.x_out; row = HP; col = c0;
+        } else {
+            const bool isB = c0 < HP + GN;
+            const int cg = c0 - HP - (isB ? 0 : GN);
+            const float iv = __fdiv_rn(1.0f, (isB ? a.B_scales : a.C_scales)[cg / a.s.d_state]);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) inv[j] = iv;
+            dst = isB ? a.B_out : a.C_out; row = GN; col = cg;
+        }
+    }
+
+    // the window before the segment: tokens t0-3 .. t0-1 in bytes 1..3 (byte 0 is shifted out by the first token)
+    uint32_t win[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) win[j] = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int8_t *rp = token_row(a, b, t0 - 3 + k, Ct);
+        u32x4 v = {0, 0, 0, 0};
+        if (rp) v = *reinterpret_cast<const u32x4 *>(rp + c0);
+#pragma unroll
+        for (int j = 0; j < 16; ++j)  // bytes: win.b1, win.b2, win.b3, new.b(j & 3)
+            win[j] = __builtin_amdgcn_perm(v[j >> 2], win[j], 0x04030201u + ((uint32_t)(j & 3) << 24));
+    }
+
+    const int8_t *ip = a.in + ((size_t)b * L + t0) * Ct + c0;
+    u32x4 nx[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+        nx[u] = t0 + u < t1 ? __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(ip + (size_t)u * Ct))
+                            : (u32x4){0, 0, 0, 0};
+    int8_t *op = dst + ((size_t)b * L + t0) * row + col;
+
+    for (int t = t0; t < t1; t += kAhead) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (t + u >= t1) break;
+            const u32x4 cur = nx[u];
+            if (t + u + kAhead < t1)
+                nx[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(ip + (size_t)(t - t0 + u + kAhead) * Ct));
+            // Codes from the fast evaluation wherever it provably rounds like the exact sequence; channels in which any
+            // lane sits too close to a rounding boundary (about 1 % of the channel-tokens of a wave) are redone with
+            // the exact sequence below, so every code is the exact sequence's code.
+            u32x4 o;
+            uint32_t redo = 0;  // wave-uniform: bit j = channel j needs the exact sequence
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float r[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int j = 4 * q + i;
+                    win[j] = __builtin_amdgcn_perm(cur[q], win[j], 0x04030201u + ((uint32_t)i << 24));
+                    const int acc = __builtin_amdgcn_sdot4((int)win[j], (int)w[j], 0, false);
+                    r[i] = __builtin_amdgcn_fmed3f(activation_over_scale_fast(acc, a.in_w_scale, bias[j], inv[j]),
+                                                   -128.0f, 127.0f);
+                    redo |= (__builtin_amdgcn_ballot_w64(near_rounding_boundary(r[i])) != 0 ? 1u : 0u) << j;
+                }
+                o[q] = codes4(r[0], r[1], r[2], r[3]);
+            }
+            if (redo) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    if (redo & (1u << j)) {
+                        const int acc = __builtin_amdgcn_sdot4((int)win[j], (int)w[j], 0, false);
+                        const uint32_t code = code1(activation_over_scale(acc, a.in_w_scale, bias[j], inv[j]));
+                        o[j >> 2] = (o[j >> 2] & ~(0xffu << (8 * (j & 3)))) | (code << (8 * (j & 3)));
+                    }
+            }
+            __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(op + (size_t)(t - t0 + u) * row));
+        }
+    }
+
+    // the state to carry on: the last three input tokens = bytes 1..3 of the windows after the last token
+    if (a.state_out && t1 == L) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            u32x4 o;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t lo = __builtin_amdgcn_perm(win[4 * q + 1], win[4 * q], 0x0c0c0400u + 0x00000101u * (k + 1));
+                const uint32_t hi = __builtin_amdgcn_perm(win[4 * q + 3], win[4 * q + 2], 0x04000c0cu + 0x01010000u * (k + 1));
+                o[q] = lo | hi;
+            }
+            *reinterpret_cast<u32x4 *>(a.state_out + ((size_t)b * 3 + k) * Ct + c0) = o;
         }
     }
 }
@@ -337,6 +481,14 @@ int conv1d_segment_tokens(const quamba_ssd_shape_t &s, bool same_state)
     return s.seqlen <= 16 * kMaxGridY ? 16 : 32;
 }
 
+// Waves of the 16-channel kernel; 0 for sequences shorter than a segment (among them all that may have one buffer as both
+// states, which has to be one segment).
+static int64_t wide_waves(const quamba_ssd_shape_t &s)
+{
+    const int64_t Ct = (int64_t)s.nheads * s.headdim + 2LL * s.ngroups * s.d_state;
+    return s.seqlen < kSegWide ? 0 : (Ct / 16 + 63) / 64 * s.batch * (((int64_t)s.seqlen + kSegWide - 1) / kSegWide);
+}
+
 hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream)
 {
     const int Ct = a.s.nheads * a.s.headdim + 2 * a.s.ngroups * a.s.d_state;
@@ -346,6 +498,15 @@ hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream)
         const int seqs = (int)std::min<int64_t>(kStepSeqs, std::max<int64_t>(1, blocks * a.s.batch / kWaveSlots));
         const dim3 grid((unsigned)blocks, (unsigned)((a.s.batch + seqs - 1) / seqs));
         hipLaunchKernelGGL(conv1d_q8_step_kernel, grid, dim3(64), 0, stream, a, seqs);
+    } else if (vec_ok(a) && wide_waves(a.s) >= kWaveSlots) {
+        // Enough waves for the 16-channel kernel.  4 / 16 channels: 4 x 4096 tokens of 10240 channels 108.2 / 101.5 us, 16 x
+        // 4096 of 1792 77.4 / 74.4, 6 x 4096 of 5376 87.5 / 88.9; with fewer waves 2 x 4096 of 10240 57.4 / 62.0, 1 x 4096
+        // 31.4 / 44.1.
+        ConvArgs v = a;
+        v.seg = kSegWide;
+        const dim3 grid((unsigned)((Ct / 16 + 63) / 64), (unsigned)((a.s.seqlen + (int64_t)v.seg - 1) / v.seg),
+                        (unsigned)a.s.batch);
+        hipLaunchKernelGGL(conv1d_q8_wide_kernel, grid, dim3(64), 0, stream, v);
     } else if (vec_ok(a)) {
         ConvArgs v = a;
         v.seg = conv1d_segment_tokens(a.s, a.state_in && a.state_in == a.state_out);
