@@ -213,3 +213,30 @@ def test_decode_steps_with_side_inputs(gpu_lib):
             ey = np.abs(y.cpu().numpy().astype(np.float64) - yref).max() / np.abs(yref).max()
             es = np.abs(st.cpu().numpy().astype(np.float64) - st_ref).max() / np.abs(st_ref).max()
             assert ey <= Y_TOL and es <= S_TOL, (t, ey, es)
+
+
+def test_step_size_codes_to_fp32_accuracy(gpu_lib):
+    """Every step-size code once, A = 0 and one non-zero token per channel: a state is dt x B.  dt is within three units of
+    2^-24 (its own two roundings, exponential and logarithm of one unit), and three products follow: 6 * 2^-24 of the
+    value.  The pre-activations code / 16 are exact and run from -8 to 8; both the wave-scan kernel and the one-thread kernel."""
+    import torch
+    q = gpu_lib
+    D, N, L = 256, 16, 37
+    one = np.ones(1, np.float32)
+    sc = q.DeviceScales(q.HostScales(np.full(4, 0.37, np.float32), np.array([1], np.int32),
+                                     np.array([64, 128, 192, 256], np.int32), 0.11 * one, one))
+    x = np.zeros((1, D, L), np.int8)
+    x[0, np.arange(D), np.arange(D) % L] = 101
+    codes = np.ascontiguousarray(np.broadcast_to(np.arange(-128, 128, dtype=np.int8)[None, :, None], (1, D, L)))
+    B = np.full((1, N, L), 93, np.int8)
+    v = np.arange(-128, 128) / 16.0
+    want = np.logaddexp(0.0, v) * (101 * np.float64(np.float32(0.37))) * (93 * np.float64(np.float32(0.11)))
+    for flags in (0, q.FLAG_GENERIC_KERNEL):
+        fin = torch.full((1, D, N), float("nan"), device="cuda")
+        q.quamba_mamba1_scan(_shape(q, 1, D, N, L, 4, flags), sc, torch.from_numpy(x).cuda(), torch.from_numpy(B).cuda(),
+                             torch.from_numpy(B).cuda(), None, torch.zeros(D, N, device="cuda"), None,
+                             torch.empty((1, D, L), dtype=torch.float16, device="cuda"), final_state=fin,
+                             gate=q.Gate(dt_q=torch.from_numpy(codes).cuda(), dt_scale=1.0 / 16))
+        err = np.abs(fin.cpu().numpy().astype(np.float64)[0] / want[:, None] - 1.0).max()
+        print(f"step sizes, flags {flags}: {err / 2 ** -24:.2f} units of 2^-24")
+        assert err <= 6 * 2.0 ** -24
