@@ -9,6 +9,8 @@
 // of them while it adds to y: 4 multiply-adds per (token, state), no exponential.  What bounds it at the sizes it is for
 // (small models) is the latency of that chain, not a unit.  One workgroup per head that walked the tokens one after the
 // other took 5.4 us per token (8 heads of 64 channels, 16 states, 256 tokens: 1388 us, now 8.0 us).
+#include <type_traits>
+
 #include "quamba_internal.h"
 
 namespace quamba {
@@ -162,6 +164,8 @@ __global__ __launch_bounds__(kTile * SG) void prefill_generic_kernel(SsdArgs a, 
         const float Pin = Pl[3] * row_earlier<8>(1.0f, Pl[3]);  // over all tokens up to the lane's last
         const float Pex = row_earlier<1>(1.0f, Pin);            // in front of its first
 
+        const int last = (nt - 1) / kE;  // the lane with the tile's last token: its replay ends with the state to carry on
+
         for (int n0 = 0; n0 < N; n0 += kNG) {
             const int ns = min(kNG, N - n0);
             if (n0) {  // the first group is staged with the tile's tokens
@@ -169,37 +173,57 @@ __global__ __launch_bounds__(kTile * SG) void prefill_generic_kernel(SsdArgs a, 
                 stage_bc(n0, ns);
                 __syncthreads();
             }
-#pragma unroll 2
-            for (int n = grp; n < ns; n += SG) {
-                const float Hc = own ? s_H[row * N + n0 + n] : 0.0f;
-                float in[kE];
-                float hv = 0.0f;
+            // K states at a time, n and the following ones of the lane group: their chains run side by side
+            auto states = [&](int n, auto count) {
+                constexpr int K = decltype(count)::value;
+                float in[K][kE], Hc[K], hh[K];
+                bool finite = true;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 Bv = *reinterpret_cast<const f32x4 *>(s_B + (n * 4 + q) * kBPitch + 4 * sub);
+                for (int j = 0; j < K; ++j) {
+                    Hc[j] = own ? s_H[row * N + n0 + n + j * SG] : 0.0f;
+                    float hv = 0.0f;
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        in[4 * q + k] = u[4 * q + k] * Bv[k];
-                        hv = fmaf(dec[4 * q + k], hv, in[4 * q + k]);
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 Bv = *reinterpret_cast<const f32x4 *>(s_B + ((n + j * SG) * 4 + q) * kBPitch + 4 * sub);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            in[j][4 * q + k] = u[4 * q + k] * Bv[k];
+                            hv = fmaf(dec[4 * q + k], hv, in[j][4 * q + k]);
+                        }
+                    }
+                    hv = fmaf(row_earlier<1>(0.0f, hv), Pl[0], hv);
+                    hv = fmaf(row_earlier<2>(0.0f, hv), Pl[1], hv);
+                    hv = fmaf(row_earlier<4>(0.0f, hv), Pl[2], hv);
+                    hv = fmaf(row_earlier<8>(0.0f, hv), Pl[3], hv);
+                    hh[j] = fmaf(Pex, Hc[j], row_earlier<1>(0.0f, hv));
+                }
+#pragma unroll
+                for (int j = 0; j < K; ++j) finite = scan_is_finite(hh[j]) && finite;
+                if (!finite) {
+#pragma unroll
+                    for (int j = 0; j < K; ++j) hh[j] = walk_lanes<kLanes>(Hc[j], dec, in[j]);
+                }
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 Cv = *reinterpret_cast<const f32x4 *>(s_C + ((n + j * SG) * 4 + q) * kBPitch + 4 * sub);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            hh[j] = fmaf(dec[4 * q + k], hh[j], in[j][4 * q + k]);
+                            y[4 * q + k] = fmaf(Cv[k], hh[j], y[4 * q + k]);
+                        }
                     }
                 }
-                hv = fmaf(row_earlier<1>(0.0f, hv), Pl[0], hv);
-                hv = fmaf(row_earlier<2>(0.0f, hv), Pl[1], hv);
-                hv = fmaf(row_earlier<4>(0.0f, hv), Pl[2], hv);
-                hv = fmaf(row_earlier<8>(0.0f, hv), Pl[3], hv);
-                float hh = fmaf(Pex, Hc, row_earlier<1>(0.0f, hv));
-                const float Hn = fmaf(Pin, Hc, hv);  // stored last: the compiler keeps LDS reads behind LDS writes
+                // stored last: the compiler keeps LDS reads behind LDS writes
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 Cv = *reinterpret_cast<const f32x4 *>(s_C + (n * 4 + q) * kBPitch + 4 * sub);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        hh = fmaf(dec[4 * q + k], hh, in[4 * q + k]);
-                        y[4 * q + k] = fmaf(Cv[k], hh, y[4 * q + k]);
-                    }
-                }
-                if (own && sub == kLanes - 1) s_H[row * N + n0 + n] = Hn;
-            }
+                for (int j = 0; j < K; ++j)
+                    if (own && sub == last) s_H[row * N + n0 + n + j * SG] = hh[j];
+            };
+            int n = grp;
+            if (SG == 1)  // (two at a time take 160 registers, which 16 waves do not have)
+                for (; n + SG < ns; n += 2 * SG) states(n, std::integral_constant<int, 2>{});
+            for (; n < ns; n += SG) states(n, std::integral_constant<int, 1>{});
         }
         // outputs: the groups' sums of a row meet (two exchanges that leave a group with 4 of the 16 tokens), then through
         // LDS to (token, row) order

@@ -246,6 +246,33 @@ __device__ __forceinline__ float group_sum(float v)
     return v;
 }
 
+// Scans of h <- dec h + in over groups of LANES lanes with E consecutive tokens each: is h, the scan's state in front of each
+// lane's tokens, what the recurrence gives?  The scan's products of decays do not give it where a number is not finite: an
+// infinite state times a product that underflows, or a product that overflows times a state of zero, is no number,
+// while step by step the state stays infinite, or zero.  The answer is the wave's.
+__device__ __forceinline__ bool scan_is_finite(float h)
+{
+    return __builtin_expect(__builtin_amdgcn_ballot_w64(!(__builtin_fabsf(h) < __builtin_inff())) == 0, 1);
+}
+
+// The state in front of each lane's tokens, the group's lanes taking their tokens one after the other from `carried`, the
+// state in front of the first.
+template <int LANES, int E>
+__device__ __forceinline__ float walk_lanes(float carried, const float (&dec)[E], const float (&in)[E])
+{
+    const int lane = __lane_id();
+    float mine = carried;
+#pragma unroll 1
+    for (int l = 0; l < LANES; ++l) {
+        float e = carried;
+#pragma unroll
+        for (int i = 0; i < E; ++i) e = fmaf(dec[i], e, in[i]);
+        mine = (lane & (LANES - 1)) == l ? carried : mine;
+        carried = __shfl(e, (lane & ~(LANES - 1)) | l, 64);
+    }
+    return mine;
+}
+
 hipError_t launch_decode(const SsdArgs &a, hipStream_t stream);
 // 8-bit cached state (Appendix E): the step on int8 codes in place, and the quantizer of an fp32 state (a.state)
 hipError_t launch_decode_q8(const SsdArgs &a, const float *state_scales, int8_t *state_q, hipStream_t stream);

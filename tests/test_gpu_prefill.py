@@ -318,6 +318,32 @@ def test_generic_kernel_around_lanes_tiles_and_row_blocks(gpu_lib, b, L, H, P, N
     check(yg, hg, yref, href, "generic")
 
 
+@pytest.mark.parametrize("b,L,H,P,N", [(1, 300, 2, 20, 24), (1, 37, 3, 16, 5), (40, 33, 4, 40, 5)])
+def test_generic_kernel_keeps_infinite_and_zero_states(gpu_lib, b, L, H, P, N):
+    """An infinite state stays infinite as long as no single decay is zero, also where the product over several tokens
+    underflows (exp(-8) per token); a state of zero without inputs stays zero where that product overflows (A > 0)."""
+    s = W.LayerShape("inf", b, L, H, P, N, 1, 64, 1, 2)
+    sc, prob, _ = make_problem(s, seed=L, calib_tokens=128)
+    prob["dt"] = np.full_like(prob["dt"], 0.5)
+    prob["A"] = np.full_like(prob["A"], -16.0)
+    prob["C"][prob["C"] == 0] = 1      # (0 times infinity is no number, in the recurrence as well)
+    init = np.random.default_rng(L).normal(0, 0.1, size=(b, H, P, N)).astype(np.float32)
+    init[:, 1, 3, 2], init[:, 0, 13, 0] = np.inf, -np.inf
+    yg, hg = run_prefill(gpu_lib, s, sc, prob, init_state=init)
+    with np.errstate(invalid="ignore"):
+        yref, href, _ = oracle.ref_prefill(sc, prob["x"], prob["B"], prob["C"], prob["dt"], prob["A"], prob["D"], init)
+    for got, ref in ((yg, yref), (hg, href)):
+        assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref))
+        assert not np.isnan(got).any()
+    fin = lambda a: np.where(np.isfinite(a), a, 0.0)
+    check(fin(yg), fin(hg), fin(yref), fin(href), "infinite states")
+
+    prob["A"] = np.full_like(prob["A"], 16.0)
+    prob["x"] = np.zeros_like(prob["x"])
+    yg, hg = run_prefill(gpu_lib, s, sc, prob)
+    assert not yg.any() and not hg.any()
+
+
 def test_dt_zero_and_permutation_invariance(gpu_lib):
     s = W.CONFIGS["m2_130m"].with_(seqlen=512)
     sc, prob, _ = make_problem(s, 5, calib_tokens=256)
