@@ -238,14 +238,19 @@ __global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, con
                     }
                 }
                 wave_scan<LPC>(P, h);
-                // the state in front of this lane's tokens: the pairs of all earlier lanes applied to the carried state
-                float Pex = dpp_fetch<0x138, 0xf>(1.0f, P), hex = dpp_fetch<0x138, 0xf>(0.0f, h);  // wave_shr:1
-                if (LPC < 64 && sub == 0) {
-                    Pex = 1.0f;
-                    hex = 0.0f;
+                // the state behind this lane's tokens, the pairs up to it applied to the carried state, is the state in
+                // front of the next lane's; behind the last lane's it is the state after the tile
+                const float end = fmaf(P, ah.y, h);
+                float hh = dpp_fetch<0x138, 0xf>(ah.y, end);  // wave_shr:1
+                if (LPC < 64 && sub == 0) hh = ah.y;
+                float carry = end;
+                if (!scan_is_finite(end)) {
+                    hh = walk_lanes<LPC>(ah.y, dec, in);
+                    carry = hh;
+#pragma unroll
+                    for (int i = 0; i < kE; ++i) carry = fmaf(dec[i], carry, in[i]);
                 }
-                float hh = fmaf(Pex, ah.y, hex);
-                if (sub == LPC - 1) s_AH[ch * N + n0 + n].y = fmaf(P, ah.y, h);  // the state after the tile
+                if (sub == LPC - 1) s_AH[ch * N + n0 + n].y = carry;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const f32x4 Cv = s_C[(n * 4 + q) * LPC + sub];

@@ -240,3 +240,28 @@ def test_step_size_codes_to_fp32_accuracy(gpu_lib):
         err = np.abs(fin.cpu().numpy().astype(np.float64)[0] / want[:, None] - 1.0).max()
         print(f"step sizes, flags {flags}: {err / 2 ** -24:.2f} units of 2^-24")
         assert err <= 6 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("D,L", [(40, 37), (40, 300), (9, 1100), (2060, 1037), (8177, 700)])
+def test_infinite_and_zero_states(gpu_lib, D, L):
+    """On every width of the scan: an infinite state stays infinite as long as no single decay is zero, also where the
+    product over several tokens underflows (exp(-8) per token); a state of zero without inputs stays zero where that
+    product overflows (A > 0)."""
+    b, N = 2, 16
+    sc, p = make_mamba1_problem(b, D, N, L, seed=L)
+    p = dict(p, dt=np.full_like(p["dt"], 0.5), A=np.full_like(p["A"], -16.0), C=np.where(p["C"] == 0, np.int8(1), p["C"]))
+    init = np.random.default_rng(L).normal(0, 0.1, size=(b, D, N)).astype(np.float32)
+    init[0, 3, 2], init[1, D - 1, 15] = np.inf, -np.inf
+    pick = np.unique(np.r_[0:9, D - 9:D])
+    yref, sref = oracle.ref_mamba1_scan(p["xs"][pick], sc.B_scales[0], sc.C_scales[0], p["x"][:, pick], p["B"], p["C"],
+                                        p["dt"][:, pick], p["A"][pick], p["D"][pick], init[:, pick])
+    y, fin = _run(gpu_lib, sc, p, b, D, N, L, init=init)
+    for got, ref, tol in ((y[:, pick], yref, Y_TOL), (fin[:, pick], sref, S_TOL)):
+        inf = np.isinf(ref)
+        assert inf.any() and np.array_equal(got[inf], ref[inf])
+        assert np.abs(got[~inf] - ref[~inf]).max() <= tol * np.abs(ref[~inf]).max()
+    assert np.isinf(fin).sum() == 2 and not np.isnan(fin).any() and not np.isnan(y).any()
+
+    p = dict(p, A=-p["A"], x=np.zeros_like(p["x"]))
+    y, fin = _run(gpu_lib, sc, p, b, D, N, L)
+    assert not y.any() and not fin.any()
