@@ -150,7 +150,10 @@ __global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, con
 
     for (int i = threadIdx.x; i < kCh * N; i += kThreads) {
         const int c = min((int)blockIdx.x * kCh + i / N, D - 1), n = i % N;
-        s_AH[i] = make_float2(A[(size_t)c * N + n] * kLog2e, init ? init[((size_t)b * D + c) * N + n] : 0.0f);
+        // A = -inf (a state that forgets everything) as the largest number: a token past the end has a step of 0, which must
+        // not make 0 times infinity of it
+        const float A2 = A[(size_t)c * N + n] * kLog2e;
+        s_AH[i] = make_float2(A2 == -__builtin_inff() ? -3.402823466e38f : A2, init ? init[((size_t)b * D + c) * N + n] : 0.0f);
     }
     if (a.z)
         for (int i = threadIdx.x; i < 256; i += kThreads) s_silu[i] = silu_of_code(a.z_scale, (int8_t)i);

@@ -265,3 +265,19 @@ def test_infinite_and_zero_states(gpu_lib, D, L):
     p = dict(p, A=-p["A"], x=np.zeros_like(p["x"]))
     y, fin = _run(gpu_lib, sc, p, b, D, N, L)
     assert not y.any() and not fin.any()
+
+
+@pytest.mark.parametrize("L", [37, 300, 1100])
+def test_states_that_forget_everything_at_a_ragged_end(gpu_lib, L):
+    """A = -inf (exp(A_log) overflows): every token's decay is zero, so the state is the last token's input alone, whatever
+    fills the lanes behind the end of the sequence."""
+    b, D, N = 1, 40, 16
+    sc, p = make_mamba1_problem(b, D, N, L, seed=L)
+    p["A"][::3, 5] = -np.inf
+    with np.errstate(invalid="ignore"):
+        yref, sref = oracle.ref_mamba1_scan(p["xs"], sc.B_scales[0], sc.C_scales[0], p["x"], p["B"], p["C"], p["dt"], p["A"],
+                                            p["D"])
+    assert (p["dt"] > 0).all() and np.isfinite(sref).all()
+    y, fin = _run(gpu_lib, sc, p, b, D, N, L)
+    assert np.abs(y - yref).max() <= Y_TOL * np.abs(yref).max()
+    assert np.abs(fin - sref).max() <= S_TOL * np.abs(sref).max()
