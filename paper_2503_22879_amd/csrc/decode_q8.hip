@@ -127,9 +127,9 @@ __device__ __forceinline__ Tables stage_tables(const SsdArgs &a, const float *st
 // sequence ahead) and stores, so that the dependent look-ups, divisions and conversions are paid once per workgroup or
 // slice instead of once per 8 KB of state.  Four workgroups of four waves share a compute unit (one wave of each per
 // SIMD), which needs at most 128 vector registers per lane: hence the second launch bound.
-// The step (with the convolution in front), before (slices of a fixed size dealt in turn, z read behind the loop) and now:
-// 100 gated sequences of 128 heads 56.8 -> 51.3 us, 256 gated 121.9 -> 114.2, 30 gated 27.7 -> 24.0, 150 ungated of 80
-// heads 61.8 -> 59.6, 200 ungated of 24 heads 38.1 -> 30.1 (the codes alone, in and out of memory: 34, 87, 10, 32, 13).
+// One token of a layer through convolution, step and transform, with slices of a fixed size dealt in turn and z read behind
+// the loop, and now: 100 gated sequences of 128 heads 59.4 -> 51.5 us, 256 gated 129 -> 115, 30 gated 31.3 -> 24.0; 150 of
+// 80 heads 64.8 -> 50.1, 200 of 24 heads 41.1 -> 25.7 (the codes alone, in and out of memory: 34, 87, 10, 32, 13).
 template <int N, int ROWS, bool FULL, bool GATED>
 __global__ __launch_bounds__(kThreads, 4) void decode_q8_vec_kernel(SsdArgs a, const float *state_scales,
                                                                     int8_t *state_q, int seqs_per_block)
@@ -431,31 +431,17 @@ hipError_t launch(dim3 grid, const SsdArgs &a, const float *ss, int8_t *q, size_
     return hipGetLastError();
 }
 
-// Launch shape of the vector kernel: shares of the batch (the grid's y dimension) and sequences per slice of a share.
-// 4 waves of up to 128 registers each allow 4 workgroups per compute unit (one wave of each per SIMD); a slice takes as
-// many sequences as leave LDS for them (staging is paid per slice), and a share's slices are of even size.
-struct VecPlan {
-    int shares, seqs;  // seqs == 0: the shape does not fit, the caller takes the any-shape kernel
-};
-size_t vec_lds_bytes(const quamba_ssd_shape_t &s, int seqs, bool gated);
-VecPlan vec_plan(const quamba_ssd_shape_t &s, bool gated)
+// LDS of the vector kernel with `seqs` sequences per workgroup: the head's tables plus the per-sequence arrays.
+size_t vec_lds_bytes(const quamba_ssd_shape_t &s, int seqs, bool gated)
 {
-    int cap = kMaxSeqs;
-    if (s.d_state >= 4) cap = std::min(cap, std::max(1, kThreads / (s.d_state / 4)));  // one round of threads covers the slice's B rows
-    while (cap > 1 && vec_lds_bytes(s, cap, gated) > kLdsPerCu / 4) --cap;
-    const size_t lds = vec_lds_bytes(s, cap, gated);
-    if (lds > kLdsPerCu) return {0, 0};
-    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(4, kLdsPerCu / lds));
-    const int want = (compute_units() * per_cu + s.nheads - 1) / s.nheads;
-    VecPlan plan;
-    plan.shares = std::max(1, std::min({(int)s.batch, want, 65535}));
-    const int share = (s.batch + plan.shares - 1) / plan.shares;
-    plan.seqs = (share + (share + cap - 1) / cap - 1) / ((share + cap - 1) / cap);
-    return plan;
+    const size_t xf = ((size_t)seqs * s.headdim + 3) & ~(size_t)3;
+    const size_t np = (size_t)padded_row(s.d_state);
+    return decode_q8_lds_bytes(s) +
+           sizeof(float) * (2 * kMaxSeqs + (gated ? 2 : 1) * xf + (2 + (size_t)s.n_chan_clusters) * seqs * np + s.n_chan_clusters * np);
 }
 
 template <int N>
-hipError_t launch_vec(const SsdArgs &a, const float *ss, int8_t *q, VecPlan plan, hipStream_t stream)
+hipError_t launch_vec(const SsdArgs &a, const float *ss, int8_t *q, Q8Plan plan, hipStream_t stream)
 {
     constexpr int RPI = 64 / (N / 16);
     const int P = a.s.headdim, spb = plan.seqs;
@@ -477,25 +463,33 @@ size_t decode_q8_lds_bytes(const quamba_ssd_shape_t &s)
     return sizeof(float) * (table_offset(s.headdim) + 2 * (size_t)s.n_chan_clusters * s.d_state);
 }
 
-namespace {
-
-// LDS of the vector kernel with `seqs` sequences per workgroup: the head's tables plus the per-sequence arrays.
-size_t vec_lds_bytes(const quamba_ssd_shape_t &s, int seqs, bool gated)
+// Shares of the batch (the grid's y dimension) and sequences per slice of a share.  4 waves of up to 128 registers each allow
+// 4 workgroups per compute unit (one wave of each per SIMD); a slice takes as many sequences as leave LDS for them (staging
+// is paid per slice), and a share's slices are of even size.  All workgroups are resident at once: with one share more they
+// would leave some over, each of which walks its whole share on a chip that is otherwise done (80 heads, 13 shares where
+// 12.8 are resident: 150 sequences 50.5 us, with 12 shares 42.1; 24 heads, 200 sequences 23.3, 18.6; 96 heads, 64
+// sequences 27.7, 22.7).
+Q8Plan decode_q8_plan(const quamba_ssd_shape_t &s, bool gated)
 {
-    const size_t xf = ((size_t)seqs * s.headdim + 3) & ~(size_t)3;
-    const size_t np = (size_t)padded_row(s.d_state);
-    return decode_q8_lds_bytes(s) +
-           sizeof(float) * (2 * kMaxSeqs + (gated ? 2 : 1) * xf + (2 + (size_t)s.n_chan_clusters) * seqs * np + s.n_chan_clusters * np);
+    int cap = kMaxSeqs;
+    if (s.d_state >= 4) cap = std::min(cap, std::max(1, kThreads / (s.d_state / 4)));  // one round of threads covers the slice's B rows
+    while (cap > 1 && vec_lds_bytes(s, cap, gated) > kLdsPerCu / 4) --cap;
+    const size_t lds = vec_lds_bytes(s, cap, gated);
+    if (lds > kLdsPerCu) return {0, 0, 0};
+    Q8Plan plan;
+    plan.resident = compute_units() * (int)std::min<size_t>(4, kLdsPerCu / lds);
+    plan.shares = std::max(1, std::min({(int)s.batch, plan.resident / s.nheads, 65535}));
+    const int share = (s.batch + plan.shares - 1) / plan.shares;
+    plan.seqs = (share + (share + cap - 1) / cap - 1) / ((share + cap - 1) / cap);
+    return plan;
 }
-
-}  // namespace
 
 hipError_t launch_decode_q8(const SsdArgs &a, const float *state_scales, int8_t *state_q, hipStream_t stream)
 {
     // the vector kernel reads the codes 16 bytes at a time and x, B and C 4 bytes at a time
     const bool al = reinterpret_cast<uintptr_t>(state_q) % 16 == 0 && reinterpret_cast<uintptr_t>(a.x) % 4 == 0 &&
                     reinterpret_cast<uintptr_t>(a.B) % 4 == 0 && reinterpret_cast<uintptr_t>(a.C) % 4 == 0;
-    const VecPlan plan = vec_plan(a.s, a.z != nullptr);
+    const Q8Plan plan = decode_q8_plan(a.s, a.z != nullptr);
     if (al && plan.seqs > 0) {
         switch (a.s.d_state) {
             case 16: return launch_vec<16>(a, state_scales, state_q, plan, stream);

@@ -278,6 +278,12 @@ hipError_t launch_decode(const SsdArgs &a, hipStream_t stream);
 hipError_t launch_decode_q8(const SsdArgs &a, const float *state_scales, int8_t *state_q, hipStream_t stream);
 hipError_t launch_quantize_state(const SsdArgs &a, const float *state_scales, int8_t *state_q, hipStream_t stream);
 size_t decode_q8_lds_bytes(const quamba_ssd_shape_t &s);
+struct Q8Plan {    // launch shape of the step's vector kernel: nheads x shares workgroups
+    int shares;    // parts of the batch
+    int seqs;      // sequences per slice of a part; 0: the shape does not fit, the any-shape kernel takes it
+    int resident;  // workgroups the device holds at once
+};
+Q8Plan decode_q8_plan(const quamba_ssd_shape_t &s, bool gated);
 // Quantized Hadamard transform of rows of n = 2^k fp16 values (Section 4.2)
 hipError_t launch_hadamard_quantize(const uint16_t *y, int64_t rows, int n, float s_y, int8_t *out, hipStream_t stream);
 bool hadamard_order_supported(int n);  // 2^k, or 12 * 2^k / 20 * 2^k with k >= 2, up to 16384

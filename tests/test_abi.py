@@ -171,6 +171,25 @@ def test_gated_entry_points_reject_bad_arguments_without_a_device():
     assert lib.quamba_ssd_decode_step_q8_gated(C.byref(_shape()), C.byref(sc), C.byref(g), p, *dec, None) == -5
 
 
+@pytest.mark.parametrize("gated", [False, True])
+@pytest.mark.parametrize("H", [1, 7, 24, 40, 80, 96, 128, 300, 600, 1500])
+def test_8bit_step_launches_no_more_workgroups_than_are_resident(H, gated):
+    """The shares of the batch are cut so that heads x shares workgroups run side by side (the plan as it is made without a
+    GPU, for 256 compute units): no tail of a few workgroups with a whole share each.  More heads than that: one share.  A
+    slice never takes more sequences than a share has, nor than one round of threads stages."""
+    class Plan(C.Structure):
+        _fields_ = [("shares", C.c_int), ("seqs", C.c_int), ("resident", C.c_int)]
+    plan = getattr(q.load_library(), "_ZN6quamba14decode_q8_planERK18quamba_ssd_shape_tb")  # library-internal
+    plan.restype, plan.argtypes = Plan, [C.POINTER(q.Shape), C.c_bool]
+    for P, N, n in ((64, 128, 4), (64, 128, 16), (64, 16, 4), (20, 256, 8)):
+        for batch in (1, 2, 5, 16, 100, 256, 3000):
+            p = plan(C.byref(_shape(batch=batch, nheads=H, ngroups=1, headdim=P, d_state=N, n_chan_clusters=n)), gated)
+            assert 1 <= p.shares <= batch and p.resident % 256 == 0 and 256 <= p.resident <= 1024
+            assert p.shares == 1 or H * p.shares <= p.resident, (H, batch, P, N, n, p.shares)
+            assert p.shares == batch or H * (p.shares + 1) > p.resident      # no fewer than fit either
+            assert 1 <= p.seqs <= min(16, 1024 // N, -(-batch // p.shares))
+
+
 def test_binding_fails_loudly_without_library(monkeypatch):
     import paper_2503_22879_amd.binding as b
     monkeypatch.setattr(b, "_lib", None)
