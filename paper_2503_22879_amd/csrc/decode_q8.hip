@@ -129,7 +129,7 @@ __device__ __forceinline__ Tables stage_tables(const SsdArgs &a, const float *st
 // SIMD), which needs at most 128 vector registers per lane: hence the second launch bound.
 // One token of a layer through convolution, step and transform, with slices of a fixed size dealt in turn and z read behind
 // the loop, and now: 100 gated sequences of 128 heads 59.4 -> 51.5 us, 256 gated 129 -> 115, 30 gated 31.3 -> 24.0; 150 of
-// 80 heads 64.8 -> 50.1, 200 of 24 heads 41.1 -> 25.7 (the codes alone, in and out of memory: 34, 87, 10, 32, 13).
+// 80 heads 64.8 -> 50.1, 200 of 24 heads 41.1 -> 25.4 (the codes alone, in and out of memory: 34, 87, 10, 32, 13).
 template <int N, int ROWS, bool FULL, bool GATED>
 __global__ __launch_bounds__(kThreads, 4) void decode_q8_vec_kernel(SsdArgs a, const float *state_scales,
                                                                     int8_t *state_q, int seqs_per_block)
@@ -473,7 +473,14 @@ Q8Plan decode_q8_plan(const quamba_ssd_shape_t &s, bool gated)
 {
     int cap = kMaxSeqs;
     if (s.d_state >= 4) cap = std::min(cap, std::max(1, kThreads / (s.d_state / 4)));  // one round of threads covers the slice's B rows
-    while (cap > 1 && vec_lds_bytes(s, cap, gated) > kLdsPerCu / 4) --cap;
+    auto fit = [&](int cap, int per_cu) {
+        while (cap > 1 && vec_lds_bytes(s, cap, gated) > kLdsPerCu / per_cu) --cap;
+        return cap;
+    };
+    // A slice of a single sequence pays its staging and two barriers for each: where a quarter of the LDS holds no more
+    // (16 channel ranges of 128 states), a third (64 sequences of 128 heads 39.5 -> 35.7 us, 256 135.5 -> 124.8; half: 38.3 and
+    // 128.2; with 8 ranges, where a quarter holds four sequences, a third is 1 to 4 % slower from 128 sequences up).
+    cap = fit(cap, fit(cap, 4) > 1 ? 4 : 3);
     const size_t lds = vec_lds_bytes(s, cap, gated);
     if (lds > kLdsPerCu) return {0, 0, 0};
     Q8Plan plan;

@@ -188,6 +188,8 @@ def test_8bit_step_launches_no_more_workgroups_than_are_resident(H, gated):
             assert p.shares == 1 or H * p.shares <= p.resident, (H, batch, P, N, n, p.shares)
             assert p.shares == batch or H * (p.shares + 1) > p.resident      # no fewer than fit either
             assert 1 <= p.seqs <= min(16, 1024 // N, -(-batch // p.shares))
+            if n == 16 and batch >= 2 * p.shares:
+                assert p.seqs > 1, (H, batch, p.shares)      # staged for more than one sequence at a time
 
 
 def test_binding_fails_loudly_without_library(monkeypatch):

@@ -178,6 +178,13 @@ def test_q8_decode_several_sequences_per_workgroup(gpu_lib, batch, H, P, N, G, m
     _big_batch_steps(gpu_lib, s, seed=9, steps=2, misalign=misalign)
 
 
+def test_q8_decode_many_channel_ranges(gpu_lib):
+    """16 channel ranges of 128 states: tables of 25 KB, slices of two and three sequences with three workgroups per compute
+    unit, the last one short."""
+    s = W.LayerShape("t", 70, 1, 128, 64, 128, 8, 64, 2, 16)
+    _big_batch_steps(gpu_lib, s, seed=9, steps=2)
+
+
 @pytest.mark.parametrize("P,N,H,G", [(64, 128, 8, 2), (20, 24, 4, 2), (7, 5, 3, 1), (33, 16, 4, 1)])
 def test_quantize_state_bit_exact(gpu_lib, P, N, H, G):
     """fp32 state -> codes of the cache: the 4-wide path, the scalar path (d_state not a multiple of 4), clamping."""
