@@ -31,6 +31,10 @@ struct Entry {
     decltype(&quamba_conv1d_q8) conv1d;
 } entry;
 
+// The ctypes structures that carry the shape and the scale tables, and the class whose tables are read directly: types of
+// binding.py.
+PyObject *shape_type, *scales_type, *device_scales_type;
+
 // Interned attribute names.
 PyObject *s_tensors, *s_struct, *s_cuda_stream, *s_z, *s_z_scale, *s_dt_q, *s_dt_scale, *s_dt_bias;
 
@@ -92,13 +96,18 @@ struct Ref {  // an owned reference
     Ref(const Ref &) = delete;
 };
 
-// A ctypes structure's bytes.
+// The bytes of a ctypes structure, an instance of `type`: another object's bytes are not a structure, however many.
 template <typename T>
-T structure(PyObject *o, const char *name)
+T structure(PyObject *o, PyObject *type, const char *name)
 {
+    if (!PyObject_TypeCheck(o, reinterpret_cast<PyTypeObject *>(type))) {
+        PyErr_Format(PyExc_TypeError, "%s must be a %s, not %s", name, reinterpret_cast<PyTypeObject *>(type)->tp_name,
+                     Py_TYPE(o)->tp_name);
+        throw Fail();
+    }
     Py_buffer view;
     if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) throw Fail();
-    const bool fits = view.len == (Py_ssize_t)sizeof(T);
+    const bool fits = view.len >= (Py_ssize_t)sizeof(T);  // a subclass may have added fields
     T v;
     if (fits) memcpy(&v, view.buf, sizeof(T));
     PyBuffer_Release(&view);
@@ -106,32 +115,27 @@ T structure(PyObject *o, const char *name)
     return v;
 }
 
-quamba_ssd_shape_t shape_of(PyObject *o) { return structure<quamba_ssd_shape_t>(o, "shape"); }
+quamba_ssd_shape_t shape_of(PyObject *o) { return structure<quamba_ssd_shape_t>(o, shape_type, "shape"); }
 
-// The scale tables: DeviceScales holds the five device tensors, in the struct's order; anything else is asked for
-// its struct().
+// The scale tables: a DeviceScales holds the five device tensors, in the struct's order; anything else (a subclass may say
+// otherwise) is asked for its struct().
 quamba_ssd_scales_t scales_of(PyObject *o)
 {
-    quamba_ssd_scales_t s;
-    PyObject *list = PyObject_GetAttr(o, s_tensors);
-    if (!list) {
-        PyErr_Clear();
-        Ref st(PyObject_CallMethodNoArgs(o, s_struct));
-        return structure<quamba_ssd_scales_t>(st.o, "scales");
+    if (Py_TYPE(o) == reinterpret_cast<PyTypeObject *>(device_scales_type)) {
+        Ref list(PyObject_GetAttr(o, s_tensors));
+        if (PyList_Check(list.o) && PyList_GET_SIZE(list.o) == 5) {
+            const void *p[5];
+            int n = 0;
+            for (; n < 5 && THPVariable_Check(PyList_GET_ITEM(list.o, n)); ++n)
+                p[n] = THPVariable_Unpack(PyList_GET_ITEM(list.o, n)).data_ptr();
+            if (n == 5)
+                return {static_cast<const float *>(p[0]), static_cast<const int32_t *>(p[1]),
+                        static_cast<const int32_t *>(p[2]), static_cast<const float *>(p[3]),
+                        static_cast<const float *>(p[4])};
+        }
     }
-    Ref held(list);
-    if (!PyList_Check(list) || PyList_GET_SIZE(list) != 5) fail(PyExc_TypeError, "%s must hold five tables", "scales");
-    const void *p[5];
-    for (int i = 0; i < 5; ++i) {
-        const at::Tensor *t = tensor_or_null(PyList_GET_ITEM(list, i), "scales");
-        p[i] = t ? t->data_ptr() : nullptr;
-    }
-    s.x_scales = static_cast<const float *>(p[0]);
-    s.head_cluster_end = static_cast<const int32_t *>(p[1]);
-    s.chan_cluster_end = static_cast<const int32_t *>(p[2]);
-    s.B_scales = static_cast<const float *>(p[3]);
-    s.C_scales = static_cast<const float *>(p[4]);
-    return s;
+    Ref st(PyObject_CallMethodNoArgs(o, s_struct));
+    return structure<quamba_ssd_scales_t>(st.o, scales_type, "scales.struct()");
 }
 
 // The optional side inputs (None: no struct).
@@ -389,17 +393,29 @@ PyObject *method(PyObject *, PyObject *const *a, Py_ssize_t n)
     }
 }
 
-// The addresses of the library's functions, in the order of Entry.
+// The addresses of the library's functions, in the order of Entry, and the types of binding.py.
 PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    void *p[9];
-    if (n != 9) {
-        PyErr_SetString(PyExc_TypeError, "expected 9 addresses");
+    constexpr int kEntries = 9;
+    PyObject **const types[] = {&shape_type, &scales_type, &device_scales_type};
+    constexpr int kTypes = sizeof(types) / sizeof(types[0]);
+    void *p[kEntries];
+    if (n != kEntries + kTypes) {
+        PyErr_Format(PyExc_TypeError, "expected %d addresses and %d types", kEntries, kTypes);
         return nullptr;
     }
-    for (int i = 0; i < 9; ++i) {
+    for (int i = 0; i < kEntries; ++i) {
         p[i] = PyLong_AsVoidPtr(a[i]);
         if (PyErr_Occurred()) return nullptr;
+    }
+    for (int i = 0; i < kTypes; ++i) {
+        if (!PyType_Check(a[kEntries + i])) {
+            PyErr_SetString(PyExc_TypeError, "expected a type");
+            return nullptr;
+        }
+        Py_INCREF(a[kEntries + i]);
+        Py_XDECREF(*types[i]);
+        *types[i] = a[kEntries + i];
     }
     static_assert(sizeof(Entry) == sizeof(p), "one address per entry point");
     memcpy(&entry, p, sizeof(entry));
