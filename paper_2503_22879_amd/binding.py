@@ -69,6 +69,14 @@ class Gate:
     dt_scale: float = 0.0
     dt_bias: object = None
 
+    def struct(self, z_shape, dt_shape, nheads) -> _GateStruct:
+        """The C structure of the side inputs, their types and shapes checked (for callers of the C library; the functions
+        below read a Gate's fields themselves)."""
+        import torch
+        return _GateStruct(_dp(self.z, torch.int8, z_shape, "gate.z"), float(self.z_scale),
+                           _dp(self.dt_q, torch.int8, dt_shape, "gate.dt_q"), float(self.dt_scale),
+                           _dp(self.dt_bias, torch.float32, (nheads,), "gate.dt_bias"))
+
 
 def library_path() -> str:
     return _LIB_PATH
@@ -157,7 +165,8 @@ def _load_bind():
     mod.bind(*(C.cast(f, C.c_void_p).value for f in (
         lib.quamba_ssd_prefill_gated, lib.quamba_ssd_prefill_noalloc, lib.quamba_ssd_decode_step_gated,
         lib.quamba_ssd_decode_step_q8_gated, lib.quamba_ssd_quantize_state, lib.quamba_hadamard_quantize,
-        lib.quamba_mamba1_scan_gated, lib.quamba_mamba1_decode_step_gated, lib.quamba_conv1d_q8)), Shape, _ScalesStruct, DeviceScales)
+        lib.quamba_mamba1_scan_gated, lib.quamba_mamba1_decode_step_gated, lib.quamba_conv1d_q8)), Shape, _ScalesStruct, _GateStruct,
+        DeviceScales, Gate)
     _bind = mod
     return mod
 

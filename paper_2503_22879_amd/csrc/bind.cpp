@@ -31,9 +31,9 @@ struct Entry {
     decltype(&quamba_conv1d_q8) conv1d;
 } entry;
 
-// The ctypes structures that carry the shape and the scale tables, and the class whose tables are read directly: types of
-// binding.py.
-PyObject *shape_type, *scales_type, *device_scales_type;
+// The ctypes structures that carry the shape, the scale tables and the side inputs, and the classes that are read directly:
+// types of binding.py.
+PyObject *shape_type, *scales_type, *gate_struct_type, *device_scales_type, *gate_type;
 
 // Interned attribute names.
 PyObject *s_tensors, *s_struct, *s_cuda_stream, *s_z, *s_z_scale, *s_dt_q, *s_dt_scale, *s_dt_bias;
@@ -138,7 +138,23 @@ quamba_ssd_scales_t scales_of(PyObject *o)
     return structure<quamba_ssd_scales_t>(st.o, scales_type, "scales.struct()");
 }
 
-// The optional side inputs (None: no struct).
+PyObject *tuple_of(std::initializer_list<int64_t> v)
+{
+    PyObject *t = PyTuple_New((Py_ssize_t)v.size());
+    Py_ssize_t i = 0;
+    if (t)
+        for (int64_t e : v) {
+            PyObject *item = PyLong_FromLongLong(e);
+            if (!item) {
+                Py_DECREF(t);
+                return nullptr;
+            }
+            PyTuple_SET_ITEM(t, i++, item);
+        }
+    return t;
+}
+
+// The optional side inputs (None: no struct): the fields of a Gate; anything else is asked for its struct().
 struct GateArg {
     quamba_ssd_gate_t g;
     bool present = false;
@@ -146,6 +162,12 @@ struct GateArg {
     {
         if (o == Py_None) return;
         present = true;
+        if (Py_TYPE(o) != reinterpret_cast<PyTypeObject *>(gate_type)) {
+            Ref zt(tuple_of(z_shape)), dtt(tuple_of(dt_shape)), nb(PyLong_FromLongLong(nbias));
+            Ref st(PyObject_CallMethodObjArgs(o, s_struct, zt.o, dtt.o, nb.o, nullptr));
+            g = structure<quamba_ssd_gate_t>(st.o, gate_struct_type, "gate.struct()");
+            return;
+        }
         Ref z(PyObject_GetAttr(o, s_z)), zs(PyObject_GetAttr(o, s_z_scale)), dq(PyObject_GetAttr(o, s_dt_q)),
             ds(PyObject_GetAttr(o, s_dt_scale)), db(PyObject_GetAttr(o, s_dt_bias));
         g.z = pointer<int8_t>(z.o, at::kChar, z_shape, "gate.z");
@@ -397,7 +419,7 @@ PyObject *method(PyObject *, PyObject *const *a, Py_ssize_t n)
 PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     constexpr int kEntries = 9;
-    PyObject **const types[] = {&shape_type, &scales_type, &device_scales_type};
+    PyObject **const types[] = {&shape_type, &scales_type, &gate_struct_type, &device_scales_type, &gate_type};
     constexpr int kTypes = sizeof(types) / sizeof(types[0]);
     void *p[kEntries];
     if (n != kEntries + kTypes) {

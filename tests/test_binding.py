@@ -65,3 +65,27 @@ def test_scales_other_than_device_scales_are_asked_for_their_struct():
     for scales in (_host_scales(), as_tuple):         # accepted: the call stops at the missing x
         with pytest.raises(q.QuambaError):
             _prefill(scales=scales)
+
+
+def test_gates_other_than_a_gate_are_asked_for_their_struct():
+    seen = []
+
+    class Own(q.Gate):
+        def struct(self, *shapes):
+            seen.append(shapes)
+            return super().struct(*shapes)
+
+    class Bytes:
+        def struct(self, *shapes):
+            return bytes(40)
+
+    with pytest.raises(q.QuambaError):                # goes on to the missing x
+        _prefill(gate=Own(z_scale=0.5))
+    assert seen == [((1, 8, 4, 8), (1, 8, 4), 4)]
+    with pytest.raises(TypeError):
+        _prefill(gate=Bytes())
+    with pytest.raises(AttributeError):
+        _prefill(gate=object())
+    st = q.Gate(z_scale=0.5, dt_scale=0.25).struct((1, 8, 4, 8), (1, 8, 4), 4)
+    assert isinstance(st, binding._GateStruct) and (st.z, st.z_scale, st.dt_q, st.dt_scale, st.dt_bias) == \
+        (None, 0.5, None, 0.25, None)
