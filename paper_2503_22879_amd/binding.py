@@ -161,12 +161,12 @@ def _load_bind():
         raise FileNotFoundError(f"{_BIND_PATH} is missing: build it with `python -m paper_2503_22879_amd.build` "
                                 "(or __graft_entry__.build())")
     from . import _bind as mod
-    # the order of Entry in csrc/bind.cpp, and the types it tells arguments by
+    # the order of Entry in csrc/bind.cpp, the types it tells arguments by, and a pointer's address
     mod.bind(*(C.cast(f, C.c_void_p).value for f in (
         lib.quamba_ssd_prefill_gated, lib.quamba_ssd_prefill_noalloc, lib.quamba_ssd_decode_step_gated,
         lib.quamba_ssd_decode_step_q8_gated, lib.quamba_ssd_quantize_state, lib.quamba_hadamard_quantize,
         lib.quamba_mamba1_scan_gated, lib.quamba_mamba1_decode_step_gated, lib.quamba_conv1d_q8)), Shape, _ScalesStruct, _GateStruct,
-        DeviceScales, Gate)
+        DeviceScales, Gate, lambda p: C.cast(p, C.c_void_p).value)
     _bind = mod
     return mod
 

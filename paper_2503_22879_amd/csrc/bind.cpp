@@ -34,6 +34,7 @@ struct Entry {
 // The ctypes structures that carry the shape, the scale tables and the side inputs, and the classes that are read directly:
 // types of binding.py.
 PyObject *shape_type, *scales_type, *gate_struct_type, *device_scales_type, *gate_type;
+PyObject *address_of;  // and its function from a ctypes pointer to its address or None
 
 // Interned attribute names.
 PyObject *s_tensors, *s_struct, *s_cuda_stream, *s_z, *s_z_scale, *s_dt_q, *s_dt_scale, *s_dt_bias;
@@ -179,7 +180,8 @@ struct GateArg {
     const quamba_ssd_gate_t *get() const { return present ? &g : nullptr; }
 };
 
-// The stream argument: None is torch's current stream, else an object with a cuda_stream attribute or the pointer itself.
+// The stream argument: None is torch's current stream, else an object with a cuda_stream attribute or the pointer itself, as
+// a number or as anything that ctypes takes for a pointer (c_void_p, a pointer or array instance).
 void *stream_of(PyObject *o)
 {
     if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
@@ -190,6 +192,13 @@ void *stream_of(PyObject *o)
         a = o;
     }
     Ref held(a);
+    if (!PyLong_Check(a)) {
+        Ref address(PyObject_CallFunctionObjArgs(address_of, a, nullptr));
+        if (address.o == Py_None) return nullptr;
+        void *p = PyLong_AsVoidPtr(address.o);
+        if (PyErr_Occurred()) throw Fail();
+        return p;
+    }
     void *p = PyLong_AsVoidPtr(a);
     if (PyErr_Occurred()) throw Fail();
     return p;
@@ -415,29 +424,29 @@ PyObject *method(PyObject *, PyObject *const *a, Py_ssize_t n)
     }
 }
 
-// The addresses of the library's functions, in the order of Entry, and the types of binding.py.
+// The addresses of the library's functions, in the order of Entry, and what binding.py has for the objects above.
 PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     constexpr int kEntries = 9;
-    PyObject **const types[] = {&shape_type, &scales_type, &gate_struct_type, &device_scales_type, &gate_type};
-    constexpr int kTypes = sizeof(types) / sizeof(types[0]);
+    PyObject **const objects[] = {&shape_type, &scales_type, &gate_struct_type, &device_scales_type, &gate_type, &address_of};
+    constexpr int kObjects = sizeof(objects) / sizeof(objects[0]);
     void *p[kEntries];
-    if (n != kEntries + kTypes) {
-        PyErr_Format(PyExc_TypeError, "expected %d addresses and %d types", kEntries, kTypes);
+    if (n != kEntries + kObjects) {
+        PyErr_Format(PyExc_TypeError, "expected %d addresses and %d objects", kEntries, kObjects);
         return nullptr;
     }
     for (int i = 0; i < kEntries; ++i) {
         p[i] = PyLong_AsVoidPtr(a[i]);
         if (PyErr_Occurred()) return nullptr;
     }
-    for (int i = 0; i < kTypes; ++i) {
-        if (!PyType_Check(a[kEntries + i])) {
-            PyErr_SetString(PyExc_TypeError, "expected a type");
+    for (int i = 0; i < kObjects; ++i) {
+        if (i + 1 < kObjects ? !PyType_Check(a[kEntries + i]) : !PyCallable_Check(a[kEntries + i])) {
+            PyErr_SetString(PyExc_TypeError, "expected types and a function");
             return nullptr;
         }
         Py_INCREF(a[kEntries + i]);
-        Py_XDECREF(*types[i]);
-        *types[i] = a[kEntries + i];
+        Py_XDECREF(*objects[i]);
+        *objects[i] = a[kEntries + i];
     }
     static_assert(sizeof(Entry) == sizeof(p), "one address per entry point");
     memcpy(&entry, p, sizeof(entry));

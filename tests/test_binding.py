@@ -89,3 +89,15 @@ def test_gates_other_than_a_gate_are_asked_for_their_struct():
     st = q.Gate(z_scale=0.5, dt_scale=0.25).struct((1, 8, 4, 8), (1, 8, 4), 4)
     assert isinstance(st, binding._GateStruct) and (st.z, st.z_scale, st.dt_q, st.dt_scale, st.dt_bias) == \
         (None, 0.5, None, 0.25, None)
+
+
+def test_a_stream_may_be_a_ctypes_pointer():
+    class Stream:
+        cuda_stream = C.c_void_p(0)
+
+    for stream in (C.c_void_p(0), C.c_void_p(64), C.pointer(C.c_int(1)), (C.c_char * 8)(), Stream(), 64):
+        with pytest.raises(q.QuambaError):            # accepted: the call stops at the missing x
+            _prefill(stream=stream)
+    for stream in (object(), 1.5, [0]):
+        with pytest.raises((TypeError, C.ArgumentError)):
+            _prefill(stream=stream)
