@@ -3,6 +3,7 @@ Python binding."""
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
@@ -32,6 +33,16 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def _rocm_include() -> str:
+    """The directory of HIP's headers: beside the compiler, wherever PATH or a link finds it."""
+    hipcc = os.path.realpath(shutil.which(HIPCC) or HIPCC)
+    for root in (os.path.dirname(os.path.dirname(hipcc)), os.environ.get("ROCM_PATH", ""), "/opt/rocm"):
+        include = os.path.join(root, "include")
+        if root and os.path.exists(os.path.join(include, "hip", "hip_runtime.h")):
+            return include
+    raise FileNotFoundError(f"no hip/hip_runtime.h beside {hipcc}, under ROCM_PATH or /opt/rocm")
+
+
 def _build_bind(force: bool) -> str:
     """The extension module that binding.py calls (host code against torch's headers; torch's libraries are already
     loaded when it is imported)."""
@@ -43,7 +54,7 @@ def _build_bind(force: bool) -> str:
                f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(ROOT, "include"),
                "-isystem", sysconfig.get_paths()["include"]]
         for d in (os.path.join(base, "include"), os.path.join(base, "include", "torch", "csrc", "api", "include"),
-                  os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include")):
+                  _rocm_include()):
             cmd += ["-isystem", d]
         cmd += [src, "-o", BIND, "-L" + os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
         subprocess.check_call(cmd)

@@ -1,0 +1,25 @@
+"""What the build asks of the machine it runs on."""
+import os
+import shutil
+
+import pytest
+
+from paper_2503_22879_amd import build
+
+
+@pytest.mark.parametrize("how", ["path", "link", "full"])
+def test_hip_headers_beside_a_compiler_that_path_or_a_link_finds(monkeypatch, tmp_path, how):
+    full = shutil.which(build.HIPCC) or build.HIPCC
+    if how == "path":
+        monkeypatch.setenv("PATH", os.path.dirname(full) + os.pathsep + os.environ["PATH"])
+        monkeypatch.setattr(build, "HIPCC", os.path.basename(full))
+    elif how == "link":
+        os.symlink(full, tmp_path / "cc")
+        monkeypatch.setattr(build, "HIPCC", str(tmp_path / "cc"))
+    monkeypatch.setattr(build, "BIND", str(tmp_path / "_bind.so"))
+    ran = []
+    monkeypatch.setattr(build.subprocess, "check_call", ran.append)
+    build._build_bind(True)
+    found = [d for flag, d in zip(ran[0], ran[0][1:]) if flag == "-isystem" and
+             os.path.exists(os.path.join(d, "hip", "hip_runtime.h"))]
+    assert found and all(os.path.isabs(d) for d in found)
