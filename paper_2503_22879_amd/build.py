@@ -2,6 +2,7 @@
 Python binding."""
 from __future__ import annotations
 
+import importlib.util
 import os
 import shutil
 import subprocess
@@ -43,9 +44,12 @@ def _rocm_include() -> str:
     raise FileNotFoundError(f"no hip/hip_runtime.h beside {hipcc}, under ROCM_PATH or /opt/rocm")
 
 
-def _build_bind(force: bool) -> str:
+def _build_bind(force: bool) -> str | None:
     """The extension module that binding.py calls (host code against torch's headers; torch's libraries are already
-    loaded when it is imported)."""
+    loaded when it is imported).  Without torch there are no tensors to call it with, and nothing is built."""
+    if importlib.util.find_spec("torch") is None:
+        print("torch is not installed: building the C library alone")
+        return None
     import torch
     src, header = os.path.join(CSRC, "bind.cpp"), os.path.join(ROOT, "include", "quamba_ssd.h")
     if force or not os.path.exists(BIND) or any(os.path.getmtime(d) > os.path.getmtime(BIND) for d in (src, header)):
@@ -66,8 +70,9 @@ def build_library(force: bool = True, jobs: int = 8) -> str:
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         bind = ex.submit(_build_bind, force)
         objs = list(ex.map(lambda s: _compile(s, force), SOURCES))
-        bind.result()
+    # the library first: a C program needs no more, also where the extension cannot be built
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
+    bind.result()
     return LIB
 
 

@@ -1,6 +1,8 @@
 """What the build asks of the machine it runs on."""
+import importlib.util
 import os
 import shutil
+import sys
 
 import pytest
 
@@ -23,3 +25,25 @@ def test_hip_headers_beside_a_compiler_that_path_or_a_link_finds(monkeypatch, tm
     found = [d for flag, d in zip(ran[0], ran[0][1:]) if flag == "-isystem" and
              os.path.exists(os.path.join(d, "hip", "hip_runtime.h"))]
     assert found and all(os.path.isabs(d) for d in found)
+
+
+def test_the_c_library_is_built_where_the_extension_cannot_be(monkeypatch, tmp_path):
+    """Without torch, and with a compiler for the extension that fails."""
+    monkeypatch.setattr(build, "OBJ", str(tmp_path))
+    monkeypatch.setattr(build, "_compile", lambda src, force: src + ".o")
+    ran = []
+
+    def check_call(cmd):
+        ran.append(cmd)
+        if build.BIND in cmd:
+            raise FileNotFoundError(cmd[0])
+
+    monkeypatch.setattr(build.subprocess, "check_call", check_call)
+    with pytest.raises(FileNotFoundError):
+        build.build_library()
+    assert any(build.LIB in cmd for cmd in ran)
+    ran.clear()
+    monkeypatch.setitem(sys.modules, "torch", None)
+    monkeypatch.setattr(importlib.util, "find_spec", lambda name: None)
+    assert build.build_library() == build.LIB
+    assert len(ran) == 1 and build.LIB in ran[0]
