@@ -6,6 +6,7 @@ import importlib.util
 import os
 import shutil
 import subprocess
+import sys
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
@@ -52,7 +53,11 @@ def _build_bind(force: bool) -> str | None:
         return None
     import torch
     src, header = os.path.join(CSRC, "bind.cpp"), os.path.join(ROOT, "include", "quamba_ssd.h")
-    if force or not os.path.exists(BIND) or any(os.path.getmtime(d) > os.path.getmtime(BIND) for d in (src, header)):
+    # what it was compiled against: other releases of either have other layouts
+    built_for, stamp = f"Python {sys.version}, torch {torch.__version__}", os.path.join(OBJ, "bind.txt")
+    known = os.path.exists(stamp) and open(stamp).read() == built_for
+    if (force or not known or not os.path.exists(BIND) or
+            any(os.path.getmtime(d) > os.path.getmtime(BIND) for d in (src, header))):
         base = os.path.dirname(torch.__file__)
         cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
                f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(ROOT, "include"),
@@ -62,6 +67,8 @@ def _build_bind(force: bool) -> str | None:
             cmd += ["-isystem", d]
         cmd += [src, "-o", BIND, "-L" + os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
         subprocess.check_call(cmd)
+        with open(stamp, "w") as f:
+            f.write(built_for)
     return BIND
 
 
@@ -77,5 +84,4 @@ def build_library(force: bool = True, jobs: int = 8) -> str:
 
 
 if __name__ == "__main__":
-    import sys
     print(build_library(force="--incremental" not in sys.argv))

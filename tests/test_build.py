@@ -19,6 +19,7 @@ def test_hip_headers_beside_a_compiler_that_path_or_a_link_finds(monkeypatch, tm
         os.symlink(full, tmp_path / "cc")
         monkeypatch.setattr(build, "HIPCC", str(tmp_path / "cc"))
     monkeypatch.setattr(build, "BIND", str(tmp_path / "_bind.so"))
+    monkeypatch.setattr(build, "OBJ", str(tmp_path))
     ran = []
     monkeypatch.setattr(build.subprocess, "check_call", ran.append)
     build._build_bind(True)
@@ -47,3 +48,23 @@ def test_the_c_library_is_built_where_the_extension_cannot_be(monkeypatch, tmp_p
     monkeypatch.setattr(importlib.util, "find_spec", lambda name: None)
     assert build.build_library() == build.LIB
     assert len(ran) == 1 and build.LIB in ran[0]
+
+
+def test_the_extension_is_built_again_for_another_torch(monkeypatch, tmp_path):
+    import torch
+    monkeypatch.setattr(build, "OBJ", str(tmp_path))
+    monkeypatch.setattr(build, "BIND", str(tmp_path / "_bind.so"))
+    ran = []
+
+    def check_call(cmd):
+        ran.append(cmd)
+        open(build.BIND, "w").close()
+
+    monkeypatch.setattr(build.subprocess, "check_call", check_call)
+    for _ in range(2):
+        build._build_bind(False)
+    assert len(ran) == 1
+    monkeypatch.setattr(torch, "__version__", torch.__version__ + ".other")
+    for _ in range(2):
+        build._build_bind(False)
+    assert len(ran) == 2
