@@ -20,6 +20,9 @@ namespace {
 
 constexpr int kWaveSlots = 4096;  // waves that keep the device full (1024 SIMDs x 4)
 constexpr int kSegWide = 32;     // tokens per workgroup of the 16-channel kernel
+// A sequence with more segments of 16 tokens than a grid may have has 16-channel waves enough for that kernel, whatever its
+// channels, and its segments of 32 tokens fit as long as the entry point takes the sequence.
+static_assert((16 * kMaxGridY) / kSegWide >= kWaveSlots && kConvMaxTokens == kSegWide * kMaxGridY, "limits of the segments");
 constexpr int kStepSeqs = 8;   // most sequences per thread of the one-token kernel
 constexpr int kAhead = 4;      // tokens whose loads are in flight
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -465,7 +468,8 @@ bool vec_ok(const ConvArgs &a)
 
 }  // namespace
 
-// Tokens per workgroup of the vector kernel.  Longer segments share the set-up and the 3-token halo between more tokens,
+// Tokens per workgroup of the vector kernel (sequences whose segments of 16 do not fit a grid never come here, see the
+// limits above).  Longer segments share the set-up and the 3-token halo between more tokens,
 // shorter ones give more waves and a shorter chain.  Measured with 4 / 8 / 16 / 32 tokens: 219 tokens of 5376 channels
 // (1155 waves of 4 tokens) 4.7 / 5.3 / 7.4 / 11.6 us, 1000 (5250) 8.15 / 8.22 / 9.9 / 13.7; 3 x 200 of 10240 channels
 // (6000) 8.24 / 8.19 / 9.9 / 13.4, 1531 (15320) 15.5 / 14.6 / 15.1 / 18.0, 4096 (40960) 33.7 / 30.0 / 30.4 / 31.2; 8 x 2048 of
@@ -478,7 +482,7 @@ int conv1d_segment_tokens(const quamba_ssd_shape_t &s, bool same_state)
     auto waves = [&](int seg) { return rows * (((int64_t)s.seqlen + seg - 1) / seg); };
     if (waves(4) <= 6 * kWaveSlots / 4) return 4;
     if (waves(8) <= 6 * kWaveSlots) return 8;
-    return s.seqlen <= 16 * kMaxGridY ? 16 : 32;
+    return 16;
 }
 
 // Waves of the 16-channel kernel; 0 for sequences shorter than a segment (among them all that may have one buffer as both

@@ -306,7 +306,7 @@ struct ConvArgs {
 };
 hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream);
 constexpr int kMaxGridY = 65535;                    // of a launch
-constexpr int kConvMaxTokens = 32 * kMaxGridY;  // longest sequence of the convolution
+constexpr int kConvMaxTokens = 32 * kMaxGridY;  // longest sequence of the convolution (segments of 32 tokens)
 // Mamba1 selective scan: shape has nheads = ngroups = 1, headdim = channels; A is [channels, d_state]
 hipError_t launch_mamba1_scan(const SsdArgs &a, const float *A, const float *init, float *fin, hipStream_t stream);
 hipError_t launch_mamba1_decode(const SsdArgs &a, const float *A, hipStream_t stream);
