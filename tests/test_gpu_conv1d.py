@@ -116,13 +116,30 @@ def test_one_token_kernel(gpu_lib, batch, H, P, N, m, n, state):
                                                (1, 45, 6, 16, 16, 3, 6),       # six ranges; segments of 4, a last one of 1
                                                (9, 291, 6, 64, 128, 2, 3),     # ... a last one of 3
                                                (15, 900, 6, 64, 16, 2, 3),     # segments of 8, the last of 4
-                                               (64, 3085, 4, 16, 16, 2, 2)])   # segments of 16, the last of 13
+                                               (16, 3085, 14, 64, 64, 2, 2),   # segments of 16, the last of 13
+                                               (64, 3085, 4, 16, 16, 2, 2)])   # 16 channels per thread, the last of 13
 def test_segments_and_carried_state(gpu_lib, batch, L, H, P, N, m, n):
-    """Every segment length of the vector kernel with ragged last segments, from a carried state."""
+    """Every segment length of the vector kernel, and the kernel with 16 channels per thread, with ragged last segments,
+    from a carried state.  (The step to segments of 16 is at 24576 waves of 8 tokens: 1024 channels, 16 x 386 segments x
+    4 blocks; to 16 channels per thread at 4096 waves of 32 tokens: 96 channels, 64 x 97 segments.)"""
     s = W.LayerShape("seg", batch, L, H, P, N, 1, 16, m, n)
     sc, _, _ = make_problem(s.with_(batch=1, seqlen=8), seed=14, calib_tokens=128)
     st = np.random.default_rng(14).integers(-128, 128, size=(batch, 3, H * P + 2 * N), dtype=np.int8)
     _check(gpu_lib, s, sc, make_conv_inputs(s, seed=14), st)
+
+
+@pytest.mark.parametrize("batch,L,H,P,N,m,n,bias", [(64, 2049, 6, 48, 16, 3, 7, True),   # ranges that end inside a thread
+                                                    (16, 4096, 18, 64, 32, 1, 1, False)])  # a second, ragged block; no bias
+def test_sixteen_channels_per_thread(gpu_lib, batch, L, H, P, N, m, n, bias):
+    """Launches of at least 4096 waves of 32 tokens: more channel ranges than four, ends of ranges inside the 16 channels of a
+    thread, no bias, and a channel block that fills no whole wave."""
+    s = W.LayerShape("wide", batch, L, H, P, N, 1, 16, m, n)
+    sc, _, _ = make_problem(s.with_(batch=1, seqlen=8), seed=16, calib_tokens=128)
+    if n > 1:
+        assert (np.asarray(sc.chan_cluster_end) % 16 != 0).any()
+    inp = make_conv_inputs(s, seed=16)
+    st = np.random.default_rng(16).integers(-128, 128, size=(batch, 3, H * P + 2 * N), dtype=np.int8) if bias else None
+    _check(gpu_lib, s, sc, inp if bias else dict(inp, bias=None), st)
 
 
 @pytest.mark.parametrize("L", [2, 7, 16])
