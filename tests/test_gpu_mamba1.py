@@ -46,13 +46,14 @@ def _check(q, b, D, N, L, seed, nranges=4, flags=0, with_init=False, with_D=True
 
 
 def test_wave_scan_kernel_several_tiles_and_a_ragged_one(gpu_lib):
-    """2608 tokens = two full tiles of 1024 and one of 560 (35 live lanes); channels not a multiple of the 8 a
-    workgroup owns (the last workgroup has waves without a channel)."""
+    """2608 tokens = five full tiles of 512 (32 lanes) and one of 48; channels not a multiple of the 16 a workgroup owns
+    (lanes of the last workgroup without a channel)."""
     ey, es = _check(gpu_lib, b=2, D=8198, N=16, L=2608, seed=1, with_init=True)
     print(f"mamba1 scan, 8198 channels x 2608 tokens: y {ey:.2e} state {es:.2e}")
 
 
 def test_wave_scan_kernel_small_shapes(gpu_lib):
+    """One workgroup per compute unit is all there is: tiles of 1024 tokens (64 lanes), and one tile of 16."""
     ey, es = _check(gpu_lib, b=1, D=203, N=16, L=1040, seed=2)
     print(f"mamba1 scan, 203 channels x 1040 tokens: y {ey:.2e} state {es:.2e}")
     _check(gpu_lib, b=3, D=64, N=16, L=16, seed=3, with_init=True, with_D=False)       # one lane of tokens
@@ -68,7 +69,7 @@ def test_sequence_lengths_around_lanes_and_tiles(gpu_lib, D, L):
 
 
 def test_any_shape_kernel_and_cross_check(gpu_lib):
-    _check(gpu_lib, b=2, D=70, N=16, L=45, seed=4, with_init=True)                      # seqlen no multiple of 16
+    _check(gpu_lib, b=2, D=70, N=16, L=45, seed=4, with_init=True, flags=gpu_lib.FLAG_GENERIC_KERNEL)  # forced, odd length
     _check(gpu_lib, b=1, D=33, N=24, L=64, seed=5, nranges=3)                           # other d_state
     _check(gpu_lib, b=1, D=130, N=16, L=256, seed=6, flags=gpu_lib.FLAG_GENERIC_KERNEL)  # forced, fast-path shape
 
@@ -158,22 +159,29 @@ def _dt_of_codes(g):
 
 
 @pytest.mark.parametrize("use_z,use_dt", [(True, False), (False, True), (True, True)])
-@pytest.mark.parametrize("b,D,N,L,flags", [(2, 203, 16, 2608, 0), (2, 70, 16, 45, 0), (1, 33, 24, 64, 0),
-                                           (1, 130, 16, 256, 1)])
+@pytest.mark.parametrize("b,D,N,L,flags", [(2, 203, 16, 2608, 0),    # 64 lanes per channel, several tiles
+                                           (2, 70, 16, 45, 0),       # 16 lanes, one tile
+                                           (2, 8177, 16, 700, 0),    # 16 lanes, several tiles
+                                           (2, 2060, 16, 1037, 0),   # 32 lanes, 8 states at a time
+                                           (2, 8198, 16, 1029, 0),   # 32 lanes, all 16 states
+                                           (1, 33, 24, 64, 0),       # any shape
+                                           (1, 130, 16, 256, 1)])    # ... forced
 def test_scan_with_side_inputs(gpu_lib, b, D, N, L, flags, use_z, use_dt):
     """Step size from int8 codes of its pre-activation plus a per-channel bias, and / or the output gate on int8 z
-    (Section 3.2), on the wave-scan kernel (several tiles and a ragged one) and the any-shape kernel: the oracle's
-    scan on the oracle's own step size, followed by the oracle's gate."""
+    (Section 3.2), on every width of the wave-scan kernel (several tiles and a ragged one, rows that start at odd
+    addresses) and the any-shape kernel: the oracle's scan on the oracle's own step size, followed by the oracle's gate.
+    Of the larger layers the oracle scans channels sampled over the workgroups."""
     import torch
     q = gpu_lib
     sc, p = make_mamba1_problem(b, D, N, L, seed=11)
     g = make_mamba1_gate(b, D, L, seed=11)
     dt_ref = _dt_of_codes(g).astype(np.float32) if use_dt else p["dt"]
     init = np.random.default_rng(11).normal(0, 0.05, size=(b, D, N)).astype(np.float32)
-    yref, sref = oracle.ref_mamba1_scan(p["xs"], sc.B_scales[0], sc.C_scales[0], p["x"], p["B"], p["C"], dt_ref, p["A"],
-                                        p["D"], init)
+    pick = np.arange(D) if D < 2048 else np.unique(np.r_[0:16, np.arange(0, D, 61), D - 16:D])
+    yref, sref = oracle.ref_mamba1_scan(p["xs"][pick], sc.B_scales[0], sc.C_scales[0], p["x"][:, pick], p["B"], p["C"],
+                                        dt_ref[:, pick], p["A"][pick], p["D"][pick], init[:, pick])
     if use_z:
-        yref = oracle.silu_gate(yref, g["z"], g["z_scale"])
+        yref = oracle.silu_gate(yref, g["z"][:, pick], g["z_scale"])
     t = {k: torch.from_numpy(np.ascontiguousarray(p[k])).cuda() for k in ("x", "B", "C", "dt", "A", "D")}
     y = torch.full((b, D, L), float("nan"), dtype=torch.float16, device="cuda")
     fin = torch.full((b, D, N), float("nan"), device="cuda")
@@ -182,8 +190,8 @@ def test_scan_with_side_inputs(gpu_lib, b, D, N, L, flags, use_z, use_dt):
                          final_state=fin, gate=_gate(q, g, use_z, use_dt))
     yg, sg = y.cpu().numpy().astype(np.float64), fin.cpu().numpy().astype(np.float64)
     assert np.isfinite(yg).all() and np.isfinite(sg).all()
-    ey = np.abs(yg - yref).max() / np.abs(yref).max()
-    es = np.abs(sg - sref).max() / np.abs(sref).max()
+    ey = np.abs(yg[:, pick] - yref).max() / np.abs(yref).max()
+    es = np.abs(sg[:, pick] - sref).max() / np.abs(sref).max()
     print(f"mamba1 scan D={D} L={L} flags={flags} z={use_z} dt_q={use_dt}: y {ey:.2e} state {es:.2e}")
     assert ey <= Y_TOL and es <= S_TOL
 
