@@ -101,3 +101,73 @@ def test_a_stream_may_be_a_ctypes_pointer():
     for stream in (object(), 1.5, [0]):
         with pytest.raises((TypeError, C.ArgumentError)):
             _prefill(stream=stream)
+
+
+def _decode_arguments(torch):
+    """A one-token step of 2 sequences, 4 heads of 8 channels, 8 states."""
+    shape = q.Shape(**{**SHAPE, "batch": 2})
+    dev = dict(device="cuda")
+    a = dict(x=torch.ones(2, 4, 8, dtype=torch.int8, **dev), B=torch.ones(2, 2, 8, dtype=torch.int8, **dev),
+             Cm=torch.ones(2, 2, 8, dtype=torch.int8, **dev), dt=torch.ones(2, 4, **dev), A=torch.zeros(4, **dev),
+             D=torch.zeros(4, **dev), state=torch.zeros(2, 4, 8, 8, **dev),
+             y=torch.zeros(2, 4, 8, dtype=torch.float16, **dev))
+    return shape, q.DeviceScales(_host_scales()), a
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,wrong", [
+    ("x", lambda t: t.to("cpu")), ("x", lambda t: t.short()), ("x", lambda t: t.view(8, 8)), ("x", lambda t: t[:1]),
+    ("x", lambda t: t.transpose(1, 2).contiguous().transpose(1, 2)), ("x", lambda t: t.tolist()), ("x", lambda t: t.data_ptr()),
+    ("B", lambda t: t.half()), ("dt", lambda t: t.double()), ("dt", lambda t: t[:, :3].contiguous()), ("A", lambda t: t.cpu()),
+    ("state", lambda t: t[..., ::2]), ("state", lambda t: t.half()), ("state", lambda t: t.cpu()), ("y", lambda t: t.float()),
+    ("y", lambda t: t.view(2, 32))])
+def test_device_tensors_are_checked(gpu_lib, name, wrong):
+    """Device, type, shape and strides of every tensor, before anything is launched: the state stays as it was."""
+    import torch
+    shape, scales, a = _decode_arguments(torch)
+    bad = {**a, name: wrong(a[name])}
+    with pytest.raises((ValueError, TypeError)):
+        q.quamba_ssd_decode_step(shape, scales, *bad.values())
+    assert not a["state"].any() and not a["y"].any()
+    q.quamba_ssd_decode_step(shape, scales, *a.values())
+    assert (a["state"] == 1).all() and (a["y"] == 8).all()      # dt x B = 1, sum of 8 C h = 8
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,wrong", [("z", lambda t: t.cpu()), ("z", lambda t: t.view(8, 8)), ("dt_q", lambda t: t.float()),
+                                        ("dt_bias", lambda t: t[:2]), ("dt_bias", lambda t: t.half()),
+                                        ("z_scale", lambda v: None), ("z_scale", lambda v: "scale")])
+def test_side_inputs_are_checked(gpu_lib, name, wrong):
+    import torch
+    shape, scales, a = _decode_arguments(torch)
+    g = dict(z=torch.ones(2, 4, 8, dtype=torch.int8, device="cuda"), z_scale=0.5,
+             dt_q=torch.ones(2, 4, dtype=torch.int8, device="cuda"), dt_scale=0.25, dt_bias=torch.zeros(4, device="cuda"))
+    with pytest.raises((ValueError, TypeError)):
+        q.quamba_ssd_decode_step(shape, scales, *a.values(), gate=q.Gate(**{**g, name: wrong(g[name])}))
+    assert not a["state"].any()
+    q.quamba_ssd_decode_step(shape, scales, *a.values(), gate=q.Gate(**g))
+    assert a["state"].any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("how", ["current", "object", "number", "pointer"])
+def test_the_call_is_enqueued_on_the_stream_it_is_given(gpu_lib, how):
+    """Its input is written on that stream behind a wait of some milliseconds: a launch on another stream would read what
+    was there before."""
+    import torch
+    s = torch.cuda.Stream()
+    src = torch.randn(64, 1024, device="cuda").half()
+    y, out, want = torch.zeros_like(src), torch.empty(64, 1024, dtype=torch.int8, device="cuda"), \
+        torch.empty(64, 1024, dtype=torch.int8, device="cuda")
+    q.quamba_hadamard_quantize(src, 1.0, want)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        torch.cuda._sleep(20_000_000)
+        y.copy_(src)
+        if how == "current":
+            q.quamba_hadamard_quantize(y, 1.0, out)
+    if how != "current":
+        q.quamba_hadamard_quantize(y, 1.0, out, stream={"object": s, "number": s.cuda_stream,
+                                                        "pointer": C.c_void_p(s.cuda_stream)}[how])
+    s.synchronize()
+    assert want.any() and torch.equal(out, want)
