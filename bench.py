@@ -36,9 +36,9 @@ KERNEL_CHUNK = 128             # tokens per chunk of prefill_mfma_kernel (the ca
 # 256 MiB device copy in the same run: factors 1.9998 and 1.0000).  These are constants taken from the committed
 # profile summaries, not measurements of this run: `traffic_source` in every roofline object names the file.
 # None for workloads that were not profiled.
-MEASURED_TRAFFIC_BYTES = {"m2_8b_b4": 496.4e6, "m2_8b_decode": 2162.3e6, "m2_8b_decode_q8": 550.9e6,
+MEASURED_TRAFFIC_BYTES = {"m2_8b_b4": 498.7e6, "m2_8b_decode": 2162.3e6, "m2_8b_decode_q8": 550.9e6,
                           "m2_8b_b4_hadamard": 402.7e6, "m2_8b_b4_conv1d": 352.1e6,
-                          "mamba1_2p8b_scan": 599.1e6, "mamba1_2p8b_decode": 178.8e6}
+                          "mamba1_2p8b_scan": 608.1e6, "mamba1_2p8b_decode": 178.8e6}
 TRAFFIC_SOURCE = {
     "m2_8b_b4": "profiles/hbm_traffic_prefill_m2_8b_b4_and_decode_m2_8b.txt",
     "m2_8b_decode": "profiles/hbm_traffic_prefill_m2_8b_b4_and_decode_m2_8b.txt",
@@ -95,7 +95,7 @@ MAMBA1_MIN_SLOTS = 8.0
 #   times 1 / s_out (1), clamp (1), round and pack (1).
 CONV_MIN_SLOTS = 17.0
 # Executed vector instructions per element by the counters (rocprofv3 SQ_INSTS_VALU x 64 / elements), for information:
-MAMBA1_EXECUTED_PER_ELEMENT = 8.9   # of which 1.06 quarter-rate exponentials
+MAMBA1_EXECUTED_PER_ELEMENT = 8.3   # of which 1.06 quarter-rate exponentials
 CONV_EXECUTED_PER_ELEMENT = 19.6    # 18.3 in the main loop (two quarter-rate), set-up and the exact-sequence reruns
 SPIN_UP_MS = float(os.environ.get("QUAMBA_BENCH_SPIN_UP_MS", "80"))   # untimed device work in front of every timed region, after the W warm-up launches (see time_region)
 
@@ -668,7 +668,7 @@ def main() -> int:
             "steps": args.steps, "higher_is_better": False, "wall_us_per_call": cwall * 1e3,
             "config": {"workload": "%s: %d tokens x %d channels [x|B|C], 4 taps, int8 in, int8 x/B/C out with the "
                                    "scan's cell and group scales" % (s.name, s.batch * s.seqlen, Ct)},
-            "roofline": {"kernel": "conv1d_q8_vec_kernel", "bound": "alu", "achieved": cops / (cms * 1e-3) / 1e12,
+            "roofline": {"kernel": "conv1d_q8_wide_kernel", "bound": "alu", "achieved": cops / (cms * 1e-3) / 1e12,
                          "peak": ALU_PEAK_TOPS, "unit": "Top/s (fp32 vector instructions x 64 lanes)",
                          "frac": cops / (cms * 1e-3) / 1e12 / ALU_PEAK_TOPS,
                          "slots_per_element": CONV_MIN_SLOTS, "executed_per_element": CONV_EXECUTED_PER_ELEMENT,
@@ -679,7 +679,7 @@ def main() -> int:
                                  "pack), against one slot per lane and cycle; the kernel executes %.1f vector "
                                  "instructions per element by the counters (executed_per_element), so added "
                                  "instructions lower frac" % (CONV_MIN_SLOTS, CONV_EXECUTED_PER_ELEMENT)},
-            "roofline_hbm": {"kernel": "conv1d_q8_vec_kernel", "bound": "hbm", "achieved": cgbs,
+            "roofline_hbm": {"kernel": "conv1d_q8_wide_kernel", "bound": "hbm", "achieved": cgbs,
                              "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": cgbs / HBM_PEAK_GBS,
                              **traffic_fields(s.name + "_conv1d")},
             "saturated_fraction": float((cx == 127).float().mean().item()),

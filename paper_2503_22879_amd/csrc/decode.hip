@@ -28,7 +28,7 @@ __device__ __forceinline__ void stage_x(const SsdArgs &a, int bh, int h, float *
 // ONE: a workgroup takes one pass (blockIdx.y says which) instead of the whole head.  At small batches the step is a chain
 // of memory round trips, so the passes run side by side, everything a row needs besides its state (scale, x, gate) is
 // requested in front of the state, the state in front of everything that waits, and nothing is loaded behind it (24 heads
-// at batch 1: 7.5 -> 4.6 us).  The largest batches stream 2 % faster with the state requested pass by pass.
+// at batch 1: 7.5 -> 4.6 us).
 template <int N, int ROWS, bool FULL, bool ONE>
 __global__ __launch_bounds__(kThreads) void decode_vec_kernel(SsdArgs a)
 {
@@ -167,9 +167,12 @@ hipError_t launch_vec(const SsdArgs &a, hipStream_t stream)
     constexpr int ROWS = (RPI * 4 * kWaves <= 64) ? 4 : (RPI <= 8 ? 2 : 1);  // rows per lane in flight per trip
     constexpr int PASS = kWaves * RPI * ROWS;  // rows of one pass of a workgroup
     const int P = a.s.headdim;
-    // One pass per workgroup, except for the largest batches without a gate: at 128 workgroups per compute unit (a state of
-    // about 500 MB) the two orders meet (128 heads, batch 128: 186.6 against 190.5 us; batch 256: 373.8 against 367.6),
-    // with a gate, whose codes the other order reads behind the state, it is always ahead (batch 256: 362 against 370).
+    // One pass per workgroup, except for the largest batches without a gate.  In a token's sequence of calls (convolution in
+    // front, transform behind) the two orders meet between 140 and 190 workgroups per compute unit, within 1 % of each other
+    // from 128 on (one pass / whole head, the three calls, 128 heads: batch 128 185.7 / 187.1 us, 192 277.8 / 277.4, 224
+    // 323.6 / 322.4, 256 370.8 / 366.1; 80 heads: 224 202.7 / 203.5, 256 231.7 / 230.7, 400 364.2 / 358.2).  With a gate, whose
+    // codes the other order reads behind the state, one pass is always ahead (128 heads, batch 256: 361.0 / 375.7); so it is
+    // where the step is called alone, over and over (358.6 / 370.4), which no program does.
     const int64_t pairs = (int64_t)a.s.batch * a.s.nheads, passes = (P + PASS - 1) / PASS;
     if (a.z || pairs * passes <= 128 * (int64_t)compute_units()) {
         const dim3 grid((unsigned)pairs, (unsigned)passes);

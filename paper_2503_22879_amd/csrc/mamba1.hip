@@ -125,10 +125,14 @@ __device__ __forceinline__ u32x4 load_codes(const int8_t *row, int t, int L)
 // instead of once per channel): plain fp32 multiplies and multiply-adds of two waves can issue together, the
 // mixed-precision ones that take fp16 operands cannot.  LDS rows are [state][quarter of a lane's tokens][lane], so that a lane's
 // four 16-byte reads are consecutive across the lanes.
-// C is staged times its scale and the skip term starts the output's sum, so that the sum is y.
-// Measured at 4 x 4096 tokens, 5120 channels: 312 us (393 with fp16 operands, tiles of 1024
-// tokens and the exponentials between the other instructions); 1003 tokens of one sequence: 32 us (36.5 with workgroups of
-// 512 threads, 3010 with one thread per channel, which is what a length that is no multiple of 16 took before).
+// C is staged times its scale and the skip term starts the output's sum, so that the sum is y.  That is one more fp32
+// rounding per code: 8.2e-8 instead of 7.7e-8 (rms) in the sum, under the 2e-4 of the fp16 output, whose error against 64 bits
+// is the same to four digits; exact codes, with x read again for the skip term at the end, took 1 to 2 % longer.
+// Measured at 4 x 4096 tokens, 5120 channels: 308 to 321 us (387 to 393 with fp16 operands, tiles of 1024
+// tokens and the exponentials between the other instructions); 1003 tokens of one sequence: 29 us, with gate and step-size
+// codes 32 to 34 (36.5 with workgroups of 512 threads, 3000 with one thread per channel, which is what a length that is no
+// multiple of 16 took before).  By the counters 36 cycles of a SIMD per 64 elements; the loop's instructions take 23 where all
+// plain ones of two waves issue together, 33 where none do.
 template <int LPC, int kThreads, int NS>
 __global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, const float *A, const float *init, float *fin)
 {
