@@ -70,7 +70,7 @@ def test_decode_passes_and_cluster_counts(gpu_lib, batch, P, N, m, n):
 
 
 def test_decode_full_batch(gpu_lib):
-    """configs[4] at full size (batch 256, 1 GiB state), 32 steps: y of every sequence against the fp64 oracle at every
+    """The 8B-shaped layer's step at full size (batch 256, 1 GiB state), 32 steps: y of every sequence against the fp64 oracle at every
     step, the whole state at the end (the oracle's fp64 state is 2 GiB of host memory)."""
     import torch
     q = gpu_lib

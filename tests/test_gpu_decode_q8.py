@@ -90,7 +90,7 @@ def test_q8_decode_clamps_like_the_oracle(gpu_lib):
 
 
 def test_q8_decode_full_batch(gpu_lib):
-    """configs[4] at full size (batch 256, 256 MiB of codes), 3 steps: the codes of every sequence bit for bit and
+    """The 8B-shaped layer's step at full size (batch 256, 256 MiB of codes), 3 steps: the codes of every sequence bit for bit and
     every y at every step (the numpy oracle walks the batch in slices of 32 sequences)."""
     import torch
     q = gpu_lib

@@ -83,7 +83,7 @@ NO_SPLIT = 0x4    # one workgroup per head even for small batches (the default s
 
 @pytest.mark.parametrize("flags", [0, GENERIC])
 def test_tiny_config(gpu_lib, flags):
-    """configs[0]: batch 1, seqlen 256, 8 heads x 64, d_state 16, chunk 64, 1x4 clusters, 2 outlier channels."""
+    """The tiny layer: batch 1, seqlen 256, 8 heads x 64, d_state 16, chunk 64, 1x4 clusters, 2 outlier channels."""
     s = W.CONFIGS["tiny"]
     sc, prob, _ = make_problem(s, 0)
     yref, href, _ = oracle.ref_prefill(sc, prob["x"], prob["B"], prob["C"], prob["dt"], prob["A"], prob["D"])
@@ -94,7 +94,7 @@ def test_tiny_config(gpu_lib, flags):
 @pytest.mark.parametrize("flags", [0, GENERIC, NO_SPLIT])
 @pytest.mark.parametrize("with_D", [True, False])
 def test_130m_shape(gpu_lib, flags, with_D):
-    """configs[1]: Mamba2-130M-shaped layer, seqlen 2048, 24 heads, d_state 128, chunk 256, 4x4 clusters."""
+    """Mamba2-130M-shaped layer, seqlen 2048, 24 heads, d_state 128, chunk 256, 4x4 clusters."""
     s = W.CONFIGS["m2_130m"]
     sc, prob, _ = make_problem(s, 1, with_D=with_D)
     yref, href, _ = oracle.ref_prefill(sc, prob["x"], prob["B"], prob["C"], prob["dt"], prob["A"], prob["D"])
@@ -469,7 +469,7 @@ def test_final_state_when_only_the_last_tokens_count(gpu_lib, L):
     """Decay of 2^-50 and more per token on every other head: the final state of such a head is the last token's
     term alone, sitting at the end of a ragged chunk behind a block prefix sum of thousands (log2 units).  Its weight
     is exp2 of the sum of dt*A over the tokens behind it, here exactly 1; formed as a difference of two prefix sums it
-    would be off by their rounding (1e-4 of the state, the whole spec allowance).  The bar here is half of the
+    would be off by their rounding (1e-4 of the state, the whole allowance).  The bar here is half of the
     allowance; what remains is the rounding of the two-term product (at most 2^-14).  L = 2333 takes the sequence
     split, whose state-pass kernel forms the same weights."""
     s = W.CONFIGS["m2_130m"].with_(seqlen=L, nheads=8)
@@ -649,7 +649,7 @@ def test_prefill_then_decode_matches_longer_prefill(gpu_lib):
 
 
 def test_2p7b_shape_full(gpu_lib):
-    """configs[2] at full size (batch 8, 80 heads, heavy-tailed outlier channels, final states returned): every
+    """The 2.7B-shaped layer at full size (batch 8, 80 heads, heavy-tailed outlier channels, final states returned): every
     (sequence, head) pair against the oracle, globally and cell by cell."""
     s = W.CONFIGS["m2_2p7b"]
     sc, prob, _ = make_problem(s, 2)
@@ -660,7 +660,7 @@ def test_2p7b_shape_full(gpu_lib):
 
 @pytest.mark.parametrize("batch", [1, 4])
 def test_8b_shape_full(gpu_lib, batch):
-    """configs[3] at full size, in the launch configuration bench.py times (batch 4) and with the channel split
+    """The 8B-shaped layer at full size, in the launch configuration bench.py times (batch 4) and with the channel split
     (batch 1): every (sequence, head) pair against the oracle, globally and in each of the 128 scale cells."""
     s = W.CONFIGS["m2_8b_b4"].with_(batch=batch)
     sc, prob, _ = make_problem(s, 3)
