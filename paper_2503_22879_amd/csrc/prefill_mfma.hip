@@ -35,6 +35,8 @@
 // (segment_state_kernel) walks all but the last segment without outputs and leaves every segment's end state (from a
 // zero start) and decay total in the workspace, then this kernel (SEG instantiations) gives every segment its own
 // workgroups, which start from the combination of the earlier segments' states (Eq. 2 is linear in the state).
+// Batches of at most half a pair per compute unit take prefill_wide_kernel (prefill_wide.hip) instead, or both where the
+// split is deep enough (prefill_mfma_plan).
 //
 // All of this is Eq. 2 with A-dot = exp(dt A), B-dot = dt B (Section 3.2) regrouped; the quantization scales of
 // Section 4.1 enter only in the epilogue because x enters linearly and channel-wise and B, C have one scale per
@@ -49,37 +51,12 @@
 #include <algorithm>
 #include <climits>
 
-#include "quamba_internal.h"
+#include "prefill_tiles.h"
 
 namespace quamba {
 namespace {
 
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kP = 64, kN = 128, kQ = 128, kBlk = 32, kNBlk = kQ / kBlk;
 constexpr int kThreads = 512;
-constexpr int kHsStride = 136;  // halves per row of H [p][n]
-constexpr int kBqStride = 144;  // bytes per row of Bq [token][n]
-constexpr float kNarrow = 1.0f / 128.0f;  // applied to G and H before narrowing to fp16; undone in the epilogue
-// Scales that keep every fp16 operand in the normal range.  x is staged as fp16 codes times kXs; the output
-// accumulators hold the output in code units times 2^-7 kAcc; the state accumulators the state times 2^-7 (kNarrow).
-// Hence the token weights on the score columns carry kAcc / kXs = 1/4 (score tiles, up to 2^14 after their own 2^-7,
-// times dt / 4 stay finite for dt up to 16), those on the rows of B carry kNarrow / kXs = 1/8 (dt / 8 times the decay
-// is far from the subnormals), and the C operand of the carried-state product carries kAcc.
-constexpr float kXs = 1.0f / 16.0f;
-constexpr float kAcc = 1.0f / 64.0f;
-// A product whose operands are separated by a decay factor below 2^-kDead (prefix sums are in log2 units) is left out
-// unless the caller asks for it: it is below 2.4e-10 of the term's own undecayed size.
-constexpr float kDead = 32.0f;
-
 // LDS map (bytes) for PT 32-channel tiles per workgroup.  Row pitches: with 4-byte banks, the 8 token rows x 16 bytes
 // a group of 16 lanes fetches from Bq fall into distinct banks (pitch of 36 banks), and so do the 4 token rows x 32
 // bytes that each of the two 16-lane groups of a half-wave fetches from x in the same cycle (pitch of 48 banks: rows
@@ -111,137 +88,6 @@ struct Lds {
     static_assert(kOffBq % 16 == 0 && kOffHs % 16 == 0 && kOffXs % 16 == 0, "LDS arrays must be 16-byte aligned");
 };
 static_assert(Lds<2>::kBytesGated <= 80 * 1024, "two workgroups must fit the 160 KB LDS of a gfx950 compute unit");
-
-// 2^x by the hardware instruction (prefix sums are carried in log2 units, so no multiply by log2 e is needed).
-__device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// LDS row of token s of the chunk: bits 2 and 3 swapped (see file comment).
-// Lane index recomputed where it is called: the mask passes through an empty asm statement, so the compiler can neither
-// hoist the result out of a loop nor keep it in a register across one.
-__device__ __forceinline__ int fresh_lane() {
-    unsigned m = ~0u;
-    asm volatile("" : "+s"(m));
-    return (int)__builtin_amdgcn_mbcnt_hi(m, __builtin_amdgcn_mbcnt_lo(m, 0u));
-}
-__device__ __forceinline__ int tok_pos(int s) { return (s & ~12) | ((s & 4) << 1) | ((s & 8) >> 1); }
-
-// Transposing LDS loads.  Inside each group of 16 lanes, result byte j of lane i comes from the 8 bytes addressed by
-// lane 2j + (i >> 3), byte i & 7 (8-bit form); result half j of lane i from the 8 bytes addressed by lane
-// 4j + (i >> 2), half i & 3 (16-bit form).  With source lane 2j + q pointing at (token row j, 8 columns starting at
-// 8q), resp. 4j + q at (token row j, 4 columns starting at 4q), lane i receives column i of 8 (resp. 4) token rows:
-// the layout of an MFMA operand whose k index is the token.
-typedef int v2i_lds __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ u32x2 lds_read_tr8(const unsigned char *p)
-{
-    return __builtin_bit_cast(
-        u32x2, __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) v2i_lds *)(p)));
-}
-__device__ __forceinline__ f16x4 lds_read_tr16(const unsigned char *p)
-{
-    typedef short v4s_lds __attribute__((ext_vector_type(4)));
-    return __builtin_bit_cast(
-        f16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s_lds *)(p)));
-}
-// 8 tokens x one column of fp16 x (two 4-token transposing loads, token rows r .. r+7 of the lane group)
-template <int PITCH_HALVES>
-__device__ __forceinline__ f16x8 lds_read_tr16x8(const unsigned char *p)
-{
-    const f16x4 lo = lds_read_tr16(p), hi = lds_read_tr16(p + 4 * 2 * PITCH_HALVES);
-    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-}
-
-// 8 int8 codes (two dwords, lowest address first) -> 8 exact fp16 values, one conversion per code: the source byte is
-// picked and sign-extended by the instruction's sub-dword source select, the result written to the low or high half of
-// the destination by its destination select (the high half keeps the low one).
-__device__ __forceinline__ uint32_t i8x2_to_f16_lo_hi(uint32_t w, int first_byte)
-{
-    uint32_t r;
-    if (first_byte == 0) {
-        asm("v_cvt_f16_i16_sdwa %0, sext(%1) dst_sel:WORD_0 dst_unused:UNUSED_PAD src0_sel:BYTE_0" : "=v"(r) : "v"(w));
-        asm("v_cvt_f16_i16_sdwa %0, sext(%1) dst_sel:WORD_1 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_1" : "+v"(r) : "v"(w));
-    } else {
-        asm("v_cvt_f16_i16_sdwa %0, sext(%1) dst_sel:WORD_0 dst_unused:UNUSED_PAD src0_sel:BYTE_2" : "=v"(r) : "v"(w));
-        asm("v_cvt_f16_i16_sdwa %0, sext(%1) dst_sel:WORD_1 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3" : "+v"(r) : "v"(w));
-    }
-    return r;
-}
-__device__ __forceinline__ f16x8 i8x8_to_f16(uint32_t w0, uint32_t w1)
-{
-    const u32x4 r = {i8x2_to_f16_lo_hi(w0, 0), i8x2_to_f16_lo_hi(w0, 2), i8x2_to_f16_lo_hi(w1, 0),
-                     i8x2_to_f16_lo_hi(w1, 2)};
-    return __builtin_bit_cast(f16x8, r);
-}
-
-// 4 int8 codes (one dword) -> fp16 values kXs * code, exact: byte^0x80 placed under the fp16 pattern of 64 (whose
-// last mantissa bit weighs 1/16) gives 64 + (code + 128) / 16; subtract 72.
-__device__ __forceinline__ f16x4 i8x4_to_f16_xs(uint32_t w)
-{
-    static_assert(kXs == 1.0f / 16.0f, "the bit pattern below encodes a step of 1/16");
-    const f16x2 bias = {(_Float16)72.0f, (_Float16)72.0f};
-    w ^= 0x80808080u;
-    union { f16x4 v; f16x2 h[2]; } r;
-    r.h[0] = __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(0x54545454u, w, 0x04010400u)) - bias;
-    r.h[1] = __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(0x54545454u, w, 0x04030402u)) - bias;
-    return r.v;
-}
-
-template <int CTRL, int ROW_MASK, bool BOUND>
-__device__ __forceinline__ float dpp_f32(float v)
-{
-    return __builtin_bit_cast(
-        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROW_MASK, 0xf, BOUND));
-}
-
-// Inclusive prefix sum over the 64 lanes of a wave with data-parallel-primitive moves only (no LDS round trips):
-// shifts by 1, 2, 4, 8 inside each row of 16 lanes (zero fill), then the last lane of row 0/2 is added to row 1/3
-// and the last lane of row 1 to rows 2 and 3.
-// `row` receives the scan inside the lane's row of 16 lanes alone (the first four steps).
-__device__ __forceinline__ float wave_inclusive_scan(float v, float &row)
-{
-    v += dpp_f32<0x111, 0xf, true>(v);   // row_shr:1
-    v += dpp_f32<0x112, 0xf, true>(v);   // row_shr:2
-    v += dpp_f32<0x114, 0xf, true>(v);   // row_shr:4
-    v += dpp_f32<0x118, 0xf, true>(v);   // row_shr:8
-    row = v;
-    v += dpp_f32<0x142, 0xa, false>(v);  // row_bcast:15 into rows 1 and 3
-    v += dpp_f32<0x143, 0xc, false>(v);  // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
-// Sum of the values of the lanes behind this one inside its row of 16 lanes (0 for the row's last lane): row shifts
-// towards lower lanes with zero fill.  Unlike the difference of two prefix sums it carries no rounding error of the
-// size of the sums in front of the lane.
-__device__ __forceinline__ float row_suffix_sum_exclusive(float v)
-{
-    float s = dpp_f32<0x101, 0xf, true>(v);  // row_shl:1
-    s += dpp_f32<0x101, 0xf, true>(s);
-    s += dpp_f32<0x102, 0xf, true>(s);       // row_shl:2
-    s += dpp_f32<0x104, 0xf, true>(s);       // row_shl:4
-    s += dpp_f32<0x108, 0xf, true>(s);       // row_shl:8
-    return s;
-}
-
-__device__ __forceinline__ f16x8 pack_f16x8(const float v[8])
-{
-    f16x8 r;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) r[j] = (_Float16)v[j];
-    return r;
-}
-
-// Workgroup -> (sequence, head).  Hardware hands consecutive workgroup ids to the 8 XCDs round-robin, each XCD with
-// its own L2.  When the number of (sequence, state group) units is a multiple of 8, all heads of a unit are put on
-// one XCD, so that the B and C rows they share are fetched into one L2 instead of eight.
-__device__ __forceinline__ int block_to_bh(const SsdArgs &a, int i)
-{
-    const int H = a.s.nheads, G = a.s.ngroups, hpg = H / G;
-    const int units = a.s.batch * G;
-    if (units % 8 != 0) return i;
-    const int x = i & 7, slot = i >> 3;
-    const int u = x + 8 * (slot / hpg), hl = slot % hpg;
-    const int b = u / G, g = u - b * G;
-    return b * H + g * hpg + hl;
-}
 
 // PT: 32-channel tiles per workgroup.  2: one workgroup per (sequence, head).  1: two workgroups per head, each with
 // half of the channels, its own half of the state and its own copy of the G^T work; chosen when there are fewer
@@ -1286,7 +1132,7 @@ hipError_t launch_scan_seg(const SsdArgs &a, hipStream_t stream)
 {
     constexpr int lds = GATED ? Lds<PT>::kBytesGated : Lds<PT>::kBytes;
     const int segs = a.nseg > 1 ? a.nseg : 1;  // one set of workgroups per segment
-    const dim3 grid((unsigned)(a.s.batch * a.s.nheads * (2 / PT) * segs));
+    const dim3 grid((unsigned)(a.pair_count * (2 / PT) * segs));
     const hipError_t e = allow_full_lds<prefill_mfma_kernel<PRECISE, PT, GATED, SEG>>();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((prefill_mfma_kernel<PRECISE, PT, GATED, SEG>), grid, dim3(kThreads), lds, stream, a);
@@ -1296,8 +1142,9 @@ hipError_t launch_scan_seg(const SsdArgs &a, hipStream_t stream)
 template <bool PRECISE, int PT, bool GATED>
 hipError_t launch_scan_gated(const SsdArgs &a, hipStream_t stream)
 {
-    return a.nseg > 1 ? launch_scan_seg<PRECISE, PT, GATED, true>(a, stream)
-                      : launch_scan_seg<PRECISE, PT, GATED, false>(a, stream);
+    if constexpr (PT == 2)  // segments of channel halves are the wide kernel's
+        if (a.nseg > 1) return launch_scan_seg<PRECISE, PT, GATED, true>(a, stream);
+    return launch_scan_seg<PRECISE, PT, GATED, false>(a, stream);
 }
 
 template <bool PRECISE, int PT>
@@ -1319,54 +1166,94 @@ hipError_t launch_segment_state(const SsdArgs &a, hipStream_t stream)
 }  // namespace
 
 // Few (sequence, head) pairs leave compute units idle, and a workgroup walks its sequence chunk by chunk.  Such
-// batches are cut along the sequence: with `pairs` workgroups per segment (twice that with the channel split) the
-// plan aims at two workgroups per compute unit, at least two chunks per segment and at most kMaxSegments segments.
+// batches may be cut along the sequence: with `pairs` workgroups per segment (twice that with channel halves) the
+// split aims at two workgroups per compute unit, at least two chunks per segment and at most kMaxSegments segments.
 constexpr int kMaxSegments = 8;
+
+namespace {
+
+struct Split {
+    int nseg = 1, seg_chunks = 0;
+    bool halves = false;  // of the channels
+    void cut(int nchunks, int segments)
+    {
+        seg_chunks = (nchunks + segments - 1) / segments;
+        nseg = (nchunks + seg_chunks - 1) / seg_chunks;  // every segment holds at least one chunk
+        if (nseg < 2) {
+            nseg = 1;
+            seg_chunks = 0;
+        }
+    }
+};
+
+// The most segments a call is cut into (what its workspace is sized for).  The split costs a second launch and a pass over
+// all but the last segment that only carries the state (about a third of the work of those tokens): it is left out below 8
+// chunks, and below 16 where the unsplit launch has a workgroup on every compute unit.
+Split largest_split(const quamba_ssd_shape_t &s)
+{
+    Split split;
+    const int64_t pairs = (int64_t)s.batch * s.nheads;
+    const int cus = compute_units();
+    const bool halves = !(s.flags & QUAMBA_FLAG_NO_CHANNEL_SPLIT) && pairs <= (int64_t)cus;
+    const int nchunks = (s.seqlen + kQ - 1) / kQ;
+    const int min_chunks = pairs * (halves ? 2 : 1) >= (int64_t)cus ? 16 : 8;
+    if ((s.flags & QUAMBA_FLAG_NO_SEQ_SPLIT) || !prefill_mfma_supports(s) || nchunks < min_chunks || pairs > (int64_t)cus)
+        return split;
+    // Whole heads (one workgroup per pair and segment) compute the score tiles once instead of twice, so the channel
+    // halves are kept only where even kMaxSegments segments of whole heads would not fill the compute units.
+    const int seg_cap = (int)std::min<int64_t>(kMaxSegments, nchunks / 2);
+    split.halves = halves && pairs * seg_cap < (int64_t)cus;
+    const int64_t fill = split.halves ? cus : 2 * (int64_t)cus;
+    split.cut(nchunks, (int)std::min<int64_t>(seg_cap, fill / pairs));
+    return split;
+}
+
+}  // namespace
+
+// Which kernel walks the sequences, and in how many segments.  The wide kernel (a workgroup of 16 waves per channel half,
+// one workgroup per compute unit) walks a chunk in 1.9 us, a lone workgroup of 8 waves in 2.7, two of them on a unit in 4.2
+// to 6; a single chunk is no faster (16 tokens of 128 heads 5.6 us, 8-wave kernel 5.4).  Where every half gets a compute unit of its own the cheapest of three is taken, by what they measured (microseconds,
+// with the final state; C chunks, 8 to 128 pairs, 4 to 64 chunks): the wide kernel unsplit 4.5 + 1.92 C; the wide kernel on S
+// segments that still get a unit each, 8 + 3.85 C / S with the state pass; whole heads in S segments, two workgroups on a unit,
+// 19 + 7.5 C / S.  (24 heads, 2048 tokens: 34.7, 23.2 with 5 segments, and 24.9 for 8 segments of channel halves of the 8-wave
+// kernel, which this replaces; 80 heads, 1024 / 4096 tokens: unsplit 20.7 / 66.1, whole heads 27.5 / 63.7; 128 heads, 2048
+// tokens: unsplit 37.8, whole heads 48.4.)
 PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s)
 {
     const int64_t pairs = (int64_t)s.batch * s.nheads;
     const int cus = compute_units();
+    const bool halves = !(s.flags & QUAMBA_FLAG_NO_CHANNEL_SPLIT) && pairs <= (int64_t)cus;
+    const Split most = largest_split(s);
     PrefillPlan plan;
-    // fewer (sequence, head) pairs than compute units: give every head two workgroups (half of the channels each)
-    plan.channel_split = !(s.flags & QUAMBA_FLAG_NO_CHANNEL_SPLIT) && pairs <= (int64_t)cus;
+    plan.wide = halves && 2 * pairs <= (int64_t)cus && s.seqlen > kQ;
+    plan.channel_split = halves;
     plan.nseg = 1;
     plan.seg_chunks = 0;
-    const int nchunks = (s.seqlen + kQ - 1) / kQ;
-    // The split costs a second launch and a pass over all but the last segment that only carries the state (about a
-    // third of the work of those tokens).  Measured on MI355X it pays from 8 chunks on where the unsplit launch leaves
-    // compute units empty, and from 16 chunks on where it already has a workgroup on every compute unit (the split
-    // then only buys the second workgroup per unit).
-    const int64_t unsplit_wgs = pairs * (plan.channel_split ? 2 : 1);
-    const int min_chunks = unsplit_wgs >= (int64_t)cus ? 16 : 8;
-    if ((s.flags & QUAMBA_FLAG_NO_SEQ_SPLIT) || !prefill_mfma_supports(s) || nchunks < min_chunks ||
-        pairs > (int64_t)cus)
-        return plan;
-    // Whole heads (one workgroup per pair and segment) compute the score tiles once instead of twice, so the channel
-    // split is kept only where even kMaxSegments segments of whole heads would not fill the compute units.
-    const int seg_cap = (int)std::min<int64_t>(kMaxSegments, nchunks / 2);
-    int nseg;
-    if (!plan.channel_split || pairs * seg_cap >= (int64_t)cus) {
-        plan.channel_split = false;
-        nseg = (int)std::min<int64_t>(seg_cap, (2 * (int64_t)cus) / pairs);
-    } else {
-        nseg = (int)std::min<int64_t>(seg_cap, (int64_t)cus / pairs);
+    if (most.nseg < 2) return plan;
+    Split split = most;
+    if (plan.wide) {
+        const int nchunks = (s.seqlen + kQ - 1) / kQ;
+        Split own;  // segments of the wide kernel
+        own.cut(nchunks, (int)std::min<int64_t>(most.nseg, cus / (2 * pairs)));
+        const int64_t unsplit = 450 + 192 * (int64_t)nchunks;
+        const int64_t cut = own.nseg < 2 ? INT64_MAX : 800 + 385 * (int64_t)own.seg_chunks;
+        const int64_t whole = most.halves ? INT64_MAX : 1900 + 750 * (int64_t)most.seg_chunks;
+        if (unsplit <= std::min(cut, whole)) return plan;
+        plan.wide = cut <= whole;
+        if (plan.wide) split = own;
     }
-    if (nseg < 2) return plan;
-    plan.seg_chunks = (nchunks + nseg - 1) / nseg;
-    plan.nseg = (nchunks + plan.seg_chunks - 1) / plan.seg_chunks;  // every segment holds at least one chunk
-    if (plan.nseg < 2) {
-        plan.nseg = 1;
-        plan.seg_chunks = 0;
-    }
+    plan.channel_split = plan.wide;
+    plan.nseg = split.nseg;
+    plan.seg_chunks = split.seg_chunks;
     return plan;
 }
 
 size_t prefill_mfma_workspace_bytes(const quamba_ssd_shape_t &s)
 {
-    const PrefillPlan plan = prefill_mfma_plan(s);
-    if (plan.nseg < 2) return 0;
+    const Split split = largest_split(s);
+    if (split.nseg < 2) return 0;
     const size_t pairs = (size_t)s.batch * s.nheads;
-    return sizeof(float) * (size_t)(plan.nseg - 1) * pairs * ((size_t)kP * kN + 1);
+    return sizeof(float) * (size_t)(split.nseg - 1) * pairs * ((size_t)kP * kN + 1);
 }
 
 hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t stream)
@@ -1379,13 +1266,15 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
     const size_t state_bytes = sizeof(float) * (size_t)a.s.batch * a.s.nheads * kP * kN;
     const uintptr_t i0 = reinterpret_cast<uintptr_t>(a.init_state), f0 = reinterpret_cast<uintptr_t>(a.state);
     const bool in_place = a.init_state && a.state && i0 < f0 + state_bytes && f0 < i0 + state_bytes;
+    const int64_t pairs = (int64_t)a.s.batch * a.s.nheads;
+    const int cus = compute_units();
     if (plan.nseg > 1 && (in_place || !workspace || reinterpret_cast<uintptr_t>(workspace) % 16 != 0)) {
         // also without a usable workspace (the entry point passes NULL when the caller's is missing or too small)
-        const int64_t pairs = (int64_t)a.s.batch * a.s.nheads;
-        plan.nseg = 1;
-        plan.channel_split = !(a.s.flags & QUAMBA_FLAG_NO_CHANNEL_SPLIT) && pairs <= (int64_t)compute_units();
+        a.s.flags |= QUAMBA_FLAG_NO_SEQ_SPLIT;
+        plan = prefill_mfma_plan(a.s);
     }
     auto launch = [&](const SsdArgs &args) {
+        if (plan.wide) return launch_prefill_wide(args, precise, stream);
         if (precise) return plan.channel_split ? launch_scan<true, 1>(args, stream) : launch_scan<true, 2>(args, stream);
         return plan.channel_split ? launch_scan<false, 1>(args, stream) : launch_scan<false, 2>(args, stream);
     };
@@ -1393,19 +1282,35 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
     a.seg_chunks = 0;
     a.seg_state = nullptr;
     a.seg_decay = nullptr;
+    a.pair_begin = 0;
+    a.pair_count = (int32_t)pairs;
     // Pacing of the two workgroups of a compute unit (see the kernel) pays when the whole launch is resident at once and
     // most compute units hold two workgroups that each walk many chunks; with more workgroups than that, the early finish
     // of the first arrivals is what lets the rest start, and pacing costs time (measured on 640 pairs).
-    const int cus = compute_units();
     auto pace = [&](int segs, int chunks_per_wg) {
-        const int64_t wgs = (int64_t)a.s.batch * a.s.nheads * (plan.channel_split ? 2 : 1) * segs;
+        const int64_t wgs = (int64_t)a.pair_count * (plan.channel_split ? 2 : 1) * segs;
         return (wgs > cus + cus / 2 && wgs <= 2 * (int64_t)cus && chunks_per_wg >= 8) ? cus : INT_MAX;
     };
     const int nchunks = (a.s.seqlen + kQ - 1) / kQ;
-    a.pace_first = pace(1, nchunks);
-    if (plan.nseg < 2) return launch(a);
+    if (plan.nseg < 2) {
+        // Workgroups of whole heads come in rounds of two per compute unit.  A second round that gives at most every other
+        // unit a workgroup goes to the wide kernel, in a launch of its own behind the (now paced) first: 640 pairs of 2048
+        // tokens 136 -> 132 us, 560 pairs 133 -> 125, 640 pairs of 1024 tokens 75 -> 70 (with the final state); with 4 chunks
+        // 39 -> 42, and behind two full rounds (1040 pairs) 110 -> 112, so both are left as one launch.
+        const int64_t rest = pairs - 2 * (int64_t)cus;
+        if (rest > 0 && 2 * rest <= (int64_t)cus && nchunks >= 8 && !(a.s.flags & QUAMBA_FLAG_NO_CHANNEL_SPLIT)) {
+            a.pair_count = (int32_t)(pairs - rest);
+            a.pace_first = pace(1, nchunks);
+            const hipError_t e = launch(a);
+            if (e != hipSuccess) return e;
+            a.pair_begin = a.pair_count;
+            a.pair_count = (int32_t)rest;
+            return launch_prefill_wide(a, precise, stream);
+        }
+        a.pace_first = pace(1, nchunks);
+        return launch(a);
+    }
 
-    const size_t pairs = (size_t)a.s.batch * a.s.nheads;
     a.nseg = plan.nseg;
     a.seg_chunks = plan.seg_chunks;
     a.seg_state = static_cast<float *>(workspace);

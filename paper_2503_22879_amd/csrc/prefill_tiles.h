@@ -1,0 +1,165 @@
+// Tiles, operand layouts and scales shared by the matrix-core prefill kernels (prefill_mfma.hip describes the arithmetic).
+#pragma once
+#include "quamba_internal.h"
+
+namespace quamba {
+namespace {
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kP = 64, kN = 128, kQ = 128, kBlk = 32, kNBlk = kQ / kBlk;
+constexpr int kHsStride = 136;  // halves per row of H [p][n]
+constexpr int kBqStride = 144;  // bytes per row of Bq [token][n]
+constexpr float kNarrow = 1.0f / 128.0f;  // applied to G and H before narrowing to fp16; undone in the epilogue
+// Scales that keep every fp16 operand in the normal range.  x is staged as fp16 codes times kXs; the output
+// accumulators hold the output in code units times 2^-7 kAcc; the state accumulators the state times 2^-7 (kNarrow).
+// Hence the token weights on the score columns carry kAcc / kXs = 1/4 (score tiles, up to 2^14 after their own 2^-7,
+// times dt / 4 stay finite for dt up to 16), those on the rows of B carry kNarrow / kXs = 1/8 (dt / 8 times the decay
+// is far from the subnormals), and the C operand of the carried-state product carries kAcc.
+constexpr float kXs = 1.0f / 16.0f;
+constexpr float kAcc = 1.0f / 64.0f;
+// A product whose operands are separated by a decay factor below 2^-kDead (prefix sums are in log2 units) is left out
+// unless the caller asks for it: it is below 2.4e-10 of the term's own undecayed size.
+constexpr float kDead = 32.0f;
+
+// 2^x by the hardware instruction (prefix sums are carried in log2 units, so no multiply by log2 e is needed).
+__device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// LDS row of token s of the chunk: bits 2 and 3 swapped (see file comment).
+// Lane index recomputed where it is called: the mask passes through an empty asm statement, so the compiler can neither
+// hoist the result out of a loop nor keep it in a register across one.
+__device__ __forceinline__ int fresh_lane() {
+    unsigned m = ~0u;
+    asm volatile("" : "+s"(m));
+    return (int)__builtin_amdgcn_mbcnt_hi(m, __builtin_amdgcn_mbcnt_lo(m, 0u));
+}
+__device__ __forceinline__ int tok_pos(int s) { return (s & ~12) | ((s & 4) << 1) | ((s & 8) >> 1); }
+
+// Transposing LDS loads.  Inside each group of 16 lanes, result byte j of lane i comes from the 8 bytes addressed by
+// lane 2j + (i >> 3), byte i & 7 (8-bit form); result half j of lane i from the 8 bytes addressed by lane
+// 4j + (i >> 2), half i & 3 (16-bit form).  With source lane 2j + q pointing at (token row j, 8 columns starting at
+// 8q), resp. 4j + q at (token row j, 4 columns starting at 4q), lane i receives column i of 8 (resp. 4) token rows:
+// the layout of an MFMA operand whose k index is the token.
+typedef int v2i_lds __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u32x2 lds_read_tr8(const unsigned char *p)
+{
+    return __builtin_bit_cast(
+        u32x2, __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) v2i_lds *)(p)));
+}
+__device__ __forceinline__ f16x4 lds_read_tr16(const unsigned char *p)
+{
+    typedef short v4s_lds __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(
+        f16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s_lds *)(p)));
+}
+// 8 tokens x one column of fp16 x (two 4-token transposing loads, token rows r .. r+7 of the lane group)
+template <int PITCH_HALVES>
+__device__ __forceinline__ f16x8 lds_read_tr16x8(const unsigned char *p)
+{
+    const f16x4 lo = lds_read_tr16(p), hi = lds_read_tr16(p + 4 * 2 * PITCH_HALVES);
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// 8 int8 codes (two dwords, lowest address first) -> 8 exact fp16 values, one conversion per code: the source byte is
+// picked and sign-extended by the instruction's sub-dword source select, the result written to the low or high half of
+// the destination by its destination select (the high half keeps the low one).
+__device__ __forceinline__ uint32_t i8x2_to_f16_lo_hi(uint32_t w, int first_byte)
+{
+    uint32_t r;
+    if (first_byte == 0) {
+        asm("v_cvt_f16_i16_sdwa %0, sext(%1) dst_sel:WORD_0 dst_unused:UNUSED_PAD src0_sel:BYTE_0" : "=v"(r) : "v"(w));
+        asm("v_cvt_f16_i16_sdwa %0, sext(%1) dst_sel:WORD_1 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_1" : "+v"(r) : "v"(w));
+    } else {
+        asm("v_cvt_f16_i16_sdwa %0, sext(%1) dst_sel:WORD_0 dst_unused:UNUSED_PAD src0_sel:BYTE_2" : "=v"(r) : "v"(w));
+        asm("v_cvt_f16_i16_sdwa %0, sext(%1) dst_sel:WORD_1 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3" : "+v"(r) : "v"(w));
+    }
+    return r;
+}
+__device__ __forceinline__ f16x8 i8x8_to_f16(uint32_t w0, uint32_t w1)
+{
+    const u32x4 r = {i8x2_to_f16_lo_hi(w0, 0), i8x2_to_f16_lo_hi(w0, 2), i8x2_to_f16_lo_hi(w1, 0),
+                     i8x2_to_f16_lo_hi(w1, 2)};
+    return __builtin_bit_cast(f16x8, r);
+}
+
+// 4 int8 codes (one dword) -> fp16 values kXs * code, exact: byte^0x80 placed under the fp16 pattern of 64 (whose
+// last mantissa bit weighs 1/16) gives 64 + (code + 128) / 16; subtract 72.
+__device__ __forceinline__ f16x4 i8x4_to_f16_xs(uint32_t w)
+{
+    static_assert(kXs == 1.0f / 16.0f, "the bit pattern below encodes a step of 1/16");
+    const f16x2 bias = {(_Float16)72.0f, (_Float16)72.0f};
+    w ^= 0x80808080u;
+    union { f16x4 v; f16x2 h[2]; } r;
+    r.h[0] = __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(0x54545454u, w, 0x04010400u)) - bias;
+    r.h[1] = __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(0x54545454u, w, 0x04030402u)) - bias;
+    return r.v;
+}
+
+template <int CTRL, int ROW_MASK, bool BOUND>
+__device__ __forceinline__ float dpp_f32(float v)
+{
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROW_MASK, 0xf, BOUND));
+}
+
+// Inclusive prefix sum over the 64 lanes of a wave with data-parallel-primitive moves only (no LDS round trips):
+// shifts by 1, 2, 4, 8 inside each row of 16 lanes (zero fill), then the last lane of row 0/2 is added to row 1/3
+// and the last lane of row 1 to rows 2 and 3.
+// `row` receives the scan inside the lane's row of 16 lanes alone (the first four steps).
+__device__ __forceinline__ float wave_inclusive_scan(float v, float &row)
+{
+    v += dpp_f32<0x111, 0xf, true>(v);   // row_shr:1
+    v += dpp_f32<0x112, 0xf, true>(v);   // row_shr:2
+    v += dpp_f32<0x114, 0xf, true>(v);   // row_shr:4
+    v += dpp_f32<0x118, 0xf, true>(v);   // row_shr:8
+    row = v;
+    v += dpp_f32<0x142, 0xa, false>(v);  // row_bcast:15 into rows 1 and 3
+    v += dpp_f32<0x143, 0xc, false>(v);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// Sum of the values of the lanes behind this one inside its row of 16 lanes (0 for the row's last lane): row shifts
+// towards lower lanes with zero fill.  Unlike the difference of two prefix sums it carries no rounding error of the
+// size of the sums in front of the lane.
+__device__ __forceinline__ float row_suffix_sum_exclusive(float v)
+{
+    float s = dpp_f32<0x101, 0xf, true>(v);  // row_shl:1
+    s += dpp_f32<0x101, 0xf, true>(s);
+    s += dpp_f32<0x102, 0xf, true>(s);       // row_shl:2
+    s += dpp_f32<0x104, 0xf, true>(s);       // row_shl:4
+    s += dpp_f32<0x108, 0xf, true>(s);       // row_shl:8
+    return s;
+}
+
+__device__ __forceinline__ f16x8 pack_f16x8(const float v[8])
+{
+    f16x8 r;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) r[j] = (_Float16)v[j];
+    return r;
+}
+
+// Workgroup -> (sequence, head).  Hardware hands consecutive workgroup ids to the 8 XCDs round-robin, each XCD with
+// its own L2.  When the number of (sequence, state group) units is a multiple of 8, all heads of a unit are put on
+// one XCD, so that the B and C rows they share are fetched into one L2 instead of eight.
+__device__ __forceinline__ int block_to_bh(const SsdArgs &a, int i)
+{
+    const int H = a.s.nheads, G = a.s.ngroups, hpg = H / G;
+    const int units = a.s.batch * G;
+    if (units % 8 != 0) return i;
+    const int x = i & 7, slot = i >> 3;
+    const int u = x + 8 * (slot / hpg), hl = slot % hpg;
+    const int b = u / G, g = u - b * G;
+    return b * H + g * hpg + hl;
+}
+
+}  // namespace
+}  // namespace quamba

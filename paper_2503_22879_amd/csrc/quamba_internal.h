@@ -76,14 +76,17 @@ struct SsdArgs {
     int32_t pace_first;        // matrix-core prefill: first workgroup id of the second dispatch round when the two
                                // workgroups of a compute unit are to be kept at the same pace (see the kernel), else
                                // INT_MAX
+    int32_t pair_begin;        // matrix-core prefill: the (sequence, head) pairs of the launch, in the order of the
+    int32_t pair_count;        // workgroup map
 };
 
-// Plan of the sequence split for a shape on the current device: segments (1 = no split), chunks per segment, and
-// whether every head is cut into two workgroups of 32 channels each.
+// Plan of the matrix-core prefill for a shape on the current device: segments of the sequence split (1 = no split), chunks
+// per segment, whether every head is cut into two workgroups of 32 channels each, and whether those are the wide kernel's.
 struct PrefillPlan {
     int nseg;
     int seg_chunks;
     bool channel_split;
+    bool wide;
 };
 PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s);
 size_t prefill_mfma_workspace_bytes(const quamba_ssd_shape_t &s);
@@ -314,6 +317,7 @@ bool mamba1_scan_supports_any(const quamba_ssd_shape_t &s);
 hipError_t launch_prefill_generic(const SsdArgs &a, hipStream_t stream);
 bool prefill_mfma_supports(const quamba_ssd_shape_t &s);
 hipError_t launch_prefill_mfma(const SsdArgs &a, void *workspace, hipStream_t stream);
+hipError_t launch_prefill_wide(const SsdArgs &a, bool precise, hipStream_t stream);
 bool prefill_generic_supports(const quamba_ssd_shape_t &s);
 
 }  // namespace quamba

@@ -154,6 +154,49 @@ def test_sequence_split_against_the_oracle_and_the_unsplit_launch(gpu_lib, H, G,
             assert np.abs(hg - hu).max() <= 2e-5 * np.abs(hu).max()
 
 
+@pytest.mark.parametrize("b,H,G,L,tiny_scales", [
+    (1, 5, 1, 129, False),     # two chunks, the second a single token; workgroup ids past the last group of 8 pairs
+    (3, 8, 8, 160, False),     # the second chunk one whole block
+    (1, 128, 8, 161, False),   # a workgroup on every compute unit, the second chunk a block and a token
+    (2, 3, 1, 256, False),     # whole chunks only
+    (1, 24, 1, 385, False),    # four chunks: both LDS sets are used again
+    (1, 40, 1, 2040, False),   # three segments of the sequence split, the last one ragged
+    (2, 5, 1, 161, True),      # the skip term leaves the fp16 range: added in the epilogue
+])
+def test_short_batches_on_workgroups_of_sixteen_waves(gpu_lib, b, H, G, L, tiny_scales):
+    """At most half a (sequence, head) pair per compute unit and more than one chunk, with and without the final state and
+    an initial state: against the oracle."""
+    s = W.CONFIGS["m2_8b_b1"].with_(batch=b, seqlen=L, nheads=H, ngroups=G)
+    sc, prob, _ = make_problem(s, 77, calib_tokens=256)
+    if tiny_scales:
+        sc.B_scales[:] *= np.float32(1e-5)
+        sc.C_scales[:] *= np.float32(1e-5)
+    h0 = W.draw_state(s, 77).astype(np.float32) * np.float32(1e-5 if tiny_scales else 1.0)
+    cells = oracle.cell_index_table(sc, s.nheads, s.headdim, s.ngroups)
+    for init in (None, h0):
+        yref, href, _ = oracle.ref_prefill(sc, prob["x"], prob["B"], prob["C"], prob["dt"], prob["A"], prob["D"],
+                                           init_state=None if init is None else init.astype(np.float64))
+        for want_state in (True, False):
+            yg, hg = run_prefill(gpu_lib, s, sc, prob, 0, init_state=init, want_state=want_state)
+            check(yg, hg, yref, href if want_state else None, f"b={b} H={H} L={L} init={init is not None}", cells=cells)
+
+
+def test_second_round_of_a_few_pairs(gpu_lib):
+    """640 (sequence, head) pairs of 9 chunks, the last one ragged: the 128 pairs behind the first 512 run in a launch of
+    their own.  Pairs of both, against the oracle."""
+    s = W.CONFIGS["m2_8b_b1"].with_(batch=5, seqlen=1030)
+    sc, prob, _ = make_problem(s, 78, calib_tokens=256)
+    pairs = [(0, 0), (1, 63), (3, 127), (4, 0), (4, 77), (4, 127)]
+    yref, href, _ = oracle.ref_prefill(sc, prob["x"], prob["B"], prob["C"], prob["dt"], prob["A"], prob["D"], pairs=pairs)
+    yg, hg = run_prefill(gpu_lib, s, sc, prob)
+    assert np.isfinite(yg).all() and np.isfinite(hg).all()
+    for k, (i, h) in enumerate(pairs):
+        ey = np.abs(yg[i, :, h] - yref[k]).max() / np.abs(yref[k]).max()
+        eh = np.abs(hg[i, h] - href[k]).max() / np.abs(href[k]).max()
+        print(f"pair ({i}, {h}): y err {ey:.3e}, state err {eh:.3e}")
+        assert ey <= Y_TOL and eh <= H_TOL
+
+
 def _random_split_cases(n, seed):
     rng = np.random.default_rng(seed)
     cases = []
