@@ -22,6 +22,7 @@ namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32_u __attribute__((aligned(2)));  // the hardware stores dwords at any address
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23: adding it rounds to nearest even, the code is the sum's low byte
@@ -279,9 +280,17 @@ __global__ __launch_bounds__(256) void hadamard_quantize_mixed_kernel(const uint
 // <= 10, 16-byte aligned rows): phase A, strides 1..16 on the 32 consecutive values a thread loads; exchange through
 // LDS, transposed inside super-blocks of 1024 values like the power-of-two kernel's first exchange; phase B, strides
 // 32..p/2 on values 32 apart (a thread's 32 values span 1024 / p blocks, the butterflies stay inside each); exchange
-// in plain order; phase C, for 2 consecutive positions the M-point sum over the blocks in ascending order, Eq. 1, one
-// 2-byte store per block.  A row need not fill its last super-block: the missing part is never written, and what
-// phase B reads of it stays in register groups of its own that are not used.
+// in plain order; phase C, for one position per thread the M-point sum over the blocks in ascending order (rows with the
+// same signs up to a block share its partial sum: 332 adds for M = 20), Eq. 1, and an exchange inside quads of lanes that
+// turns the codes of four rows at one position into those of one row at four positions, a dword to store.  A row need not
+// fill its last super-block: the missing part is never written, and what phase B reads of it stays in register groups of
+// its own that are not used.
+// Phase C is two thirds of the vector instructions.  With two positions per thread it ran on half the waves a row has now, two
+// of a row's three, at 5 waves per SIMD, and LDS (23 KB a row) admits no more rows: one position and 7 waves per SIMD take
+// 16384 rows of 5120 values from 74.7 to 69.7 us (3.6 TB/s), 3000 from 16.7 to 14.4, 256 from 4.4 to 3.6; of 1536 values from 21.3
+// to 18.2.  Not faster: two or four rows to a workgroup, which leaves no lane idle in phases A and B (62.8 against 59.0 us on
+// rows in the last-level cache); a loop over rows with the next one's loads in flight (74.4); the sums of 4 to 16 of the
+// rows as v_mfma_f32_4x4x1_16b_f32, bit for bit the same (70 to 79 against 65).
 template <int M, int LOGP>
 __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *out, float inv_s)
 {
@@ -289,8 +298,8 @@ __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *o
     extern __shared__ float lds[];  // NSB * 1152 floats
     const int t = threadIdx.x;
     const size_t row = (size_t)blockIdx.x * N;
-    float v[32];
     if (t < T) {
+        float v[32];
         const u32x4 *src = reinterpret_cast<const u32x4 *>(y + row + 32 * t);
         u32x4 nx[4];
 #pragma unroll
@@ -311,6 +320,7 @@ __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *o
     }
     __syncthreads();
     const int t_lo = t & 31, t_hi = t >> 5;
+    float v[32];
     if (t_hi < NSB) {
         // phase B: values i = t_lo + 32 e + 1024 t_hi, e = 0..31; e's low LOGP - 5 bits are the strides 32..p/2
         const f32x4 *pb = reinterpret_cast<const f32x4 *>(lds + 36 * t_lo + 1152 * t_hi);
@@ -329,25 +339,28 @@ __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *o
             if (1024 * t_hi + 32 * e < N) pb[32 * e] = v[e];  // uniform per wave half: whole groups of 32 lanes
     }
     __syncthreads();
-    if (t < P / 2) {
-        // phase C: positions 2 t and 2 t + 1 of every block
-        float t0[M], t1[M];
+    // phase C: position t of every block, four rows of the M-point sums at a time
+    float x[M];
 #pragma unroll
-        for (int b = 0; b < M; ++b) {
-            t0[b] = lds[b * P + 2 * t];
-            t1[b] = lds[b * P + 2 * t + 1];
+    for (int b = 0; b < M; ++b) x[b] = lds[b * P + t];
+    int8_t *dst = out + row + (size_t)(t & 3) * P + (t & ~3);
+    const uint32_t sel1 = t & 1 ? 0x03070105u : 0x06020400u, sel2 = t & 2 ? 0x03020706u : 0x05040100u;
+#pragma unroll
+    for (int a = 0; a < M; a += 4) {
+        float sc[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float acc = x[0] * paley_sign<M>(a + i, 0);
+#pragma unroll
+            for (int b = 1; b < M; ++b) acc = acc + x[b] * paley_sign<M>(a + i, b);
+            sc[i] = acc * inv_s;
         }
-#pragma unroll
-        for (int a = 0; a < M; ++a) {
-            float a0 = t0[0] * paley_sign<M>(a, 0), a1 = t1[0] * paley_sign<M>(a, 0);
-#pragma unroll
-            for (int b = 1; b < M; ++b) {
-                a0 = a0 + t0[b] * paley_sign<M>(a, b);
-                a1 = a1 + t1[b] * paley_sign<M>(a, b);
-            }
-            const float sc[4] = {a0 * inv_s, a1 * inv_s, 0.0f, 0.0f};
-            *reinterpret_cast<uint16_t *>(out + row + (size_t)a * P + 2 * t) = (uint16_t)codes_packed<2>(sc);
-        }
+        // a lane's dword holds the codes of rows a .. a + 3; after the exchange inside the quad, of four positions of row
+        // a + t % 4
+        const uint32_t w = codes_packed<4>(sc);
+        const uint32_t w1 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w, 0xB1, 0xf, 0xf, true), w, sel1);
+        const uint32_t w2 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w1, 0x4E, 0xf, 0xf, true), w1, sel2);
+        __builtin_nontemporal_store(w2, reinterpret_cast<u32_u *>(dst + (size_t)a * P));
     }
 }
 
@@ -355,8 +368,8 @@ template <int M, int LOGP>
 hipError_t launch_mixed_fast(const uint16_t *y, int64_t rows, float inv_s, int8_t *out, hipStream_t stream)
 {
     constexpr int P = 1 << LOGP, N = M * P, NSB = (N + 1023) / 1024;
-    constexpr int need = N / 32 > 32 * NSB ? N / 32 : 32 * NSB;
-    constexpr int threads = ((need > P / 2 ? need : P / 2) + 63) / 64 * 64;
+    constexpr int threads = P;
+    static_assert(threads >= N / 32 && threads >= 32 * NSB, "every phase has its threads");
     constexpr int lds = NSB * 1152 * (int)sizeof(float);
     static_assert(threads <= 1024 && lds <= 160 * 1024, "launch shape");
     if (lds > 48 * 1024) {

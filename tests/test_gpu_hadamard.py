@@ -93,6 +93,22 @@ def test_subnormal_and_extreme_fp16_inputs(gpu_lib):
     _check(_run(gpu_lib, big, s_big), big, s_big)
 
 
+@pytest.mark.parametrize("n", [1536, 2560, 3072, 5120, 6144])
+@pytest.mark.parametrize("off", [0, 2])
+def test_mixed_orders_store_dwords_at_even_addresses(gpu_lib, n, off):
+    """The register-blocked kernel of the orders 12 * 2^k and 20 * 2^k stores four codes at a time, at any even address;
+    bytes in front of and behind the output stay as they are."""
+    import torch
+    rows = 5
+    y16, sigma = W.draw_ssd_output(rows, n, seed=n + off, outlier_frac=0.01)
+    s_y = _scale(sigma, k=3.0)
+    buf = torch.full((rows * n + 8,), 77, dtype=torch.int8, device="cuda")
+    out = buf[off:off + rows * n].view(rows, n)
+    gpu_lib.quamba_hadamard_quantize(torch.from_numpy(y16).cuda(), s_y, out)
+    assert np.array_equal(out.cpu().numpy(), oracle.hadamard_quantize(y16, s_y))
+    assert (buf[:off] == 77).all() and (buf[off + rows * n:] == 77).all()
+
+
 def test_unaligned_pointers_and_leading_axes(gpu_lib):
     """A view that starts 2 bytes into an allocation takes the path without 16-byte loads; leading axes flatten."""
     import torch
