@@ -1,6 +1,6 @@
 // Chunked prefill of the 8-bit SSD on the gfx950 matrix cores.
 //
-// One workgroup (8 waves) owns one (sequence, head), or half of a head's channels when the batch is too small to
+// One workgroup (8 waves) owns one (sequence, head), or half of a head's channels when a short batch is too small to
 // fill the chip, and walks it in chunks of kQ = 128 tokens; the head's state never leaves the chip.  The waves split
 // into two roles that run side by side between the two barriers of a chunk: waves 0..3 produce the outputs (each owns
 // one 32-token block of the chunk), waves 4..7 own the state (each a quarter of its columns): they stage the chunk into
@@ -35,8 +35,8 @@
 // (segment_state_kernel) walks all but the last segment without outputs and leaves every segment's end state (from a
 // zero start) and decay total in the workspace, then this kernel (SEG instantiations) gives every segment its own
 // workgroups, which start from the combination of the earlier segments' states (Eq. 2 is linear in the state).
-// Batches of at most half a pair per compute unit take prefill_wide_kernel (prefill_wide.hip) instead, or both where the
-// split is deep enough (prefill_mfma_plan).
+// Batches of at most a pair per compute unit take prefill_wide_kernel (prefill_wide.hip) instead, unless the split is deep
+// enough or the sequences are of one chunk (prefill_mfma_plan).
 //
 // All of this is Eq. 2 with A-dot = exp(dt A), B-dot = dt B (Section 3.2) regrouped; the quantization scales of
 // Section 4.1 enter only in the epilogue because x enters linearly and channel-wise and B, C have one scale per
@@ -90,8 +90,8 @@ struct Lds {
 static_assert(Lds<2>::kBytesGated <= 80 * 1024, "two workgroups must fit the 160 KB LDS of a gfx950 compute unit");
 
 // PT: 32-channel tiles per workgroup.  2: one workgroup per (sequence, head).  1: two workgroups per head, each with
-// half of the channels, its own half of the state and its own copy of the G^T work; chosen when there are fewer
-// heads in the batch than compute units, so that the whole chip works on short batches.
+// half of the channels, its own half of the state and its own copy of the G^T work; chosen for sequences of one chunk
+// when there is at most half a pair per compute unit, so that the whole chip works on short batches.
 // GATED: the output is multiplied by SiLU(z) of the caller's int8 gate codes (Section 3.2) in the epilogue.
 // SEG: the launch belongs to a sequence split (see SsdArgs); the instantiations without it carry none of its code.
 template <bool PRECISE, int PT, bool GATED, bool SEG>
@@ -1210,32 +1210,34 @@ Split largest_split(const quamba_ssd_shape_t &s)
 
 }  // namespace
 
-// Which kernel walks the sequences, and in how many segments.  The wide kernel (a workgroup of 16 waves per channel half,
-// one workgroup per compute unit) walks a chunk in 1.9 us, a lone workgroup of 8 waves in 2.7, two of them on a unit in 4.2
-// to 6; a single chunk is no faster (16 tokens of 128 heads 5.6 us, 8-wave kernel 5.4).  Where every half gets a compute unit of its own the cheapest of three is taken, by what they measured (microseconds,
-// with the final state; C chunks, 8 to 128 pairs, 4 to 64 chunks): the wide kernel unsplit 4.5 + 1.92 C; the wide kernel on S
-// segments that still get a unit each, 8 + 3.85 C / S with the state pass; whole heads in S segments, two workgroups on a unit,
-// 19 + 7.5 C / S.  (24 heads, 2048 tokens: 34.7, 23.2 with 5 segments, and 24.9 for 8 segments of channel halves of the 8-wave
-// kernel, which this replaces; 80 heads, 1024 / 4096 tokens: unsplit 20.7 / 66.1, whole heads 27.5 / 63.7; 128 heads, 2048
-// tokens: unsplit 37.8, whole heads 48.4.)
+// Which kernel walks the sequences, and in how many segments.  The wide kernel (workgroups of 16 waves, one to a compute
+// unit) walks a chunk of a channel half in 1.9 us and of a whole head in 2.8, a lone workgroup of 8 waves in 2.7, two of them on
+// a unit in 4.2 to 6.  A single chunk is no faster on it: 16 tokens of 128 heads 6.0 us, 8-wave kernel in channel halves 5.5; of
+// 192 heads 7.0, whole heads 6.5.  From two chunks on the cheapest of three is taken, by what they measured (microseconds, with
+// the final state; C chunks, 8 to 256 pairs, 2 to 64 chunks): the wide kernel unsplit, 4.5 + 1.92 C where every channel half
+// gets a unit of its own, else 5.5 + 2.83 C; channel halves in S segments that still get a unit each, 8 + 3.85 C / S with the
+// state pass; whole heads of the 8-wave kernel in S segments, two workgroups on a unit, 19 + 7.5 C / S.  (24 heads, 2048 tokens:
+// 34.7, 23.2 with 5 segments, and 24.9 for 8 segments of channel halves of the 8-wave kernel, which this replaces; 80 heads,
+// 1024 / 4096 tokens: unsplit 20.7 / 66.1, whole heads 27.5 / 63.7; 128 heads, 2048 tokens: unsplit 37.8, whole heads 48.4; 160
+// pairs, 2500 / 4096 tokens: unsplit 62.4 / 96.7, whole heads 68.6 / 96.1.)
 PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s)
 {
     const int64_t pairs = (int64_t)s.batch * s.nheads;
     const int cus = compute_units();
-    const bool halves = !(s.flags & QUAMBA_FLAG_NO_CHANNEL_SPLIT) && pairs <= (int64_t)cus;
+    const bool few = !(s.flags & QUAMBA_FLAG_NO_CHANNEL_SPLIT) && pairs <= (int64_t)cus;
     const Split most = largest_split(s);
     PrefillPlan plan;
-    plan.wide = halves && 2 * pairs <= (int64_t)cus && s.seqlen > kQ;
-    plan.channel_split = halves;
+    plan.wide = few && s.seqlen > kQ;
+    plan.channel_split = few && 2 * pairs <= (int64_t)cus;
     plan.nseg = 1;
     plan.seg_chunks = 0;
     if (most.nseg < 2) return plan;
     Split split = most;
     if (plan.wide) {
         const int nchunks = (s.seqlen + kQ - 1) / kQ;
-        Split own;  // segments of the wide kernel
-        own.cut(nchunks, (int)std::min<int64_t>(most.nseg, cus / (2 * pairs)));
-        const int64_t unsplit = 450 + 192 * (int64_t)nchunks;
+        Split own;  // segments of the wide kernel's channel halves
+        if (plan.channel_split) own.cut(nchunks, (int)std::min<int64_t>(most.nseg, cus / (2 * pairs)));
+        const int64_t unsplit = plan.channel_split ? 450 + 192 * (int64_t)nchunks : 550 + 283 * (int64_t)nchunks;
         const int64_t cut = own.nseg < 2 ? INT64_MAX : 800 + 385 * (int64_t)own.seg_chunks;
         const int64_t whole = most.halves ? INT64_MAX : 1900 + 750 * (int64_t)most.seg_chunks;
         if (unsplit <= std::min(cut, whole)) return plan;
@@ -1274,7 +1276,7 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
         plan = prefill_mfma_plan(a.s);
     }
     auto launch = [&](const SsdArgs &args) {
-        if (plan.wide) return launch_prefill_wide(args, precise, stream);
+        if (plan.wide) return launch_prefill_wide(args, plan.channel_split, precise, stream);
         if (precise) return plan.channel_split ? launch_scan<true, 1>(args, stream) : launch_scan<true, 2>(args, stream);
         return plan.channel_split ? launch_scan<false, 1>(args, stream) : launch_scan<false, 2>(args, stream);
     };
@@ -1296,7 +1298,8 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
         // Workgroups of whole heads come in rounds of two per compute unit.  A second round that gives at most every other
         // unit a workgroup goes to the wide kernel, in a launch of its own behind the (now paced) first: 640 pairs of 2048
         // tokens 136 -> 132 us, 560 pairs 133 -> 125, 640 pairs of 1024 tokens 75 -> 70 (with the final state); with 4 chunks
-        // 39 -> 42, and behind two full rounds (1040 pairs) 110 -> 112, so both are left as one launch.
+        // 39 -> 42, and behind two full rounds (1040 pairs) 110 -> 112, so both are left as one launch; so are second rounds of up
+        // to a workgroup per unit (768 pairs of 1024 tokens 81 -> 83 with whole heads on the wide kernel, 720 of 2048 157 -> 155).
         const int64_t rest = pairs - 2 * (int64_t)cus;
         if (rest > 0 && 2 * rest <= (int64_t)cus && nchunks >= 8 && !(a.s.flags & QUAMBA_FLAG_NO_CHANNEL_SPLIT)) {
             a.pair_count = (int32_t)(pairs - rest);
@@ -1305,7 +1308,7 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
             if (e != hipSuccess) return e;
             a.pair_begin = a.pair_count;
             a.pair_count = (int32_t)rest;
-            return launch_prefill_wide(a, precise, stream);
+            return launch_prefill_wide(a, true, precise, stream);
         }
         a.pace_first = pace(1, nchunks);
         return launch(a);

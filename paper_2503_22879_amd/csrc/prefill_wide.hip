@@ -1,17 +1,17 @@
-// Chunked prefill of batches that leave compute units to spare: at most half a (sequence, head) pair per unit, so that
-// every channel half of every pair (or of every segment of its sequence) has a unit to itself.
+// Chunked prefill of batches of at most one (sequence, head) pair per compute unit, where every pair (with half a pair per
+// unit: every channel half of every pair, or of every segment of its sequence) has a unit to itself.
 //
-// The arithmetic is that of prefill_mfma_kernel (prefill_mfma.hip describes it), for 32 of a head's channels.  What bounds such
-// a launch is the serial walk over the chunks: a lone wave issues an instruction every 8 cycles, and with 8 waves in two
-// phases between two barriers a chunk took 2.7 us.  Here a workgroup has 16 waves, four to a SIMD, in four roles that work
-// side by side on everything a chunk needs, and one barrier per chunk:
+// The arithmetic is that of prefill_mfma_kernel (prefill_mfma.hip describes it), for 32 (PT = 1) or all 64 (PT = 2) of a head's
+// channels.  What bounds such a launch is the serial walk over the chunks: a lone wave issues an instruction every 8 cycles,
+// and with 8 waves in two phases between two barriers a chunk of 32 channels took 2.7 us.  Here a workgroup has 16 waves, four
+// to a SIMD, in four roles that work side by side on everything a chunk needs, and one barrier per chunk:
 //   waves  0..3   the later terms of a 32-token block's outputs (the pair in front of the diagonal of the two longer blocks,
 //                 the diagonal, the skip term) and, one chunk later, its scaled outputs
 //   waves  4..7   the earlier terms (carried state, first block pairs), left in LDS for the wave that writes the outputs;
 //                 the one of block 0, which has no pairs, also forms the next chunk's token weights
 //   waves  8..11  the state update (a quarter of the states each), and the state as fp16 for the next chunk
 //   waves 12..15  staging of the next chunk: x, gate codes, B and C rows
-// so that LDS holds two of everything a chunk reads (160 KB with the gate, which one workgroup per unit may take).  C rows come
+// so that LDS holds two of what a chunk reads (up to the whole 160 KB, which one workgroup per unit may take).  C rows come
 // through LDS: loaded by the lanes that use them, 16 bytes a lane and row, they kept the address unit busy for 2000 cycles of
 // a chunk.  The skip term is a product of the x codes with a diagonal matrix (its fp16 coefficient and the remainder), the causal
 // mask an AND on the narrowed scores, and the carried state's decay factor is applied to the finished sums: fewer vector
@@ -21,8 +21,12 @@
 // Measured with the final state (the best of the 8-wave kernel's launches, whole, cut into segments or in channel halves /
 // this kernel): 128 heads, one sequence of 1531 tokens with gate and step-size codes 49.4 / 34.9 us, 2500 tokens 56 / 46; 120
 // pairs, 1000 tokens 32.2 / 22.0; 80 heads, 1000 tokens 27.4 / 20.8; 24 heads, 2048 tokens (5 segments) 24.3 / 22.8, 500
-// tokens 14.3 / 11.9.  A chunk takes 4000 cycles, 4600 with the two-term state update; the roles' waves wait 500 to 1500 of
-// them at the barrier, the vector ALUs issue 3000.  Wave priorities for the state waves cost 3 %.
+// tokens 14.3 / 11.9; two sequences of 128 heads, 1024 tokens 36.1 / 30.6, 4096 tokens 128 / 107, 1531 tokens with gate and codes
+// 64.4 / 47.5.  A chunk of 32 channels takes 4000 cycles, 4600 with the two-term state update; the roles' waves wait 500 to 1500 of
+// them at the barrier, the vector ALUs issue 3000.  A chunk of 64 channels takes 5600 (6200): its state waves are busy for 5100 of
+// them, the others for 3600 to 4600, and LDS for 3000.  Wave priorities for the state waves cost 1 to 3 %, their operands requested
+// two or three steps ahead change nothing.  Two rounds of this kernel are slower than two workgroups of 8 waves side by side
+// (512 pairs, 4096 tokens: 193 / 169 us; 384 pairs, 2048 tokens 105 / 89).
 #include "prefill_tiles.h"
 
 namespace quamba {
@@ -30,56 +34,79 @@ namespace {
 
 constexpr int kWideThreads = 1024;
 
-template <bool GATED>
+// LDS map (bytes) for PT 32-channel tiles per workgroup: two sets of what a chunk reads.  With 64 channels two sets of everything
+// would not fit: the state, the early terms and, with a gate, the C rows then have one place, and who writes it waits until
+// its readers have said that they are done with the chunk before (counters behind the tables).
+template <int PT, bool GATED>
 struct WideLds {
-    static constexpr int kPw = 32;                           // channels of the workgroup
-    static constexpr int kXsStride = 48;                     // halves per row of x [token][p]
-    static constexpr int kZsStride = kPw + 8;                // bytes per row of gate codes [token][p]
-    // one set per chunk in work
-    static constexpr int kOffCum = 0;                        // float[128]
-    static constexpr int kOffLoc = kOffCum + 4 * kQ;         // float[128]
-    static constexpr int kOffDt = kOffLoc + 4 * kQ;          // float[128]
-    static constexpr int kOffW2 = kOffDt + 4 * kQ;           // float[128]
-    static constexpr int kOffWe = kOffW2 + 4 * kQ;           // fp16[128]
-    static constexpr int kOffWs = kOffWe + 2 * kQ;           // fp16[128]
-    static constexpr int kOffWd = kOffWs + 2 * kQ;           // fp16[128]
-    static constexpr int kOffTot = kOffWd + 2 * kQ;          // float[4]
-    static constexpr int kOffGap = kOffTot + 4 * kNBlk;      // float[4][4]
+    static constexpr bool kOneH = PT == 2, kOnePart = PT == 2, kOneC = PT == 2 && GATED;
+    static constexpr int kPw = 32 * PT;                         // channels of the workgroup
+    static constexpr int kXsStride = PT == 2 ? 64 : 48;         // halves per row of x [token][p]
+    static constexpr int kZsStride = kPw + 8;                   // bytes per row of gate codes [token][p]
+    static constexpr int kC = kQ * kN, kH = 2 * kPw * kHsStride, kPart = kNBlk * PT * 4 * 64 * 16;
+    static constexpr int kOffCum = 0;                           // float[128]
+    static constexpr int kOffLoc = kOffCum + 4 * kQ;            // float[128]
+    static constexpr int kOffDt = kOffLoc + 4 * kQ;             // float[128]
+    static constexpr int kOffW2 = kOffDt + 4 * kQ;              // float[128]
+    static constexpr int kOffWe = kOffW2 + 4 * kQ;              // fp16[128]
+    static constexpr int kOffWs = kOffWe + 2 * kQ;              // fp16[128]
+    static constexpr int kOffWd = kOffWs + 2 * kQ;              // fp16[128]
+    static constexpr int kOffTot = kOffWd + 2 * kQ;             // float[4]
+    static constexpr int kOffGap = kOffTot + 4 * kNBlk;         // float[4][4]
     static constexpr int kOffBq = kOffGap + 4 * kNBlk * kNBlk;  // int8 [128][144]
-    static constexpr int kOffCq = kOffBq + kQ * kBqStride;      // int8 [128][128], 16-byte pieces of row r at piece ^ (r & 7)
-    static constexpr int kOffHs = kOffCq + kQ * kN;             // fp16 [kPw][136]
-    static constexpr int kOffXs = kOffHs + 2 * kPw * kHsStride; // fp16 [128][kXsStride]
+    static constexpr int kOffXs = kOffBq + kQ * kBqStride;      // fp16 [128][kXsStride]
     static constexpr int kOffZs = kOffXs + 2 * kQ * kXsStride;  // int8 [128][kZsStride]
     static constexpr int kSet = kOffZs + (GATED ? kQ * kZsStride : 0);
-    static constexpr int kOffPart = 2 * kSet;                // float[2][4 blocks][4][64 lanes][4]
-    static constexpr int kPart = kNBlk * 4 * 64 * 16;
-    static constexpr int kOffSx = kOffPart + 2 * kPart;      // float[kPw]
-    static constexpr int kOffSilu = kOffSx + 4 * kPw;        // float[256]
-    static constexpr int kBytes = kOffSilu + (GATED ? 4 * 256 : 0);
-    static_assert(kOffBq % 16 == 0 && kOffHs % 16 == 0 && kOffXs % 16 == 0 && kSet % 16 == 0, "16-byte alignment");
+    static constexpr int kOffCq = 2 * kSet;                     // int8 [128][128], 16-byte pieces of row r at piece ^ (r & 7)
+    static constexpr int kOffHs = kOffCq + (kOneC ? 1 : 2) * kC;        // fp16 [kPw][136]
+    static constexpr int kOffPart = kOffHs + (kOneH ? 1 : 2) * kH;      // float[4 blocks][PT * 4][64 lanes][4]
+    static constexpr int kOffSx = kOffPart + (kOnePart ? 1 : 2) * kPart;  // float[kPw]
+    static constexpr int kOffDone = kOffSx + 4 * kPw;           // int[16]: chunks read of the early terms [4], the state [4], C [8]
+    static constexpr int kOffSilu = kOffDone + 4 * 16;          // float[256]
+    static constexpr int kOffKeep = kOffSilu + (GATED ? 4 * 256 : 0);   // uint32[2][64 lanes][4] (PT == 2): the causal mask
+    static constexpr int kBytes = kOffKeep + (PT == 2 ? 2048 : 0);
+    static_assert(kOffBq % 16 == 0 && kOffHs % 16 == 0 && kOffXs % 16 == 0 && kSet % 16 == 0 && kOffDone % 16 == 0, "16-byte alignment");
     static_assert(kBytes <= (int)kLdsPerCu, "one workgroup per compute unit");
 };
 
-template <bool PRECISE, bool GATED, bool SEG>
+// Byte offset of 8 bytes of x in a row of the LDS: 32-byte piece (16 channels), 8-byte part.  Rows of 64 channels have no room for
+// padding: their pieces change places with bit 1 of the row, which puts the 4 rows x 32 bytes that the lane groups of a
+// transposing read fetch together on distinct banks.
+template <int PT>
+__device__ __forceinline__ int x_part(int row, int piece, int part)
+{
+    return (PT == 2 ? piece ^ (row & 2) : piece) * 32 + part * 8;
+}
+
+template <bool PRECISE, int PT, bool GATED, bool SEG>
 __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a)
 {
-    typedef WideLds<GATED> LY;
+    typedef WideLds<PT, GATED> LY;
     constexpr int kPw = LY::kPw, kXsStride = LY::kXsStride, kZsStride = LY::kZsStride;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    f32x4 *s_part = reinterpret_cast<f32x4 *>(smem + LY::kOffPart);
+    int *s_done = reinterpret_cast<int *>(smem + LY::kOffDone);
+    auto c_rows = [&](int buf) { return smem + LY::kOffCq + (LY::kOneC ? 0 : buf * LY::kC); };
+    auto h_rows = [&](int buf) { return smem + LY::kOffHs + (LY::kOneH ? 0 : buf * LY::kH); };
+    auto part_of = [&](int buf) { return reinterpret_cast<f32x4 *>(smem + LY::kOffPart + (LY::kOnePart ? 0 : buf * LY::kPart)); };
+    // "Chunks 0 .. n-1 of this walk are read" and the wait for it.  A reader says so in the phase of chunk n-1 or n without
+    // waiting for anyone but the readers of the early terms (which wait for nobody), so every wait ends.
+    auto done = [&](int slot, int n) { __hip_atomic_store(s_done + slot, n, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP); };
+    auto wait_done = [&](int slot, int n) {
+        while (__hip_atomic_load(s_done + slot, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < n) __builtin_amdgcn_s_sleep(1);
+    };
     float *s_sx = reinterpret_cast<float *>(smem + LY::kOffSx);
     float *s_silu = reinterpret_cast<float *>(smem + LY::kOffSilu);
 
     const int L = a.s.seqlen, H = a.s.nheads, G = a.s.ngroups;
-    const int wgs_per_seg = 2 * a.pair_count;
+    const int wgs_per_seg = (2 / PT) * a.pair_count;
     const int seg = SEG ? (int)blockIdx.x / wgs_per_seg : 0;
     const int nchunks = (L + kQ - 1) / kQ;
     const int c_begin = SEG ? seg * a.seg_chunks : 0;
     const int c_end = (SEG && seg + 1 < a.nseg) ? c_begin + a.seg_chunks : nchunks;
     const bool convert_init = a.init_state && (!SEG || seg == 0);
     const int bid = SEG ? (int)blockIdx.x - seg * wgs_per_seg : (int)blockIdx.x;
-    int pair, half;
-    {
+    int pair = bid, half = 0;
+    if (PT == 1) {
         const int npairs = a.pair_count, full = npairs >> 3;
         if (bid < 16 * full) {
             pair = (bid & 7) | ((bid >> 4) << 3);
@@ -97,6 +124,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
     const int wave16 = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int role = wave16 >> 2, wave = wave16 & 3;
     const int tid4 = tid & 255;
+    if (tid < 16) s_done[tid] = 0;  // read and written behind the first barrier
     // Lane-derived values are made anew in every chunk (fresh_lane): kept across the loop over chunks, the addresses formed
     // from them would push other values into scratch memory.
     int l32 = lane & 31, hb = lane >> 5;
@@ -113,6 +141,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
     const float d_acc = Dh / (y_scale * kXs);
     const bool d_by_mfma = fabsf(d_acc) < 3.0e4f;
     const float dead = (a.s.flags & QUAMBA_FLAG_NO_DECAY_SKIP) ? __builtin_inff() : kDead;
+    typedef uint32_t xvec __attribute__((ext_vector_type(PT)));
     const uint32_t x_row = (uint32_t)H * kP, b_row = (uint32_t)G * kN, dt_row = (uint32_t)H * 4u;
 
     // The chunk's token weights from its step sizes, two tokens per lane (one wave; the weights are those of
@@ -198,8 +227,8 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
     if (role < 2) {
         // ================= output waves =================
         // B and C rows in registers, int8 score tile G^T of (block sb, the wave's block)
-        auto load_c_rows = [&](const unsigned char *set, int tb, i32x4(&ct)[4]) {
-            const unsigned char *row = set + LY::kOffCq + (tb * kBlk + l32) * kN;
+        auto load_c_rows = [&](int buf, int tb, i32x4(&ct)[4]) {
+            const unsigned char *row = c_rows(buf) + (tb * kBlk + l32) * kN;
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk)
                 ct[kk] = *reinterpret_cast<const i32x4 *>(row + 16 * ((2 * kk + hb) ^ (l32 & 7)));
@@ -217,19 +246,24 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
             return gi;
         };
         // x of 16 tokens (first token in the wave's LDS order: row), operand of the products with the score tiles
-        auto load_x = [&](const unsigned char *set, int row) {
-            const int i16 = l32 & 15, c16 = l32 >> 4;
-            return lds_read_tr16x8<kXsStride>(set + LY::kOffXs +
-                                              ((row + 8 * hb + (i16 >> 2)) * kXsStride + 16 * c16 + 4 * (i16 & 3)) * 2);
+        auto load_x = [&](const unsigned char *set, int row, int pt) {
+            const int i16 = l32 & 15, c16 = l32 >> 4, r = 8 * hb + (i16 >> 2);
+            return lds_read_tr16x8<kXsStride>(set + LY::kOffXs + (row + r) * kXsStride * 2 + x_part<PT>(r, 2 * pt + c16, i16 & 3));
         };
         // acc += x^T (G^T exp(cum_t - m) exp(m - cum_s) dt_s) of the block pairs sb0 <= sb < end in front of the diagonal;
         // gi holds the tile of sb0 and, with `more`, ends as the tile of `end`
         auto off_diagonal = [&](const unsigned char *set, int tb, int sb0, int end, bool more, float loc_t,
-                                const i32x4(&ct)[4], i32x16 &gi, f32x16 &acc) {
+                                const i32x4(&ct)[4], i32x16 &gi, f32x16 (&acc)[PT]) {
             const float *s_gap = reinterpret_cast<const float *>(set + LY::kOffGap);
             const _Float16 *s_we = reinterpret_cast<const _Float16 *>(set + LY::kOffWe);
             for (int sb = sb0; sb < end; ++sb) {
-                const f16x8 x0 = load_x(set, sb * kBlk), x1 = load_x(set, sb * kBlk + 16);
+                if (PT == 2) new_lane();
+                f16x8 x0[PT], x1[PT];
+#pragma unroll
+                for (int pt = 0; pt < PT; ++pt) {
+                    x0[pt] = load_x(set, sb * kBlk, pt);
+                    x1[pt] = load_x(set, sb * kBlk + 16, pt);
+                }
                 const f16x8 w0 = *reinterpret_cast<const f16x8 *>(s_we + sb * kBlk + 8 * hb);
                 const f16x8 w1 = *reinterpret_cast<const f16x8 *>(s_we + sb * kBlk + 16 + 8 * hb);
                 const float rowf = exp2_fast(loc_t + s_gap[tb * kNBlk + sb]) * kNarrow;
@@ -239,8 +273,11 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
                 const f16x8 l0 = pack_f16x8(lv) * w0, l1 = pack_f16x8(lv + 8) * w1;
                 __builtin_amdgcn_sched_barrier(0);
                 if (more || sb + 1 < end) gi = score_tile(set, sb + 1, ct);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(x0, l0, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(x1, l1, acc, 0, 0, 0);
+#pragma unroll
+                for (int pt = 0; pt < PT; ++pt) {
+                    acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x0[pt], l0, acc[pt], 0, 0, 0);
+                    acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x1[pt], l1, acc[pt], 0, 0, 0);
+                }
             }
         };
         // first block whose decay towards block tb is alive (tb if none is)
@@ -255,71 +292,89 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
             const int tb = wave, mid = tb >= 2 ? tb - 1 : tb;
             if (tid < kPw) s_sx[tid] = x_scale_lookup(a, h, p_base + tid) * (d_by_mfma ? y_scale : 1.0f);
             if (GATED) s_silu[tid] = silu_of_code(a.z_scale, (int8_t)tid);
-            // per lane (token t of the block): which of its 16 score rows s are at or in front of t, two to a dword, and the
-            // skip term's coefficient on the diagonal, as fp16 and its remainder, as operands of their own
-            uint32_t keep[8];
-            f16x8 skip[2], skip_rest[2];
-            {
-                const float d = d_by_mfma ? d_acc : 0.0f;
-                const _Float16 d16 = (_Float16)d, rest = (_Float16)(d - (float)d16);
+            // per lane (token t of the block): which of its 16 score rows s are at or in front of t, two to a dword; with 64 channels
+            // they wait in LDS, the registers are the sums'
+            u32x4 keep[2];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int s = 8 * (r >> 2) + 4 * hb + (r & 3);
-                    if (r & 1)
-                        keep[r >> 1] |= s <= l32 ? 0xffff0000u : 0u;
-                    else
-                        keep[r >> 1] = s <= l32 ? 0xffffu : 0u;
-                    skip[r >> 3][r & 7] = s == l32 ? d16 : (_Float16)0.0f;
-                    skip_rest[r >> 3][r & 7] = s == l32 ? rest : (_Float16)0.0f;
-                }
+            for (int r = 0; r < 16; r += 2) {
+                const int s = 8 * (r >> 2) + 4 * hb + (r & 3);
+                keep[r >> 3][(r >> 1) & 3] = (s <= l32 ? 0xffffu : 0u) | (s + 1 <= l32 ? 0xffff0000u : 0u);
+            }
+            u32x4 *s_keep = reinterpret_cast<u32x4 *>(smem + LY::kOffKeep);
+            if (PT == 2 && wave < 2) s_keep[64 * wave + lane] = keep[wave];
+            // the skip term's coefficient on the diagonal, as fp16 and its remainder, as operands of their own
+            const float d_sel = d_by_mfma ? d_acc : 0.0f;
+            const uint32_t d16 = f32_to_f16_bits(d_sel);
+            const uint32_t d16_rest = f32_to_f16_bits(d_sel - (float)(_Float16)d_sel);
+            auto diagonal = [&](uint32_t bits, f16x8(&op)[2]) {
+                const bool own = ((l32 >> 2) & 1) == hb;  // row s == t is register 4 (t / 8) + t % 4
+                const int at = own ? 2 * (l32 >> 3) + ((l32 >> 1) & 1) : 8;
+                const uint32_t val = l32 & 1 ? bits << 16 : bits;
+                u32x4 w[2];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) w[k >> 2][k & 3] = at == k ? val : 0u;
+                op[0] = __builtin_bit_cast(f16x8, w[0]);
+                op[1] = __builtin_bit_cast(f16x8, w[1]);
+            };
+            f16x8 skip[2], skip_rest[2];
+            if (PT == 1) {
+                diagonal(d16, skip);
+                diagonal(d16_rest, skip_rest);
             }
             if (convert_init) __syncthreads();
             __syncthreads();  // the first chunk is staged
 
-            f32x16 acc;
-            uint32_t zq[4];
-            f16x4 xq[4];
+            f32x16 acc[PT];
+            uint32_t zq[PT][4];
+            f16x4 xq[PT][4];
             // outputs of the block's tokens of chunk c, from acc and what the early wave has left in LDS
             auto epilogue = [&](int c, int buf) {
                 const int t0 = c * kQ;
                 const int nv = min(kQ, L - t0);
                 const int tl = tb * kBlk + l32;
                 uint16_t *yrow = a.y + ((((size_t)b * L + t0) + min(tl, nv - 1)) * H + h) * kP + p_base + 8 * hb;
-                const f32x4 *part = s_part + buf * (LY::kPart / 16) + tb * 4 * 64 + 32 * hb + l32;
+                const f32x4 *part = part_of(buf) + tb * PT * 4 * 64 + 32 * hb + l32;
 #pragma unroll
-                for (int rg = 0; rg < 4; ++rg) {
-                    const f32x4 v4 = part[rg * 64];
+                for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[4 * rg + i] += v4[i];
-                }
+                    for (int rg = 0; rg < 4; ++rg) {
+                        const f32x4 v4 = part[(pt * 4 + rg) * 64];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[pt][4 * rg + i] += v4[i];
+                    }
+                if (LY::kOnePart) done(tb, c - c_begin + 1);
                 if (!d_by_mfma) {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        acc[r] = fmaf(y_scale, acc[r], Dh * ((float)xq[r >> 2][r & 3] * (1.0f / kXs)));
+                    for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            acc[pt][r] = fmaf(y_scale, acc[pt][r], Dh * ((float)xq[pt][r >> 2][r & 3] * (1.0f / kXs)));
                 }
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    uint32_t w[2][2];
+                for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                        const int rg = 2 * j + e;
-                        const f32x4 k4 = *reinterpret_cast<const f32x4 *>(s_sx + 8 * rg + 4 * hb);
-                        f16x4 o;
+                    for (int j = 0; j < 2; ++j) {
+                        uint32_t w[2][2];
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            float v = k4[i] * acc[4 * rg + i];
-                            if (GATED) v *= s_silu[(zq[rg] >> (8 * i)) & 0xffu];
-                            o[i] = (_Float16)v;
+                        for (int e = 0; e < 2; ++e) {
+                            const int rg = 2 * j + e;
+                            const f32x4 k4 = *reinterpret_cast<const f32x4 *>(s_sx + 32 * pt + 8 * rg + 4 * hb);
+                            f16x4 o;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                float v = k4[i] * acc[pt][4 * rg + i];
+                                if (GATED) v *= s_silu[(zq[pt][rg] >> (8 * i)) & 0xffu];
+                                o[i] = (_Float16)v;
+                            }
+                            const u32x2 ow = __builtin_bit_cast(u32x2, o);
+                            w[e][0] = ow[0];
+                            w[e][1] = ow[1];
                         }
-                        const u32x2 ow = __builtin_bit_cast(u32x2, o);
-                        w[e][0] = ow[0];
-                        w[e][1] = ow[1];
+                        const auto s0 = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
+                        const auto s1 = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
+                        const u32x4 v = {s0[0], s1[0], s0[1], s1[1]};
+                        if (tl < nv) *reinterpret_cast<u32x4 *>(yrow + 32 * pt + 16 * j) = v;
                     }
-                    const auto s0 = __builtin_amdgcn_permlane32_swap(w[0][0], w[1][0], false, false);
-                    const auto s1 = __builtin_amdgcn_permlane32_swap(w[0][1], w[1][1], false, false);
-                    const u32x4 v = {s0[0], s1[0], s0[1], s1[1]};
-                    if (tl < nv) *reinterpret_cast<u32x4 *>(yrow + 16 * j) = v;
-                }
             };
             for (int c = c_begin; c < c_end; ++c) {
                 const int buf = (c - c_begin) & 1;
@@ -329,24 +384,43 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
                 const float *s_tot = reinterpret_cast<const float *>(set + LY::kOffTot);
                 new_lane();
                 const int tl = tb * kBlk + l32;
+                i32x4 ct[4];
+                if (LY::kOneC) {
+                    load_c_rows(buf, tb, ct);
+                    done(8 + tb, c - c_begin + 1);
+                }
                 if (c > c_begin) epilogue(c - 1, buf ^ 1);
                 if (tb * kBlk < min(kQ, L - c * kQ)) {
-                    i32x4 ct[4];
-                    load_c_rows(set, tb, ct);
+                    if (!LY::kOneC) load_c_rows(buf, tb, ct);
                     const float loc_t = s_loc[tl];
                     int first = tb;
                     if (mid < tb) {
                         const float r_tb = s_cum[tb * kBlk - 1];
                         first = __builtin_amdgcn_readfirstlane(r_tb - s_cum[mid * kBlk + kBlk - 1] < -dead) ? tb : mid;
                     }
-                    i32x16 gi = score_tile(set, first, ct);
+                    i32x16 gi;
+                    if (PT == 1) gi = score_tile(set, first, ct);
                     // the skip term: D x as a product with a diagonal matrix
-                    const f16x8 x0 = load_x(set, tb * kBlk), x1 = load_x(set, tb * kBlk + 16);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(x0, skip_rest[0], (f32x16)(0.0f), 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(x1, skip_rest[1], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(x0, skip[0], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(x1, skip[1], acc, 0, 0, 0);
+                    if (PT == 2) {
+                        diagonal(d16, skip);
+                        diagonal(d16_rest, skip_rest);
+                    }
+                    f16x8 x0[PT], x1[PT];
+#pragma unroll
+                    for (int pt = 0; pt < PT; ++pt) {
+                        x0[pt] = load_x(set, tb * kBlk, pt);
+                        x1[pt] = load_x(set, tb * kBlk + 16, pt);
+                        acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x0[pt], skip_rest[0], (f32x16)(0.0f), 0, 0, 0);
+                        acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x1[pt], skip_rest[1], acc[pt], 0, 0, 0);
+                        acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x0[pt], skip[0], acc[pt], 0, 0, 0);
+                        acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x1[pt], skip[1], acc[pt], 0, 0, 0);
+                    }
+                    if (PT == 2) {
+                        new_lane();
+                        gi = score_tile(set, first, ct);
+                    }
                     off_diagonal(set, tb, first, tb, true, loc_t, ct, gi, acc);
+                    if (PT == 2) new_lane();
                     // diagonal block pair: per-element decay, causal mask on the narrowed values
                     const bool factored = __builtin_amdgcn_readfirstlane(-s_tot[tb] < 64.0f);
                     f16x4 lq[4];
@@ -370,23 +444,39 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
                                 lq[rg][i] = (_Float16)((float)gi[4 * rg + i] * (exp2_fast(loc_t - cs4[i]) * ds4[i]));
                         }
                     }
+                    if (PT == 2) {
+                        keep[0] = s_keep[32 * hb + l32];
+                        keep[1] = s_keep[64 + 32 * hb + l32];
+                    }
                     u32x4 l0 = __builtin_bit_cast(u32x4, __builtin_shufflevector(lq[0], lq[1], 0, 1, 2, 3, 4, 5, 6, 7));
                     u32x4 l1 = __builtin_bit_cast(u32x4, __builtin_shufflevector(lq[2], lq[3], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
-                        l0[k] &= keep[k];
-                        l1[k] &= keep[4 + k];
+                        l0[k] &= keep[0][k];
+                        l1[k] &= keep[1][k];
                     }
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(x0, __builtin_bit_cast(f16x8, l0), acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(x1, __builtin_bit_cast(f16x8, l1), acc, 0, 0, 0);
 #pragma unroll
-                    for (int rg = 0; rg < 4; ++rg) {
-                        if (GATED)
-                            zq[rg] = *reinterpret_cast<const uint32_t *>(set + LY::kOffZs + tl * kZsStride + 8 * rg + 4 * hb);
-                        if (!d_by_mfma)
-                            xq[rg] = *reinterpret_cast<const f16x4 *>(set + LY::kOffXs +
-                                                                      (tok_pos(tl) * kXsStride + 8 * rg + 4 * hb) * 2);
+                    for (int pt = 0; pt < PT; ++pt) {
+                        if (PT == 2) {  // (with 32 channels the operands are still in registers)
+                            x0[pt] = load_x(set, tb * kBlk, pt);
+                            x1[pt] = load_x(set, tb * kBlk + 16, pt);
+                        }
+                        acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x0[pt], __builtin_bit_cast(f16x8, l0), acc[pt], 0, 0, 0);
+                        acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x1[pt], __builtin_bit_cast(f16x8, l1), acc[pt], 0, 0, 0);
                     }
+#pragma unroll
+                    for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+                        for (int rg = 0; rg < 4; ++rg) {
+                            if (GATED)
+                                zq[pt][rg] = *reinterpret_cast<const uint32_t *>(set + LY::kOffZs + tl * kZsStride + 32 * pt +
+                                                                                 8 * rg + 4 * hb);
+                            if (!d_by_mfma) {
+                                const int row = tok_pos(tl);
+                                xq[pt][rg] = *reinterpret_cast<const f16x4 *>(set + LY::kOffXs + row * kXsStride * 2 +
+                                                                              x_part<PT>(row, 2 * pt + (rg >> 1), 2 * (rg & 1) + hb));
+                            }
+                        }
                 }
                 __syncthreads();  // the next chunk is staged; this one's early terms are in LDS
             }
@@ -416,40 +506,60 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
                 if (tb * kBlk < min(kQ, L - c * kQ)) {
                     const int tl = tb * kBlk + l32;
                     i32x4 ct[4];
-                    load_c_rows(set, tb, ct);
+                    load_c_rows(buf, tb, ct);
+                    if (LY::kOneC) done(12 + tb, c - c_begin + 1);
                     const float loc_t = s_loc[tl], cum_t = s_cum[tl];
                     const float r_tb = tb > 0 ? s_cum[tb * kBlk - 1] : 0.0f;
                     const int sb0 = first_alive(s_cum, tb, r_tb);
                     i32x16 gi;
                     if (sb0 < mid) gi = score_tile(set, sb0, ct);
-                    f32x16 acc = (f32x16)(0.0f);
+                    f32x16 acc[PT];
+#pragma unroll
+                    for (int pt = 0; pt < PT; ++pt) acc[pt] = (f32x16)(0.0f);
                     if (!__builtin_amdgcn_readfirstlane(r_tb < -dead)) {
                         // carried state: Y^T[p,t] = exp(cum_t) sum_n H[p,n] Cq[t,n]
-                        const _Float16 *s_hs = reinterpret_cast<const _Float16 *>(set + LY::kOffHs) + l32 * kHsStride + 16 * hb;
+                        const _Float16 *s_hs = reinterpret_cast<const _Float16 *>(h_rows(buf)) + l32 * kHsStride + 16 * hb;
 #pragma unroll
                         for (int k8 = 0; k8 < 8; ++k8) {
-                            const f16x8 hf = *reinterpret_cast<const f16x8 *>(s_hs + 32 * (k8 >> 1) + 8 * (k8 & 1));
+                            f16x8 hf[PT];
+#pragma unroll
+                            for (int pt = 0; pt < PT; ++pt)
+                                hf[pt] = *reinterpret_cast<const f16x8 *>(s_hs + 32 * pt * kHsStride + 32 * (k8 >> 1) + 8 * (k8 & 1));
                             const i32x4 c4 = ct[k8 >> 1];
                             const f16x8 cf = i8x8_to_f16((uint32_t)c4[2 * (k8 & 1)], (uint32_t)c4[2 * (k8 & 1) + 1]);
-                            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(hf, cf, acc, 0, 0, 0);
+#pragma unroll
+                            for (int pt = 0; pt < PT; ++pt)
+                                acc[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(hf[pt], cf, acc[pt], 0, 0, 0);
                         }
                         const float e_t = exp2_fast(cum_t) * kAcc;
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[r] *= e_t;
-                    }
-                    off_diagonal(set, tb, sb0, mid, false, loc_t, ct, gi, acc);
-                    f32x4 *part = s_part + buf * (LY::kPart / 16) + tb * 4 * 64 + 32 * hb + l32;
+                        for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
-                    for (int rg = 0; rg < 4; ++rg)
-                        part[rg * 64] = (f32x4){acc[4 * rg], acc[4 * rg + 1], acc[4 * rg + 2], acc[4 * rg + 3]};
+                            for (int r = 0; r < 16; ++r) acc[pt][r] *= e_t;
+                    }
+                    if (LY::kOneH) done(4 + tb, c - c_begin + 1);
+                    off_diagonal(set, tb, sb0, mid, false, loc_t, ct, gi, acc);
+                    f32x4 *part = part_of(buf) + tb * PT * 4 * 64 + 32 * hb + l32;
+                    if (LY::kOnePart) wait_done(tb, c - c_begin);
+#pragma unroll
+                    for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+                        for (int rg = 0; rg < 4; ++rg)
+                            part[(pt * 4 + rg) * 64] =
+                                (f32x4){acc[pt][4 * rg], acc[pt][4 * rg + 1], acc[pt][4 * rg + 2], acc[pt][4 * rg + 3]};
+                } else if (PT == 2) {  // a block past the end (of the last chunk) reads nothing
+                    done(4 + tb, c - c_begin + 1);
+                    if (LY::kOneC) done(12 + tb, c - c_begin + 1);
                 }
                 __syncthreads();
             }
         }
     } else if (role == 2) {
         // ================= state waves =================
-        // st[r]: p = l32, n = 32 wave + 8 (r/4) + 4 hb + r%4, as in prefill_mfma_kernel
-        f32x16 st = (f32x16)(0.0f);
+        // st[pt][r]: p = 32 pt + l32, n = 32 wave + 8 (r/4) + 4 hb + r%4, as in prefill_mfma_kernel
+        f32x16 st[PT];
+#pragma unroll
+        for (int pt = 0; pt < PT; ++pt) st[pt] = (f32x16)(0.0f);
         const int n_lane = 32 * wave + 4 * hb;
         const size_t st_row = ((size_t)bh * kP + p_base + l32) * kN + n_lane;
         if (SEG && seg > 0) {
@@ -460,35 +570,42 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
                 const float w = exp2_fast(dsum);
                 const float *src = a.seg_state + (size_t)j * pairs * kP * kN + st_row;
 #pragma unroll
-                for (int rg = 0; rg < 4; ++rg) {
-                    const f32x4 v = *reinterpret_cast<const f32x4 *>(src + 8 * rg);
+                for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) st[4 * rg + i] = fmaf(w, v[i], st[4 * rg + i]);
-                }
+                    for (int rg = 0; rg < 4; ++rg) {
+                        const f32x4 v = *reinterpret_cast<const f32x4 *>(src + 32 * pt * kN + 8 * rg);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) st[pt][4 * rg + i] = fmaf(w, v[i], st[pt][4 * rg + i]);
+                    }
                 dsum += a.seg_decay[(size_t)j * pairs + bh];
             }
         }
         if (convert_init) {
             __syncthreads();  // the scales are in LDS
-            const float inv = kNarrow * (d_by_mfma ? y_scale : 1.0f) / (s_sx[l32] * sB);
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                const f32x4 v = *reinterpret_cast<const f32x4 *>(a.init_state + st_row + 8 * rg);
+            for (int pt = 0; pt < PT; ++pt) {
+                const float inv = kNarrow * (d_by_mfma ? y_scale : 1.0f) / (s_sx[32 * pt + l32] * sB);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) st[4 * rg + i] = v[i] * inv;
+                for (int rg = 0; rg < 4; ++rg) {
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(a.init_state + st_row + 32 * pt * kN + 8 * rg);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) st[pt][4 * rg + i] = v[i] * inv;
+                }
             }
         }
-        auto publish = [&](unsigned char *set) {  // the state as fp16, operand of the next chunk's C.H product
-            unsigned char *row = set + LY::kOffHs + (l32 * kHsStride + 32 * wave + 4 * hb) * 2;
+        auto publish = [&](int buf) {  // the state as fp16, operand of the next chunk's C.H product
+            unsigned char *row = h_rows(buf) + (l32 * kHsStride + 32 * wave + 4 * hb) * 2;
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                f16x4 v;
+            for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = (_Float16)st[4 * rg + i];
-                *reinterpret_cast<f16x4 *>(row + 16 * rg) = v;
-            }
+                for (int rg = 0; rg < 4; ++rg) {
+                    f16x4 v;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = (_Float16)st[pt][4 * rg + i];
+                    *reinterpret_cast<f16x4 *>(row + 32 * pt * kHsStride * 2 + 16 * rg) = v;
+                }
         };
-        publish(smem);
+        publish(0);
         __syncthreads();  // the first chunk is staged
         const bool want_state = a.state && (!SEG || seg + 1 == a.nseg);
         for (int c = c_begin; c < c_end; ++c) {
@@ -501,30 +618,42 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
                 const int i16 = l32 & 15, c16 = l32 >> 4;
                 const unsigned char *bq_src =
                     set + LY::kOffBq + (8 * hb + (i16 >> 1)) * kBqStride + 32 * wave + 16 * c16 + 8 * (i16 & 1);
-                const unsigned char *xs_src =
-                    set + LY::kOffXs + ((8 * hb + (i16 >> 2)) * kXsStride + 16 * c16 + 4 * (i16 & 3)) * 2;
+                const int xr = 8 * hb + (i16 >> 2);
+                const unsigned char *xs_src = set + LY::kOffXs + xr * kXsStride * 2;
                 const _Float16 *s_ws = reinterpret_cast<const _Float16 *>(set + LY::kOffWs) + 8 * hb;
                 const _Float16 *s_wd = reinterpret_cast<const _Float16 *>(set + LY::kOffWd) + 8 * hb;
                 struct Ops {
                     u32x2 bw;
-                    f16x8 x, wv, wd;
+                    f16x8 x[PT], wv, wd;
                 };
                 auto fetch = [&](int step, Ops &o) {
                     const int row = 16 * step;
                     o.bw = lds_read_tr8(bq_src + row * kBqStride);
-                    o.x = lds_read_tr16x8<kXsStride>(xs_src + row * kXsStride * 2);
+#pragma unroll
+                    for (int pt = 0; pt < PT; ++pt)
+                        o.x[pt] = lds_read_tr16x8<kXsStride>(xs_src + row * kXsStride * 2 +
+                                                             x_part<PT>(xr, 2 * pt + c16, i16 & 3));
                     o.wv = *reinterpret_cast<const f16x8 *>(s_ws + row);
                     if (PRECISE) o.wd = *reinterpret_cast<const f16x8 *>(s_wd + row);
                 };
                 auto decay = [&](float log2_dec) {
                     const float dec = exp2_fast(log2_dec);
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) st[r] *= dec;
+                    for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) st[pt][r] *= dec;
                 };
                 auto add = [&](const Ops &o) {
                     const f16x8 bf = i8x8_to_f16(o.bw[0], o.bw[1]) * o.wv;
-                    st = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf, o.x, st, 0, 0, 0);
-                    if (PRECISE) st = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf * o.wd, o.x, st, 0, 0, 0);
+#pragma unroll
+                    for (int pt = 0; pt < PT; ++pt)
+                        st[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf, o.x[pt], st[pt], 0, 0, 0);
+                    if (PRECISE) {
+                        const f16x8 rest = bf * o.wd;
+#pragma unroll
+                        for (int pt = 0; pt < PT; ++pt)
+                            st[pt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(rest, o.x[pt], st[pt], 0, 0, 0);
+                    }
                 };
                 // What a block adds decays by exp2(cum_last - m) before the chunk ends; the dead blocks are the first ones and
                 // only decay.  A chunk without dead blocks runs as straight code, so that its LDS reads, conversions and
@@ -554,18 +683,27 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
                         add(o1);
                     }
                 }
-                if (c + 1 < c_end) publish(smem + (buf ^ 1) * LY::kSet);
+                if (c + 1 < c_end) {
+                    if (LY::kOneH) {
+#pragma unroll
+                        for (int k = 0; k < kNBlk; ++k) wait_done(4 + k, c - c_begin + 1);
+                    }
+                    publish(buf ^ 1);
+                }
             }
             __syncthreads();
         }
         if (want_state) {
-            const float sc = s_sx[l32] * sB / ((d_by_mfma ? y_scale : 1.0f) * kNarrow);
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                f32x4 v;
+            for (int pt = 0; pt < PT; ++pt) {
+                const float sc = s_sx[32 * pt + l32] * sB / ((d_by_mfma ? y_scale : 1.0f) * kNarrow);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = st[4 * rg + i] * sc;
-                *reinterpret_cast<f32x4 *>(a.state + st_row + 8 * rg) = v;
+                for (int rg = 0; rg < 4; ++rg) {
+                    f32x4 v;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = st[pt][4 * rg + i] * sc;
+                    *reinterpret_cast<f32x4 *>(a.state + st_row + 32 * pt * kN + 8 * rg) = v;
+                }
             }
         }
     } else {
@@ -573,8 +711,8 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
         // A thread takes tokens r0 + 32 k of a chunk, of each 4 channels of x and z and 16 states of B and C (8 lanes cover a
         // row, a wave 8 consecutive rows).
         const int r0 = tid4 >> 3, p8 = tid4 & 7;
-        const uint32_t x_off = r0 * x_row + 4u * p8, b_off = r0 * b_row + 16u * p8;
-        uint32_t xr[4], zr[4];
+        const uint32_t x_off = r0 * x_row + (uint32_t)(4 * PT) * p8, b_off = r0 * b_row + 16u * p8;
+        xvec xr[4], zr[4];
         u32x4 br[4], cr[4];
         auto issue_loads = [&](int c) {
             const size_t tok = (size_t)b * L + c * kQ;
@@ -588,38 +726,51 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
                 if (nv < kQ) {  // rows past the end are read from the last row and zeroed where they are stored
                     const uint32_t row = (uint32_t)min(r0 + kBlk * k, nv - 1);
                     xk = bk = 0;
-                    xo = row * x_row + 4u * p8;
+                    xo = row * x_row + (uint32_t)(4 * PT) * p8;
                     bo = row * b_row + 16u * p8;
                 }
-                xr[k] = *reinterpret_cast<const uint32_t *>(xbase + xk + xo);
-                if (GATED) zr[k] = *reinterpret_cast<const uint32_t *>(zbase + xk + xo);
+                xr[k] = *reinterpret_cast<const xvec *>(xbase + xk + xo);
+                if (GATED) zr[k] = *reinterpret_cast<const xvec *>(zbase + xk + xo);
                 br[k] = *reinterpret_cast<const u32x4 *>(bbase + bk + bo);
                 cr[k] = *reinterpret_cast<const u32x4 *>(cbase + bk + bo);
             }
         };
-        auto stage = [&](int c, unsigned char *set) {
+        auto stage = [&](int c, int buf) {
+            unsigned char *set = smem + buf * LY::kSet;
             const int nv = min(kQ, L - c * kQ), row0 = tok_pos(r0);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 if (nv < kQ && r0 + kBlk * k >= nv) {
-                    xr[k] = 0u;
+                    xr[k] = (xvec)(0u);
                     br[k] = cr[k] = (u32x4){0u, 0u, 0u, 0u};
                 }
                 const int row = row0 + kBlk * k, tok = r0 + kBlk * k;
-                *reinterpret_cast<f16x4 *>(set + LY::kOffXs + (row * kXsStride + 4 * p8) * 2) = i8x4_to_f16_xs(xr[k]);
-                if (GATED) *reinterpret_cast<uint32_t *>(set + LY::kOffZs + tok * kZsStride + 4 * p8) = zr[k];
+                unsigned char *xs_row = set + LY::kOffXs + row * kXsStride * 2;
+#pragma unroll
+                for (int q = 0; q < PT; ++q)
+                    *reinterpret_cast<f16x4 *>(xs_row + x_part<PT>(row, p8 * PT >> 2, (p8 * PT & 3) + q)) = i8x4_to_f16_xs(xr[k][q]);
+                if (GATED) *reinterpret_cast<xvec *>(set + LY::kOffZs + tok * kZsStride + 4 * PT * p8) = zr[k];
                 *reinterpret_cast<u32x4 *>(set + LY::kOffBq + row * kBqStride + 16 * p8) = br[k];
-                *reinterpret_cast<u32x4 *>(set + LY::kOffCq + tok * kN + 16 * (p8 ^ (r0 & 7))) = cr[k];
+                if (!LY::kOneC) *reinterpret_cast<u32x4 *>(c_rows(buf) + tok * kN + 16 * (p8 ^ (r0 & 7))) = cr[k];
+            }
+            if (LY::kOneC) {
+                if (c > c_begin) {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) wait_done(8 + k, c - c_begin);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    *reinterpret_cast<u32x4 *>(c_rows(0) + (r0 + kBlk * k) * kN + 16 * (p8 ^ (r0 & 7))) = cr[k];
             }
         };
         issue_loads(c_begin);
         if (convert_init) __syncthreads();
-        stage(c_begin, smem);
+        stage(c_begin, 0);
         if (c_begin + 1 < c_end) issue_loads(c_begin + 1);
         __syncthreads();  // the first chunk is staged
         for (int c = c_begin; c < c_end; ++c) {
             if (c + 1 < c_end) {
-                stage(c + 1, smem + ((c + 1 - c_begin) & 1) * LY::kSet);
+                stage(c + 1, (c + 1 - c_begin) & 1);
                 if (c + 2 < c_end) issue_loads(c + 2);
             }
             __syncthreads();
@@ -627,29 +778,33 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
     }
 }
 
-template <bool PRECISE, bool GATED, bool SEG>
+template <bool PRECISE, int PT, bool GATED, bool SEG>
 hipError_t launch(const SsdArgs &a, hipStream_t stream)
 {
     const int segs = a.nseg > 1 ? a.nseg : 1;
-    const dim3 grid((unsigned)(2 * a.pair_count * segs));
-    const hipError_t e = allow_full_lds<prefill_wide_kernel<PRECISE, GATED, SEG>>();
+    const dim3 grid((unsigned)((2 / PT) * a.pair_count * segs));
+    const hipError_t e = allow_full_lds<prefill_wide_kernel<PRECISE, PT, GATED, SEG>>();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((prefill_wide_kernel<PRECISE, GATED, SEG>), grid, dim3(kWideThreads), (WideLds<GATED>::kBytes),
+    hipLaunchKernelGGL((prefill_wide_kernel<PRECISE, PT, GATED, SEG>), grid, dim3(kWideThreads), (WideLds<PT, GATED>::kBytes),
                        stream, a);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_prefill_wide(const SsdArgs &a, bool precise, hipStream_t stream)
+hipError_t launch_prefill_wide(const SsdArgs &a, bool halves, bool precise, hipStream_t stream)
 {
     const bool seg = a.nseg > 1;
-    if (precise) {
-        if (a.z) return seg ? launch<true, true, true>(a, stream) : launch<true, true, false>(a, stream);
-        return seg ? launch<true, false, true>(a, stream) : launch<true, false, false>(a, stream);
+    if (!halves) {
+        if (precise) return a.z ? launch<true, 2, true, false>(a, stream) : launch<true, 2, false, false>(a, stream);
+        return a.z ? launch<false, 2, true, false>(a, stream) : launch<false, 2, false, false>(a, stream);
     }
-    if (a.z) return seg ? launch<false, true, true>(a, stream) : launch<false, true, false>(a, stream);
-    return seg ? launch<false, false, true>(a, stream) : launch<false, false, false>(a, stream);
+    if (precise) {
+        if (a.z) return seg ? launch<true, 1, true, true>(a, stream) : launch<true, 1, true, false>(a, stream);
+        return seg ? launch<true, 1, false, true>(a, stream) : launch<true, 1, false, false>(a, stream);
+    }
+    if (a.z) return seg ? launch<false, 1, true, true>(a, stream) : launch<false, 1, true, false>(a, stream);
+    return seg ? launch<false, 1, false, true>(a, stream) : launch<false, 1, false, false>(a, stream);
 }
 
 }  // namespace quamba

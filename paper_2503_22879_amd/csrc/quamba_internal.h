@@ -317,7 +317,7 @@ bool mamba1_scan_supports_any(const quamba_ssd_shape_t &s);
 hipError_t launch_prefill_generic(const SsdArgs &a, hipStream_t stream);
 bool prefill_mfma_supports(const quamba_ssd_shape_t &s);
 hipError_t launch_prefill_mfma(const SsdArgs &a, void *workspace, hipStream_t stream);
-hipError_t launch_prefill_wide(const SsdArgs &a, bool precise, hipStream_t stream);
+hipError_t launch_prefill_wide(const SsdArgs &a, bool halves, bool precise, hipStream_t stream);
 bool prefill_generic_supports(const quamba_ssd_shape_t &s);
 
 }  // namespace quamba

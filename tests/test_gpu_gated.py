@@ -53,6 +53,30 @@ def test_prefill_gated(gpu_lib, flags, use_z, use_dt):
     assert ey <= Y_TOL and eh <= H_TOL
 
 
+@pytest.mark.parametrize("batch,L", [(3, 161), (6, 300)])
+@pytest.mark.parametrize("use_z,use_dt", [(True, False), (False, True), (True, True)])
+def test_prefill_gated_on_workgroups_of_sixteen_waves(gpu_lib, batch, L, use_z, use_dt):
+    """72 pairs run in channel halves, 144 as whole heads, where the gate leaves LDS one place for the C rows."""
+    import torch
+    q = gpu_lib
+    s = W.CONFIGS["m2_130m"].with_(batch=batch, seqlen=L)
+    sc, prob, r = make_problem(s, 24, calib_tokens=256)
+    g = make_gate_inputs(s, r, 24)
+    dt_ref = oracle.dt_from_codes(g["dt_q"], g["dt_scale"], g["dt_bias"]).astype(np.float32) if use_dt else prob["dt"]
+    yref, href, _ = oracle.ref_prefill(sc, prob["x"], prob["B"], prob["C"], dt_ref, prob["A"], prob["D"])
+    if use_z:
+        yref = oracle.silu_gate(yref, g["z"], g["z_scale"])
+    t = {k: (torch.from_numpy(v).cuda() if v is not None else None) for k, v in prob.items()}
+    y = torch.full((batch, L, s.nheads, s.headdim), float("nan"), dtype=torch.float16, device="cuda")
+    fin = torch.full((batch, s.nheads, s.headdim, s.d_state), float("nan"), device="cuda")
+    q.quamba_ssd_prefill(to_shape(q, s), q.DeviceScales(host_scales(q, sc)), t["x"], t["B"], t["C"],
+                         None if use_dt else t["dt"], t["A"], t["D"], None, y, fin, gate=_gate(q, g, use_z, use_dt))
+    yg, hg = y.cpu().numpy().astype(np.float64), fin.cpu().numpy().astype(np.float64)
+    assert np.isfinite(yg).all() and np.isfinite(hg).all()
+    assert np.abs(yg - yref).max() <= Y_TOL * np.abs(yref).max()
+    assert np.abs(hg - href).max() <= H_TOL * np.abs(href).max()
+
+
 @pytest.mark.parametrize("flags", [0, NO_SPLIT])
 def test_prefill_gated_with_the_sequence_split(gpu_lib, flags):
     """130M-shaped layer at full length with both side inputs and a workspace: the launch is cut along the sequence

@@ -162,10 +162,14 @@ def test_sequence_split_against_the_oracle_and_the_unsplit_launch(gpu_lib, H, G,
     (1, 24, 1, 385, False),    # four chunks: both LDS sets are used again
     (1, 40, 1, 2040, False),   # three segments of the sequence split, the last one ragged
     (2, 5, 1, 161, True),      # the skip term leaves the fp16 range: added in the epilogue
+    (3, 43, 1, 129, False),    # whole heads: one pair more than every other compute unit, the second chunk a single token
+    (2, 128, 8, 289, False),   # whole heads on every compute unit, three chunks: every place in LDS is used again
+    (2, 72, 1, 512, False),    # whole heads, whole chunks
+    (3, 48, 1, 161, True),     # whole heads, the skip term in the epilogue
 ])
 def test_short_batches_on_workgroups_of_sixteen_waves(gpu_lib, b, H, G, L, tiny_scales):
-    """At most half a (sequence, head) pair per compute unit and more than one chunk, with and without the final state and
-    an initial state: against the oracle."""
+    """At most a (sequence, head) pair per compute unit (channel halves with at most half a pair) and more than one chunk, with
+    and without the final state and an initial state: against the oracle."""
     s = W.CONFIGS["m2_8b_b1"].with_(batch=b, seqlen=L, nheads=H, ngroups=G)
     sc, prob, _ = make_problem(s, 77, calib_tokens=256)
     if tiny_scales:
