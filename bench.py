@@ -96,7 +96,7 @@ MAMBA1_MIN_SLOTS = 8.0
 CONV_MIN_SLOTS = 17.0
 # Executed vector instructions per element by the counters (rocprofv3 SQ_INSTS_VALU x 64 / elements), for information:
 MAMBA1_EXECUTED_PER_ELEMENT = 8.3   # of which 1.06 quarter-rate exponentials
-CONV_EXECUTED_PER_ELEMENT = 19.6    # 18.3 in the main loop (two quarter-rate), set-up and the exact-sequence reruns
+CONV_EXECUTED_PER_ELEMENT = 17.8    # 15.4 in the main loop (two quarter-rate), set-up and the exact-sequence reruns
 SPIN_UP_MS = float(os.environ.get("QUAMBA_BENCH_SPIN_UP_MS", "80"))   # untimed device work in front of every timed region, after the W warm-up launches (see time_region)
 
 
@@ -668,7 +668,7 @@ def main() -> int:
             "steps": args.steps, "higher_is_better": False, "wall_us_per_call": cwall * 1e3,
             "config": {"workload": "%s: %d tokens x %d channels [x|B|C], 4 taps, int8 in, int8 x/B/C out with the "
                                    "scan's cell and group scales" % (s.name, s.batch * s.seqlen, Ct)},
-            "roofline": {"kernel": "conv1d_q8_wide_kernel", "bound": "alu", "achieved": cops / (cms * 1e-3) / 1e12,
+            "roofline": {"kernel": "conv1d_q8_vec_kernel", "bound": "alu", "achieved": cops / (cms * 1e-3) / 1e12,
                          "peak": ALU_PEAK_TOPS, "unit": "Top/s (fp32 vector instructions x 64 lanes)",
                          "frac": cops / (cms * 1e-3) / 1e12 / ALU_PEAK_TOPS,
                          "slots_per_element": CONV_MIN_SLOTS, "executed_per_element": CONV_EXECUTED_PER_ELEMENT,
@@ -679,7 +679,7 @@ def main() -> int:
                                  "pack), against one slot per lane and cycle; the kernel executes %.1f vector "
                                  "instructions per element by the counters (executed_per_element), so added "
                                  "instructions lower frac" % (CONV_MIN_SLOTS, CONV_EXECUTED_PER_ELEMENT)},
-            "roofline_hbm": {"kernel": "conv1d_q8_wide_kernel", "bound": "hbm", "achieved": cgbs,
+            "roofline_hbm": {"kernel": "conv1d_q8_vec_kernel", "bound": "hbm", "achieved": cgbs,
                              "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": cgbs / HBM_PEAK_GBS,
                              **traffic_fields(s.name + "_conv1d")},
             "saturated_fraction": float((cx == 127).float().mean().item()),

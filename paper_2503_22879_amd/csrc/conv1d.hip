@@ -19,10 +19,11 @@ namespace quamba {
 namespace {
 
 constexpr int kWaveSlots = 4096;  // waves that keep the device full (1024 SIMDs x 4)
-constexpr int kSegWide = 32;     // tokens per workgroup of the 16-channel kernel
-// A sequence with more segments of 16 tokens than a grid may have has 16-channel waves enough for that kernel, whatever its
-// channels, and its segments of 32 tokens fit as long as the entry point takes the sequence.
-static_assert((16 * kMaxGridY) / kSegWide >= kWaveSlots && kConvMaxTokens == kSegWide * kMaxGridY, "limits of the segments");
+constexpr int kSegMax = 32;      // tokens per workgroup of the vector kernel at most
+constexpr int kSegWaves = 6144;  // shorter segments make no more waves than this
+// A sequence with more segments of kSegMax - 4 tokens than a grid may have makes more waves than kSegWaves of them, whatever its
+// channels, and its segments of kSegMax fit as long as the entry point takes the sequence.
+static_assert(kMaxGridY >= kSegWaves && kConvMaxTokens == kSegMax * kMaxGridY, "limits of the segments");
 constexpr int kStepSeqs = 8;   // most sequences per thread of the one-token kernel
 constexpr int kAhead = 4;      // tokens whose loads are in flight
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -172,18 +173,79 @@ __device__ __forceinline__ uint32_t codes_of_windows(const uint32_t (&win)[4], c
     return o;
 }
 
+// The same codes with less per code, for threads that make many: the fast evaluation in four steps on constants of the
+// channel,
+//     v' = acc (s inv) + bias inv,  t = acc (-s log2 e) - bias log2 e,  u = v' / (1 + 2^t) + 128,  code = rint(u) - 128,
+// whose conversion to a byte rounds to even and saturates (a NaN becomes 0, the code -128, as the exact sequence's clamp has
+// it).  With V = acc s + bias and R = inv SiLU(V) in real numbers, e = 2^-24, |V SiLU'(V)| <= |SiLU(V)| + 0.44,
+// V^2 w (1 - w) <= 0.44 and |V| w (1 - w) <= 0.23 for w = 1 / (1 + exp(-V)), the exact sequence's value is within
+//     9 e |R| + e inv (1.8 + 1.1 |bias|)
+// of R (roundings of v; the exponential's argument, 2 e |V|, and polynomial, 3 e; four operations), and u - 128 within
+//     7 e |R| + e inv (1.4 + 3 |bias|) + 2^-17
+// (constants, v' and t: 3 e |V| + 4 e |bias|; hardware exponential and reciprocal, 2 e each; the sum's rounding below 256).
+// 16 e = 9.6e-7 and |R| <= |v'|, so a distance of u from its integer of less than 0.5 - 1.3e-6 |v'| - th, th = inv (2.5e-7 +
+// 3e-7 |bias|) + 1e-5, decides the exact sequence's code.  Other codes are redone with it (NaN compares as such), and all
+// of them where a constant is so large that a finite sum could leave the range of fp32.
+struct FastChannels4 {
+    f32x4 a, b, t;
+    float limit;  // 0.5 less the largest th of the four; negative: always the exact sequence
+    __device__ __forceinline__ FastChannels4(float s, const f32x4 &bias, const float (&inv)[4])
+    {
+        float th = 0.0f, big = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            a[j] = s * inv[j];
+            b[j] = bias[j] * inv[j];
+            t[j] = -bias[j] * from_bits(0x3FB8AA3Bu);
+            const float ab = __builtin_fabsf(bias[j]);
+            th = fmaxf(th, __builtin_fabsf(inv[j]) * __builtin_fmaf(3e-7f, ab, 2.5e-7f));
+            big += 65536.0f * __builtin_fabsf(a[j]) + __builtin_fabsf(b[j]) + ab;
+        }
+        big += 65536.0f * __builtin_fabsf(s);
+        limit = big < 1e37f ? 0.49999f - th : -1.0f;  // not so for a NaN
+    }
+    __device__ __forceinline__ uint32_t codes(const uint32_t (&win)[4], const u32x4 &w, float s, float minus_s_log2e, const f32x4 &bias,
+                                              const float (&inv)[4]) const
+    {
+        float e[4];
+        uint32_t o = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float acc = (float)__builtin_amdgcn_sdot4((int)win[j], (int)w[j], 0, false);
+            const float E = __builtin_amdgcn_exp2f(__builtin_fmaf(acc, minus_s_log2e, t[j]));
+            const float v = __builtin_fmaf(acc, a[j], b[j]);
+            const float u = __builtin_fmaf(v, __builtin_amdgcn_rcpf(1.0f + E), 128.0f);
+            o = __builtin_amdgcn_cvt_pk_u8_f32(u, j, o);
+            e[j] = __builtin_fmaf(1.3e-6f, __builtin_fabsf(v), __builtin_fabsf(u - __builtin_rintf(u)));
+        }
+        o ^= 0x80808080u;
+        const float m = fmaxf(fmaxf(fmaxf(e[0], e[1]), e[2]), e[3]);
+        if (__builtin_amdgcn_ballot_w64(!(m < limit)) != 0) {  // about 1 in 30 of the wave's tokens
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (__builtin_amdgcn_ballot_w64(!(e[j] < limit)) != 0) {
+                    const int acc = __builtin_amdgcn_sdot4((int)win[j], (int)w[j], 0, false);
+                    const uint32_t code = code1(activation_over_scale(acc, s, bias[j], inv[j]));
+                    o = (o & ~(0xffu << (8 * j))) | (code << (8 * j));
+                }
+        }
+        return o;
+    }
+};
+
 // Vector kernel: headdim, d_state multiples of 16 and 16-byte aligned tensors.  A thread owns 4 consecutive channels and walks
 // a segment of a.seg tokens, the loads of the next 4 in flight; grid = (channel blocks of 64 x 4, segments, batch); one
-// wave per workgroup, no LDS, no barrier.  Bound by the vector ALU where there are enough waves, by the chain from launch to
-// store where there are few.  4 channels keep the kernel at 41 registers, so that 8 waves share a SIMD, and the chain
-// short; 16 channels (116 registers, 4 waves, a quarter of the waves) and 8 were slower below 4 of the former's waves per SIMD: 16 tokens of
-// 1792 channels 16.8 (16 channels) / 5.6 (8) / 3.6 us (4), 1531 tokens of 10240 channels 22.0 / 17.5 / 14.6 us, 8 x 2048
-// tokens of 5376 channels 67.9 / 59.5 / 55.6 us.
-__global__ __launch_bounds__(64) void conv1d_q8_vec_kernel(ConvArgs a)
+// wave per workgroup, no LDS, no barrier.  Bound by the vector ALU where there are enough waves (by the counters 17.8
+// instructions per code with the set-up and 97 % busy at 4 x 4096 tokens of 10240 channels), by the chain from launch to
+// store where there are few.  4 channels keep the kernel at 61 registers, so that 8 waves share a SIMD, and the chain short.  With each load
+// waited for where it was made (as the compiler has it for a load behind a branch), and one more rounding, clamp and
+// compare per code: 8 x 2048 tokens of 5376 channels 61 -> 49 us, 4 x 4096 of 10240 108 -> 87 (there with 16 channels per
+// thread), 1 x 4096 32 -> 25, 1531 14.6 -> 11.3; of that the shorter evaluation 5 us of the first.
+__global__ __launch_bounds__(64, 8) void conv1d_q8_vec_kernel(ConvArgs a)
 {
     const int HP = a.s.nheads * a.s.headdim, GN = a.s.ngroups * a.s.d_state, Ct = HP + 2 * GN;
-    const int c0 = 4 * (blockIdx.x * 64 + threadIdx.x);
-    if (c0 >= Ct) return;
+    const uint32_t c0 = 4 * (blockIdx.x * 64 + threadIdx.x);
+    if ((int)c0 >= Ct) return;
     const int b = blockIdx.z, L = a.s.seqlen;
     const int t0 = blockIdx.y * a.seg, t1 = min(t0 + a.seg, L);
 
@@ -195,13 +257,20 @@ __global__ __launch_bounds__(64) void conv1d_q8_vec_kernel(ConvArgs a)
         before[k] = rp ? *reinterpret_cast<const uint32_t *>(rp + c0) : 0u;
     }
     const int8_t *ip = a.in + ((size_t)b * L + t0) * Ct + c0;
+    // Tokens past the segment's end read its last one: behind a branch the compiler would wait for each load where it is made.
+    auto request = [&](int t) {
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u)
-        nx[u] = t0 + u < t1 ? __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(ip + (size_t)u * Ct)) : 0u;
+        for (int u = 0; u < kAhead; ++u)
+            nx[u] = *reinterpret_cast<const uint32_t *>(ip + (size_t)min(t - t0 + u, t1 - t0 - 1) * Ct);
+    };
+    request(t0);
     const u32x4 w = *reinterpret_cast<const u32x4 *>(a.weight + (size_t)c0 * 4);
     f32x4 bias = {0.0f, 0.0f, 0.0f, 0.0f};
     if (a.bias) bias = *reinterpret_cast<const f32x4 *>(a.bias + c0);
     const Channels4 ch(a, c0);
+    const FastChannels4 fast(a.in_w_scale, bias, ch.inv);
+    float minus_s_log2e = -a.in_w_scale * from_bits(0x3FB8AA3Bu);
+    asm volatile("" : "+v"(minus_s_log2e));  // a vector register: next to a scalar operand instructions of two waves do not pair
 
     // the window before the segment: tokens t0-3 .. t0-1 in bytes 1..3 (byte 0 is shifted out by the first token)
     uint32_t win[4] = {0, 0, 0, 0};
@@ -214,17 +283,25 @@ __global__ __launch_bounds__(64) void conv1d_q8_vec_kernel(ConvArgs a)
     for (int k = 0; k < 3; ++k) shift_in(before[k]);
 
     int8_t *op = ch.dst + ((size_t)b * L + t0) * ch.row + ch.col;
-    for (int t = t0; t < t1; t += kAhead) {
+    int t = t0;
+    auto token = [&](uint32_t codes) {
+        shift_in(codes);
+        __builtin_nontemporal_store(fast.codes(win, w, a.in_w_scale, minus_s_log2e, bias, ch.inv),
+                                    reinterpret_cast<uint32_t *>(op));
+        op += ch.row;
+        ++t;
+    };
+    // whole groups, so that the wait for the loads of the next one counts its stores behind them, then the rest
+    while (t + kAhead <= t1) {
+        uint32_t cur[kAhead];
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            if (t + u >= t1) break;
-            shift_in(nx[u]);
-            if (t + u + kAhead < t1)
-                nx[u] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(ip + (size_t)(t - t0 + u + kAhead) * Ct));
-            __builtin_nontemporal_store(codes_of_windows(win, w, a.in_w_scale, bias, ch.inv),
-                                        reinterpret_cast<uint32_t *>(op + (size_t)(t - t0 + u) * ch.row));
-        }
+        for (int u = 0; u < kAhead; ++u) cur[u] = nx[u];
+        request(t + kAhead);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) token(cur[u]);
     }
+#pragma unroll 1
+    for (int u = 0; t < t1; ++u) token(u == 0 ? nx[0] : u == 1 ? nx[1] : nx[2]);
 
     // the state to carry on: the last three input tokens = bytes 1..3 of the windows after the last token
     if (a.state_out && t1 == L) {
@@ -233,149 +310,6 @@ __global__ __launch_bounds__(64) void conv1d_q8_vec_kernel(ConvArgs a)
             const uint32_t lo = __builtin_amdgcn_perm(win[1], win[0], 0x0c0c0400u + 0x00000101u * (k + 1));
             const uint32_t hi = __builtin_amdgcn_perm(win[3], win[2], 0x04000c0cu + 0x01010000u * (k + 1));
             *reinterpret_cast<uint32_t *>(a.state_out + ((size_t)b * 3 + k) * Ct + c0) = lo | hi;
-        }
-    }
-}
-
-// The vector kernel with 16 consecutive channels per thread, for launches that give it 4 waves per SIMD even so: the loads,
-// addresses and stores of a token are shared by four times the channels.  Same conditions; grid = (channel blocks of 64 x 16,
-// segments, batch); one wave per workgroup, no LDS, no barrier.
-__global__ __launch_bounds__(64) void conv1d_q8_wide_kernel(ConvArgs a)
-{
-    const int HP = a.s.nheads * a.s.headdim, GN = a.s.ngroups * a.s.d_state, Ct = HP + 2 * GN;
-    const int c0 = 16 * (blockIdx.x * 64 + threadIdx.x);
-    if (c0 >= Ct) return;
-    const int b = blockIdx.z, L = a.s.seqlen;
-    const int t0 = blockIdx.y * a.seg, t1 = min(t0 + a.seg, L);
-
-    // per-channel constants: packed taps, bias, reciprocal output scale (one correctly rounded division each)
-    uint32_t w[16];
-    float bias[16], inv[16];
-    int8_t *dst; int row, col;
-    {
-        const u32x4 *wp = reinterpret_cast<const u32x4 *>(a.weight + (size_t)c0 * 4);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const u32x4 v = wp[q];
-            w[4 * q] = v[0]; w[4 * q + 1] = v[1]; w[4 * q + 2] = v[2]; w[4 * q + 3] = v[3];
-        }
-        if (a.bias) {
-            const f32x4 *bp = reinterpret_cast<const f32x4 *>(a.bias + c0);  // c0 is a multiple of 16: 64-byte aligned
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 v = bp[q];
-                bias[4 * q] = v[0]; bias[4 * q + 1] = v[1]; bias[4 * q + 2] = v[2]; bias[4 * q + 3] = v[3];
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 16; ++j) bias[j] = 0.0f;
-        }
-        // The 16 channels share one output tensor and one head or state group (16 divides headdim and d_state), so
-        // one lookup finds the first channel's cell; the channel ranges of a head are ascending, so the following
-        // channels only step to the next range when they pass its end.
-        if (c0 < HP) {
-            SsdArgs t;
-            t.s = a.s; t.x_scales = a.x_scales; t.head_cluster_end = a.head_cluster_end;
-            t.chan_cluster_end = a.chan_cluster_end;
-            const int h = c0 / a.s.headdim, p0 = c0 - h * a.s.headdim;
-            int base;
-            int cell = cell_lookup(t, h, p0, &base);
-            const int last = base + a.s.n_chan_clusters - 1;
-            int end = cell < last ? a.chan_cluster_end[cell] : a.s.headdim;
-            float iv = __fdiv_rn(1.0f, a.x_scales[cell]);
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                while (p0 + j >= end) {  // at most n - 1 steps over the 16 channels together
-                    ++cell;
-                    end = cell < last ? a.chan_cluster_end[cell] : a.s.headdim;
-                    iv = __fdiv_rn(1.0f, a.x_scales[cell]);
-                }
-                inv[j] = iv;
-            }
-            dst = a.x_out; row = HP; col = c0;
-        } else {
-            const bool isB = c0 < HP + GN;
-            const int cg = c0 - HP - (isB ? 0 : GN);
-            const float iv = __fdiv_rn(1.0f, (isB ? a.B_scales : a.C_scales)[cg / a.s.d_state]);
-#pragma unroll
-            for (int j = 0; j < 16; ++j) inv[j] = iv;
-            dst = isB ? a.B_out : a.C_out; row = GN; col = cg;
-        }
-    }
-
-    // the window before the segment: tokens t0-3 .. t0-1 in bytes 1..3 (byte 0 is shifted out by the first token)
-    uint32_t win[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) win[j] = 0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int8_t *rp = token_row(a, b, t0 - 3 + k, Ct);
-        u32x4 v = {0, 0, 0, 0};
-        if (rp) v = *reinterpret_cast<const u32x4 *>(rp + c0);
-#pragma unroll
-        for (int j = 0; j < 16; ++j)  // bytes: win.b1, win.b2, win.b3, new.b(j & 3)
-            win[j] = __builtin_amdgcn_perm(v[j >> 2], win[j], 0x04030201u + ((uint32_t)(j & 3) << 24));
-    }
-
-    const int8_t *ip = a.in + ((size_t)b * L + t0) * Ct + c0;
-    u32x4 nx[kAhead];
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u)
-        nx[u] = t0 + u < t1 ? __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(ip + (size_t)u * Ct))
-                            : (u32x4){0, 0, 0, 0};
-    int8_t *op = dst + ((size_t)b * L + t0) * row + col;
-
-    for (int t = t0; t < t1; t += kAhead) {
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            if (t + u >= t1) break;
-            const u32x4 cur = nx[u];
-            if (t + u + kAhead < t1)
-                nx[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(ip + (size_t)(t - t0 + u + kAhead) * Ct));
-            // Codes from the fast evaluation wherever it provably rounds like the exact sequence; channels in which any
-            // lane sits too close to a rounding boundary (about 1 % of the channel-tokens of a wave) are redone with
-            // the exact sequence below, so every code is the exact sequence's code.
-            u32x4 o;
-            uint32_t redo = 0;  // wave-uniform: bit j = channel j needs the exact sequence
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float r[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int j = 4 * q + i;
-                    win[j] = __builtin_amdgcn_perm(cur[q], win[j], 0x04030201u + ((uint32_t)i << 24));
-                    const int acc = __builtin_amdgcn_sdot4((int)win[j], (int)w[j], 0, false);
-                    r[i] = __builtin_amdgcn_fmed3f(activation_over_scale_fast(acc, a.in_w_scale, bias[j], inv[j]),
-                                                   -128.0f, 127.0f);
-                    redo |= (__builtin_amdgcn_ballot_w64(near_rounding_boundary(r[i])) != 0 ? 1u : 0u) << j;
-                }
-                o[q] = codes4(r[0], r[1], r[2], r[3]);
-            }
-            if (redo) {
-#pragma unroll
-                for (int j = 0; j < 16; ++j)
-                    if (redo & (1u << j)) {
-                        const int acc = __builtin_amdgcn_sdot4((int)win[j], (int)w[j], 0, false);
-                        const uint32_t code = code1(activation_over_scale(acc, a.in_w_scale, bias[j], inv[j]));
-                        o[j >> 2] = (o[j >> 2] & ~(0xffu << (8 * (j & 3)))) | (code << (8 * (j & 3)));
-                    }
-            }
-            __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(op + (size_t)(t - t0 + u) * row));
-        }
-    }
-
-    // the state to carry on: the last three input tokens = bytes 1..3 of the windows after the last token
-    if (a.state_out && t1 == L) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            u32x4 o;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t lo = __builtin_amdgcn_perm(win[4 * q + 1], win[4 * q], 0x0c0c0400u + 0x00000101u * (k + 1));
-                const uint32_t hi = __builtin_amdgcn_perm(win[4 * q + 3], win[4 * q + 2], 0x04000c0cu + 0x01010000u * (k + 1));
-                o[q] = lo | hi;
-            }
-            *reinterpret_cast<u32x4 *>(a.state_out + ((size_t)b * 3 + k) * Ct + c0) = o;
         }
     }
 }
@@ -468,29 +402,23 @@ bool vec_ok(const ConvArgs &a)
 
 }  // namespace
 
-// Tokens per workgroup of the vector kernel (sequences whose segments of 16 do not fit a grid never come here, see the
-// limits above).  Longer segments share the set-up and the 3-token halo between more tokens,
-// shorter ones give more waves and a shorter chain.  Measured with 4 / 8 / 16 / 32 tokens: 219 tokens of 5376 channels
-// (1155 waves of 4 tokens) 4.7 / 5.3 / 7.4 / 11.6 us, 1000 (5250) 8.15 / 8.22 / 9.9 / 13.7; 3 x 200 of 10240 channels
-// (6000) 8.24 / 8.19 / 9.9 / 13.4, 1531 (15320) 15.5 / 14.6 / 15.1 / 18.0, 4096 (40960) 33.7 / 30.0 / 30.4 / 31.2; 8 x 2048 of
-// 5376 channels (86016) 70.9 / 59.0 / 55.6 / 57.0.
+// Tokens per workgroup of the vector kernel.  Longer segments share the set-up and the 3-token halo between more tokens, shorter
+// ones give more waves and a shorter chain: 4 tokens while that is at most 3 waves per SIMD, else the shortest with at most
+// 6.  Measured with 4 / 8 / 12 tokens: 500 tokens of 5376 channels (2625 waves of 4 tokens) 5.2 / 5.5 / 5.5 us, 2048 of
+// 1792 (3584) 6.2 / 5.8 / 6.7, 1000 of 5376 (5250) 7.5 / 6.7 / 7.0, 1000 of 10240 (10000) 10.2 / 9.0 / 10.0; with 8 / 12 /
+// 16 / 20 / 32: 1531 of 10240 (15320) 13.0 / 11.8 / 12.2 / 11.9 / -, 4096 (40960) 27.8 / 26.5 / 25.5 / 24.9 / 25.9; with 16 / 20 / 32 /
+// 44 / 80: 8 x 2048 of 5376 (86016) 48.9 / 49.1 / 50.1 / 48.3 / 52, 4 x 4096 of 10240 (163840) 94 / 90 / 87 / 88 / 94, 16 x 4096
+// of 5376 (344064) 195 / 193 / 184 / 185 / 184.
 int conv1d_segment_tokens(const quamba_ssd_shape_t &s, bool same_state)
 {
     if (same_state) return s.seqlen;  // one buffer is both states: whoever writes it has to be the one who read it
     const int64_t Ct = (int64_t)s.nheads * s.headdim + 2LL * s.ngroups * s.d_state;
     const int64_t rows = (Ct / 4 + 63) / 64 * s.batch;
     auto waves = [&](int seg) { return rows * (((int64_t)s.seqlen + seg - 1) / seg); };
-    if (waves(4) <= 6 * kWaveSlots / 4) return 4;
-    if (waves(8) <= 6 * kWaveSlots) return 8;
-    return 16;
-}
-
-// Waves of the 16-channel kernel; 0 for sequences shorter than a segment (among them all that may have one buffer as both
-// states, which has to be one segment).
-static int64_t wide_waves(const quamba_ssd_shape_t &s)
-{
-    const int64_t Ct = (int64_t)s.nheads * s.headdim + 2LL * s.ngroups * s.d_state;
-    return s.seqlen < kSegWide ? 0 : (Ct / 16 + 63) / 64 * s.batch * (((int64_t)s.seqlen + kSegWide - 1) / kSegWide);
+    if (waves(4) <= kSegWaves / 2) return 4;
+    int seg = 8;
+    while (seg < kSegMax && waves(seg) > kSegWaves) seg += 4;
+    return seg;
 }
 
 hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream)
@@ -502,15 +430,6 @@ hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream)
         const int seqs = (int)std::min<int64_t>(kStepSeqs, std::max<int64_t>(1, blocks * a.s.batch / kWaveSlots));
         const dim3 grid((unsigned)blocks, (unsigned)((a.s.batch + seqs - 1) / seqs));
         hipLaunchKernelGGL(conv1d_q8_step_kernel, grid, dim3(64), 0, stream, a, seqs);
-    } else if (vec_ok(a) && wide_waves(a.s) >= kWaveSlots) {
-        // Enough waves for the 16-channel kernel.  4 / 16 channels: 4 x 4096 tokens of 10240 channels 108.2 / 101.5 us, 16 x
-        // 4096 of 1792 77.4 / 74.4, 6 x 4096 of 5376 87.5 / 88.9; with fewer waves 2 x 4096 of 10240 57.4 / 62.0, 1 x 4096
-        // 31.4 / 44.1.
-        ConvArgs v = a;
-        v.seg = kSegWide;
-        const dim3 grid((unsigned)((Ct / 16 + 63) / 64), (unsigned)((a.s.seqlen + (int64_t)v.seg - 1) / v.seg),
-                        (unsigned)a.s.batch);
-        hipLaunchKernelGGL(conv1d_q8_wide_kernel, grid, dim3(64), 0, stream, v);
     } else if (vec_ok(a)) {
         ConvArgs v = a;
         v.seg = conv1d_segment_tokens(a.s, a.state_in && a.state_in == a.state_out);

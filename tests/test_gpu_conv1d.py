@@ -119,9 +119,8 @@ def test_one_token_kernel(gpu_lib, batch, H, P, N, m, n, state):
                                                (16, 3085, 14, 64, 64, 2, 2),   # segments of 16, the last of 13
                                                (64, 3085, 4, 16, 16, 2, 2)])   # 16 channels per thread, the last of 13
 def test_segments_and_carried_state(gpu_lib, batch, L, H, P, N, m, n):
-    """Every segment length of the vector kernel, and the kernel with 16 channels per thread, with ragged last segments,
-    from a carried state.  (The step to segments of 16 is at 24576 waves of 8 tokens: 1024 channels, 16 x 386 segments x
-    4 blocks; to 16 channels per thread at 4096 waves of 32 tokens: 96 channels, 64 x 97 segments.)"""
+    """Short and the longest segments of the vector kernel, with ragged last ones, from a carried state.  (Longer ones
+    than 8 tokens from 6144 waves of 8 up, 32 where 28 still make more than 6144.)"""
     s = W.LayerShape("seg", batch, L, H, P, N, 1, 16, m, n)
     sc, _, _ = make_problem(s.with_(batch=1, seqlen=8), seed=14, calib_tokens=128)
     st = np.random.default_rng(14).integers(-128, 128, size=(batch, 3, H * P + 2 * N), dtype=np.int8)
@@ -131,7 +130,7 @@ def test_segments_and_carried_state(gpu_lib, batch, L, H, P, N, m, n):
 @pytest.mark.parametrize("batch,L,H,P,N,m,n,bias", [(64, 2049, 6, 48, 16, 3, 7, True),   # ranges that end inside a thread
                                                     (16, 4096, 18, 64, 32, 1, 1, False)])  # a second, ragged block; no bias
 def test_sixteen_channels_per_thread(gpu_lib, batch, L, H, P, N, m, n, bias):
-    """Launches of at least 4096 waves of 32 tokens: more channel ranges than four, ends of ranges inside the 16 channels of a
+    """Launches of at least 4096 waves of 32 tokens: more channel ranges than four, ends of ranges inside the channels of a
     thread, no bias, and a channel block that fills no whole wave."""
     s = W.LayerShape("wide", batch, L, H, P, N, 1, 16, m, n)
     sc, _, _ = make_problem(s.with_(batch=1, seqlen=8), seed=16, calib_tokens=128)
@@ -140,6 +139,24 @@ def test_sixteen_channels_per_thread(gpu_lib, batch, L, H, P, N, m, n, bias):
     inp = make_conv_inputs(s, seed=16)
     st = np.random.default_rng(16).integers(-128, 128, size=(batch, 3, H * P + 2 * N), dtype=np.int8) if bias else None
     _check(gpu_lib, s, sc, inp if bias else dict(inp, bias=None), st)
+
+
+@pytest.mark.parametrize("L,scale,bias,s_in", [
+    (1531, 1.0, 1.0, 1.0),       # segments of 16 tokens, the last of 11
+    (1150, 1.0, 30.0, 1.0),      # of 12, the last of 10; large biases
+    (2301, 1e-3, 1.0, 1e-3),     # of 24, the last of 21; small outputs: a wider margin around the rounding boundaries
+    (45, 1e-4, 100.0, 1.0),      # a margin of most of a code
+    (45, 1e-9, 1.0, 1.0),        # wider than a code: the exact sequence throughout
+    (45, 1e-3, 0.0, 1e36)])      # constants beyond the range of fp32
+def test_margin_around_the_rounding_boundaries(gpu_lib, L, scale, bias, s_in):
+    """The codes are the exact sequence's whatever the constants the fast evaluation's error bound depends on."""
+    s = W.LayerShape("margin", 64, L, 4, 16, 16, 1, 16, 2, 2)
+    sc, _, _ = make_problem(s.with_(batch=1, seqlen=8), seed=17, calib_tokens=128)
+    for name in ("x_scales", "B_scales", "C_scales"):
+        setattr(sc, name, (np.asarray(getattr(sc, name)) * np.float32(scale)).astype(np.float32))
+    inp = make_conv_inputs(s, seed=17)
+    _check(gpu_lib, s, sc, dict(inp, bias=inp["bias"] * np.float32(bias),
+                                in_w_scale=float(np.float32(inp["in_w_scale"] * s_in))))
 
 
 @pytest.mark.parametrize("L", [2, 7, 16])
