@@ -233,10 +233,23 @@ __global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, con
                 float h = 0.0f, P = dtsum * ah.x;
 #pragma unroll
                 for (int i = 0; i < kE; ++i) dec[i] = dt[i] * ah.x;
+                // 64 lanes per channel leave 2 waves on a SIMD, too few to cover the LDS reads, and registers to spare: there the
+                // operands are read while the exponentials and the lane scan run (1536 channels of one sequence, 4096
+                // tokens 48.7 -> 45.5 us, 700 tokens 13.7 -> 13.0).  With 4 waves that changes nothing (306 / 305 us at 4 x
+                // 4096 tokens of 5120 channels) or spills.
+                f32x4 Bn[4], Cn[4];
+                auto ahead = [&](f32x4 (&v)[4], const f32x4 *from) {
+                    if constexpr (LPC == 64) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) v[q] = from[(n * 4 + q) * LPC + sub];
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                };
+                ahead(Bn, s_B);
                 exp2_burst(dec, P);  // P becomes the product of the lane's 16 decay factors
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const f32x4 Bv = s_B[(n * 4 + q) * LPC + sub];
+                    const f32x4 Bv = LPC == 64 ? Bn[q] : s_B[(n * 4 + q) * LPC + sub];
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const int i = 4 * q + k;
@@ -244,6 +257,7 @@ __global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, con
                         h = fmaf(dec[i], h, in[i]);
                     }
                 }
+                ahead(Cn, s_C);
                 wave_scan<LPC>(P, h);
                 // the state behind this lane's tokens, the pairs up to it applied to the carried state, is the state in
                 // front of the next lane's; behind the last lane's it is the state after the tile
@@ -260,7 +274,7 @@ __global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, con
                 if (sub == LPC - 1) s_AH[ch * N + n0 + n].y = carry;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const f32x4 Cv = s_C[(n * 4 + q) * LPC + sub];
+                    const f32x4 Cv = LPC == 64 ? Cn[q] : s_C[(n * 4 + q) * LPC + sub];
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const int i = 4 * q + k;
