@@ -96,8 +96,8 @@ typedef struct quamba_ssd_scales_t {
 /*
  * Bytes of device workspace with which quamba_ssd_prefill runs this shape fastest on the current device (may be 0).
  * Non-zero only for batches short enough for the sequence split of the matrix-core kernel
- * (QUAMBA_FLAG_NO_SEQ_SPLIT): the states at the segment boundaries, (segments - 1) * batch * nheads *
- * (headdim * d_state + 1) floats.  A call with a NULL, smaller or not 16-byte aligned workspace is not an error: it
+ * (QUAMBA_FLAG_NO_SEQ_SPLIT): room for the states at the segment boundaries, (segments - 1) * batch * nheads *
+ * (headdim * d_state + 1) floats for the most segments the shape may be cut into.  A call with a NULL, smaller or not 16-byte aligned workspace is not an error: it
  * takes the unsplit launch (same results to rounding, slower on such batches).  The workspace is scratch: written
  * and read by the call's own launches, contents undefined afterwards; calls that share one workspace must not
  * overlap.  Returns 0 for an invalid shape; quamba_ssd_prefill reports the error.
