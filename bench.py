@@ -36,8 +36,8 @@ KERNEL_CHUNK = 128             # tokens per chunk of prefill_mfma_kernel (the ca
 # 256 MiB device copy in the same run: factors 1.9998 and 1.0000).  These are constants taken from the committed
 # profile summaries, not measurements of this run: `traffic_source` in every roofline object names the file.
 # None for workloads that were not profiled.
-MEASURED_TRAFFIC_BYTES = {"m2_8b_b4": 498.7e6, "m2_8b_decode": 2162.3e6, "m2_8b_decode_q8": 550.9e6,
-                          "m2_8b_b4_hadamard": 402.7e6, "m2_8b_b4_conv1d": 352.1e6,
+MEASURED_TRAFFIC_BYTES = {"m2_8b_b4": 497.1e6, "m2_8b_decode": 2162.3e6, "m2_8b_decode_q8": 550.9e6,
+                          "m2_8b_b4_hadamard": 402.7e6, "m2_8b_b4_conv1d": 350.2e6,
                           "mamba1_2p8b_scan": 608.1e6, "mamba1_2p8b_decode": 178.8e6}
 TRAFFIC_SOURCE = {
     "m2_8b_b4": "profiles/hbm_traffic_prefill_m2_8b_b4_and_decode_m2_8b.txt",
@@ -96,7 +96,7 @@ MAMBA1_MIN_SLOTS = 8.0
 CONV_MIN_SLOTS = 17.0
 # Executed vector instructions per element by the counters (rocprofv3 SQ_INSTS_VALU x 64 / elements), for information:
 MAMBA1_EXECUTED_PER_ELEMENT = 8.3   # of which 1.06 quarter-rate exponentials
-CONV_EXECUTED_PER_ELEMENT = 17.8    # 15.4 in the main loop (two quarter-rate), set-up and the exact-sequence reruns
+CONV_EXECUTED_PER_ELEMENT = 18.2    # 15.4 in the main loop (two quarter-rate), set-up and the exact-sequence reruns
 SPIN_UP_MS = float(os.environ.get("QUAMBA_BENCH_SPIN_UP_MS", "80"))   # untimed device work in front of every timed region, after the W warm-up launches (see time_region)
 
 

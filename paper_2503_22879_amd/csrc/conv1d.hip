@@ -44,7 +44,8 @@ __device__ __forceinline__ float activation_over_scale(int acc, float s_cw, floa
 // The same value through the hardware's approximate base-2 exponential and reciprocal (1 unit in the last place
 // each): v / (1 + 2^(-v log2 e)) * inv.  It shares v and the rounded exponent argument with the exact sequence above
 // (whose e is 2^-|t| for the same t), so the two differ only by the roundings after that point: by less than
-// 1e-6 of the value (derivation in the design notes).  Deeply negative v gives 2^t = inf and the result -0.
+// 1e-6 of the value (the exact sequence's polynomial, 3e-7 at most, and four operations; here two units in the last place,
+// a sum and two products; the value's sensitivity to e is below 1).  Deeply negative v gives 2^t = inf and the result -0.
 __device__ __forceinline__ float activation_over_scale_fast(int acc, float s_cw, float bias, float inv)
 {
     float v = (float)acc * s_cw;
@@ -235,8 +236,8 @@ struct FastChannels4 {
 
 // Vector kernel: headdim, d_state multiples of 16 and 16-byte aligned tensors.  A thread owns 4 consecutive channels and walks
 // a segment of a.seg tokens, the loads of the next 4 in flight; grid = (channel blocks of 64 x 4, segments, batch); one
-// wave per workgroup, no LDS, no barrier.  Bound by the vector ALU where there are enough waves (by the counters 17.8
-// instructions per code with the set-up and 97 % busy at 4 x 4096 tokens of 10240 channels), by the chain from launch to
+// wave per workgroup, no LDS, no barrier.  Bound by the vector ALU where there are enough waves (by the counters 18
+// instructions per code with the set-up and 91 to 97 % busy at 4 x 4096 tokens of 10240 channels), by the chain from launch to
 // store where there are few.  4 channels keep the kernel at 61 registers, so that 8 waves share a SIMD, and the chain short.  With each load
 // waited for where it was made (as the compiler has it for a load behind a branch), and one more rounding, clamp and
 // compare per code: 8 x 2048 tokens of 5376 channels 61 -> 49 us, 4 x 4096 of 10240 108 -> 87 (there with 16 channels per
