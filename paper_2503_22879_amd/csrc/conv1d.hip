@@ -242,6 +242,8 @@ struct FastChannels4 {
 // waited for where it was made (as the compiler has it for a load behind a branch), and one more rounding, clamp and
 // compare per code: 8 x 2048 tokens of 5376 channels 61 -> 49 us, 4 x 4096 of 10240 108 -> 87 (there with 16 channels per
 // thread), 1 x 4096 32 -> 25, 1531 14.6 -> 11.3; of that the shorter evaluation 5 us of the first.
+// KEEP: plain stores, which leave the codes in the caches for the scan behind.
+template <bool KEEP>
 __global__ __launch_bounds__(64, 8) void conv1d_q8_vec_kernel(ConvArgs a)
 {
     const int HP = a.s.nheads * a.s.headdim, GN = a.s.ngroups * a.s.d_state, Ct = HP + 2 * GN;
@@ -287,8 +289,10 @@ __global__ __launch_bounds__(64, 8) void conv1d_q8_vec_kernel(ConvArgs a)
     int t = t0;
     auto token = [&](uint32_t codes) {
         shift_in(codes);
-        __builtin_nontemporal_store(fast.codes(win, w, a.in_w_scale, minus_s_log2e, bias, ch.inv),
-                                    reinterpret_cast<uint32_t *>(op));
+        uint32_t *const to = reinterpret_cast<uint32_t *>(op);
+        const uint32_t o = fast.codes(win, w, a.in_w_scale, minus_s_log2e, bias, ch.inv);
+        if (KEEP) *to = o;
+        else __builtin_nontemporal_store(o, to);
         op += ch.row;
         ++t;
     };
@@ -351,7 +355,7 @@ __global__ __launch_bounds__(64) void conv1d_q8_step_kernel(ConvArgs a, int seqs
         const uint32_t p23 = __builtin_amdgcn_perm(c.x, c.r2, 0x05010400u), q23 = __builtin_amdgcn_perm(c.x, c.r2, 0x07030602u);
         const uint32_t win[4] = {__builtin_amdgcn_perm(p23, p01, 0x05040100u), __builtin_amdgcn_perm(p23, p01, 0x07060302u),
                                  __builtin_amdgcn_perm(q23, q01, 0x05040100u), __builtin_amdgcn_perm(q23, q01, 0x07060302u)};
-        // non-temporal like the vector kernel's: with plain stores the decode step behind ran 4 % slower at batch 256
+        // non-temporal: with plain stores the decode step behind ran 4 % slower at batch 256
         __builtin_nontemporal_store(codes_of_windows(win, w, a.in_w_scale, bias, ch.inv),
                                     reinterpret_cast<uint32_t *>(ch.dst + (size_t)b * ch.row + ch.col));
         if (a.state_out) {
@@ -436,7 +440,14 @@ hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream)
         v.seg = conv1d_segment_tokens(a.s, a.state_in && a.state_in == a.state_out);
         const dim3 grid((unsigned)((Ct / 4 + 63) / 64), (unsigned)((a.s.seqlen + (int64_t)v.seg - 1) / v.seg),
                         (unsigned)a.s.batch);
-        hipLaunchKernelGGL(conv1d_q8_vec_kernel, grid, dim3(64), 0, stream, v);
+        // Plain stores where the caches can hold the codes until the scan reads them.  Convolution and scan together,
+        // non-temporal / plain: 1531 tokens of 10240 channels (16 MB) with gate and step-size codes 48.4 / 46.1 us, 2048 of 1792
+        // 30.8 / 29.9, 1000 of 5376 29.4 / 28.7, 8 x 2048 of 5376 (88 MB) 188.3 / 187.2, 2 x 4096 of 10240 (84 MB) 157.3 / 157.6,
+        // 4 x 4096 of 10240 (168 MB) 272.9 / 276.5, 16 x 2048 of 5376 (176 MB) 334.3 / 339.9.
+        if ((int64_t)a.s.batch * a.s.seqlen * Ct <= 96LL << 20)
+            hipLaunchKernelGGL(conv1d_q8_vec_kernel<true>, grid, dim3(64), 0, stream, v);
+        else
+            hipLaunchKernelGGL(conv1d_q8_vec_kernel<false>, grid, dim3(64), 0, stream, v);
     } else {
         const dim3 grid((unsigned)((Ct + 255) / 256), (unsigned)a.s.batch);
         hipLaunchKernelGGL(conv1d_q8_any_kernel, grid, dim3(256), 0, stream, a);

@@ -159,6 +159,32 @@ def test_margin_around_the_rounding_boundaries(gpu_lib, L, scale, bias, s_in):
                                 in_w_scale=float(np.float32(inp["in_w_scale"] * s_in))))
 
 
+def test_large_call_is_its_sequences(gpu_lib):
+    """More codes than are left in the caches (96 MiB) against calls of a few of the sequences, codes bit for bit."""
+    import torch
+    s = W.CONFIGS["m2_130m"].with_(batch=16, seqlen=4001)
+    sc, _, _ = make_problem(s.with_(batch=1, seqlen=8), seed=18, calib_tokens=128)
+    inp = make_conv_inputs(s.with_(batch=1, seqlen=8), seed=18)
+    dsc = gpu_lib.DeviceScales(host_scales(gpu_lib, sc))
+    Ct = inp["xBC"].shape[2]
+    assert 16 * 4001 * Ct > 96 << 20
+    g = torch.Generator(device="cuda").manual_seed(18)
+    x = torch.randint(-128, 128, (16, 4001, Ct), generator=g, device="cuda", dtype=torch.int8)
+    w, bias = torch.from_numpy(inp["weight"]).cuda(), torch.from_numpy(inp["bias"]).cuda()
+
+    def run(part):
+        b = part.shape[0]
+        out = [torch.full((b, 4001, h, p), 99, dtype=torch.int8, device="cuda")
+               for h, p in ((s.nheads, s.headdim), (s.ngroups, s.d_state), (s.ngroups, s.d_state))]
+        out.append(torch.full((b, 3, Ct), 99, dtype=torch.int8, device="cuda"))
+        gpu_lib.quamba_conv1d_q8(to_shape(gpu_lib, s.with_(batch=b)), dsc, part, w, bias, inp["in_w_scale"], *out[:3],
+                                 conv_state_out=out[3])
+        return out
+    whole, parts = run(x), [run(x[i:i + 4].contiguous()) for i in range(0, 16, 4)]
+    for i, t in enumerate(whole):
+        assert torch.equal(t, torch.cat([p[i] for p in parts]))
+
+
 @pytest.mark.parametrize("L", [2, 7, 16])
 def test_short_sequence_with_one_buffer_as_both_states(gpu_lib, L):
     s = W.CONFIGS["m2_130m"].with_(batch=3, seqlen=L)
