@@ -116,8 +116,8 @@ def test_one_token_kernel(gpu_lib, batch, H, P, N, m, n, state):
                                                (1, 45, 6, 16, 16, 3, 6),       # six ranges; segments of 4, a last one of 1
                                                (9, 291, 6, 64, 128, 2, 3),     # ... a last one of 3
                                                (15, 900, 6, 64, 16, 2, 3),     # segments of 8, the last of 4
-                                               (16, 3085, 14, 64, 64, 2, 2),   # segments of 16, the last of 13
-                                               (64, 3085, 4, 16, 16, 2, 2)])   # 16 channels per thread, the last of 13
+                                               (16, 3085, 14, 64, 64, 2, 2),   # segments of 32, the last of 13
+                                               (64, 3085, 4, 16, 16, 2, 2)])   # one channel block, the last of 13
 def test_segments_and_carried_state(gpu_lib, batch, L, H, P, N, m, n):
     """Short and the longest segments of the vector kernel, with ragged last ones, from a carried state.  (Longer ones
     than 8 tokens from 6144 waves of 8 up, 32 where 28 still make more than 6144.)"""
