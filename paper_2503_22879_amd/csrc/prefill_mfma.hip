@@ -1132,7 +1132,7 @@ hipError_t launch_scan_seg(const SsdArgs &a, hipStream_t stream)
 {
     constexpr int lds = GATED ? Lds<PT>::kBytesGated : Lds<PT>::kBytes;
     const int segs = a.nseg > 1 ? a.nseg : 1;  // one set of workgroups per segment
-    const dim3 grid((unsigned)(a.pair_count * (2 / PT) * segs));
+    const dim3 grid((unsigned)(a.s.batch * a.s.nheads * (2 / PT) * segs));
     const hipError_t e = allow_full_lds<prefill_mfma_kernel<PRECISE, PT, GATED, SEG>>();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((prefill_mfma_kernel<PRECISE, PT, GATED, SEG>), grid, dim3(kThreads), lds, stream, a);
@@ -1284,32 +1284,15 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
     a.seg_chunks = 0;
     a.seg_state = nullptr;
     a.seg_decay = nullptr;
-    a.pair_begin = 0;
-    a.pair_count = (int32_t)pairs;
     // Pacing of the two workgroups of a compute unit (see the kernel) pays when the whole launch is resident at once and
     // most compute units hold two workgroups that each walk many chunks; with more workgroups than that, the early finish
     // of the first arrivals is what lets the rest start, and pacing costs time (measured on 640 pairs).
     auto pace = [&](int segs, int chunks_per_wg) {
-        const int64_t wgs = (int64_t)a.pair_count * (plan.channel_split ? 2 : 1) * segs;
+        const int64_t wgs = pairs * (plan.channel_split ? 2 : 1) * segs;
         return (wgs > cus + cus / 2 && wgs <= 2 * (int64_t)cus && chunks_per_wg >= 8) ? cus : INT_MAX;
     };
     const int nchunks = (a.s.seqlen + kQ - 1) / kQ;
     if (plan.nseg < 2) {
-        // Workgroups of whole heads come in rounds of two per compute unit.  A second round that gives at most every other
-        // unit a workgroup goes to the wide kernel, in a launch of its own behind the (now paced) first: 640 pairs of 2048
-        // tokens 136 -> 132 us, 560 pairs 133 -> 125, 640 pairs of 1024 tokens 75 -> 70 (with the final state); with 4 chunks
-        // 39 -> 42, and behind two full rounds (1040 pairs) 110 -> 112, so both are left as one launch; so are second rounds of up
-        // to a workgroup per unit (768 pairs of 1024 tokens 81 -> 83 with whole heads on the wide kernel, 720 of 2048 157 -> 155).
-        const int64_t rest = pairs - 2 * (int64_t)cus;
-        if (rest > 0 && 2 * rest <= (int64_t)cus && nchunks >= 8 && !(a.s.flags & QUAMBA_FLAG_NO_CHANNEL_SPLIT)) {
-            a.pair_count = (int32_t)(pairs - rest);
-            a.pace_first = pace(1, nchunks);
-            const hipError_t e = launch(a);
-            if (e != hipSuccess) return e;
-            a.pair_begin = a.pair_count;
-            a.pair_count = (int32_t)rest;
-            return launch_prefill_wide(a, true, precise, stream);
-        }
         a.pace_first = pace(1, nchunks);
         return launch(a);
     }

@@ -98,7 +98,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
     float *s_silu = reinterpret_cast<float *>(smem + LY::kOffSilu);
 
     const int L = a.s.seqlen, H = a.s.nheads, G = a.s.ngroups;
-    const int wgs_per_seg = (2 / PT) * a.pair_count;
+    const int npairs = a.s.batch * H, wgs_per_seg = (2 / PT) * npairs;
     const int seg = SEG ? (int)blockIdx.x / wgs_per_seg : 0;
     const int nchunks = (L + kQ - 1) / kQ;
     const int c_begin = SEG ? seg * a.seg_chunks : 0;
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
     const int bid = SEG ? (int)blockIdx.x - seg * wgs_per_seg : (int)blockIdx.x;
     int pair = bid, half = 0;
     if (PT == 1) {
-        const int npairs = a.pair_count, full = npairs >> 3;
+        const int full = npairs >> 3;
         if (bid < 16 * full) {
             pair = (bid & 7) | ((bid >> 4) << 3);
             half = (bid >> 3) & 1;
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
         }
     }
     const int p_base = 32 * half;
-    const int bh = block_to_bh(a, a.pair_begin + pair);
+    const int bh = block_to_bh(a, pair);
     const int b = bh / H, h = bh - b * H, g = h / (H / G);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave16 = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -782,7 +782,7 @@ template <bool PRECISE, int PT, bool GATED, bool SEG>
 hipError_t launch(const SsdArgs &a, hipStream_t stream)
 {
     const int segs = a.nseg > 1 ? a.nseg : 1;
-    const dim3 grid((unsigned)((2 / PT) * a.pair_count * segs));
+    const dim3 grid((unsigned)((2 / PT) * a.s.batch * a.s.nheads * segs));
     const hipError_t e = allow_full_lds<prefill_wide_kernel<PRECISE, PT, GATED, SEG>>();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((prefill_wide_kernel<PRECISE, PT, GATED, SEG>), grid, dim3(kWideThreads), (WideLds<PT, GATED>::kBytes),

@@ -76,8 +76,6 @@ struct SsdArgs {
     int32_t pace_first;        // matrix-core prefill: first workgroup id of the second dispatch round when the two
                                // workgroups of a compute unit are to be kept at the same pace (see the kernel), else
                                // INT_MAX
-    int32_t pair_begin;        // matrix-core prefill: the (sequence, head) pairs of the launch, in the order of the
-    int32_t pair_count;        // workgroup map
 };
 
 // Plan of the matrix-core prefill for a shape on the current device: segments of the sequence split (1 = no split), chunks

@@ -186,8 +186,8 @@ def test_short_batches_on_workgroups_of_sixteen_waves(gpu_lib, b, H, G, L, tiny_
 
 
 def test_second_round_of_a_few_pairs(gpu_lib):
-    """640 (sequence, head) pairs of 9 chunks, the last one ragged: the 128 pairs behind the first 512 run in a launch of
-    their own.  Pairs of both, against the oracle."""
+    """640 (sequence, head) pairs of 9 chunks, the last one ragged: 512 workgroups are resident at once, 128 run in a second
+    round.  Pairs of both, against the oracle."""
     s = W.CONFIGS["m2_8b_b1"].with_(batch=5, seqlen=1030)
     sc, prob, _ = make_problem(s, 78, calib_tokens=256)
     pairs = [(0, 0), (1, 63), (3, 127), (4, 0), (4, 77), (4, 127)]
@@ -199,6 +199,21 @@ def test_second_round_of_a_few_pairs(gpu_lib):
         eh = np.abs(hg[i, h] - href[k]).max() / np.abs(href[k]).max()
         print(f"pair ({i}, {h}): y err {ey:.3e}, state err {eh:.3e}")
         assert ey <= Y_TOL and eh <= H_TOL
+
+
+@pytest.mark.parametrize("batch,H,G,L", [(2, 128, 8, 300), (5, 128, 8, 1030), (22, 24, 1, 1025)])
+def test_equal_sequences_of_one_call_have_equal_results(gpu_lib, batch, H, G, L):
+    """All (sequence, head) pairs of a call go through one kernel, also those of a second round of workgroups (640 and 528
+    pairs where 512 are resident): sequences with the same inputs have the same outputs and states, bit for bit."""
+    s = W.CONFIGS["m2_8b_b1"].with_(batch=1, seqlen=L, nheads=H, ngroups=G)
+    sc, prob, _ = make_problem(s, 79, calib_tokens=256)
+    rep = {k: np.repeat(v, batch, axis=0) if k in ("x", "B", "C", "dt") else v for k, v in prob.items()}
+    for want_state in (True, False):
+        yg, hg = run_prefill(gpu_lib, s.with_(batch=batch), sc, rep, want_state=want_state)
+        assert np.isfinite(yg).all()
+        assert all(np.array_equal(yg[i], yg[0]) for i in range(1, batch))
+        if want_state:
+            assert all(np.array_equal(hg[i], hg[0]) for i in range(1, batch))
 
 
 def _random_split_cases(n, seed):
