@@ -1213,14 +1213,18 @@ Split largest_split(const quamba_ssd_shape_t &s)
 // Which kernel walks the sequences, and in how many segments.  The wide kernel (workgroups of 16 waves, one to a compute
 // unit) walks a chunk of a channel half in 1.9 us and of a whole head in 2.8, a lone workgroup of 8 waves in 2.7, two of them on
 // a unit in 4.2 to 6.  A single chunk is no faster on it: 16 tokens of 128 heads 6.0 us, 8-wave kernel in channel halves 5.5; of
-// 192 heads 7.0, whole heads 6.5.  From two chunks on the cheapest of three is taken, by what they measured (microseconds, with
-// the final state; C chunks, 8 to 256 pairs, 2 to 64 chunks): the wide kernel unsplit, 4.5 + 1.92 C where every channel half
-// gets a unit of its own, else 5.5 + 2.83 C; channel halves in S segments that still get a unit each, 8 + 3.85 C / S with the
-// state pass; whole heads of the 8-wave kernel in S segments, two workgroups on a unit, 19 + 7.5 C / S.  (24 heads, 2048 tokens:
-// 34.7, 23.2 with 5 segments, and 24.9 for 8 segments of channel halves of the 8-wave kernel, which this replaces; 80 heads,
-// 1024 / 4096 tokens: unsplit 20.7 / 66.1, whole heads 27.5 / 63.7; 128 heads, 2048 tokens: unsplit 37.8, whole heads 48.4; 160
-// pairs, 2500 / 4096 tokens: unsplit 62.4 / 96.7, whole heads 68.6 / 96.1.)
-PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s)
+// 192 heads 7.0, whole heads 6.5; whole heads from half a pair per unit on (128 tokens of 129 heads 7.75 in halves, 8.06 whole,
+// and without the final state 6.67, 6.36; of 144 heads 8.27, 7.99).  From two chunks on the cheapest of three is taken, by what
+// they measured (microseconds, with the final state; C chunks, 33 to 256 pairs of 8 to 32 chunks; in brackets what gate or
+// step-size codes add): the wide kernel unsplit, 5 + 1.98 C (0.25 C) where every channel half gets a unit of its own, else
+// 7 + 2.85 C (0.25 C); channel halves in segments of S chunks that still get a unit each, 8.5 + 3.6 S (0.75 S) with the state
+// pass; whole heads of the 8-wave kernel in N segments of S chunks, 8 + 0.8 N + 5.9 S (1.5 S), 3 more where the state pass and 6
+// more where the outputs have more workgroups than units, and 1.4 S times the share of the units that two of these meet on.  Over
+// those shapes the choice is within 0.1 % of the best form on average, 2 % off at most with the final state (3 % with codes, 7 %
+// without the state).  (24 heads, 2048 tokens: unsplit 34.7, 4 segments 23.2; 80 heads, 1024 / 4096 tokens: unsplit 20.7 /
+// 66.1, whole heads 27.5 / 63.7; 128 heads, 2048 tokens: 37.8, 48.4; 129 pairs, 2048 / 4096 tokens: unsplit 52.3 / 97.9, whole
+// heads 55.4 / 91.2, with codes at 4096 106.0, 107.2; 160 pairs: 52.8 / 98.6, 62.0 / 97.1.)
+PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, bool codes)
 {
     const int64_t pairs = (int64_t)s.batch * s.nheads;
     const int cus = compute_units();
@@ -1237,9 +1241,16 @@ PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s)
         const int nchunks = (s.seqlen + kQ - 1) / kQ;
         Split own;  // segments of the wide kernel's channel halves
         if (plan.channel_split) own.cut(nchunks, (int)std::min<int64_t>(most.nseg, cus / (2 * pairs)));
-        const int64_t unsplit = plan.channel_split ? 450 + 192 * (int64_t)nchunks : 550 + 283 * (int64_t)nchunks;
-        const int64_t cut = own.nseg < 2 ? INT64_MAX : 800 + 385 * (int64_t)own.seg_chunks;
-        const int64_t whole = most.halves ? INT64_MAX : 1900 + 750 * (int64_t)most.seg_chunks;
+        const int64_t chunk = (plan.channel_split ? 198 : 285) + (codes ? 25 : 0);
+        const int64_t unsplit = (plan.channel_split ? 500 : 700) + chunk * nchunks;
+        const int64_t cut = own.nseg < 2 ? INT64_MAX : 850 + (codes ? 435 : 360) * (int64_t)own.seg_chunks;
+        const int64_t state_wgs = pairs * (most.nseg - 1), wgs = pairs * most.nseg;
+        // (the workgroups that come second to a unit are those of the last, shorter segment, as long as these are enough)
+        const int last = nchunks - (most.nseg - 1) * most.seg_chunks;
+        const int64_t step = (state_wgs > cus ? 300 : 0) +
+                             (wgs <= cus ? 0 : wgs - cus > pairs ? 600 : 600 * last / most.seg_chunks);
+        const int64_t whole = most.halves ? INT64_MAX : 800 + step + 80 * most.nseg + (codes ? 740 : 590) * (int64_t)most.seg_chunks +
+                                                            140 * most.seg_chunks * std::max<int64_t>(0, wgs - cus) / cus;
         if (unsplit <= std::min(cut, whole)) return plan;
         plan.wide = cut <= whole;
         if (plan.wide) split = own;
@@ -1262,7 +1273,8 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
 {
     SsdArgs a = a_in;
     const bool precise = a.state != nullptr || (a.s.flags & QUAMBA_FLAG_PRECISE_STATE);
-    PrefillPlan plan = prefill_mfma_plan(a.s);
+    const bool codes = a.z || a.dt_q;
+    PrefillPlan plan = prefill_mfma_plan(a.s, codes);
     // A final state that overlaps the initial state (allowed: an update in place) rules the split out: the last
     // segment's workgroups write the final state while those of the first segment may still have to read the initial one.
     const size_t state_bytes = sizeof(float) * (size_t)a.s.batch * a.s.nheads * kP * kN;
@@ -1273,7 +1285,7 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
     if (plan.nseg > 1 && (in_place || !workspace || reinterpret_cast<uintptr_t>(workspace) % 16 != 0)) {
         // also without a usable workspace (the entry point passes NULL when the caller's is missing or too small)
         a.s.flags |= QUAMBA_FLAG_NO_SEQ_SPLIT;
-        plan = prefill_mfma_plan(a.s);
+        plan = prefill_mfma_plan(a.s, codes);
     }
     auto launch = [&](const SsdArgs &args) {
         if (plan.wide) return launch_prefill_wide(args, plan.channel_split, precise, stream);

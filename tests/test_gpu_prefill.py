@@ -249,6 +249,32 @@ def test_sequence_split_on_drawn_shapes(gpu_lib, b, H, G, L, flags, seed, want_s
           f"drawn split b={b} H={H} G={G} L={L} flags={flags} state={want_state} init={use_init}")
 
 
+@pytest.mark.parametrize("H,L,split", [
+    (24, 2048, True),     # 4 segments of channel halves on 16 waves, 23 us; unsplit 35
+    (48, 4096, True),     # 8 segments of whole heads on 8 waves 51, unsplit 67
+    (60, 2048, False),    # unsplit 36.5, 8 segments of whole heads 38.5, 2 of channel halves 38.0
+    (128, 2048, False),   # unsplit 41, 4 segments of whole heads 47
+    (129, 2048, False),   # unsplit (whole heads on 16 waves) 52, 3 segments 55
+    (129, 4096, True),    # 3 segments 91, unsplit 98
+    (150, 3584, False),   # unsplit 87, 3 segments 88
+])
+def test_split_is_made_where_it_is_the_faster_form(gpu_lib, H, L, split):
+    """A split call leaves the states of its segments in the workspace, an unsplit one never touches it."""
+    import torch
+    q = gpu_lib
+    g = torch.Generator(device="cuda").manual_seed(H)
+    s = W.CONFIGS["m2_8b_b1"].with_(batch=1, seqlen=L, nheads=H, ngroups=1)
+    sc, _, _ = make_problem(s.with_(seqlen=8), 80, calib_tokens=128)
+    code = lambda *shape: torch.randint(-9, 10, shape, generator=g, device="cuda", dtype=torch.int8)
+    ws = torch.full((q.quamba_ssd_prefill_workspace_size(to_shape(q, s)),), 0x5A, dtype=torch.uint8, device="cuda")
+    assert ws.numel() > 0
+    q.quamba_ssd_prefill(to_shape(q, s), q.DeviceScales(host_scales(q, sc)), code(1, L, H, 64), code(1, L, 1, 128),
+                         code(1, L, 1, 128), torch.full((1, L, H), 0.01, device="cuda"), torch.full((H,), -1.0, device="cuda"), None,
+                         None, torch.empty((1, L, H, 64), dtype=torch.float16, device="cuda"),
+                         torch.empty((1, H, 64, 128), device="cuda"), ws)
+    assert bool((ws != 0x5A).any()) == split
+
+
 def test_state_updated_in_place_on_a_shape_that_would_be_split(gpu_lib):
     """final_state may be the init_state buffer.  With a sequence split the last segment would write it while the
     first still reads it, so such a call takes the unsplit launch: bit for bit the flagged launch with two buffers."""
