@@ -1244,13 +1244,13 @@ PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, bool codes)
         const int64_t chunk = (plan.channel_split ? 198 : 285) + (codes ? 25 : 0);
         const int64_t unsplit = (plan.channel_split ? 500 : 700) + chunk * nchunks;
         const int64_t cut = own.nseg < 2 ? INT64_MAX : 850 + (codes ? 435 : 360) * (int64_t)own.seg_chunks;
-        const int64_t state_wgs = pairs * (most.nseg - 1), wgs = pairs * most.nseg;
+        const int64_t state_wgs = pairs * (most.nseg - 1), wgs = pairs * most.nseg, len = most.seg_chunks;
         // (the workgroups that come second to a unit are those of the last, shorter segment, as long as these are enough)
-        const int last = nchunks - (most.nseg - 1) * most.seg_chunks;
+        const int64_t last = nchunks - (most.nseg - 1) * len;
         const int64_t step = (state_wgs > cus ? 300 : 0) +
-                             (wgs <= cus ? 0 : wgs - cus > pairs ? 600 : 600 * last / most.seg_chunks);
-        const int64_t whole = most.halves ? INT64_MAX : 800 + step + 80 * most.nseg + (codes ? 740 : 590) * (int64_t)most.seg_chunks +
-                                                            140 * most.seg_chunks * std::max<int64_t>(0, wgs - cus) / cus;
+                             (wgs <= cus ? 0 : wgs - cus > pairs ? 600 : 600 * last / len);
+        const int64_t whole = most.halves ? INT64_MAX : 800 + step + 80 * most.nseg + (codes ? 740 : 590) * len +
+                                                            140 * len * std::max<int64_t>(0, wgs - cus) / cus;
         if (unsplit <= std::min(cut, whole)) return plan;
         plan.wide = cut <= whole;
         if (plan.wide) split = own;
