@@ -285,10 +285,13 @@ __global__ __launch_bounds__(256) void hadamard_quantize_mixed_kernel(const uint
 // turns the codes of four rows at one position into those of one row at four positions, a dword to store.  A row need not
 // fill its last super-block: the missing part is never written, and what phase B reads of it stays in register groups of
 // its own that are not used.
-// Phase C is two thirds of the vector instructions.  With two positions per thread it ran on half the waves a row has now, two
-// of a row's three, at 5 waves per SIMD, and LDS (23 KB a row) admits no more rows: one position and 7 waves per SIMD take
-// 16384 rows of 5120 values from 74.7 to 69.7 us (3.6 TB/s), 3000 from 16.7 to 14.4, 256 from 4.4 to 3.6; of 1536 values from 21.3
-// to 18.2.  Not faster: two or four rows to a workgroup, which leaves no lane idle in phases A and B (62.8 against 59.0 us on
+// With two positions per thread phase C, which holds most of the vector instructions, ran on half the waves a row has now, two of a
+// row's three, at 5 waves per SIMD, and LDS (23 KB a row) admits no more rows: one position and 7 waves per SIMD take 16384 rows of
+// 5120 values from 69.9 to 66.4 us (3.8 TB/s), 3000 from 16.5 to 15.4, 256 from 4.2 to 3.4; 16384 of 1536 values from 20.5 to 20.1.
+// Plain stores: non-temporal ones take up to 13 % off the transform alone and put more on the reader of the codes (with an int8
+// product of 2560 columns behind, plain / non-temporal: 2867 rows of 5120 79.3 / 83.5 us, 13653 of 1536 95 / 105, 8192 of 2560
+// 97 / 108, 3413 of 6144 91 / 96; 1000 to 1700 rows of 5120 46.8 / 45.6, 63.2 / 61.6).
+// Not faster: two or four rows to a workgroup, which leaves no lane idle in phases A and B (62.8 against 59.0 us on
 // rows in the last-level cache); a loop over rows with the next one's loads in flight (74.4); the sums of 4 to 16 of the
 // rows as v_mfma_f32_4x4x1_16b_f32, bit for bit the same (70 to 79 against 65).
 template <int M, int LOGP>
@@ -360,7 +363,7 @@ __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *o
         const uint32_t w = codes_packed<4>(sc);
         const uint32_t w1 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w, 0xB1, 0xf, 0xf, true), w, sel1);
         const uint32_t w2 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w1, 0x4E, 0xf, 0xf, true), w1, sel2);
-        __builtin_nontemporal_store(w2, reinterpret_cast<u32_u *>(dst + (size_t)a * P));
+        *reinterpret_cast<u32_u *>(dst + (size_t)a * P) = w2;
     }
 }
 
