@@ -285,16 +285,19 @@ __global__ __launch_bounds__(256) void hadamard_quantize_mixed_kernel(const uint
 // turns the codes of four rows at one position into those of one row at four positions, a dword to store.  A row need not
 // fill its last super-block: the missing part is never written, and what phase B reads of it stays in register groups of
 // its own that are not used.
-// With two positions per thread phase C, which holds most of the vector instructions, ran on half the waves a row has now, two of a
-// row's three, at 5 waves per SIMD, and LDS (23 KB a row) admits no more rows: one position and 7 waves per SIMD take 16384 rows of
-// 5120 values from 69.9 to 66.4 us (3.8 TB/s), 3000 from 16.5 to 15.4, 256 from 4.2 to 3.4; 16384 of 1536 values from 20.5 to 20.1.
+// At order 5120 phase C issues 433 vector instructions in each of 4 waves, phases A and B 275 in 3.  With two positions per thread it
+// ran on half the waves, at 5 waves per SIMD, and LDS (23 KB a row) admits no more rows: one position and 7 waves per SIMD take
+// 16384 rows of 5120 values from 69.9 to 66.4 us (3.8 TB/s), 3000 from 16.5 to 15.4, 256 from 4.2 to 3.4; 16384 of 1536 values
+// from 20.5 to 20.1.
 // Plain stores: non-temporal ones take up to 13 % off the transform alone and put more on the reader of the codes (with an int8
 // product of 2560 columns behind, plain / non-temporal: 2867 rows of 5120 79.3 / 83.5 us, 13653 of 1536 95 / 105, 8192 of 2560
 // 97 / 108, 3413 of 6144 91 / 96; 1000 to 1700 rows of 5120 46.8 / 45.6, 63.2 / 61.6).
 // Not faster: two or four rows to a workgroup, which leaves no lane idle in phases A and B (62.8 against 59.0 us on
 // rows in the last-level cache); a loop over rows with the next one's loads in flight (74.4); the sums of 4 to 16 of the
 // rows as v_mfma_f32_4x4x1_16b_f32, bit for bit the same (70 to 79 against 65).
-template <int M, int LOGP>
+// POS = 2 is phase C with two positions per thread and 2-byte stores, a whole line of a row from every wave (launch_mixed says
+// where it is the better one).
+template <int M, int LOGP, int POS>
 __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *out, float inv_s)
 {
     constexpr int P = 1 << LOGP, N = M * P, T = N / 32, NSB = (N + 1023) / 1024;
@@ -342,46 +345,78 @@ __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *o
             if (1024 * t_hi + 32 * e < N) pb[32 * e] = v[e];  // uniform per wave half: whole groups of 32 lanes
     }
     __syncthreads();
-    // phase C: position t of every block, four rows of the M-point sums at a time
-    float x[M];
+    if constexpr (POS == 2) {
+        // phase C: positions 2 t and 2 t + 1 of every block
+        float t0[M], t1[M];
 #pragma unroll
-    for (int b = 0; b < M; ++b) x[b] = lds[b * P + t];
-    int8_t *dst = out + row + (size_t)(t & 3) * P + (t & ~3);
-    const uint32_t sel1 = t & 1 ? 0x03070105u : 0x06020400u, sel2 = t & 2 ? 0x03020706u : 0x05040100u;
-#pragma unroll
-    for (int a = 0; a < M; a += 4) {
-        float sc[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float acc = x[0] * paley_sign<M>(a + i, 0);
-#pragma unroll
-            for (int b = 1; b < M; ++b) acc = acc + x[b] * paley_sign<M>(a + i, b);
-            sc[i] = acc * inv_s;
+        for (int b = 0; b < M; ++b) {
+            t0[b] = lds[b * P + 2 * t];
+            t1[b] = lds[b * P + 2 * t + 1];
         }
-        // a lane's dword holds the codes of rows a .. a + 3; after the exchange inside the quad, of four positions of row
-        // a + t % 4
-        const uint32_t w = codes_packed<4>(sc);
-        const uint32_t w1 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w, 0xB1, 0xf, 0xf, true), w, sel1);
-        const uint32_t w2 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w1, 0x4E, 0xf, 0xf, true), w1, sel2);
-        *reinterpret_cast<u32_u *>(dst + (size_t)a * P) = w2;
+#pragma unroll
+        for (int a = 0; a < M; ++a) {
+            float a0 = t0[0] * paley_sign<M>(a, 0), a1 = t1[0] * paley_sign<M>(a, 0);
+#pragma unroll
+            for (int b = 1; b < M; ++b) {
+                a0 = a0 + t0[b] * paley_sign<M>(a, b);
+                a1 = a1 + t1[b] * paley_sign<M>(a, b);
+            }
+            const float sc[4] = {a0 * inv_s, a1 * inv_s, 0.0f, 0.0f};
+            *reinterpret_cast<uint16_t *>(out + row + (size_t)a * P + 2 * t) = (uint16_t)codes_packed<2>(sc);
+        }
+    } else {
+        // phase C: position t of every block, four rows of the M-point sums at a time
+        float x[M];
+#pragma unroll
+        for (int b = 0; b < M; ++b) x[b] = lds[b * P + t];
+        int8_t *dst = out + row + (size_t)(t & 3) * P + (t & ~3);
+        const uint32_t sel1 = t & 1 ? 0x03070105u : 0x06020400u, sel2 = t & 2 ? 0x03020706u : 0x05040100u;
+#pragma unroll
+        for (int a = 0; a < M; a += 4) {
+            float sc[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float acc = x[0] * paley_sign<M>(a + i, 0);
+#pragma unroll
+                for (int b = 1; b < M; ++b) acc = acc + x[b] * paley_sign<M>(a + i, b);
+                sc[i] = acc * inv_s;
+            }
+            // a lane's dword holds the codes of rows a .. a + 3; after the exchange inside the quad, of four positions of row
+            // a + t % 4
+            const uint32_t w = codes_packed<4>(sc);
+            const uint32_t w1 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w, 0xB1, 0xf, 0xf, true), w, sel1);
+            const uint32_t w2 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w1, 0x4E, 0xf, 0xf, true), w1, sel2);
+            *reinterpret_cast<u32_u *>(dst + (size_t)a * P) = w2;
+        }
     }
 }
 
-template <int M, int LOGP>
+template <int M, int LOGP, int POS>
 hipError_t launch_mixed_fast(const uint16_t *y, int64_t rows, float inv_s, int8_t *out, hipStream_t stream)
 {
     constexpr int P = 1 << LOGP, N = M * P, NSB = (N + 1023) / 1024;
-    constexpr int threads = P;
+    constexpr int threads = P / POS;
     static_assert(threads >= N / 32 && threads >= 32 * NSB, "every phase has its threads");
     constexpr int lds = NSB * 1152 * (int)sizeof(float);
     static_assert(threads <= 1024 && lds <= 160 * 1024, "launch shape");
     if (lds > 48 * 1024) {
-        const hipError_t e = allow_full_lds<hadamard_quantize_mixed_fast_kernel<M, LOGP>>();
+        const hipError_t e = allow_full_lds<hadamard_quantize_mixed_fast_kernel<M, LOGP, POS>>();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((hadamard_quantize_mixed_fast_kernel<M, LOGP>), dim3((unsigned)rows), dim3(threads), lds, stream, y,
-                       out, inv_s);
+    hipLaunchKernelGGL((hadamard_quantize_mixed_fast_kernel<M, LOGP, POS>), dim3((unsigned)rows), dim3(threads), lds, stream,
+                       y, out, inv_s);
     return hipGetLastError();
+}
+
+template <int M, int LOGP>
+hipError_t launch_mixed(const uint16_t *y, int64_t rows, float inv_s, int8_t *out, hipStream_t stream)
+{
+    // Orders 12 * 256 and 12 * 512 whose codes outgrow the caches of the dies: half lines cost more than the waves gain (order 6144,
+    // one / two positions: 426 rows 3.9 / 4.0 us, 1365 7.9 / 7.8, 3413 15.7 / 14.8, 14336 54.9 / 51.0; order 3072: 1365 rows 5.3 /
+    // 5.5, 4778 12.7 / 12.6, 28672 57.0 / 53.3).  Not so for the other orders (5120: 307 rows 4.0 / 5.0, 17203 64.9 / 68.3).
+    if constexpr (M == 12 && (LOGP == 8 || LOGP == 9))
+        if (rows * M * (1 << LOGP) > 6LL << 20) return launch_mixed_fast<M, LOGP, 2>(y, rows, inv_s, out, stream);
+    return launch_mixed_fast<M, LOGP, 1>(y, rows, inv_s, out, stream);
 }
 
 template <int LOGN>
@@ -434,13 +469,13 @@ hipError_t launch_hadamard_quantize(const uint16_t *y, int64_t rows, int n, floa
         const int m = (n % 12 == 0 && ((n / 12) & (n / 12 - 1)) == 0) ? 12 : 20;
         if (reinterpret_cast<uintptr_t>(y) % 16 == 0 && reinterpret_cast<uintptr_t>(out) % 2 == 0) {
             switch (n) {  // the register-blocked kernel for blocks of 128 .. 1024 values
-                case 12 * 128: return launch_mixed_fast<12, 7>(y, rows, inv_s, out, stream);
-                case 12 * 256: return launch_mixed_fast<12, 8>(y, rows, inv_s, out, stream);
-                case 12 * 512: return launch_mixed_fast<12, 9>(y, rows, inv_s, out, stream);
-                case 12 * 1024: return launch_mixed_fast<12, 10>(y, rows, inv_s, out, stream);
-                case 20 * 128: return launch_mixed_fast<20, 7>(y, rows, inv_s, out, stream);
-                case 20 * 256: return launch_mixed_fast<20, 8>(y, rows, inv_s, out, stream);
-                case 20 * 512: return launch_mixed_fast<20, 9>(y, rows, inv_s, out, stream);
+                case 12 * 128: return launch_mixed<12, 7>(y, rows, inv_s, out, stream);
+                case 12 * 256: return launch_mixed<12, 8>(y, rows, inv_s, out, stream);
+                case 12 * 512: return launch_mixed<12, 9>(y, rows, inv_s, out, stream);
+                case 12 * 1024: return launch_mixed<12, 10>(y, rows, inv_s, out, stream);
+                case 20 * 128: return launch_mixed<20, 7>(y, rows, inv_s, out, stream);
+                case 20 * 256: return launch_mixed<20, 8>(y, rows, inv_s, out, stream);
+                case 20 * 512: return launch_mixed<20, 9>(y, rows, inv_s, out, stream);
                 default: break;
             }
         }

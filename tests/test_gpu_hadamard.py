@@ -109,6 +109,28 @@ def test_mixed_orders_store_dwords_at_even_addresses(gpu_lib, n, off):
     assert (buf[:off] == 77).all() and (buf[off + rows * n:] == 77).all()
 
 
+@pytest.mark.parametrize("n,rows", [(3072, 2049), (6144, 1025), (1536, 4099), (5120, 1231)])
+@pytest.mark.parametrize("off", [0, 2])
+def test_large_mixed_calls_are_their_rows(gpu_lib, n, rows, off):
+    """More than 6 MiB of codes (orders 12 * 256 and 12 * 512 then take two positions per thread) against calls of a few of the
+    rows and, on some rows, the oracle; at an output address that is a multiple of 2 only as well."""
+    import torch
+    assert rows * n > 6 << 20
+    g = torch.Generator(device="cuda").manual_seed(n + off)
+    y = (torch.randn((rows, n), generator=g, device="cuda") * 0.1).to(torch.float16)
+    s_y = 3.0 * 0.1 * float(np.sqrt(n)) / 127.0
+    buf = torch.full((rows * n + 8,), 77, dtype=torch.int8, device="cuda")
+    out = buf[off:off + rows * n].view(rows, n)
+    gpu_lib.quamba_hadamard_quantize(y, s_y, out)
+    part = torch.full_like(y, 99, dtype=torch.int8)
+    for i in range(0, rows, 500):
+        gpu_lib.quamba_hadamard_quantize(y[i:i + 500], s_y, part[i:i + 500])
+    assert torch.equal(out, part)
+    pick = np.array([0, 1, rows // 2, rows - 1])
+    assert np.array_equal(out.cpu().numpy()[pick], oracle.hadamard_quantize(y.cpu().numpy()[pick], s_y))
+    assert (buf[:off] == 77).all() and (buf[off + rows * n:] == 77).all()
+
+
 def test_unaligned_pointers_and_leading_axes(gpu_lib):
     """A view that starts 2 bytes into an allocation takes the path without 16-byte loads; leading axes flatten."""
     import torch
