@@ -1300,7 +1300,7 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
     // most compute units hold two workgroups that each walk many chunks; with more workgroups than that, the early finish
     // of the first arrivals is what lets the rest start, and pacing costs time (measured on 640 pairs).
     auto pace = [&](int segs, int chunks_per_wg) {
-        const int64_t wgs = pairs * (plan.channel_split ? 2 : 1) * segs;
+        const int64_t wgs = pairs * segs;  // (whole heads: channel halves of this kernel walk a single chunk)
         return (wgs > cus + cus / 2 && wgs <= 2 * (int64_t)cus && chunks_per_wg >= 8) ? cus : INT_MAX;
     };
     const int nchunks = (a.s.seqlen + kQ - 1) / kQ;

@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
         _Float16 *s_wd = reinterpret_cast<_Float16 *>(set + LY::kOffWd);
         float *s_tot = reinterpret_cast<float *>(set + LY::kOffTot);
         float *s_gap = reinterpret_cast<float *>(set + LY::kOffGap);
-            if (a.dt_q) {
+        if (a.dt_q) {
             const float bias = a.dt_bias ? a.dt_bias[h] : 0.0f;
             const float v0 = a.dt_scale * (float)__builtin_bit_cast(int, d0) + bias;
             const float v1 = a.dt_scale * (float)__builtin_bit_cast(int, d1) + bias;
@@ -280,11 +280,11 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
                 }
             }
         };
-        // first block whose decay towards block tb is alive (tb if none is)
+        // first block in front of the nearest one whose decay towards block tb is alive (the nearest one if none is; between the
+        // two lies nothing that could decay)
         auto first_alive = [&](const float *s_cum, int tb, float r_tb) {
-            const float m0 = s_cum[kBlk - 1], m1 = s_cum[2 * kBlk - 1], m2 = s_cum[3 * kBlk - 1];
-            return __builtin_amdgcn_readfirstlane((0 < tb && r_tb - m0 < -dead) + (1 < tb && r_tb - m1 < -dead) +
-                                                  (2 < tb && r_tb - m2 < -dead));
+            const float m0 = s_cum[kBlk - 1], m1 = s_cum[2 * kBlk - 1];
+            return __builtin_amdgcn_readfirstlane((1 < tb && r_tb - m0 < -dead) + (2 < tb && r_tb - m1 < -dead));
         };
 
         if (role == 0) {
@@ -379,7 +379,6 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
             for (int c = c_begin; c < c_end; ++c) {
                 const int buf = (c - c_begin) & 1;
                 const unsigned char *set = smem + buf * LY::kSet;
-                const float *s_cum = reinterpret_cast<const float *>(set + LY::kOffCum);
                 const float *s_loc = reinterpret_cast<const float *>(set + LY::kOffLoc);
                 const float *s_tot = reinterpret_cast<const float *>(set + LY::kOffTot);
                 new_lane();
@@ -393,13 +392,8 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
                 if (tb * kBlk < min(kQ, L - c * kQ)) {
                     if (!LY::kOneC) load_c_rows(buf, tb, ct);
                     const float loc_t = s_loc[tl];
-                    int first = tb;
-                    if (mid < tb) {
-                        const float r_tb = s_cum[tb * kBlk - 1];
-                        first = __builtin_amdgcn_readfirstlane(r_tb - s_cum[mid * kBlk + kBlk - 1] < -dead) ? tb : mid;
-                    }
                     i32x16 gi;
-                    if (PT == 1) gi = score_tile(set, first, ct);
+                    if (PT == 1) gi = score_tile(set, mid, ct);
                     // the skip term: D x as a product with a diagonal matrix
                     if (PT == 2) {
                         diagonal(d16, skip);
@@ -417,9 +411,9 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
                     }
                     if (PT == 2) {
                         new_lane();
-                        gi = score_tile(set, first, ct);
+                        gi = score_tile(set, mid, ct);
                     }
-                    off_diagonal(set, tb, first, tb, true, loc_t, ct, gi, acc);
+                    off_diagonal(set, tb, mid, tb, true, loc_t, ct, gi, acc);
                     if (PT == 2) new_lane();
                     // diagonal block pair: per-element decay, causal mask on the narrowed values
                     const bool factored = __builtin_amdgcn_readfirstlane(-s_tot[tb] < 64.0f);
