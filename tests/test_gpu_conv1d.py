@@ -129,8 +129,8 @@ def test_segments_and_carried_state(gpu_lib, batch, L, H, P, N, m, n):
 
 @pytest.mark.parametrize("batch,L,H,P,N,m,n,bias", [(64, 2049, 6, 48, 16, 3, 7, True),   # ranges that end inside a thread
                                                     (16, 4096, 18, 64, 32, 1, 1, False)])  # a second, ragged block; no bias
-def test_sixteen_channels_per_thread(gpu_lib, batch, L, H, P, N, m, n, bias):
-    """Launches of at least 4096 waves of 32 tokens: more channel ranges than four, ends of ranges inside the channels of a
+def test_channel_ranges_and_blocks_of_large_calls(gpu_lib, batch, L, H, P, N, m, n, bias):
+    """Segments of 32 tokens: more channel ranges than four, ends of ranges inside the channels of a
     thread, no bias, and a channel block that fills no whole wave."""
     s = W.LayerShape("wide", batch, L, H, P, N, 1, 16, m, n)
     sc, _, _ = make_problem(s.with_(batch=1, seqlen=8), seed=16, calib_tokens=128)

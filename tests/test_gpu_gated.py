@@ -75,6 +75,12 @@ def test_prefill_gated_on_workgroups_of_sixteen_waves(gpu_lib, batch, L, use_z, 
     assert np.isfinite(yg).all() and np.isfinite(hg).all()
     assert np.abs(yg - yref).max() <= Y_TOL * np.abs(yref).max()
     assert np.abs(hg - href).max() <= H_TOL * np.abs(href).max()
+    # without the final state: the single-term state update
+    y.fill_(float("nan"))
+    q.quamba_ssd_prefill(to_shape(q, s), q.DeviceScales(host_scales(q, sc)), t["x"], t["B"], t["C"],
+                         None if use_dt else t["dt"], t["A"], t["D"], None, y, gate=_gate(q, g, use_z, use_dt))
+    yg = y.cpu().numpy().astype(np.float64)
+    assert np.isfinite(yg).all() and np.abs(yg - yref).max() <= Y_TOL * np.abs(yref).max()
 
 
 @pytest.mark.parametrize("flags", [0, NO_SPLIT])

@@ -19,7 +19,8 @@ CELL_TOL = 2e-3
 REL_FLOOR = 1e-4  # element-wise relative error is reported with |y_ref| floored at REL_FLOOR * max|y_ref| (information)
 
 
-def run_prefill(q, s, sc, prob, flags=0, init_state=None, want_state=True, chunk=None):
+def run_prefill(q, s, sc, prob, flags=0, init_state=None, want_state=True, chunk=None, used=None):
+    """used: a list that receives the number of bytes of the workspace up to the last one the call has written."""
     import torch
     dsc = q.DeviceScales(host_scales(q, sc))
     shape = to_shape(q, s, flags=flags, **({} if chunk is None else {"chunk": chunk}))
@@ -28,9 +29,12 @@ def run_prefill(q, s, sc, prob, flags=0, init_state=None, want_state=True, chunk
     fin = torch.full((s.batch, s.nheads, s.headdim, s.d_state), float("nan"), device="cuda") if want_state else None
     init = torch.from_numpy(init_state.astype(np.float32)).cuda() if init_state is not None else None
     ws_bytes = q.quamba_ssd_prefill_workspace_size(shape)
-    ws = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device="cuda")
+    ws = torch.full((max(ws_bytes, 1),), 0x5A, dtype=torch.uint8, device="cuda")
     q.quamba_ssd_prefill(shape, dsc, t["x"], t["B"], t["C"], t["dt"], t["A"], t["D"], init, y, fin, ws)
     torch.cuda.synchronize()
+    if used is not None:
+        written = ws.view(torch.int32) != 0x5A5A5A5A if ws_bytes else ws[:0]
+        used.append(4 * (int(written.nonzero().max()) + 1) if written.any() else 0)
     return y.cpu().numpy().astype(np.float64), (fin.cpu().numpy().astype(np.float64) if want_state else None)
 
 
@@ -123,11 +127,11 @@ NO_SEQ_SPLIT = 0x10
 
 
 @pytest.mark.parametrize("H,G,L,flags", [
-    (24, 1, 2048, 0),          # 130M shape: 8 segments of 2 chunks, two workgroups per head and segment
-    (24, 1, 2333, 0),          # 19 chunks: 7 segments of 3 chunks, the last one a single ragged chunk
-    (24, 1, 1100, NO_SPLIT),   # 9 chunks, whole heads: 3 segments of 3 chunks, the last chunk ragged
-    (128, 8, 4096, 0),         # 8B shape at batch 1: whole heads, 4 segments
-    (80, 1, 1500, 0),          # 12 chunks, 80 heads: 6 segments of whole heads, ragged last chunk
+    (24, 1, 2048, 0),          # 130M shape: 4 segments of 4 chunks, two workgroups of 16 waves per head and segment
+    (24, 1, 2333, 0),          # 19 chunks: 5 segments of 4 chunks, the last one of 3 with a ragged end
+    (24, 1, 1100, NO_SPLIT),   # 9 chunks, whole heads on 8 waves: 3 segments of 3 chunks, the last chunk ragged
+    (128, 8, 4096, 0),         # 8B shape at batch 1: room for 4 segments, run unsplit
+    (80, 1, 1500, 0),          # 12 chunks, 80 heads: room for 6 segments, run unsplit
 ])
 def test_sequence_split_against_the_oracle_and_the_unsplit_launch(gpu_lib, H, G, L, flags):
     """Short batches are cut along the sequence (a state pass, then one set of workgroups per segment).  With an
@@ -214,6 +218,54 @@ def test_equal_sequences_of_one_call_have_equal_results(gpu_lib, batch, H, G, L)
         assert all(np.array_equal(yg[i], yg[0]) for i in range(1, batch))
         if want_state:
             assert all(np.array_equal(hg[i], hg[0]) for i in range(1, batch))
+
+
+@pytest.mark.parametrize("H,G,L,segments", [
+    (48, 1, 2048, 8),     # 2 chunks each, 384 workgroups
+    (33, 3, 2500, 7),     # 3 chunks each, the last segment 2 with a ragged end; the state pass on fewer workgroups than units
+    (80, 1, 3970, 6),     # 6 chunks each, the last one 2; the workgroup map of 8 pairs
+    (130, 2, 4000, 3),    # 11 chunks each, the last one 10; more pairs than every other unit
+])
+def test_segments_of_whole_heads(gpu_lib, H, G, L, segments):
+    """Plans that cut the sequence into segments of whole heads on workgroups of 8 waves, two to a compute unit: with an initial
+    state, against the oracle and the same kernel's unsplit launch (the bars of the test above)."""
+    s = W.CONFIGS["m2_8b_b1"].with_(batch=1, seqlen=L, nheads=H, ngroups=G)
+    sc, prob, _ = make_problem(s, 34, calib_tokens=256)
+    h0 = W.draw_state(s, 34).astype(np.float32)
+    yref, href, _ = oracle.ref_prefill(sc, prob["x"], prob["B"], prob["C"], prob["dt"], prob["A"], prob["D"],
+                                       init_state=h0.astype(np.float64))
+    cells = oracle.cell_index_table(sc, s.nheads, s.headdim, s.ngroups)
+    for want_state in (True, False):
+        used = []
+        yg, hg = run_prefill(gpu_lib, s, sc, prob, 0, init_state=h0, want_state=want_state, used=used)
+        assert used == [4 * (segments - 1) * H * (64 * 128 + 1)], "bytes of workspace written"
+        check(yg, hg, yref, href if want_state else None, f"whole heads H={H} L={L} state={want_state}", cells=cells)
+        yu, hu = run_prefill(gpu_lib, s, sc, prob, NO_SPLIT | NO_SEQ_SPLIT, init_state=h0, want_state=want_state)
+        flipped = np.count_nonzero(yg != yu)
+        assert flipped <= 1e-2 * yg.size, f"{flipped} of {yg.size} outputs differ from the unsplit launch"
+        assert np.abs(yg - yu).max() <= 2.0 ** -9 * np.abs(yu).max()
+        if want_state:
+            assert np.abs(hg - hu).max() <= 2e-5 * np.abs(hu).max()
+
+
+def repeat_sequences(s, prob, pairs):
+    """The problem's sequences over and over, until there are at least `pairs` (sequence, head) pairs: (shape, problem)."""
+    k = -(-pairs // (s.batch * s.nheads))
+    rep = {n: np.concatenate([v] * k) if n in ("x", "B", "C", "dt") else v for n, v in prob.items()}
+    return s.with_(batch=k * s.batch), rep
+
+
+def check_every_launch_form(q, s, sc, prob, yref, href, what, state_tol=None):
+    """The problem as it is (a few pairs: channel halves on 16 waves) and with its sequences repeated to 130 pairs (whole heads on 16
+    waves), each with and without the final state, and on whole heads on 8 waves with it."""
+    for pairs, want_state, flags in ((1, True, 0), (1, False, 0), (1, True, NO_SPLIT), (130, True, 0), (130, False, 0)):
+        s1, p1 = repeat_sequences(s, prob, pairs)
+        k = s1.batch // s.batch
+        yg, hg = run_prefill(q, s1, sc, p1, flags=flags, want_state=want_state)
+        check(yg, hg, np.concatenate([yref] * k), np.concatenate([href] * k) if want_state else None,
+              f"{what}, {s1.batch * s1.nheads} pairs, state={want_state}, flags={flags}")
+        if want_state and state_tol:
+            assert np.abs(hg - np.concatenate([href] * k)).max() <= state_tol * np.abs(href).max()
 
 
 def _random_split_cases(n, seed):
@@ -598,11 +650,7 @@ def test_step_sizes_that_jump_inside_a_chunk(gpu_lib, seed):
     p1["dt"] = dt.astype(np.float32)
     p1["A"] = (-rng.uniform(0.5, 16.0, s.nheads)).astype(np.float32)
     yref, href, _ = oracle.ref_prefill(sc, p1["x"], p1["B"], p1["C"], p1["dt"], p1["A"], p1["D"])
-    for want_state, flags in ((True, 0), (True, NO_SPLIT), (False, 0)):
-        yg, hg = run_prefill(gpu_lib, s, sc, p1, flags=flags, want_state=want_state)
-        check(yg, hg, yref, href if want_state else None, f"jumping step sizes, seed={seed}, state={want_state}, flags={flags}")
-        if want_state:
-            assert np.abs(hg - href).max() <= 5e-5 * np.abs(href).max()
+    check_every_launch_form(gpu_lib, s, sc, p1, yref, href, f"jumping step sizes, seed={seed}", state_tol=5e-5)
 
 
 @pytest.mark.parametrize("mode", [0, 1, 2, 3, 4])
@@ -639,10 +687,9 @@ def test_drawn_step_size_patterns(gpu_lib, mode, seed):
         p1["A"][rng.random(H) < 0.3] = 0.0
     yref, href, _ = oracle.ref_prefill(sc, p1["x"], p1["B"], p1["C"], p1["dt"], p1["A"], p1["D"])
     assert np.isfinite(yref).all() and 0 < np.abs(yref).max() < 6e4
-    for want_state, flags in ((True, 0), (False, NO_SPLIT)):
-        yg, hg = run_prefill(gpu_lib, s, sc, p1, flags=flags, want_state=want_state)
-        check(yg, hg, yref, href if want_state else None,
-              f"step-size pattern {mode}, seed {seed}, L={L}, H={H}, state={want_state}, flags={flags}")
+    yg, _ = run_prefill(gpu_lib, s, sc, p1, flags=NO_SPLIT, want_state=False)
+    check(yg, None, yref, None, f"step-size pattern {mode}, seed {seed}, L={L}, H={H}, whole heads without the state")
+    check_every_launch_form(gpu_lib, s, sc, p1, yref, href, f"step-size pattern {mode}, seed {seed}, L={L}, H={H}")
 
 
 def test_step_sizes_up_to_the_documented_limit(gpu_lib):
@@ -664,13 +711,16 @@ def test_step_sizes_up_to_the_documented_limit(gpu_lib):
         yg, hg = run_prefill(gpu_lib, s, sc, p1, flags=flags, want_state=want_state)
         check(yg, hg, yref, href if want_state else None, f"dt up to 15.9, state={want_state}, flags={flags}",
               cells=oracle.cell_index_table(sc, s.nheads, s.headdim, s.ngroups))
+        if want_state:
+            check_every_launch_form(gpu_lib, s, sc, p1, yref, href, "dt up to 15.9")
 
 
 NO_DECAY_SKIP = 0x8
 
 
+@pytest.mark.parametrize("pairs,flags", [(48, 0), (48, NO_SPLIT), (144, 0)])   # halves on 16 waves, whole heads on 8 and on 16
 @pytest.mark.parametrize("want_state", [True, False])
-def test_blocks_with_dead_decay_are_left_out_without_a_trace(gpu_lib, want_state):
+def test_blocks_with_dead_decay_are_left_out_without_a_trace(gpu_lib, want_state, pairs, flags):
     """By default 32-token blocks whose decay factor is below 2^-32 are not computed.  Heads range from no decay to
     a decay that kills the carried state within a block (dt scaled per head), so every skip (carried state, far score
     blocks, state blocks) is taken on some heads and none on others; the result must meet the oracle like the full
@@ -686,12 +736,16 @@ def test_blocks_with_dead_decay_are_left_out_without_a_trace(gpu_lib, want_state
     init = (0.05 * np.random.default_rng(14).standard_normal((2, s.nheads, s.headdim, s.d_state))).astype(np.float32)
     yref, href, _ = oracle.ref_prefill(sc, p1["x"], p1["B"], p1["C"], p1["dt"], p1["A"], p1["D"],
                                        init_state=init.astype(np.float64), want_state=want_state)
-    y0, h0 = run_prefill(gpu_lib, s, sc, p1, flags=0, init_state=init, want_state=want_state)
-    y1, h1 = run_prefill(gpu_lib, s, sc, p1, flags=NO_DECAY_SKIP, init_state=init, want_state=want_state)
+    k = pairs // 48
+    s, p1 = repeat_sequences(s, p1, pairs)
+    init, yref, href = (None if v is None else np.concatenate([v] * k) for v in (init, yref, href))
+    y0, h0 = run_prefill(gpu_lib, s, sc, p1, flags=flags, init_state=init, want_state=want_state)
+    y1, h1 = run_prefill(gpu_lib, s, sc, p1, flags=flags | NO_DECAY_SKIP, init_state=init, want_state=want_state)
     check(y0, h0, yref, href if want_state else None, "decay skip on")
     check(y1, h1, yref, href if want_state else None, "decay skip off")
-    # what is left out is below 2^-32 of a term: it can flip the fp16 rounding of an output that sat on a tie, no more
-    assert (y0 != y1).sum() <= 16 and np.abs(y0 - y1).max() <= 2.0 ** -10 * np.abs(yref).max()
+    # what is left out is below 2^-32 of a term: it can flip the fp16 rounding of an output that sat on a tie, no more (and
+    # does so in every copy of a sequence)
+    assert (y0 != y1).sum() <= 16 * k and np.abs(y0 - y1).max() <= 2.0 ** -10 * np.abs(yref).max()
     if want_state:
         assert np.abs(h0 - h1).max() <= 1e-6 * np.abs(href).max()
 
