@@ -1214,17 +1214,24 @@ Split largest_split(const quamba_ssd_shape_t &s)
 // unit) walks a chunk of a channel half in 1.9 us and of a whole head in 2.8, a lone workgroup of 8 waves in 2.7, two of them on
 // a unit in 4.2 to 6.  A single chunk is no faster on it: 16 tokens of 128 heads 6.0 us, 8-wave kernel in channel halves 5.5; of
 // 192 heads 7.0, whole heads 6.5; whole heads from half a pair per unit on (128 tokens of 129 heads 7.75 in halves, 8.06 whole,
-// and without the final state 6.67, 6.36; of 144 heads 8.27, 7.99).  From two chunks on the cheapest of three is taken, by what
-// they measured (microseconds, with the final state; C chunks, 33 to 256 pairs of 8 to 32 chunks; in brackets what gate or
-// step-size codes add): the wide kernel unsplit, 5 + 1.98 C (0.25 C) where every channel half gets a unit of its own, else
-// 7 + 2.85 C (0.25 C); channel halves in segments of S chunks that still get a unit each, 8.5 + 3.6 S (0.75 S) with the state
-// pass; whole heads of the 8-wave kernel in N segments of S chunks, 8 + 0.8 N + 5.9 S (1.5 S), 3 more where the state pass and 6
-// more where the outputs have more workgroups than units, and 1.4 S times the share of the units that two of these meet on.  Over
-// those shapes the choice is within 0.1 % of the best form on average, 2 % off at most with the final state (3 % with codes, 7 %
-// without the state).  (24 heads, 2048 tokens: unsplit 34.7, 4 segments 23.2; 80 heads, 1024 / 4096 tokens: unsplit 20.7 /
-// 66.1, whole heads 27.5 / 63.7; 128 heads, 2048 tokens: 37.8, 48.4; 129 pairs, 2048 / 4096 tokens: unsplit 52.3 / 97.9, whole
-// heads 55.4 / 91.2, with codes at 4096 106.0, 107.2; 160 pairs: 52.8 / 98.6, 62.0 / 97.1.)
-PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, bool codes)
+// and without the final state 6.67, 6.36; of 144 heads 8.27, 7.99).  From two chunks on the cheapest of three forms is taken: the
+// wide kernel unsplit, its channel halves in segments that still get a unit each, and segments of whole heads on the 8-wave
+// kernel.  All were timed over 33 to 256 pairs of 8 to 48 chunks with and without the final state, gate codes and step-size codes.
+//
+// With at most half a pair per unit their costs are compared (microseconds; C chunks, S of a segment, N segments; in brackets what
+// the final state, gate codes and step-size codes add): unsplit 5.2 + 1.66 C (0.2, 0.1, 0.22 C), 0.15 C more as the units fill,
+// and where calls outgrow the last-level cache, between 85 and 120 MB read and written, 0.09 to 0.31 per MB; halves in segments
+// 8.9 + 3.01 S (0.52, 0.13, 0.59 S) with the state pass; whole heads 1.32 N + 5.44 S (1.23, 0.88, 0.69 S), 2.8 more where the state
+// pass and 6.9 more where the outputs have more workgroups than units, and 1.23 S times the share of the units that two of these
+// meet on.  Over these and 120 drawn shapes the choice is within 0.1 % of the best form on average, 5 % off at most (8 % at one).  (24 heads, 2048 tokens: unsplit 34.7, 4 segments 23.2; 80 heads, 1024 / 4096 tokens:
+// unsplit 20.7 / 66.1, whole heads 27.5 / 63.7; 128 heads, 2048 tokens: 37.8, 48.4; 112 heads, 6144 tokens without the state and
+// with step-size codes 114.6, 102.3.)
+//
+// Above, segments of whole heads are the faster form for up to two thirds of a pair per unit (3 segments) from a number of chunks
+// on: 26, and half a chunk per pair more (129 pairs, 24 / 28 / 32 chunks: unsplit 74.8 / 86.0 / 97.4, segments 73.8 / 81.2 / 91.5; 160
+// pairs, 32 / 48: 98.3 / 143.8, 100.9 / 143.4); 18 later with the final state and step-size codes (129 pairs, 40: 108, 108); 22 with both
+// codes, 26 with both and the state, whatever the pairs (160 pairs, 20 / 24 / 48: 75.4 / 97.6 / 188.5, 77.3 / 89.0 / 157.9).
+PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, const PrefillOperands &with)
 {
     const int64_t pairs = (int64_t)s.batch * s.nheads;
     const int cus = compute_units();
@@ -1237,23 +1244,33 @@ PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, bool codes)
     plan.seg_chunks = 0;
     if (most.nseg < 2) return plan;
     Split split = most;
-    if (plan.wide) {
-        const int nchunks = (s.seqlen + kQ - 1) / kQ;
+    const int nchunks = (s.seqlen + kQ - 1) / kQ;
+    const int fin = with.state, gate = with.gate, dtq = with.dt_codes;
+    if (plan.channel_split) {
         Split own;  // segments of the wide kernel's channel halves
-        if (plan.channel_split) own.cut(nchunks, (int)std::min<int64_t>(most.nseg, cus / (2 * pairs)));
-        const int64_t chunk = (plan.channel_split ? 198 : 285) + (codes ? 25 : 0);
-        const int64_t unsplit = (plan.channel_split ? 500 : 700) + chunk * nchunks;
-        const int64_t cut = own.nseg < 2 ? INT64_MAX : 850 + (codes ? 435 : 360) * (int64_t)own.seg_chunks;
+        own.cut(nchunks, (int)std::min<int64_t>(most.nseg, cus / (2 * pairs)));
+        // costs in hundredths of a microsecond
+        const int64_t mbytes = pairs * s.seqlen * (kP * (3 + gate) + (dtq ? 1 : 4)) / 1000000;
+        const int64_t chunk = 166 + 20 * fin + 10 * gate + 22 * dtq;
+        const int64_t unsplit = 520 + chunk * nchunks +
+                                (9 + 11 * gate + 17 * dtq - 6 * gate * dtq) * std::min<int64_t>(35, std::max<int64_t>(0, mbytes - 85)) +
+                                15 * nchunks * std::max<int64_t>(0, 10 * pairs - 4 * cus) / cus;
+        const int64_t cut = own.nseg < 2 ? INT64_MAX : 890 + (301 + 52 * fin + 13 * gate + 59 * dtq) * (int64_t)own.seg_chunks;
         const int64_t state_wgs = pairs * (most.nseg - 1), wgs = pairs * most.nseg, len = most.seg_chunks;
         // (the workgroups that come second to a unit are those of the last, shorter segment, as long as these are enough)
         const int64_t last = nchunks - (most.nseg - 1) * len;
-        const int64_t step = (state_wgs > cus ? 300 : 0) +
-                             (wgs <= cus ? 0 : wgs - cus > pairs ? 600 : 600 * last / len);
-        const int64_t whole = most.halves ? INT64_MAX : 800 + step + 80 * most.nseg + (codes ? 740 : 590) * len +
-                                                            140 * len * std::max<int64_t>(0, wgs - cus) / cus;
+        const int64_t step = (state_wgs > cus ? 283 : 0) +
+                             (wgs <= cus ? 0 : wgs - cus > pairs ? 687 : 687 * last / len);
+        const int64_t whole = most.halves ? INT64_MAX
+                                          : step + 132 * most.nseg + (544 + 123 * fin + 88 * gate + 69 * dtq) * len +
+                                                123 * len * std::max<int64_t>(0, wgs - cus) / cus;
         if (unsplit <= std::min(cut, whole)) return plan;
         plan.wide = cut <= whole;
         if (plan.wide) split = own;
+    } else if (plan.wide) {
+        const int64_t from = gate && dtq ? (fin ? 26 : 22) : (fin && dtq ? 44 : 26) + (pairs - cus / 2 - 1) / 2;
+        if (most.nseg < 3 || nchunks < from) return plan;
+        plan.wide = false;
     }
     plan.channel_split = plan.wide;
     plan.nseg = split.nseg;
@@ -1273,8 +1290,8 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
 {
     SsdArgs a = a_in;
     const bool precise = a.state != nullptr || (a.s.flags & QUAMBA_FLAG_PRECISE_STATE);
-    const bool codes = a.z || a.dt_q;
-    PrefillPlan plan = prefill_mfma_plan(a.s, codes);
+    const PrefillOperands with = {precise, a.z != nullptr, a.dt_q != nullptr};
+    PrefillPlan plan = prefill_mfma_plan(a.s, with);
     // A final state that overlaps the initial state (allowed: an update in place) rules the split out: the last
     // segment's workgroups write the final state while those of the first segment may still have to read the initial one.
     const size_t state_bytes = sizeof(float) * (size_t)a.s.batch * a.s.nheads * kP * kN;
@@ -1285,7 +1302,7 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
     if (plan.nseg > 1 && (in_place || !workspace || reinterpret_cast<uintptr_t>(workspace) % 16 != 0)) {
         // also without a usable workspace (the entry point passes NULL when the caller's is missing or too small)
         a.s.flags |= QUAMBA_FLAG_NO_SEQ_SPLIT;
-        plan = prefill_mfma_plan(a.s, codes);
+        plan = prefill_mfma_plan(a.s, with);
     }
     auto launch = [&](const SsdArgs &args) {
         if (plan.wide) return launch_prefill_wide(args, plan.channel_split, precise, stream);

@@ -78,16 +78,19 @@ struct SsdArgs {
                                // INT_MAX
 };
 
-// Plan of the matrix-core prefill for a shape on the current device, with or without side inputs as codes: segments of the
-// sequence split (1 = no split), chunks per segment, whether every head is cut into two workgroups of 32 channels each, and
-// whether the workgroups are the wide kernel's.
+// Plan of the matrix-core prefill for a shape on the current device: segments of the sequence split (1 = no split), chunks per
+// segment, whether every head is cut into two workgroups of 32 channels each, and whether the workgroups are the wide
+// kernel's.  It depends on what the call has besides x, B and C: the two-term state update, gate codes, step-size codes.
+struct PrefillOperands {
+    bool state, gate, dt_codes;
+};
 struct PrefillPlan {
     int nseg;
     int seg_chunks;
     bool channel_split;
     bool wide;
 };
-PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, bool codes);
+PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, const PrefillOperands &with);
 size_t prefill_mfma_workspace_bytes(const quamba_ssd_shape_t &s);
 
 // Step size of (token or sequence) index idx of head h: the caller's fp32 dt, or softplus(s_dt * code + bias[h])

@@ -221,9 +221,9 @@ def test_equal_sequences_of_one_call_have_equal_results(gpu_lib, batch, H, G, L)
 
 
 @pytest.mark.parametrize("H,G,L,segments", [
-    (48, 1, 2048, 8),     # 2 chunks each, 384 workgroups
+    (48, 1, 2250, 6),     # 3 chunks each, the last one ragged; 288 workgroups
     (33, 3, 2500, 7),     # 3 chunks each, the last segment 2 with a ragged end; the state pass on fewer workgroups than units
-    (80, 1, 3970, 6),     # 6 chunks each, the last one 2; the workgroup map of 8 pairs
+    (80, 1, 5000, 6),     # 7 chunks each, the last one 5 with a ragged end
     (130, 2, 4000, 3),    # 11 chunks each, the last one 10; more pairs than every other unit
 ])
 def test_segments_of_whole_heads(gpu_lib, H, G, L, segments):
@@ -301,16 +301,20 @@ def test_sequence_split_on_drawn_shapes(gpu_lib, b, H, G, L, flags, seed, want_s
           f"drawn split b={b} H={H} G={G} L={L} flags={flags} state={want_state} init={use_init}")
 
 
-@pytest.mark.parametrize("H,L,split", [
-    (24, 2048, True),     # 4 segments of channel halves on 16 waves, 23 us; unsplit 35
-    (48, 4096, True),     # 8 segments of whole heads on 8 waves 51, unsplit 67
-    (60, 2048, False),    # unsplit 36.5, 8 segments of whole heads 38.5, 2 of channel halves 38.0
-    (128, 2048, False),   # unsplit 41, 4 segments of whole heads 47
-    (129, 2048, False),   # unsplit (whole heads on 16 waves) 52, 3 segments 55
-    (129, 4096, True),    # 3 segments 91, unsplit 98
-    (150, 3584, False),   # unsplit 87, 3 segments 88
+@pytest.mark.parametrize("H,L,split,state,gate,dt_codes", [
+    (24, 2048, True, True, False, False),     # 4 segments of channel halves on 16 waves, 23 us; unsplit 35
+    (48, 4096, True, True, False, False),     # 8 segments of whole heads on 8 waves 51, unsplit 67
+    (60, 2048, False, True, False, False),    # unsplit 36.5, 8 segments of whole heads 38.5, 2 of channel halves 38.0
+    (128, 2048, False, True, False, False),   # unsplit 41, 4 segments of whole heads 47
+    (129, 2048, False, True, False, False),   # unsplit (whole heads on 16 waves) 52, 3 segments 55
+    (129, 4096, True, True, False, False),    # 3 segments 91, unsplit 98
+    (150, 3584, False, True, False, False),   # unsplit 87, 3 segments 88
+    (160, 3500, True, False, True, True),     # 3 segments 103, unsplit 113
+    (160, 3500, False, False, False, False),  # unsplit 74, 3 segments 79
+    (129, 4000, False, True, False, True),    # unsplit 101, 3 segments 102
+    (112, 6100, True, False, False, True),    # 4 segments of whole heads 102, unsplit 115
 ])
-def test_split_is_made_where_it_is_the_faster_form(gpu_lib, H, L, split):
+def test_split_is_made_where_it_is_the_faster_form(gpu_lib, H, L, split, state, gate, dt_codes):
     """A split call leaves the states of its segments in the workspace, an unsplit one never touches it."""
     import torch
     q = gpu_lib
@@ -320,10 +324,13 @@ def test_split_is_made_where_it_is_the_faster_form(gpu_lib, H, L, split):
     code = lambda *shape: torch.randint(-9, 10, shape, generator=g, device="cuda", dtype=torch.int8)
     ws = torch.full((q.quamba_ssd_prefill_workspace_size(to_shape(q, s)),), 0x5A, dtype=torch.uint8, device="cuda")
     assert ws.numel() > 0
+    g8 = q.Gate(z=code(1, L, H, 64) if gate else None, z_scale=0.1 if gate else 0.0, dt_q=code(1, L, H) if dt_codes else None,
+                dt_scale=0.1 if dt_codes else 0.0)
     q.quamba_ssd_prefill(to_shape(q, s), q.DeviceScales(host_scales(q, sc)), code(1, L, H, 64), code(1, L, 1, 128),
-                         code(1, L, 1, 128), torch.full((1, L, H), 0.01, device="cuda"), torch.full((H,), -1.0, device="cuda"), None,
+                         code(1, L, 1, 128), None if dt_codes else torch.full((1, L, H), 0.01, device="cuda"),
+                         torch.full((H,), -1.0, device="cuda"), None,
                          None, torch.empty((1, L, H, 64), dtype=torch.float16, device="cuda"),
-                         torch.empty((1, H, 64, 128), device="cuda"), ws)
+                         torch.empty((1, H, 64, 128), device="cuda") if state else None, ws, gate=g8 if gate or dt_codes else None)
     assert bool((ws != 0x5A).any()) == split
 
 

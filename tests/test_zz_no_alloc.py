@@ -39,7 +39,7 @@ def _both(q, s, seed):
 
 def test_noalloc_entry_point_matches_the_workspace_entry_point(gpu_lib):
     q = gpu_lib
-    big = W.CONFIGS["m2_2p7b"].with_(batch=1, seqlen=4096)   # 80 heads: 6 segments, 13.1 MB of scratch
+    big = W.CONFIGS["m2_2p7b"].with_(batch=1, seqlen=5120)   # 80 heads: 6 segments, 13.1 MB of scratch
     unsplit = W.CONFIGS["m2_8b_b1"]                          # 128 heads x 4096 tokens: room for 4 segments, run unsplit
     small = W.CONFIGS["m2_130m"]                             # 24 heads x 2048 tokens: 4 segments
     none = W.CONFIGS["m2_130m"].with_(seqlen=300)            # too short for a split: no scratch
