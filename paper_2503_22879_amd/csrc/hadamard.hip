@@ -411,11 +411,17 @@ hipError_t launch_mixed_fast(const uint16_t *y, int64_t rows, float inv_s, int8_
 template <int M, int LOGP>
 hipError_t launch_mixed(const uint16_t *y, int64_t rows, float inv_s, int8_t *out, hipStream_t stream)
 {
-    // Orders 12 * 256 and 12 * 512 whose codes outgrow the caches of the dies: half lines cost more than the waves gain (order 6144,
-    // one / two positions: 426 rows 3.9 / 4.0 us, 1365 7.9 / 7.8, 3413 15.7 / 14.8, 14336 54.9 / 51.0; order 3072: 1365 rows 5.3 /
-    // 5.5, 4778 12.7 / 12.6, 28672 57.0 / 53.3).  Not so for the other orders (5120: 307 rows 4.0 / 5.0, 17203 64.9 / 68.3).
+    // Two positions on large calls of orders 12 * 128 .. 12 * 512 (order 12 * 1024 gains from one position at every size, 20 * 2^k has
+    // no threads to spare with two).  12 * 256 and 12 * 512 whose codes outgrow the caches of the dies: half lines cost more than
+    // the waves gain (order 6144, one / two positions: 498 rows 3.97 / 4.12 us, 822 5.94 / 5.92, 909 6.49 / 6.16, 14336 54.9 / 51.0;
+    // order 3072: 1488 rows 5.65 / 5.84, 1645 6.01 / 5.97, 1818 6.48 / 6.31, 28672 57.0 / 53.3).  12 * 128 while the rows are more
+    // than 9 of the 16 workgroups that a unit holds with one position (2204 rows 4.41 / 4.66, 2436 4.96 / 4.85, 3637 6.53 / 6.09,
+    // 4020 6.88 / 6.56, 4443 7.59 / 7.71).
     if constexpr (M == 12 && (LOGP == 8 || LOGP == 9))
-        if (rows * M * (1 << LOGP) > 6LL << 20) return launch_mixed_fast<M, LOGP, 2>(y, rows, inv_s, out, stream);
+        if (rows * M * (1 << LOGP) > 5LL << 20) return launch_mixed_fast<M, LOGP, 2>(y, rows, inv_s, out, stream);
+    if constexpr (M == 12 && LOGP == 7)
+        if (rows > 9 * compute_units() && rows <= 16 * compute_units())
+            return launch_mixed_fast<M, LOGP, 2>(y, rows, inv_s, out, stream);
     return launch_mixed_fast<M, LOGP, 1>(y, rows, inv_s, out, stream);
 }
 
