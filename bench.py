@@ -91,9 +91,9 @@ ALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12   # 39.3: fp32 vector issue slots pe
 #   its exponential (4), (dt x) * B (1; dt x is shared by the states), h = a h + u (1 fused), y += C h (1 fused).
 MAMBA1_MIN_SLOTS = 8.0
 #   W8A8 convolution + SiLU + Eq. 1, per output element: the 4-tap window (1 byte permute) and its exact integer dot
-#   product (1), to float (1), times the scale plus bias (1 fused), exp (4), 1 + e (1), reciprocal (4), v * sigmoid (1),
-#   times 1 / s_out (1), clamp (1), round and pack (1).
-CONV_MIN_SLOTS = 17.0
+#   product (1), to float (1), times the scale plus bias as value over s_out and as argument of the exponential (2 fused),
+#   exp (4), 1 + e (1), reciprocal (4), value * sigmoid (1 fused), round, clamp and pack (1).
+CONV_MIN_SLOTS = 16.0
 # Executed vector instructions per element by the counters (rocprofv3 SQ_INSTS_VALU x 64 / elements), for information:
 MAMBA1_EXECUTED_PER_ELEMENT = 8.3   # of which 1.06 quarter-rate exponentials
 CONV_EXECUTED_PER_ELEMENT = 18.2    # 15.4 in the main loop (two quarter-rate), set-up and the exact-sequence reruns
@@ -674,9 +674,9 @@ def main() -> int:
                          "slots_per_element": CONV_MIN_SLOTS, "executed_per_element": CONV_EXECUTED_PER_ELEMENT,
                          **traffic_fields(s.name + "_conv1d"),
                          "note": "priced on what the method needs per output element, %.0f vector issue slots (window "
-                                 "permute, 4-tap integer dot product, to float, scale + bias, exponential and "
-                                 "reciprocal at quarter rate, 1 + e, times sigmoid, times 1/s_out, clamp, round and "
-                                 "pack), against one slot per lane and cycle; the kernel executes %.1f vector "
+                                 "permute, 4-tap integer dot product, to float, scale + bias over s_out and as "
+                                 "argument, exponential and reciprocal at quarter rate, 1 + e, times sigmoid, one "
+                                 "conversion that rounds, clamps and packs), against one slot per lane and cycle; the kernel executes %.1f vector "
                                  "instructions per element by the counters (executed_per_element), so added "
                                  "instructions lower frac" % (CONV_MIN_SLOTS, CONV_EXECUTED_PER_ELEMENT)},
             "roofline_hbm": {"kernel": "conv1d_q8_vec_kernel", "bound": "hbm", "achieved": cgbs,
