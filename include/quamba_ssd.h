@@ -50,10 +50,11 @@ typedef enum quamba_status {
 #define QUAMBA_FLAG_PRECISE_STATE 0x2u  /* prefill: compute chunk states with a two-term fp16 product so       
                                            that final_state meets 1e-4 of its max; implied when final_state
                                            is requested, settable to get the same arithmetic without it       */
-#define QUAMBA_FLAG_NO_CHANNEL_SPLIT 0x4u /* prefill: keep one workgroup per (sequence, head) even when the batch
-                                           has fewer heads than the device has compute units (by default such
-                                           batches give every head two workgroups of 32 channels each); the
-                                           results of the two launch shapes agree to rounding                  */
+#define QUAMBA_FLAG_NO_CHANNEL_SPLIT 0x4u /* prefill: one workgroup of 8 waves per (sequence, head), or per head and
+                                           segment, whatever the batch (by default batches of at most a (sequence,
+                                           head) pair per compute unit run on a kernel of 16 waves, and with at most
+                                           half a pair per unit every head gets two workgroups of 32 channels each);
+                                           the results of the launch shapes agree to rounding                  */
 
 #define QUAMBA_FLAG_NO_DECAY_SKIP 0x8u  /* prefill: also compute the products whose decay factor exp(sum of dt*A)
                                            over the tokens between their operands is below 2^-32 (by default the
@@ -94,13 +95,14 @@ typedef struct quamba_ssd_scales_t {
 } quamba_ssd_scales_t;
 
 /*
- * Bytes of device workspace with which quamba_ssd_prefill runs this shape fastest on the current device (may be 0).
- * Non-zero only for batches short enough for the sequence split of the matrix-core kernel
+ * Bytes of device workspace with which quamba_ssd_prefill takes its fastest launch for this shape on the current device
+ * (may be 0).  Non-zero only for batches short enough for the sequence split of the matrix-core kernel
  * (QUAMBA_FLAG_NO_SEQ_SPLIT): room for the states at the segment boundaries, (segments - 1) * batch * nheads *
- * (headdim * d_state + 1) floats for the most segments the shape may be cut into.  A call with a NULL, smaller or not 16-byte aligned workspace is not an error: it
- * takes the unsplit launch (same results to rounding, slower on such batches).  The workspace is scratch: written
- * and read by the call's own launches, contents undefined afterwards; calls that share one workspace must not
- * overlap.  Returns 0 for an invalid shape; quamba_ssd_prefill reports the error.
+ * (headdim * d_state + 1) floats for the most segments the shape may be cut into.  A call may make fewer segments, or none
+ * where the unsplit launch is the faster one, and then leaves the rest untouched.  A call with a NULL, smaller or not 16-byte
+ * aligned workspace is not an error: it takes the unsplit launch (same results to rounding, slower on such batches).  The
+ * workspace is scratch: written and read by the call's own launches, contents undefined afterwards; calls that share one
+ * workspace must not overlap.  Returns 0 for an invalid shape; quamba_ssd_prefill reports the error.
  */
 size_t quamba_ssd_prefill_workspace_size(const quamba_ssd_shape_t *shape);
 

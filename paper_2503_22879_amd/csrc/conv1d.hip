@@ -4,7 +4,7 @@
 // (Section 4.1) -- written straight into the scan's three input tensors.  The channel order is the sorted order
 // the offline reordering gives the convolution's weights (Section 4.2), so nothing is permuted here.
 //
-// A thread owns 4 consecutive channels (one 4-byte load per token) and walks a segment of 4, 8 or 16 tokens.  Per channel it
+// A thread owns 4 consecutive channels (one 4-byte load per token) and walks a segment of 4 to 32 tokens.  Per channel it
 // keeps the last four input codes in one dword (byte k = tap k, the newest in byte 3): a byte permute shifts the new
 // code in, one 4-way int8 dot product with the channel's packed taps gives the exact integer sum.  The code is an
 // integer decided by fp32 arithmetic; the decision sequence (stated in the header) is evaluated with every operation
@@ -44,7 +44,7 @@ __device__ __forceinline__ float activation_over_scale(int acc, float s_cw, floa
 // The same value through the hardware's approximate base-2 exponential and reciprocal (1 unit in the last place
 // each): v / (1 + 2^(-v log2 e)) * inv.  It shares v and the rounded exponent argument with the exact sequence above
 // (whose e is 2^-|t| for the same t), so the two differ only by the roundings after that point: by less than
-// 1e-6 of the value (the exact sequence's polynomial, 3e-7 at most, and four operations; here two units in the last place,
+// 1e-6 of the value (the exact sequence's polynomial, 3 * 2^-24 at most, and four operations; here two units in the last place,
 // a sum and two products; the value's sensitivity to e is below 1).  Deeply negative v gives 2^t = inf and the result -0.
 __device__ __forceinline__ float activation_over_scale_fast(int acc, float s_cw, float bias, float inv)
 {
@@ -185,8 +185,8 @@ __device__ __forceinline__ uint32_t codes_of_windows(const uint32_t (&win)[4], c
 //     7 e |R| + e inv (1.4 + 3 |bias|) + 2^-17
 // (constants, v' and t: 3 e |V| + 4 e |bias|; hardware exponential and reciprocal, 2 e each; the sum's rounding below 256).
 // 16 e = 9.6e-7 and |R| <= |v'|, so a distance of u from its integer of less than 0.5 - 1.3e-6 |v'| - th, th = inv (2.5e-7 +
-// 3e-7 |bias|) + 1e-5, decides the exact sequence's code.  Other codes are redone with it (NaN compares as such), and all
-// of them where a constant is so large that a finite sum could leave the range of fp32.
+// 3e-7 |bias|) + 1e-5, decides the exact sequence's code.  Other codes are redone with it, and all of them where a constant is
+// not finite or so large that a sum could leave the range of fp32 (the only ways to a NaN, which the maximum of four would hide).
 struct FastChannels4 {
     f32x4 a, b, t;
     float limit;  // 0.5 less the largest th of the four; negative: always the exact sequence
@@ -441,9 +441,11 @@ hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream)
         const dim3 grid((unsigned)((Ct / 4 + 63) / 64), (unsigned)((a.s.seqlen + (int64_t)v.seg - 1) / v.seg),
                         (unsigned)a.s.batch);
         // Plain stores where the caches can hold the codes until the scan reads them.  Convolution and scan together,
-        // non-temporal / plain: 1531 tokens of 10240 channels (16 MB) with gate and step-size codes 48.4 / 46.1 us, 2048 of 1792
-        // 30.8 / 29.9, 1000 of 5376 29.4 / 28.7, 8 x 2048 of 5376 (88 MB) 188.3 / 187.2, 2 x 4096 of 10240 (84 MB) 157.3 / 157.6,
-        // 4 x 4096 of 10240 (168 MB) 272.9 / 276.5, 16 x 2048 of 5376 (176 MB) 334.3 / 339.9.
+        // non-temporal / plain, scan without side inputs: 3.5 MiB (2048 tokens of 1792 channels) 31.2 / 30.2 us, 5 MiB 29.1 / 28.7, 10
+        // to 40 MiB within 1 %, 52 MiB 121.4 / 115.9, 80 (2 x 4096 of 10240) 156.2 / 150.6, 84 (8 x 2048 of 5376) 181.7 / 181.0, 94
+        // 204.1 / 198.4, 109 219.4 / 221.8, 160 270 / 270 to 276.  With gate and step-size codes, which take their share of the caches:
+        // 5 MiB 32.4 / 30.5, 10 56.1 / 51.8, 20 60.6 / 58.1, but from 28 MiB on 1 to 2.4 % longer (84: 208.4 / 213.6).  The
+        // convolution does not know what the scan will read; the line is the one without.
         if ((int64_t)a.s.batch * a.s.seqlen * Ct <= 96LL << 20)
             hipLaunchKernelGGL(conv1d_q8_vec_kernel<true>, grid, dim3(64), 0, stream, v);
         else

@@ -285,7 +285,8 @@ __global__ __launch_bounds__(256) void hadamard_quantize_mixed_kernel(const uint
 // turns the codes of four rows at one position into those of one row at four positions, a dword to store.  A row need not
 // fill its last super-block: the missing part is never written, and what phase B reads of it stays in register groups of
 // its own that are not used.
-// At order 5120 phase C issues 433 vector instructions in each of 4 waves, phases A and B 275 in 3.  With two positions per thread it
+// Bound by vector issue: at order 5120 phase C issues 433 vector instructions in each of 4 waves, phases A and B 275 in 3, and the
+// vector ALUs are busy 99 % of the time at 4 cycles each (profiles/short_prompts_and_mixed_hadamard.txt).  With two positions per thread it
 // ran on half the waves, at 5 waves per SIMD, and LDS (23 KB a row) admits no more rows: one position and 7 waves per SIMD take
 // 16384 rows of 5120 values from 69.9 to 66.4 us (3.8 TB/s), 3000 from 16.5 to 15.4, 256 from 4.2 to 3.4; 16384 of 1536 values
 // from 20.5 to 20.1.

@@ -33,7 +33,6 @@ constexpr float kDead = 32.0f;
 // 2^x by the hardware instruction (prefix sums are carried in log2 units, so no multiply by log2 e is needed).
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// LDS row of token s of the chunk: bits 2 and 3 swapped (see file comment).
 // Lane index recomputed where it is called: the mask passes through an empty asm statement, so the compiler can neither
 // hoist the result out of a loop nor keep it in a register across one.
 __device__ __forceinline__ int fresh_lane() {
@@ -41,6 +40,7 @@ __device__ __forceinline__ int fresh_lane() {
     asm volatile("" : "+s"(m));
     return (int)__builtin_amdgcn_mbcnt_hi(m, __builtin_amdgcn_mbcnt_lo(m, 0u));
 }
+// LDS row of token s of the chunk: bits 2 and 3 swapped (prefill_mfma.hip says why).
 __device__ __forceinline__ int tok_pos(int s) { return (s & ~12) | ((s & 4) << 1) | ((s & 8) >> 1); }
 
 // Transposing LDS loads.  Inside each group of 16 lanes, result byte j of lane i comes from the 8 bytes addressed by

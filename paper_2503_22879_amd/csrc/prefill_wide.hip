@@ -20,10 +20,12 @@
 //
 // Measured with the final state (the best of the 8-wave kernel's launches, whole, cut into segments or in channel halves /
 // this kernel): 128 heads, one sequence of 1531 tokens with gate and step-size codes 49.4 / 34.9 us, 2500 tokens 56 / 46; 120
-// pairs, 1000 tokens 32.2 / 22.0; 80 heads, 1000 tokens 27.4 / 20.8; 24 heads, 2048 tokens (5 segments) 24.3 / 22.8, 500
+// pairs, 1000 tokens 32.2 / 22.0; 80 heads, 1000 tokens 27.4 / 20.8; 24 heads, 2048 tokens (4 segments) 24.3 / 22.8, 500
 // tokens 14.3 / 11.9; two sequences of 128 heads, 1024 tokens 36.1 / 30.6, 4096 tokens 128 / 107, 1531 tokens with gate and codes
-// 64.4 / 47.5.  A chunk of 32 channels takes 4000 cycles, 4600 with the two-term state update; the roles' waves wait 500 to 1500 of
-// them at the barrier, the vector ALUs issue 3000.  A chunk of 64 channels takes 5600 (6200): its state waves are busy for 5100 of
+// 64.4 / 47.5.  By cycle counters read in the kernel (a build of its own) a chunk of 32 channels takes 4000 cycles, 4600 with the
+// two-term state update; the roles' waves wait 500 to 1500 of them at the barrier, the vector ALUs issue 3000 (the hardware's
+// counters, profiles/short_prompts_and_mixed_hadamard.txt, have 840 instructions per SIMD and chunk, the launch's set-up
+// included, 960 with gate and step-size codes).  A chunk of 64 channels takes 5600 (6200): its state waves are busy for 5100 of
 // them, the others for 3600 to 4600, and LDS for 3000.  Wave priorities for the state waves cost 1 to 3 %, their operands requested
 // two or three steps ahead change nothing.  Two rounds of this kernel are slower than two workgroups of 8 waves side by side
 // (512 pairs, 4096 tokens: 193 / 169 us; 384 pairs, 2048 tokens 105 / 89).
