@@ -1221,9 +1221,9 @@ Split largest_split(const quamba_ssd_shape_t &s)
 // With at most half a pair per unit their costs are compared (microseconds; C chunks, S of a segment, N segments; in brackets what
 // the final state, gate codes and step-size codes add): unsplit 5.2 + 1.66 C (0.2, 0.1, 0.22 C), 0.15 C more as the units fill,
 // and where calls outgrow the last-level cache, between 85 and 120 MB read and written, 0.09 to 0.31 per MB; halves in segments
-// 8.9 + 3.01 S (0.52, 0.13, 0.59 S) with the state pass; whole heads 1.32 N + 5.44 S (1.23, 0.88, 0.69 S), 2.8 more where the state
-// pass and 6.9 more where the outputs have more workgroups than units, and 1.23 S times the share of the units that two of these
-// meet on.  Over these and 120 drawn shapes the choice is within 0.1 % of the best form on average, 5 % off at most (8 % at one).  (24 heads, 2048 tokens: unsplit 34.7, 4 segments 23.2; 80 heads, 1024 / 4096 tokens:
+// 8.9 + 3.01 S (0.52, 0.13, 0.59 S) with the state pass; whole heads 3.9 + 1.2 N + 5.2 S (1.21, 0.88, 0.7 S), 3 more where the state
+// pass and 4 more where the outputs have more workgroups than units, and 1.43 S times the share of the units that two of these
+// meet on.  Over these and 120 drawn shapes the choice is within 0.1 % of the best form on average, 4 % off at most.  (24 heads, 2048 tokens: unsplit 34.7, 4 segments 23.2; 80 heads, 1024 / 4096 tokens:
 // unsplit 20.7 / 66.1, whole heads 27.5 / 63.7; 128 heads, 2048 tokens: 37.8, 48.4; 112 heads, 6144 tokens without the state and
 // with step-size codes 114.6, 102.3.)
 //
@@ -1259,11 +1259,11 @@ PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, const PrefillOperands
         const int64_t state_wgs = pairs * (most.nseg - 1), wgs = pairs * most.nseg, len = most.seg_chunks;
         // (the workgroups that come second to a unit are those of the last, shorter segment, as long as these are enough)
         const int64_t last = nchunks - (most.nseg - 1) * len;
-        const int64_t step = (state_wgs > cus ? 283 : 0) +
-                             (wgs <= cus ? 0 : wgs - cus > pairs ? 687 : 687 * last / len);
+        const int64_t step = (state_wgs > cus ? 300 : 0) +
+                             (wgs <= cus ? 0 : wgs - cus > pairs ? 404 : 404 * last / len);
         const int64_t whole = most.halves ? INT64_MAX
-                                          : step + 132 * most.nseg + (544 + 123 * fin + 88 * gate + 69 * dtq) * len +
-                                                123 * len * std::max<int64_t>(0, wgs - cus) / cus;
+                                          : 391 + step + 120 * most.nseg + (520 + 121 * fin + 88 * gate + 70 * dtq) * len +
+                                                143 * len * std::max<int64_t>(0, wgs - cus) / cus;
         if (unsplit <= std::min(cut, whole)) return plan;
         plan.wide = cut <= whole;
         if (plan.wide) split = own;

@@ -305,6 +305,7 @@ def test_sequence_split_on_drawn_shapes(gpu_lib, b, H, G, L, flags, seed, want_s
     (24, 2048, True, True, False, False),     # 4 segments of channel halves on 16 waves, 23 us; unsplit 35
     (48, 4096, True, True, False, False),     # 8 segments of whole heads on 8 waves 51, unsplit 67
     (60, 2048, False, True, False, False),    # unsplit 36.5, 8 segments of whole heads 38.5, 2 of channel halves 38.0
+    (64, 1000, False, False, False, False),   # unsplit 18.6, 4 segments of whole heads, a workgroup on every unit, 20.9
     (128, 2048, False, True, False, False),   # unsplit 41, 4 segments of whole heads 47
     (129, 2048, False, True, False, False),   # unsplit (whole heads on 16 waves) 52, 3 segments 55
     (129, 4096, True, True, False, False),    # 3 segments 91, unsplit 98
