@@ -2,13 +2,13 @@
 // headdim, d_state, seqlen and alignment) and as an on-device cross-check of it.
 //
 // A row of the state (one channel of one head) needs nothing of the other rows, and along the sequence the recurrence is a
-// scan, so a workgroup takes 16 rows and tiles of 256 tokens: 16 lanes share a row, 16 consecutive tokens each.  The
+// scan, so a workgroup takes 16 rows (4 in small launches) and tiles of 256 tokens: 16 lanes share a row, 16 consecutive tokens each.  The
 // decay depends on the head and the token alone, so its products over the lanes' tokens and the scan's products of those
 // are formed once per tile and serve every state; per state a lane then folds its 16 inputs into one value, four
 // data-parallel-primitive steps carry it across the row's lanes, and the lane replays its tokens from the state in front
 // of them while it adds to y: 4 multiply-adds per (token, state), no exponential.  What bounds it at the sizes it is for
 // (small models) is the latency of that chain, not a unit.  One workgroup per head that walked the tokens one after the
-// other took 5.4 us per token (8 heads of 64 channels, 16 states, 256 tokens: 1388 us, now 7.9 us).
+// other took 5.4 us per token (8 heads of 64 channels, 16 states, 256 tokens: 1388 us, now 5.9 us).
 #include <type_traits>
 
 #include "quamba_internal.h"
@@ -16,18 +16,16 @@
 namespace quamba {
 namespace {
 
-constexpr int kRows = 16;          // state rows (channels) per workgroup
 constexpr int kE = 16;             // tokens per lane
 constexpr int kLanes = 16;         // lanes per row
 constexpr int kTile = kE * kLanes; // tokens per tile
 constexpr int kNG = 16;            // states staged at a time
-constexpr int kBPitch = 4 * kLanes + 4;  // floats from one (state, quarter) of the staged B or C to the next: the pad
-                                         // spreads a token's writes over the banks
+constexpr int kBPitch = 4 * kLanes + 16; // floats from one (state, quarter) of the staged B or C to the next: the pad
+                                         // puts the writes of 64 consecutive tokens on as many banks
 constexpr int kXPitch = kTile + 16;      // bytes from one row's codes to the next
 constexpr int kYPitch = kTile + 2;       // halves from one row's outputs to the next
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-static_assert(kRows * kLanes == kTile, "256 threads are the (row, lane) pairs, or the tokens of the tile");
 
 __device__ __forceinline__ float code_to_float(uint32_t w, int k) { return (float)(int)(int8_t)(w >> (8 * k)); }
 
@@ -39,18 +37,25 @@ __device__ __forceinline__ float row_earlier(float edge, float v)
                                                                  0x110 + STEP, 0xf, 0xf, false));
 }
 
-constexpr size_t kernel_lds_bytes(int N)
+constexpr size_t kernel_lds_bytes(int N, int rows)
 {
-    return sizeof(float) * (2 * kNG * 4 * kBPitch + 2 * kTile + kRows * (size_t)N) + kRows * kXPitch + 2 * kRows * kYPitch;
+    return sizeof(float) * (2 * kNG * 4 * kBPitch + 2 * kTile + rows * (size_t)N) + rows * kXPitch + 2 * rows * kYPitch;
 }
 
 // WIDE: d_state is a multiple of 4 and B and C are 4-byte aligned (their codes are read 4 at a time).
 // SG: groups of 16 lanes that share a row, each with every SG-th state.  1: a wave holds 4 rows.  4: a wave is one row, whose
 // four sums meet at the end; four times the waves with a quarter of the chain, for launches that would leave the chip empty.
-template <bool WIDE, int SG>
-__global__ __launch_bounds__(kTile * SG) void prefill_generic_kernel(SsdArgs a, int x_vec, int y_vec)
+// ROWS: rows per workgroup.  4 (with SG = 4, one wave per SIMD) puts a small launch on four times the compute units: 16 waves on
+// one unit issue 9400 cycles of vector instructions, 3.9 of 7.9 us at 8 heads of 64 channels, 16 states, 256 tokens (now 5.9);
+// a lane then has the registers to take all its states of a group side by side (four chains of multiply-adds instead of one), and
+// of its 10000 cycles 2400 go by until the arguments are there, 2000 until the tile's loads are, 1200 in the staging and 2900
+// in the states.
+template <bool WIDE, int SG, int ROWS>
+__global__ __launch_bounds__(ROWS * kLanes * SG) void prefill_generic_kernel(SsdArgs a, int x_vec, int y_vec)
 {
-    constexpr int kThreads = kTile * SG;
+    constexpr int kRows = ROWS, kThreads = ROWS * kLanes * SG;
+    static_assert(kThreads >= kTile, "a thread for every (row, lane group, lane), and for every token of the tile");
+    typedef uint32_t xcodes __attribute__((ext_vector_type(ROWS / 4)));
     extern __shared__ f32x4 lds4[];
     float *s_B = reinterpret_cast<float *>(lds4);  // [kNG][4][kBPitch]: state, quarter of a lane's tokens, lane x 4 tokens
     float *s_C = s_B + kNG * 4 * kBPitch;          // the same, times s_C
@@ -68,32 +73,46 @@ __global__ __launch_bounds__(kTile * SG) void prefill_generic_kernel(SsdArgs a, 
     const bool own = row < rows;
     const float Ah = a.A[h], Dh = a.D ? a.D[h] : 0.0f;
     const float sB = a.B_scales[g], sC = a.C_scales[g];
-    const float sx = x_scale_lookup(a, h, p0 + min(row, rows - 1));
     const size_t st0 = ((size_t)bh * P + p0) * N;  // the workgroup's rows of the states
 
-    for (int e = tid; e < rows * N; e += kThreads) s_H[e] = a.init_state ? a.init_state[st0 + e] : 0.0f;
-
+    float sx = 0.0f;
+    auto look_up = [&]() {
+        for (int e = tid; e < rows * N; e += kThreads) s_H[e] = a.init_state ? a.init_state[st0 + e] : 0.0f;
+        sx = ROWS == 4 ? x_scale_lookup_wide(a, h, p0 + min(row, rows - 1)) : x_scale_lookup(a, h, p0 + min(row, rows - 1));
+    };
+    if (ROWS == 16) look_up();
     for (int t0 = 0; t0 < L; t0 += kTile) {
         const int nt = min(kTile, L - t0);
         const size_t tok0 = (size_t)b * L + t0;
-        // B and C of a group of states, transposed: state-major, fp32
+        // B and C of a group of states, transposed: state-major, fp32.  A thread takes 4 states at a time of one token; all of its
+        // loads are on their way before the first is used.
+        constexpr int kItems = kTile * kNG / 4 / kThreads;  // such quads per thread and group
+        const int t_bc = tid & (kTile - 1), quad0 = tid / kTile;
+        uint32_t bw[kItems], cw[kItems];
+        auto load_bc = [&](int n0, int ns) {
+            if (!WIDE) return;
+            const size_t off = ((tok0 + min(t_bc, nt - 1)) * G + g) * N + n0;
+#pragma unroll
+            for (int i = 0; i < kItems; ++i) {
+                const int n = min(4 * (quad0 * kItems + i), ns - 4);
+                bw[i] = *reinterpret_cast<const uint32_t *>(a.B + off + n);
+                cw[i] = *reinterpret_cast<const uint32_t *>(a.C + off + n);
+            }
+        };
+        auto put_bc = [&](int n, int t, float bv, float cv) {
+            const int at = (n * 4 + ((t >> 2) & 3)) * kBPitch + 4 * (t >> 4) + (t & 3);
+            s_B[at] = bv;
+            s_C[at] = sC * cv;
+        };
         auto stage_bc = [&](int n0, int ns) {
             if (WIDE) {
-                const int quads = ns >> 2;
-                for (int e = tid; e < kTile * quads; e += kThreads) {
-                    const int t = e / quads, n = 4 * (e - t * quads);
-                    uint32_t bw = 0, cw = 0;
-                    if (t < nt) {
-                        const size_t off = ((tok0 + t) * G + g) * N + n0 + n;
-                        bw = *reinterpret_cast<const uint32_t *>(a.B + off);
-                        cw = *reinterpret_cast<const uint32_t *>(a.C + off);
-                    }
-                    const int at = (n * 4 + ((t >> 2) & 3)) * kBPitch + 4 * (t >> 4) + (t & 3);
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        s_B[at + 4 * k * kBPitch] = code_to_float(bw, k);
-                        s_C[at + 4 * k * kBPitch] = sC * code_to_float(cw, k);
-                    }
+                for (int i = 0; i < kItems; ++i) {
+                    const int n = 4 * (quad0 * kItems + i);
+                    if (n >= ns) break;
+                    if (t_bc >= nt) bw[i] = cw[i] = 0;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) put_bc(n + k, t_bc, code_to_float(bw[i], k), code_to_float(cw[i], k));
                 }
             } else {
                 for (int e = tid; e < kTile * ns; e += kThreads) {
@@ -102,28 +121,32 @@ __global__ __launch_bounds__(kTile * SG) void prefill_generic_kernel(SsdArgs a, 
                     if (t < nt) {
                         const size_t off = ((tok0 + t) * G + g) * N + n0 + n;
                         bv = (float)a.B[off];
-                        cv = sC * (float)a.C[off];
+                        cv = (float)a.C[off];
                     }
-                    const int at = (n * 4 + ((t >> 2) & 3)) * kBPitch + 4 * (t >> 4) + (t & 3);
-                    s_B[at] = bv;
-                    s_C[at] = cv;
+                    put_bc(n, t, bv, cv);
                 }
             }
         };
         // thread = token: decay, step size, and the token's codes of the 16 rows.  Tokens past the end are identity
         // steps: decay 1, input 0.
         float dec_t = 1.0f, dtB_t = 0.0f;
-        u32x4 xq = {0, 0, 0, 0};
+        xcodes xq = (xcodes)(0u);
+        const size_t dt_at = (tok0 + min(tid, nt - 1)) * H + h;
+        const float dt_raw = a.dt_q ? (float)a.dt_q[dt_at] : a.dt[dt_at];
+        load_bc(0, min(kNG, N));
         if (tid < nt) {  // nt <= kTile
-            const float dt = step_size(a, (tok0 + tid) * H + h, h);
             const int8_t *xp = a.x + ((tok0 + tid) * H + h) * P + p0;
             if (x_vec) {
-                xq = *reinterpret_cast<const u32x4 *>(xp);
+                xq = *reinterpret_cast<const xcodes *>(xp);
             } else {
 #pragma unroll
                 for (int r = 0; r < kRows; ++r)
                     xq[r >> 2] |= (uint32_t)(uint8_t)xp[min(r, rows - 1)] << (8 * (r & 3));
             }
+        }
+        if (ROWS == 4 && t0 == 0) look_up();  // behind the first tile's loads: the look-ups wait for one another
+        if (tid < nt) {
+            const float dt = a.dt_q ? step_size_of_code(a, dt_raw, h) : dt_raw;
             dec_t = expf(dt * Ah);
             dtB_t = dt * sB;
         }
@@ -169,6 +192,7 @@ __global__ __launch_bounds__(kTile * SG) void prefill_generic_kernel(SsdArgs a, 
         for (int n0 = 0; n0 < N; n0 += kNG) {
             const int ns = min(kNG, N - n0);
             if (n0) {  // the first group is staged with the tile's tokens
+                load_bc(n0, ns);
                 __syncthreads();
                 stage_bc(n0, ns);
                 __syncthreads();
@@ -221,8 +245,10 @@ __global__ __launch_bounds__(kTile * SG) void prefill_generic_kernel(SsdArgs a, 
                     if (own && sub == last) s_H[row * N + n0 + n + j * SG] = hh[j];
             };
             int n = grp;
-            if (SG == 1)  // (two at a time take 160 registers, which 16 waves do not have)
-                for (; n + SG < ns; n += 2 * SG) states(n, std::integral_constant<int, 2>{});
+            // (two at a time take 160 registers, which 16 waves do not have)
+            constexpr int kSide = SG == 1 ? 2 : ROWS == 4 ? 4 : 1;
+            if (kSide > 1)
+                for (; n + (kSide - 1) * SG < ns; n += kSide * SG) states(n, std::integral_constant<int, kSide>{});
             for (; n < ns; n += SG) states(n, std::integral_constant<int, 1>{});
         }
         // outputs: the groups' sums of a row meet (two exchanges that leave a group with 4 of the 16 tokens), then through
@@ -254,13 +280,13 @@ __global__ __launch_bounds__(kTile * SG) void prefill_generic_kernel(SsdArgs a, 
         if (tid < nt) {
             uint16_t *yp = a.y + ((tok0 + tid) * H + h) * P + p0;
             if (y_vec) {
-                u32x4 o[2];
+                xcodes o[2];
 #pragma unroll
                 for (int r = 0; r < kRows; r += 2)
-                    o[r >> 3][(r >> 1) & 3] =
+                    o[r / (kRows / 2)][(r / 2) % (kRows / 4)] =
                         (uint32_t)s_y[r * kYPitch + tid] | ((uint32_t)s_y[(r + 1) * kYPitch + tid] << 16);
-                reinterpret_cast<u32x4 *>(yp)[0] = o[0];
-                reinterpret_cast<u32x4 *>(yp)[1] = o[1];
+                reinterpret_cast<xcodes *>(yp)[0] = o[0];
+                reinterpret_cast<xcodes *>(yp)[1] = o[1];
             } else {
                 for (int r = 0; r < rows; ++r) yp[r] = s_y[r * kYPitch + tid];
             }
@@ -272,14 +298,31 @@ __global__ __launch_bounds__(kTile * SG) void prefill_generic_kernel(SsdArgs a, 
     }
 }
 
-template <bool WIDE, int SG>
-hipError_t launch(dim3 grid, const SsdArgs &a, int x_vec, int y_vec, hipStream_t stream)
+template <bool WIDE, int SG, int ROWS>
+hipError_t launch(const SsdArgs &a, hipStream_t stream)
 {
-    const hipError_t e = allow_full_lds<prefill_generic_kernel<WIDE, SG>>();
+    const hipError_t e = allow_full_lds<prefill_generic_kernel<WIDE, SG, ROWS>>();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((prefill_generic_kernel<WIDE, SG>), grid, dim3(kTile * SG), kernel_lds_bytes(a.s.d_state), stream, a,
-                       x_vec, y_vec);
+    auto aligned = [](const void *p, size_t n) { return reinterpret_cast<uintptr_t>(p) % n == 0; };
+    const int whole = a.s.headdim % ROWS == 0;  // every row block is complete and starts at a multiple of ROWS codes
+    const dim3 grid((unsigned)(a.s.batch * a.s.nheads), (unsigned)((a.s.headdim + ROWS - 1) / ROWS));
+    hipLaunchKernelGGL((prefill_generic_kernel<WIDE, SG, ROWS>), grid, dim3(ROWS * kLanes * SG), kernel_lds_bytes(a.s.d_state, ROWS),
+                       stream, a, whole && aligned(a.x, ROWS), whole && aligned(a.y, ROWS));
     return hipGetLastError();
+}
+
+template <bool WIDE>
+hipError_t launch_rows(const SsdArgs &a, hipStream_t stream)
+{
+    // Blocks of 16 rows.  Up to one per compute unit: four lane groups per row (16 waves) instead of one (4 waves).  Up to one per
+    // two units: blocks of 4 rows (4 waves), of which a unit holds two with the registers they take (8 heads of 64 channels, 16
+    // states, 256 tokens, 16 / 4 rows: batch 1 7.8 / 5.9 us, 4 8.3 / 7.4, 5 8.4 / 11.4; 24 heads, 64 states, 1000 tokens 53.9 / 45.4).
+    // Codes that are read one at a time cost the four-fold staging more than the waves gain (10 states, 200 tokens 7.7 / 9.5).
+    const int64_t blocks = (int64_t)a.s.batch * a.s.nheads * ((a.s.headdim + 15) / 16);
+    if (blocks > compute_units()) return launch<WIDE, 1, 16>(a, stream);
+    if constexpr (WIDE)
+        if (2 * blocks <= compute_units()) return launch<WIDE, 4, 4>(a, stream);
+    return launch<WIDE, 4, 16>(a, stream);
 }
 
 }  // namespace
@@ -289,20 +332,13 @@ hipError_t launch(dim3 grid, const SsdArgs &a, int x_vec, int y_vec, hipStream_t
 bool prefill_generic_supports(const quamba_ssd_shape_t &s)
 {
     const size_t P = (size_t)s.headdim, N = (size_t)s.d_state;
-    return sizeof(float) * (P * N + 33 * P + 32 * N + 16) <= kLdsPerCu && kernel_lds_bytes(s.d_state) <= kLdsPerCu;
+    return sizeof(float) * (P * N + 33 * P + 32 * N + 16) <= kLdsPerCu && kernel_lds_bytes(s.d_state, 16) <= kLdsPerCu;
 }
 
 hipError_t launch_prefill_generic(const SsdArgs &a, hipStream_t stream)
 {
-    auto aligned = [](const void *p, size_t n) { return reinterpret_cast<uintptr_t>(p) % n == 0; };
-    const bool wide = a.s.d_state % 4 == 0 && aligned(a.B, 4) && aligned(a.C, 4);
-    const int whole = a.s.headdim % kRows == 0;  // every row block is complete and starts at a multiple of 16 codes
-    const int x_vec = whole && aligned(a.x, 16), y_vec = whole && aligned(a.y, 16);
-    const dim3 grid((unsigned)(a.s.batch * a.s.nheads), (unsigned)((a.s.headdim + kRows - 1) / kRows));
-    // up to one workgroup per compute unit: four lane groups per row (16 waves) instead of one (4 waves)
-    const bool split = (int64_t)grid.x * grid.y <= compute_units();
-    if (wide) return split ? launch<true, 4>(grid, a, x_vec, y_vec, stream) : launch<true, 1>(grid, a, x_vec, y_vec, stream);
-    return split ? launch<false, 4>(grid, a, x_vec, y_vec, stream) : launch<false, 1>(grid, a, x_vec, y_vec, stream);
+    const bool wide = a.s.d_state % 4 == 0 && reinterpret_cast<uintptr_t>(a.B) % 4 == 0 && reinterpret_cast<uintptr_t>(a.C) % 4 == 0;
+    return wide ? launch_rows<true>(a, stream) : launch_rows<false>(a, stream);
 }
 
 }  // namespace quamba

@@ -95,11 +95,14 @@ size_t prefill_mfma_workspace_bytes(const quamba_ssd_shape_t &s);
 
 // Step size of (token or sequence) index idx of head h: the caller's fp32 dt, or softplus(s_dt * code + bias[h])
 // (Section 3.2: Delta = softplus(F(x)) with the bias) when the pre-activation comes as int8 codes.
+__device__ __forceinline__ float step_size_of_code(const SsdArgs &a, float code, int h)
+{
+    const float v = a.dt_scale * code + (a.dt_bias ? a.dt_bias[h] : 0.0f);
+    return fmaxf(v, 0.0f) + log1pf(expf(-fabsf(v)));  // log(1 + exp(v)) without overflow
+}
 __device__ __forceinline__ float step_size(const SsdArgs &a, size_t idx, int h)
 {
-    if (!a.dt_q) return a.dt[idx];
-    const float v = a.dt_scale * (float)a.dt_q[idx] + (a.dt_bias ? a.dt_bias[h] : 0.0f);
-    return fmaxf(v, 0.0f) + log1pf(expf(-fabsf(v)));  // log(1 + exp(v)) without overflow
+    return a.dt_q ? step_size_of_code(a, (float)a.dt_q[idx], h) : a.dt[idx];
 }
 
 // SiLU(z) = z / (1 + exp(-z)) of a gate code (Section 3.2: the optional branch z multiplies the SSM output).

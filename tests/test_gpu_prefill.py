@@ -466,7 +466,23 @@ def test_generic_kernel_around_lanes_tiles_and_row_blocks(gpu_lib, b, L, H, P, N
     check(yg, hg, yref, href, "generic")
 
 
-@pytest.mark.parametrize("b,L,H,P,N", [(1, 300, 2, 20, 24), (1, 37, 3, 16, 5), (40, 33, 4, 40, 5)])
+@pytest.mark.parametrize("b,L,H,P,N,G", [(4, 257, 8, 64, 16, 1), (5, 257, 8, 61, 20, 1), (6, 17, 8, 62, 36, 2), (1, 513, 2, 3, 4, 1),
+                                         (1, 48, 3, 66, 12, 1)])
+def test_generic_kernel_in_blocks_of_4_rows_and_in_small_ones_of_16(gpu_lib, b, L, H, P, N, G):
+    """At most a block of 16 rows per two compute units is taken in blocks of 4 rows (the first call has as many as that, the last
+    two few, with ragged ends), up to one per unit in blocks of 16 with four lane groups per row."""
+    s = W.LayerShape("g4", b, L, H, P, N, G, 64, 1, min(2, P))
+    sc, prob, _ = make_problem(s, seed=L + P, calib_tokens=128)
+    init = np.random.default_rng(L).normal(0, 0.1, size=(b, H, P, N)).astype(np.float32)
+    yg, hg = run_prefill(gpu_lib, s, sc, prob, init_state=init)
+    yref, href, _ = oracle.ref_prefill(sc, prob["x"], prob["B"], prob["C"], prob["dt"], prob["A"], prob["D"], init)
+    check(yg, hg, yref, href, "generic")
+    one = {k: v[:1] if k in ("x", "B", "C", "dt") else v for k, v in prob.items()}
+    y1, h1 = run_prefill(gpu_lib, s.with_(batch=1), sc, one, init_state=init[:1])
+    assert np.array_equal(y1, yg[:1]) and np.array_equal(h1, hg[:1])      # the same sums in the same order, whatever the blocks
+
+
+@pytest.mark.parametrize("b,L,H,P,N", [(1, 300, 2, 20, 24), (1, 37, 3, 16, 5), (40, 33, 4, 40, 5), (9, 33, 4, 64, 8)])
 def test_generic_kernel_keeps_infinite_and_zero_states(gpu_lib, b, L, H, P, N):
     """An infinite state stays infinite as long as no single decay is zero, also where the product over several tokens
     underflows (exp(-8) per token); a state of zero without inputs stays zero where that product overflows (A > 0)."""
