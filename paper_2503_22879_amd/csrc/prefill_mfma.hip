@@ -563,14 +563,12 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(SsdArgs a)
             float dsum = 0.0f;
             for (int j = seg - 1; j >= 0; --j) {
                 const float w = exp2_fast(dsum);
-                const float *src = a.seg_state + ((size_t)j * pairs + bh) * kP * kN;
 #pragma unroll
                 for (int pt = 0; pt < PT; ++pt) {
-                    const int p = pt * 32 + l32;
 #pragma unroll
                     for (int rg = 0; rg < 4; ++rg) {
-                        const int n0 = 32 * wave + 8 * rg + 4 * hb;
-                        const f32x4 v = *reinterpret_cast<const f32x4 *>(src + (size_t)(p_base + p) * kN + n0);
+                        const f32x4 v = *reinterpret_cast<const f32x4 *>(
+                            a.seg_state + segment_state_at((size_t)j * pairs + bh, half + pt, wave, rg, lane));
 #pragma unroll
                         for (int i = 0; i < 4; ++i) st[pt][4 * rg + i] = fmaf(w, v[i], st[pt][4 * rg + i]);
                     }
@@ -1105,17 +1103,14 @@ __global__ __launch_bounds__(kStateThreads, 2) void segment_state_kernel(SsdArgs
     }
 
     const size_t pairs = (size_t)a.s.batch * H;
-    float *dst = a.seg_state + ((size_t)seg * pairs + bh) * kP * kN;
 #pragma unroll
     for (int pt = 0; pt < PT; ++pt) {
-        const int p = pt * 32 + l32;
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg) {
-            const int n0 = 32 * wave + 8 * rg + 4 * hb;
             f32x4 v;
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] = st[pt][4 * rg + i];
-            *reinterpret_cast<f32x4 *>(dst + (size_t)(p_base + p) * kN + n0) = v;
+            *reinterpret_cast<f32x4 *>(a.seg_state + segment_state_at((size_t)seg * pairs + bh, half + pt, wave, rg, lane)) = v;
         }
     }
     if (wave == 0 && lane == 0 && half == 0) a.seg_decay[(size_t)seg * pairs + bh] = seg_cum;
@@ -1168,8 +1163,6 @@ hipError_t launch_segment_state(const SsdArgs &a, hipStream_t stream)
 // Few (sequence, head) pairs leave compute units idle, and a workgroup walks its sequence chunk by chunk.  Such
 // batches may be cut along the sequence: with `pairs` workgroups per segment (twice that with channel halves) the
 // split aims at two workgroups per compute unit, at least two chunks per segment and at most kMaxSegments segments.
-constexpr int kMaxSegments = 8;
-
 namespace {
 
 struct Split {
@@ -1214,7 +1207,7 @@ Split largest_split(const quamba_ssd_shape_t &s)
 // unit) walks a chunk of a channel half in 1.9 us and of a whole head in 2.8, a lone workgroup of 8 waves in 2.7, two of them on
 // a unit in 4.2 to 6.  A single chunk is no faster on it: 16 tokens of 128 heads 6.0 us, 8-wave kernel in channel halves 5.5; of
 // 192 heads 7.0, whole heads 6.5; whole heads from half a pair per unit on (128 tokens of 129 heads 7.75 in halves, 8.06 whole,
-// and without the final state 6.67, 6.36; of 144 heads 8.27, 7.99).  From two chunks on the cheapest of three forms is taken: the
+// and without the final state 6.67, 6.36; of 144 heads 8.27, 7.99).  From two chunks on the cheapest of three forms (and a fourth, below) is taken: the
 // wide kernel unsplit, its channel halves in segments that still get a unit each, and segments of whole heads on the 8-wave
 // kernel.  All were timed over 33 to 256 pairs of 8 to 48 chunks with and without the final state, gate codes and step-size codes.
 //
@@ -1226,6 +1219,16 @@ Split largest_split(const quamba_ssd_shape_t &s)
 // meet on.  Over these and 120 drawn shapes the choice is within 0.1 % of the best form on average, 4 % off at most.  (24 heads, 2048 tokens: unsplit 34.7, 4 segments 23.2; 80 heads, 1024 / 4096 tokens:
 // unsplit 20.7 / 66.1, whole heads 27.5 / 63.7; 128 heads, 2048 tokens: 37.8, 48.4; 112 heads, 6144 tokens without the state and
 // with step-size codes 114.6, 102.3.)
+//
+// Up to 42 pairs of the 256 units (six segments or more get a unit per whole head) a fourth form, segments of whole heads on the wide
+// kernel, computes the score tiles once instead of twice and keeps the 16 waves: 9.6 + 2.88 S (0.48 + 0.72 S, 0.4 S, 0.57 S) + 0.0059
+// per pair and chunk with the state pass.  It is compared with what the form chosen so far takes since the end states lie in
+// accumulator order: halves 7 + 3.14 S (0.28 + 0.48 S, 0.18 S, 0.65 S), whole heads of 8 waves 8.3 + 3.58 S (1.15 S, 0.56 S, 0.79 S) +
+// 0.0061 per pair and chunk, 2.3 more and 3.8 more as above; each with 0.2 to 0.7 for every hundred end states that its segments start
+// from.  (Fitted to all forms of 1008 calls of 6 to 128 pairs, 8 to 44 chunks and all operands, 2 to 3 % rms; taken where it
+// promises 0.6 us, in 140 of them, the form needs 9.3 % less on average, 4.5 % more in one.  24 heads, 2048 tokens: halves 23.4, whole heads 21.3, of 8 waves 21.4; 32 heads,
+// 6144 tokens 53.6, 43.6, 44.6; 40 heads, 2048 tokens 31.1, 26.1, 29.5.  With five segments, 43 to 51 pairs, it is 1 to 8 % ahead from
+// 20 chunks on, below it the two kernels of whole heads are level.)
 //
 // Above, segments of whole heads are the faster form for up to two thirds of a pair per unit (3 segments) from a number of chunks
 // on: 26, and half a chunk per pair more (129 pairs, 24 / 28 / 32 chunks: unsplit 74.8 / 86.0 / 97.4, segments 73.8 / 81.2 / 91.5; 160
@@ -1264,15 +1267,39 @@ PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, const PrefillOperands
         const int64_t whole = most.halves ? INT64_MAX
                                           : 391 + step + 120 * most.nseg + (520 + 121 * fin + 88 * gate + 70 * dtq) * len +
                                                 143 * len * std::max<int64_t>(0, wgs - cus) / cus;
-        if (unsplit <= std::min(cut, whole)) return plan;
-        plan.wide = cut <= whole;
-        if (plan.wide) split = own;
+        const bool keep = unsplit <= std::min(cut, whole);
+        plan.wide = keep || cut <= whole;
+        if (!keep && plan.wide) split = own;
+        plan.channel_split = plan.wide;
+        // Up to a pair for every six units: the wide kernel's whole heads in segments, where they are the cheapest of the three
+        // as they are now (see above).
+        Split heads;
+        heads.cut(nchunks, (int)std::min<int64_t>(most.nseg, cus / pairs));
+        if (cus / pairs >= 6 && heads.nseg >= 2) {
+            auto states_read = [&](const Split &x) { return pairs * x.nseg * (x.nseg - 1) / 2; };
+            const int64_t taken =
+                keep ? unsplit * 98 / 100
+                : plan.wide
+                    ? 700 + (314 + 48 * fin + 18 * gate + 65 * dtq) * (int64_t)own.seg_chunks + 28 * fin + 73 * states_read(own) / 100
+                    : 827 + (state_wgs > cus ? 233 : 0) + (wgs <= cus ? 0 : wgs - cus > pairs ? 381 : 381 * last / len) +
+                          (358 + 115 * fin + 56 * gate + 79 * dtq) * len + 18 * states_read(most) / 100 +
+                          61 * pairs * nchunks / 100 + 13 * len * std::max<int64_t>(0, wgs - cus) / cus;
+            const int64_t in_heads = 961 + (288 + 72 * fin + 40 * gate + 57 * dtq) * (int64_t)heads.seg_chunks + 48 * fin +
+                                     35 * states_read(heads) / 100 + 59 * pairs * nchunks / 100;
+            if (in_heads + 60 < taken) {
+                plan.wide = true;
+                plan.channel_split = false;
+                plan.nseg = heads.nseg;
+                plan.seg_chunks = heads.seg_chunks;
+                return plan;
+            }
+        }
+        if (keep) return plan;
     } else if (plan.wide) {
         const int64_t from = gate && dtq ? (fin ? 26 : 22) : (fin && dtq ? 44 : 26) + (pairs - cus / 2 - 1) / 2;
         if (most.nseg < 3 || nchunks < from) return plan;
-        plan.wide = false;
+        plan.wide = plan.channel_split = false;
     }
-    plan.channel_split = plan.wide;
     plan.nseg = split.nseg;
     plan.seg_chunks = split.seg_chunks;
     return plan;

@@ -147,6 +147,17 @@ __device__ __forceinline__ f16x8 pack_f16x8(const float v[8])
     return r;
 }
 
+// A segment's end state in the workspace, where the state pass writes and the outputs' kernels read it: as it stands in the
+// accumulators, 4 values of a lane behind those of the lane before, so that a wave moves 1 KB of consecutive memory at once.  (In
+// the order [p][n] of the caller's states it touches 32 lines of 32 bytes each: 1.2 us per segment and workgroup.)  Wave w's values
+// 4 rg .. 4 rg + 3 of the channels 32 q .. 32 q + 31 lie behind the returned offset.
+__device__ __forceinline__ size_t segment_state_at(size_t pair, int q, int wave, int rg, int lane)
+{
+    return pair * (kP * kN) + (size_t)(((q * 4 + wave) * 4 + rg) * 64 + lane) * 4;
+}
+
+constexpr int kMaxSegments = 8;  // of the sequence split
+
 // Workgroup -> (sequence, head).  Hardware hands consecutive workgroup ids to the 8 XCDs round-robin, each XCD with
 // its own L2.  When the number of (sequence, state group) units is a multiple of 8, all heads of a unit are put on
 // one XCD, so that the B and C rows they share are fetched into one L2 instead of eight.

@@ -1,5 +1,5 @@
 // Chunked prefill of batches of at most one (sequence, head) pair per compute unit, where every pair (with half a pair per
-// unit: every channel half of every pair, or of every segment of its sequence) has a unit to itself.
+// unit: every channel half of every pair, or every half or whole head of every segment of its sequence) has a unit to itself.
 //
 // The arithmetic is that of prefill_mfma_kernel (prefill_mfma.hip describes it), for 32 (PT = 1) or all 64 (PT = 2) of a head's
 // channels.  What bounds such a launch is the serial walk over the chunks: a lone wave issues an instruction every 8 cycles,
@@ -18,11 +18,19 @@
 // instructions than selects and scaled operands, and fewer roundings (error of y against 64 bits 2.5 to 3.0e-4, 8-wave kernel
 // 2.6 to 3.2e-4).
 //
+// Segments of a sequence are walked by workgroups of a few chunks, whose start counts: there the waves stand the other way round, in
+// the order in which the first chunk needs them.  The last of 16 waves starts 2200 cycles after the first, and with the staging waves
+// last the first chunk was staged at 5900 to 7900 cycles, now at 4500 to 6000 (24 heads of 2048 tokens in 4 segments of halves 24.4 ->
+// 23.5 us).  A SIMD serves its oldest wave first, and a chunk takes longer when that is a staging wave (64 channels 4700 cycles
+// instead of 4000), so priorities restore the other order of service.  They cost a chunk 1 %: 12 chunks of 128 heads with gate and
+// step-size codes 45.8 -> 46.3 us, so unsplit calls do without both.
+//
 // Measured with the final state (the best of the 8-wave kernel's launches, whole, cut into segments or in channel halves /
 // this kernel): 128 heads, one sequence of 1531 tokens with gate and step-size codes 49.4 / 34.9 us, 2500 tokens 56 / 46; 120
-// pairs, 1000 tokens 32.2 / 22.0; 80 heads, 1000 tokens 27.4 / 20.8; 24 heads, 2048 tokens (4 segments) 24.3 / 22.8, 500
-// tokens 14.3 / 11.9; two sequences of 128 heads, 1024 tokens 36.1 / 30.6, 4096 tokens 128 / 107, 1531 tokens with gate and codes
-// 64.4 / 47.5.  By cycle counters read in the kernel (a build of its own) a chunk of 32 channels takes 4000 cycles, 4600 with the
+// pairs, 1000 tokens 32.2 / 22.0; 80 heads, 1000 tokens 27.4 / 20.8; 24 heads, 2048 tokens (8 segments of whole heads) 24.3 / 21.5,
+// 500 tokens 14.3 / 11.9; 40 heads, 2048 tokens (6 segments of whole heads) 29.5 / 26.1; two sequences of 128 heads, 1024 tokens 36.1 /
+// 30.6, 4096 tokens 128 / 107, 1531 tokens with gate and codes 64.4 / 47.5.  By cycle counters read in the kernel (a build of its
+// own) a chunk of 32 channels takes 4000 cycles, 4600 with the
 // two-term state update; the roles' waves wait 500 to 1500 of them at the barrier, the vector ALUs issue 3000 (the hardware's
 // counters, profiles/short_prompts_and_mixed_hadamard.txt, have 840 instructions per SIMD and chunk, the launch's set-up
 // included, 960 with gate and step-size codes).  A chunk of 64 channels takes 5600 (6200): its state waves are busy for 5100 of
@@ -124,9 +132,14 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
     const int b = bh / H, h = bh - b * H, g = h / (H / G);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave16 = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int role = wave16 >> 2, wave = wave16 & 3;
+    const int role = SEG ? 3 - (wave16 >> 2) : wave16 >> 2, wave = wave16 & 3;
     const int tid4 = tid & 255;
     if (tid < 16) s_done[tid] = 0;  // read and written behind the first barrier
+    if (SEG) {  // (see the top: the outputs' waves are the youngest of their SIMD)
+        if (role == 0) __builtin_amdgcn_s_setprio(3);
+        else if (role == 1) __builtin_amdgcn_s_setprio(2);
+        else if (role == 2) __builtin_amdgcn_s_setprio(1);
+    }
     // Lane-derived values are made anew in every chunk (fresh_lane): kept across the loop over chunks, the addresses formed
     // from them would push other values into scratch memory.
     int l32 = lane & 31, hb = lane >> 5;
@@ -292,8 +305,8 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
         if (role == 0) {
             // ---- the later terms and the outputs of block `wave` ----
             const int tb = wave, mid = tb >= 2 ? tb - 1 : tb;
-            if (tid < kPw) s_sx[tid] = x_scale_lookup(a, h, p_base + tid) * (d_by_mfma ? y_scale : 1.0f);
-            if (GATED) s_silu[tid] = silu_of_code(a.z_scale, (int8_t)tid);
+            if (tid4 < kPw) s_sx[tid4] = x_scale_lookup_wide(a, h, p_base + tid4) * (d_by_mfma ? y_scale : 1.0f);
+            if (GATED) s_silu[tid4] = silu_of_code(a.z_scale, (int8_t)tid4);
             // per lane (token t of the block): which of its 16 score rows s are at or in front of t, two to a dword; with 64 channels
             // they wait in LDS, the registers are the sums'
             u32x4 keep[2];
@@ -564,12 +577,12 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
             float dsum = 0.0f;
             for (int j = seg - 1; j >= 0; --j) {
                 const float w = exp2_fast(dsum);
-                const float *src = a.seg_state + (size_t)j * pairs * kP * kN + st_row;
 #pragma unroll
                 for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
                     for (int rg = 0; rg < 4; ++rg) {
-                        const f32x4 v = *reinterpret_cast<const f32x4 *>(src + 32 * pt * kN + 8 * rg);
+                        const f32x4 v = *reinterpret_cast<const f32x4 *>(
+                            a.seg_state + segment_state_at((size_t)j * pairs + bh, half + pt, wave, rg, lane));
 #pragma unroll
                         for (int i = 0; i < 4; ++i) st[pt][4 * rg + i] = fmaf(w, v[i], st[pt][4 * rg + i]);
                     }
@@ -792,8 +805,12 @@ hipError_t launch_prefill_wide(const SsdArgs &a, bool halves, bool precise, hipS
 {
     const bool seg = a.nseg > 1;
     if (!halves) {
-        if (precise) return a.z ? launch<true, 2, true, false>(a, stream) : launch<true, 2, false, false>(a, stream);
-        return a.z ? launch<false, 2, true, false>(a, stream) : launch<false, 2, false, false>(a, stream);
+        if (precise) {
+            if (a.z) return seg ? launch<true, 2, true, true>(a, stream) : launch<true, 2, true, false>(a, stream);
+            return seg ? launch<true, 2, false, true>(a, stream) : launch<true, 2, false, false>(a, stream);
+        }
+        if (a.z) return seg ? launch<false, 2, true, true>(a, stream) : launch<false, 2, true, false>(a, stream);
+        return seg ? launch<false, 2, false, true>(a, stream) : launch<false, 2, false, false>(a, stream);
     }
     if (precise) {
         if (a.z) return seg ? launch<true, 1, true, true>(a, stream) : launch<true, 1, true, false>(a, stream);

@@ -71,7 +71,7 @@ struct SsdArgs {
     // own workgroups, which start from the combination of those.
     int32_t nseg;
     int32_t seg_chunks;
-    float *seg_state;          // [nseg-1][batch*nheads][headdim][d_state], in the kernel's accumulator units
+    float *seg_state;          // [nseg-1][batch*nheads][headdim * d_state], in the kernel's accumulator units and order
     float *seg_decay;          // [nseg-1][batch*nheads]
     int32_t pace_first;        // matrix-core prefill: first workgroup id of the second dispatch round when the two
                                // workgroups of a compute unit are to be kept at the same pace (see the kernel), else

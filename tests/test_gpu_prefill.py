@@ -127,7 +127,7 @@ NO_SEQ_SPLIT = 0x10
 
 
 @pytest.mark.parametrize("H,G,L,flags", [
-    (24, 1, 2048, 0),          # 130M shape: 4 segments of 4 chunks, two workgroups of 16 waves per head and segment
+    (24, 1, 2048, 0),          # 130M shape: 8 segments of 2 chunks, a workgroup of 16 waves per head and segment
     (24, 1, 2333, 0),          # 19 chunks: 5 segments of 4 chunks, the last one of 3 with a ragged end
     (24, 1, 1100, NO_SPLIT),   # 9 chunks, whole heads on 8 waves: 3 segments of 3 chunks, the last chunk ragged
     (128, 8, 4096, 0),         # 8B shape at batch 1: room for 4 segments, run unsplit
@@ -164,7 +164,7 @@ def test_sequence_split_against_the_oracle_and_the_unsplit_launch(gpu_lib, H, G,
     (1, 128, 8, 161, False),   # a workgroup on every compute unit, the second chunk a block and a token
     (2, 3, 1, 256, False),     # whole chunks only
     (1, 24, 1, 385, False),    # four chunks: both LDS sets are used again
-    (1, 40, 1, 2040, False),   # three segments of the sequence split, the last one ragged
+    (1, 40, 1, 2040, False),   # six segments of the sequence split, the last one ragged
     (2, 5, 1, 161, True),      # the skip term leaves the fp16 range: added in the epilogue
     (3, 43, 1, 129, False),    # whole heads: one pair more than every other compute unit, the second chunk a single token
     (2, 128, 8, 289, False),   # whole heads on every compute unit, three chunks: every place in LDS is used again
@@ -248,6 +248,39 @@ def test_segments_of_whole_heads(gpu_lib, H, G, L, segments):
             assert np.abs(hg - hu).max() <= 2e-5 * np.abs(hu).max()
 
 
+@pytest.mark.parametrize("H,G,L,segments,tiny_scales", [
+    (24, 1, 2048, 8, False),    # whole heads on 16 waves: 2 chunks each
+    (24, 3, 1921, 8, False),    # the same, the last chunk a single token
+    (40, 1, 2010, 6, False),    # 3 chunks each, the last one a single ragged chunk
+    (32, 2, 2050, 6, True),     # 3 chunks each, the last one 2 with two tokens; the skip term in the epilogue
+    (16, 1, 2048, 8, False),    # channel halves on 16 waves: 2 chunks each
+    (20, 5, 1700, 5, True),     # 3 chunks each, the last one 2; the skip term in the epilogue
+])
+def test_segments_on_workgroups_of_sixteen_waves(gpu_lib, H, G, L, segments, tiny_scales):
+    """Plans that cut the sequence into segments of whole heads or of channel halves on workgroups of 16 waves: with an initial state,
+    against the oracle and the same kernel's unsplit launch (the bars of the tests above)."""
+    s = W.CONFIGS["m2_8b_b1"].with_(batch=1, seqlen=L, nheads=H, ngroups=G)
+    sc, prob, _ = make_problem(s, 36, calib_tokens=256)
+    if tiny_scales:
+        sc.B_scales[:] *= np.float32(1e-5)
+        sc.C_scales[:] *= np.float32(1e-5)
+    h0 = W.draw_state(s, 36).astype(np.float32) * np.float32(1e-5 if tiny_scales else 1.0)
+    yref, href, _ = oracle.ref_prefill(sc, prob["x"], prob["B"], prob["C"], prob["dt"], prob["A"], prob["D"],
+                                       init_state=h0.astype(np.float64))
+    cells = oracle.cell_index_table(sc, s.nheads, s.headdim, s.ngroups)
+    for want_state in (True, False):
+        used = []
+        yg, hg = run_prefill(gpu_lib, s, sc, prob, 0, init_state=h0, want_state=want_state, used=used)
+        assert used == [4 * (segments - 1) * H * (64 * 128 + 1)], "bytes of workspace written"
+        check(yg, hg, yref, href if want_state else None, f"16 waves H={H} L={L} state={want_state}", cells=cells)
+        yu, hu = run_prefill(gpu_lib, s, sc, prob, NO_SEQ_SPLIT, init_state=h0, want_state=want_state)
+        flipped = np.count_nonzero(yg != yu)
+        assert flipped <= 1e-2 * yg.size, f"{flipped} of {yg.size} outputs differ from the unsplit launch"
+        assert np.abs(yg - yu).max() <= 2.0 ** -9 * np.abs(yu).max()
+        if want_state:
+            assert np.abs(hg - hu).max() <= 2e-5 * np.abs(hu).max()
+
+
 def repeat_sequences(s, prob, pairs):
     """The problem's sequences over and over, until there are at least `pairs` (sequence, head) pairs: (shape, problem)."""
     k = -(-pairs // (s.batch * s.nheads))
@@ -302,7 +335,7 @@ def test_sequence_split_on_drawn_shapes(gpu_lib, b, H, G, L, flags, seed, want_s
 
 
 @pytest.mark.parametrize("H,L,split,state,gate,dt_codes", [
-    (24, 2048, True, True, False, False),     # 4 segments of channel halves on 16 waves, 23 us; unsplit 35
+    (24, 2048, True, True, False, False),     # 8 segments of whole heads on 16 waves, 21 us; unsplit 35
     (48, 4096, True, True, False, False),     # 8 segments of whole heads on 8 waves 51, unsplit 67
     (60, 2048, False, True, False, False),    # unsplit 36.5, 8 segments of whole heads 38.5, 2 of channel halves 38.0
     (64, 1000, False, False, False, False),   # unsplit 18.6, 4 segments of whole heads, a workgroup on every unit, 20.9
