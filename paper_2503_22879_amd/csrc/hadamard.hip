@@ -56,6 +56,19 @@ __device__ __forceinline__ uint32_t codes_packed(const float (&r)[4])
     return out;
 }
 
+// The same without the sub-dword add, for the kernel that is bound by vector issue (see there): the sums' low bytes gathered by
+// byte permutes.
+template <int K>
+__device__ __forceinline__ uint32_t codes_gathered(const float (&r)[4])
+{
+    uint32_t c[4];
+#pragma unroll
+    for (int k = 0; k < K; ++k) c[k] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_fmed3f(r[k], -128.0f, 127.0f) + kMagic);
+    const uint32_t lo = __builtin_amdgcn_perm(c[1], c[0], 0x0c0c0400u);
+    if (K == 2) return lo;
+    return __builtin_amdgcn_perm(__builtin_amdgcn_perm(c[3], c[2], 0x0c0c0400u), lo, 0x05040100u);
+}
+
 // In-register butterflies of one phase: v[e], e = 0..31, strides 1..2^(BITS-1) on the register index.
 template <int BITS, int FIRST = 1>
 __device__ __forceinline__ void butterflies(float (&v)[32])
@@ -285,24 +298,32 @@ __global__ __launch_bounds__(256) void hadamard_quantize_mixed_kernel(const uint
 // turns the codes of four rows at one position into those of one row at four positions, a dword to store.  A row need not
 // fill its last super-block: the missing part is never written, and what phase B reads of it stays in register groups of
 // its own that are not used.
-// Bound by vector issue: at order 5120 phase C issues 433 vector instructions in each of 4 waves, phases A and B 275 in 3, and the
-// vector ALUs are busy 99 % of the time at 4 cycles each (profiles/short_prompts_and_mixed_hadamard.txt).  With two positions per thread it
-// ran on half the waves, at 5 waves per SIMD, and LDS (23 KB a row) admits no more rows: one position and 7 waves per SIMD take
-// 16384 rows of 5120 values from 69.9 to 66.4 us (3.8 TB/s), 3000 from 16.5 to 15.4, 256 from 4.2 to 3.4; 16384 of 1536 values
-// from 20.5 to 20.1.
+// Bound by vector issue where many rows are in flight: two waves of a SIMD issue side by side (one vector instruction in 2.1 cycles
+// instead of 4.2) only while both are at plain ones, and a sub-dword, lane-move, packed or mixed-precision instruction of either
+// also sets them one behind the other for long after.  MANY, for more than two rows per unit, therefore converts the inputs
+// plainly and gathers the codes' bytes with permutes (v_cvt_f32_f16, v_perm_b32: more instructions than v_fma_mix_f32 and sub-dword
+// adds, which calls of few rows keep for their shorter chain), and the first exchange turns its 16-byte pieces instead of padding
+// rows, so that a row takes 20 KB of LDS and a unit holds 8 of order 5120 instead of 7.  16384 rows of 5120 values 70.0 -> 64.3 us
+// (3.9 TB/s), 3000 17.1 -> 15.6, 1600 11.3 -> 9.8; of 2560 42.7 -> 37.8, of 1536 22.3 -> 21.5, of 3072 38.2 -> 36.7.  One position per
+// thread in phase C instead of two: 69.9 -> 66.4 before that.
 // Plain stores: non-temporal ones take up to 13 % off the transform alone and put more on the reader of the codes (with an int8
 // product of 2560 columns behind, plain / non-temporal: 2867 rows of 5120 79.3 / 83.5 us, 13653 of 1536 95 / 105, 8192 of 2560
 // 97 / 108, 3413 of 6144 91 / 96; 1000 to 1700 rows of 5120 46.8 / 45.6, 63.2 / 61.6).
-// Not faster: two or four rows to a workgroup, which leaves no lane idle in phases A and B (62.8 against 59.0 us on
+// Not faster: a wave to a row, its butterflies between lanes as v_fmac_f32_dpp and lane swizzles without LDS or barriers (77 to 82 us
+// for 16384 rows of 5120); s_nop around the instructions named above (69 against 69); two or four rows to a workgroup, which leaves no lane idle in phases A and B (62.8 against 59.0 us on
 // rows in the last-level cache); a loop over rows with the next one's loads in flight (74.4); the sums of 4 to 16 of the
 // rows as v_mfma_f32_4x4x1_16b_f32, bit for bit the same (70 to 79 against 65).
 // POS = 2 is phase C with two positions per thread and 2-byte stores, a whole line of a row from every wave (launch_mixed says
 // where it is the better one).
-template <int M, int LOGP, int POS>
+template <int LOGP, bool MANY>
+constexpr bool mixed_turned() { return MANY || LOGP == 7; }
+
+template <int M, int LOGP, int POS, bool MANY>
 __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *out, float inv_s)
 {
     constexpr int P = 1 << LOGP, N = M * P, T = N / 32, NSB = (N + 1023) / 1024;
-    extern __shared__ float lds[];  // NSB * 1152 floats
+    constexpr bool kTurned = mixed_turned<LOGP, MANY>();
+    extern __shared__ float lds[];  // NSB * (kTurned ? 1024 : 1152) floats
     const int t = threadIdx.x;
     const size_t row = (size_t)blockIdx.x * N;
     if (t < T) {
@@ -316,24 +337,44 @@ __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *o
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const uint32_t w = nx[q][i];
-                asm("v_fma_mix_f32 %0, %1, 1.0, %1 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(v[8 * q + 2 * i]) : "v"(w));
-                asm("v_fma_mix_f32 %0, %1, 1.0, -%1 op_sel:[0,0,1] op_sel_hi:[1,0,1]"
-                    : "=v"(v[8 * q + 2 * i + 1]) : "v"(w));
+                if (!MANY) {
+                    asm("v_fma_mix_f32 %0, %1, 1.0, %1 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(v[8 * q + 2 * i]) : "v"(w));
+                    asm("v_fma_mix_f32 %0, %1, 1.0, -%1 op_sel:[0,0,1] op_sel_hi:[1,0,1]"
+                        : "=v"(v[8 * q + 2 * i + 1]) : "v"(w));
+                    continue;
+                }
+                uint32_t high;
+                asm("v_lshrrev_b32 %0, 16, %1" : "=v"(high) : "v"(w));
+                const float a = (float)__builtin_bit_cast(_Float16, (uint16_t)w);
+                const float b = (float)__builtin_bit_cast(_Float16, (uint16_t)high);
+                v[8 * q + 2 * i] = a + b;
+                v[8 * q + 2 * i + 1] = a - b;
             }
         butterflies<5, 2>(v);
-        float *pa = lds + (t & 31) + 1152 * (t >> 5);
+        if (kTurned) {  // value k of the thread lies in row k, whose 16-byte pieces change places with the low bits of k
+            float *pa = lds + 1024 * (t >> 5) + (t & 3);
+            const int piece = t >> 2 & 7;
 #pragma unroll
-        for (int k = 0; k < 32; ++k) pa[36 * k] = v[k];
+            for (int k7 = 0; k7 < 8; ++k7) {
+                float *row_k = pa + 4 * (piece ^ k7);
+#pragma unroll
+                for (int k = k7; k < 32; k += 8) row_k[32 * k] = v[k];
+            }
+        } else {
+            float *pa = lds + (t & 31) + 1152 * (t >> 5);
+#pragma unroll
+            for (int k = 0; k < 32; ++k) pa[36 * k] = v[k];
+        }
     }
     __syncthreads();
     const int t_lo = t & 31, t_hi = t >> 5;
     float v[32];
     if (t_hi < NSB) {
         // phase B: values i = t_lo + 32 e + 1024 t_hi, e = 0..31; e's low LOGP - 5 bits are the strides 32..p/2
-        const f32x4 *pb = reinterpret_cast<const f32x4 *>(lds + 36 * t_lo + 1152 * t_hi);
+        const f32x4 *pb = reinterpret_cast<const f32x4 *>(lds + (kTurned ? 32 : 36) * t_lo + (kTurned ? 1024 : 1152) * t_hi);
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const f32x4 w = pb[q];
+            const f32x4 w = pb[kTurned ? q ^ (t_lo & 7) : q];
             v[4 * q] = w[0]; v[4 * q + 1] = w[1]; v[4 * q + 2] = w[2]; v[4 * q + 3] = w[3];
         }
         butterflies<LOGP - 5>(v);
@@ -363,7 +404,7 @@ __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *o
                 a1 = a1 + t1[b] * paley_sign<M>(a, b);
             }
             const float sc[4] = {a0 * inv_s, a1 * inv_s, 0.0f, 0.0f};
-            *reinterpret_cast<uint16_t *>(out + row + (size_t)a * P + 2 * t) = (uint16_t)codes_packed<2>(sc);
+            *reinterpret_cast<uint16_t *>(out + row + (size_t)a * P + 2 * t) = (uint16_t)(MANY ? codes_gathered<2>(sc) : codes_packed<2>(sc));
         }
     } else {
         // phase C: position t of every block, four rows of the M-point sums at a time
@@ -384,7 +425,7 @@ __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *o
             }
             // a lane's dword holds the codes of rows a .. a + 3; after the exchange inside the quad, of four positions of row
             // a + t % 4
-            const uint32_t w = codes_packed<4>(sc);
+            const uint32_t w = MANY ? codes_gathered<4>(sc) : codes_packed<4>(sc);
             const uint32_t w1 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w, 0xB1, 0xf, 0xf, true), w, sel1);
             const uint32_t w2 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w1, 0x4E, 0xf, 0xf, true), w1, sel2);
             *reinterpret_cast<u32_u *>(dst + (size_t)a * P) = w2;
@@ -392,21 +433,30 @@ __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *o
     }
 }
 
-template <int M, int LOGP, int POS>
-hipError_t launch_mixed_fast(const uint16_t *y, int64_t rows, float inv_s, int8_t *out, hipStream_t stream)
+template <int M, int LOGP, int POS, bool MANY>
+hipError_t launch_mixed_form(const uint16_t *y, int64_t rows, float inv_s, int8_t *out, hipStream_t stream)
 {
     constexpr int P = 1 << LOGP, N = M * P, NSB = (N + 1023) / 1024;
     constexpr int threads = P / POS;
     static_assert(threads >= N / 32 && threads >= 32 * NSB, "every phase has its threads");
-    constexpr int lds = NSB * 1152 * (int)sizeof(float);
+    constexpr int lds = NSB * (mixed_turned<LOGP, MANY>() ? 1024 : 1152) * (int)sizeof(float);
     static_assert(threads <= 1024 && lds <= 160 * 1024, "launch shape");
     if (lds > 48 * 1024) {
-        const hipError_t e = allow_full_lds<hadamard_quantize_mixed_fast_kernel<M, LOGP, POS>>();
+        const hipError_t e = allow_full_lds<hadamard_quantize_mixed_fast_kernel<M, LOGP, POS, MANY>>();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((hadamard_quantize_mixed_fast_kernel<M, LOGP, POS>), dim3((unsigned)rows), dim3(threads), lds, stream,
+    hipLaunchKernelGGL((hadamard_quantize_mixed_fast_kernel<M, LOGP, POS, MANY>), dim3((unsigned)rows), dim3(threads), lds, stream,
                        y, out, inv_s);
     return hipGetLastError();
+}
+
+template <int M, int LOGP, int POS>
+hipError_t launch_mixed_fast(const uint16_t *y, int64_t rows, float inv_s, int8_t *out, hipStream_t stream)
+{
+    // More than two rows per compute unit: enough waves for a SIMD's vector instructions to count.  (Order 5120, the short forms / these:
+    // 512 rows 5.04 / 5.10 us, 600 6.30 / 5.87, 1600 11.3 / 9.8, 16384 70.0 / 64.3; 12288: 256 rows 5.41 / 5.53, 800 12.57 / 12.35.)
+    if (rows > 2 * compute_units()) return launch_mixed_form<M, LOGP, POS, true>(y, rows, inv_s, out, stream);
+    return launch_mixed_form<M, LOGP, POS, false>(y, rows, inv_s, out, stream);
 }
 
 template <int M, int LOGP>

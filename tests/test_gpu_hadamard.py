@@ -131,6 +131,26 @@ def test_large_mixed_calls_are_their_rows(gpu_lib, n, rows, off):
     assert (buf[:off] == 77).all() and (buf[off + rows * n:] == 77).all()
 
 
+@pytest.mark.parametrize("n", [1536, 2560, 3072, 5120, 6144, 10240, 12288])
+def test_mixed_orders_around_two_rows_per_compute_unit(gpu_lib, n):
+    """Calls of more than two rows per compute unit form the codes with other instructions than shorter ones: the same codes, on
+    ordinary rows, fp16 subnormals and zeros, the largest fp16 values and both clamps."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    g = np.random.default_rng(n)
+    base, sigma = W.draw_ssd_output(8, n, seed=n, outlier_frac=0.01)
+    base[1] = (g.integers(0, 0x0400, size=n, dtype=np.uint16) | (g.integers(0, 2, size=n, dtype=np.uint16) << 15)).view(np.float16)
+    base[2] = np.where(g.integers(0, 2, size=n) == 1, 65504.0, -65504.0).astype(np.float16)
+    base[3] = 0
+    s_y = _scale(sigma, k=3.0)
+    for scale in (s_y, 2.0 ** -20):
+        ref = oracle.hadamard_quantize(base, scale)
+        for rows in (2 * cus, 2 * cus + 1):
+            y16 = np.concatenate([base] * (rows // 8 + 1))[:rows]
+            got = _run(gpu_lib, y16, scale)
+            assert all(np.array_equal(got[i], ref[i % 8]) for i in range(rows))
+
+
 def test_unaligned_pointers_and_leading_axes(gpu_lib):
     """A view that starts 2 bytes into an allocation takes the path without 16-byte loads; leading axes flatten."""
     import torch
