@@ -118,9 +118,9 @@ __device__ __forceinline__ u32x4 load_codes(const int8_t *row, int t, int L)
     return v;
 }
 
-// N = 16 states, seqlen >= 16.  grid = (channels / (kThreads / LPC), batch); LPC lanes share a channel (64, 32 or 16), so a
+// A workgroup's kThreads / LPC channels of one sequence, N = 16 states, seqlen >= 16.  LPC lanes share a channel (64, 32 or 16), so a
 // wave holds 64 / LPC channels.  B and C of NS states are staged at a time: 8 with workgroups of 256 threads, whose 34 KB of
-// LDS let four of them share a compute unit, all 16 with 512.  The loop over states stays rolled: the 16 tokens of a lane
+// LDS let four of them share a compute unit, all 16 with 512 (8 in mamba1_scan_halves_kernel).  The loop over states stays rolled: the 16 tokens of a lane
 // already give every instruction 16 independent copies, and unrolling further only costs registers.  B and C are staged as fp32 (converted once per workgroup
 // instead of once per channel): plain fp32 multiplies and multiply-adds of two waves can issue together, the
 // mixed-precision ones that take fp16 operands cannot.  LDS rows are [state][quarter of a lane's tokens][lane], so that a lane's
@@ -134,18 +134,17 @@ __device__ __forceinline__ u32x4 load_codes(const int8_t *row, int t, int L)
 // multiple of 16 took before).  By the counters 36 cycles of a SIMD per 64 elements; the loop's instructions take 23 where all
 // plain ones of two waves issue together, 33 where none do.
 template <int LPC, int kThreads, int NS>
-__global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, const float *A, const float *init, float *fin)
+__device__ __forceinline__ void scan_channels(
+    SsdArgs a, const float *A, const float *init, float *fin, int b, unsigned blk,  // the sequence, which kThreads / LPC of its channels
+    f32x4 *s_B, f32x4 *s_C,  // [state][quarter][lane]
+    float2 *s_AH,            // [channel][state]: A log2(e), the state before the tile
+    float *s_silu)           // SiLU(z_scale * code), by the gate code's byte
 {
     constexpr int N = 16, kTile = LPC * kE, kCh = kThreads / LPC;  // channels of the workgroup
-    // separate arrays, so that the compiler sees that the state's write does not touch the C read behind it
-    __shared__ f32x4 s_B[NS * 4 * LPC], s_C[NS * 4 * LPC];  // [state][quarter][lane]
-    __shared__ float2 s_AH[kCh * N];                      // [channel][state]: A log2(e), the state before the tile
-    __shared__ float s_silu[256];                         // SiLU(z_scale * code), by the gate code's byte
     const int D = a.s.headdim, L = a.s.seqlen;
-    const int b = blockIdx.y;
     const int sub = threadIdx.x & (LPC - 1);  // the lane inside its channel's group
     const int ch = threadIdx.x / LPC;         // the channel inside the workgroup
-    const int d = blockIdx.x * kCh + ch;
+    const int d = blk * kCh + ch;
     const bool own = d < D;                   // lanes without a channel redo the last one and store nothing
     const int dd = own ? d : D - 1;
     const float sC = a.C_scales[0];
@@ -153,7 +152,7 @@ __global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, con
     const float sxB = sx * a.B_scales[0], Dx = (a.D ? a.D[dd] : 0.0f) * sx;
 
     for (int i = threadIdx.x; i < kCh * N; i += kThreads) {
-        const int c = min((int)blockIdx.x * kCh + i / N, D - 1), n = i % N;
+        const int c = min((int)blk * kCh + i / N, D - 1), n = i % N;
         // A = -inf (a state that forgets everything) as the largest number: a token past the end has a step of 0, which must
         // not make 0 times infinity of it
         const float A2 = A[(size_t)c * N + n] * kLog2e;
@@ -233,13 +232,13 @@ __global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, con
                 float h = 0.0f, P = dtsum * ah.x;
 #pragma unroll
                 for (int i = 0; i < kE; ++i) dec[i] = dt[i] * ah.x;
-                // 64 lanes per channel leave 2 waves on a SIMD, too few to cover the LDS reads, and registers to spare: there the
+                // 64 lanes per channel and all 16 states staged leave 2 waves on a SIMD, too few to cover the LDS reads, and registers to spare: there the
                 // operands are read while the exponentials and the lane scan run (1536 channels of one sequence, 4096
                 // tokens 48.7 -> 45.5 us, 700 tokens 13.7 -> 13.0).  With 4 waves that changes nothing (306 / 305 us at 4 x
                 // 4096 tokens of 5120 channels) or spills.
                 f32x4 Bn[4], Cn[4];
                 auto ahead = [&](f32x4 (&v)[4], const f32x4 *from) {
-                    if constexpr (LPC == 64) {
+                    if constexpr (LPC == 64 && NS == 16) {
 #pragma unroll
                         for (int q = 0; q < 4; ++q) v[q] = from[(n * 4 + q) * LPC + sub];
                         __builtin_amdgcn_sched_barrier(0);
@@ -249,7 +248,7 @@ __global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, con
                 exp2_burst(dec, P);  // P becomes the product of the lane's 16 decay factors
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const f32x4 Bv = LPC == 64 ? Bn[q] : s_B[(n * 4 + q) * LPC + sub];
+                    const f32x4 Bv = LPC == 64 && NS == 16 ? Bn[q] : s_B[(n * 4 + q) * LPC + sub];
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const int i = 4 * q + k;
@@ -274,7 +273,7 @@ __global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, con
                 if (sub == LPC - 1) s_AH[ch * N + n0 + n].y = carry;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const f32x4 Cv = LPC == 64 ? Cn[q] : s_C[(n * 4 + q) * LPC + sub];
+                    const f32x4 Cv = LPC == 64 && NS == 16 ? Cn[q] : s_C[(n * 4 + q) * LPC + sub];
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const int i = 4 * q + k;
@@ -309,10 +308,43 @@ __global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, con
     if (fin) {
         __syncthreads();
         for (int i = threadIdx.x; i < kCh * N; i += kThreads) {
-            const int c = blockIdx.x * kCh + i / N;
+            const int c = blk * kCh + i / N;
             if (c < D) fin[((size_t)b * D + c) * N + i % N] = s_AH[i].y;
         }
     }
+}
+
+// grid = (channels / (kThreads / LPC), batch)
+template <int LPC, int kThreads, int NS>
+__global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, const float *A, const float *init, float *fin)
+{
+    // separate arrays, so that the compiler sees that the state's write does not touch the C read behind it
+    __shared__ f32x4 s_B[NS * 4 * LPC], s_C[NS * 4 * LPC];
+    __shared__ float2 s_AH[kThreads / LPC * 16];
+    __shared__ float s_silu[256];
+    scan_channels<LPC, kThreads, NS>(a, A, init, fin, blockIdx.y, blockIdx.x, s_B, s_C, s_AH, s_silu);
+}
+
+// The same for groups of 16 channels of all sequences: the first `whole` as workgroups with 32 lanes per channel, each of the others
+// as two workgroups with 64 lanes per channel, 8 channels each, 8 states staged at a time, which is the same LDS.  A launch whose
+// last round leaves compute units half empty is as slow there as one wave's instruction stream (80 us for 16 channels and 4096
+// tokens on a unit, 117 for 32 channels on it); half the channels on twice the waves take 65 us, 41 where a unit has one such half
+// (a wave's tile spans 1024 tokens of one channel instead of 512 of two; B and C are converted for 8 channels instead of 16,
+// which costs a full chip 5 to 10 %).  Bound as above.  5120 channels of two sequences, 4096 tokens 199 -> 162 us, 1003 tokens 55 -> 45;
+// 1536 channels of two 86 -> 66 and 25.6 -> 22.1.
+__global__ __launch_bounds__(512, 4) void mamba1_scan_halves_kernel(SsdArgs a, const float *A, const float *init,
+                                                                   float *fin, int whole)
+{
+    __shared__ f32x4 s_B[16 * 4 * 32], s_C[16 * 4 * 32];  // or of 8 states and 64 lanes
+    __shared__ float2 s_AH[16 * 16];
+    __shared__ float s_silu[256];
+    const int groups = (a.s.headdim + 15) / 16;  // of a sequence
+    const int w = blockIdx.x, g = w < whole ? w : whole + (w - whole) / 2;
+    const int b = g / groups, c = g - b * groups, half = (w - whole) & 1;
+    if (w < whole)
+        scan_channels<32, 512, 16>(a, A, init, fin, b, c, s_B, s_C, s_AH, s_silu);
+    else if (16 * c + 8 * half < a.s.headdim)
+        scan_channels<64, 512, 8>(a, A, init, fin, b, 2 * c + half, s_B, s_C, s_AH, s_silu);
 }
 
 // Any d_state <= 64 and any seqlen: one thread per (sequence, channel), token by token.
@@ -453,6 +485,21 @@ hipError_t launch_mamba1_scan(const SsdArgs &a, const float *A, const float *ini
         // eighth does not pay.
         auto cost = [&](int ch, int tile) { return per_cu(ch) * ((a.s.seqlen + (int64_t)tile - 1) / tile * tile); };
         const int64_t c16 = cost(16, 32 * kE), c8 = cost(8, 32 * kE), c32 = cost(32, 16 * kE);
+        // Halves of groups of 16 channels behind the rounds of two groups per compute unit, where a unit has at most one group of
+        // the rest.  Costs in channels of a full unit times tokens: the rest takes 22 (one group on a unit) as whole groups, 18 as
+        // halves, 13 where a unit has one half; but a half's tiles are twice as long, so that it walks more padded tokens (9 : 10
+        // and 6 : 10 per tile of 1024 against 512; 1500 tokens of 192 groups 36.1 / 36.5 us, of 512 + 128 groups 77 -> 68).  Behind
+        // two rounds and more (1280 groups 308 / 309 us) a group per unit starts as units come free and gains nothing any more; at
+        // most a half per unit does until about eight rounds (2112 groups 409 -> 380 us, 4160 groups 979 -> 968).
+        const int64_t groups = (int64_t)a.s.batch * ((D + 15) / 16), whole = groups / (2 * cus) * (2 * cus), rest = groups - whole;
+        const int64_t tiles = (a.s.seqlen + 32 * kE - 1) / (32 * kE), long_tiles = (tiles + 1) / 2;
+        const bool few = 2 * rest <= cus;
+        if (rest > 0 && rest <= cus && whole <= (few ? 16 : 2) * cus && (few ? 6 : 9) * long_tiles <= 5 * tiles &&
+            16 * (whole / cus) * tiles * 32 * kE + (few ? 13 : 18) * long_tiles * 64 * kE <= c32) {
+            hipLaunchKernelGGL(mamba1_scan_halves_kernel, dim3((unsigned)(whole + 2 * rest)), dim3(512), 0, stream, a, A,
+                               init, fin, (int)whole);
+            return hipGetLastError();
+        }
         if (9 * std::min(c8, c32) <= 8 * c16) {
             if (c8 <= c32) return launch_scan<32, 256, 8>(a, A, init, fin, stream);
             return launch_scan<16, 512, 16>(a, A, init, fin, stream);

@@ -289,3 +289,19 @@ def test_states_that_forget_everything_at_a_ragged_end(gpu_lib, L):
     y, fin = _run(gpu_lib, sc, p, b, D, N, L)
     assert np.abs(y - yref).max() <= Y_TOL * np.abs(yref).max()
     assert np.abs(fin - sref).max() <= S_TOL * np.abs(sref).max()
+
+
+@pytest.mark.parametrize("b,D,L", [(1, 2085, 520),    # no whole group, more than half a unit's worth of halves, the last one empty
+                                   (1, 4096, 1024),   # ... as many groups as compute units
+                                   (3, 2736, 513),    # two groups per unit and one: two halves behind them
+                                   (3, 4090, 900),    # ... and a group per unit
+                                   (1, 8192, 600)])   # two groups per unit, no halves
+@pytest.mark.parametrize("sides", [False, True])
+def test_groups_of_channels_in_halves(gpu_lib, b, D, L, sides):
+    """Channels in groups of 16, those behind the last full round as halves of 8 channels on 64 lanes each, at the edges of that
+    rule on 256 compute units, at the same bars."""
+    test_scan_with_side_inputs(gpu_lib, b, D, 16, L, 0, sides, sides)
+
+
+def test_infinite_and_zero_states_in_halves(gpu_lib):
+    test_infinite_and_zero_states(gpu_lib, 2000, 600)
