@@ -141,6 +141,7 @@ __device__ __forceinline__ void scan_channels(
     float *s_silu)           // SiLU(z_scale * code), by the gate code's byte
 {
     constexpr int N = 16, kTile = LPC * kE, kCh = kThreads / LPC;  // channels of the workgroup
+    constexpr bool kAhead = (LPC == 64 && NS == 16) || kThreads == 768;
     const int D = a.s.headdim, L = a.s.seqlen;
     const int sub = threadIdx.x & (LPC - 1);  // the lane inside its channel's group
     const int ch = threadIdx.x / LPC;         // the channel inside the workgroup
@@ -232,13 +233,14 @@ __device__ __forceinline__ void scan_channels(
                 float h = 0.0f, P = dtsum * ah.x;
 #pragma unroll
                 for (int i = 0; i < kE; ++i) dec[i] = dt[i] * ah.x;
-                // 64 lanes per channel and all 16 states staged leave 2 waves on a SIMD, too few to cover the LDS reads, and registers to spare: there the
-                // operands are read while the exponentials and the lane scan run (1536 channels of one sequence, 4096
-                // tokens 48.7 -> 45.5 us, 700 tokens 13.7 -> 13.0).  With 4 waves that changes nothing (306 / 305 us at 4 x
-                // 4096 tokens of 5120 channels) or spills.
+                // 64 lanes per channel with all 16 states staged leave 2 waves on a SIMD, 24 channels of 32 lanes 3: too few to
+                // cover the LDS reads, and registers to spare.  There the operands are read while the exponentials and the lane scan
+                // run (1536 channels of one sequence, 4096 tokens 48.7 -> 45.5 us, 700 tokens 13.7 -> 13.0; 20 channels of 32 lanes
+                // on a unit 99.3 -> 95.1).  With 4 waves that changes nothing (306 / 305 us at 4 x 4096 tokens of 5120
+                // channels) or spills.
                 f32x4 Bn[4], Cn[4];
                 auto ahead = [&](f32x4 (&v)[4], const f32x4 *from) {
-                    if constexpr (LPC == 64 && NS == 16) {
+                    if constexpr (kAhead) {
 #pragma unroll
                         for (int q = 0; q < 4; ++q) v[q] = from[(n * 4 + q) * LPC + sub];
                         __builtin_amdgcn_sched_barrier(0);
@@ -248,7 +250,7 @@ __device__ __forceinline__ void scan_channels(
                 exp2_burst(dec, P);  // P becomes the product of the lane's 16 decay factors
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const f32x4 Bv = LPC == 64 && NS == 16 ? Bn[q] : s_B[(n * 4 + q) * LPC + sub];
+                    const f32x4 Bv = kAhead ? Bn[q] : s_B[(n * 4 + q) * LPC + sub];
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const int i = 4 * q + k;
@@ -273,7 +275,7 @@ __device__ __forceinline__ void scan_channels(
                 if (sub == LPC - 1) s_AH[ch * N + n0 + n].y = carry;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const f32x4 Cv = LPC == 64 && NS == 16 ? Cn[q] : s_C[(n * 4 + q) * LPC + sub];
+                    const f32x4 Cv = kAhead ? Cn[q] : s_C[(n * 4 + q) * LPC + sub];
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const int i = 4 * q + k;
@@ -316,7 +318,7 @@ __device__ __forceinline__ void scan_channels(
 
 // grid = (channels / (kThreads / LPC), batch)
 template <int LPC, int kThreads, int NS>
-__global__ __launch_bounds__(kThreads, 4) void mamba1_scan_kernel(SsdArgs a, const float *A, const float *init, float *fin)
+__global__ __launch_bounds__(kThreads, kThreads == 768 ? 3 : 4) void mamba1_scan_kernel(SsdArgs a, const float *A, const float *init, float *fin)
 {
     // separate arrays, so that the compiler sees that the state's write does not touch the C read behind it
     __shared__ f32x4 s_B[NS * 4 * LPC], s_C[NS * 4 * LPC];
@@ -494,12 +496,20 @@ hipError_t launch_mamba1_scan(const SsdArgs &a, const float *A, const float *ini
         const int64_t groups = (int64_t)a.s.batch * ((D + 15) / 16), whole = groups / (2 * cus) * (2 * cus), rest = groups - whole;
         const int64_t tiles = (a.s.seqlen + 32 * kE - 1) / (32 * kE), long_tiles = (tiles + 1) / 2;
         const bool few = 2 * rest <= cus;
-        if (rest > 0 && rest <= cus && whole <= (few ? 16 : 2) * cus && (few ? 6 : 9) * long_tiles <= 5 * tiles &&
-            16 * (whole / cus) * tiles * 32 * kE + (few ? 13 : 18) * long_tiles * 64 * kE <= c32) {
+        // groups of 8 channels in workgroups of 256 threads, in the same measure: four on a unit 32, three 29, two 24, one 22
+        const int64_t eights = per_cu(8) / 8, alone[4] = {0, 22, 24, 29}, tokens = tiles * 32 * kE;
+        const int64_t halves = 16 * (whole / cus) * tokens + (few ? 13 : 18) * long_tiles * 64 * kE;
+        if (rest > 0 && rest <= cus && whole <= (few ? 16 : 2) * cus && (few ? 6 : 9) * long_tiles <= 5 * tiles && halves <= c32 &&
+            halves <= (eights / 4 * 32 + alone[eights % 4]) * tokens) {
             hipLaunchKernelGGL(mamba1_scan_halves_kernel, dim3((unsigned)(whole + 2 * rest)), dim3(512), 0, stream, a, A,
                                init, fin, (int)whole);
             return hipGetLastError();
         }
+        // 24 channels in one workgroup per compute unit where they hold all channels and groups of 16 do not: 4 x 1536 channels, 4096
+        // tokens 110.6 -> 104.1 us, 1003 tokens with side inputs 35.5 -> 31.5; 5120 channels 106.9 -> 97.3, 36.3 -> 33.0 (those as
+        // three and two workgroups of 8 channels per unit, below)
+        if (groups > cus && eights > 2 && (int64_t)a.s.batch * ((D + 23) / 24) <= cus)
+            return launch_scan<32, 768, 16>(a, A, init, fin, stream);
         if (9 * std::min(c8, c32) <= 8 * c16) {
             if (c8 <= c32) return launch_scan<32, 256, 8>(a, A, init, fin, stream);
             return launch_scan<16, 512, 16>(a, A, init, fin, stream);

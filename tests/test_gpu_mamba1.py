@@ -63,8 +63,8 @@ def test_wave_scan_kernel_small_shapes(gpu_lib):
                                  (20, 513), (9, 1023), (9, 1025), (2060, 1037), (8177, 700)])
 def test_sequence_lengths_around_lanes_and_tiles(gpu_lib, D, L):
     """Rows that start at any byte and end inside a lane's 16 tokens, on every tile width: one token less and more than a
-    lane (16), and than a tile of 16, 32 and 64 lanes; 2060 channels give the 32-lane kernel with the smaller
-    workgroups several tiles, 8177 of 700 tokens the 16-lane kernel."""
+    lane (16), and than a tile of 16, 32 and 64 lanes; 2060 channels give the 32-lane kernel with workgroups of 24
+    channels several tiles, 8177 of 700 tokens the 16-lane kernel."""
     _check(gpu_lib, b=2, D=D, N=16, L=L, seed=L, with_init=L % 2 == 1, with_D=L % 3 != 0)
 
 
@@ -162,8 +162,8 @@ def _dt_of_codes(g):
 @pytest.mark.parametrize("b,D,N,L,flags", [(2, 203, 16, 2608, 0),    # 64 lanes per channel, several tiles
                                            (2, 70, 16, 45, 0),       # 16 lanes, one tile
                                            (2, 8177, 16, 700, 0),    # 16 lanes, several tiles
-                                           (2, 2060, 16, 1037, 0),   # 32 lanes, 8 states at a time
-                                           (2, 8198, 16, 1029, 0),   # 32 lanes, all 16 states
+                                           (2, 2060, 16, 1037, 0),   # 32 lanes, 24 channels
+                                           (2, 8198, 16, 1029, 0),   # 32 lanes, 16 channels; 64 lanes behind
                                            (1, 33, 24, 64, 0),       # any shape
                                            (1, 130, 16, 256, 1)])    # ... forced
 def test_scan_with_side_inputs(gpu_lib, b, D, N, L, flags, use_z, use_dt):
@@ -295,11 +295,14 @@ def test_states_that_forget_everything_at_a_ragged_end(gpu_lib, L):
                                    (1, 4096, 1024),   # ... as many groups as compute units
                                    (3, 2736, 513),    # two groups per unit and one: two halves behind them
                                    (3, 4090, 900),    # ... and a group per unit
-                                   (1, 8192, 600)])   # two groups per unit, no halves
+                                   (1, 8192, 600),    # two groups per unit, no halves
+                                   (3, 1537, 600),    # 24 channels per workgroup, the last with one
+                                   (4, 1536, 513),    # ... as many workgroups as compute units
+                                   (2, 6400, 900)])   # 8 channels per workgroup, 8 states at a time
 @pytest.mark.parametrize("sides", [False, True])
-def test_groups_of_channels_in_halves(gpu_lib, b, D, L, sides):
-    """Channels in groups of 16, those behind the last full round as halves of 8 channels on 64 lanes each, at the edges of that
-    rule on 256 compute units, at the same bars."""
+def test_how_channels_are_shared_out(gpu_lib, b, D, L, sides):
+    """Groups of 16 channels, those behind the last full round as halves of 8 channels on 64 lanes each, and workgroups of 24 and
+    of 8 channels, at the edges of their rules on 256 compute units, at the same bars."""
     test_scan_with_side_inputs(gpu_lib, b, D, 16, L, 0, sides, sides)
 
 
