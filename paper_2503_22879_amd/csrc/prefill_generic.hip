@@ -20,8 +20,10 @@ constexpr int kE = 16;             // tokens per lane
 constexpr int kLanes = 16;         // lanes per row
 constexpr int kTile = kE * kLanes; // tokens per tile
 constexpr int kNG = 16;            // states staged at a time
-constexpr int kBPitch = 4 * kLanes + 16; // floats from one (state, quarter) of the staged B or C to the next: the pad
-                                         // puts the writes of 64 consecutive tokens on as many banks
+// Floats from one (state, quarter) of the staged B or C to the next.  A pad of 16 puts the writes of 64 consecutive tokens on as many
+// banks: where four lane groups share a row, a unit has at most two workgroups whatever they take.  With one lane group three share
+// a unit, for which 16 more KB between them would leave no room (see launch_rows).
+constexpr int b_pitch(int SG) { return 4 * kLanes + (SG == 4 ? 16 : 4); }
 constexpr int kXPitch = kTile + 16;      // bytes from one row's codes to the next
 constexpr int kYPitch = kTile + 2;       // halves from one row's outputs to the next
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -37,9 +39,9 @@ __device__ __forceinline__ float row_earlier(float edge, float v)
                                                                  0x110 + STEP, 0xf, 0xf, false));
 }
 
-constexpr size_t kernel_lds_bytes(int N, int rows)
+constexpr size_t kernel_lds_bytes(int N, int rows, int SG)
 {
-    return sizeof(float) * (2 * kNG * 4 * kBPitch + 2 * kTile + rows * (size_t)N) + rows * kXPitch + 2 * rows * kYPitch;
+    return sizeof(float) * (2 * kNG * 4 * b_pitch(SG) + 2 * kTile + rows * (size_t)N) + rows * kXPitch + 2 * rows * kYPitch;
 }
 
 // WIDE: d_state is a multiple of 4 and B and C are 4-byte aligned (their codes are read 4 at a time).
@@ -50,10 +52,11 @@ constexpr size_t kernel_lds_bytes(int N, int rows)
 // a lane then has the registers to take all its states of a group side by side (four chains of multiply-adds instead of one), and
 // of its 10000 cycles 2400 go by until the arguments are there, 2000 until the tile's loads are, 1200 in the staging and 2900
 // in the states.
-template <bool WIDE, int SG, int ROWS>
-__global__ __launch_bounds__(ROWS * kLanes * SG) void prefill_generic_kernel(SsdArgs a, int x_vec, int y_vec)
+// WAVES: of a SIMD, for which registers are kept free (1: the compiler takes what it likes).
+template <bool WIDE, int SG, int ROWS, int WAVES>
+__global__ __launch_bounds__(ROWS * kLanes * SG, WAVES) void prefill_generic_kernel(SsdArgs a, int x_vec, int y_vec)
 {
-    constexpr int kRows = ROWS, kThreads = ROWS * kLanes * SG;
+    constexpr int kRows = ROWS, kThreads = ROWS * kLanes * SG, kBPitch = b_pitch(SG);
     static_assert(kThreads >= kTile, "a thread for every (row, lane group, lane), and for every token of the tile");
     typedef uint32_t xcodes __attribute__((ext_vector_type(ROWS / 4)));
     extern __shared__ f32x4 lds4[];
@@ -298,18 +301,20 @@ __global__ __launch_bounds__(ROWS * kLanes * SG) void prefill_generic_kernel(Ssd
     }
 }
 
-template <bool WIDE, int SG, int ROWS>
+template <bool WIDE, int SG, int ROWS, int WAVES>
 hipError_t launch(const SsdArgs &a, hipStream_t stream)
 {
-    const hipError_t e = allow_full_lds<prefill_generic_kernel<WIDE, SG, ROWS>>();
+    const hipError_t e = allow_full_lds<prefill_generic_kernel<WIDE, SG, ROWS, WAVES>>();
     if (e != hipSuccess) return e;
     auto aligned = [](const void *p, size_t n) { return reinterpret_cast<uintptr_t>(p) % n == 0; };
     const int whole = a.s.headdim % ROWS == 0;  // every row block is complete and starts at a multiple of ROWS codes
     const dim3 grid((unsigned)(a.s.batch * a.s.nheads), (unsigned)((a.s.headdim + ROWS - 1) / ROWS));
-    hipLaunchKernelGGL((prefill_generic_kernel<WIDE, SG, ROWS>), grid, dim3(ROWS * kLanes * SG), kernel_lds_bytes(a.s.d_state, ROWS),
-                       stream, a, whole && aligned(a.x, ROWS), whole && aligned(a.y, ROWS));
+    hipLaunchKernelGGL((prefill_generic_kernel<WIDE, SG, ROWS, WAVES>), grid, dim3(ROWS * kLanes * SG),
+                       kernel_lds_bytes(a.s.d_state, ROWS, SG), stream, a, whole && aligned(a.x, ROWS), whole && aligned(a.y, ROWS));
     return hipGetLastError();
 }
+
+static_assert(3 * kernel_lds_bytes(80, 16, 1) <= kLdsPerCu, "three workgroups of 16 rows per compute unit");
 
 template <bool WIDE>
 hipError_t launch_rows(const SsdArgs &a, hipStream_t stream)
@@ -318,11 +323,15 @@ hipError_t launch_rows(const SsdArgs &a, hipStream_t stream)
     // two units: blocks of 4 rows (4 waves), of which a unit holds two with the registers they take (8 heads of 64 channels, 16
     // states, 256 tokens, 16 / 4 rows: batch 1 7.8 / 5.9 us, 4 8.3 / 7.4, 5 8.4 / 11.4; 24 heads, 64 states, 1000 tokens 53.9 / 45.4).
     // Codes that are read one at a time cost the four-fold staging more than the waves gain (10 states, 200 tokens 7.7 / 9.5).
+    // Above two per unit a third one has to fit, in 168 registers and 51 KB (16 states; 8 heads of 64 channels, 256 tokens, with 174
+    // registers and 57 KB / so: batch 17 17.8 / 13.2 us, 64 42.1 / 36.3; 17 of 64 states 51.3 / 35.6).  Up to there 174 are the better
+    // (batch 16 11.4 / 11.8).
     const int64_t blocks = (int64_t)a.s.batch * a.s.nheads * ((a.s.headdim + 15) / 16);
-    if (blocks > compute_units()) return launch<WIDE, 1, 16>(a, stream);
+    if (blocks > 2 * (int64_t)compute_units()) return launch<WIDE, 1, 16, 3>(a, stream);
+    if (blocks > compute_units()) return launch<WIDE, 1, 16, WIDE ? 1 : 3>(a, stream);
     if constexpr (WIDE)
-        if (2 * blocks <= compute_units()) return launch<WIDE, 4, 4>(a, stream);
-    return launch<WIDE, 4, 16>(a, stream);
+        if (2 * blocks <= compute_units()) return launch<WIDE, 4, 4, 1>(a, stream);
+    return launch<WIDE, 4, 16, 1>(a, stream);
 }
 
 }  // namespace
@@ -332,7 +341,7 @@ hipError_t launch_rows(const SsdArgs &a, hipStream_t stream)
 bool prefill_generic_supports(const quamba_ssd_shape_t &s)
 {
     const size_t P = (size_t)s.headdim, N = (size_t)s.d_state;
-    return sizeof(float) * (P * N + 33 * P + 32 * N + 16) <= kLdsPerCu && kernel_lds_bytes(s.d_state, 16) <= kLdsPerCu;
+    return sizeof(float) * (P * N + 33 * P + 32 * N + 16) <= kLdsPerCu && kernel_lds_bytes(s.d_state, 16, 4) <= kLdsPerCu;
 }
 
 hipError_t launch_prefill_generic(const SsdArgs &a, hipStream_t stream)

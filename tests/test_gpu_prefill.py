@@ -487,10 +487,12 @@ def test_exact_integer_case(gpu_lib):
 
 @pytest.mark.parametrize("b,L,H,P,N,G", [(1, 256, 8, 64, 16, 1), (2, 15, 6, 20, 24, 2), (1, 257, 4, 17, 128, 2),
                                          (2, 300, 2, 7, 3, 1), (1, 1, 2, 5, 1, 1), (1, 700, 4, 33, 17, 2),
-                                         (3, 255, 3, 16, 4, 3), (1, 40, 2, 5, 1100, 1), (20, 33, 4, 70, 20, 2)])
+                                         (3, 255, 3, 16, 4, 3), (1, 40, 2, 5, 1100, 1), (20, 33, 4, 70, 20, 2),
+                                         (16, 33, 8, 64, 16, 1), (17, 257, 8, 61, 20, 2), (17, 33, 8, 61, 5, 1)])
 def test_generic_kernel_around_lanes_tiles_and_row_blocks(gpu_lib, b, L, H, P, N, G):
     """Lengths around a lane's 16 tokens and a tile's 256, channels around a block of 16 rows, states around a staged
-    group of 16 and in fours or not, few row blocks (four lane groups per row) and many (one): 20 x 4 heads x 5 blocks."""
+    group of 16 and in fours or not, few row blocks (four lane groups per row) and many (one): 20 x 4 heads x 5 blocks,
+    two blocks per compute unit, and more."""
     s = W.LayerShape("g", b, L, H, P, N, G, 64, min(2, H // G), min(2, P))
     sc, prob, _ = make_problem(s, seed=L, calib_tokens=128)
     init = np.random.default_rng(L).normal(0, 0.1, size=(b, H, P, N)).astype(np.float32)
