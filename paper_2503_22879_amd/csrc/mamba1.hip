@@ -133,7 +133,7 @@ __device__ __forceinline__ u32x4 load_codes(const int8_t *row, int t, int L)
 // codes 32 to 34 (36.5 with workgroups of 512 threads, 3000 with one thread per channel, which is what a length that is no
 // multiple of 16 took before).  By the counters 36 cycles of a SIMD per 64 elements; the loop's instructions take 23 where all
 // plain ones of two waves issue together, 33 where none do.
-template <int LPC, int kThreads, int NS>
+template <int LPC, int kThreads, int NS, bool HALVES = false>
 __device__ __forceinline__ void scan_channels(
     const SsdArgs &a, const float *A, const float *init, float *fin, int b, unsigned blk,  // the sequence, which kThreads / LPC of its channels
     f32x4 *s_B, f32x4 *s_C,  // [state][quarter][lane]
@@ -179,6 +179,10 @@ __device__ __forceinline__ void scan_channels(
         xq = load_codes(a.x + row, t, L);
         if (a.dt_q) {
             raw[0] = load_codes(a.dt_q + row, t, L);
+            // What a branch leaves undefined lives on from the tile before, through the loop over states.  (The forms that have these 12
+            // registers to spare, and <32, 256, 8>, which keeps 2 others in scratch memory from tile to tile instead, are 0 to 2 % faster
+            // as the compiler shares registers out then.)
+            if (HALVES) raw[1] = raw[2] = raw[3] = (u32x4)(0u);
         } else if (t + kE <= L) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)  // plain, not non-temporal: four loads share a sector
@@ -373,9 +377,9 @@ __global__ __launch_bounds__(512, 4) void mamba1_scan_halves_kernel(SsdArgs a, c
     const int w = blockIdx.x, g = w < whole ? w : whole + (w - whole) / 2;
     const int b = g / groups, c = g - b * groups, half = (w - whole) & 1;
     if (w < whole)
-        scan_channels<32, 512, 16>(a, A, init, fin, b, c, s_B, s_C, s_AH, s_silu);
+        scan_channels<32, 512, 16, true>(a, A, init, fin, b, c, s_B, s_C, s_AH, s_silu);
     else if (16 * c + 8 * half < a.s.headdim)
-        scan_channels<64, 512, 8>(a, A, init, fin, b, 2 * c + half, s_B, s_C, s_AH, s_silu);
+        scan_channels<64, 512, 8, true>(a, A, init, fin, b, 2 * c + half, s_B, s_C, s_AH, s_silu);
 }
 
 // Any d_state <= 64 and any seqlen: one thread per (sequence, channel), token by token.

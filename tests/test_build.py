@@ -1,7 +1,9 @@
 """What the build asks of the machine it runs on."""
 import importlib.util
 import os
+import re
 import shutil
+import subprocess
 import sys
 
 import pytest
@@ -68,3 +70,14 @@ def test_the_extension_is_built_again_for_another_torch(monkeypatch, tmp_path):
     for _ in range(2):
         build._build_bind(False)
     assert len(ran) == 2
+
+
+def test_the_mamba1_scan_of_uneven_launches_keeps_everything_in_registers(tmp_path):
+    """By the compiler's report: the kernel whose waves have 128 registers each and two bodies to fit into them."""
+    src = os.path.join(build.CSRC, "mamba1.hip")
+    cmd = [build.HIPCC, *build.FLAGS, "-x", "hip", "--cuda-device-only", "-c", src, "-o", str(tmp_path / "o"),
+           "-Rpass-analysis=kernel-resource-usage"]
+    report = subprocess.run(cmd, check=True, capture_output=True, text=True).stderr
+    scratch = dict(re.findall(r"Function Name: (\S+).*?ScratchSize \[bytes/lane\]: (\d+)", report, re.S))
+    found = [int(v) for k, v in scratch.items() if "mamba1_scan_halves_kernel" in k]
+    assert found == [0], scratch
