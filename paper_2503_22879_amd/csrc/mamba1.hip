@@ -31,6 +31,11 @@ __device__ __forceinline__ float dpp_fetch(float old, float v)
                                                                  CTRL, ROW_MASK, 0xf, false));
 }
 
+__device__ __forceinline__ float lane_value(float v, int lane)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+
 // Inclusive scan of (P, h) pairs over groups of LPC lanes (16, 32 or 64).  One step applies the pair fetched from an earlier lane first and
 // the lane's own after it: (Ps, hs) then (P, h) -> (Ps P, P hs + h), as two instructions whose first source is the
 // shifted lane: h += hs * P, then P *= Ps.  Lanes without a source lane (and rows the mask leaves out) are not
@@ -142,6 +147,11 @@ __device__ __forceinline__ void scan_channels(
 {
     constexpr int N = 16, kTile = LPC * kE, kCh = kThreads / LPC;  // channels of the workgroup
     constexpr bool kAlone = LPC == 64 && NS == 16, kAhead = kAlone || kThreads == 768;
+    // Lanes of a scan.  In mamba1_scan_halves_kernel the 64 lanes of a channel take their tile as two of 32 lanes, one after the other,
+    // and groups of 32 lanes decide for themselves where a number is not finite: the same operations, bit for bit, in both parts of
+    // its launch, so that equal sequences of a call have equal results.
+    constexpr bool kTwo = HALVES && LPC == 64;
+    constexpr int kScan = kTwo ? 32 : LPC;
     const int D = a.s.headdim, L = a.s.seqlen;
     const int sub = threadIdx.x & (LPC - 1);  // the lane inside its channel's group
     const int ch = threadIdx.x / LPC;         // the channel inside the workgroup
@@ -239,6 +249,7 @@ __device__ __forceinline__ void scan_channels(
 #pragma unroll
             for (int i = 0; i < kE; ++i) dt[i] = t + i < L ? dt[i] : 0.0f;
         }
+        const int last = kTwo && t0 + kScan * kE >= L ? kScan - 1 : LPC - 1;  // the lane that ends the tile
         float u[kE], y[kE];
         float dtsum = 0.0f;
 #pragma unroll
@@ -292,20 +303,41 @@ __device__ __forceinline__ void scan_channels(
                     }
                 }
                 ahead(Cn, s_C);
-                wave_scan<LPC>(P, h);
+                wave_scan<kScan>(P, h);
                 // the state behind this lane's tokens, the pairs up to it applied to the carried state, is the state in
                 // front of the next lane's; behind the last lane's it is the state after the tile
-                const float end = fmaf(P, ah.y, h);
+                float end = fmaf(P, ah.y, h), from = ah.y;
+                if (kTwo) {
+                    const float first_end = lane_value(end, kScan - 1);  // (in all lanes' code: the others' `end` has to be there)
+                    from = sub < kScan ? ah.y : first_end;
+                    end = fmaf(P, from, h);
+                }
                 float hh = dpp_fetch<0x138, 0xf>(ah.y, end);  // wave_shr:1
                 if (LPC < 64 && sub == 0) hh = ah.y;
                 float carry = end;
                 if (!scan_is_finite(end)) {
-                    hh = walk_lanes<LPC>(ah.y, dec, in);
-                    carry = hh;
+                    const bool walked = !HALVES || !group_is_finite<kScan>(end);
+                    const float front = walk_lanes<kScan>(ah.y, dec, in);
+                    float behind = front;
 #pragma unroll
-                    for (int i = 0; i < kE; ++i) carry = fmaf(dec[i], carry, in[i]);
+                    for (int i = 0; i < kE; ++i) behind = fmaf(dec[i], behind, in[i]);
+                    hh = walked ? front : hh;
+                    carry = walked ? behind : carry;
+                    if (kTwo) {  // the second tile of 32 lanes goes on from where the first one really ends
+                        from = lane_value(carry, kScan - 1);
+                        end = fmaf(P, from, h);
+                        const bool walk_on = sub >= kScan && !group_is_finite<kScan>(end);
+                        const float before = dpp_fetch<0x138, 0xf>(from, end), on = walk_lanes<kScan>(from, dec, in);
+                        behind = on;
+#pragma unroll
+                        for (int i = 0; i < kE; ++i) behind = fmaf(dec[i], behind, in[i]);
+                        if (sub >= kScan) {
+                            hh = walk_on ? on : sub == kScan ? from : before;
+                            carry = walk_on ? behind : end;
+                        }
+                    }
                 }
-                if (sub == LPC - 1) s_AH[ch * N + n0 + n].y = carry;
+                if (sub == last) s_AH[ch * N + n0 + n].y = carry;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const f32x4 Cv = kAhead ? Cn[q] : s_C[(n * 4 + q) * LPC + sub];

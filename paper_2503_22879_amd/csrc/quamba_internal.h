@@ -263,6 +263,14 @@ __device__ __forceinline__ bool scan_is_finite(float h)
     return __builtin_expect(__builtin_amdgcn_ballot_w64(!(__builtin_fabsf(h) < __builtin_inff())) == 0, 1);
 }
 
+// The same for the lane's group of LANES lanes alone.
+template <int LANES>
+__device__ __forceinline__ bool group_is_finite(float h)
+{
+    const uint64_t wave = __builtin_amdgcn_ballot_w64(!(__builtin_fabsf(h) < __builtin_inff()));
+    return LANES == 64 ? wave == 0 : (wave >> (__lane_id() & ~(LANES - 1)) & ((1ull << (LANES & 63)) - 1)) == 0;
+}
+
 // The state in front of each lane's tokens, the group's lanes taking their tokens one after the other from `carried`, the
 // state in front of the first.
 template <int LANES, int E>

@@ -306,5 +306,34 @@ def test_how_channels_are_shared_out(gpu_lib, b, D, L, sides):
     test_scan_with_side_inputs(gpu_lib, b, D, 16, L, 0, sides, sides)
 
 
+@pytest.mark.parametrize("b,D,L", [(2, 5120, 1003), (2, 5120, 4096), (3, 5120, 600), (6, 1536, 1003), (6, 1536, 2561), (3, 4099, 1537),
+                                   (2, 1536, 4096), (2, 6400, 1003), (3, 1537, 700)])
+@pytest.mark.parametrize("infinite", [False, True])
+def test_equal_sequences_of_one_call_have_equal_results(gpu_lib, b, D, L, infinite):
+    """Sequences with the same inputs have the same outputs and final states, bit for bit, also where a launch takes some groups of
+    channels on 32 lanes each and the others on 64: with small steps, whose states carry far over the ends of the tiles, and with
+    infinite initial states in some channels, which leave their neighbours' results as they are."""
+    import torch
+    q = gpu_lib
+    g = torch.Generator(device="cuda").manual_seed(D + L)
+    codes = lambda *s: torch.randint(-128, 128, s, generator=g, device="cuda", dtype=torch.int8)
+    rand = lambda *s: torch.rand(s, generator=g, device="cuda")
+    sc, _ = make_mamba1_problem(1, D, 16, 16, seed=3)
+    x, B, C, dt, init = codes(1, D, L), codes(1, 16, L), codes(1, 16, L), 0.006 * rand(1, D, L), rand(1, D, 16) - 0.5
+    if infinite:
+        init[0, ::37, 5] = float("inf")
+        init[0, 5::74, 11] = -float("inf")
+    x, B, C, dt, init = (v.expand(b, *v.shape[1:]).contiguous() for v in (x, B, C, dt, init))
+    A, Dk = -0.5 - 1.5 * rand(D, 16), rand(D) - 0.5
+    y = torch.empty((b, D, L), dtype=torch.float16, device="cuda")
+    fin = torch.empty((b, D, 16), device="cuda")
+    q.quamba_mamba1_scan(_shape(q, b, D, 16, L, 4), q.DeviceScales(host_scales(q, sc)), x, B, C, dt, A, Dk, y, init_state=init,
+                         final_state=fin)
+    assert infinite or (torch.isfinite(y).all() and torch.isfinite(fin).all())
+    y, fin = y.view(torch.int16), fin.view(torch.int32)
+    for i in range(1, b):
+        assert torch.equal(y[i], y[0]) and torch.equal(fin[i], fin[0]), i
+
+
 def test_infinite_and_zero_states_in_halves(gpu_lib):
     test_infinite_and_zero_states(gpu_lib, 2000, 600)
