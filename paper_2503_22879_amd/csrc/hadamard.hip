@@ -304,8 +304,9 @@ __global__ __launch_bounds__(256) void hadamard_quantize_mixed_kernel(const uint
 // plainly and gathers the codes' bytes with permutes (v_cvt_f32_f16, v_perm_b32: more instructions than v_fma_mix_f32 and sub-dword
 // adds, which calls of few rows keep for their shorter chain), and the first exchange turns its 16-byte pieces instead of padding
 // rows, so that a row takes 20 KB of LDS and a unit holds 8 of order 5120 instead of 7.  16384 rows of 5120 values 70.0 -> 64.3 us
-// (3.9 TB/s), 3000 17.1 -> 15.6, 1600 11.3 -> 9.8; of 2560 42.7 -> 37.8, of 1536 22.3 -> 21.5, of 3072 38.2 -> 36.7.  One position per
-// thread in phase C instead of two: 69.9 -> 66.4 before that.
+// (3.9 TB/s), 3000 17.1 -> 15.6, 1600 11.3 -> 9.8; of 2560 42.7 -> 37.8, of 1536 22.3 -> 21.5, of 3072 38.2 -> 36.7.  By the counters a
+// SIMD takes 3.0 cycles per vector instruction at 35.8 a value, 4.1 at 32.3 before.  One position per thread in phase C instead of
+// two: 69.9 -> 66.4 before that.
 // Plain stores: non-temporal ones take up to 13 % off the transform alone and put more on the reader of the codes (with an int8
 // product of 2560 columns behind, plain / non-temporal: 2867 rows of 5120 79.3 / 83.5 us, 13653 of 1536 95 / 105, 8192 of 2560
 // 97 / 108, 3413 of 6144 91 / 96; 1000 to 1700 rows of 5120 46.8 / 45.6, 63.2 / 61.6).
@@ -315,6 +316,9 @@ __global__ __launch_bounds__(256) void hadamard_quantize_mixed_kernel(const uint
 // rows as v_mfma_f32_4x4x1_16b_f32, bit for bit the same (70 to 79 against 65).
 // POS = 2 is phase C with two positions per thread and 2-byte stores, a whole line of a row from every wave (launch_mixed says
 // where it is the better one).
+// Turned or padded pieces in the first exchange: turned where many rows are in flight, for LDS's sake, and in short calls of orders
+// 12 * 128 and 20 * 128 (256 rows of 1536 values, padded / turned 3.16 / 3.03 us, of 2560 3.75 / 3.57; longer blocks are level to
+// 4 % slower, 64 rows of 12288 4.26 / 4.42, but for 512 rows of 10240, 7.95 / 7.47).
 template <int LOGP, bool MANY>
 constexpr bool mixed_turned() { return MANY || LOGP == 7; }
 
@@ -404,7 +408,7 @@ __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *o
                 a1 = a1 + t1[b] * paley_sign<M>(a, b);
             }
             const float sc[4] = {a0 * inv_s, a1 * inv_s, 0.0f, 0.0f};
-            *reinterpret_cast<uint16_t *>(out + row + (size_t)a * P + 2 * t) = (uint16_t)(MANY ? codes_gathered<2>(sc) : codes_packed<2>(sc));
+            *reinterpret_cast<uint16_t *>(out + row + (size_t)a * P + 2 * t) = (uint16_t)codes_gathered<2>(sc);
         }
     } else {
         // phase C: position t of every block, four rows of the M-point sums at a time
@@ -438,6 +442,7 @@ hipError_t launch_mixed_form(const uint16_t *y, int64_t rows, float inv_s, int8_
 {
     constexpr int P = 1 << LOGP, N = M * P, NSB = (N + 1023) / 1024;
     constexpr int threads = P / POS;
+    static_assert(POS == 1 || MANY, "two positions only on large calls");
     static_assert(threads >= N / 32 && threads >= 32 * NSB, "every phase has its threads");
     constexpr int lds = NSB * (mixed_turned<LOGP, MANY>() ? 1024 : 1152) * (int)sizeof(float);
     static_assert(threads <= 1024 && lds <= 160 * 1024, "launch shape");
@@ -450,15 +455,6 @@ hipError_t launch_mixed_form(const uint16_t *y, int64_t rows, float inv_s, int8_
     return hipGetLastError();
 }
 
-template <int M, int LOGP, int POS>
-hipError_t launch_mixed_fast(const uint16_t *y, int64_t rows, float inv_s, int8_t *out, hipStream_t stream)
-{
-    // More than two rows per compute unit: enough waves for a SIMD's vector instructions to count.  (Order 5120, the short forms / these:
-    // 512 rows 5.04 / 5.10 us, 600 6.30 / 5.87, 1600 11.3 / 9.8, 16384 70.0 / 64.3; 12288: 256 rows 5.41 / 5.53, 800 12.57 / 12.35.)
-    if (rows > 2 * compute_units()) return launch_mixed_form<M, LOGP, POS, true>(y, rows, inv_s, out, stream);
-    return launch_mixed_form<M, LOGP, POS, false>(y, rows, inv_s, out, stream);
-}
-
 template <int M, int LOGP>
 hipError_t launch_mixed(const uint16_t *y, int64_t rows, float inv_s, int8_t *out, hipStream_t stream)
 {
@@ -469,11 +465,15 @@ hipError_t launch_mixed(const uint16_t *y, int64_t rows, float inv_s, int8_t *ou
     // than 9 of the 16 workgroups that a unit holds with one position (2204 rows 4.41 / 4.66, 2436 4.96 / 4.85, 3637 6.53 / 6.09,
     // 4020 6.88 / 6.56, 4443 7.59 / 7.71).
     if constexpr (M == 12 && (LOGP == 8 || LOGP == 9))
-        if (rows * M * (1 << LOGP) > 5LL << 20) return launch_mixed_fast<M, LOGP, 2>(y, rows, inv_s, out, stream);
+        if (rows * M * (1 << LOGP) > 5LL << 20) return launch_mixed_form<M, LOGP, 2, true>(y, rows, inv_s, out, stream);
     if constexpr (M == 12 && LOGP == 7)
         if (rows > 9 * compute_units() && rows <= 16 * compute_units())
-            return launch_mixed_fast<M, LOGP, 2>(y, rows, inv_s, out, stream);
-    return launch_mixed_fast<M, LOGP, 1>(y, rows, inv_s, out, stream);
+            return launch_mixed_form<M, LOGP, 2, true>(y, rows, inv_s, out, stream);
+    // More than two rows per compute unit: enough waves for a SIMD's vector instructions to count.  (Order 5120, the short forms / these:
+    // 512 rows 5.04 / 5.10 us, 600 6.30 / 5.87, 1600 11.3 / 9.8, 16384 70.0 / 64.3; 12288: 256 rows 5.41 / 5.53, 800 12.57 / 12.35.
+    // One line for all orders: on inputs that lie in the caches, calls just above it lose up to 1.7 %, 520 rows of 3072 3.58 / 3.62.)
+    if (rows > 2 * compute_units()) return launch_mixed_form<M, LOGP, 1, true>(y, rows, inv_s, out, stream);
+    return launch_mixed_form<M, LOGP, 1, false>(y, rows, inv_s, out, stream);
 }
 
 template <int LOGN>
