@@ -125,7 +125,7 @@ __device__ __forceinline__ u32x4 load_codes(const int8_t *row, int t, int L)
 
 // A workgroup's kThreads / LPC channels of one sequence, N = 16 states, seqlen >= 16.  LPC lanes share a channel (64, 32 or 16), so a
 // wave holds 64 / LPC channels.  B and C of NS states are staged at a time: 8 with workgroups of 256 threads, whose 34 KB of
-// LDS let four of them share a compute unit, all 16 with 512 (8 in mamba1_scan_halves_kernel).  The loop over states stays rolled: the 16 tokens of a lane
+// LDS let four of them share a compute unit, all 16 with 512 and 768 (8 in the halves of mamba1_scan_halves_kernel).  The loop over states stays rolled: the 16 tokens of a lane
 // already give every instruction 16 independent copies, and unrolling further only costs registers.  B and C are staged as fp32 (converted once per workgroup
 // instead of once per channel): plain fp32 multiplies and multiply-adds of two waves can issue together, the
 // mixed-precision ones that take fp16 operands cannot.  LDS rows are [state][quarter of a lane's tokens][lane], so that a lane's
@@ -134,9 +134,9 @@ __device__ __forceinline__ u32x4 load_codes(const int8_t *row, int t, int L)
 // rounding per code: 8.2e-8 instead of 7.7e-8 (rms) in the sum, under the 2e-4 of the fp16 output, whose error against 64 bits
 // is the same to four digits; exact codes, with x read again for the skip term at the end, took 1 to 2 % longer.
 // Measured at 4 x 4096 tokens, 5120 channels: 308 to 321 us (387 to 393 with fp16 operands, tiles of 1024
-// tokens and the exponentials between the other instructions); 1003 tokens of one sequence: 29 us, with gate and step-size
-// codes 32 to 34 (36.5 with workgroups of 512 threads, 3000 with one thread per channel, which is what a length that is no
-// multiple of 16 took before).  By the counters 36 cycles of a SIMD per 64 elements; the loop's instructions take 23 where all
+// tokens and the exponentials between the other instructions); 1003 tokens of one sequence: 28.5 us, with gate and step-size
+// codes 30.6 (32 to 34 with workgroups of 8 channels, 36.5 with 512 threads, 3000 with one thread per channel, which is what a length
+// that is no multiple of 16 took before).  By the counters 36 cycles of a SIMD per 64 elements; the loop's instructions take 23 where all
 // plain ones of two waves issue together, 33 where none do.
 template <int LPC, int kThreads, int NS, bool HALVES = false>
 __device__ __forceinline__ void scan_channels(
@@ -397,8 +397,8 @@ __global__ __launch_bounds__(kThreads, kThreads == 768 ? 3 : 4) void mamba1_scan
 // last round leaves compute units half empty is as slow there as one wave's instruction stream (80 us for 16 channels and 4096
 // tokens on a unit, 117 for 32 channels on it); half the channels on twice the waves take 65 us, 41 where a unit has one such half
 // (a wave's tile spans 1024 tokens of one channel instead of 512 of two; B and C are converted for 8 channels instead of 16,
-// which costs a full chip 5 to 10 %).  Bound as above.  5120 channels of two sequences, 4096 tokens 199 -> 162 us, 1003 tokens 55 -> 45;
-// 1536 channels of two 86 -> 66 and 25.6 -> 22.1.
+// which costs a full chip 5 to 10 %).  Bound as above.  5120 channels of two sequences, 4096 tokens 188 -> 149 us, 1003 tokens 58.4 ->
+// 51.7; 1536 channels of two 89 -> 69 and 23.3 -> 20.7.
 __global__ __launch_bounds__(512, 4) void mamba1_scan_halves_kernel(SsdArgs a, const float *A, const float *init,
                                                                    float *fin, int whole)
 {
@@ -530,58 +530,75 @@ hipError_t launch_scan(const SsdArgs &a, const float *A, const float *init, floa
     return hipGetLastError();
 }
 
+// Groups of 16 channels in the full rounds of two per compute unit.
+int64_t whole_groups(const quamba_ssd_shape_t &s)
+{
+    const int64_t round = 2 * (int64_t)compute_units();
+    return (int64_t)s.batch * ((s.headdim + 15) / 16) / round * round;
+}
+
 }  // namespace
 
 bool mamba1_scan_supports_any(const quamba_ssd_shape_t &s) { return s.d_state <= kMaxStates; }
 
+Mamba1Form mamba1_scan_form(const quamba_ssd_shape_t &s)
+{
+    const int D = s.headdim, cus = compute_units();
+    const int64_t batch = s.batch, L = s.seqlen;
+    if ((s.flags & QUAMBA_FLAG_GENERIC_KERNEL) || s.d_state != 16 || L < kE) return Mamba1Form::any;
+    // Lanes per channel: 16 for sequences one such tile (256 tokens) holds, where more lanes would idle; 64 when there
+    // are so few channels that a workgroup per compute unit is all there is, which halves the tiles each walks.
+    if (L <= 16 * kE) return Mamba1Form::lanes16;
+    auto per_cu = [&](int ch) { return (batch * ((D + ch - 1) / ch) + cus - 1) / cus * ch; };
+    if (L > 32 * kE && per_cu(8) <= 8) return Mamba1Form::lanes64;
+    // Else the time follows the channels of the fullest compute unit times the tokens of their tiles (about 1 us per
+    // 1000, from 1003 tokens up).  16 channels of 32 lanes in a workgroup; 8 where that spreads the channels more evenly
+    // (6400 channels, two sequences: 56 instead of 64 on a unit; 16 / 8 channels 1003 tokens 64.2 / 62.0 us, 4096 224.5 / 210.5; where
+    // it does not, its staging costs up to 5 %: 4 x 1003 tokens of 5120 channels 82 against 84 us); 32 of 16 lanes where their
+    // tiles of 256 tokens leave less over (3 x 700 tokens of 5120 channels 63.5 -> 47.7 us).  A difference below an
+    // eighth does not pay.
+    auto cost = [&](int ch, int tile) { return per_cu(ch) * ((L + tile - 1) / tile * tile); };
+    const int64_t c16 = cost(16, 32 * kE), c8 = cost(8, 32 * kE), c32 = cost(32, 16 * kE);
+    // Halves of groups of 16 channels behind the rounds of two groups per compute unit, where a unit has at most one group of
+    // the rest.  Costs in channels of a full unit times tokens: the rest takes 22 (one group on a unit) as whole groups, 18 as
+    // halves, 13 where a unit has one half; but a half's tiles are twice as long, so that it walks more padded tokens (9 : 10
+    // and 6 : 10 per tile of 1024 against 512; 1500 tokens of 192 groups 36.1 / 36.5 us, of 512 + 128 groups 77 -> 68).  Behind
+    // two rounds and more (1280 groups 308 / 309 us) a group per unit starts as units come free and gains nothing any more; at
+    // most a half per unit does until about eight rounds (2112 groups 409 -> 380 us, 4160 groups 979 -> 968).
+    const int64_t groups = batch * ((D + 15) / 16), whole = whole_groups(s), rest = groups - whole;
+    const int64_t tiles = (L + 32 * kE - 1) / (32 * kE), long_tiles = (tiles + 1) / 2;
+    const bool few = 2 * rest <= cus;
+    // groups of 8 channels in workgroups of 256 threads, in the same measure: four on a unit 32, three 29, two 24, one 22
+    const int64_t eights = per_cu(8) / 8, alone[4] = {0, 22, 24, 29}, tokens = tiles * 32 * kE;
+    const int64_t halves = 16 * (whole / cus) * tokens + (few ? 13 : 18) * long_tiles * 64 * kE;
+    if (rest > 0 && rest <= cus && whole <= (few ? 16 : 2) * cus && (few ? 6 : 9) * long_tiles <= 5 * tiles && halves <= c32 &&
+        halves <= (eights / 4 * 32 + alone[eights % 4]) * tokens)
+        return Mamba1Form::halves;
+    // 24 channels in one workgroup per compute unit where they hold all channels and groups of 16 do not: 4 x 1536 channels, 4096
+    // tokens 110.6 -> 104.1 us, 1003 tokens with side inputs 35.5 -> 31.5; 5120 channels of one sequence 104.2 -> 92.5, 34.3 -> 30.8
+    // (those were three and two workgroups of 8 channels per unit)
+    if (groups > cus && eights > 2 && batch * ((D + 23) / 24) <= cus) return Mamba1Form::channels24;
+    if (9 * std::min(c8, c32) <= 8 * c16) return c8 <= c32 ? Mamba1Form::channels8 : Mamba1Form::lanes16;
+    return Mamba1Form::lanes32;
+}
+
 hipError_t launch_mamba1_scan(const SsdArgs &a, const float *A, const float *init, float *fin, hipStream_t stream)
 {
-    const int D = a.s.headdim;
-    if (!(a.s.flags & QUAMBA_FLAG_GENERIC_KERNEL) && a.s.d_state == 16 && a.s.seqlen >= kE) {
-        // Lanes per channel: 16 for sequences one such tile (256 tokens) holds, where more lanes would idle; 64 when there
-        // are so few channels that a workgroup per compute unit is all there is, which halves the tiles each walks.
-        if (a.s.seqlen <= 16 * kE) return launch_scan<16, 512, 16>(a, A, init, fin, stream);
-        const int cus = compute_units();
-        auto per_cu = [&](int ch) { return ((int64_t)a.s.batch * ((D + ch - 1) / ch) + cus - 1) / cus * ch; };
-        if (a.s.seqlen > 32 * kE && per_cu(8) <= 8) return launch_scan<64, 512, 16>(a, A, init, fin, stream);
-        // Else the time follows the channels of the fullest compute unit times the tokens of their tiles (about 1 us per
-        // 1000, from 1003 tokens up).  16 channels of 32 lanes in a workgroup; 8 where that spreads the channels more evenly
-        // (5120 channels, one sequence: 24 instead of 32 on a unit; 1003 tokens 36.5 -> 32.2 us, 4096 117 -> 105 us; where it
-        // does not, its staging costs up to 5 %: 4 x 1003 tokens 82 against 84 us); 32 of 16 lanes where their
-        // tiles of 256 tokens leave less over (3 x 700 tokens of 5120 channels 63.5 -> 47.7 us).  A difference below an
-        // eighth does not pay.
-        auto cost = [&](int ch, int tile) { return per_cu(ch) * ((a.s.seqlen + (int64_t)tile - 1) / tile * tile); };
-        const int64_t c16 = cost(16, 32 * kE), c8 = cost(8, 32 * kE), c32 = cost(32, 16 * kE);
-        // Halves of groups of 16 channels behind the rounds of two groups per compute unit, where a unit has at most one group of
-        // the rest.  Costs in channels of a full unit times tokens: the rest takes 22 (one group on a unit) as whole groups, 18 as
-        // halves, 13 where a unit has one half; but a half's tiles are twice as long, so that it walks more padded tokens (9 : 10
-        // and 6 : 10 per tile of 1024 against 512; 1500 tokens of 192 groups 36.1 / 36.5 us, of 512 + 128 groups 77 -> 68).  Behind
-        // two rounds and more (1280 groups 308 / 309 us) a group per unit starts as units come free and gains nothing any more; at
-        // most a half per unit does until about eight rounds (2112 groups 409 -> 380 us, 4160 groups 979 -> 968).
-        const int64_t groups = (int64_t)a.s.batch * ((D + 15) / 16), whole = groups / (2 * cus) * (2 * cus), rest = groups - whole;
-        const int64_t tiles = (a.s.seqlen + 32 * kE - 1) / (32 * kE), long_tiles = (tiles + 1) / 2;
-        const bool few = 2 * rest <= cus;
-        // groups of 8 channels in workgroups of 256 threads, in the same measure: four on a unit 32, three 29, two 24, one 22
-        const int64_t eights = per_cu(8) / 8, alone[4] = {0, 22, 24, 29}, tokens = tiles * 32 * kE;
-        const int64_t halves = 16 * (whole / cus) * tokens + (few ? 13 : 18) * long_tiles * 64 * kE;
-        if (rest > 0 && rest <= cus && whole <= (few ? 16 : 2) * cus && (few ? 6 : 9) * long_tiles <= 5 * tiles && halves <= c32 &&
-            halves <= (eights / 4 * 32 + alone[eights % 4]) * tokens) {
-            hipLaunchKernelGGL(mamba1_scan_halves_kernel, dim3((unsigned)(whole + 2 * rest)), dim3(512), 0, stream, a, A,
+    switch (mamba1_scan_form(a.s)) {
+        case Mamba1Form::lanes16: return launch_scan<16, 512, 16>(a, A, init, fin, stream);
+        case Mamba1Form::lanes32: return launch_scan<32, 512, 16>(a, A, init, fin, stream);
+        case Mamba1Form::lanes64: return launch_scan<64, 512, 16>(a, A, init, fin, stream);
+        case Mamba1Form::channels8: return launch_scan<32, 256, 8>(a, A, init, fin, stream);
+        case Mamba1Form::channels24: return launch_scan<32, 768, 16>(a, A, init, fin, stream);
+        case Mamba1Form::halves: {
+            const int64_t groups = (int64_t)a.s.batch * ((a.s.headdim + 15) / 16), whole = whole_groups(a.s);
+            hipLaunchKernelGGL(mamba1_scan_halves_kernel, dim3((unsigned)(whole + 2 * (groups - whole))), dim3(512), 0, stream, a, A,
                                init, fin, (int)whole);
             return hipGetLastError();
         }
-        // 24 channels in one workgroup per compute unit where they hold all channels and groups of 16 do not: 4 x 1536 channels, 4096
-        // tokens 110.6 -> 104.1 us, 1003 tokens with side inputs 35.5 -> 31.5; 5120 channels 106.9 -> 97.3, 36.3 -> 33.0 (those as
-        // three and two workgroups of 8 channels per unit, below)
-        if (groups > cus && eights > 2 && (int64_t)a.s.batch * ((D + 23) / 24) <= cus)
-            return launch_scan<32, 768, 16>(a, A, init, fin, stream);
-        if (9 * std::min(c8, c32) <= 8 * c16) {
-            if (c8 <= c32) return launch_scan<32, 256, 8>(a, A, init, fin, stream);
-            return launch_scan<16, 512, 16>(a, A, init, fin, stream);
-        }
-        return launch_scan<32, 512, 16>(a, A, init, fin, stream);
+        default: break;
     }
-    const dim3 grid((unsigned)((D + 63) / 64), (unsigned)a.s.batch);
+    const dim3 grid((unsigned)((a.s.headdim + 63) / 64), (unsigned)a.s.batch);
     hipLaunchKernelGGL(mamba1_scan_any_kernel, grid, dim3(64), 0, stream, a, A, init, fin);
     return hipGetLastError();
 }

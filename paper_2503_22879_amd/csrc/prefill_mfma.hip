@@ -1230,6 +1230,11 @@ Split largest_split(const quamba_ssd_shape_t &s)
 // 6144 tokens 53.6, 43.6, 44.6; 40 heads, 2048 tokens 31.1, 26.1, 29.5.  With five segments, 43 to 51 pairs, it is 1 to 8 % ahead from
 // 20 chunks on, below it the two kernels of whole heads are level.)
 //
+// From 43 pairs on the choice is still made by the first set of costs, fitted before the end states lay in accumulator order: whole heads
+// in segments have become cheaper since, and a few calls run unsplit that they would take less for (50 to 60 heads, 2048 tokens: 36 us,
+// whole heads 33.6; by the second set of costs, 5 % or more in 1 of 150 calls of 43 to 128 pairs and 8 to 48 chunks).  43 to 48 heads,
+// 2048 tokens, and 56 to 80 of 2560 to 4096 take segments and need 31 to 33 and 37 to 61 us, unsplit 36 and 44 to 66.
+//
 // Above, segments of whole heads are the faster form for up to two thirds of a pair per unit (3 segments) from a number of chunks
 // on: 26, and half a chunk per pair more (129 pairs, 24 / 28 / 32 chunks: unsplit 74.8 / 86.0 / 97.4, segments 73.8 / 81.2 / 91.5; 160
 // pairs, 32 / 48: 98.3 / 143.8, 100.9 / 143.4); 18 later with the final state and step-size codes (129 pairs, 40: 108, 108); 22 with both

@@ -324,6 +324,9 @@ hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream);
 constexpr int kMaxGridY = 65535;                    // of a launch
 constexpr int kConvMaxTokens = 32 * kMaxGridY;  // longest sequence of the convolution (segments of 32 tokens)
 // Mamba1 selective scan: shape has nheads = ngroups = 1, headdim = channels; A is [channels, d_state]
+// Which kernel takes a scan: by lanes per channel, or channels per workgroup, or mamba1_scan_halves_kernel, or the one for any shape
+enum class Mamba1Form : int { any, lanes16, lanes32, lanes64, channels8, channels24, halves };
+Mamba1Form mamba1_scan_form(const quamba_ssd_shape_t &s);
 hipError_t launch_mamba1_scan(const SsdArgs &a, const float *A, const float *init, float *fin, hipStream_t stream);
 hipError_t launch_mamba1_decode(const SsdArgs &a, const float *A, hipStream_t stream);
 bool mamba1_scan_supports_any(const quamba_ssd_shape_t &s);

@@ -2,6 +2,8 @@
 (numpy sort-and-cluster + Eq. 1), so that no oracle input ever comes from the HIP library."""
 from __future__ import annotations
 
+import ctypes as C
+
 import numpy as np
 
 import oracle
@@ -38,6 +40,18 @@ def to_shape(q, s: W.LayerShape, flags: int = 0, **over):
              ngroups=s.ngroups, chunk=s.chunk, n_head_clusters=s.m, n_chan_clusters=s.n, flags=flags)
     d.update(over)
     return q.Shape(**d)
+
+
+class _Plan(C.Structure):
+    _fields_ = [("segments", C.c_int), ("chunks", C.c_int), ("halves", C.c_bool), ("sixteen_waves", C.c_bool)]
+
+
+def prefill_plan(q, shape, state=False, gate=False, dt_codes=False):
+    """How the library cuts a prefill call on this device (PrefillPlan in csrc/quamba_internal.h): segments of the sequence
+    and chunks of each, workgroups of channel halves or whole heads, of 16 or 8 waves."""
+    f = q.load_library()._ZN6quamba17prefill_mfma_planERK18quamba_ssd_shape_tRKNS_15PrefillOperandsE
+    f.restype = _Plan
+    return f(C.byref(shape), (C.c_bool * 3)(state, gate, dt_codes))
 
 
 def host_scales(q, sc):

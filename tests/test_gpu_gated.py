@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 import workloads as W
-from helpers import (make_problem, make_decode_inputs, make_gate_inputs, make_state_cache, to_shape, host_scales)
+from helpers import (make_problem, make_decode_inputs, make_gate_inputs, make_state_cache, prefill_plan, to_shape, host_scales)
 
 pytestmark = pytest.mark.gpu
 
@@ -86,7 +86,8 @@ def test_prefill_gated_on_workgroups_of_sixteen_waves(gpu_lib, batch, L, use_z, 
 @pytest.mark.parametrize("flags", [0, NO_SPLIT])
 def test_prefill_gated_with_the_sequence_split(gpu_lib, flags):
     """130M-shaped layer at full length with both side inputs and a workspace: the launch is cut along the sequence
-    (the state pass reads the step-size codes, the output pass applies the gate), with initial and final state."""
+    (the state pass reads the step-size codes, the output pass applies the gate), with initial state, with and without the
+    final state; whole heads on 16 waves, or on 8 with the flag."""
     import torch
     q = gpu_lib
     s = W.CONFIGS["m2_130m"]
@@ -113,6 +114,14 @@ def test_prefill_gated_with_the_sequence_split(gpu_lib, flags):
     eh = np.abs(hg - href).max() / np.abs(href).max()
     print(f"gated prefill with the sequence split, flags={flags}: y err {ey:.3e}, state err {eh:.3e}")
     assert ey <= Y_TOL and eh <= H_TOL
+    y.fill_(float("nan"))
+    q.quamba_ssd_prefill(shape, q.DeviceScales(host_scales(q, sc)), t["x"], t["B"], t["C"], None, t["A"], t["D"],
+                         torch.from_numpy(init).cuda(), y, None, ws, gate=_gate(q, g, True, True))
+    yg = y.cpu().numpy().astype(np.float64)
+    assert np.isfinite(yg).all() and np.abs(yg - yref).max() <= Y_TOL * np.abs(yref).max()
+    for state in (True, False):
+        plan = prefill_plan(q, shape, state=state, gate=True, dt_codes=True)
+        assert plan.segments > 1 and plan.sixteen_waves == (flags == 0) and not plan.halves
 
 
 def test_prefill_gated_8b_shape_sampled(gpu_lib):

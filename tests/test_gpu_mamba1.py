@@ -1,5 +1,7 @@
 """GPU parity of the 8-bit Mamba1 selective scan (quamba_mamba1_scan, quamba_mamba1_decode_step) against the fp64
 oracle, through the C ABI: y within 2e-3 of the largest |y| (fp32 scan, fp16 output), states within 1e-4."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -16,6 +18,12 @@ S_TOL = 1e-4
 def _shape(q, b, D, N, L, nranges, flags=0):
     return q.Shape(batch=b, seqlen=L, nheads=1, headdim=D, d_state=N, ngroups=1, chunk=1, n_head_clusters=1,
                    n_chan_clusters=nranges, flags=flags)
+
+
+def _form(q, b, D, N, L, flags=0):
+    """The kernel that the library chooses for a scan on this device (Mamba1Form in csrc/quamba_internal.h)."""
+    f = q.load_library()._ZN6quamba16mamba1_scan_formERK18quamba_ssd_shape_t
+    return ["any", "16 lanes", "32 lanes", "64 lanes", "8 channels", "24 channels", "halves"][f(C.byref(_shape(q, b, D, N, L, 4, flags)))]
 
 
 def _run(q, sc, p, b, D, N, L, nranges=4, flags=0, init=None, with_D=True, want_state=True):
@@ -163,7 +171,8 @@ def _dt_of_codes(g):
                                            (2, 70, 16, 45, 0),       # 16 lanes, one tile
                                            (2, 8177, 16, 700, 0),    # 16 lanes, several tiles
                                            (2, 2060, 16, 1037, 0),   # 32 lanes, 24 channels
-                                           (2, 8198, 16, 1029, 0),   # 32 lanes, 16 channels; 64 lanes behind
+                                           (2, 8198, 16, 1029, 0),   # 32 lanes, 16 channels
+                                           (2, 8198, 16, 1301, 0),   # ... and 64 lanes behind, several tiles of both
                                            (1, 33, 24, 64, 0),       # any shape
                                            (1, 130, 16, 256, 1)])    # ... forced
 def test_scan_with_side_inputs(gpu_lib, b, D, N, L, flags, use_z, use_dt):
@@ -291,43 +300,47 @@ def test_states_that_forget_everything_at_a_ragged_end(gpu_lib, L):
     assert np.abs(fin - sref).max() <= S_TOL * np.abs(sref).max()
 
 
-@pytest.mark.parametrize("b,D,L", [(1, 2085, 520),    # no whole group, more than half a unit's worth of halves, the last one empty
-                                   (1, 4096, 1024),   # ... as many groups as compute units
-                                   (3, 2736, 513),    # two groups per unit and one: two halves behind them
-                                   (3, 4090, 900),    # ... and a group per unit
-                                   (1, 8192, 600),    # two groups per unit, no halves
-                                   (3, 1537, 600),    # 24 channels per workgroup, the last with one
-                                   (4, 1536, 513),    # ... as many workgroups as compute units
-                                   (2, 6400, 900)])   # 8 channels per workgroup, 8 states at a time
+@pytest.mark.parametrize("b,D,L,form", [(1, 2085, 520, "halves"),    # no whole group, more than half a unit's worth of halves, the last one empty
+                                        (1, 4096, 1024, "halves"),   # ... as many groups as compute units
+                                        (3, 2736, 513, "halves"),    # two groups per unit and one: two halves behind them
+                                        (3, 4090, 900, "halves"),    # ... and a group per unit
+                                        (1, 8192, 600, "16 lanes"),  # two groups per unit, whose tiles of 512 tokens would be half empty
+                                        (1, 8192, 1000, "32 lanes"),  # ... and would not, no halves
+                                        (3, 1537, 600, "24 channels"),  # the last workgroup with one
+                                        (4, 1536, 513, "24 channels"),  # as many workgroups as compute units
+                                        (2, 6400, 900, "8 channels")])  # 8 states at a time
 @pytest.mark.parametrize("sides", [False, True])
-def test_how_channels_are_shared_out(gpu_lib, b, D, L, sides):
+def test_how_channels_are_shared_out(gpu_lib, b, D, L, form, sides):
     """Groups of 16 channels, those behind the last full round as halves of 8 channels on 64 lanes each, and workgroups of 24 and
     of 8 channels, at the edges of their rules on 256 compute units, at the same bars."""
+    assert _form(gpu_lib, b, D, 16, L) == form
     test_scan_with_side_inputs(gpu_lib, b, D, 16, L, 0, sides, sides)
 
 
-@pytest.mark.parametrize("b,D,L", [(2, 5120, 1003), (2, 5120, 4096), (3, 5120, 600), (6, 1536, 1003), (6, 1536, 2561), (3, 4099, 1537),
-                                   (2, 1536, 4096), (2, 6400, 1003), (3, 1537, 700)])
+@pytest.mark.parametrize("b,D,L,form", [(2, 5120, 1003, "halves"), (2, 5120, 4096, "halves"), (6, 1536, 1003, "halves"),
+                                        (6, 1536, 2561, "halves"), (2, 1536, 4096, "halves"), (3, 5120, 600, "16 lanes"),
+                                        (3, 4099, 1537, "8 channels"), (2, 6400, 1003, "8 channels"), (3, 1537, 700, "24 channels")])
 @pytest.mark.parametrize("infinite", [False, True])
-def test_equal_sequences_of_one_call_have_equal_results(gpu_lib, b, D, L, infinite):
+def test_equal_sequences_of_one_call_have_equal_results(gpu_lib, b, D, L, form, infinite):
     """Sequences with the same inputs have the same outputs and final states, bit for bit, also where a launch takes some groups of
     channels on 32 lanes each and the others on 64: with small steps, whose states carry far over the ends of the tiles, and with
     infinite initial states in some channels, which leave their neighbours' results as they are."""
     import torch
     q = gpu_lib
+    assert _form(q, b, D, 16, L) == form
     g = torch.Generator(device="cuda").manual_seed(D + L)
     codes = lambda *s: torch.randint(-128, 128, s, generator=g, device="cuda", dtype=torch.int8)
     rand = lambda *s: torch.rand(s, generator=g, device="cuda")
     sc, _ = make_mamba1_problem(1, D, 16, 16, seed=3)
-    x, B, C, dt, init = codes(1, D, L), codes(1, 16, L), codes(1, 16, L), 0.006 * rand(1, D, L), rand(1, D, 16) - 0.5
+    x, B, Cm, dt, init = codes(1, D, L), codes(1, 16, L), codes(1, 16, L), 0.006 * rand(1, D, L), rand(1, D, 16) - 0.5
     if infinite:
         init[0, ::37, 5] = float("inf")
         init[0, 5::74, 11] = -float("inf")
-    x, B, C, dt, init = (v.expand(b, *v.shape[1:]).contiguous() for v in (x, B, C, dt, init))
+    x, B, Cm, dt, init = (v.expand(b, *v.shape[1:]).contiguous() for v in (x, B, Cm, dt, init))
     A, Dk = -0.5 - 1.5 * rand(D, 16), rand(D) - 0.5
     y = torch.empty((b, D, L), dtype=torch.float16, device="cuda")
     fin = torch.empty((b, D, 16), device="cuda")
-    q.quamba_mamba1_scan(_shape(q, b, D, 16, L, 4), q.DeviceScales(host_scales(q, sc)), x, B, C, dt, A, Dk, y, init_state=init,
+    q.quamba_mamba1_scan(_shape(q, b, D, 16, L, 4), q.DeviceScales(host_scales(q, sc)), x, B, Cm, dt, A, Dk, y, init_state=init,
                          final_state=fin)
     assert infinite or (torch.isfinite(y).all() and torch.isfinite(fin).all())
     y, fin = y.view(torch.int16), fin.view(torch.int32)
@@ -335,5 +348,8 @@ def test_equal_sequences_of_one_call_have_equal_results(gpu_lib, b, D, L, infini
         assert torch.equal(y[i], y[0]) and torch.equal(fin[i], fin[0]), i
 
 
-def test_infinite_and_zero_states_in_halves(gpu_lib):
-    test_infinite_and_zero_states(gpu_lib, 2000, 600)
+@pytest.mark.parametrize("D,L,form", [(2000, 600, "halves"), (2000, 1537, "halves"), (6400, 900, "8 channels")])
+def test_infinite_and_zero_states_in_halves_and_in_workgroups_of_8_channels(gpu_lib, D, L, form):
+    """... over one tile and several."""
+    assert _form(gpu_lib, 2, D, 16, L) == form
+    test_infinite_and_zero_states(gpu_lib, D, L)

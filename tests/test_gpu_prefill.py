@@ -4,7 +4,7 @@ import pytest
 
 import oracle
 import workloads as W
-from helpers import make_problem, to_shape, host_scales
+from helpers import make_problem, prefill_plan, to_shape, host_scales
 
 pytestmark = pytest.mark.gpu
 
@@ -248,15 +248,15 @@ def test_segments_of_whole_heads(gpu_lib, H, G, L, segments):
             assert np.abs(hg - hu).max() <= 2e-5 * np.abs(hu).max()
 
 
-@pytest.mark.parametrize("H,G,L,segments,tiny_scales", [
-    (24, 1, 2048, 8, False),    # whole heads on 16 waves: 2 chunks each
-    (24, 3, 1921, 8, False),    # the same, the last chunk a single token
-    (40, 1, 2010, 6, False),    # 3 chunks each, the last one a single ragged chunk
-    (32, 2, 2050, 6, True),     # 3 chunks each, the last one 2 with two tokens; the skip term in the epilogue
-    (16, 1, 2048, 8, False),    # channel halves on 16 waves: 2 chunks each
-    (20, 5, 1700, 5, True),     # 3 chunks each, the last one 2; the skip term in the epilogue
+@pytest.mark.parametrize("H,G,L,segments,halves,tiny_scales", [
+    (24, 1, 2048, 8, False, False),    # whole heads on 16 waves: 2 chunks each
+    (24, 3, 1921, 8, False, False),    # the same, the last chunk a single token
+    (40, 1, 2010, 6, False, False),    # 3 chunks each, the last one a single ragged chunk
+    (32, 2, 2050, 6, False, True),     # 3 chunks each, the last one 2 with two tokens; the skip term in the epilogue
+    (16, 1, 2048, 8, True, False),     # channel halves on 16 waves: 2 chunks each
+    (20, 5, 1700, 5, True, True),      # 3 chunks each, the last one 2; the skip term in the epilogue
 ])
-def test_segments_on_workgroups_of_sixteen_waves(gpu_lib, H, G, L, segments, tiny_scales):
+def test_segments_on_workgroups_of_sixteen_waves(gpu_lib, H, G, L, segments, halves, tiny_scales):
     """Plans that cut the sequence into segments of whole heads or of channel halves on workgroups of 16 waves: with an initial state,
     against the oracle and the same kernel's unsplit launch (the bars of the tests above)."""
     s = W.CONFIGS["m2_8b_b1"].with_(batch=1, seqlen=L, nheads=H, ngroups=G)
@@ -272,6 +272,8 @@ def test_segments_on_workgroups_of_sixteen_waves(gpu_lib, H, G, L, segments, tin
         used = []
         yg, hg = run_prefill(gpu_lib, s, sc, prob, 0, init_state=h0, want_state=want_state, used=used)
         assert used == [4 * (segments - 1) * H * (64 * 128 + 1)], "bytes of workspace written"
+        plan = prefill_plan(gpu_lib, to_shape(gpu_lib, s), state=want_state)
+        assert plan.sixteen_waves and plan.halves == halves
         check(yg, hg, yref, href if want_state else None, f"16 waves H={H} L={L} state={want_state}", cells=cells)
         yu, hu = run_prefill(gpu_lib, s, sc, prob, NO_SEQ_SPLIT, init_state=h0, want_state=want_state)
         flipped = np.count_nonzero(yg != yu)
@@ -335,16 +337,16 @@ def test_sequence_split_on_drawn_shapes(gpu_lib, b, H, G, L, flags, seed, want_s
 
 
 @pytest.mark.parametrize("H,L,split,state,gate,dt_codes", [
-    (24, 2048, True, True, False, False),     # 8 segments of whole heads on 16 waves, 21 us; unsplit 35
-    (48, 4096, True, True, False, False),     # 8 segments of whole heads on 8 waves 51, unsplit 67
-    (60, 2048, False, True, False, False),    # unsplit 36.5, 8 segments of whole heads 38.5, 2 of channel halves 38.0
-    (64, 1000, False, False, False, False),   # unsplit 18.6, 4 segments of whole heads, a workgroup on every unit, 20.9
-    (128, 2048, False, True, False, False),   # unsplit 41, 4 segments of whole heads 47
-    (129, 2048, False, True, False, False),   # unsplit (whole heads on 16 waves) 52, 3 segments 55
+    (24, 2048, True, True, False, False),     # 8 segments of whole heads on 16 waves, 22 us; unsplit 35
+    (48, 4096, True, True, False, False),     # 8 segments of whole heads on 8 waves 46, unsplit 66
+    (60, 2048, False, True, False, False),    # unsplit 36, 2 of channel halves 38; 8 segments of whole heads 34 by now (see the plan)
+    (64, 1000, False, False, False, False),   # unsplit 18.6, 4 segments of whole heads, a workgroup on every unit, 19.5
+    (128, 2048, False, True, False, False),   # unsplit 42, 4 segments of whole heads 47
+    (129, 2048, False, True, False, False),   # unsplit (whole heads on 16 waves) 52, 3 segments 54.5
     (129, 4096, True, True, False, False),    # 3 segments 91, unsplit 98
-    (150, 3584, False, True, False, False),   # unsplit 87, 3 segments 88
+    (150, 3584, False, True, False, False),   # unsplit 86.9, 3 segments 87.3
     (160, 3500, True, False, True, True),     # 3 segments 103, unsplit 113
-    (160, 3500, False, False, False, False),  # unsplit 74, 3 segments 79
+    (160, 3500, False, False, False, False),  # unsplit 73, 3 segments 76
     (129, 4000, False, True, False, True),    # unsplit 101, 3 segments 102
     (112, 6100, True, False, False, True),    # 4 segments of whole heads 102, unsplit 115
 ])
