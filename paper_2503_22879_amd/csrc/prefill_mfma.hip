@@ -819,7 +819,7 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(SsdArgs a)
 // of kStateDepth chunks are in flight, each chunk's in a register set of its own, and the LDS operands of a group of
 // 16 tokens are requested one group ahead of their use.  Measured per chunk and workgroup (cycles): staging 640,
 // barrier 260, issuing the next loads 640, state update 2090, barrier 160; a vector instruction takes a lone wave of these
-// phases 8 cycles (4 to 5 where nothing depends on it) and an LDS instruction 12, which is what they add up to.  Eight waves that split a
+// phases 8 cycles (4 to issue it) and an LDS instruction 12, which is what they add up to.  Eight waves that split a
 // chunk's tokens between two copies of the state were not faster (the phases are serial between the barriers and
 // the two waves of a SIMD share its LDS and memory paths).
 constexpr int kStateThreads = 256;

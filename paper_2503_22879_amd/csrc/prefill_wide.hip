@@ -2,7 +2,7 @@
 // unit: every channel half of every pair, or every half or whole head of every segment of its sequence) has a unit to itself.
 //
 // The arithmetic is that of prefill_mfma_kernel (prefill_mfma.hip describes it), for 32 (PT = 1) or all 64 (PT = 2) of a head's
-// channels.  What bounds such a launch is the serial walk over the chunks: a lone wave issues an instruction every 4 to 5
+// channels.  What bounds such a launch is the serial walk over the chunks: a lone wave issues an instruction every 4
 // cycles and waits alone for each result, and with 8 waves in two phases between two barriers a chunk of 32 channels took 2.7 us.  Here a workgroup has 16 waves, four
 // to a SIMD, in four roles that work side by side on everything a chunk needs, and one barrier per chunk:
 //   waves  0..3   the later terms of a 32-token block's outputs (the pair in front of the diagonal of the two longer blocks,
