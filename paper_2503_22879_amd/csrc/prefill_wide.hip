@@ -305,6 +305,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
         if (role == 0) {
             // ---- the later terms and the outputs of block `wave` ----
             const int tb = wave, mid = tb >= 2 ? tb - 1 : tb;
+            if (SEG) new_lane();  // (not kept from in front of the other roles' code)
             if (tid4 < kPw) s_sx[tid4] = x_scale_lookup_wide(a, h, p_base + tid4) * (d_by_mfma ? y_scale : 1.0f);
             if (GATED) s_silu[tid4] = silu_of_code(a.z_scale, (int8_t)tid4);
             // per lane (token t of the block): which of its 16 score rows s are at or in front of t, two to a dword; with 64 channels
@@ -569,8 +570,11 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
         f32x16 st[PT];
 #pragma unroll
         for (int pt = 0; pt < PT; ++pt) st[pt] = (f32x16)(0.0f);
-        const int n_lane = 32 * wave + 4 * hb;
-        const size_t st_row = ((size_t)bh * kP + p_base + l32) * kN + n_lane;
+        // the lane's row of the caller's states, where it is read and where it is written: kept over the chunks it would not fit
+        auto st_row = [&]() {
+            new_lane();
+            return ((size_t)bh * kP + p_base + l32) * kN + 32 * wave + 4 * hb;
+        };
         if (SEG && seg > 0) {
             // the combination of the earlier segments' states, see prefill_mfma_kernel
             const size_t pairs = (size_t)a.s.batch * H;
@@ -591,12 +595,13 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
         }
         if (convert_init) {
             __syncthreads();  // the scales are in LDS
+            const float *init = a.init_state + st_row();
 #pragma unroll
             for (int pt = 0; pt < PT; ++pt) {
                 const float inv = kNarrow * (d_by_mfma ? y_scale : 1.0f) / (s_sx[32 * pt + l32] * sB);
 #pragma unroll
                 for (int rg = 0; rg < 4; ++rg) {
-                    const f32x4 v = *reinterpret_cast<const f32x4 *>(a.init_state + st_row + 32 * pt * kN + 8 * rg);
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(init + 32 * pt * kN + 8 * rg);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) st[pt][4 * rg + i] = v[i] * inv;
                 }
@@ -703,6 +708,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
             __syncthreads();
         }
         if (want_state) {
+            float *state = a.state + st_row();
 #pragma unroll
             for (int pt = 0; pt < PT; ++pt) {
                 const float sc = s_sx[32 * pt + l32] * sB / ((d_by_mfma ? y_scale : 1.0f) * kNarrow);
@@ -711,7 +717,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
                     f32x4 v;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) v[i] = st[pt][4 * rg + i] * sc;
-                    *reinterpret_cast<f32x4 *>(a.state + st_row + 32 * pt * kN + 8 * rg) = v;
+                    *reinterpret_cast<f32x4 *>(state + 32 * pt * kN + 8 * rg) = v;
                 }
             }
         }

@@ -72,12 +72,12 @@ def test_the_extension_is_built_again_for_another_torch(monkeypatch, tmp_path):
     assert len(ran) == 2
 
 
-def test_the_mamba1_scan_of_uneven_launches_keeps_everything_in_registers(tmp_path):
-    """By the compiler's report: the kernel whose waves have 128 registers each and two bodies to fit into them."""
-    src = os.path.join(build.CSRC, "mamba1.hip")
-    cmd = [build.HIPCC, *build.FLAGS, "-x", "hip", "--cuda-device-only", "-c", src, "-o", str(tmp_path / "o"),
-           "-Rpass-analysis=kernel-resource-usage"]
+@pytest.mark.parametrize("source,kernel", [("mamba1.hip", "mamba1_scan_halves_kernel"), ("prefill_wide.hip", "prefill_wide_kernel")])
+def test_kernels_that_fill_their_registers_keep_everything_in_them(tmp_path, source, kernel):
+    """By the compiler's report: no scratch memory in the kernels whose waves have 128 registers and several bodies to fit into them."""
+    cmd = [build.HIPCC, *build.FLAGS, "-x", "hip", "--cuda-device-only", "-c", os.path.join(build.CSRC, source), "-o",
+           str(tmp_path / "o"), "-Rpass-analysis=kernel-resource-usage"]
     report = subprocess.run(cmd, check=True, capture_output=True, text=True).stderr
-    scratch = dict(re.findall(r"Function Name: (\S+).*?ScratchSize \[bytes/lane\]: (\d+)", report, re.S))
-    found = [int(v) for k, v in scratch.items() if "mamba1_scan_halves_kernel" in k]
-    assert found == [0], scratch
+    scratch = re.findall(r"Function Name: (\S+).*?ScratchSize \[bytes/lane\]: (\d+)", report, re.S)
+    found = {name: int(size) for name, size in scratch if kernel in name}
+    assert found and not any(found.values()), found
