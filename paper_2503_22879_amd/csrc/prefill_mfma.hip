@@ -35,6 +35,8 @@
 // (segment_state_kernel) walks all but the last segment without outputs and leaves every segment's end state (from a
 // zero start) and decay total in the workspace, then this kernel (SEG instantiations) gives every segment its own
 // workgroups, which start from the combination of the earlier segments' states (Eq. 2 is linear in the state).
+// Batches of a few more pairs than the device holds workgroups share their rounds (shared_rounds): pairs that would run in a nearly
+// empty last round are walked in two pieces, the second by another workgroup that goes on from the first one's accumulators.
 // Batches of at most a pair per compute unit take prefill_wide_kernel (prefill_wide.hip) instead, unless the split is deep
 // enough or the sequences are of one chunk (prefill_mfma_plan).
 //
@@ -76,6 +78,7 @@ struct Lds {
     static constexpr int kOffLoc = kOffSx + 4 * kP;          // float[128]  prefix sums inside each 32-token block
     static constexpr int kOffTot = kOffLoc + 4 * kQ;         // float[4]    the blocks' totals
     static constexpr int kOffGap = kOffTot + 4 * kNBlk;      // float[4][4] [tb][sb]: sum of the totals of blocks sb+1..tb-1
+    static constexpr int kOffLeft = kOffGap + 4 * kNBlk * kNBlk;  // int: has the piece in front left its state?
     static constexpr int kOffBq = kOffGap + 4 * kNBlk * kNBlk + 48;  // int8 [128][144]
     static constexpr int kOffHs = kOffBq + kQ * kBqStride;   // fp16 [kPw][136]
     static constexpr int kOffXs = kOffHs + 2 * kPw * kHsStride;  // fp16 [128][kXsStride]
@@ -89,14 +92,52 @@ struct Lds {
 };
 static_assert(Lds<2>::kBytesGated <= 80 * 1024, "two workgroups must fit the 160 KB LDS of a gfx950 compute unit");
 
+enum class Walk { whole, segment, shared };
+
+// Shared rounds: launches of a few more (sequence, head) pairs than the device holds workgroups (two to a unit).  See shared_rounds.
+struct SharedRounds {
+    static constexpr int kPlaces = 8;  // of a group: workgroups that share its pairs
+    struct Piece {
+        int c_begin, c_end;  // chunks
+        int16_t pair;        // of the group, behind the lead
+        int16_t cut;         // at the piece's end or start
+    };
+    int groups;   // workgroup i: step i / groups of the list of group i % groups
+    int lead;     // steps that are whole pairs, in front of the pieces
+    int steps;    // in all; 0: the launch is not of this kind
+    int polls;    // of a wait for the piece in front
+    float *state; // [cut][group][headdim * d_state]: the accumulators at the cuts
+    int *left;    // [cut][group]: waves that have left their part of them there
+    Piece piece[2 * kPlaces + kPlaces - 2];
+};
+struct SharedArgs : SsdArgs {
+    SharedRounds rounds;
+};
+template <Walk WALK>
+struct WalkArgs {
+    typedef SsdArgs type;
+};
+template <>
+struct WalkArgs<Walk::shared> {
+    typedef SharedArgs type;
+};
+
+// (A kernel, not hipMemsetAsync: the call may be captured into a graph.)
+__global__ void clear_counts_kernel(int *p, int n)
+{
+    for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
+}
+
 // PT: 32-channel tiles per workgroup.  2: one workgroup per (sequence, head).  1: two workgroups per head, each with
 // half of the channels, its own half of the state and its own copy of the G^T work; chosen for sequences of one chunk
 // when there is at most half a pair per compute unit, so that the whole chip works on short batches.
 // GATED: the output is multiplied by SiLU(z) of the caller's int8 gate codes (Section 3.2) in the epilogue.
-// SEG: the launch belongs to a sequence split (see SsdArgs); the instantiations without it carry none of its code.
-template <bool PRECISE, int PT, bool GATED, bool SEG>
-__global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(SsdArgs a)
+// WALK: what a workgroup walks of its sequence: all of it, a segment of a sequence split (see SsdArgs), or a piece of shared rounds
+// (see SharedRounds); the instantiations for whole sequences carry none of the others' code.
+template <bool PRECISE, int PT, bool GATED, Walk WALK>
+__global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(typename WalkArgs<WALK>::type a)
 {
+    constexpr bool SEG = WALK == Walk::segment, SHARED = WALK == Walk::shared;
     typedef Lds<PT> LY;
     constexpr int kPw = LY::kPw;  // channels of this workgroup
     constexpr int kXsStride = LY::kXsStride;
@@ -111,6 +152,7 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(SsdArgs a)
     float *s_loc = reinterpret_cast<float *>(smem + LY::kOffLoc);
     float *s_tot = reinterpret_cast<float *>(smem + LY::kOffTot);
     float *s_gap = reinterpret_cast<float *>(smem + LY::kOffGap);
+    int *s_left = reinterpret_cast<int *>(smem + LY::kOffLeft);  // SHARED only
     unsigned char *s_bq = smem + LY::kOffBq;
     _Float16 *s_hs = reinterpret_cast<_Float16 *>(smem + LY::kOffHs);
     unsigned char *s_xs = smem + LY::kOffXs;  // fp16 rows, addressed in bytes
@@ -124,13 +166,27 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(SsdArgs a)
     const int wgs_per_seg = a.s.batch * H * (2 / PT);
     const int seg = SEG ? (int)blockIdx.x / wgs_per_seg : 0;
     const int nchunks = (L + kQ - 1) / kQ;
-    const int c_begin = SEG ? seg * a.seg_chunks : 0;
-    const int c_end = (SEG && seg + 1 < a.nseg) ? c_begin + a.seg_chunks : nchunks;
-    const bool convert_init = a.init_state && (!SEG || seg == 0);  // the caller's initial state belongs to segment 0
+    int c_begin = SEG ? seg * a.seg_chunks : 0;
+    int c_end = (SEG && seg + 1 < a.nseg) ? c_begin + a.seg_chunks : nchunks;
+    int shared_pair = 0, cut = 0;
+    if constexpr (SHARED) {
+        const int step = (int)blockIdx.x / a.rounds.groups, group = (int)blockIdx.x - step * a.rounds.groups;
+        shared_pair = step;
+        if (step >= a.rounds.lead) {
+            const SharedRounds::Piece piece = a.rounds.piece[step - a.rounds.lead];
+            shared_pair = a.rounds.lead + piece.pair;
+            c_begin = piece.c_begin;
+            c_end = piece.c_end;
+            cut = piece.cut * a.rounds.groups + group;
+        }
+        shared_pair = shared_pair * a.rounds.groups + group;
+        if (shared_pair >= a.s.batch * H) return;  // a group may have one pair less
+    }
+    bool convert_init = a.init_state && c_begin == 0;  // the caller's initial state stands in front of the first chunk
     // with two workgroups per head, ids i and i + 8 (same XCD, and the same compute unit when two workgroups fit one)
     // take the two halves of a head
     const int bid = SEG ? (int)blockIdx.x - seg * wgs_per_seg : (int)blockIdx.x;
-    int pair = bid, half = 0;  // index of the (sequence, head) pair before the XCD mapping; channel half
+    int pair = SHARED ? shared_pair : bid, half = 0;  // index of the (sequence, head) pair before the XCD mapping; channel half
     if (PT == 1) {
         // complete groups of 8 pairs take 16 consecutive ids (8 first halves, 8 second halves); the last, incomplete
         // group of r pairs takes the remaining 2 r ids (r first halves, r second halves)
@@ -215,6 +271,16 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(SsdArgs a)
         };
         issue_c_rows(c_begin);
         fill_tables();
+        if constexpr (SHARED) {
+            if (c_begin > 0) {
+                __syncthreads();  // the first state wave has looked for the state that the piece in front leaves
+                if (!__builtin_amdgcn_readfirstlane(*s_left)) {
+                    c_begin = 0;
+                    convert_init = a.init_state != nullptr;
+                    issue_c_rows(c_begin);
+                }
+            }
+        }
         if (convert_init) __syncthreads();  // the state waves wait for the scales
         for (int c = c_begin; c < c_end; ++c) {
             set_chunk_priority(c);
@@ -499,6 +565,15 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(SsdArgs a)
             }
         }
     } else {
+        // Where a piece's accumulators lie in the workspace (SHARED only).  They are stored and loaded at device scope, past the
+        // caches of the XCD, on whichever of them the piece behind runs: a release fence would write back the XCD's whole cache, and
+        // 448 of them took 80 us of a launch.
+        constexpr int kDeviceScope = 16;  // the instructions' SC1 bit
+        auto left_state = [&](int cut) {
+            if constexpr (SHARED)
+                return __builtin_amdgcn_make_buffer_rsrc(a.rounds.state + (size_t)cut * (kP * kN), 0, 4 * kP * kN, 0x00020000);
+        };
+        auto left_at = [&](int pt, int wave, int rg, int lane) { return (int)(4 * segment_state_at(0, pt, wave, rg, lane)); };
         // ================= state waves: staging, token weights, state update ================= Carried state in x-code
         // * B-code units times kStScale (true state = s_x(p) s_B * st / kStScale): the state is carried already
         // narrowed by 2^-7, so that its fp16 copy for the C.H product needs no multiply (the factor rides on the token
@@ -553,7 +628,41 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(SsdArgs a)
                 br[k] = *reinterpret_cast<const u32x4 *>(bbase + (row * b_row + 16u * bn16));
             }
         };
+        int left_now = 0;  // (asked for in front of the chunk's loads: results return in order)
+        if constexpr (SHARED)
+            if (c_begin > 0 && wave == 0) left_now = __hip_atomic_load(a.rounds.left + cut, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         issue_loads(c_begin);
+        if constexpr (SHARED) {
+            // The piece goes on from the accumulators that the piece in front of it left in the workspace.  That one waits for
+            // nobody, and its workgroup comes well in front of this one.  Should it not be there after some milliseconds all the same,
+            // the walk begins at the sequence's start, which gives the same results.
+            if (c_begin > 0) {
+                if (wave == 0 && lane == 0) {
+                    int n = left_now;
+                    for (int i = 0; n < 4 && i < a.rounds.polls; ++i) {
+                        __builtin_amdgcn_s_sleep(8);
+                        n = __hip_atomic_load(a.rounds.left + cut, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                    *s_left = n >= 4 && a.rounds.polls >= 0;  // (below zero, in tests: as if it never came)
+                }
+                __syncthreads();
+                if (__builtin_amdgcn_readfirstlane(*s_left)) {
+#pragma unroll
+                    for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+                        for (int rg = 0; rg < 4; ++rg) {
+                            const f32x4 v = __builtin_bit_cast(
+                                f32x4, __builtin_amdgcn_raw_buffer_load_b128(left_state(cut), left_at(pt, wave, rg, lane), 0, kDeviceScope));
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) st[pt][4 * rg + i] = v[i];
+                        }
+                } else {
+                    c_begin = 0;
+                    convert_init = a.init_state != nullptr;
+                    issue_loads(c_begin);
+                }
+            }
+        }
         if (SEG && seg > 0) {
             // Start state of segment seg from the state pass: with local_j the state segment j ends with when started
             // from zero (segment 0: from the caller's initial state) and d_j the sum of dt*A*log2(e) over its tokens,
@@ -791,7 +900,23 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(SsdArgs a)
             __syncthreads();  // the output waves are done with x, B, the weights and the fp16 state of this chunk
         }
 
-        if (a.state && (!SEG || seg + 1 == a.nseg)) {
+        if constexpr (SHARED) {
+            if (c_end < nchunks) {  // the accumulators for the piece behind, then a count for each of the four waves
+#pragma unroll
+                for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+                    for (int rg = 0; rg < 4; ++rg) {
+                        f32x4 v;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[i] = st[pt][4 * rg + i];
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), left_state(cut), left_at(pt, wave, rg, lane), 0,
+                                                               kDeviceScope);
+                    }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores have been performed
+                if (lane == 0) __hip_atomic_fetch_add(a.rounds.left + cut, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        if (a.state && c_end == nchunks) {
 #pragma unroll
             for (int pt = 0; pt < PT; ++pt) {
                 const int p = pt * 32 + l32;
@@ -1122,30 +1247,40 @@ bool prefill_mfma_supports(const quamba_ssd_shape_t &s) { return s.headdim == kP
 
 namespace {
 
-template <bool PRECISE, int PT, bool GATED, bool SEG>
-hipError_t launch_scan_seg(const SsdArgs &a, hipStream_t stream)
+template <bool PRECISE, int PT, bool GATED, Walk WALK>
+hipError_t launch_walk(const typename WalkArgs<WALK>::type &a, unsigned workgroups, hipStream_t stream)
 {
     constexpr int lds = GATED ? Lds<PT>::kBytesGated : Lds<PT>::kBytes;
-    const int segs = a.nseg > 1 ? a.nseg : 1;  // one set of workgroups per segment
-    const dim3 grid((unsigned)(a.s.batch * a.s.nheads * (2 / PT) * segs));
-    const hipError_t e = allow_full_lds<prefill_mfma_kernel<PRECISE, PT, GATED, SEG>>();
+    const hipError_t e = allow_full_lds<prefill_mfma_kernel<PRECISE, PT, GATED, WALK>>();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((prefill_mfma_kernel<PRECISE, PT, GATED, SEG>), grid, dim3(kThreads), lds, stream, a);
+    hipLaunchKernelGGL((prefill_mfma_kernel<PRECISE, PT, GATED, WALK>), dim3(workgroups), dim3(kThreads), lds, stream, a);
     return hipGetLastError();
 }
 
 template <bool PRECISE, int PT, bool GATED>
 hipError_t launch_scan_gated(const SsdArgs &a, hipStream_t stream)
 {
+    const unsigned wgs = (unsigned)(a.s.batch * a.s.nheads * (2 / PT));
     if constexpr (PT == 2)  // segments of channel halves are the wide kernel's
-        if (a.nseg > 1) return launch_scan_seg<PRECISE, PT, GATED, true>(a, stream);
-    return launch_scan_seg<PRECISE, PT, GATED, false>(a, stream);
+        if (a.nseg > 1) return launch_walk<PRECISE, PT, GATED, Walk::segment>(a, wgs * a.nseg, stream);  // one set of workgroups per segment
+    return launch_walk<PRECISE, PT, GATED, Walk::whole>(a, wgs, stream);
 }
 
 template <bool PRECISE, int PT>
 hipError_t launch_scan(const SsdArgs &a, hipStream_t stream)
 {
     return a.z ? launch_scan_gated<PRECISE, PT, true>(a, stream) : launch_scan_gated<PRECISE, PT, false>(a, stream);
+}
+
+template <bool PRECISE>
+hipError_t launch_shared(const SharedArgs &a, hipStream_t stream)
+{
+    const SharedRounds &r = a.rounds;
+    hipLaunchKernelGGL(clear_counts_kernel, dim3(1), dim3(512), 0, stream, r.left, (SharedRounds::kPlaces - 1) * r.groups);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const unsigned wgs = (unsigned)(r.steps * r.groups);
+    return a.z ? launch_walk<PRECISE, 2, true, Walk::shared>(a, wgs, stream) : launch_walk<PRECISE, 2, false, Walk::shared>(a, wgs, stream);
 }
 
 // The state pass of a sequence split: segments 0 .. nseg-2, one workgroup per (segment, sequence, head or channel half).
@@ -1310,8 +1445,96 @@ PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, const PrefillOperands
     return plan;
 }
 
+namespace {
+
+// Launches of more pairs than the device holds workgroups (`all`, two to a unit) whose last round would leave most places empty: a
+// workgroup walks its pair for as long as a full round takes, or three quarters of that where it has its unit to itself,
+// while the other places stand idle.  Here every 8 places of a round (a group; all on one XCD) share their pairs: the
+// pairs of a group stand in a line that is cut into 8 equal parts, one for a place.  A pair that lies across a cut is walked in two
+// pieces, up to some chunk by the place behind the cut, as the first thing it does, and from there on by the place in front of
+// it, as its last, from the accumulators that the first piece leaves in the workspace: the same operations on the same numbers as an
+// uncut walk.  Pieces are workgroups of one launch, in the order in which they start; first pieces wait for nobody.  Of
+// launches of several rounds the last two are shared.
+//
+// The cuts cost about 2 chunks' time and 0.15 of a pair's walk (one more workgroup's start, the state through memory, the
+// launch that clears the counts, ends that are less even than the cuts), so the rule asks for more idle time than that.  Measured,
+// whole pairs / shared (us, with the final state where not said otherwise): 560 pairs, 2048 tokens 144 / 121; 640: 146 / 131, 1024 tokens
+// 80 / 75.5, 4096 without the state 244 / 221; 720, 1800 tokens 147 / 138; 800, 2048 tokens 180 / 163; 1152, 2048 tokens 233 / 223.  Not taken by
+// the rule: 768, 1024 tokens 83 / 85; 896, 2048 tokens 182 / 176; 1280, 1024 tokens 128.5 / 132; 960, 1500 tokens 149 / 149.
+//
+// The second of two workgroups on a unit falls behind the first (see set_chunk_priority).  Where nearly all of a launch is in its first
+// round, those of its second half are paced as without sharing (560 pairs 124 -> 119); elsewhere the later pieces, which come
+// second to nearly every unit, are (640 pairs 130 -> 129, of 4096 tokens 222 -> 218, paced as the former 224).
+SharedRounds shared_rounds(const quamba_ssd_shape_t &s)
+{
+    constexpr int places = SharedRounds::kPlaces;
+    SharedRounds r = {};  // steps == 0: not for this shape
+    const int64_t pairs = (int64_t)s.batch * s.nheads, groups = 2 * compute_units() / places;
+    const int nchunks = (s.seqlen + kQ - 1) / kQ;
+    if (!prefill_mfma_supports(s) || (s.flags & QUAMBA_FLAG_NO_SEQ_SPLIT) || groups == 0 || pairs > INT_MAX / 4 || nchunks < 8) return r;
+    const int64_t all = groups * places, over = pairs % all;
+    const int64_t idle = (over <= all / 2 ? all - all / 4 : all) - over;  // places' worth of a full round
+    if (pairs < all || over == 0 || nchunks * (100 * idle / all - 15) <= 200) return r;
+    const int jobs = (int)((pairs + groups - 1) / groups);  // of the group with the most
+    const int shared = jobs % places ? places + jobs % places : 2 * places;
+    r.groups = (int)groups;
+    r.lead = jobs - shared;
+    int64_t start[2 * places + places - 2];
+    int n = 0;
+    for (int k = 0; k < places; ++k) {
+        auto cut = [&](int i) { return ((int64_t)i * shared * nchunks + places / 2) / places; };
+        const int64_t lo = cut(k), hi = cut(k + 1);
+        for (int64_t j = lo / nchunks; j * nchunks < hi; ++j) {
+            const int64_t from = std::max<int64_t>(lo - j * nchunks, 0), to = std::min<int64_t>(hi - j * nchunks, nchunks);
+            SharedRounds::Piece p = {0, nchunks, (int16_t)j, 0};
+            if (from > 0) {
+                p.c_end = (int)(to - from);
+                p.cut = (int16_t)(k - 1);
+            } else if (to < nchunks) {
+                p.c_begin = (int)(nchunks - to);
+                p.cut = (int16_t)k;
+            }
+            const int64_t t = std::max<int64_t>(j * nchunks - lo, 0);
+            int i = n++;
+            for (; i > 0 && start[i - 1] > t; --i) {  // in the order in which they start
+                start[i] = start[i - 1];
+                r.piece[i] = r.piece[i - 1];
+            }
+            start[i] = t;
+            r.piece[i] = p;
+        }
+    }
+    r.steps = r.lead + n;
+    r.polls = 1 << 14;
+    return r;
+}
+
+size_t shared_rounds_bytes(const SharedRounds &r)
+{
+    return (size_t)(SharedRounds::kPlaces - 1) * r.groups * (sizeof(float) * kP * kN + sizeof(int));
+}
+
+}  // namespace
+
+bool prefill_mfma_shares_rounds(const quamba_ssd_shape_t &s) { return shared_rounds(s).steps != 0; }
+
+hipError_t launch_prefill_shared(const SsdArgs &a, void *workspace, bool precise, int polls, hipStream_t stream)
+{
+    SharedArgs sa = {a, shared_rounds(a.s)};
+    SharedRounds &r = sa.rounds;
+    const size_t cuts = (size_t)(SharedRounds::kPlaces - 1) * r.groups;
+    r.state = static_cast<float *>(workspace);
+    r.left = reinterpret_cast<int *>(r.state + cuts * kP * kN);
+    if (polls) r.polls = polls;
+    const int64_t all = (int64_t)SharedRounds::kPlaces * r.groups, over = (int64_t)a.s.batch * a.s.nheads % all;
+    sa.pace_first = (int)(5 * over < all ? all / 2 : all);
+    return precise ? launch_shared<true>(sa, stream) : launch_shared<false>(sa, stream);
+}
+
 size_t prefill_mfma_workspace_bytes(const quamba_ssd_shape_t &s)
 {
+    const SharedRounds r = shared_rounds(s);
+    if (r.steps) return shared_rounds_bytes(r);
     const Split split = largest_split(s);
     if (split.nseg < 2) return 0;
     const size_t pairs = (size_t)s.batch * s.nheads;
@@ -1353,6 +1576,9 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
         return (wgs > cus + cus / 2 && wgs <= 2 * (int64_t)cus && chunks_per_wg >= 8) ? cus : INT_MAX;
     };
     const int nchunks = (a.s.seqlen + kQ - 1) / kQ;
+    // (not with a final state in the place of the initial one: a piece that starts over would read it)
+    if (workspace && !in_place && reinterpret_cast<uintptr_t>(workspace) % 16 == 0 && prefill_mfma_shares_rounds(a.s))
+        return launch_prefill_shared(a, workspace, precise, 0, stream);
     if (plan.nseg < 2) {
         a.pace_first = pace(1, nchunks);
         return launch(a);

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <cstddef>
 
 #include "quamba_ssd.h"
 
@@ -77,6 +78,8 @@ struct SsdArgs {
                                // workgroups of a compute unit are to be kept at the same pace (see the kernel), else
                                // INT_MAX
 };
+
+static_assert(sizeof(SsdArgs) == 224 && offsetof(SsdArgs, z) == 152 && offsetof(SsdArgs, pace_first) == 216, "tests/test_gpu_prefill.py repeats the layout");
 
 // Plan of the matrix-core prefill for a shape on the current device: segments of the sequence split (1 = no split), chunks per
 // segment, whether every head is cut into two workgroups of 32 channels each, and whether the workgroups are the wide
@@ -333,6 +336,10 @@ bool mamba1_scan_supports_any(const quamba_ssd_shape_t &s);
 hipError_t launch_prefill_generic(const SsdArgs &a, hipStream_t stream);
 bool prefill_mfma_supports(const quamba_ssd_shape_t &s);
 hipError_t launch_prefill_mfma(const SsdArgs &a, void *workspace, hipStream_t stream);
+// Launches whose last round of workgroups is shared (prefill_mfma.hip).  polls: how often a piece looks for the one in front of it
+// before it does without; 0: the default; below 0: it does without.
+bool prefill_mfma_shares_rounds(const quamba_ssd_shape_t &s);
+hipError_t launch_prefill_shared(const SsdArgs &a, void *workspace, bool precise, int polls, hipStream_t stream);
 hipError_t launch_prefill_wide(const SsdArgs &a, bool halves, bool precise, hipStream_t stream);
 bool prefill_generic_supports(const quamba_ssd_shape_t &s);
 

@@ -103,6 +103,18 @@ def test_workspace_of_the_sequence_split():
     assert q.quamba_ssd_prefill_workspace_size(_shape(batch=1, seqlen=512, nheads=24, ngroups=1, **mm)) == 0
 
 
+def test_workspace_of_shared_rounds():
+    """Batches that leave most places of their last round of 512 workgroups empty: 7 states and counts for each of 64 groups.  Full rounds,
+    rounds that are full enough and short sequences need none."""
+    mm = dict(headdim=64, d_state=128, chunk=256, n_head_clusters=1, n_chan_clusters=1, ngroups=1)
+    need = 7 * 64 * (4 * 64 * 128 + 4)
+    for pairs, seqlen in ((513, 1024), (640, 1024), (640, 2048), (800, 2048), (1152, 1024), (2048 + 64, 1025)):
+        assert q.quamba_ssd_prefill_workspace_size(_shape(batch=1, nheads=pairs, seqlen=seqlen, **mm)) == need
+    for pairs, seqlen in ((512, 4096), (640, 300), (768, 1024), (896, 2048), (1024, 4096), (1280, 1024)):
+        assert q.quamba_ssd_prefill_workspace_size(_shape(batch=1, nheads=pairs, seqlen=seqlen, **mm)) == 0
+    assert q.quamba_ssd_prefill_workspace_size(_shape(batch=1, nheads=640, seqlen=2048, flags=q.FLAG_NO_SEQ_SPLIT, **mm)) == 0
+
+
 def test_noalloc_prefill_validates_like_the_prefill():
     lib = q.load_library()
     dummy = C.create_string_buffer(64)

@@ -1,4 +1,6 @@
 """GPU parity of quamba_ssd_prefill against the fp64 oracle (through the C ABI)."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -218,6 +220,70 @@ def test_equal_sequences_of_one_call_have_equal_results(gpu_lib, batch, H, G, L)
         assert all(np.array_equal(yg[i], yg[0]) for i in range(1, batch))
         if want_state:
             assert all(np.array_equal(hg[i], hg[0]) for i in range(1, batch))
+
+
+class _Args(C.Structure):
+    """SsdArgs of csrc/quamba_internal.h."""
+    _fields_ = ([("shape", C.c_int32 * 10)] + [(n, C.c_void_p) for n in ("x_scales", "head_end", "chan_end", "B_scales", "C_scales", "x",
+                "B", "C", "dt", "A", "D", "init", "state", "y", "z")] + [("z_scale", C.c_float), ("dt_q", C.c_void_p), ("dt_scale", C.c_float),
+                ("dt_bias", C.c_void_p), ("nseg", C.c_int32), ("seg_chunks", C.c_int32), ("seg_state", C.c_void_p),
+                ("seg_decay", C.c_void_p), ("pace_first", C.c_int32)])
+
+
+@pytest.mark.parametrize("batch,H,G,L,operands", [
+    (11, 48, 1, 1024, ("state",)),                    # 528 pairs, 8 chunks: the fewest of both
+    (5, 128, 8, 1030, ("state", "init")),             # 640 pairs, the last chunk of 6 tokens
+    (7, 80, 1, 1500, ("gate", "codes", "init")),      # 560 pairs: groups of 8 and 9
+    (10, 80, 1, 2048, ("state", "gate")),             # 800 pairs: more than half of a second round
+    (9, 128, 8, 1100, ("state", "codes")),            # 1152 pairs: whole ones in front
+    (17, 31, 1, 1290, ()),                            # 527 pairs: no multiple of 8
+    (5, 129, 1, 1290, ("gate", "state", "codes", "init"))])
+def test_shared_rounds_give_the_unshared_launch_bit_for_bit(gpu_lib, batch, H, G, L, operands):
+    """Pairs walked in two pieces by two workgroups (calls with a workspace), and pieces that do without the one in front of them,
+    against the launch of whole pairs (calls without a workspace), whose results other tests compare with the oracle."""
+    import torch
+    q = gpu_lib
+    s = W.CONFIGS["m2_8b_b1"].with_(batch=batch, seqlen=L, nheads=H, ngroups=G)
+    sc = make_problem(s.with_(batch=1, seqlen=128), 90, calib_tokens=256)[0]
+    dsc, shape = q.DeviceScales(host_scales(q, sc)), to_shape(q, s)
+    d = torch.Generator(device="cuda").manual_seed(H + L)
+    code = lambda *n: torch.randint(-127, 128, n, generator=d, device="cuda", dtype=torch.int8)
+    real = lambda *n: torch.randn(n, generator=d, device="cuda")
+    x, B, Cq = code(batch, L, H, 64), code(batch, L, G, 128) // 8, code(batch, L, G, 128) // 8
+    A, D = -torch.exp(2.7 * torch.rand(H, generator=d, device="cuda")), real(H)
+    pre = real(batch, L, H) - 3.0
+    gate = {}
+    if "gate" in operands:
+        gate.update(z=code(batch, L, H, 64), z_scale=0.03)
+    if "codes" in operands:
+        gate.update(dt_q=(pre * 20).clamp(-128, 127).to(torch.int8), dt_scale=0.05, dt_bias=real(H) * 0.1)
+    dt = None if "codes" in operands else torch.nn.functional.softplus(pre)
+    init = real(batch, H, 64, 128) if "init" in operands else None
+    need = q.quamba_ssd_prefill_workspace_size(shape)
+    assert 0 < need < 16 << 20
+    results = []
+    for how in ("whole", "shared", "again", "alone"):
+        y = torch.full((batch, L, H, 64), float("nan"), dtype=torch.float16, device="cuda")
+        fin = torch.full((batch, H, 64, 128), float("nan"), device="cuda") if "state" in operands else None
+        if how != "again":
+            ws = torch.full((need,), 0x5A, dtype=torch.uint8, device="cuda")
+        if how != "alone":
+            q.quamba_ssd_prefill(shape, dsc, x, B, Cq, dt, A, D, init, y, fin, None if how == "whole" else ws,
+                                 gate=q.Gate(**gate) if gate else None)
+        else:
+            p = lambda t: t.data_ptr() if t is not None else None
+            a = _Args((C.c_int32 * 10).from_buffer_copy(shape), *(p(t) for t in dsc.tensors), p(x), p(B), p(Cq), p(dt), p(A), p(D), p(init), p(fin), p(y), p(gate.get("z")), gate.get("z_scale", 0.0),
+                      p(gate.get("dt_q")), gate.get("dt_scale", 0.0), p(gate.get("dt_bias")), 1, 0, None, None, 2**31 - 1)
+            f = q.load_library()._ZN6quamba21launch_prefill_sharedERKNS_7SsdArgsEPvbiP12ihipStream_t
+            assert f(C.byref(a), C.c_void_p(p(ws)), C.c_bool(fin is not None), -1,
+                     C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        torch.cuda.synchronize()
+        results.append((y, fin))
+    y0, h0 = results[0]
+    assert torch.isfinite(y0).all()
+    for how, (y, h) in zip(("shared", "again", "alone"), results[1:]):
+        assert torch.equal(y0.view(torch.int16), y.view(torch.int16)), how
+        assert h0 is None or torch.equal(h0, h), how
 
 
 @pytest.mark.parametrize("H,G,L,segments", [
