@@ -134,19 +134,20 @@ __device__ __forceinline__ u32x4 load_codes(const int8_t *row, int t, int L)
 // rounding per code: 8.2e-8 instead of 7.7e-8 (rms) in the sum, under the 2e-4 of the fp16 output, whose error against 64 bits
 // is the same to four digits; exact codes, with x read again for the skip term at the end, took 1 to 2 % longer.
 // Measured at 4 x 4096 tokens, 5120 channels: 308 to 321 us (387 to 393 with fp16 operands, tiles of 1024
-// tokens and the exponentials between the other instructions); 1003 tokens of one sequence: 28.5 us, with gate and step-size
+// tokens and the exponentials between the other instructions); 1003 tokens of one sequence in workgroups of 24: 28.5 us, with gate and step-size
 // codes 30.6 (32 to 34 with workgroups of 8 channels, 36.5 with 512 threads, 3000 with one thread per channel, which is what a length
 // that is no multiple of 16 took before).  By the counters 36 cycles of a SIMD per 64 elements; the loop's instructions take 23 where all
 // plain ones of two waves issue together, 33 where none do.
-template <int LPC, int kThreads, int NS, bool HALVES = false>
+template <int LPC, int kThreads, int NS, bool HALVES = false, int kTiles = 1, bool MIXED = false>
 __device__ __forceinline__ void scan_channels(
     const SsdArgs &a, const float *A, const float *init, float *fin, int b, unsigned blk,  // the sequence, which kThreads / LPC of its channels
-    f32x4 *s_B, f32x4 *s_C,  // [state][quarter][lane]
+    f32x4 *s_B, f32x4 *s_C,  // [state][quarter][lane of a tile, kTiles of them]
     float2 *s_AH,            // [channel][state]: A log2(e), the state before the tile
     float *s_silu)           // SiLU(z_scale * code), by the gate code's byte
 {
-    constexpr int N = 16, kTile = LPC * kE, kCh = kThreads / LPC;  // channels of the workgroup
-    constexpr bool kAlone = LPC == 64 && NS == 16, kAhead = kAlone || kThreads == 768;
+    constexpr int N = 16, kTile = LPC * kE, kCh = MIXED ? 20 : kThreads / LPC;  // channels of the workgroup
+    constexpr int kLanes = LPC * kTiles, kStagers = kThreads / kLanes;
+    constexpr bool kAlone = LPC == 64 && NS == 16 && !MIXED, kAhead = kAlone || kThreads == 768;
     // Lanes of a scan.  In mamba1_scan_halves_kernel the 64 lanes of a channel take their tile as two of 32 lanes, one after the other,
     // and groups of 32 lanes decide for themselves where a number is not finite: the same operations, bit for bit, in both parts of
     // its launch, so that equal sequences of a call have equal results.
@@ -154,7 +155,8 @@ __device__ __forceinline__ void scan_channels(
     constexpr int kScan = kTwo ? 32 : LPC;
     const int D = a.s.headdim, L = a.s.seqlen;
     const int sub = threadIdx.x & (LPC - 1);  // the lane inside its channel's group
-    const int ch = threadIdx.x / LPC;         // the channel inside the workgroup
+    const int ch = MIXED && LPC == 64 ? 16 + (threadIdx.x - 512) / 64 : threadIdx.x / LPC;  // the channel inside the workgroup
+    const int stage_lane = threadIdx.x & (kLanes - 1), stager = threadIdx.x / kLanes;
     const int d = blk * kCh + ch;
     const bool own = d < D;                   // lanes without a channel redo the last one and store nothing
     const int dd = own ? d : D - 1;
@@ -204,22 +206,22 @@ __device__ __forceinline__ void scan_channels(
         }
     };
     auto stage_bc = [&](const u32x4 &v, int r) {
-        f32x4 *dst = (r < NS ? s_B : s_C) + (r & (NS - 1)) * 4 * LPC + sub;
+        f32x4 *dst = (r < NS ? s_B : s_C) + (r & (NS - 1)) * 4 * kLanes + stage_lane;
         const float f = r < NS ? 1.0f : sC;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            dst[q * LPC] = (f32x4){byte_to_float(v[q], 0) * f, byte_to_float(v[q], 1) * f, byte_to_float(v[q], 2) * f,
+            dst[q * kLanes] = (f32x4){byte_to_float(v[q], 0) * f, byte_to_float(v[q], 1) * f, byte_to_float(v[q], 2) * f,
                                    byte_to_float(v[q], 3) * f};
     };
     // The lane's 16 codes of every row of B and C that it stages, requested together (one after the other: 6400 channels of two
     // sequences, 4096 tokens 222.8 -> 217.2 us, 5120 channels of one with side inputs 104.7 -> 103.1).
-    constexpr int kTrips = (2 * NS + kCh - 1) / kCh;
+    constexpr int kTrips = (2 * NS + kStagers - 1) / kStagers;
     u32x4 xq, raw[4], bc[kTrips];
     auto load_rows = [&](int t0, int n0) {
 #pragma unroll
         for (int i = 0; i < kTrips; ++i) {
-            const int r = min(ch + i * kCh, 2 * NS - 1);
-            bc[i] = load_codes((r < NS ? a.B : a.C) + ((size_t)b * N + n0 + (r & (NS - 1))) * L, t0 + kE * sub, L);
+            const int r = min(stager + i * kStagers, 2 * NS - 1);
+            bc[i] = load_codes((r < NS ? a.B : a.C) + ((size_t)b * N + n0 + (r & (NS - 1))) * L, t0 + kE * stage_lane, L);
         }
     };
     // Where a unit has one workgroup of 2 waves per SIMD, nothing covers the loads between two tiles: there the next tile's are in
@@ -230,7 +232,7 @@ __device__ __forceinline__ void scan_channels(
         load_rows(t0, 0);
     };
     if constexpr (kAlone) load_ahead(0);
-    for (int t0 = 0; t0 < L; t0 += kTile) {
+    for (int t0 = 0, slot = 0; t0 < L; t0 += kTile, slot = kTiles > 1 ? (slot + 1) % kTiles : 0) {
         if constexpr (!kAlone) load_tile(t0, xq, raw);
         size_t row;
         int t;
@@ -261,15 +263,17 @@ __device__ __forceinline__ void scan_channels(
         }
 #pragma unroll 1
         for (int n0 = 0; n0 < N; n0 += NS) {
-            if (!kAlone) load_rows(t0, n0);
-            __syncthreads();  // the workgroup is done with the states before
-            // the tile's NS rows each of B and C codes, 16 codes per thread and trip
+            if (kTiles == 1 || slot == 0) {
+                if (!kAlone) load_rows(t0, n0);
+                __syncthreads();  // the workgroup is done with the states before
+                // the tile's NS rows each of B and C codes, 16 codes per thread and trip
 #pragma unroll
-            for (int i = 0; i < kTrips; ++i)
-                if (ch + i * kCh < 2 * NS) stage_bc(bc[i], ch + i * kCh);
-            if constexpr (kAlone)
-                if (t0 + kTile < L) load_ahead(t0 + kTile);
-            __syncthreads();
+                for (int i = 0; i < kTrips; ++i)
+                    if (stager + i * kStagers < 2 * NS) stage_bc(bc[i], stager + i * kStagers);
+                if constexpr (kAlone)
+                    if (t0 + kTile < L) load_ahead(t0 + kTile);
+                __syncthreads();
+            }
 #pragma unroll 1
             for (int n = 0; n < NS; ++n) {
                 const float2 ah = s_AH[ch * N + n0 + n];
@@ -286,7 +290,7 @@ __device__ __forceinline__ void scan_channels(
                 auto ahead = [&](f32x4 (&v)[4], const f32x4 *from) {
                     if constexpr (kAhead) {
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) v[q] = from[(n * 4 + q) * LPC + sub];
+                        for (int q = 0; q < 4; ++q) v[q] = from[(n * 4 + q) * kLanes + slot * LPC + sub];
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 };
@@ -294,7 +298,7 @@ __device__ __forceinline__ void scan_channels(
                 exp2_burst(dec, P);  // P becomes the product of the lane's 16 decay factors
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const f32x4 Bv = kAhead ? Bn[q] : s_B[(n * 4 + q) * LPC + sub];
+                    const f32x4 Bv = kAhead ? Bn[q] : s_B[(n * 4 + q) * kLanes + slot * LPC + sub];
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const int i = 4 * q + k;
@@ -340,7 +344,7 @@ __device__ __forceinline__ void scan_channels(
                 if (sub == last) s_AH[ch * N + n0 + n].y = carry;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const f32x4 Cv = kAhead ? Cn[q] : s_C[(n * 4 + q) * LPC + sub];
+                    const f32x4 Cv = kAhead ? Cn[q] : s_C[(n * 4 + q) * kLanes + slot * LPC + sub];
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const int i = 4 * q + k;
@@ -390,6 +394,24 @@ __global__ __launch_bounds__(kThreads, kThreads == 768 ? 3 : 4) void mamba1_scan
     __shared__ float2 s_AH[kThreads / LPC * 16];
     __shared__ float s_silu[256];
     scan_channels<LPC, kThreads, NS>(a, A, init, fin, blockIdx.y, blockIdx.x, s_B, s_C, s_AH, s_silu);
+}
+
+// 20 channels per workgroup of 12 waves, one to a compute unit: 16 on 32 lanes each in waves 0..7, the other 4 on 64 lanes each in
+// waves 8..11, so that each of the four SIMDs has the work of 5 channels.  (Groups of 32 lanes alone are 6 channels on some or all of
+// them: 24 channels per workgroup leave a sixth of the units without one, 20 on 10 waves load two SIMDs with three waves.)  B
+// and C of 1024 tokens are staged at a time, one tile of a channel on 64 lanes, two of one on 32.  Bound by the vector ALU as
+// above.  5120 channels of one sequence, 24 channels per workgroup / these: 1003 tokens 30.4 / 27.4 us, with state and side inputs
+// 32.4 / 29.2, 1500 43.3 / 40.2, 4096 97.8 / 83.6; 3 x 1536 channels, 4096 tokens 94.6 / 80.0.  500 tokens 18.1 / 18.6: half of the
+// 64 lanes' tile is empty there.
+__global__ __launch_bounds__(768, 3) void mamba1_scan_mixed_kernel(SsdArgs a, const float *A, const float *init, float *fin)
+{
+    __shared__ f32x4 s_B[16 * 4 * 64], s_C[16 * 4 * 64];
+    __shared__ float2 s_AH[20 * 16];
+    __shared__ float s_silu[256];
+    if (threadIdx.x < 512)
+        scan_channels<32, 768, 16, false, 2, true>(a, A, init, fin, blockIdx.y, blockIdx.x, s_B, s_C, s_AH, s_silu);
+    else
+        scan_channels<64, 768, 16, false, 1, true>(a, A, init, fin, blockIdx.y, blockIdx.x, s_B, s_C, s_AH, s_silu);
 }
 
 // The same for groups of 16 channels of all sequences: the first `whole` as workgroups with 32 lanes per channel, each of the others
@@ -575,11 +597,19 @@ Mamba1Form mamba1_scan_form(const quamba_ssd_shape_t &s)
         halves <= (eights / 4 * 32 + alone[eights % 4]) * tokens)
         return Mamba1Form::halves;
     // 24 channels in one workgroup per compute unit where they hold all channels and groups of 16 do not: 4 x 1536 channels, 4096
-    // tokens 110.6 -> 104.1 us, 1003 tokens with side inputs 35.5 -> 31.5; 5120 channels of one sequence 104.2 -> 92.5, 34.3 -> 30.8
-    // (those were three and two workgroups of 8 channels per unit)
+    // tokens 110.6 -> 104.1 us, 1003 tokens with side inputs 35.5 -> 31.5; 5120 channels of one sequence 104.2 -> 92.5
+    // (those were three and two workgroups of 8 channels per unit).  Where 20 per unit hold all channels: mamba1_scan_mixes.
     if (groups > cus && eights > 2 && batch * ((D + 23) / 24) <= cus) return Mamba1Form::channels24;
     if (9 * std::min(c8, c32) <= 8 * c16) return c8 <= c32 ? Mamba1Form::channels8 : Mamba1Form::lanes16;
     return Mamba1Form::lanes32;
+}
+
+// The one workgroup per unit of Mamba1Form::channels24 takes 20 channels, some on 64 lanes, where these hold all and the sequences
+// are longer than a tile of 32 lanes (measured at mamba1_scan_mixed_kernel).
+bool mamba1_scan_mixes(const quamba_ssd_shape_t &s)
+{
+    return mamba1_scan_form(s) == Mamba1Form::channels24 && s.seqlen > 32 * kE &&
+           (int64_t)s.batch * ((s.headdim + 19) / 20) <= compute_units();
 }
 
 hipError_t launch_mamba1_scan(const SsdArgs &a, const float *A, const float *init, float *fin, hipStream_t stream)
@@ -589,7 +619,11 @@ hipError_t launch_mamba1_scan(const SsdArgs &a, const float *A, const float *ini
         case Mamba1Form::lanes32: return launch_scan<32, 512, 16>(a, A, init, fin, stream);
         case Mamba1Form::lanes64: return launch_scan<64, 512, 16>(a, A, init, fin, stream);
         case Mamba1Form::channels8: return launch_scan<32, 256, 8>(a, A, init, fin, stream);
-        case Mamba1Form::channels24: return launch_scan<32, 768, 16>(a, A, init, fin, stream);
+        case Mamba1Form::channels24:
+            if (!mamba1_scan_mixes(a.s)) return launch_scan<32, 768, 16>(a, A, init, fin, stream);
+            hipLaunchKernelGGL(mamba1_scan_mixed_kernel, dim3((unsigned)((a.s.headdim + 19) / 20), (unsigned)a.s.batch), dim3(768), 0, stream, a,
+                               A, init, fin);
+            return hipGetLastError();
         case Mamba1Form::halves: {
             const int64_t groups = (int64_t)a.s.batch * ((a.s.headdim + 15) / 16), whole = whole_groups(a.s);
             hipLaunchKernelGGL(mamba1_scan_halves_kernel, dim3((unsigned)(whole + 2 * (groups - whole))), dim3(512), 0, stream, a, A,

@@ -330,6 +330,7 @@ constexpr int kConvMaxTokens = 32 * kMaxGridY;  // longest sequence of the convo
 // Which kernel takes a scan: by lanes per channel, or channels per workgroup, or mamba1_scan_halves_kernel, or the one for any shape
 enum class Mamba1Form : int { any, lanes16, lanes32, lanes64, channels8, channels24, halves };
 Mamba1Form mamba1_scan_form(const quamba_ssd_shape_t &s);
+bool mamba1_scan_mixes(const quamba_ssd_shape_t &s);  // channels24: mamba1_scan_mixed_kernel
 hipError_t launch_mamba1_scan(const SsdArgs &a, const float *A, const float *init, float *fin, hipStream_t stream);
 hipError_t launch_mamba1_decode(const SsdArgs &a, const float *A, hipStream_t stream);
 bool mamba1_scan_supports_any(const quamba_ssd_shape_t &s);

@@ -353,3 +353,29 @@ def test_infinite_and_zero_states_in_halves_and_in_workgroups_of_8_channels(gpu_
     """... over one tile and several."""
     assert _form(gpu_lib, 2, D, 16, L) == form
     test_infinite_and_zero_states(gpu_lib, D, L)
+
+
+@pytest.mark.parametrize("b,D,L,mixed", [(1, 5120, 513, True),     # a full workgroup on every unit; one token in the second tile of 32 lanes
+                                         (1, 5120, 512, False),    # one tile of 32 lanes
+                                         (1, 5121, 513, False),    # a channel more than 20 per unit
+                                         (3, 1681, 1024, True),    # the last workgroup of a sequence with one channel
+                                         (2, 2137, 1025, True),    # ... with 17: one on 64 lanes; a third tile of one token
+                                         (1, 4300, 2060, True)])
+@pytest.mark.parametrize("sides", [False, True])
+def test_workgroups_of_20_channels_on_32_and_64_lanes(gpu_lib, b, D, L, mixed, sides):
+    """16 channels on 32 lanes and 4 on 64 in one workgroup, at the edges of their rule and of their tiles."""
+    mixes = gpu_lib.load_library()._ZN6quamba17mamba1_scan_mixesERK18quamba_ssd_shape_t
+    mixes.restype = C.c_bool
+    assert mixes(C.byref(_shape(gpu_lib, b, D, 16, L, 4))) == mixed
+    test_scan_with_side_inputs(gpu_lib, b, D, 16, L, 0, sides, sides)
+
+
+def test_infinite_and_zero_states_on_32_and_64_lanes(gpu_lib):
+    test_infinite_and_zero_states(gpu_lib, 2500, 1600)  # two sequences: 20 channels per unit
+
+
+@pytest.mark.parametrize("b,D,L", [(3, 1537, 1300), (1, 5120, 1003)])
+def test_equal_sequences_on_32_and_64_lanes(gpu_lib, b, D, L):
+    """... whose channels are shared out alike; and twice the same call."""
+    for infinite in (False, True):
+        test_equal_sequences_of_one_call_have_equal_results(gpu_lib, b, D, L, "24 channels", infinite)
