@@ -671,6 +671,7 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(typename Walk
             const size_t pairs = (size_t)a.s.batch * H;
             float dsum = 0.0f;
             for (int j = seg - 1; j >= 0; --j) {
+                if (__builtin_amdgcn_readfirstlane(dsum < -dead)) break;  // dead, like a block so far away
                 const float w = exp2_fast(dsum);
 #pragma unroll
                 for (int pt = 0; pt < PT; ++pt) {

@@ -580,6 +580,10 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
             const size_t pairs = (size_t)a.s.batch * H;
             float dsum = 0.0f;
             for (int j = seg - 1; j >= 0; --j) {
+                // Dead, like a block so far away.  The states come from memory one after the other, and the first chunk waits for
+                // them: 24 heads, 2048 tokens in 8 segments 21.8 -> 20.3 us where two of up to seven are alive (decays of 2^-14 a
+                // chunk and more).
+                if (__builtin_amdgcn_readfirstlane(dsum < -dead)) break;
                 const float w = exp2_fast(dsum);
 #pragma unroll
                 for (int pt = 0; pt < PT; ++pt)
