@@ -978,10 +978,10 @@ __global__ __launch_bounds__(kStateThreads, 2) void segment_state_kernel(SsdArgs
     unsigned char *s_xs = smem + LY::kOffXs;
 
     const int L = a.s.seqlen, H = a.s.nheads, G = a.s.ngroups;
-    const int wgs_per_seg = a.s.batch * H * (2 / PT);
-    const int seg = (int)blockIdx.x / wgs_per_seg;  // 0 .. nseg-2
+    asm volatile("" ::"s"(a.x), "s"(a.B), "s"(a.A), "s"(a.dt), "s"(a.seg_state), "s"(a.inv_heads));  // as in prefill_wide_kernel
+    const int seg = quotient((int)blockIdx.x, a.inv_wgs_per_seg);  // 0 .. nseg-2
     const int c_begin = seg * a.seg_chunks, c_end = c_begin + a.seg_chunks;
-    const int bid = (int)blockIdx.x - seg * wgs_per_seg;
+    const int bid = (int)blockIdx.x - seg * a.wgs_per_seg;
     int pair = bid, half = 0;  // as in prefill_mfma_kernel
     if (PT == 1) {
         const int npairs = a.s.batch * H, full = npairs >> 3;
@@ -995,8 +995,9 @@ __global__ __launch_bounds__(kStateThreads, 2) void segment_state_kernel(SsdArgs
         }
     }
     const int p_base = 32 * half;
-    const int bh = block_to_bh(a, pair);
-    const int b = bh / H, h = bh - b * H, g = h / (H / G);
+    int b, h, g;
+    place_of(a, pair, b, h, g);
+    const int bh = b * H + h;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hb = lane >> 5;
@@ -1565,6 +1566,12 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
         if (precise) return plan.channel_split ? launch_scan<true, 1>(args, stream) : launch_scan<true, 2>(args, stream);
         return plan.channel_split ? launch_scan<false, 1>(args, stream) : launch_scan<false, 2>(args, stream);
     };
+    a.wgs_per_seg = (int)pairs * (plan.channel_split ? 2 : 1);
+    a.heads_per_group = a.s.nheads / a.s.ngroups;
+    a.inv_wgs_per_seg = reciprocal(a.wgs_per_seg);
+    a.inv_heads_per_group = reciprocal(a.heads_per_group);
+    a.inv_groups = reciprocal(a.s.ngroups);
+    a.inv_heads = reciprocal(a.s.nheads);
     a.nseg = 1;
     a.seg_chunks = 0;
     a.seg_state = nullptr;

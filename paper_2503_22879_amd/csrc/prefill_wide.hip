@@ -108,13 +108,17 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
     float *s_silu = reinterpret_cast<float *>(smem + LY::kOffSilu);
 
     const int L = a.s.seqlen, H = a.s.nheads, G = a.s.ngroups;
-    const int npairs = a.s.batch * H, wgs_per_seg = (2 / PT) * npairs;
-    const int seg = SEG ? (int)blockIdx.x / wgs_per_seg : 0;
+    // All of the arguments' lines asked for at once, where the compiler would wait for each before it asks for the next (not where a
+    // register would have to go to scratch memory for it).
+    if (PT == 1 || SEG)
+        asm volatile("" ::"s"(a.x), "s"(a.B), "s"(a.C), "s"(a.A), "s"(a.D), "s"(a.seg_state), "s"(a.inv_heads));
+    const int npairs = a.s.batch * H;
+    const int seg = SEG ? quotient((int)blockIdx.x, a.inv_wgs_per_seg) : 0;
     const int nchunks = (L + kQ - 1) / kQ;
     const int c_begin = SEG ? seg * a.seg_chunks : 0;
     const int c_end = (SEG && seg + 1 < a.nseg) ? c_begin + a.seg_chunks : nchunks;
     const bool convert_init = a.init_state && (!SEG || seg == 0);
-    const int bid = SEG ? (int)blockIdx.x - seg * wgs_per_seg : (int)blockIdx.x;
+    const int bid = SEG ? (int)blockIdx.x - seg * a.wgs_per_seg : (int)blockIdx.x;
     int pair = bid, half = 0;
     if (PT == 1) {
         const int full = npairs >> 3;
@@ -128,8 +132,9 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
         }
     }
     const int p_base = 32 * half;
-    const int bh = block_to_bh(a, pair);
-    const int b = bh / H, h = bh - b * H, g = h / (H / G);
+    int b, h, g;
+    place_of(a, pair, b, h, g);
+    const int bh = b * H + h;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave16 = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int role = SEG ? 3 - (wave16 >> 2) : wave16 >> 2, wave = wave16 & 3;

@@ -77,9 +77,12 @@ struct SsdArgs {
     int32_t pace_first;        // matrix-core prefill: first workgroup id of the second dispatch round when the two
                                // workgroups of a compute unit are to be kept at the same pace (see the kernel), else
                                // INT_MAX
+    // Reciprocals for the kernels of short batches (quotient in prefill_tiles.h), whose start counts, and what they divide
+    uint32_t inv_wgs_per_seg, inv_heads_per_group, inv_groups, inv_heads;
+    int32_t heads_per_group, wgs_per_seg;
 };
 
-static_assert(sizeof(SsdArgs) == 224 && offsetof(SsdArgs, z) == 152 && offsetof(SsdArgs, pace_first) == 216, "tests/test_gpu_prefill.py repeats the layout");
+static_assert(sizeof(SsdArgs) == 248 && offsetof(SsdArgs, z) == 152 && offsetof(SsdArgs, pace_first) == 216, "tests/test_gpu_prefill.py repeats the layout");
 
 // Plan of the matrix-core prefill for a shape on the current device: segments of the sequence split (1 = no split), chunks per
 // segment, whether every head is cut into two workgroups of 32 channels each, and whether the workgroups are the wide

@@ -227,7 +227,7 @@ class _Args(C.Structure):
     _fields_ = ([("shape", C.c_int32 * 10)] + [(n, C.c_void_p) for n in ("x_scales", "head_end", "chan_end", "B_scales", "C_scales", "x",
                 "B", "C", "dt", "A", "D", "init", "state", "y", "z")] + [("z_scale", C.c_float), ("dt_q", C.c_void_p), ("dt_scale", C.c_float),
                 ("dt_bias", C.c_void_p), ("nseg", C.c_int32), ("seg_chunks", C.c_int32), ("seg_state", C.c_void_p),
-                ("seg_decay", C.c_void_p), ("pace_first", C.c_int32)])
+                ("seg_decay", C.c_void_p), ("pace_first", C.c_int32), ("not_here", C.c_int32 * 6)])
 
 
 @pytest.mark.parametrize("batch,H,G,L,operands", [
@@ -273,7 +273,7 @@ def test_shared_rounds_give_the_unshared_launch_bit_for_bit(gpu_lib, batch, H, G
         else:
             p = lambda t: t.data_ptr() if t is not None else None
             a = _Args((C.c_int32 * 10).from_buffer_copy(shape), *(p(t) for t in dsc.tensors), p(x), p(B), p(Cq), p(dt), p(A), p(D), p(init), p(fin), p(y), p(gate.get("z")), gate.get("z_scale", 0.0),
-                      p(gate.get("dt_q")), gate.get("dt_scale", 0.0), p(gate.get("dt_bias")), 1, 0, None, None, 2**31 - 1)
+                      p(gate.get("dt_q")), gate.get("dt_scale", 0.0), p(gate.get("dt_bias")), 1, 0, None, None, 2**31 - 1, (C.c_int32 * 6)())
             f = q.load_library()._ZN6quamba21launch_prefill_sharedERKNS_7SsdArgsEPvbiP12ihipStream_t
             assert f(C.byref(a), C.c_void_p(p(ws)), C.c_bool(fin is not None), -1,
                      C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
