@@ -117,6 +117,8 @@ __device__ __forceinline__ const int8_t *token_row(const ConvArgs &a, int b, int
 // What a thread that owns the 4 consecutive channels from c0 needs of them besides its filter: reciprocal output scales
 // (one correctly rounded division each) and where the codes go.  headdim and d_state are multiples of 4 here, so the channels
 // share an output tensor and a head or state group.
+// By reciprocals from the host: three integer divisions more were a tenth of a one-token call (100 sequences of 10240 channels 4.6 -> 4.2
+// us, 256 6.8 -> 6.4, one of 1792 2.52 -> 2.41) and 1 to 3 % of prompts.
 struct Channels4 {
     float inv[4];
     int8_t *dst;
@@ -128,9 +130,10 @@ struct Channels4 {
             SsdArgs t;
             t.s = a.s; t.x_scales = a.x_scales; t.head_cluster_end = a.head_cluster_end;
             t.chan_cluster_end = a.chan_cluster_end;
-            const int h = c0 / a.s.headdim, p0 = c0 - h * a.s.headdim;
+            const int h = quotient(c0, a.inv_headdim), p0 = c0 - h * a.s.headdim;
+            const int g = quotient(h, a.inv_heads_per_group);
             if (a.s.n_chan_clusters <= 4) {  // two memory round trips
-                const Ranges4 r(t, head_cell_lookup(t, h));
+                const Ranges4 r(t, head_cell_lookup(t, g, h - g * a.heads_per_group));
 #pragma unroll
                 for (int j = 0; j < 4; ++j) inv[j] = __fdiv_rn(1.0f, r.pick(p0 + j));
             } else {
@@ -141,7 +144,7 @@ struct Channels4 {
         } else {
             const bool isB = c0 < HP + GN;
             const int cg = c0 - HP - (isB ? 0 : GN);
-            inv[0] = inv[1] = inv[2] = inv[3] = __fdiv_rn(1.0f, (isB ? a.B_scales : a.C_scales)[cg / a.s.d_state]);
+            inv[0] = inv[1] = inv[2] = inv[3] = __fdiv_rn(1.0f, (isB ? a.B_scales : a.C_scales)[quotient(cg, a.inv_d_state)]);
             dst = isB ? a.B_out : a.C_out; row = GN; col = cg;
         }
     }
@@ -400,6 +403,8 @@ __global__ __launch_bounds__(256) void conv1d_q8_any_kernel(ConvArgs a)
 
 bool vec_ok(const ConvArgs &a)
 {
+    const uint64_t Ct = (uint64_t)a.s.nheads * a.s.headdim + 2ull * a.s.ngroups * a.s.d_state;
+    if (Ct * std::max({a.s.headdim, a.s.d_state, a.s.nheads}) >> 32) return false;  // the reciprocals are exact below
     auto al = [](const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
     return a.s.headdim % 16 == 0 && a.s.d_state % 16 == 0 && al(a.in) && al(a.weight) && al(a.bias) && al(a.state_in) &&
            al(a.state_out) && al(a.x_out) && al(a.B_out) && al(a.C_out);
@@ -426,9 +431,14 @@ int conv1d_segment_tokens(const quamba_ssd_shape_t &s, bool same_state)
     return seg;
 }
 
-hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream)
+hipError_t launch_conv1d_q8(const ConvArgs &args, hipStream_t stream)
 {
+    ConvArgs a = args;
     const int Ct = a.s.nheads * a.s.headdim + 2 * a.s.ngroups * a.s.d_state;
+    a.heads_per_group = a.s.nheads / a.s.ngroups;
+    a.inv_headdim = reciprocal(a.s.headdim);
+    a.inv_heads_per_group = reciprocal(a.heads_per_group);
+    a.inv_d_state = reciprocal(a.s.d_state);
     if (vec_ok(a) && a.s.seqlen == 1) {
         // enough waves to fill the chip, then as many sequences per thread as keep it full (the set-up is shared by them)
         const int64_t blocks = (Ct / 4 + 63) / 64;
@@ -436,9 +446,8 @@ hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream)
         const dim3 grid((unsigned)blocks, (unsigned)((a.s.batch + seqs - 1) / seqs));
         hipLaunchKernelGGL(conv1d_q8_step_kernel, grid, dim3(64), 0, stream, a, seqs);
     } else if (vec_ok(a)) {
-        ConvArgs v = a;
-        v.seg = conv1d_segment_tokens(a.s, a.state_in && a.state_in == a.state_out);
-        const dim3 grid((unsigned)((Ct / 4 + 63) / 64), (unsigned)((a.s.seqlen + (int64_t)v.seg - 1) / v.seg),
+        a.seg = conv1d_segment_tokens(a.s, a.state_in && a.state_in == a.state_out);
+        const dim3 grid((unsigned)((Ct / 4 + 63) / 64), (unsigned)((a.s.seqlen + (int64_t)a.seg - 1) / a.seg),
                         (unsigned)a.s.batch);
         // Plain stores where the caches can hold the codes until the scan reads them.  Convolution and scan together,
         // non-temporal / plain, scan without side inputs: 3.5 MiB (2048 tokens of 1792 channels) 31.2 / 30.2 us, 5 MiB 29.1 / 28.7, 10
@@ -447,9 +456,9 @@ hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream)
         // 5 MiB 32.4 / 30.5, 10 56.1 / 51.8, 20 60.6 / 58.1, but from 28 MiB on 1 to 2.4 % longer (84: 208.4 / 213.6).  The
         // convolution does not know what the scan will read; the line is the one without.
         if ((int64_t)a.s.batch * a.s.seqlen * Ct <= 96LL << 20)
-            hipLaunchKernelGGL(conv1d_q8_vec_kernel<true>, grid, dim3(64), 0, stream, v);
+            hipLaunchKernelGGL(conv1d_q8_vec_kernel<true>, grid, dim3(64), 0, stream, a);
         else
-            hipLaunchKernelGGL(conv1d_q8_vec_kernel<false>, grid, dim3(64), 0, stream, v);
+            hipLaunchKernelGGL(conv1d_q8_vec_kernel<false>, grid, dim3(64), 0, stream, a);
     } else {
         const dim3 grid((unsigned)((Ct + 255) / 256), (unsigned)a.s.batch);
         hipLaunchKernelGGL(conv1d_q8_any_kernel, grid, dim3(256), 0, stream, a);

@@ -158,17 +158,6 @@ __device__ __forceinline__ size_t segment_state_at(size_t pair, int q, int wave,
 
 constexpr int kMaxSegments = 8;  // of the sequence split
 
-// x / d from ceil(2^32 / d), exact for x d < 2^32 (the kernels of short batches have at most a few thousand workgroups); 0 stands for
-// d = 1.  An integer division is some 25 dependent instructions, and six of them stood in front of a workgroup's first load: with
-// these, and the arguments' lines asked for together, 24 heads, 2048 tokens (two kernels) 20.3 -> 19.8 us, 1200 tokens 14.9 -> 14.2, 300
-// tokens of 256 heads 12.6 -> 11.8, 1531 of 128 behind the convolution 46.2 -> 45.8.
-inline uint32_t reciprocal(uint32_t d) { return d > 1 ? (uint32_t)((((uint64_t)1 << 32) + d - 1) / d) : 0u; }
-__device__ __forceinline__ int quotient(int x, uint32_t inv)
-{
-    const int q = (int)(((uint64_t)(uint32_t)x * inv) >> 32);
-    return inv ? q : x;
-}
-
 // Workgroup -> (sequence, head).  Hardware hands consecutive workgroup ids to the 8 XCDs round-robin, each XCD with
 // its own L2.  When the number of (sequence, state group) units is a multiple of 8, all heads of a unit are put on
 // one XCD, so that the B and C rows they share are fetched into one L2 instead of eight.
