@@ -190,6 +190,36 @@ __device__ __forceinline__ uint32_t codes_of_windows(const uint32_t (&win)[4], c
 // 16 e = 9.6e-7 and |R| <= |v'|, so a distance of u from its integer of less than 0.5 - 1.3e-6 |v'| - th, th = inv (2.5e-7 +
 // 3e-7 |bias|) + 1e-5, decides the exact sequence's code.  Other codes are redone with it, and all of them where a constant is
 // not finite or so large that a sum could leave the range of fp32 (the only ways to a NaN, which the maximum of four would hide).
+//
+// A SIMD issues plain fp32 instructions of two waves at once, but dot products, exponentials and reciprocals alone (the latter two for
+// 8 cycles), and with those of its waves scattered between the others' plain ones the pairing hardly ever happens.  So they come in
+// bursts of the four channels at raised wave priority.  4 x 4096 tokens of 10240 channels 88.4 -> 79.4 us, 8 x 2048 of 5376 50.5 -> 46.7,
+// 1531 of 10240 13.2 -> 12.6 (exponentials and reciprocals alone: 82.9, 47.8, 12.7; without the priority 87; bursts of two tokens, at 69
+// registers, 84.5, 48.5, 13.3).
+#define QUAMBA_4(ins, args) ins " %0, " args(0) "\n\t" ins " %1, " args(1) "\n\t" ins " %2, " args(2) "\n\t" ins " %3, " args(3) "\n\t"
+#define QUAMBA_SELF(i) "%" #i
+__device__ __forceinline__ void exp2_burst(float (&v)[4])
+{
+    // (the idle cycle is the wait that the use of a result needs)
+    asm volatile("s_setprio 2\n\t" QUAMBA_4("v_exp_f32", QUAMBA_SELF) "s_setprio 0\n\ts_nop 0"
+                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+}
+__device__ __forceinline__ void rcp_burst(float (&v)[4])
+{
+    asm volatile("s_setprio 2\n\t" QUAMBA_4("v_rcp_f32", QUAMBA_SELF) "s_setprio 0\n\ts_nop 0"
+                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+}
+#undef QUAMBA_SELF
+#undef QUAMBA_4
+__device__ __forceinline__ void dot_burst(int (&d)[4], const uint32_t (&win)[4], const u32x4 &w)
+{
+    // (a dot product's result may be read by another kind of instruction three cycles behind it)
+    asm volatile("s_setprio 2\n\tv_dot4_i32_i8 %0, %4, %8, 0\n\tv_dot4_i32_i8 %1, %5, %9, 0\n\tv_dot4_i32_i8 %2, %6, %10, 0\n\t"
+                 "v_dot4_i32_i8 %3, %7, %11, 0\n\ts_setprio 0\n\ts_nop 1"
+                 : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3])
+                 : "v"(win[0]), "v"(win[1]), "v"(win[2]), "v"(win[3]), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]));
+}
+
 struct FastChannels4 {
     f32x4 a, b, t;
     float limit;  // 0.5 less the largest th of the four; negative: always the exact sequence
@@ -211,16 +241,24 @@ struct FastChannels4 {
     __device__ __forceinline__ uint32_t codes(const uint32_t (&win)[4], const u32x4 &w, float s, float minus_s_log2e, const f32x4 &bias,
                                               const float (&inv)[4]) const
     {
-        float e[4];
+        int dots[4];
+        float e[4], E[4], v[4];
         uint32_t o = 0;
+        dot_burst(dots, win, w);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const float acc = (float)__builtin_amdgcn_sdot4((int)win[j], (int)w[j], 0, false);
-            const float E = __builtin_amdgcn_exp2f(__builtin_fmaf(acc, minus_s_log2e, t[j]));
-            const float v = __builtin_fmaf(acc, a[j], b[j]);
-            const float u = __builtin_fmaf(v, __builtin_amdgcn_rcpf(1.0f + E), 128.0f);
+            E[j] = __builtin_fmaf((float)dots[j], minus_s_log2e, t[j]);
+            v[j] = __builtin_fmaf((float)dots[j], a[j], b[j]);
+        }
+        exp2_burst(E);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) E[j] = 1.0f + E[j];
+        rcp_burst(E);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float u = __builtin_fmaf(v[j], E[j], 128.0f);
             o = __builtin_amdgcn_cvt_pk_u8_f32(u, j, o);
-            e[j] = __builtin_fmaf(1.3e-6f, __builtin_fabsf(v), __builtin_fabsf(u - __builtin_rintf(u)));
+            e[j] = __builtin_fmaf(1.3e-6f, __builtin_fabsf(v[j]), __builtin_fabsf(u - __builtin_rintf(u)));
         }
         o ^= 0x80808080u;
         const float m = fmaxf(fmaxf(fmaxf(e[0], e[1]), e[2]), e[3]);
@@ -241,7 +279,7 @@ struct FastChannels4 {
 // a segment of a.seg tokens, the loads of the next 4 in flight; grid = (channel blocks of 64 x 4, segments, batch); one
 // wave per workgroup, no LDS, no barrier.  Bound by the vector ALU where there are enough waves (by the counters 18
 // instructions per code with the set-up and 91 to 97 % busy at 4 x 4096 tokens of 10240 channels), by the chain from launch to
-// store where there are few.  4 channels keep the kernel at 61 registers, so that 8 waves share a SIMD, and the chain short.  With each load
+// store where there are few.  4 channels keep the kernel at 58 registers, so that 8 waves share a SIMD, and the chain short.  With each load
 // waited for where it was made (as the compiler has it for a load behind a branch), and one more rounding, clamp and
 // compare per code: 8 x 2048 tokens of 5376 channels 61 -> 49 us, 4 x 4096 of 10240 108 -> 87 (there with 16 channels per
 // thread), 1 x 4096 32 -> 25, 1531 14.6 -> 11.3; of that the shorter evaluation 5 us of the first.
@@ -403,8 +441,8 @@ __global__ __launch_bounds__(256) void conv1d_q8_any_kernel(ConvArgs a)
 
 bool vec_ok(const ConvArgs &a)
 {
-    const uint64_t Ct = (uint64_t)a.s.nheads * a.s.headdim + 2ull * a.s.ngroups * a.s.d_state;
-    if (Ct * std::max({a.s.headdim, a.s.d_state, a.s.nheads}) >> 32) return false;  // the reciprocals are exact below
+    const uint64_t H = a.s.nheads, P = a.s.headdim, G = a.s.ngroups, N = a.s.d_state;
+    if ((H * P * P | H * (H / G) | G * N * N) >> 32) return false;  // the reciprocals are exact below
     auto al = [](const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
     return a.s.headdim % 16 == 0 && a.s.d_state % 16 == 0 && al(a.in) && al(a.weight) && al(a.bias) && al(a.state_in) &&
            al(a.state_out) && al(a.x_out) && al(a.B_out) && al(a.C_out);
