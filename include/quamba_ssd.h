@@ -101,7 +101,8 @@ typedef struct quamba_ssd_scales_t {
  * (headdim * d_state + 1) floats for the most segments the shape may be cut into.  A call may make fewer segments, or none
  * where the unsplit launch is the faster one, and then leaves the rest untouched.  Non-zero, below 16 MiB, also for batches that would
  * leave most of the device idle in their last round of workgroups: room for the states of the sequences that two workgroups walk one
- * after the other (not with QUAMBA_FLAG_NO_SEQ_SPLIT; the same results, bit for bit).  A call with a NULL, smaller or not 16-byte
+ * after the other (not with QUAMBA_FLAG_NO_SEQ_SPLIT; the same results, bit for bit, where batch * nheads is at least twice the
+ * device's compute units, to rounding below).  A call with a NULL, smaller or not 16-byte
  * aligned workspace is not an error: it takes the unsplit launch (same results to rounding, slower on such batches).  The
  * workspace is scratch: written and read by the call's own launches, contents undefined afterwards; calls that share one
  * workspace must not overlap.  Returns 0 for an invalid shape; quamba_ssd_prefill reports the error.

@@ -92,36 +92,6 @@ struct Lds {
 };
 static_assert(Lds<2>::kBytesGated <= 80 * 1024, "two workgroups must fit the 160 KB LDS of a gfx950 compute unit");
 
-enum class Walk { whole, segment, shared };
-
-// Shared rounds: launches of a few more (sequence, head) pairs than the device holds workgroups (two to a unit).  See shared_rounds.
-struct SharedRounds {
-    static constexpr int kPlaces = 8;  // of a group: workgroups that share its pairs
-    struct Piece {
-        int c_begin, c_end;  // chunks
-        int16_t pair;        // of the group, behind the lead
-        int16_t cut;         // at the piece's end or start
-    };
-    int groups;   // workgroup i: step i / groups of the list of group i % groups
-    int lead;     // steps that are whole pairs, in front of the pieces
-    int steps;    // in all; 0: the launch is not of this kind
-    int polls;    // of a wait for the piece in front
-    float *state; // [cut][group][headdim * d_state]: the accumulators at the cuts
-    int *left;    // [cut][group]: waves that have left their part of them there
-    Piece piece[2 * kPlaces + kPlaces - 2];
-};
-struct SharedArgs : SsdArgs {
-    SharedRounds rounds;
-};
-template <Walk WALK>
-struct WalkArgs {
-    typedef SsdArgs type;
-};
-template <>
-struct WalkArgs<Walk::shared> {
-    typedef SharedArgs type;
-};
-
 // (A kernel, not hipMemsetAsync: the call may be captured into a graph.)
 __global__ void clear_counts_kernel(int *p, int n)
 {
@@ -169,19 +139,8 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(typename Walk
     int c_begin = SEG ? seg * a.seg_chunks : 0;
     int c_end = (SEG && seg + 1 < a.nseg) ? c_begin + a.seg_chunks : nchunks;
     int shared_pair = 0, cut = 0;
-    if constexpr (SHARED) {
-        const int step = (int)blockIdx.x / a.rounds.groups, group = (int)blockIdx.x - step * a.rounds.groups;
-        shared_pair = step;
-        if (step >= a.rounds.lead) {
-            const SharedRounds::Piece piece = a.rounds.piece[step - a.rounds.lead];
-            shared_pair = a.rounds.lead + piece.pair;
-            c_begin = piece.c_begin;
-            c_end = piece.c_end;
-            cut = piece.cut * a.rounds.groups + group;
-        }
-        shared_pair = shared_pair * a.rounds.groups + group;
-        if (shared_pair >= a.s.batch * H) return;  // a group may have one pair less
-    }
+    if constexpr (SHARED)
+        if (!shared_piece(a, shared_pair, cut, c_begin, c_end)) return;
     bool convert_init = a.init_state && c_begin == 0;  // the caller's initial state stands in front of the first chunk
     // with two workgroups per head, ids i and i + 8 (same XCD, and the same compute unit when two workgroups fit one)
     // take the two halves of a head
@@ -565,15 +524,6 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(typename Walk
             }
         }
     } else {
-        // Where a piece's accumulators lie in the workspace (SHARED only).  They are stored and loaded at device scope, past the
-        // caches of the XCD, on whichever of them the piece behind runs: a release fence would write back the XCD's whole cache, and
-        // 448 of them took 80 us of a launch.
-        constexpr int kDeviceScope = 16;  // the instructions' SC1 bit
-        auto left_state = [&](int cut) {
-            if constexpr (SHARED)
-                return __builtin_amdgcn_make_buffer_rsrc(a.rounds.state + (size_t)cut * (kP * kN), 0, 4 * kP * kN, 0x00020000);
-        };
-        auto left_at = [&](int pt, int wave, int rg, int lane) { return (int)(4 * segment_state_at(0, pt, wave, rg, lane)); };
         // ================= state waves: staging, token weights, state update ================= Carried state in x-code
         // * B-code units times kStScale (true state = s_x(p) s_B * st / kStScale): the state is carried already
         // narrowed by 2^-7, so that its fp16 copy for the C.H product needs no multiply (the factor rides on the token
@@ -630,32 +580,14 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(typename Walk
         };
         int left_now = 0;  // (asked for in front of the chunk's loads: results return in order)
         if constexpr (SHARED)
-            if (c_begin > 0 && wave == 0) left_now = __hip_atomic_load(a.rounds.left + cut, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (c_begin > 0 && wave == 0) left_now = left_count(a, cut);
         issue_loads(c_begin);
         if constexpr (SHARED) {
-            // The piece goes on from the accumulators that the piece in front of it left in the workspace.  That one waits for
-            // nobody, and its workgroup comes well in front of this one.  Should it not be there after some milliseconds all the same,
-            // the walk begins at the sequence's start, which gives the same results.
             if (c_begin > 0) {
-                if (wave == 0 && lane == 0) {
-                    int n = left_now;
-                    for (int i = 0; n < 4 && i < a.rounds.polls; ++i) {
-                        __builtin_amdgcn_s_sleep(8);
-                        n = __hip_atomic_load(a.rounds.left + cut, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                    *s_left = n >= 4 && a.rounds.polls >= 0;  // (below zero, in tests: as if it never came)
-                }
+                if (wave == 0 && lane == 0) *s_left = await_left(a, cut, left_now);
                 __syncthreads();
                 if (__builtin_amdgcn_readfirstlane(*s_left)) {
-#pragma unroll
-                    for (int pt = 0; pt < PT; ++pt)
-#pragma unroll
-                        for (int rg = 0; rg < 4; ++rg) {
-                            const f32x4 v = __builtin_bit_cast(
-                                f32x4, __builtin_amdgcn_raw_buffer_load_b128(left_state(cut), left_at(pt, wave, rg, lane), 0, kDeviceScope));
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) st[pt][4 * rg + i] = v[i];
-                        }
+                    read_left_state(a, cut, wave, lane, st);
                 } else {
                     c_begin = 0;
                     convert_init = a.init_state != nullptr;
@@ -901,22 +833,8 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(typename Walk
             __syncthreads();  // the output waves are done with x, B, the weights and the fp16 state of this chunk
         }
 
-        if constexpr (SHARED) {
-            if (c_end < nchunks) {  // the accumulators for the piece behind, then a count for each of the four waves
-#pragma unroll
-                for (int pt = 0; pt < PT; ++pt)
-#pragma unroll
-                    for (int rg = 0; rg < 4; ++rg) {
-                        f32x4 v;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) v[i] = st[pt][4 * rg + i];
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), left_state(cut), left_at(pt, wave, rg, lane), 0,
-                                                               kDeviceScope);
-                    }
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores have been performed
-                if (lane == 0) __hip_atomic_fetch_add(a.rounds.left + cut, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
+        if constexpr (SHARED)
+            if (c_end < nchunks) leave_state(a, cut, wave, lane, st);  // for the piece behind
         if (a.state && c_end == nchunks) {
 #pragma unroll
             for (int pt = 0; pt < PT; ++pt) {
@@ -1281,6 +1199,7 @@ hipError_t launch_shared(const SharedArgs &a, hipStream_t stream)
     hipLaunchKernelGGL(clear_counts_kernel, dim3(1), dim3(512), 0, stream, r.left, (SharedRounds::kPlaces - 1) * r.groups);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (r.wide) return launch_prefill_wide_shared(a, PRECISE, stream);
     const unsigned wgs = (unsigned)(r.steps * r.groups);
     return a.z ? launch_walk<PRECISE, 2, true, Walk::shared>(a, wgs, stream) : launch_walk<PRECISE, 2, false, Walk::shared>(a, wgs, stream);
 }
@@ -1449,9 +1368,9 @@ PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, const PrefillOperands
 
 namespace {
 
-// Launches of more pairs than the device holds workgroups (`all`, two to a unit) whose last round would leave most places empty: a
-// workgroup walks its pair for as long as a full round takes, or three quarters of that where it has its unit to itself,
-// while the other places stand idle.  Here every 8 places of a round (a group; all on one XCD) share their pairs: the
+// Launches of more pairs than the device holds workgroups (`all`) whose last round would leave most places empty: a
+// workgroup walks its pair for as long as a full round takes, or three quarters of that where it is one of two that a unit could
+// have, while the other places stand idle.  Here every 8 places of a round (a group; all on one XCD) share their pairs: the
 // pairs of a group stand in a line that is cut into 8 equal parts, one for a place.  A pair that lies across a cut is walked in two
 // pieces, up to some chunk by the place behind the cut, as the first thing it does, and from there on by the place in front of
 // it, as its last, from the accumulators that the first piece leaves in the workspace: the same operations on the same numbers as an
@@ -1464,6 +1383,14 @@ namespace {
 // 80 / 75.5, 4096 without the state 244 / 221; 720, 1800 tokens 147 / 138; 800, 2048 tokens 180 / 163; 1152, 2048 tokens 233 / 223.  Not taken by
 // the rule: 768, 1024 tokens 83 / 85; 896, 2048 tokens 182 / 176; 1280, 1024 tokens 128.5 / 132; 960, 1500 tokens 149 / 149.
 //
+// From one pair per unit to two, places are units, each with a workgroup of 16 waves (prefill_wide_kernel).  That walks a chunk in
+// 3.1 us, two workgroups of 8 waves two chunks in 5, and unlike theirs its time goes with the chunks of a place, not with those of
+// a pair: 3.15 us for each of them and 12 against 5 us for each of a pair and 8, of which the rule is made (65 and 92 to a pair's 100
+// a chunk).  Workgroups of 8 waves / shared (us, with the final state): 264 pairs, 700 tokens 35.9 / 34.3, 1024 46.6 / 41.0, 2048 85.3 /
+// 68.4, 4096 163.8 / 122.5; 320 pairs 1024 to 4096 tokens 47.1 / 44.5, 89.7 / 74.6, 171.9 / 137.3; 312, 1300 tokens 58.8 / 56.3.  Not
+// taken by the rule: 512 tokens of 264 pairs 27.8 / 28.6, of 320 28.5 / 28.7; 336 pairs, 1300 tokens 59.4 / 60.4; 384 pairs, 1024 tokens
+// 49.0 / 52.5, 2048 89.0 / 86.4 and in another run 90.1 / 91.0, 4096 169.3 / 161.5; 400 pairs, 2048 tokens 90.1 / 94.5, 4096 172.8 / 175.9.
+//
 // The second of two workgroups on a unit falls behind the first (see set_chunk_priority).  Where nearly all of a launch is in its first
 // round, those of its second half are paced as without sharing (560 pairs 124 -> 119); elsewhere the later pieces, which come
 // second to nearly every unit, are (640 pairs 130 -> 129, of 4096 tokens 222 -> 218, paced as the former 224).
@@ -1471,14 +1398,18 @@ SharedRounds shared_rounds(const quamba_ssd_shape_t &s)
 {
     constexpr int places = SharedRounds::kPlaces;
     SharedRounds r = {};  // steps == 0: not for this shape
-    const int64_t pairs = (int64_t)s.batch * s.nheads, groups = 2 * compute_units() / places;
+    const int64_t pairs = (int64_t)s.batch * s.nheads, cus = compute_units();
+    r.wide = pairs > cus && pairs < 2 * cus;
+    const int64_t groups = (r.wide ? cus : 2 * cus) / places;
     const int nchunks = (s.seqlen + kQ - 1) / kQ;
-    if (!prefill_mfma_supports(s) || (s.flags & QUAMBA_FLAG_NO_SEQ_SPLIT) || groups == 0 || pairs > INT_MAX / 4 || nchunks < 8) return r;
+    if (!prefill_mfma_supports(s) || (s.flags & QUAMBA_FLAG_NO_SEQ_SPLIT) || groups == 0 || pairs > INT_MAX / 4 || nchunks < (r.wide ? 2 : 8)) return r;
     const int64_t all = groups * places, over = pairs % all;
     const int64_t idle = (over <= all / 2 ? all - all / 4 : all) - over;  // places' worth of a full round
-    if (pairs < all || over == 0 || nchunks * (100 * idle / all - 15) <= 200) return r;
     const int jobs = (int)((pairs + groups - 1) / groups);  // of the group with the most
     const int shared = jobs % places ? places + jobs % places : 2 * places;
+    if (r.wide ? 65 * ((jobs * nchunks + places - 1) / places) + 92 >= 100 * nchunks
+               : pairs < all || over == 0 || nchunks * (100 * idle / all - 15) <= 200)
+        return r;
     r.groups = (int)groups;
     r.lead = jobs - shared;
     int64_t start[2 * places + places - 2];
@@ -1518,11 +1449,23 @@ size_t shared_rounds_bytes(const SharedRounds &r)
 
 }  // namespace
 
+// What a workgroup finds its place by (place_of).
+static void set_places(SsdArgs &a, bool halves)
+{
+    a.wgs_per_seg = a.s.batch * a.s.nheads * (halves ? 2 : 1);
+    a.heads_per_group = a.s.nheads / a.s.ngroups;
+    a.inv_wgs_per_seg = reciprocal(a.wgs_per_seg);
+    a.inv_heads_per_group = reciprocal(a.heads_per_group);
+    a.inv_groups = reciprocal(a.s.ngroups);
+    a.inv_heads = reciprocal(a.s.nheads);
+}
+
 bool prefill_mfma_shares_rounds(const quamba_ssd_shape_t &s) { return shared_rounds(s).steps != 0; }
 
 hipError_t launch_prefill_shared(const SsdArgs &a, void *workspace, bool precise, int polls, hipStream_t stream)
 {
     SharedArgs sa = {a, shared_rounds(a.s)};
+    set_places(sa, false);
     SharedRounds &r = sa.rounds;
     const size_t cuts = (size_t)(SharedRounds::kPlaces - 1) * r.groups;
     r.state = static_cast<float *>(workspace);
@@ -1566,12 +1509,6 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
         if (precise) return plan.channel_split ? launch_scan<true, 1>(args, stream) : launch_scan<true, 2>(args, stream);
         return plan.channel_split ? launch_scan<false, 1>(args, stream) : launch_scan<false, 2>(args, stream);
     };
-    a.wgs_per_seg = (int)pairs * (plan.channel_split ? 2 : 1);
-    a.heads_per_group = a.s.nheads / a.s.ngroups;
-    a.inv_wgs_per_seg = reciprocal(a.wgs_per_seg);
-    a.inv_heads_per_group = reciprocal(a.heads_per_group);
-    a.inv_groups = reciprocal(a.s.ngroups);
-    a.inv_heads = reciprocal(a.s.nheads);
     a.nseg = 1;
     a.seg_chunks = 0;
     a.seg_state = nullptr;
@@ -1587,6 +1524,7 @@ hipError_t launch_prefill_mfma(const SsdArgs &a_in, void *workspace, hipStream_t
     // (not with a final state in the place of the initial one: a piece that starts over would read it)
     if (workspace && !in_place && reinterpret_cast<uintptr_t>(workspace) % 16 == 0 && prefill_mfma_shares_rounds(a.s))
         return launch_prefill_shared(a, workspace, precise, 0, stream);
+    set_places(a, plan.channel_split);
     if (plan.nseg < 2) {
         a.pace_first = pace(1, nchunks);
         return launch(a);

@@ -3,6 +3,41 @@
 #include "quamba_internal.h"
 
 namespace quamba {
+
+// What a workgroup walks of its sequence: all of it, a segment of a sequence split (see SsdArgs), or a piece of shared rounds.
+enum class Walk { whole, segment, shared };
+
+// Shared rounds: launches of a few more (sequence, head) pairs than the device holds workgroups.  See shared_rounds (prefill_mfma.hip).
+struct SharedRounds {
+    static constexpr int kPlaces = 8;  // of a group: workgroups that share its pairs
+    struct Piece {
+        int c_begin, c_end;  // chunks
+        int16_t pair;        // of the group, behind the lead
+        int16_t cut;         // at the piece's end or start
+    };
+    bool wide;    // places are compute units, each with a workgroup of 16 waves; otherwise half units, of 8 waves
+    int groups;   // workgroup i: step i / groups of the list of group i % groups
+    int lead;     // steps that are whole pairs, in front of the pieces
+    int steps;    // in all; 0: the launch is not of this kind
+    int polls;    // of a wait for the piece in front
+    float *state; // [cut][group][headdim * d_state]: the accumulators at the cuts
+    int *left;    // [cut][group]: waves that have left their part of them there
+    Piece piece[2 * kPlaces + kPlaces - 2];
+};
+struct SharedArgs : SsdArgs {
+    SharedRounds rounds;
+};
+template <Walk WALK>
+struct WalkArgs {
+    typedef SsdArgs type;
+};
+template <>
+struct WalkArgs<Walk::shared> {
+    typedef SharedArgs type;
+};
+
+hipError_t launch_prefill_wide_shared(const SharedArgs &a, bool precise, hipStream_t stream);
+
 namespace {
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -154,6 +189,76 @@ __device__ __forceinline__ f16x8 pack_f16x8(const float v[8])
 __device__ __forceinline__ size_t segment_state_at(size_t pair, int q, int wave, int rg, int lane)
 {
     return pair * (kP * kN) + (size_t)(((q * 4 + wave) * 4 + rg) * 64 + lane) * 4;
+}
+
+// Where a piece of shared rounds leaves its accumulators in the workspace.  They are stored and loaded at device scope, past the
+// caches of the XCD, on whichever of them the piece behind runs: a release fence would write back the XCD's whole cache, and
+// 448 of them took 80 us of a launch.
+constexpr int kDeviceScope = 16;  // the instructions' SC1 bit
+__device__ __forceinline__ auto left_state(const SharedArgs &a, int cut)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(a.rounds.state + (size_t)cut * (kP * kN), 0, 4 * kP * kN, 0x00020000);
+}
+__device__ __forceinline__ int left_at(int pt, int wave, int rg, int lane) { return (int)(4 * segment_state_at(0, pt, wave, rg, lane)); }
+template <int PT>
+__device__ __forceinline__ void read_left_state(const SharedArgs &a, int cut, int wave, int lane, f32x16 (&st)[PT])
+{
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) {
+            const f32x4 v = __builtin_bit_cast(
+                f32x4, __builtin_amdgcn_raw_buffer_load_b128(left_state(a, cut), left_at(pt, wave, rg, lane), 0, kDeviceScope));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) st[pt][4 * rg + i] = v[i];
+        }
+}
+// ... and a count for each of the four waves that hold them.
+template <int PT>
+__device__ __forceinline__ void leave_state(const SharedArgs &a, int cut, int wave, int lane, const f32x16 (&st)[PT])
+{
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+        for (int rg = 0; rg < 4; ++rg) {
+            f32x4 v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = st[pt][4 * rg + i];
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), left_state(a, cut), left_at(pt, wave, rg, lane), 0,
+                                                   kDeviceScope);
+        }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores have been performed
+    if (lane == 0) __hip_atomic_fetch_add(a.rounds.left + cut, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int left_count(const SharedArgs &a, int cut)
+{
+    return __hip_atomic_load(a.rounds.left + cut, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The piece goes on from the accumulators that the piece in front of it leaves.  That one waits for nobody, and its workgroup
+// comes well in front of this one.  Should it not be there after some milliseconds all the same (false), the walk begins at the
+// sequence's start, which gives the same results.  n: the count as it was last seen.
+__device__ __forceinline__ bool await_left(const SharedArgs &a, int cut, int n)
+{
+    for (int i = 0; n < 4 && i < a.rounds.polls; ++i) {
+        __builtin_amdgcn_s_sleep(8);
+        n = left_count(a, cut);
+    }
+    return n >= 4 && a.rounds.polls >= 0;  // (below zero, in tests: as if it never came)
+}
+// The piece of a workgroup, false if it has none (a group may have one pair less).
+__device__ __forceinline__ bool shared_piece(const SharedArgs &a, int &pair, int &cut, int &c_begin, int &c_end)
+{
+    const int step = (int)blockIdx.x / a.rounds.groups, group = (int)blockIdx.x - step * a.rounds.groups;
+    pair = step;
+    if (step >= a.rounds.lead) {
+        const SharedRounds::Piece piece = a.rounds.piece[step - a.rounds.lead];
+        pair = a.rounds.lead + piece.pair;
+        c_begin = piece.c_begin;
+        c_end = piece.c_end;
+        cut = piece.cut * a.rounds.groups + group;
+    }
+    pair = pair * a.rounds.groups + group;
+    return pair < a.s.batch * a.s.nheads;
 }
 
 constexpr int kMaxSegments = 8;  // of the sequence split

@@ -1,5 +1,6 @@
 // Chunked prefill of batches of at most one (sequence, head) pair per compute unit, where every pair (with half a pair per
-// unit: every channel half of every pair, or every half or whole head of every segment of its sequence) has a unit to itself.
+// unit: every channel half of every pair, or every half or whole head of every segment of its sequence) has a unit to itself; and of
+// up to one and a third, whose units share the pairs (shared_rounds in prefill_mfma.hip).
 //
 // The arithmetic is that of prefill_mfma_kernel (prefill_mfma.hip describes it), for 32 (PT = 1) or all 64 (PT = 2) of a head's
 // channels.  What bounds such a launch is the serial walk over the chunks: a lone wave issues an instruction every 4
@@ -36,7 +37,7 @@
 // included, 960 with gate and step-size codes).  A chunk of 64 channels takes 5600 (6200): its state waves are busy for 5100 of
 // them, the others for 3600 to 4600, and LDS for 3000.  Wave priorities for the state waves cost 1 to 3 %, their operands requested
 // two or three steps ahead change nothing.  Two rounds of this kernel are slower than two workgroups of 8 waves side by side
-// (512 pairs, 4096 tokens: 193 / 169 us; 384 pairs, 2048 tokens 105 / 89).
+// (512 pairs, 4096 tokens: 193 / 169 us; 384 pairs, 2048 tokens 105 / 89, with the units sharing the pairs 86).
 #include "prefill_tiles.h"
 
 namespace quamba {
@@ -72,7 +73,8 @@ struct WideLds {
     static constexpr int kOffPart = kOffHs + (kOneH ? 1 : 2) * kH;      // float[4 blocks][PT * 4][64 lanes][4]
     static constexpr int kOffSx = kOffPart + (kOnePart ? 1 : 2) * kPart;  // float[kPw]
     static constexpr int kOffDone = kOffSx + 4 * kPw;           // int[16]: chunks read of the early terms [4], the state [4], C [8]
-    static constexpr int kOffSilu = kOffDone + 4 * 16;          // float[256]
+    static constexpr int kOffLeft = kOffDone + 4 * 16;          // int: a piece of shared rounds goes on from the one in front of it
+    static constexpr int kOffSilu = kOffLeft + 16;              // float[256]
     static constexpr int kOffKeep = kOffSilu + (GATED ? 4 * 256 : 0);   // uint32[2][64 lanes][4] (PT == 2): the causal mask
     static constexpr int kBytes = kOffKeep + (PT == 2 ? 2048 : 0);
     static_assert(kOffBq % 16 == 0 && kOffHs % 16 == 0 && kOffXs % 16 == 0 && kSet % 16 == 0 && kOffDone % 16 == 0, "16-byte alignment");
@@ -88,9 +90,11 @@ __device__ __forceinline__ int x_part(int row, int piece, int part)
     return (PT == 2 ? piece ^ (row & 2) : piece) * 32 + part * 8;
 }
 
-template <bool PRECISE, int PT, bool GATED, bool SEG>
-__global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a)
+template <bool PRECISE, int PT, bool GATED, Walk WALK>
+__global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(typename WalkArgs<WALK>::type a)
 {
+    constexpr bool SEG = WALK == Walk::segment, SHARED = WALK == Walk::shared;
+    static_assert(!SHARED || PT == 2, "pieces are of whole heads");
     typedef WideLds<PT, GATED> LY;
     constexpr int kPw = LY::kPw, kXsStride = LY::kXsStride, kZsStride = LY::kZsStride;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -115,11 +119,13 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
     const int npairs = a.s.batch * H;
     const int seg = SEG ? quotient((int)blockIdx.x, a.inv_wgs_per_seg) : 0;
     const int nchunks = (L + kQ - 1) / kQ;
-    const int c_begin = SEG ? seg * a.seg_chunks : 0;
-    const int c_end = (SEG && seg + 1 < a.nseg) ? c_begin + a.seg_chunks : nchunks;
-    const bool convert_init = a.init_state && (!SEG || seg == 0);
+    int c_begin = SEG ? seg * a.seg_chunks : 0;
+    int c_end = (SEG && seg + 1 < a.nseg) ? c_begin + a.seg_chunks : nchunks;
     const int bid = SEG ? (int)blockIdx.x - seg * a.wgs_per_seg : (int)blockIdx.x;
-    int pair = bid, half = 0;
+    int pair = bid, half = 0, cut = 0;
+    if constexpr (SHARED)
+        if (!shared_piece(a, pair, cut, c_begin, c_end)) return;
+    bool convert_init = a.init_state && c_begin == 0;  // the caller's initial state stands in front of the first chunk
     if (PT == 1) {
         const int full = npairs >> 3;
         if (bid < 16 * full) {
@@ -152,6 +158,18 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
         const int ln = fresh_lane();
         l32 = ln & 31;
         hb = ln >> 5;
+    };
+
+    // A piece that begins behind the first chunk goes on from the state that the piece in front of it leaves, for which the first
+    // state wave looks; without it, it starts over (true).
+    int *s_left = reinterpret_cast<int *>(smem + LY::kOffLeft);
+    auto starts_over = [&]() {
+        if (!SHARED || c_begin == 0) return false;
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(*s_left)) return false;
+        c_begin = 0;
+        convert_init = a.init_state != nullptr;
+        return true;
     };
 
     const float Ah = a.A[h] * 1.44269504088896340736f;
@@ -342,6 +360,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
                 diagonal(d16, skip);
                 diagonal(d16_rest, skip_rest);
             }
+            starts_over();
             if (convert_init) __syncthreads();
             __syncthreads();  // the first chunk is staged
 
@@ -501,8 +520,10 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
             // has no pairs, also turns the next chunk's step sizes into its token weights ----
             const int tb = kNBlk - 1 - wave, mid = tb >= 2 ? tb - 1 : tb;
             float dt0, dt1;
+            if (tb == 0) load_dt(c_begin, dt0, dt1);
+            const bool over = starts_over();
             if (tb == 0) {
-                load_dt(c_begin, dt0, dt1);
+                if (over) load_dt(c_begin, dt0, dt1);
                 token_weights(c_begin, smem, dt0, dt1);
                 if (c_begin + 1 < c_end) load_dt(c_begin + 1, dt0, dt1);
             }
@@ -580,6 +601,12 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
             new_lane();
             return ((size_t)bh * kP + p_base + l32) * kN + 32 * wave + 4 * hb;
         };
+        if constexpr (SHARED) {
+            if (c_begin > 0) {
+                if (wave == 0 && lane == 0) *s_left = await_left(a, cut, left_count(a, cut));
+                if (!starts_over()) read_left_state(a, cut, wave, lane, st);
+            }
+        }
         if (SEG && seg > 0) {
             // the combination of the earlier segments' states, see prefill_mfma_kernel
             const size_t pairs = (size_t)a.s.batch * H;
@@ -630,13 +657,13 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
         };
         publish(0);
         __syncthreads();  // the first chunk is staged
-        const bool want_state = a.state && (!SEG || seg + 1 == a.nseg);
+        const bool want_state = a.state && c_end == nchunks, leave = SHARED && c_end < nchunks;
         for (int c = c_begin; c < c_end; ++c) {
             const int buf = (c - c_begin) & 1;
             const unsigned char *set = smem + buf * LY::kSet;
             const float *s_cum = reinterpret_cast<const float *>(set + LY::kOffCum);
             const float *s_tot = reinterpret_cast<const float *>(set + LY::kOffTot);
-            if (c + 1 < c_end || want_state) {
+            if (c + 1 < c_end || want_state || leave) {
                 new_lane();
                 const int i16 = l32 & 15, c16 = l32 >> 4;
                 const unsigned char *bq_src =
@@ -716,6 +743,8 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
             }
             __syncthreads();
         }
+        if constexpr (SHARED)
+            if (leave) leave_state(a, cut, wave, lane, st);  // for the piece behind
         if (want_state) {
             float *state = a.state + st_row();
 #pragma unroll
@@ -788,6 +817,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
             }
         };
         issue_loads(c_begin);
+        if (starts_over()) issue_loads(c_begin);
         if (convert_init) __syncthreads();
         stage(c_begin, 0);
         if (c_begin + 1 < c_end) issue_loads(c_begin + 1);
@@ -802,37 +832,42 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(SsdArgs a
     }
 }
 
-template <bool PRECISE, int PT, bool GATED, bool SEG>
-hipError_t launch(const SsdArgs &a, hipStream_t stream)
+template <bool PRECISE, int PT, bool GATED, Walk WALK>
+hipError_t launch_walk(const typename WalkArgs<WALK>::type &a, unsigned workgroups, hipStream_t stream)
 {
-    const int segs = a.nseg > 1 ? a.nseg : 1;
-    const dim3 grid((unsigned)((2 / PT) * a.s.batch * a.s.nheads * segs));
-    const hipError_t e = allow_full_lds<prefill_wide_kernel<PRECISE, PT, GATED, SEG>>();
+    const hipError_t e = allow_full_lds<prefill_wide_kernel<PRECISE, PT, GATED, WALK>>();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((prefill_wide_kernel<PRECISE, PT, GATED, SEG>), grid, dim3(kWideThreads), (WideLds<PT, GATED>::kBytes),
+    hipLaunchKernelGGL((prefill_wide_kernel<PRECISE, PT, GATED, WALK>), dim3(workgroups), dim3(kWideThreads), (WideLds<PT, GATED>::kBytes),
                        stream, a);
     return hipGetLastError();
+}
+
+template <bool PRECISE, int PT, bool GATED>
+hipError_t launch(const SsdArgs &a, hipStream_t stream)
+{
+    const unsigned wgs = (unsigned)((2 / PT) * a.s.batch * a.s.nheads);
+    if (a.nseg > 1) return launch_walk<PRECISE, PT, GATED, Walk::segment>(a, wgs * a.nseg, stream);
+    return launch_walk<PRECISE, PT, GATED, Walk::whole>(a, wgs, stream);
 }
 
 }  // namespace
 
 hipError_t launch_prefill_wide(const SsdArgs &a, bool halves, bool precise, hipStream_t stream)
 {
-    const bool seg = a.nseg > 1;
     if (!halves) {
-        if (precise) {
-            if (a.z) return seg ? launch<true, 2, true, true>(a, stream) : launch<true, 2, true, false>(a, stream);
-            return seg ? launch<true, 2, false, true>(a, stream) : launch<true, 2, false, false>(a, stream);
-        }
-        if (a.z) return seg ? launch<false, 2, true, true>(a, stream) : launch<false, 2, true, false>(a, stream);
-        return seg ? launch<false, 2, false, true>(a, stream) : launch<false, 2, false, false>(a, stream);
+        if (precise) return a.z ? launch<true, 2, true>(a, stream) : launch<true, 2, false>(a, stream);
+        return a.z ? launch<false, 2, true>(a, stream) : launch<false, 2, false>(a, stream);
     }
-    if (precise) {
-        if (a.z) return seg ? launch<true, 1, true, true>(a, stream) : launch<true, 1, true, false>(a, stream);
-        return seg ? launch<true, 1, false, true>(a, stream) : launch<true, 1, false, false>(a, stream);
-    }
-    if (a.z) return seg ? launch<false, 1, true, true>(a, stream) : launch<false, 1, true, false>(a, stream);
-    return seg ? launch<false, 1, false, true>(a, stream) : launch<false, 1, false, false>(a, stream);
+    if (precise) return a.z ? launch<true, 1, true>(a, stream) : launch<true, 1, false>(a, stream);
+    return a.z ? launch<false, 1, true>(a, stream) : launch<false, 1, false>(a, stream);
+}
+
+hipError_t launch_prefill_wide_shared(const SharedArgs &a, bool precise, hipStream_t stream)
+{
+    const unsigned wgs = (unsigned)(a.rounds.steps * a.rounds.groups);
+    if (precise)
+        return a.z ? launch_walk<true, 2, true, Walk::shared>(a, wgs, stream) : launch_walk<true, 2, false, Walk::shared>(a, wgs, stream);
+    return a.z ? launch_walk<false, 2, true, Walk::shared>(a, wgs, stream) : launch_walk<false, 2, false, Walk::shared>(a, wgs, stream);
 }
 
 }  // namespace quamba

@@ -113,6 +113,12 @@ def test_workspace_of_shared_rounds():
     for pairs, seqlen in ((512, 4096), (640, 300), (768, 1024), (896, 2048), (1024, 4096), (1280, 1024)):
         assert q.quamba_ssd_prefill_workspace_size(_shape(batch=1, nheads=pairs, seqlen=seqlen, **mm)) == 0
     assert q.quamba_ssd_prefill_workspace_size(_shape(batch=1, nheads=640, seqlen=2048, flags=q.FLAG_NO_SEQ_SPLIT, **mm)) == 0
+    # from 256 pairs on, rounds of 256 workgroups in 32 groups
+    for pairs, seqlen in ((257, 1024), (320, 1024), (336, 2048)):
+        assert q.quamba_ssd_prefill_workspace_size(_shape(batch=1, nheads=pairs, seqlen=seqlen, **mm)) == need // 2
+    for pairs, seqlen in ((264, 512), (320, 700), (384, 4096), (511, 4096)):
+        assert q.quamba_ssd_prefill_workspace_size(_shape(batch=1, nheads=pairs, seqlen=seqlen, **mm)) == 0
+    assert q.quamba_ssd_prefill_workspace_size(_shape(batch=1, nheads=320, seqlen=2048, flags=q.FLAG_NO_SEQ_SPLIT, **mm)) == 0
 
 
 def test_noalloc_prefill_validates_like_the_prefill():

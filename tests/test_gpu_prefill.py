@@ -227,7 +227,8 @@ class _Args(C.Structure):
     _fields_ = ([("shape", C.c_int32 * 10)] + [(n, C.c_void_p) for n in ("x_scales", "head_end", "chan_end", "B_scales", "C_scales", "x",
                 "B", "C", "dt", "A", "D", "init", "state", "y", "z")] + [("z_scale", C.c_float), ("dt_q", C.c_void_p), ("dt_scale", C.c_float),
                 ("dt_bias", C.c_void_p), ("nseg", C.c_int32), ("seg_chunks", C.c_int32), ("seg_state", C.c_void_p),
-                ("seg_decay", C.c_void_p), ("pace_first", C.c_int32), ("not_here", C.c_int32 * 6)])
+                ("seg_decay", C.c_void_p), ("pace_first", C.c_int32), ("inv", C.c_uint32 * 4), ("heads_per_group", C.c_int32),
+                ("wgs_per_seg", C.c_int32)])
 
 
 @pytest.mark.parametrize("batch,H,G,L,operands", [
@@ -237,10 +238,17 @@ class _Args(C.Structure):
     (10, 80, 1, 2048, ("state", "gate")),             # 800 pairs: more than half of a second round
     (9, 128, 8, 1100, ("state", "codes")),            # 1152 pairs: whole ones in front
     (17, 31, 1, 1290, ()),                            # 527 pairs: no multiple of 8
-    (5, 129, 1, 1290, ("gate", "state", "codes", "init"))])
+    (5, 129, 1, 1290, ("gate", "state", "codes", "init")),
+    # below 512 pairs, on workgroups of 16 waves
+    (11, 24, 1, 2048, ("state",)),                    # 264 pairs: groups of 8 and 9
+    (2, 160, 8, 1030, ("state", "init", "gate")),     # 320 pairs, the last chunk of 6 tokens
+    (1, 257, 1, 1290, ("gate", "codes", "init")),     # one pair more than compute units
+    (10, 31, 1, 1100, ("state", "codes", "gate")),    # 310 pairs: no multiple of 8
+    (4, 80, 1, 1025, ())])
 def test_shared_rounds_give_the_unshared_launch_bit_for_bit(gpu_lib, batch, H, G, L, operands):
     """Pairs walked in two pieces by two workgroups (calls with a workspace), and pieces that do without the one in front of them,
-    against the launch of whole pairs (calls without a workspace), whose results other tests compare with the oracle."""
+    against the launch of whole pairs, whose results other tests compare with the oracle (calls without a workspace; below 512 pairs,
+    where these take the other kernel, the launch itself)."""
     import torch
     q = gpu_lib
     s = W.CONFIGS["m2_8b_b1"].with_(batch=batch, seqlen=L, nheads=H, ngroups=G)
@@ -267,16 +275,21 @@ def test_shared_rounds_give_the_unshared_launch_bit_for_bit(gpu_lib, batch, H, G
         fin = torch.full((batch, H, 64, 128), float("nan"), device="cuda") if "state" in operands else None
         if how != "again":
             ws = torch.full((need,), 0x5A, dtype=torch.uint8, device="cuda")
-        if how != "alone":
+        if how != "alone" and (how != "whole" or batch * H > 512):
             q.quamba_ssd_prefill(shape, dsc, x, B, Cq, dt, A, D, init, y, fin, None if how == "whole" else ws,
                                  gate=q.Gate(**gate) if gate else None)
         else:
             p = lambda t: t.data_ptr() if t is not None else None
             a = _Args((C.c_int32 * 10).from_buffer_copy(shape), *(p(t) for t in dsc.tensors), p(x), p(B), p(Cq), p(dt), p(A), p(D), p(init), p(fin), p(y), p(gate.get("z")), gate.get("z_scale", 0.0),
-                      p(gate.get("dt_q")), gate.get("dt_scale", 0.0), p(gate.get("dt_bias")), 1, 0, None, None, 2**31 - 1, (C.c_int32 * 6)())
-            f = q.load_library()._ZN6quamba21launch_prefill_sharedERKNS_7SsdArgsEPvbiP12ihipStream_t
-            assert f(C.byref(a), C.c_void_p(p(ws)), C.c_bool(fin is not None), -1,
-                     C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+                      p(gate.get("dt_q")), gate.get("dt_scale", 0.0), p(gate.get("dt_bias")), 1, 0, None, None, 2**31 - 1)
+            lib, stream, precise = q.load_library(), C.c_void_p(torch.cuda.current_stream().cuda_stream), C.c_bool(fin is not None)
+            if how == "whole":
+                a.inv = (C.c_uint32 * 4)(*((2**32 + n - 1) // n if n > 1 else 0 for n in (batch * H, H // G, G, H)))
+                a.heads_per_group, a.wgs_per_seg = H // G, batch * H
+                assert lib._ZN6quamba19launch_prefill_wideERKNS_7SsdArgsEbbP12ihipStream_t(C.byref(a), C.c_bool(False), precise, stream) == 0
+            else:
+                f = lib._ZN6quamba21launch_prefill_sharedERKNS_7SsdArgsEPvbiP12ihipStream_t
+                assert f(C.byref(a), C.c_void_p(p(ws)), precise, -1, stream) == 0
         torch.cuda.synchronize()
         results.append((y, fin))
     y0, h0 = results[0]
