@@ -289,6 +289,35 @@ __global__ __launch_bounds__(256) void hadamard_quantize_mixed_kernel(const uint
     }
 }
 
+// The words of the quad's neighbouring (lane ^ 1) or opposite (lane ^ 2) lanes, in one burst at raised wave priority, where it stays
+// (two wait states between a vector instruction and a lane move of its result).
+template <int STEP, int K>
+__device__ __forceinline__ void swap_lanes(const uint32_t (&w)[K], uint32_t (&o)[K])
+{
+    static_assert(K == 3 || K == 5, "the rows of the 12- and 20-point sums, four to a word");
+#define QUAMBA_MOVE(to, from, perm) "\n\tv_mov_b32_dpp %" #to ", %" #from " quad_perm:" perm " row_mask:0xf bank_mask:0xf"
+#define QUAMBA_MOVE3(perm) QUAMBA_MOVE(0, 3, perm) QUAMBA_MOVE(1, 4, perm) QUAMBA_MOVE(2, 5, perm)
+#define QUAMBA_MOVE5(perm) QUAMBA_MOVE(0, 5, perm) QUAMBA_MOVE(1, 6, perm) QUAMBA_MOVE(2, 7, perm) QUAMBA_MOVE(3, 8, perm) QUAMBA_MOVE(4, 9, perm)
+#define QUAMBA_MOVE_ALL(perm)                                                                                             \
+    if constexpr (K == 5)                                                                                                 \
+        asm volatile("s_nop 1\n\ts_setprio 2" QUAMBA_MOVE5(perm)                                                          \
+                     : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4])                                    \
+                     : "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]));                                            \
+    else                                                                                                                  \
+        asm volatile("s_nop 1\n\ts_setprio 2" QUAMBA_MOVE3(perm)                                                          \
+                     : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2])                                                              \
+                     : "v"(w[0]), "v"(w[1]), "v"(w[2]));
+    if constexpr (STEP == 0) {
+        QUAMBA_MOVE_ALL("[1,0,3,2]")
+    } else {
+        QUAMBA_MOVE_ALL("[2,3,0,1]")
+    }
+#undef QUAMBA_MOVE_ALL
+#undef QUAMBA_MOVE5
+#undef QUAMBA_MOVE3
+#undef QUAMBA_MOVE
+}
+
 // The same orders with the register-blocked phases of the power-of-two kernel (p = 2^LOGP values per block, 7 <= LOGP
 // <= 10, 16-byte aligned rows): phase A, strides 1..16 on the 32 consecutive values a thread loads; exchange through
 // LDS, transposed inside super-blocks of 1024 values like the power-of-two kernel's first exchange; phase B, strides
@@ -306,13 +335,15 @@ __global__ __launch_bounds__(256) void hadamard_quantize_mixed_kernel(const uint
 // rows, so that a row takes 20 KB of LDS and a unit holds 8 of order 5120 instead of 7.  16384 rows of 5120 values 70.0 -> 64.3 us
 // (3.9 TB/s), 3000 17.1 -> 15.6, 1600 11.3 -> 9.8; of 2560 42.7 -> 37.8, of 1536 22.3 -> 21.5, of 3072 38.2 -> 36.7.  By the counters a
 // SIMD takes 3.0 cycles per vector instruction at 35.8 a value, 4.1 at 32.3 before.  One position per thread in phase C instead of
-// two: 69.9 -> 66.4 before that.
+// two: 69.9 -> 66.4 before that.  There the lane moves of all words stand in one burst at raised priority, and phases A and B, in which
+// a part of the waves works and the others wait, run at raised priority too: 8000 rows of 10240 values 67.1 -> 63.3 us, 600 8.85 ->
+// 8.23, 800 of 6144 6.27 -> 5.86, 1500 of 2560 6.14 -> 5.82, 16384 of 5120 67.1 -> 66.4 (not with blocks of 1024 values, 4000 rows of
+// 12288 42.6 -> 43.1).
 // Plain stores: non-temporal ones take up to 13 % off the transform alone and put more on the reader of the codes (with an int8
 // product of 2560 columns behind, plain / non-temporal: 2867 rows of 5120 79.3 / 83.5 us, 13653 of 1536 95 / 105, 8192 of 2560
 // 97 / 108, 3413 of 6144 91 / 96; 1000 to 1700 rows of 5120 46.8 / 45.6, 63.2 / 61.6).
 // Not faster: a wave to a row, its butterflies between lanes as v_fmac_f32_dpp and lane swizzles without LDS or barriers (77 to 82 us
-// for 16384 rows of 5120); s_nop around the instructions named above (69 against 69); two or four rows to a workgroup, which leaves no lane idle in phases A and B (62.8 against 59.0 us on
-// rows in the last-level cache); a loop over rows with the next one's loads in flight (74.4); the sums of 4 to 16 of the
+// for 16384 rows of 5120); s_nop around the instructions named above (69 against 69); a loop over rows with the next one's loads in flight (74.4); the sums of 4 to 16 of the
 // rows as v_mfma_f32_4x4x1_16b_f32, bit for bit the same (70 to 79 against 65).
 // POS = 2 is phase C with two positions per thread and 2-byte stores, a whole line of a row from every wave (launch_mixed says
 // where it is the better one).
@@ -322,15 +353,18 @@ __global__ __launch_bounds__(256) void hadamard_quantize_mixed_kernel(const uint
 template <int LOGP, bool MANY>
 constexpr bool mixed_turned() { return MANY || LOGP == 7; }
 
-template <int M, int LOGP, int POS, bool MANY>
-__global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *out, float inv_s)
+template <int M, int LOGP, int POS, int ROWS, bool MANY>
+__global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *out, float inv_s, int64_t rows)
 {
-    constexpr int P = 1 << LOGP, N = M * P, T = N / 32, NSB = (N + 1023) / 1024;
-    constexpr bool kTurned = mixed_turned<LOGP, MANY>();
+    // the ROWS rows of a workgroup are one line of N values to phases A and B, which stay inside blocks of P
+    constexpr int P = 1 << LOGP, N = ROWS * M * P, T = N / 32, NSB = (N + 1023) / 1024;
+    constexpr bool kTurned = mixed_turned<LOGP, MANY>(), kBursts = MANY && LOGP < 10;
     extern __shared__ float lds[];  // NSB * (kTurned ? 1024 : 1152) floats
-    const int t = threadIdx.x;
-    const size_t row = (size_t)blockIdx.x * N;
-    if (t < T) {
+    if (kBursts) __builtin_amdgcn_s_setprio(1);
+    int t = threadIdx.x;
+    size_t row = (size_t)blockIdx.x * N;
+    const int here = ROWS == 1 ? 1 : (int)min((int64_t)ROWS, rows - (int64_t)blockIdx.x * ROWS);  // the last workgroup may have fewer
+    if (t < (ROWS == 1 ? T : here * (M * P / 32))) {
         float v[32];
         const u32x4 *src = reinterpret_cast<const u32x4 *>(y + row + 32 * t);
         u32x4 nx[4];
@@ -391,13 +425,22 @@ __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *o
             if (1024 * t_hi + 32 * e < N) pb[32 * e] = v[e];  // uniform per wave half: whole groups of 32 lanes
     }
     __syncthreads();
+    if (kBursts) __builtin_amdgcn_s_setprio(0);
+    const float *line = lds;
+    if (ROWS > 1) {
+        const int r = t >> (LOGP + 1 - POS);
+        if (r >= here) return;
+        t &= P / POS - 1;
+        line += r * (M * P);
+        row += (size_t)r * (M * P);
+    }
     if constexpr (POS == 2) {
         // phase C: positions 2 t and 2 t + 1 of every block
         float t0[M], t1[M];
 #pragma unroll
         for (int b = 0; b < M; ++b) {
-            t0[b] = lds[b * P + 2 * t];
-            t1[b] = lds[b * P + 2 * t + 1];
+            t0[b] = line[b * P + 2 * t];
+            t1[b] = line[b * P + 2 * t + 1];
         }
 #pragma unroll
         for (int a = 0; a < M; ++a) {
@@ -414,9 +457,10 @@ __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *o
         // phase C: position t of every block, four rows of the M-point sums at a time
         float x[M];
 #pragma unroll
-        for (int b = 0; b < M; ++b) x[b] = lds[b * P + t];
+        for (int b = 0; b < M; ++b) x[b] = line[b * P + t];
         int8_t *dst = out + row + (size_t)(t & 3) * P + (t & ~3);
         const uint32_t sel1 = t & 1 ? 0x03070105u : 0x06020400u, sel2 = t & 2 ? 0x03020706u : 0x05040100u;
+        uint32_t w[M / 4];
 #pragma unroll
         for (int a = 0; a < M; a += 4) {
             float sc[4];
@@ -427,37 +471,55 @@ __global__ void hadamard_quantize_mixed_fast_kernel(const uint16_t *y, int8_t *o
                 for (int b = 1; b < M; ++b) acc = acc + x[b] * paley_sign<M>(a + i, b);
                 sc[i] = acc * inv_s;
             }
-            // a lane's dword holds the codes of rows a .. a + 3; after the exchange inside the quad, of four positions of row
-            // a + t % 4
-            const uint32_t w = MANY ? codes_gathered<4>(sc) : codes_packed<4>(sc);
-            const uint32_t w1 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w, 0xB1, 0xf, 0xf, true), w, sel1);
-            const uint32_t w2 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w1, 0x4E, 0xf, 0xf, true), w1, sel2);
-            *reinterpret_cast<u32_u *>(dst + (size_t)a * P) = w2;
+            w[a / 4] = MANY ? codes_gathered<4>(sc) : codes_packed<4>(sc);
+            if (!kBursts) {
+                // a lane's dword holds the codes of rows a .. a + 3; after the exchange inside the quad, of four positions of row
+                // a + t % 4
+                const uint32_t w1 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w[a / 4], 0xB1, 0xf, 0xf, true), w[a / 4], sel1);
+                const uint32_t w2 = __builtin_amdgcn_perm(__builtin_amdgcn_update_dpp(0u, w1, 0x4E, 0xf, 0xf, true), w1, sel2);
+                *reinterpret_cast<u32_u *>(dst + (size_t)a * P) = w2;
+            }
+        }
+        if constexpr (kBursts) {  // the same exchange of all rows
+            uint32_t other[M / 4];
+            swap_lanes<0>(w, other);
+#pragma unroll
+            for (int k = 0; k < M / 4; ++k) w[k] = __builtin_amdgcn_perm(other[k], w[k], sel1);
+            swap_lanes<1>(w, other);
+#pragma unroll
+            for (int k = 0; k < M / 4; ++k)
+                *reinterpret_cast<u32_u *>(dst + (size_t)(4 * k) * P) = __builtin_amdgcn_perm(other[k], w[k], sel2);
+            __builtin_amdgcn_s_setprio(0);
         }
     }
 }
 
-template <int M, int LOGP, int POS, bool MANY>
+template <int M, int LOGP, int POS, int ROWS, bool MANY>
 hipError_t launch_mixed_form(const uint16_t *y, int64_t rows, float inv_s, int8_t *out, hipStream_t stream)
 {
-    constexpr int P = 1 << LOGP, N = M * P, NSB = (N + 1023) / 1024;
-    constexpr int threads = P / POS;
+    constexpr int P = 1 << LOGP, N = ROWS * M * P, NSB = (N + 1023) / 1024;
+    constexpr int threads = ROWS * P / POS;
     static_assert(POS == 1 || MANY, "two positions only on large calls");
     static_assert(threads >= N / 32 && threads >= 32 * NSB, "every phase has its threads");
     constexpr int lds = NSB * (mixed_turned<LOGP, MANY>() ? 1024 : 1152) * (int)sizeof(float);
     static_assert(threads <= 1024 && lds <= 160 * 1024, "launch shape");
     if (lds > 48 * 1024) {
-        const hipError_t e = allow_full_lds<hadamard_quantize_mixed_fast_kernel<M, LOGP, POS, MANY>>();
+        const hipError_t e = allow_full_lds<hadamard_quantize_mixed_fast_kernel<M, LOGP, POS, ROWS, MANY>>();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((hadamard_quantize_mixed_fast_kernel<M, LOGP, POS, MANY>), dim3((unsigned)rows), dim3(threads), lds, stream,
-                       y, out, inv_s);
+    hipLaunchKernelGGL((hadamard_quantize_mixed_fast_kernel<M, LOGP, POS, ROWS, MANY>), dim3((unsigned)((rows + ROWS - 1) / ROWS)),
+                       dim3(threads), lds, stream, y, out, inv_s, rows);
     return hipGetLastError();
 }
 
 template <int M, int LOGP>
 hipError_t launch_mixed(const uint16_t *y, int64_t rows, float inv_s, int8_t *out, hipStream_t stream)
 {
+    // More than 16 rows per unit: several to a workgroup where the waves of one would be left partly idle in phases A and B (48, 80 and 96
+    // threads' work).  One row / several (us): order 2560, 2600 rows 8.70 / 8.96, 5000 13.9 / 13.2, 16384 38.4 / 34.8; 1536: 5000 8.17 /
+    // 8.22, 10000 13.2 / 12.8, 16384 19.1 / 18.4; 3072: 3000 8.99 / 9.19, 6000 15.2 / 14.8, 16384 38.2 / 37.1.  Order 5120 has 160
+    // threads' work for 3 waves and loses more by the longer barriers than it gains (16384 rows 66.4 / 67.3).
+    const bool many_more = rows > 16 * (int64_t)compute_units();
     // Two positions on large calls of orders 12 * 128 .. 12 * 512 (order 12 * 1024 gains from one position at every size, 20 * 2^k has
     // no threads to spare with two).  12 * 256 and 12 * 512 whose codes outgrow the caches of the dies: half lines cost more than
     // the waves gain (order 6144, one / two positions: 498 rows 3.97 / 4.12 us, 822 5.94 / 5.92, 909 6.49 / 6.16, 14336 54.9 / 51.0;
@@ -465,15 +527,19 @@ hipError_t launch_mixed(const uint16_t *y, int64_t rows, float inv_s, int8_t *ou
     // than 9 of the 16 workgroups that a unit holds with one position (2204 rows 4.41 / 4.66, 2436 4.96 / 4.85, 3637 6.53 / 6.09,
     // 4020 6.88 / 6.56, 4443 7.59 / 7.71).
     if constexpr (M == 12 && (LOGP == 8 || LOGP == 9))
-        if (rows * M * (1 << LOGP) > 5LL << 20) return launch_mixed_form<M, LOGP, 2, true>(y, rows, inv_s, out, stream);
+        if (rows * M * (1 << LOGP) > 5LL << 20) {
+            if (LOGP == 8 && many_more) return launch_mixed_form<M, LOGP, 2, LOGP == 8 ? 2 : 1, true>(y, rows, inv_s, out, stream);
+            return launch_mixed_form<M, LOGP, 2, 1, true>(y, rows, inv_s, out, stream);
+        }
     if constexpr (M == 12 && LOGP == 7)
         if (rows > 9 * compute_units() && rows <= 16 * compute_units())
-            return launch_mixed_form<M, LOGP, 2, true>(y, rows, inv_s, out, stream);
+            return launch_mixed_form<M, LOGP, 2, 1, true>(y, rows, inv_s, out, stream);
     // More than two rows per compute unit: enough waves for a SIMD's vector instructions to count.  (Order 5120, the short forms / these:
     // 512 rows 5.04 / 5.10 us, 600 6.30 / 5.87, 1600 11.3 / 9.8, 16384 70.0 / 64.3; 12288: 256 rows 5.41 / 5.53, 800 12.57 / 12.35.
     // One line for all orders: on inputs that lie in the caches, calls just above it lose up to 1.7 %, 520 rows of 3072 3.58 / 3.62.)
-    if (rows > 2 * compute_units()) return launch_mixed_form<M, LOGP, 1, true>(y, rows, inv_s, out, stream);
-    return launch_mixed_form<M, LOGP, 1, false>(y, rows, inv_s, out, stream);
+    if (LOGP == 7 && many_more) return launch_mixed_form<M, LOGP, 1, LOGP == 7 ? 4 : 1, true>(y, rows, inv_s, out, stream);
+    if (rows > 2 * compute_units()) return launch_mixed_form<M, LOGP, 1, 1, true>(y, rows, inv_s, out, stream);
+    return launch_mixed_form<M, LOGP, 1, 1, false>(y, rows, inv_s, out, stream);
 }
 
 template <int LOGN>

@@ -109,12 +109,13 @@ def test_mixed_orders_store_dwords_at_even_addresses(gpu_lib, n, off):
     assert (buf[:off] == 77).all() and (buf[off + rows * n:] == 77).all()
 
 
-@pytest.mark.parametrize("n,rows", [(3072, 1707), (6144, 1025), (1536, 2305), (1536, 4096), (1536, 4099), (5120, 1231)])
+@pytest.mark.parametrize("n,rows", [(3072, 1707), (6144, 1025), (1536, 2305), (1536, 4096), (1536, 4099), (5120, 1231),
+                                    (2560, 4097), (2560, 4098), (3072, 4097), (10240, 513)])
 @pytest.mark.parametrize("off", [0, 2])
 def test_large_mixed_calls_are_their_rows(gpu_lib, n, rows, off):
     """Calls of more than 5 MiB of codes (orders 12 * 256 and 12 * 512 then take two positions per thread), and of 9 to 16 rows per
-    compute unit (order 12 * 128 does), against calls of a few of the rows and, on some rows, the oracle; at an output address
-    that is a multiple of 2 only as well."""
+    compute unit (order 12 * 128 does), and of more, with several rows to a workgroup (the last one not full), against calls of a
+    few of the rows and, on some rows, the oracle; at an output address that is a multiple of 2 only as well."""
     import torch
     g = torch.Generator(device="cuda").manual_seed(n + off)
     y = (torch.randn((rows, n), generator=g, device="cuda") * 0.1).to(torch.float16)
