@@ -1263,33 +1263,30 @@ Split largest_split(const quamba_ssd_shape_t &s)
 // unit) walks a chunk of a channel half in 1.9 us and of a whole head in 2.8, a lone workgroup of 8 waves in 2.7, two of them on
 // a unit in 4.2 to 6.  A single chunk is no faster on it: 16 tokens of 128 heads 6.0 us, 8-wave kernel in channel halves 5.5; of
 // 192 heads 7.0, whole heads 6.5; whole heads from half a pair per unit on (128 tokens of 129 heads 7.75 in halves, 8.06 whole,
-// and without the final state 6.67, 6.36; of 144 heads 8.27, 7.99).  From two chunks on the cheapest of three forms (and a fourth, below) is taken: the
-// wide kernel unsplit, its channel halves in segments that still get a unit each, and segments of whole heads on the 8-wave
-// kernel.  All were timed over 33 to 256 pairs of 8 to 48 chunks with and without the final state, gate codes and step-size codes.
+// and without the final state 6.67, 6.36; of 144 heads 8.27, 7.99).  From two chunks on the cheapest of four forms is taken: the
+// wide kernel unsplit, its channel halves or its whole heads in segments that still get a unit each, and segments of whole heads on
+// the 8-wave kernel.
 //
-// With at most half a pair per unit their costs are compared (microseconds; C chunks, S of a segment, N segments; in brackets what
-// the final state, gate codes and step-size codes add): unsplit 5.2 + 1.66 C (0.2, 0.1, 0.22 C), 0.15 C more as the units fill,
-// and where calls outgrow the last-level cache, between 85 and 120 MB read and written, 0.09 to 0.31 per MB; halves in segments
-// 8.9 + 3.01 S (0.52, 0.13, 0.59 S) with the state pass; whole heads 3.9 + 1.2 N + 5.2 S (1.21, 0.88, 0.7 S), 3 more where the state
-// pass and 4 more where the outputs have more workgroups than units, and 1.43 S times the share of the units that two of these
-// meet on.  Over these and 120 drawn shapes the choice is within 0.1 % of the best form on average, 4 % off at most.  (24 heads, 2048 tokens: unsplit 34.7, 4 segments 23.2; 80 heads, 1024 / 4096 tokens:
-// unsplit 20.7 / 66.1, whole heads 27.5 / 63.7; 128 heads, 2048 tokens: 37.8, 48.4; 112 heads, 6144 tokens without the state and
-// with step-size codes 114.6, 102.3.)
+// With at most half a pair per unit their costs are compared (microseconds; C chunks, S of a segment, N segments; in brackets
+// what the final state, gate codes and step-size codes add), first by those that were fitted before the end states lay in accumulator
+// order: unsplit 5.2 + 1.66 C (0.2, 0.1, 0.22 C), 0.15 C more as the units fill, and where calls outgrow the last-level cache, between
+// 85 and 120 MB read and written, 0.09 to 0.31 per MB; halves in segments 8.9 + 3.01 S (0.52, 0.13, 0.59 S) with the state pass; whole
+// heads of 8 waves 3.9 + 1.2 N + 5.2 S (1.21, 0.88, 0.7 S), 3 more where the state pass and 4 more where the outputs have more
+// workgroups than units, and 1.43 S times the share of the units that two of these meet on.  Up to 42 pairs of the 256 units (six
+// segments or more get a unit per whole head) whole heads on the wide kernel are compared with their choice, by costs fitted after it.
 //
-// Up to 42 pairs of the 256 units (six segments or more get a unit per whole head) a fourth form, segments of whole heads on the wide
-// kernel, computes the score tiles once instead of twice and keeps the 16 waves: 9.6 + 2.88 S (0.48 + 0.72 S, 0.4 S, 0.57 S) + 0.0059
-// per pair and chunk with the state pass.  It is compared with what the form chosen so far takes since the end states lie in
-// accumulator order: halves 7 + 3.14 S (0.28 + 0.48 S, 0.18 S, 0.65 S), whole heads of 8 waves 8.3 + 3.58 S (1.15 S, 0.56 S, 0.79 S) +
-// 0.0061 per pair and chunk, 2.3 more and 3.8 more as above; each with 0.2 to 0.7 for every hundred end states that its segments start
-// from.  (Fitted to all forms of 1008 calls of 6 to 128 pairs, 8 to 44 chunks and all operands, 2 to 3 % rms; taken where it
-// promises 0.6 us, in 140 of them, the form needs 9.3 % less on average, 4.5 % more in one.  24 heads, 2048 tokens: halves 23.4, whole heads 21.3, of 8 waves 21.4; 32 heads,
-// 6144 tokens 53.6, 43.6, 44.6; 40 heads, 2048 tokens 31.1, 26.1, 29.5.  With five segments, 43 to 51 pairs, it is 1 to 8 % ahead from
-// 20 chunks on, below it the two kernels of whole heads are level.)
-//
-// From 43 pairs on the choice is still made by the first set of costs, fitted before the end states lay in accumulator order: whole heads
-// in segments have become cheaper since, and a few calls run unsplit that they would take less for (50 to 60 heads, 2048 tokens: 36 us,
-// whole heads 33.6; by the second set of costs, 5 % or more in 1 of 150 calls of 43 to 128 pairs and 8 to 48 chunks).  43 to 48 heads,
-// 2048 tokens, and 56 to 80 of 2560 to 4096 take segments and need 31 to 33 and 37 to 61 us, unsplit 36 and 44 to 66.
+// Segments have become cheaper since (workgroups find their place sooner, segments whose state has decayed are not read), so a third
+// set (cost_of) looks for a better form in any number of segments: unsplit 5.2 + 1.62 C (0.5 + 0.15 C, 0.09 C, 0.22 C) and as
+// above; halves 7.4 + 2.73 S (0.48 S, 0.13 S, 0.71 S); whole heads 8.7 + 3.65 S (0.79 S, 0.3 S, 0.61 S); of 8 waves 8.8 + 4.04 S (0.5 + 0.9 S,
+// 0.45 S, 0.84 S), 2.4 more where the state pass has more workgroups than units, 4.3 times the share of a segment that workgroups
+// walk beside another, 0.7 S for the state pass and 1.5 S for the outputs as the units fill; each with 0.04 to 0.3 for every hundred end
+// states that its segments start from and 0.12 to 0.36 for every hundred chunks of all pairs.  Fitted to all forms in all numbers of
+// segments of 1870 calls of 10 to 128 pairs, 8 to 64 chunks and five sets of operands (2.3 to 3.7 % rms).  It decides up to 42 pairs among
+// the wide kernel's forms that leave a few units free (2.0 % less time on average, 1 % more at most; 24 heads, 3000 tokens: 8
+// segments of whole heads of 8 waves 24.6, of 16 22.2); up to 51 pairs (five segments) where the first costs leave a call
+// unsplit (43 to 51 pairs 4.5 % less; 48 heads, 1250 tokens 24.7 / 21.3, 1531 28.3 / 25.3, 2048 without the state 31.3 / 24.5); above, in
+// how many segments of which kernel a call is cut that they cut, for a promised 1 us (386 calls, 2 % less, 17 % at most).  60 heads, 2048 tokens, which
+// they leave unsplit (36 us, 8 segments of whole heads 31), and its like could gain more.
 //
 // Above, segments of whole heads are the faster form for up to two thirds of a pair per unit (3 segments) from a number of chunks
 // on: 26, and half a chunk per pair more (129 pairs, 24 / 28 / 32 chunks: unsplit 74.8 / 86.0 / 97.4, segments 73.8 / 81.2 / 91.5; 160
@@ -1307,14 +1304,14 @@ PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, const PrefillOperands
     plan.nseg = 1;
     plan.seg_chunks = 0;
     if (most.nseg < 2) return plan;
-    Split split = most;
     const int nchunks = (s.seqlen + kQ - 1) / kQ;
     const int fin = with.state, gate = with.gate, dtq = with.dt_codes;
     if (plan.channel_split) {
+        // costs in hundredths of a microsecond; the first ones
+        const int64_t mbytes = pairs * s.seqlen * (kP * (3 + gate) + (dtq ? 1 : 4)) / 1000000;
+        const bool six = 6 * pairs <= cus, five = 5 * pairs <= cus;  // segments of whole heads with a unit each
         Split own;  // segments of the wide kernel's channel halves
         own.cut(nchunks, (int)std::min<int64_t>(most.nseg, cus / (2 * pairs)));
-        // costs in hundredths of a microsecond
-        const int64_t mbytes = pairs * s.seqlen * (kP * (3 + gate) + (dtq ? 1 : 4)) / 1000000;
         const int64_t chunk = 166 + 20 * fin + 10 * gate + 22 * dtq;
         const int64_t unsplit = 520 + chunk * nchunks +
                                 (9 + 11 * gate + 17 * dtq - 6 * gate * dtq) * std::min<int64_t>(35, std::max<int64_t>(0, mbytes - 85)) +
@@ -1329,14 +1326,14 @@ PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, const PrefillOperands
                                           : 391 + step + 120 * most.nseg + (520 + 121 * fin + 88 * gate + 70 * dtq) * len +
                                                 143 * len * std::max<int64_t>(0, wgs - cus) / cus;
         const bool keep = unsplit <= std::min(cut, whole);
-        plan.wide = keep || cut <= whole;
-        if (!keep && plan.wide) split = own;
-        plan.channel_split = plan.wide;
-        // Up to a pair for every six units: the wide kernel's whole heads in segments, where they are the cheapest of the three
-        // as they are now (see above).
-        Split heads;
-        heads.cut(nchunks, (int)std::min<int64_t>(most.nseg, cus / pairs));
-        if (cus / pairs >= 6 && heads.nseg >= 2) {
+        if (!keep) {
+            plan.wide = plan.channel_split = cut <= whole;
+            plan.nseg = (plan.wide ? own : most).nseg;
+            plan.seg_chunks = (plan.wide ? own : most).seg_chunks;
+        }
+        if (six) {
+            Split heads;
+            heads.cut(nchunks, (int)std::min<int64_t>(most.nseg, cus / pairs));
             auto states_read = [&](const Split &x) { return pairs * x.nseg * (x.nseg - 1) / 2; };
             const int64_t taken =
                 keep ? unsplit * 98 / 100
@@ -1347,22 +1344,46 @@ PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, const PrefillOperands
                           61 * pairs * nchunks / 100 + 13 * len * std::max<int64_t>(0, wgs - cus) / cus;
             const int64_t in_heads = 961 + (288 + 72 * fin + 40 * gate + 57 * dtq) * (int64_t)heads.seg_chunks + 48 * fin +
                                      35 * states_read(heads) / 100 + 59 * pairs * nchunks / 100;
-            if (in_heads + 60 < taken) {
-                plan.wide = true;
-                plan.channel_split = false;
-                plan.nseg = heads.nseg;
-                plan.seg_chunks = heads.seg_chunks;
-                return plan;
+            if (heads.nseg >= 2 && in_heads + 60 < taken) plan = {heads.nseg, heads.seg_chunks, false, true};
+        } else if (keep ? !five : five) {
+            return plan;
+        }
+        const int64_t big = std::min<int64_t>(35, std::max<int64_t>(0, mbytes - 85)), work = 12 * pairs * nchunks / 100;
+        auto cost_of = [&](const PrefillPlan &x) {
+            const int64_t n = x.nseg, S = x.seg_chunks, wgs = pairs * n, state_wgs = wgs - pairs, states = wgs * (n - 1) / 2;
+            if (n < 2)
+                return 522 + 52 * fin + (162 + 15 * fin + 9 * gate + 22 * dtq) * nchunks + (15 + 11 * dtq) * big + work +
+                       12 * nchunks * std::max<int64_t>(0, 10 * pairs - 4 * cus) / cus;
+            if (x.channel_split) return 744 + (273 + 48 * fin + 13 * gate + 71 * dtq) * S + 30 * states / 100 + 3 * work;
+            if (x.wide)
+                return 868 + (365 + 79 * fin + 30 * gate + 61 * dtq) * S + 32 * states / 100 + 2 * work +
+                       3 * S * std::max<int64_t>(0, wgs - 25 * cus / 32) / 56;
+            const int64_t second = wgs <= cus ? 0 : wgs - cus > pairs ? S : nchunks - (n - 1) * S;  // chunks of workgroups that share a unit
+            return 875 + 53 * fin + (404 + 90 * fin + 45 * gate + 84 * dtq) * S + 4 * states / 100 + work + (state_wgs > cus ? 242 : 0) +
+                   426 * second / S + S * (149 * std::max<int64_t>(0, wgs - cus) + 69 * std::min<int64_t>(cus, state_wgs)) / cus;
+        };
+        int64_t best = cost_of(plan) - (!six ? 100 : plan.wide ? 50 : 0);
+        for (int n = 2; n <= most.nseg; ++n) {
+            Split x;
+            x.cut(nchunks, n);
+            if (x.nseg != n) continue;
+            for (const PrefillPlan &form : {PrefillPlan{n, x.seg_chunks, true, true}, PrefillPlan{n, x.seg_chunks, false, true},
+                                            PrefillPlan{n, x.seg_chunks, false, false}}) {
+                if (form.wide ? pairs * n * (form.channel_split ? 2 : 1) > (six && !form.channel_split ? 25 * cus / 32 : cus) : six) continue;
+                const int64_t cost = cost_of(form);
+                if (cost >= best) continue;
+                best = cost;
+                plan = form;
             }
         }
-        if (keep) return plan;
+        return plan;
     } else if (plan.wide) {
         const int64_t from = gate && dtq ? (fin ? 26 : 22) : (fin && dtq ? 44 : 26) + (pairs - cus / 2 - 1) / 2;
         if (most.nseg < 3 || nchunks < from) return plan;
         plan.wide = plan.channel_split = false;
     }
-    plan.nseg = split.nseg;
-    plan.seg_chunks = split.seg_chunks;
+    plan.nseg = most.nseg;
+    plan.seg_chunks = most.seg_chunks;
     return plan;
 }
 

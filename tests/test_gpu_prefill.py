@@ -334,6 +334,8 @@ def test_segments_of_whole_heads(gpu_lib, H, G, L, segments):
     (32, 2, 2050, 6, False, True),     # 3 chunks each, the last one 2 with two tokens; the skip term in the epilogue
     (16, 1, 2048, 8, True, False),     # channel halves on 16 waves: 2 chunks each
     (20, 5, 1700, 5, True, True),      # 3 chunks each, the last one 2; the skip term in the epilogue
+    (50, 1, 1500, 4, False, False),    # whole heads: 3 chunks each, 200 workgroups
+    (24, 1, 3000, 8, False, False),    # 3 chunks each
 ])
 def test_segments_on_workgroups_of_sixteen_waves(gpu_lib, H, G, L, segments, halves, tiny_scales):
     """Plans that cut the sequence into segments of whole heads or of channel halves on workgroups of 16 waves: with an initial state,
