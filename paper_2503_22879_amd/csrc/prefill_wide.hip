@@ -28,7 +28,7 @@
 //
 // Measured with the final state (the best of the 8-wave kernel's launches, whole, cut into segments or in channel halves /
 // this kernel): 128 heads, one sequence of 1531 tokens with gate and step-size codes 49.4 / 34.9 us, 2500 tokens 56 / 46; 120
-// pairs, 1000 tokens 32.2 / 22.0; 80 heads, 1000 tokens 27.4 / 20.8; 24 heads, 2048 tokens (8 segments of whole heads) 24.3 / 21.5,
+// pairs, 1000 tokens 32.2 / 22.0; 80 heads, 1000 tokens 27.4 / 20.8; 24 heads, 2048 tokens (8 segments of whole heads) 24.3 / 19.8,
 // 500 tokens 14.3 / 11.9; 40 heads, 2048 tokens (6 segments of whole heads) 29.5 / 26.1; two sequences of 128 heads, 1024 tokens 36.1 /
 // 30.6, 4096 tokens 128 / 107, 1531 tokens with gate and codes 64.4 / 47.5.  By cycle counters read in the kernel (a build of its
 // own) a chunk of 32 channels takes 4000 cycles, 4600 with the
