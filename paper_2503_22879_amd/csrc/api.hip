@@ -164,9 +164,7 @@ extern "C" int quamba_ssd_prefill_noalloc(const quamba_ssd_shape_t *shape, const
     if (!x || !B || !C || !dt || !A || !y) return QUAMBA_ENULL;
     rc = check_shape(shape, true);
     if (rc != QUAMBA_OK) return rc;
-    // (launches that share their rounds do without: such calls may run side by side)
-    const bool shares = !(shape->flags & QUAMBA_FLAG_GENERIC_KERNEL) && quamba::prefill_mfma_shares_rounds(*shape);
-    const size_t need = shares ? 0 : quamba_ssd_prefill_workspace_size(shape);
+    const size_t need = quamba::prefill_mfma_takes_scratch(*shape) ? quamba_ssd_prefill_workspace_size(shape) : 0;
     if (need > kScratchBytes) return QUAMBA_EWORKSPACE;
     unsigned char *ws = nullptr;
     if (need) {

@@ -1235,6 +1235,21 @@ struct Split {
     }
 };
 
+// Short sequences of few pairs, 5 to 8 chunks, in segments of a single chunk on the wide kernel, where all of them get a unit: the unsplit
+// walk takes 1.6 us a chunk, state pass and start states about 4.5 us.  Channel halves where these get a unit each, whole heads
+// otherwise.  Unsplit / so (us; 8 chunks: in halves of 2 chunks / so), with the final state: 8 heads, 5 chunks 13.5 / 10.2, 7 17.4 / 10.3; 24
+// heads, 530 tokens 13.0 / 10.1, 640 14.0 / 10.7, 700 15.4 / 12.2, 896 17.9 / 13.6, 1000 15.2 / 14.0; 32 heads, 645 15.2 / 12.0, 900 14.1 / 12.9;
+// 40 heads, 645 15.3 / 12.6.  Not taken by the rule: whole heads with 5 chunks (48 heads, 530 tokens without the state 12.0 / 12.8); pairs that
+// are no multiple of 8, whose segments' states are read on other XCDs than left them (28 heads, 900 tokens 14.3 / 15.1, 42, 700 15.7 /
+// 16.4); 4 chunks, 12.1 / 10.9 (24 heads) to level (40), which callers have no workspace for.
+bool splits_to_chunks(const quamba_ssd_shape_t &s)
+{
+    const int nchunks = (s.seqlen + kQ - 1) / kQ;
+    const int64_t pairs = (int64_t)s.batch * s.nheads;
+    return prefill_mfma_supports(s) && !(s.flags & (QUAMBA_FLAG_NO_SEQ_SPLIT | QUAMBA_FLAG_NO_CHANNEL_SPLIT)) && nchunks >= 5 &&
+           nchunks <= kMaxSegments && pairs % 8 == 0 && pairs * nchunks * (nchunks == 5 ? 2 : 1) <= (int64_t)compute_units();
+}
+
 // The most segments a call is cut into (what its workspace is sized for).  The split costs a second launch and a pass over
 // all but the last segment that only carries the state (about a third of the work of those tokens): it is left out below 8
 // chunks, and below 16 where the unsplit launch has a workgroup on every compute unit.
@@ -1245,6 +1260,11 @@ Split largest_split(const quamba_ssd_shape_t &s)
     const int cus = compute_units();
     const bool halves = !(s.flags & QUAMBA_FLAG_NO_CHANNEL_SPLIT) && pairs <= (int64_t)cus;
     const int nchunks = (s.seqlen + kQ - 1) / kQ;
+    if (splits_to_chunks(s)) {
+        split.nseg = nchunks;
+        split.seg_chunks = 1;
+        return split;
+    }
     const int min_chunks = pairs * (halves ? 2 : 1) >= (int64_t)cus ? 16 : 8;
     if ((s.flags & QUAMBA_FLAG_NO_SEQ_SPLIT) || !prefill_mfma_supports(s) || nchunks < min_chunks || pairs > (int64_t)cus)
         return split;
@@ -1304,6 +1324,10 @@ PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, const PrefillOperands
     plan.nseg = 1;
     plan.seg_chunks = 0;
     if (most.nseg < 2) return plan;
+    if (splits_to_chunks(s)) {
+        plan = {most.nseg, 1, 2 * pairs * most.nseg <= (int64_t)cus, true};
+        return plan;
+    }
     const int nchunks = (s.seqlen + kQ - 1) / kQ;
     const int fin = with.state, gate = with.gate, dtq = with.dt_codes;
     if (plan.channel_split) {
@@ -1482,6 +1506,8 @@ static void set_places(SsdArgs &a, bool halves)
 }
 
 bool prefill_mfma_shares_rounds(const quamba_ssd_shape_t &s) { return shared_rounds(s).steps != 0; }
+
+bool prefill_mfma_takes_scratch(const quamba_ssd_shape_t &s) { return !prefill_mfma_shares_rounds(s) && s.seqlen > 7 * kQ; }
 
 hipError_t launch_prefill_shared(const SsdArgs &a, void *workspace, bool precise, int polls, hipStream_t stream)
 {

@@ -359,6 +359,9 @@ hipError_t launch_prefill_mfma(const SsdArgs &a, void *workspace, hipStream_t st
 // Launches whose last round of workgroups is shared (prefill_mfma.hip).  polls: how often a piece looks for the one in front of it
 // before it does without; 0: the default; below 0: it does without.
 bool prefill_mfma_shares_rounds(const quamba_ssd_shape_t &s);
+// Calls without a workspace of their own use the library's scratch memory: not where they share rounds, nor up to 7 chunks, since such
+// calls may run side by side.
+bool prefill_mfma_takes_scratch(const quamba_ssd_shape_t &s);
 hipError_t launch_prefill_shared(const SsdArgs &a, void *workspace, bool precise, int polls, hipStream_t stream);
 hipError_t launch_prefill_wide(const SsdArgs &a, bool halves, bool precise, hipStream_t stream);
 bool prefill_generic_supports(const quamba_ssd_shape_t &s);
