@@ -65,7 +65,7 @@ typedef enum quamba_status {
 
 #define QUAMBA_FLAG_NO_SEQ_SPLIT 0x10u  /* prefill: walk every sequence with one workgroup (or pair of workgroups) from
                                            its first to its last token even when the batch is too short to fill the
-                                           chip (by default such batches are cut into up to 8 segments: a first
+                                           chip (by default such batches are cut into up to 9 segments: a first
                                            launch computes the state at the end of every segment, a second one gives
                                            every segment its own workgroups; the results agree to rounding)       */
 

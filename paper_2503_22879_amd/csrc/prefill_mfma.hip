@@ -1235,10 +1235,10 @@ struct Split {
     }
 };
 
-// Short sequences of few pairs, 5 to 8 chunks, in segments of a single chunk on the wide kernel, where all of them get a unit: the unsplit
+// Short sequences of few pairs, 5 to 9 chunks, in segments of a single chunk on the wide kernel, where all of them get a unit: the unsplit
 // walk takes 1.6 us a chunk, state pass and start states about 4.5 us.  Channel halves where these get a unit each, whole heads
-// otherwise.  Unsplit / so (us; 8 chunks: in halves of 2 chunks / so), with the final state: 8 heads, 5 chunks 13.5 / 10.2, 7 17.4 / 10.3; 24
-// heads, 530 tokens 13.0 / 10.1, 640 14.0 / 10.7, 700 15.4 / 12.2, 896 17.9 / 13.6, 1000 15.2 / 14.0; 32 heads, 645 15.2 / 12.0, 900 14.1 / 12.9;
+// otherwise.  Unsplit / so (us; 8 and 9 chunks: in halves of 2 and 3 chunks / so), with the final state: 8 heads, 5 chunks 13.5 / 10.2, 7 17.4 / 10.3; 24
+// heads, 530 tokens 13.0 / 10.1, 640 14.0 / 10.7, 700 15.4 / 12.2, 896 17.9 / 13.6, 1000 15.2 / 14.0, 1100 17.5 / 14.5; 32 heads, 645 15.2 / 12.0, 900 14.1 / 12.9;
 // 40 heads, 645 15.3 / 12.6.  Not taken by the rule: whole heads with 5 chunks (48 heads, 530 tokens without the state 12.0 / 12.8); pairs that
 // are no multiple of 8, whose segments' states are read on other XCDs than left them (28 heads, 900 tokens 14.3 / 15.1, 42, 700 15.7 /
 // 16.4); 4 chunks, 12.1 / 10.9 (24 heads) to level (40), which callers have no workspace for.
@@ -1270,7 +1270,9 @@ Split largest_split(const quamba_ssd_shape_t &s)
         return split;
     // Whole heads (one workgroup per pair and segment) compute the score tiles once instead of twice, so the channel
     // halves are kept only where even kMaxSegments segments of whole heads would not fill the compute units.
-    const int seg_cap = (int)std::min<int64_t>(kMaxSegments, nchunks / 2);
+    // (9 where as many get a unit: 17 or 18 chunks are then two to a segment, 25 to 27 three; 24 heads, 18 and 26 chunks with the final
+    // state 22.0 / 20.6 us, 28.3 / 24.5.)
+    const int seg_cap = (int)std::min<int64_t>(pairs * kMaxSegments <= (int64_t)cus ? kMaxSegments : kMaxSegments - 1, nchunks / 2);
     split.halves = halves && pairs * seg_cap < (int64_t)cus;
     const int64_t fill = split.halves ? cus : 2 * (int64_t)cus;
     split.cut(nchunks, (int)std::min<int64_t>(seg_cap, fill / pairs));

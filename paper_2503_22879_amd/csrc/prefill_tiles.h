@@ -261,7 +261,7 @@ __device__ __forceinline__ bool shared_piece(const SharedArgs &a, int &pair, int
     return pair < a.s.batch * a.s.nheads;
 }
 
-constexpr int kMaxSegments = 8;  // of the sequence split
+constexpr int kMaxSegments = 9;  // of the sequence split
 
 // Workgroup -> (sequence, head).  Hardware hands consecutive workgroup ids to the 8 XCDs round-robin, each XCD with
 // its own L2.  When the number of (sequence, state group) units is a multiple of 8, all heads of a unit are put on

@@ -101,8 +101,8 @@ def test_workspace_of_the_sequence_split():
         d.update(kw)
         assert q.quamba_ssd_prefill_workspace_size(_shape(**d)) == 0, kw
     assert q.quamba_ssd_prefill_workspace_size(_shape(batch=1, seqlen=512, nheads=24, ngroups=1, **mm)) == 0
-    # 5 to 8 chunks that get a unit each are segments of their own
-    for batch, seqlen, segments in ((1, 513, 5), (1, 896, 7), (1, 1024, 8), (2, 600, 1), (2, 641, 1)):
+    # 5 to 9 chunks that get a unit each are segments of their own; 18 are 9 segments of 2
+    for batch, seqlen, segments in ((1, 513, 5), (1, 896, 7), (1, 1024, 8), (1, 1100, 9), (1, 2300, 9), (2, 600, 1), (2, 641, 1)):
         size = q.quamba_ssd_prefill_workspace_size(_shape(batch=batch, seqlen=seqlen, nheads=24, ngroups=1, **mm))
         assert size == 4 * (segments - 1) * batch * 24 * unit
     assert q.quamba_ssd_prefill_workspace_size(_shape(batch=1, seqlen=600, nheads=20, ngroups=1, **mm)) == 0

@@ -336,7 +336,9 @@ def test_segments_of_whole_heads(gpu_lib, H, G, L, segments):
     (20, 5, 1700, 5, True, True),      # 3 chunks each, the last one 2; the skip term in the epilogue
     (50, 1, 1500, 4, False, False),    # whole heads: 3 chunks each, 200 workgroups
     (24, 1, 3000, 8, False, False),    # 3 chunks each
-    (24, 1, 641, 6, False, False),     # a chunk each, the last one a single token
+    (24, 1, 3300, 9, False, False),    # 3 chunks each, the last one 2
+    (24, 1, 1025, 9, False, False),    # a chunk each, the last one a single token
+    (24, 1, 641, 6, False, False),     # the same
     (32, 1, 1001, 8, False, False),    # the same, a workgroup on every unit
     (24, 3, 600, 5, True, True),       # halves, a chunk each; the skip term in the epilogue
     (16, 1, 1000, 8, True, False),     # halves, a chunk each, a workgroup on every unit
