@@ -601,12 +601,9 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(typename Walk
             //   H = local_{seg-1} + 2^{d_{seg-1}} local_{seg-2} + 2^{d_{seg-1} + d_{seg-2}} local_{seg-3} + ...
             // (accumulator units: no scales involved)
             const size_t pairs = (size_t)a.s.batch * H;
-            float dsum = 0.0f;
-            for (int j = seg - 1; j >= 0; --j) {
-                if (__builtin_amdgcn_readfirstlane(dsum < -dead)) break;  // dead, like a block so far away
-                const float w = exp2_fast(dsum);
+            auto add_segment = [&](int j, float w) {
 #pragma unroll
-                for (int pt = 0; pt < PT; ++pt) {
+                for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
                     for (int rg = 0; rg < 4; ++rg) {
                         const f32x4 v = *reinterpret_cast<const f32x4 *>(
@@ -614,8 +611,17 @@ __global__ __launch_bounds__(kThreads, 4) void prefill_mfma_kernel(typename Walk
 #pragma unroll
                         for (int i = 0; i < 4; ++i) st[pt][4 * rg + i] = fmaf(w, v[i], st[pt][4 * rg + i]);
                     }
+            };
+            const SegmentsInFront front(a, seg, pairs, bh);
+            add_segment(seg - 1, 1.0f);
+            float dsum = front.decay(seg - 1);
+            for (int j = seg - 2; j >= 0; --j) {
+                if (dsum < -dead && front.cannot_count(dsum, Ah, st)) {
+                    if (!a.init_state) break;
+                    for (; j > 0; --j) dsum += front.decay(j);
                 }
-                dsum += a.seg_decay[(size_t)j * pairs + bh];
+                add_segment(j, exp2_fast(dsum));
+                dsum += front.decay(j);
             }
         }
         if (convert_init) {

@@ -191,6 +191,46 @@ __device__ __forceinline__ size_t segment_state_at(size_t pair, int q, int wave,
     return pair * (kP * kN) + (size_t)(((q * 4 + wave) * 4 + rg) * 64 + lane) * 4;
 }
 
+constexpr int kMaxSegments = 9;  // of the sequence split
+
+// The segments in front of one: their decays, one to a lane, and where the walk back over their states may end.  The states come
+// from memory one after the other, and the segment's first chunk waits for them: of 24 heads, 2048 tokens in 8 segments, with decays of
+// 2^-14 a chunk and more, two or three of up to seven are read, which takes 1.5 us less than all.
+// The walk ends where the rest cannot change a bit of the sum: half a unit in a value's last place is more than 2^-25 of it, and a state
+// that its segment began at zero is, in accumulator units, at most the largest codes' product times the sum of the segment's step
+// sizes, which its decay gives (dt >= 0; up to 1024, far from where an operand in fp16 could overflow).  An end at a share of the
+// undecayed size (2^-32: 19.5 us instead of 19.7, 5 segments of a chunk 10.2 instead of 10.5) would lose what stands beside zeros or far smaller
+// values.  The segment of the caller's initial state, of any size or not finite, is always read.
+struct SegmentsInFront {
+    float mine;
+    __device__ __forceinline__ SegmentsInFront(const SsdArgs &a, int seg, size_t pairs, int bh)
+        : mine(a.seg_decay[(size_t)min((int)threadIdx.x & 63, seg - 1) * pairs + bh])
+    {
+    }
+    __device__ __forceinline__ float decay(int j) const
+    {
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine), j));
+    }
+    template <int PT>
+    __device__ __forceinline__ bool cannot_count(float log2_decay, float Ah, const f32x16 (&st)[PT]) const
+    {
+        static_assert(kMaxSegments <= 16, "a row of lanes");
+        float lowest = mine;
+        lowest = fminf(lowest, dpp_f32<0x128, 0xf, true>(lowest));  // row_ror
+        lowest = fminf(lowest, dpp_f32<0x124, 0xf, true>(lowest));
+        lowest = fminf(lowest, dpp_f32<0x122, 0xf, true>(lowest));
+        lowest = fminf(lowest, dpp_f32<0x121, 0xf, true>(lowest));
+        float least = __builtin_inff();
+#pragma unroll
+        for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) least = fminf(least, fabsf(st[pt][r]));
+        constexpr float margin = 2.0f;  // over what rounding adds to the sums
+        const float largest = exp2_fast(log2_decay) * lowest * (margin * kNarrow * 0x1p14f * 0x1p25f);  // times Ah, as below
+        return __all(mine <= 0.0f && Ah < 0.0f && lowest >= 1024.0f * Ah && largest > least * Ah);
+    }
+};
+
 // Where a piece of shared rounds leaves its accumulators in the workspace.  They are stored and loaded at device scope, past the
 // caches of the XCD, on whichever of them the piece behind runs: a release fence would write back the XCD's whole cache, and
 // 448 of them took 80 us of a launch.
@@ -260,8 +300,6 @@ __device__ __forceinline__ bool shared_piece(const SharedArgs &a, int &pair, int
     pair = pair * a.rounds.groups + group;
     return pair < a.s.batch * a.s.nheads;
 }
-
-constexpr int kMaxSegments = 9;  // of the sequence split
 
 // Workgroup -> (sequence, head).  Hardware hands consecutive workgroup ids to the 8 XCDs round-robin, each XCD with
 // its own L2.  When the number of (sequence, state group) units is a multiple of 8, all heads of a unit are put on

@@ -610,13 +610,7 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(typename 
         if (SEG && seg > 0) {
             // the combination of the earlier segments' states, see prefill_mfma_kernel
             const size_t pairs = (size_t)a.s.batch * H;
-            float dsum = 0.0f;
-            for (int j = seg - 1; j >= 0; --j) {
-                // Dead, like a block so far away.  The states come from memory one after the other, and the first chunk waits for
-                // them: 24 heads, 2048 tokens in 8 segments 21.8 -> 20.3 us where two of up to seven are alive (decays of 2^-14 a
-                // chunk and more).
-                if (__builtin_amdgcn_readfirstlane(dsum < -dead)) break;
-                const float w = exp2_fast(dsum);
+            auto add_segment = [&](int j, float w) {
 #pragma unroll
                 for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
@@ -626,7 +620,17 @@ __global__ __launch_bounds__(kWideThreads, 4) void prefill_wide_kernel(typename 
 #pragma unroll
                         for (int i = 0; i < 4; ++i) st[pt][4 * rg + i] = fmaf(w, v[i], st[pt][4 * rg + i]);
                     }
-                dsum += a.seg_decay[(size_t)j * pairs + bh];
+            };
+            const SegmentsInFront front(a, seg, pairs, bh);
+            add_segment(seg - 1, 1.0f);
+            float dsum = front.decay(seg - 1);
+            for (int j = seg - 2; j >= 0; --j) {
+                if (dsum < -dead && front.cannot_count(dsum, Ah, st)) {
+                    if (!a.init_state) break;
+                    for (; j > 0; --j) dsum += front.decay(j);
+                }
+                add_segment(j, exp2_fast(dsum));
+                dsum += front.decay(j);
             }
         }
         if (convert_init) {

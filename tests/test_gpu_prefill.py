@@ -370,6 +370,60 @@ def test_segments_on_workgroups_of_sixteen_waves(gpu_lib, H, G, L, segments, hal
             assert np.abs(hg - hu).max() <= 2e-5 * np.abs(hu).max()
 
 
+def _three_forms_of_segments(q, H, L, dt):
+    """A problem of constant step size whose plan is whole heads on 16 waves (24 heads), channel halves (16) or whole heads on 8
+    waves (80), with an initial state: (shape, scales, problem, state)."""
+    s = W.CONFIGS["m2_8b_b1"].with_(batch=1, seqlen=L, nheads=H, ngroups=1)
+    sc, prob, _ = make_problem(s, 38, calib_tokens=256)
+    prob = dict(prob, A=np.full_like(prob["A"], -1.0), dt=np.full_like(prob["dt"], dt))
+    plan = prefill_plan(q, to_shape(q, s), state=True)
+    assert plan.segments > 5 and (plan.sixteen_waves, plan.halves) == (H < 80, H == 16)
+    return s, sc, prob, W.draw_state(s, 38).astype(np.float32)
+
+
+@pytest.mark.parametrize("H,L", [(24, 2048), (16, 2048), (80, 4096)])
+@pytest.mark.parametrize("what", ["codes of zero behind it", "large", "infinite"])
+def test_an_old_state_reaches_the_final_one_through_segments_that_decay(gpu_lib, H, L, what):
+    """An initial state and first segment that decay by 2^-60 on the way, 2^-32 before the last segments, and count all the same:
+    nothing stands beside them, they are that much larger, or they are not finite."""
+    s, sc, prob, h0 = _three_forms_of_segments(gpu_lib, H, L, 60 * np.log(2) / L)
+    if what == "codes of zero behind it":
+        prob["x"] = prob["x"].copy()
+        prob["x"][:, 200:] = 0
+    elif what == "large":
+        h0 = h0 * np.float32(2.0 ** 56)
+    else:
+        h0[0, :, 3, 5], h0[0, :, 40, 100], h0[0, :, 63, 127] = np.inf, -np.inf, np.nan
+    _, hg = run_prefill(gpu_lib, s, sc, prob, 0, init_state=h0)
+    _, hu = run_prefill(gpu_lib, s, sc, prob, NO_SEQ_SPLIT, init_state=h0)
+    finite = np.isfinite(hu)
+    assert finite.all() == (what != "infinite") and np.array_equal(np.isfinite(hg), finite)
+    assert np.array_equal(hg[~finite], hu[~finite], equal_nan=True)
+    assert np.abs(hg[finite] - hu[finite]).max() <= H_TOL * np.abs(hu[finite]).max()
+    if what != "infinite":
+        _, href, _ = oracle.ref_prefill(sc, prob["x"], prob["B"], prob["C"], prob["dt"], prob["A"], prob["D"],
+                                        init_state=h0.astype(np.float64))
+        assert np.abs(href).max() > 0 and np.abs(hg - href).max() <= H_TOL * np.abs(href).max()
+
+
+@pytest.mark.parametrize("H,L", [(24, 2048), (16, 2048), (80, 4096)])
+@pytest.mark.parametrize("log2_dec", [14, 20, 30])
+@pytest.mark.parametrize("init", [False, True])
+@pytest.mark.parametrize("small_behind", [False, True])
+def test_segments_that_are_not_read_change_no_bit(gpu_lib, H, L, log2_dec, init, small_behind):
+    """States that decay by up to 2^-30 a chunk, which leaves no 32-token block out, against the same launches that read all segments
+    (QUAMBA_FLAG_NO_DECAY_SKIP): of like size, or the largest codes in front and the smallest behind."""
+    s, sc, prob, h0 = _three_forms_of_segments(gpu_lib, H, L, log2_dec * np.log(2) / 128)
+    if small_behind:
+        front = np.arange(L)[None, :, None, None] < L // 2
+        for n in ("x", "B"):
+            prob[n] = np.where(front, np.where(prob[n] < 0, -128, 127), np.sign(prob[n])).astype(np.int8)
+    h0 = h0 if init else None
+    (yg, hg), (yu, hu) = (run_prefill(gpu_lib, s, sc, prob, flags, init_state=h0) for flags in (0, 0x8))
+    assert np.isfinite(hu).all() and np.array_equal(hg, hu)
+    assert np.isfinite(yu).all() and np.array_equal(yg, yu)
+
+
 def repeat_sequences(s, prob, pairs):
     """The problem's sequences over and over, until there are at least `pairs` (sequence, head) pairs: (shape, problem)."""
     k = -(-pairs // (s.batch * s.nheads))
