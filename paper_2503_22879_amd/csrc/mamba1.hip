@@ -273,6 +273,10 @@ __device__ __forceinline__ void scan_channels(
                 if constexpr (kAlone)
                     if (t0 + kTile < L) load_ahead(t0 + kTile);
                 __syncthreads();
+            } else {  // the states that the wave's lanes have left in front of this tile
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             }
 #pragma unroll 1
             for (int n = 0; n < NS; ++n) {
