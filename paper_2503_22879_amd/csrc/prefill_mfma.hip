@@ -1460,7 +1460,7 @@ SharedRounds shared_rounds(const quamba_ssd_shape_t &s)
     const int64_t idle = (over <= all / 2 ? all - all / 4 : all) - over;  // places' worth of a full round
     const int jobs = (int)((pairs + groups - 1) / groups);  // of the group with the most
     const int shared = jobs % places ? places + jobs % places : 2 * places;
-    if (r.wide ? 65 * ((jobs * nchunks + places - 1) / places) + 92 >= 100 * nchunks
+    if (r.wide ? 65 * (((int64_t)jobs * nchunks + places - 1) / places) + 92 >= 100 * (int64_t)nchunks
                : pairs < all || over == 0 || nchunks * (100 * idle / all - 15) <= 200)
         return r;
     r.groups = (int)groups;

@@ -126,6 +126,14 @@ def test_workspace_of_shared_rounds():
     assert q.quamba_ssd_prefill_workspace_size(_shape(batch=1, nheads=320, seqlen=2048, flags=q.FLAG_NO_SEQ_SPLIT, **mm)) == 0
 
 
+def test_shared_rounds_of_the_longest_sequences():
+    """The rule counts in hundredths of a chunk, which outgrow 32 bits: 511 pairs share rounds at no length, 320 at every one from 1024 on."""
+    mm = dict(headdim=64, d_state=128, chunk=256, n_head_clusters=1, n_chan_clusters=1, ngroups=1, batch=1)
+    for seqlen in (1 << 20, 1 << 28, 2**31 - 128):
+        assert q.quamba_ssd_prefill_workspace_size(_shape(nheads=511, seqlen=seqlen, **mm)) == 0
+        assert q.quamba_ssd_prefill_workspace_size(_shape(nheads=320, seqlen=seqlen, **mm)) == 7 * 32 * (4 * 64 * 128 + 4)
+
+
 def test_noalloc_prefill_validates_like_the_prefill():
     lib = q.load_library()
     dummy = C.create_string_buffer(64)
