@@ -118,7 +118,8 @@ __device__ __forceinline__ const int8_t *token_row(const ConvArgs &a, int b, int
 // (one correctly rounded division each) and where the codes go.  headdim and d_state are multiples of 4 here, so the channels
 // share an output tensor and a head or state group.
 // By reciprocals from the host: three integer divisions more were a tenth of a one-token call (100 sequences of 10240 channels 4.6 -> 4.2
-// us, 256 6.8 -> 6.4, one of 1792 2.52 -> 2.41) and 1 to 3 % of prompts.
+// us, 256 6.8 -> 6.4, one of 1792 2.52 -> 2.41) and 1 to 3 % of prompts.  Reciprocals that are exact for any sizes cost up to 0.5 % of it, and
+// keep heads of more than 2^16 channels here (2048 tokens of one of 65552: 67 us, one channel to a thread 757).
 struct Channels4 {
     float inv[4];
     int8_t *dst;
@@ -130,8 +131,8 @@ struct Channels4 {
             SsdArgs t;
             t.s = a.s; t.x_scales = a.x_scales; t.head_cluster_end = a.head_cluster_end;
             t.chan_cluster_end = a.chan_cluster_end;
-            const int h = quotient(c0, a.inv_headdim), p0 = c0 - h * a.s.headdim;
-            const int g = quotient(h, a.inv_heads_per_group);
+            const int h = quotient(c0, a.by_headdim), p0 = c0 - h * a.s.headdim;
+            const int g = quotient(h, a.by_heads_per_group);
             if (a.s.n_chan_clusters <= 4) {  // two memory round trips
                 const Ranges4 r(t, head_cell_lookup(t, g, h - g * a.heads_per_group));
 #pragma unroll
@@ -144,7 +145,7 @@ struct Channels4 {
         } else {
             const bool isB = c0 < HP + GN;
             const int cg = c0 - HP - (isB ? 0 : GN);
-            inv[0] = inv[1] = inv[2] = inv[3] = __fdiv_rn(1.0f, (isB ? a.B_scales : a.C_scales)[quotient(cg, a.inv_d_state)]);
+            inv[0] = inv[1] = inv[2] = inv[3] = __fdiv_rn(1.0f, (isB ? a.B_scales : a.C_scales)[quotient(cg, a.by_d_state)]);
             dst = isB ? a.B_out : a.C_out; row = GN; col = cg;
         }
     }
@@ -441,10 +442,8 @@ __global__ __launch_bounds__(256) void conv1d_q8_any_kernel(ConvArgs a)
 
 bool vec_ok(const ConvArgs &a)
 {
-    const uint64_t H = a.s.nheads, P = a.s.headdim, G = a.s.ngroups, N = a.s.d_state;
-    if ((H * P * P | H * (H / G) | G * N * N) >> 32) return false;  // the reciprocals are exact below
     auto al = [](const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
-    return a.s.headdim % 16 == 0 && a.s.d_state % 16 == 0 && al(a.in) && al(a.weight) && al(a.bias) && al(a.state_in) &&
+    return conv1d_takes_four_channels(a.s) && al(a.in) && al(a.weight) && al(a.bias) && al(a.state_in) &&
            al(a.state_out) && al(a.x_out) && al(a.B_out) && al(a.C_out);
 }
 
@@ -469,14 +468,16 @@ int conv1d_segment_tokens(const quamba_ssd_shape_t &s, bool same_state)
     return seg;
 }
 
+bool conv1d_takes_four_channels(const quamba_ssd_shape_t &s) { return s.headdim % 16 == 0 && s.d_state % 16 == 0; }
+
 hipError_t launch_conv1d_q8(const ConvArgs &args, hipStream_t stream)
 {
     ConvArgs a = args;
     const int Ct = a.s.nheads * a.s.headdim + 2 * a.s.ngroups * a.s.d_state;
     a.heads_per_group = a.s.nheads / a.s.ngroups;
-    a.inv_headdim = reciprocal(a.s.headdim);
-    a.inv_heads_per_group = reciprocal(a.heads_per_group);
-    a.inv_d_state = reciprocal(a.s.d_state);
+    a.by_headdim = divisor(a.s.headdim);
+    a.by_heads_per_group = divisor(a.heads_per_group);
+    a.by_d_state = divisor(a.s.d_state);
     if (vec_ok(a) && a.s.seqlen == 1) {
         // enough waves to fill the chip, then as many sequences per thread as keep it full (the set-up is shared by them)
         const int64_t blocks = (Ct / 4 + 63) / 64;

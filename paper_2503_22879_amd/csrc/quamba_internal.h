@@ -26,15 +26,33 @@ inline int compute_units()
     return n;
 }
 
-// x / d from ceil(2^32 / d), exact for x d < 2^32; 0 stands for
-// d = 1.  An integer division is some 25 dependent instructions, and six of them stood in front of a workgroup's first load: with
-// these, and the arguments' lines asked for together, 24 heads, 2048 tokens (two kernels) 20.3 -> 19.8 us, 1200 tokens 14.9 -> 14.2, 300
-// tokens of 256 heads 12.6 -> 11.8, 1531 of 128 behind the convolution 46.2 -> 45.8.
+// x / d from ceil(2^32 / d), exact for x d < 2^32; 0 stands for d = 1.  An integer division is some 25 dependent instructions, and six
+// of them stood in front of a workgroup's first load: with these, and the arguments' lines asked for together, 24 heads, 2048 tokens
+// (two kernels) 20.3 -> 19.8 us, 1200 tokens 14.9 -> 14.2, 300 tokens of 256 heads 12.6 -> 11.8, 1531 of 128 behind the convolution
+// 46.2 -> 45.8.
 inline uint32_t reciprocal(uint32_t d) { return d > 1 ? (uint32_t)((((uint64_t)1 << 32) + d - 1) / d) : 0u; }
 __device__ __forceinline__ int quotient(int x, uint32_t inv)
 {
     const int q = (int)(((uint64_t)(uint32_t)x * inv) >> 32);
     return inv ? q : x;
+}
+// ... of any 0 <= x < 2^31, for one instruction more: from ceil(2^(31 + k) / d), 2^(k - 1) < d <= 2^k, which fits 32 bits; rounded up
+// it makes the quotient less than 2^-k <= 1 / d too large.  inv = 0 stands for d = 1.
+struct Divisor {
+    uint32_t inv;
+    int32_t shift;
+};
+inline Divisor divisor(uint32_t d)
+{
+    if (d < 2) return {0u, 0};
+    int k = 1;
+    while (((uint64_t)1 << k) < d) ++k;
+    return {(uint32_t)((((uint64_t)1 << (31 + k)) + d - 1) / d), k - 1};
+}
+__device__ __forceinline__ int quotient(int x, const Divisor &d)
+{
+    const int q = (int)((uint32_t)(((uint64_t)(uint32_t)x * d.inv) >> 32) >> d.shift);
+    return d.inv ? q : x;
 }
 
 // Lets a kernel that takes dynamic LDS only use all of it.  The attribute belongs to the (kernel, device) pair and does
@@ -340,8 +358,9 @@ struct ConvArgs {
     int8_t *x_out, *B_out, *C_out;
     int seg;                  // tokens per workgroup (set by the launcher, as what follows)
     int heads_per_group;
-    uint32_t inv_headdim, inv_heads_per_group, inv_d_state;  // for `quotient`
+    Divisor by_headdim, by_heads_per_group, by_d_state;
 };
+bool conv1d_takes_four_channels(const quamba_ssd_shape_t &s);  // to a thread, where the addresses are aligned
 hipError_t launch_conv1d_q8(const ConvArgs &a, hipStream_t stream);
 constexpr int kMaxGridY = 65535;                    // of a launch
 constexpr int kConvMaxTokens = 32 * kMaxGridY;  // longest sequence of the convolution (segments of 32 tokens)

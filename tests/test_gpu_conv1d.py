@@ -1,5 +1,7 @@
 """GPU parity of the W8A8 causal convolution in front of the scan (quamba_conv1d_q8) against the oracle, through the
 C ABI: the int8 codes of x, B and C and the carried conv state bit for bit."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -210,6 +212,30 @@ def test_any_shape_kernel_odd_sizes_and_unaligned_input(gpu_lib):
     s2 = W.CONFIGS["m2_130m"].with_(batch=1, seqlen=33)
     sc2, _, _ = make_problem(s2.with_(seqlen=8), seed=6, calib_tokens=256)
     _check(gpu_lib, s2, sc2, make_conv_inputs(s2, seed=6), offset=1)
+
+
+@pytest.mark.parametrize("L", [1, 5])
+@pytest.mark.parametrize("G,H,P,N", [(1, 8, 65552, 16), (4, 262160, 16, 16), (8, 8, 16, 65552)])
+def test_widest_heads_and_groups(gpu_lib, G, H, P, N, L):
+    """Heads of more than 2^16 channels, groups of as many heads or states: by the rounded-up reciprocal alone some channels' head or
+    group is one too high.  Four channels to a thread all the same."""
+    d = max(P, N, H // G)
+    step = 1 if d == H // G else 4
+    c = np.arange(0, (H if step == 1 else 8 * d), step)
+    assert ((c * -(-2**32 // d) >> 32) != c // d).any()
+    s = W.LayerShape("wide", 1, L, H, P, N, G, 16, 1, 2 if G == 1 else 1)
+    takes = gpu_lib.load_library()._ZN6quamba26conv1d_takes_four_channelsERK18quamba_ssd_shape_t
+    takes.restype = C.c_bool
+    assert takes(C.byref(to_shape(gpu_lib, s)))
+    g = np.random.default_rng(H + L)
+    Ct = H * P + 2 * G * N
+    scales = lambda: np.float32(0.01) * (1 + np.arange(G, dtype=np.float32))
+    sc = oracle.Scales(1, 1, scales(), np.full(G, H // G, np.int32), np.full(G, P, np.int32), scales(), scales())
+    if G == 1:  # ... nor its place in the head
+        sc = oracle.Scales(1, 2, np.float32([0.01, 0.03]), sc.head_cluster_end, np.array([P - 3, P], np.int32), sc.B_scales, sc.C_scales)
+    inp = {"xBC": g.integers(-127, 128, (1, L, Ct), dtype=np.int8), "weight": g.integers(-127, 128, (Ct, 4), dtype=np.int8),
+           "bias": g.standard_normal(Ct).astype(np.float32), "in_w_scale": 1e-4}
+    _check(gpu_lib, s, sc, inp, g.integers(-128, 128, (1, 3, Ct), dtype=np.int8))
 
 
 def test_extreme_codes_and_saturation(gpu_lib):
