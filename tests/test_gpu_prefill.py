@@ -536,6 +536,35 @@ def test_state_updated_in_place_on_a_shape_that_would_be_split(gpu_lib):
     assert np.array_equal(y_inp, y_ref) and np.array_equal(h_inp, h_ref)
 
 
+@pytest.mark.parametrize("batch,H,G", [(11, 24, 1), (5, 128, 8)])
+def test_state_updated_in_place_on_a_shape_that_would_share_rounds(gpu_lib, batch, H, G):
+    """264 and 640 pairs: a piece that starts over would read an initial state that another has overwritten, so such a call takes the
+    launch of whole pairs, leaves its workspace alone and gives what that launch gives with two buffers."""
+    import torch
+    q = gpu_lib
+    s = W.CONFIGS["m2_8b_b1"].with_(batch=batch, seqlen=1100, nheads=H, ngroups=G)
+    dsc = q.DeviceScales(host_scales(q, make_problem(s.with_(batch=1, seqlen=128), 34, calib_tokens=256)[0]))
+    d = torch.Generator(device="cuda").manual_seed(batch)
+    code = lambda *n: torch.randint(-127, 128, n, generator=d, device="cuda", dtype=torch.int8)
+    x, B, Cq = code(batch, 1100, H, 64), code(batch, 1100, G, 128) // 8, code(batch, 1100, G, 128) // 8
+    dt = 0.1 * torch.rand((batch, 1100, H), generator=d, device="cuda")
+    A, h0 = -torch.rand(H, generator=d, device="cuda"), torch.randn((batch, H, 64, 128), generator=d, device="cuda")
+    ws = torch.full((q.quamba_ssd_prefill_workspace_size(to_shape(q, s)),), 0x5A, dtype=torch.uint8, device="cuda")
+
+    def run(flags, init, fin):
+        y = torch.full((batch, 1100, H, 64), float("nan"), dtype=torch.float16, device="cuda")
+        q.quamba_ssd_prefill(to_shape(q, s, flags=flags), dsc, x, B, Cq, dt, A, None, init, y, fin, ws)
+        return y.view(torch.int16), fin
+
+    state = h0.clone()
+    y_inp, h_inp = run(0, state, state)
+    assert ws.numel() and bool((ws == 0x5A).all())
+    y_ref, h_ref = run(NO_SEQ_SPLIT, h0.clone(), torch.empty_like(h0))
+    assert torch.isfinite(h_ref).all() and torch.equal(y_inp, y_ref) and torch.equal(h_inp, h_ref)
+    run(0, h0.clone(), torch.empty_like(h0))  # two buffers: shared
+    assert bool((ws != 0x5A).any())
+
+
 def test_sequence_split_without_a_usable_workspace_takes_the_unsplit_launch(gpu_lib):
     """A missing, short or misaligned workspace is not an error: the call runs unsplit, bit for bit like the flag."""
     import torch
