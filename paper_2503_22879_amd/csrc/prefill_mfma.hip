@@ -1389,7 +1389,7 @@ PrefillPlan prefill_mfma_plan(const quamba_ssd_shape_t &s, const PrefillOperands
             if (x.channel_split) return 744 + (273 + 48 * fin + 13 * gate + 71 * dtq) * S + 30 * states / 100 + 3 * work;
             if (x.wide)
                 return 868 + (365 + 79 * fin + 30 * gate + 61 * dtq) * S + 32 * states / 100 + 2 * work +
-                       3 * S * std::max<int64_t>(0, wgs - 25 * cus / 32) / 56;
+                       96 * S * std::max<int64_t>(0, wgs - 25 * cus / 32) / (7 * cus);
             const int64_t second = wgs <= cus ? 0 : wgs - cus > pairs ? S : nchunks - (n - 1) * S;  // chunks of workgroups that share a unit
             return 875 + 53 * fin + (404 + 90 * fin + 45 * gate + 84 * dtq) * S + 4 * states / 100 + work + (state_wgs > cus ? 242 : 0) +
                    426 * second / S + S * (149 * std::max<int64_t>(0, wgs - cus) + 69 * std::min<int64_t>(cus, state_wgs)) / cus;
