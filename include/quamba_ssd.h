@@ -61,7 +61,12 @@ typedef enum quamba_status {
                                            chunked kernel leaves such 32-token blocks out: the carried-state term of
                                            an output block, score blocks far below the diagonal, a block's share of
                                            the chunk state; what is left out is below 2.4e-10 of the term's own
-                                           undecayed size, five orders under the tightest tolerance)          */
+                                           undecayed size, five orders under the tightest tolerance).  The
+                                           state that is carried into a chunk is carried on
+                                           whole: a call cut along the sequence stops reading
+                                           the end states of earlier segments only where the
+                                           rest cannot change a bit of their sum (with this
+                                           flag it reads all)                                 */
 
 #define QUAMBA_FLAG_NO_SEQ_SPLIT 0x10u  /* prefill: walk every sequence with one workgroup (or pair of workgroups) from
                                            its first to its last token even when the batch is too short to fill the
@@ -99,10 +104,11 @@ typedef struct quamba_ssd_scales_t {
  * (may be 0).  Non-zero for batches short enough for the sequence split of the matrix-core kernel
  * (QUAMBA_FLAG_NO_SEQ_SPLIT): room for the states at the segment boundaries, (segments - 1) * batch * nheads *
  * (headdim * d_state + 1) floats for the most segments the shape may be cut into.  A call may make fewer segments, or none
- * where the unsplit launch is the faster one, and then leaves the rest untouched.  Non-zero, below 16 MiB, also for batches that would
- * leave most of the device idle in their last round of workgroups: room for the states of the sequences that two workgroups walk one
- * after the other (not with QUAMBA_FLAG_NO_SEQ_SPLIT; the same results, bit for bit, where batch * nheads is at least twice the
- * device's compute units, to rounding below).  A call with a NULL, smaller or not 16-byte
+ * where the unsplit launch is the faster one, and then leaves the rest untouched.  Non-zero also for batches that would leave most
+ * of the device idle in their last round of workgroups: room for the states of the sequences that two workgroups walk one after
+ * the other, 7 * k * (headdim * d_state + 1) floats, k an eighth of the device's compute units below two (sequence, head) pairs per
+ * unit and a quarter from there on (7.3 and 14.7 MB on 256 units; not with QUAMBA_FLAG_NO_SEQ_SPLIT; the same results, bit for bit, where
+ * batch * nheads is at least twice the compute units, to rounding below).  A call with a NULL, smaller or not 16-byte
  * aligned workspace is not an error: it takes the unsplit launch (same results to rounding, slower on such batches).  The
  * workspace is scratch: written and read by the call's own launches, contents undefined afterwards; calls that share one
  * workspace must not overlap.  Returns 0 for an invalid shape; quamba_ssd_prefill reports the error.
@@ -140,9 +146,12 @@ int quamba_ssd_prefill(const quamba_ssd_shape_t *shape, const quamba_ssd_scales_
 
 /*
  * quamba_ssd_prefill for callers that cannot provide a workspace and must not allocate: code under HIP graph
- * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and results as quamba_ssd_prefill
- * without the workspace; the scratch memory of the sequence split is a fixed area of 16 MiB inside the library's
- * device image (one per GPU, held until the process ends), enough for every shape the matrix-core kernel takes.
+ * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments as quamba_ssd_prefill without the
+ * workspace, and the same results, to rounding where the launches differ; the scratch memory of the sequence split is
+ * a fixed area of 16 MiB inside the library's device image (one per GPU, held until the process ends), enough for every
+ * shape the matrix-core kernel cuts into segments.  Sequences of up to 896 tokens and batches that share their last
+ * round of workgroups take the launch without scratch memory here, also where quamba_ssd_prefill_workspace_size is not
+ * 0 and a workspace would make quamba_ssd_prefill faster: such calls touch nothing of the area.
  * The call allocates nothing and synchronises nothing.  All calls on one GPU share that area: calls that overlap in
  * time on the same GPU (different streams) race on it and must be ordered by the caller; nothing in it has to be
  * cleared between calls (a call writes what it reads).
