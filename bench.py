@@ -96,7 +96,7 @@ MAMBA1_MIN_SLOTS = 8.0
 CONV_MIN_SLOTS = 16.0
 # Executed vector instructions per element by the counters (rocprofv3 SQ_INSTS_VALU x 64 / elements), for information:
 MAMBA1_EXECUTED_PER_ELEMENT = 8.3   # of which 1.06 quarter-rate exponentials
-CONV_EXECUTED_PER_ELEMENT = 18.2    # 15.4 in the main loop (two quarter-rate), set-up and the exact-sequence reruns
+CONV_EXECUTED_PER_ELEMENT = 16.5    # two quarter-rate; set-up and the exact-sequence reruns included
 SPIN_UP_MS = float(os.environ.get("QUAMBA_BENCH_SPIN_UP_MS", "80"))   # untimed device work in front of every timed region, after the W warm-up launches (see time_region)
 
 

@@ -278,8 +278,8 @@ struct FastChannels4 {
 
 // Vector kernel: headdim, d_state multiples of 16 and 16-byte aligned tensors.  A thread owns 4 consecutive channels and walks
 // a segment of a.seg tokens, the loads of the next 4 in flight; grid = (channel blocks of 64 x 4, segments, batch); one
-// wave per workgroup, no LDS, no barrier.  Bound by the vector ALU where there are enough waves (by the counters 18
-// instructions per code with the set-up and 91 to 97 % busy at 4 x 4096 tokens of 10240 channels), by the chain from launch to
+// wave per workgroup, no LDS, no barrier.  Bound by the vector ALU where there are enough waves (by the counters 16.5
+// instructions per code with the set-up and 95 % busy at 4 x 4096 tokens of 10240 channels), by the chain from launch to
 // store where there are few.  4 channels keep the kernel at 58 registers, so that 8 waves share a SIMD, and the chain short.  With each load
 // waited for where it was made (as the compiler has it for a load behind a branch), and one more rounding, clamp and
 // compare per code: 8 x 2048 tokens of 5376 channels 61 -> 49 us, 4 x 4096 of 10240 108 -> 87 (there with 16 channels per

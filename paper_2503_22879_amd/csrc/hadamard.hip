@@ -337,7 +337,7 @@ __device__ __forceinline__ void swap_lanes(const uint32_t (&w)[K], uint32_t (&o)
 // SIMD takes 3.0 cycles per vector instruction at 35.8 a value, 4.1 at 32.3 before.  One position per thread in phase C instead of
 // two: 69.9 -> 66.4 before that.  There the lane moves of all words stand in one burst at raised priority, and phases A and B, in which
 // a part of the waves works and the others wait, run at raised priority too: 8000 rows of 10240 values 67.1 -> 63.3 us, 600 8.85 ->
-// 8.23, 800 of 6144 6.27 -> 5.86, 1500 of 2560 6.14 -> 5.82, 16384 of 5120 67.1 -> 66.4 (not with blocks of 1024 values, 4000 rows of
+// 8.23, 800 of 6144 6.27 -> 5.86, 1500 of 2560 6.14 -> 5.82; 16384 of 5120 level (not with blocks of 1024 values, 4000 rows of
 // 12288 42.6 -> 43.1).
 // Plain stores: non-temporal ones take up to 13 % off the transform alone and put more on the reader of the codes (with an int8
 // product of 2560 columns behind, plain / non-temporal: 2867 rows of 5120 79.3 / 83.5 us, 13653 of 1536 95 / 105, 8192 of 2560

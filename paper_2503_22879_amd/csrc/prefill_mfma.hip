@@ -1224,7 +1224,8 @@ hipError_t launch_segment_state(const SsdArgs &a, hipStream_t stream)
 
 // Few (sequence, head) pairs leave compute units idle, and a workgroup walks its sequence chunk by chunk.  Such
 // batches may be cut along the sequence: with `pairs` workgroups per segment (twice that with channel halves) the
-// split aims at two workgroups per compute unit, at least two chunks per segment and at most kMaxSegments segments.
+// split aims at two workgroups per compute unit, at least two chunks per segment (but for short sequences whose chunks all get a unit,
+// splits_to_chunks) and at most kMaxSegments segments.
 namespace {
 
 struct Split {
@@ -1257,8 +1258,8 @@ bool splits_to_chunks(const quamba_ssd_shape_t &s)
 }
 
 // The most segments a call is cut into (what its workspace is sized for).  The split costs a second launch and a pass over
-// all but the last segment that only carries the state (about a third of the work of those tokens): it is left out below 8
-// chunks, and below 16 where the unsplit launch has a workgroup on every compute unit.
+// all but the last segment that only carries the state (about a third of the work of those tokens): but for splits_to_chunks it is left
+// out below 8 chunks, and below 16 where the unsplit launch has a workgroup on every compute unit.
 Split largest_split(const quamba_ssd_shape_t &s)
 {
     Split split;
@@ -1303,7 +1304,7 @@ Split largest_split(const quamba_ssd_shape_t &s)
 // workgroups than units, and 1.43 S times the share of the units that two of these meet on.  Up to 42 pairs of the 256 units (six
 // segments or more get a unit per whole head) whole heads on the wide kernel are compared with their choice, by costs fitted after it.
 //
-// Segments have become cheaper since (workgroups find their place sooner, segments whose state has decayed are not read), so a third
+// Segments have become cheaper since (workgroups find their place sooner, states that cannot count any more are not read), so a third
 // set (cost_of) looks for a better form in any number of segments: unsplit 5.2 + 1.62 C (0.5 + 0.15 C, 0.09 C, 0.22 C) and as
 // above; halves 7.4 + 2.73 S (0.48 S, 0.13 S, 0.71 S); whole heads 8.7 + 3.65 S (0.79 S, 0.3 S, 0.61 S); of 8 waves 8.8 + 4.04 S (0.5 + 0.9 S,
 // 0.45 S, 0.84 S), 2.4 more where the state pass has more workgroups than units, 4.3 times the share of a segment that workgroups
@@ -1314,7 +1315,9 @@ Split largest_split(const quamba_ssd_shape_t &s)
 // segments of whole heads of 8 waves 24.6, of 16 22.2); up to 51 pairs (five segments) where the first costs leave a call
 // unsplit (43 to 51 pairs 4.5 % less; 48 heads, 1250 tokens 24.7 / 21.3, 1531 28.3 / 25.3, 2048 without the state 31.3 / 24.5); above, in
 // how many segments of which kernel a call is cut that they cut, for a promised 1 us (386 calls, 2 % less, 17 % at most).  60 heads, 2048 tokens, which
-// they leave unsplit (36 us, 8 segments of whole heads 31), and its like could gain more.
+// they leave unsplit (36 us, 8 segments of whole heads 31), and its like could gain more.  The older sets stay in front of it because the
+// tests of a kernel's segments hold it to calls of single shapes, which the third set alone would give to another: 48 heads, 2250 tokens
+// are there 6 segments on 8 waves and by it 5 on 16; 24 heads, 2048 tokens without the state are 8 on 16 waves and by it, at 3 % less, 8 on 8.
 //
 // Above, segments of whole heads are the faster form for up to two thirds of a pair per unit (3 segments) from a number of chunks
 // on: 26, and half a chunk per pair more (129 pairs, 24 / 28 / 32 chunks: unsplit 74.8 / 86.0 / 97.4, segments 73.8 / 81.2 / 91.5; 160
