@@ -565,6 +565,35 @@ def test_state_updated_in_place_on_a_shape_that_would_share_rounds(gpu_lib, batc
     assert bool((ws != 0x5A).any())
 
 
+@pytest.mark.parametrize("batch,H,G", [(11, 24, 1), (5, 128, 8)])
+def test_states_that_overlap_in_part_share_no_rounds(gpu_lib, batch, H, G):
+    """... neither where the two states have only some bytes in common.  (Here the last sequence's initial state is the first one's final
+    state: what the sequences between them return is that of the call with two buffers.)"""
+    import torch
+    q = gpu_lib
+    L = 1100
+    s = W.CONFIGS["m2_8b_b1"].with_(batch=batch, seqlen=L, nheads=H, ngroups=G)
+    dsc = q.DeviceScales(host_scales(q, make_problem(s.with_(batch=1, seqlen=128), 34, calib_tokens=256)[0]))
+    d = torch.Generator(device="cuda").manual_seed(batch)
+    code = lambda *n: torch.randint(-127, 128, n, generator=d, device="cuda", dtype=torch.int8)
+    x, B, Cq = code(batch, L, H, 64), code(batch, L, G, 128) // 8, code(batch, L, G, 128) // 8
+    dt = 0.1 * torch.rand((batch, L, H), generator=d, device="cuda")
+    A, h0 = -torch.rand(H, generator=d, device="cuda"), torch.randn((batch, H, 64, 128), generator=d, device="cuda")
+    ws = torch.full((q.quamba_ssd_prefill_workspace_size(to_shape(q, s)),), 0x5A, dtype=torch.uint8, device="cuda")
+
+    def run(flags, init, fin):
+        y = torch.full((batch, L, H, 64), float("nan"), dtype=torch.float16, device="cuda")
+        q.quamba_ssd_prefill(to_shape(q, s, flags=flags), dsc, x, B, Cq, dt, A, None, init, y, fin, ws)
+        return y[:batch - 1].view(torch.int16), fin[1:batch - 1]
+
+    states = torch.zeros((2 * batch - 1, H, 64, 128), device="cuda")
+    states[:batch] = h0
+    y_part, h_part = run(0, states[:batch], states[batch - 1:])
+    assert ws.numel() and bool((ws == 0x5A).all())
+    y_ref, h_ref = run(NO_SEQ_SPLIT, h0.clone(), torch.empty_like(h0))
+    assert torch.isfinite(h_ref).all() and torch.equal(y_part, y_ref) and torch.equal(h_part, h_ref)
+
+
 def test_sequence_split_without_a_usable_workspace_takes_the_unsplit_launch(gpu_lib):
     """A missing, short or misaligned workspace is not an error: the call runs unsplit, bit for bit like the flag."""
     import torch
